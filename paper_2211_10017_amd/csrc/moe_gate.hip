@@ -1,13 +1,12 @@
 // moe_gate_topk: router logits, top-k selection and gate probabilities (Sec. 3.3).
 //
-// Mapping: a lane owns one expert (NE experts when E > 64) for TB tokens (TB = 1 when there are
-// few tokens, so that they spread over more blocks); when E < 64 a
-// wavefront is cut into 64/EL token groups of EL = pow2ceil(E) lanes.  The four wavefronts of
-// a block take the four partial sums of the contract (128-element blocks of the feature axis
-// dealt round-robin), so the floating-point order is fixed by the definition, not by the
-// launch shape.  Softmax and top-k are butterfly reductions over the EL lanes of a group.
-// FP16 batches of 16384 tokens and more with 64 experts take another mapping, a token per lane
-// (gate_token_lanes_kernel below), with the same order of the additions.
+// The logits of many tokens are a matrix product, and the fp32 matrix instructions of this chip round like a chain of fp32
+// fused multiply-adds, so the contract's sequential partial sums (128-element blocks of the feature axis dealt round-robin to
+// four sums) run on the matrix cores bit for bit: a wavefront owns one of the four partial sums for a tile of tokens and
+// experts, the four meet in LDS, and sixteen lanes finish a token.  Two tilings: gate_mfma_kernel (16 tokens x 16 experts
+// per instruction) and gate_quad_kernel (4 tokens x 64 experts).  T = 8192, d = 4096, 64 experts: 196 -> 48 us (bf16 208 ->
+// 47), T = 4096, d = 2048, 128 experts: 76 -> 28.6 us, T = 16384, d = 1024, 64 experts: 55 -> 32 us against multiply-adds in
+// the vector ALU with a lane per expert or per token; T = 64, d = 1024, 32 experts: 13 -> 9 us with cold caches.
 #include <math.h>
 
 #include <type_traits>
@@ -17,7 +16,6 @@
 namespace moe {
 
 constexpr int kGateBlk = 128;    // feature block of one partial-sum turn
-constexpr int kGateWRow = 64;     // LDS row of the staged gate-weight block: 64 experts' weights for one feature
 
 template <bool BF16>
 __device__ inline float act_to_float(uint16_t v)
@@ -28,427 +26,408 @@ __device__ inline float act_to_float(uint16_t v)
     return __half2float(h);
 }
 
-// acc + x * w in fp32 with both operands widened exactly (one v_fma_mix_f32 for fp16 inputs).
-template <bool BF16>
-__device__ inline float mac(uint16_t xb, uint16_t wb, float acc)
-{
-    if (BF16) return fmaf(__uint_as_float((uint32_t)xb << 16), __uint_as_float((uint32_t)wb << 16), acc);
-    return fmaf((float)__builtin_bit_cast(_Float16, xb), (float)__builtin_bit_cast(_Float16, wb), acc);
-}
-
-// Value of the partner lane of butterfly step `off` within a lane group.  Steps 1 and 2 are quad
-// permutes, 4 and 8 the half-row and row mirrors (the same partner sets once the value is uniform
-// over 4 resp. 8 lanes, which the earlier steps have made it), all in the VALU's data-parallel
-// primitives, the steps across 16-lane rows and 32-lane halves the row and half swaps.  Used in ascending
-// order of `off` by reductions whose operation is commutative.
+// Value of the partner lane of butterfly step `off` within a row of sixteen lanes: quad permutes for 1 and 2, the half-row and
+// row mirrors for 4 and 8 (the same partner sets once the value is uniform over 4 resp. 8 lanes, which the earlier
+// steps have made it), all in the VALU's data-parallel primitives.  Used in ascending order of `off` by reductions
+// whose operation is commutative.
 template <int OFF, typename V>
 __device__ inline V butterfly_partner(V v)
 {
-    const int b = __builtin_bit_cast(int, v);
-    int r;
-    if (OFF == 1) r = __builtin_amdgcn_update_dpp(0, b, 0xB1, 0xf, 0xf, false);        // quad_perm [1,0,3,2]
-    else if (OFF == 2) r = __builtin_amdgcn_update_dpp(0, b, 0x4E, 0xf, 0xf, false);   // quad_perm [2,3,0,1]
-    else if (OFF == 4) r = __builtin_amdgcn_update_dpp(0, b, 0x141, 0xf, 0xf, false);  // row_half_mirror
-    else if (OFF == 8) r = __builtin_amdgcn_update_dpp(0, b, 0x140, 0xf, 0xf, false);  // row_mirror
-    else if (OFF == 16) {
-        // rows of 16 lanes: the swap leaves [r0, r0, r2, r2] and [r1, r1, r3, r3]; a lane in an even row
-        // takes the second, a lane in an odd row the first
-        const auto sw = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
-        r = (int)((threadIdx.x & 16) ? sw[0] : sw[1]);
-    } else {
-        // halves of 32 lanes: the swap leaves [lo, lo] and [hi, hi]
-        const auto sw = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
-        r = (int)((threadIdx.x & 32) ? sw[0] : sw[1]);
-    }
-    return __builtin_bit_cast(V, r);
+    constexpr int CTRL = OFF == 1 ? 0xB1 : OFF == 2 ? 0x4E : OFF == 4 ? 0x141 : 0x140;    // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror, row_mirror
+    return __builtin_bit_cast(V, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
 }
 
-// f(partner value getter) for every butterfly step of a group of EL lanes (EL = 8, 16, 32 or 64)
-template <typename F>
-__device__ inline void butterfly_steps(int EL, F &&f)
+// The outputs of one token: its k chosen experts (logits selv, descending) and their gate probabilities, den = the sum of
+// exp(logit - largest logit) over all experts.
+__device__ inline void store_choice(int t, int T, int E, int k, int renorm, const int (&sel)[2], const float (&selv)[2], float den,
+                                    const uint8_t *__restrict__ finished, int32_t *__restrict__ expert_idx,
+                                    float *__restrict__ expert_scale)
 {
-    f(std::integral_constant<int, 1>{});
-    f(std::integral_constant<int, 2>{});
-    f(std::integral_constant<int, 4>{});
-    if (EL > 8) f(std::integral_constant<int, 8>{});
-    if (EL > 16) f(std::integral_constant<int, 16>{});
-    if (EL > 32) f(std::integral_constant<int, 32>{});
-}
-
-// With E <= 64 the 128 x E block of the gate weight that a wavefront needs per turn is copied
-// to LDS with 16-byte loads first (one latency per turn instead of one per row).
-template <bool BF16, int NE, int TB, int GM>
-__global__ __launch_bounds__(256) void gate_kernel(const uint16_t *__restrict__ x,
-                                                   const uint16_t *__restrict__ wg,
-                                                   const float *__restrict__ bias,
-                                                   const uint8_t *__restrict__ finished, int T, int d,
-                                                   int E, int EL, int k, int renorm,
-                                                   int32_t *__restrict__ expert_idx,
-                                                   float *__restrict__ expert_scale)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: addresses built from it are scalar
-    const int G = 64 / EL;                        // token groups per wavefront
-    const int grp = lane / EL, le = lane % EL;
-    const int ntok = G * TB;                 // tokens per block
-    const int t0 = blockIdx.x * ntok;
-
-    // wave-private staging areas: x [ntok][128] and (NE == 1) the gate weight block [128][E]
-    constexpr bool WLDS = NE == 1;
-    const size_t x_halfs = (GM == 1 && NE == 1 && !BF16) ? 0 : (size_t)ntok * kGateBlk;   // (x through scalar loads: no staging)
-    const size_t wave_halfs = x_halfs + (WLDS ? (size_t)kGateWRow * kGateBlk : 0);
-    uint16_t *xs = reinterpret_cast<uint16_t *>(smem) + (size_t)wave * wave_halfs;
-    uint16_t *ws = xs + x_halfs;
-    float *part = reinterpret_cast<float *>(smem);   // [4][NE][TB][64], over the staging areas once they are used up
-
-    float acc[NE][TB];
-#pragma unroll
-    for (int a = 0; a < NE; ++a)
-#pragma unroll
-        for (int b = 0; b < TB; ++b) acc[a][b] = 0.0f;
-
-    const int e_shift = 31 - __builtin_clz(EL);
-    const int nblk = (d + kGateBlk - 1) / kGateBlk;
-    const int turns = (nblk + 3) / 4;             // same trip count for all four wavefronts
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    // GM == 1 and at most 64 experts (a lane group is the whole wavefront): a token's features are
-    // the same for every lane, so they are fetched with scalar loads and feed the MACs from scalar
-    // registers; no x staging.  (With more experts per lane the scalar registers run out.)
-    constexpr bool SX = GM == 1 && NE == 1 && !BF16;   // (bf16 features would be widened in scalar registers, two per dword: they run out)
-    constexpr int XR = SX ? 1 : (GM * TB >= 4 ? GM * TB / 4 : 1);   // x vectors per lane per turn (ntok <= GM * TB rows, 4 rows per pass)
-    constexpr int WR = WLDS ? 16 : 1;             // gate-weight vectors per lane per turn (128 x E halfs, E <= 64)
-    struct Staged { u32x4 x[XR]; u32x4 w[WR]; };
-
-    // global -> registers for one turn; nothing is waited for here
-    auto fetch = [&](int turn, Staged &st) {
-        const int blk = min(turn * 4 + wave, max(nblk - 1, 0));     // clamped: a turn past the end re-reads the last block
-        const int i0 = blk * kGateBlk;
-        const int lim = min(kGateBlk, d - i0);
-#pragma unroll
-        for (int r = 0; r < (SX ? 0 : XR); ++r) {
-            const int row = (lane >> 4) + 4 * r;
-            const int seg = (lane & 15) * 8;
-            const int t = min(t0 + min(row, ntok - 1), T - 1);
-            st.x[r] = *reinterpret_cast<const u32x4 *>(x + (size_t)t * d + i0 + min(seg, lim - 8));
-        }
-        if (WLDS) {
-            const u32x4 *src = reinterpret_cast<const u32x4 *>(wg + (size_t)i0 * E);
-            const int nvec = lim * E / 8;
-#pragma unroll
-            for (int u = 0; u < WR; ++u)
-                if (u * 64 < nvec) st.w[u] = src[min(u * 64 + lane, nvec - 1)];
-        }
-    };
-    // registers -> LDS: x rows as they are (zero past the block's end) and the weight block
-    auto stash = [&](int turn, const Staged &st) {
-        const int blk = turn * 4 + wave;
-        const int lim = blk < nblk ? min(kGateBlk, d - blk * kGateBlk) : 0;     // multiple of 8
-#pragma unroll
-        for (int r = 0; r < (SX ? 0 : XR); ++r) {
-            const int row = (lane >> 4) + 4 * r;
-            const int seg = (lane & 15) * 8;
-            if (row < ntok) {
-                u32x4 v = st.x[r];
-                if (seg >= lim) v = u32x4{0, 0, 0, 0};
-                *reinterpret_cast<u32x4 *>(xs + row * kGateBlk + seg) = v;
-            }
-        }
-        if (WLDS) {
-            // rows of the block keep their order, padded to 64 experts: [i][64]
-            const int nvec = lim * E / 8;
-#pragma unroll
-            for (int u = 0; u < WR; ++u) {
-                const int v = u * 64 + lane;
-                if (v < nvec) {
-                    int i, e;
-                    if (E == EL) {                               // power of two: shifts
-                        i = (v * 8) >> e_shift;
-                        e = (v * 8) & (E - 1);
-                    } else {                                     // one division per vector
-                        i = (v * 8) / E;
-                        e = v * 8 - i * E;
-                    }
-                    if ((E & 7) == 0) {
-                        *reinterpret_cast<u32x4 *>(ws + i * kGateWRow + e) = st.w[u];
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) {
-                            ws[i * kGateWRow + e] = (uint16_t)(st.w[u][q >> 1] >> (16 * (q & 1)));
-                            if (++e == E) { e = 0; ++i; }
-                        }
-                    }
-                }
-            }
-        }
-    };
-    auto compute = [&](int turn) __attribute__((always_inline)) {
-        const int blk = turn * 4 + wave;
-        const int i0 = blk * kGateBlk;
-        const int lim = blk < nblk ? min(kGateBlk, d - i0) : 0;
-#pragma unroll 2
-        for (int i = 0; i < lim; i += 8) {       // unrolled: several LDS reads in flight per wavefront
-            uint16_t wv[NE][8];
-#pragma unroll
-            for (int a = 0; a < NE; ++a) {
-                const int e = min(a * 64 + le, E - 1);
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    wv[a][u] = WLDS ? ws[(i + u) * kGateWRow + e] : wg[(size_t)(i0 + i + u) * E + e];
-            }
-            // tokens in batches of up to eight: their rows are read first, then the features are
-            // walked with the tokens innermost, so that consecutive MACs are independent
-            constexpr int XB = TB < 8 ? TB : 8;
-#pragma unroll
-            for (int b0 = 0; b0 < TB; b0 += XB) {
-                uint4 raw[XB];
-#pragma unroll
-                for (int b = 0; b < XB; ++b) {
-                    if (SX)     // uniform address: a scalar load
-                        raw[b] = *reinterpret_cast<const uint4 *>(x + (size_t)min(t0 + b0 + b, T - 1) * d + i0 + i);
-                    else
-                        raw[b] = *reinterpret_cast<const uint4 *>(xs + (grp * TB + b0 + b) * kGateBlk + i);
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-#pragma unroll
-                    for (int b = 0; b < XB; ++b) {
-                        const uint32_t r = u < 2 ? raw[b].x : u < 4 ? raw[b].y : u < 6 ? raw[b].z : raw[b].w;
-                        const uint16_t xb = (uint16_t)(r >> (16 * (u & 1)));
-#pragma unroll
-                        for (int a = 0; a < NE; ++a) acc[a][b0 + b] = mac<BF16>(xb, wv[a][u], acc[a][b0 + b]);
-                    }
-                }
-            }
-        }
-    };
-    // The loads of two turns are always in flight: with few tokens the whole kernel is one memory
-    // latency long, and two turns cover d = 1024.
-    // The staging areas are private to a wavefront, and LDS serves one wavefront's instructions in
-    // order, so a turn needs no barrier between its writes and reads.
-    Staged s0, s1;
-    fetch(0, s0);
-    fetch(1, s1);
-    for (int turn = 0; turn < turns; turn += 2) {
-        stash(turn, s0);
-        if (turn + 2 < turns) fetch(turn + 2, s0);
-        compute(turn);
-        if (turn + 1 < turns) {
-            stash(turn + 1, s1);
-            if (turn + 3 < turns) fetch(turn + 3, s1);
-            compute(turn + 1);
-        }
-    }
-
-    __syncthreads();                              // every wavefront is done with its staging area
-#pragma unroll
-    for (int a = 0; a < NE; ++a)
-#pragma unroll
-        for (int b = 0; b < TB; ++b) part[((wave * NE + a) * TB + b) * 64 + lane] = acc[a][b];
-    __syncthreads();
-
-    // wavefront `wave` finishes token slots b = wave, wave + 4, ... of every group
-    for (int b = wave; b < TB; b += 4) {
-    const int t = t0 + grp * TB + b;
-    float lg[NE];
-    const float NEG = -INFINITY;
-#pragma unroll
-    for (int a = 0; a < NE; ++a) {
-        const int e = a * 64 + le;
-        float p0 = part[((0 * NE + a) * TB + b) * 64 + lane];
-        float p1 = part[((1 * NE + a) * TB + b) * 64 + lane];
-        float p2 = part[((2 * NE + a) * TB + b) * 64 + lane];
-        float p3 = part[((3 * NE + a) * TB + b) * 64 + lane];
-        float l = ((p0 + p1) + p2) + p3;
-        if (e < E && bias) l = l + bias[e];
-        lg[a] = e < E ? l : NEG;
-    }
-
-    // best (value, index) with ties to the lower index
-    int sel[2] = {0, 0};
-    float selv[2] = {0.0f, 0.0f};
-    for (int j = 0; j < k; ++j) {
-        float bv = NEG;
-        int be = 0x7fffffff;
-#pragma unroll
-        for (int a = 0; a < NE; ++a) {
-            const int e = a * 64 + le;
-            const bool taken = j == 1 && e == sel[0];
-            if (e < E && !taken && (lg[a] > bv || be == 0x7fffffff)) { bv = lg[a]; be = e; }
-        }
-        butterfly_steps(EL, [&](auto off) {
-            constexpr int OFF = decltype(off)::value;
-            const float ov = butterfly_partner<OFF>(bv);
-            const int oe = butterfly_partner<OFF>(be);
-            if (oe != 0x7fffffff && (be == 0x7fffffff || ov > bv || (ov == bv && oe < be))) { bv = ov; be = oe; }
-        });
-        sel[j] = be;
-        selv[j] = bv;
-    }
-    const float lmax = selv[0];
-    float den = 0.0f;
-#pragma unroll
-    for (int a = 0; a < NE; ++a)
-        if (a * 64 + le < E) den += expf(lg[a] - lmax);
-    butterfly_steps(EL, [&](auto off) { den += butterfly_partner<decltype(off)::value>(den); });
-
-    if (le == 0 && t < T) {
-        if (finished && finished[t]) {
-            // batch pruning (Sec. 3.5): the row gets an expert index past the real experts, so the
-            // sort moves it behind every active row, and a zero scale
-            for (int j = 0; j < k; ++j) {
-                expert_idx[k * t + j] = E;
-                expert_scale[k * t + j] = 0.0f;
-            }
-        } else if (k == 1) {
-            expert_idx[t] = sel[0];
-            expert_scale[t] = 1.0f / den;
-        } else {
-            const float e2 = expf(selv[1] - lmax);
-            float s0 = 1.0f / den, s1 = e2 / den;
-            if (renorm) { s0 = 1.0f / (1.0f + e2); s1 = e2 / (1.0f + e2); }
-            expert_idx[2 * t] = sel[0];
-            expert_idx[2 * t + 1] = sel[1];
-            expert_scale[2 * t] = s0;
-            expert_scale[2 * t + 1] = s1;
-        }
-    }
-    }   // token slots of this wavefront
-}
-
-// Many tokens, 64 experts: a lane owns one token.  The block's wavefronts are the four partial sums of
-// the contract times 64 / EW slices of the experts; a feature's EW gate weights are the same for every
-// lane, so they come through scalar loads and feed the MACs from scalar registers (one row of the gate
-// weight is 128 contiguous bytes), while each lane walks its own token's features, 32 at a time, one
-// chunk ahead.  Nothing is staged or exchanged until the partial sums meet in LDS; then every wavefront
-// finishes the logits of 64 / NW experts for all 64 tokens and the candidates are merged per token.
-// Same floating-point order of the logits as gate_kernel.  FP16 only (bf16 weights would be widened in
-// scalar registers, which run out).
-template <int EW>
-__global__ __launch_bounds__(256 * (64 / EW)) void gate_token_lanes_kernel(const uint16_t *__restrict__ x,
-                                                               const uint16_t *__restrict__ wg,
-                                                               const float *__restrict__ bias,
-                                                               const uint8_t *__restrict__ finished, int T, int d,
-                                                               int k, int renorm, int32_t *__restrict__ expert_idx,
-                                                               float *__restrict__ expert_scale)
-{
-    constexpr int E = 64, NW = 4 * (E / EW), EPW = E / NW;      // wavefronts per block, experts a wavefront finishes
-    extern __shared__ __align__(16) unsigned char smem[];
-    float *part = reinterpret_cast<float *>(smem);           // [4 partial sums][64 experts][64 tokens]
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int p = wave & 3, slice = wave >> 2;
-    const int t = blockIdx.x * 64 + lane;
-    const uint4 *xrow = reinterpret_cast<const uint4 *>(x + (size_t)min(t, T - 1) * d);
-    float acc[EW];
-#pragma unroll
-    for (int e = 0; e < EW; ++e) acc[e] = 0.0f;
-
-    const int nblk = d / kGateBlk;                            // d is a multiple of the block here
-    const int nch = ((nblk - p + 3) / 4) * 4;                 // 32-feature chunks of this partial sum
-    auto first_feature = [&](int c) { return (p + 4 * (c >> 2)) * kGateBlk + (c & 3) * 32; };
-    uint4 nxt[4];
-    if (nch > 0) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) nxt[v] = xrow[first_feature(0) / 8 + v];
-    }
-#pragma unroll 1
-    for (int c = 0; c < nch; ++c) {
-        uint4 cur[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) cur[v] = nxt[v];
-        const int cn = min(c + 1, nch - 1);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) nxt[v] = xrow[first_feature(cn) / 8 + v];
-        const uint32_t *wrow = reinterpret_cast<const uint32_t *>(wg + (size_t)first_feature(c) * E + slice * EW);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const uint32_t xw[4] = {cur[v].x, cur[v].y, cur[v].z, cur[v].w};
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uint16_t xb = (uint16_t)(xw[u >> 1] >> (16 * (u & 1)));
-                const uint32_t *w = wrow + (v * 8 + u) * (E / 2);     // uniform address: scalar loads
-#pragma unroll
-                for (int q = 0; q < EW / 2; ++q) {
-                    const uint32_t w2 = w[q];
-                    acc[2 * q] = mac<false>(xb, (uint16_t)w2, acc[2 * q]);
-                    acc[2 * q + 1] = mac<false>(xb, (uint16_t)(w2 >> 16), acc[2 * q + 1]);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < EW; ++e) part[(p * E + slice * EW + e) * 64 + lane] = acc[e];
-    __syncthreads();
-
-    // wavefront w: logits of experts w * EPW ... for the lane's token, best two of them with ties to
-    // the lower index (experts in ascending order, a later one must be strictly larger)
-    float lg[EPW];
-    float bv = 0.0f, sv = 0.0f;
-    int be = 0, se = 0;
-#pragma unroll
-    for (int j = 0; j < EPW; ++j) {
-        const int e = wave * EPW + j;
-        float l = ((part[e * 64 + lane] + part[(E + e) * 64 + lane]) + part[(2 * E + e) * 64 + lane]) + part[(3 * E + e) * 64 + lane];
-        if (bias) l = l + bias[e];
-        lg[j] = l;
-        const bool first = j == 0 || l > bv;
-        const bool second = !first && (j == 1 || l > sv);
-        sv = first ? bv : second ? l : sv;
-        se = first ? be : second ? e : se;
-        bv = first ? l : bv;
-        be = first ? e : be;
-    }
-    __syncthreads();                                         // the partial sums are used up: candidates take their place
-    float *cand_v = part;                                    // [NW][2][64]
-    int *cand_e = reinterpret_cast<int *>(part + NW * 2 * 64);      // [NW][2][64]
-    float *den_part = part + 2 * NW * 2 * 64;                // [NW][64]
-    cand_v[(wave * 2 + 0) * 64 + lane] = bv;
-    cand_v[(wave * 2 + 1) * 64 + lane] = sv;
-    cand_e[(wave * 2 + 0) * 64 + lane] = be;
-    cand_e[(wave * 2 + 1) * 64 + lane] = se;
-    __syncthreads();
-    // every wavefront merges the candidates of its token, in ascending order of the experts
-    bv = cand_v[lane]; sv = cand_v[64 + lane];
-    be = cand_e[lane]; se = cand_e[64 + lane];
-#pragma unroll
-    for (int c = 2; c < 2 * NW; ++c) {
-        const float l = cand_v[c * 64 + lane];
-        const int e = cand_e[c * 64 + lane];
-        const bool first = l > bv;
-        const bool second = !first && l > sv;
-        sv = first ? bv : second ? l : sv;
-        se = first ? be : second ? e : se;
-        bv = first ? l : bv;
-        be = first ? e : be;
-    }
-    float den = 0.0f;
-#pragma unroll
-    for (int j = 0; j < EPW; ++j) den += expf(lg[j] - bv);
-    den_part[wave * 64 + lane] = den;
-    __syncthreads();
-    if (wave != 0 || t >= T) return;
-    den = den_part[lane];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) den += den_part[w * 64 + lane];
     if (finished && finished[t]) {
-        // batch pruning (Sec. 3.5): an expert index past the real experts and a zero scale
+        // batch pruning (Sec. 3.5): the row gets an expert index past the real experts, so the
+        // sort moves it behind every active row, and a zero scale
         for (int j = 0; j < k; ++j) {
             expert_idx[k * t + j] = E;
             expert_scale[k * t + j] = 0.0f;
         }
     } else if (k == 1) {
-        expert_idx[t] = be;
+        expert_idx[t] = sel[0];
         expert_scale[t] = 1.0f / den;
     } else {
-        const float e2 = expf(sv - bv);
+        const float e2 = expf(selv[1] - selv[0]);
         float s0 = 1.0f / den, s1 = e2 / den;
         if (renorm) { s0 = 1.0f / (1.0f + e2); s1 = e2 / (1.0f + e2); }
-        expert_idx[2 * t] = be;
-        expert_idx[2 * t + 1] = se;
+        expert_idx[2 * t] = sel[0];
+        expert_idx[2 * t + 1] = sel[1];
         expert_scale[2 * t] = s0;
         expert_scale[2 * t + 1] = s1;
     }
+}
+
+// Logits, top-k, softmax and the stores of the NT tokens of a block (a multiple of four) from the four partial sums in LDS,
+// part[p][token][ld].  Sixteen lanes finish a token, four tokens per wavefront at a time: lane (j, kk) of a wavefront holds
+// the logits of NB neighbouring experts (of each of S slices of 16 NB experts) of token kk, so a reduction is a few
+// comparisons in the lane and four data-parallel steps within the row of sixteen lanes.
+template <int S, int NB>
+__device__ inline void finish_tokens(const float *part, int NT, int ld, int t0, int wave, int nwave,
+                                     const float *__restrict__ bias, const uint8_t *__restrict__ finished, int T, int E,
+                                     int k, int renorm, int32_t *__restrict__ expert_idx, float *__restrict__ expert_scale)
+{
+    const int j = threadIdx.x & 15, kk = (threadIdx.x >> 4) & 3;
+    for (int b0 = 4 * wave; b0 < NT; b0 += 4 * nwave) {
+        const int b = b0 + kk, t = t0 + b;
+        float lg[S][NB];
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const int e = (s * 16 + j) * NB + q;
+                const float *src = part + (size_t)b * ld + e;
+                float l = ((src[0] + src[(size_t)NT * ld]) + src[(size_t)2 * NT * ld]) + src[(size_t)3 * NT * ld];
+                if (bias) l = l + bias[min(e, E - 1)];
+                lg[s][q] = e < E ? l : -INFINITY;
+            }
+        auto steps = [](auto &&f) __attribute__((always_inline)) {
+            f(std::integral_constant<int, 1>{});
+            f(std::integral_constant<int, 2>{});
+            f(std::integral_constant<int, 4>{});
+            f(std::integral_constant<int, 8>{});
+        };
+        // best (value, index) with ties to the lower index
+        int sel[2] = {0, 0};
+        float selv[2] = {0.0f, 0.0f};
+        for (int r = 0; r < k; ++r) {
+            float bv = -INFINITY;
+            int be = 0x7fffffff;
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int q = 0; q < NB; ++q) {
+                    const int e = (s * 16 + j) * NB + q;
+                    const bool taken = r == 1 && e == sel[0];
+                    if (e < E && !taken && (lg[s][q] > bv || be == 0x7fffffff)) { bv = lg[s][q]; be = e; }
+                }
+            steps([&](auto off) {
+                constexpr int OFF = decltype(off)::value;
+                const float ov = butterfly_partner<OFF>(bv);
+                const int oe = butterfly_partner<OFF>(be);
+                if (oe != 0x7fffffff && (be == 0x7fffffff || ov > bv || (ov == bv && oe < be))) { bv = ov; be = oe; }
+            });
+            sel[r] = be;
+            selv[r] = bv;
+        }
+        const float lmax = selv[0];
+        float den = 0.0f;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+                if ((s * 16 + j) * NB + q < E) den += expf(lg[s][q] - lmax);
+        steps([&](auto off) { den += butterfly_partner<decltype(off)::value>(den); });
+        if (j == 0 && t < T) store_choice(t, T, E, k, renorm, sel, selv, den, finished, expert_idx, expert_scale);
+    }
+}
+
+// f(integral_constant<I>) for I = 0 .. N-1
+template <int I, int N, class F>
+__device__ inline void gate_static_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        gate_static_for<I + 1, N>(f);
+    }
+}
+
+// The logits on the matrix cores.  v_mfma_f32_16x16x4_f32 adds its four products to the accumulator one after
+// the other, each with the rounding (and the subnormal numbers) of an fp32 fma, so a chain of them over ascending
+// features IS the contract's sequential partial sum, bit for bit, at twice the rate of v_fma_mix_f32 (256 flops
+// per clock and CU) and with far fewer operand reads: 16 tokens x 16 experts x 4 features per instruction.
+// A wavefront owns 16 TT tokens x 16 NB experts of ONE partial sum; the block's first four wavefronts are the four
+// partial sums (S slices of 128 experts each when E > 128).  Lane (j, kk) = (lane & 15, lane >> 4) supplies
+// feature 4 n + kk of token j and of NB neighbouring experts j NB ..: these sit side by side in the row of the gate
+// weight, so one load of 2 NB bytes feeds NB instructions, and nothing is staged through LDS.  A token's features
+// come 64 bytes at a time, 16 per lane, and change lanes in registers.  R groups of 32 features are in flight per
+// wavefront (a ring).
+template <bool BF16, int NB, int S, int TT, int R, bool VEC>
+__global__ __launch_bounds__(256 * S) void gate_mfma_kernel(const uint16_t *__restrict__ x,
+                                                        const uint16_t *__restrict__ wg,
+                                                        const float *__restrict__ bias,
+                                                        const uint8_t *__restrict__ finished, int T, int d,
+                                                        int E, int k, int renorm,
+                                                        int32_t *__restrict__ expert_idx,
+                                                        float *__restrict__ expert_scale)
+{
+    typedef float f4_t __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    constexpr int EP = 16 * NB;                         // experts of a slice
+    constexpr int NT = 16 * TT;                         // tokens of the block
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *part = reinterpret_cast<float *>(smem);      // [4][NT][ld]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int nwave = 4 * S, ld = S * EP + 4;
+    const int p = wave & 3, slice = wave >> 2;
+    const int j = lane & 15, kk = lane >> 4;
+    const int t0 = blockIdx.x * NT;
+
+    const int nblk = (d + kGateBlk - 1) / kGateBlk;
+    // quads (four features) of this partial sum: its 128-feature blocks are p, p + 4, ...; only the last block of all may be short
+    const int mine = p < nblk ? (nblk - p + 3) / 4 : 0;
+    const int nquad = mine * 32 - (mine && (nblk - 1) % 4 == p ? (nblk * kGateBlk - d) / 4 : 0);
+
+    // loads through buffer descriptors; every address is clamped into the row (what lies past the end is not used)
+    const int rows = min(NT, T - t0);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
+    int x_row[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) x_row[t] = min(16 * t + j, rows - 1) * d;
+    const int e0 = slice * EP + j * NB;                 // this lane's experts e0 .. e0 + NB - 1 (clamped where they do not exist)
+    const int w_off = (kk * E + (VEC ? min(e0, E - NB) : 0)) * 2;
+
+    constexpr int WD = NB >= 2 ? NB / 2 : 1;            // dwords of one weight load
+    struct Group { u32x4 x[TT]; uint32_t w[8][WD]; } ring[R];
+    auto load = [&](Group &c, int g) __attribute__((always_inline)) {
+        const int f = (p + 4 * (g >> 2)) * kGateBlk + (g & 3) * 32;
+        const int fl = min(f + 8 * kk, d - 8);
+#pragma unroll
+        for (int t = 0; t < TT; ++t) c.x[t] = __builtin_amdgcn_raw_buffer_load_b128(rx, (x_row[t] + fl) * 2, 0, 0);
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+            const int so = min(f + 4 * n, d - 4) * E * 2;
+            if constexpr (!VEC) {
+#pragma unroll
+                for (int u = 0; u < WD; ++u)
+                    c.w[n][u] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off + 2 * min(e0 + 2 * u, E - 1), so, 0) |
+                                (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off + 2 * min(e0 + 2 * u + 1, E - 1), so, 0) << 16;
+            } else if constexpr (NB == 1) {
+                c.w[n][0] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off, so, 0);
+            } else if constexpr (NB == 2) {
+                c.w[n][0] = __builtin_amdgcn_raw_buffer_load_b32(rw, w_off, so, 0);
+            } else if constexpr (NB == 4) {
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rw, w_off, so, 0);
+                c.w[n][0] = v.x; c.w[n][1] = v.y;
+            } else {
+                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, w_off, so, 0);
+                c.w[n][0] = v.x; c.w[n][1] = v.y; c.w[n][2] = v.z; c.w[n][3] = v.w;
+            }
+        }
+    };
+    // A lane's 16 bytes hold features 8 kk .. 8 kk + 7 of the group; quad n wants feature 4 n + kk.  Halves i and
+    // 4 + i are paired (i = 0 .. 3), and the 4 x 4 matrix of pairs over (kk, i) is transposed across the four rows of
+    // sixteen lanes: dword s then holds features 8 s + kk and 8 s + 4 + kk, the operands of quads 2 s and 2 s + 1.
+    auto spread = [&](u32x4 v, uint32_t (&q)[4]) __attribute__((always_inline)) {
+        q[0] = __builtin_amdgcn_perm(v.z, v.x, 0x05040100u);
+        q[1] = __builtin_amdgcn_perm(v.z, v.x, 0x07060302u);
+        q[2] = __builtin_amdgcn_perm(v.w, v.y, 0x05040100u);
+        q[3] = __builtin_amdgcn_perm(v.w, v.y, 0x07060302u);
+        const auto a = __builtin_amdgcn_permlane16_swap(q[0], q[1], false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap(q[2], q[3], false, false);
+        const auto c = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
+        const auto e = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
+        q[0] = c[0]; q[1] = e[0]; q[2] = c[1]; q[3] = e[1];
+    };
+    f4_t acc[TT][NB];
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int q = 0; q < NB; ++q) acc[t][q] = f4_t{0.f, 0.f, 0.f, 0.f};
+    // All operands of a group are widened to fp32 in one go, then its 8 NB TT matrix instructions run back to back: fp32
+    // matrix instructions share their pipe with the vector ALU, and every change between the two costs (one
+    // conversion between any two of them: 44 clocks instead of 32 each).
+    struct Ops { float x[8][TT], w[8][NB]; };
+    auto widen = [&](const Group &c, Ops &o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < TT; ++t) {
+            uint32_t q[4];
+            spread(c.x[t], q);
+#pragma unroll
+            for (int n = 0; n < 8; ++n) o.x[n][t] = act_to_float<BF16>((uint16_t)(q[n >> 1] >> (16 * (n & 1))));
+        }
+#pragma unroll
+        for (int n = 0; n < 8; ++n)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) o.w[n][b] = act_to_float<BF16>((uint16_t)(c.w[n][b >> 1] >> (16 * (b & 1))));
+    };
+    auto multiply = [&](const Ops &o, int n) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+            for (int t = 0; t < TT; ++t) acc[t][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.x[n][t], o.w[n][q], acc[t][q], 0, 0, 0);
+    };
+    gate_static_for<0, R>([&](auto o) {
+        load(ring[decltype(o)::value], decltype(o)::value);
+        __builtin_amdgcn_sched_barrier(0);              // the loads stay in the loop's order: the wait counts of the first trip fit all of them
+    });
+    const int ng = (nquad + 7) / 8;
+    int g0 = 0;
+    for (; (g0 + R) * 8 <= nquad; g0 += R) {
+        gate_static_for<0, R>([&](auto gc) {
+            constexpr int g = decltype(gc)::value;
+            Ops o;
+            widen(ring[g], o);
+            __builtin_amdgcn_sched_barrier(0);
+            load(ring[g], g0 + g + R);                  // (past the end: in-bounds loads that are not used)
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int n = 0; n < 8; ++n) multiply(o, n);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+    gate_static_for<0, R>([&](auto gc) {                // fewer than 8 R quads are left, all of them in the ring
+        constexpr int g = decltype(gc)::value;
+        if (g0 + g < ng) {
+            Ops o;
+            widen(ring[g], o);
+#pragma unroll
+            for (int n = 0; n < 8; ++n)
+                if ((g0 + g) * 8 + n < nquad) multiply(o, n);
+        }
+    });
+    // acc[t][q][i]: token 16 t + 4 kk + i, expert slice EP + j NB + q
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float *dst = part + ((size_t)p * NT + 16 * t + 4 * kk + i) * ld + slice * EP + j * NB;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) dst[q] = acc[t][q][i];
+        }
+    __syncthreads();
+
+    finish_tokens<S, NB>(part, NT, ld, t0, wave, nwave, bias, finished, T, E, k, renorm, expert_idx, expert_scale);
+}
+
+// Few tokens and 33 to 64 experts: the same chains in v_mfma_f32_4x4x1_16b_f32, sixteen 4 x 4 x 1 products that make up
+// 4 tokens x 64 experts x 1 feature.  A block takes four tokens instead of sixteen, so the batch spreads over four times
+// as many compute units at the same rate of the matrix pipe; lane l supplies expert l's weight and token l & 3's feature, and
+// ends up with expert l's logits of the four tokens.  Per feature a wavefront loads one coalesced row of 64 weights straight into
+// the register it is used from (a ring of R octets of features).
+template <bool BF16, int R>
+__global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
+                                                            const float *__restrict__ bias,
+                                                            const uint8_t *__restrict__ finished, int T, int d, int E,
+                                                            int k, int renorm, int32_t *__restrict__ expert_idx,
+                                                            float *__restrict__ expert_scale)
+{
+    typedef float f4_t __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int NT = 4, ld = 64 + 4;
+    __shared__ float part[4 * NT * ld];
+    const int lane = threadIdx.x & 63;
+    const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = blockIdx.x * NT;
+    const int nblk = (d + kGateBlk - 1) / kGateBlk;
+    const int mine = p < nblk ? (nblk - p + 3) / 4 : 0;
+    const int nq = mine * 16 - (mine && (nblk - 1) % 4 == p ? (nblk * kGateBlk - d) / 8 : 0);     // octets of this partial sum
+    auto feature = [&](int q) { return min((p + 4 * (q >> 4)) * kGateBlk + (q & 15) * 8, d - 8); };   // clamped into the row
+    const int rows = min(NT, T - t0);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
+    const int x_off = min(lane & 3, rows - 1) * d * 2, w_off = min(lane, E - 1) * 2;
+
+    struct Octet { u32x4 x; uint16_t w[8]; } ring[R];
+    auto load = [&](Octet &c, int q) __attribute__((always_inline)) {
+        const int f = feature(q);
+        c.x = __builtin_amdgcn_raw_buffer_load_b128(rx, x_off, f * 2, 0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c.w[u] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off, (f + u) * E * 2, 0);
+    };
+    f4_t acc = {0.f, 0.f, 0.f, 0.f};
+    struct Ops { float x[8], w[8]; };
+    auto widen = [&](const Octet &c, Ops &o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t v = u < 2 ? c.x.x : u < 4 ? c.x.y : u < 6 ? c.x.z : c.x.w;
+            o.x[u] = act_to_float<BF16>((uint16_t)(v >> (16 * (u & 1))));
+            o.w[u] = act_to_float<BF16>(c.w[u]);
+        }
+    };
+    auto multiply = [&](const Ops &o) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f32_4x4x1f32(o.x[u], o.w[u], acc, 0, 0, 0);
+    };
+    gate_static_for<0, R>([&](auto o) {
+        load(ring[decltype(o)::value], decltype(o)::value);
+        __builtin_amdgcn_sched_barrier(0);              // the loads stay in the loop's order
+    });
+    int q0 = 0;
+    for (; q0 + R <= nq; q0 += R) {
+        gate_static_for<0, R / 2>([&](auto oc) {        // two octets at a time: conversions and matrix instructions in longer runs
+            constexpr int o = 2 * decltype(oc)::value;
+            Ops a, b;
+            widen(ring[o], a);
+            widen(ring[o + 1], b);
+            __builtin_amdgcn_sched_barrier(0);
+            load(ring[o], q0 + o + R);                  // (past the end: in-bounds loads that are not used)
+            load(ring[o + 1], q0 + o + 1 + R);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(a);
+            multiply(b);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+    gate_static_for<0, R - 1>([&](auto oc) {
+        constexpr int o = decltype(oc)::value;
+        if (q0 + o < nq) {
+            Ops a;
+            widen(ring[o], a);
+            multiply(a);
+        }
+    });
+#pragma unroll
+    for (int i = 0; i < NT; ++i) part[(p * NT + i) * ld + lane] = acc[i];
+    __syncthreads();
+    finish_tokens<1, 4>(part, NT, ld, t0, p, 4, bias, finished, T, E, k, renorm, expert_idx, expert_scale);
+}
+
+template <bool BF16, int NB, int S, int TT, int R, bool VEC>
+static void launch_gate_mfma(const uint16_t *x, const uint16_t *wg, const float *bias, const uint8_t *finished, int T, int d, int E,
+                                 int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
+{
+    const size_t smem = (size_t)4 * 16 * TT * (S * 16 * NB + 4) * sizeof(float);
+    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(&gate_mfma_kernel<BF16, NB, S, TT, R, VEC>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
+    (void)raised;
+    hipLaunchKernelGGL((gate_mfma_kernel<BF16, NB, S, TT, R, VEC>), dim3((T + 16 * TT - 1) / (16 * TT)), dim3(256 * S), smem, s, x, wg, bias,
+                       finished, T, d, E, k, renorm, expert_idx, expert_scale);
+}
+
+template <bool BF16>
+static void launch_gate(const uint16_t *x, const uint16_t *wg, const float *bias, const uint8_t *finished, int T, int d, int E,
+                        int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
+{
+    // 33 to 64 experts and up to four tokens per compute unit: four-token blocks.  (64 experts, T = 64: 10.0 against 12.7 us
+    // for sixteen-token blocks at d = 1024, 25.8 against 28.0 us at d = 4096; T = 2048: 17.5 against 11.8 us.  Beyond 64
+    // experts its one-row loads of the gate weight are the bound and it loses everywhere; up to 32 it idles half its lanes.)
+    if (E > 32 && E <= 64 && T <= 1024) {
+        hipLaunchKernelGGL((gate_quad_kernel<BF16, 8>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        return;
+    }
+    // Two row tiles per wavefront (one load and conversion of the gate weight for 32 tokens) once that still gives every
+    // compute unit a block.  (T = 8192, d = 4096, 64 experts: 48.5 against 52 us; T = 4096: 45 against 30 us.)  With up to 16
+    // experts the conversions of the tokens, not of the weights, are the larger part: one tile always.
+    const bool two = (T + 31) / 32 >= 256;
+#define MOE_GATE_MFMA(NB, S, TT, R, VEC) launch_gate_mfma<BF16, NB, S, TT, R, VEC>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale, s)
+    if (E <= 16) MOE_GATE_MFMA(1, 1, 1, 8, true);
+    else if (E <= 32) {
+        if (E % 2) MOE_GATE_MFMA(2, 1, 1, 4, false);
+        else if (two) MOE_GATE_MFMA(2, 1, 2, 4, true);
+        else MOE_GATE_MFMA(2, 1, 1, 8, true);
+    } else if (E <= 64) {
+        if (E % 4) MOE_GATE_MFMA(4, 1, 1, 2, false);
+        else if (two) MOE_GATE_MFMA(4, 1, 2, 4, true);
+        else MOE_GATE_MFMA(4, 1, 1, 6, true);
+    } else if (E <= 128) {
+        if (E % 4) MOE_GATE_MFMA(4, 2, 1, 2, false);
+        else if (two) MOE_GATE_MFMA(4, 2, 2, 4, true);
+        else MOE_GATE_MFMA(4, 2, 1, 4, true);
+    } else {
+        if (E % 8) MOE_GATE_MFMA(8, 2, 1, 1, false);
+        else MOE_GATE_MFMA(8, 2, 1, 3, true);
+    }
+#undef MOE_GATE_MFMA
 }
 
 }  // namespace moe
@@ -467,49 +446,8 @@ extern "C" int moe_gate_topk(const void *x, int act_dtype, const void *wg, const
     if (act_dtype != MOE_F16 && act_dtype != MOE_BF16) return fail(MOE_ERR_UNSUPPORTED, "moe_gate_topk: act_dtype must be fp16 or bf16");
     if (!aligned16(x) || !aligned16(wg)) return fail(MOE_ERR_INVALID_ARG, "moe_gate_topk: x and wg must be 16-byte aligned");
     hipStream_t s = as_stream(stream);
-    const bool bf = act_dtype == MOE_BF16;
-    if (!bf && E == 64 && d % kGateBlk == 0 && T >= 16384) {     // a token per lane, and a block of 64 tokens for every CU at least
-        dim3 grid((T + 63) / 64), block(512);
-        const size_t smem = (size_t)4 * 64 * 64 * sizeof(float);
-        hipLaunchKernelGGL((gate_token_lanes_kernel<32>), grid, block, smem, s, (const uint16_t *)x, (const uint16_t *)wg,
-                           bias, finished, T, d, k, renormalize, expert_idx, expert_scale);
-        return check_launch("moe_gate_topk");
-    }
-    int EL = 8;
-    while (EL < E && EL < 64) EL *= 2;
-    const int NE = (E + 63) / 64;
-    // tokens per lane group: sixteen when every lane group is a whole wavefront and there are
-    // enough tokens to fill the chip that way (each block stages the whole gate weight, so more
-    // tokens per block mean less staging per token), thirty-two for bf16 rows, which go through
-    // LDS (with FP16 rows in scalar registers that many tokens measured twice as slow); else four;
-    // one when even that would leave most of the chip idle
-    const int tb = (bf && EL == 64 && NE == 1 && T / 32 >= 256) ? 32 : (EL == 64 && T / 16 >= 256) ? 16 : ((long)T * EL / 64 + 3) / 4 >= 256 ? 4 : 1;
-    const int ntok = (64 / EL) * tb;
-    const size_t wave_halfs = (tb == 16 && NE == 1 && !bf ? 0 : (size_t)ntok * kGateBlk) + (NE == 1 ? (size_t)kGateWRow * kGateBlk : 0);
-    const size_t part_bytes = (size_t)4 * (NE == 3 ? 4 : NE) * tb * 64 * 4;      // shares the staging space
-    const size_t smem = (size_t)4 * wave_halfs * 2 > part_bytes ? (size_t)4 * wave_halfs * 2 : part_bytes;
-    dim3 grid((T + ntok - 1) / ntok), block(256);
     const uint16_t *xp = (const uint16_t *)x, *wp = (const uint16_t *)wg;
-#define MOE_GATE_LAUNCH(BF, NEV, TBV, GMV)                                                             \
-    do {                                                                                               \
-        /* more than 64 KB of dynamic LDS must be asked for once (a local static: once, also across threads) */ \
-        static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(&gate_kernel<BF, NEV, TBV, GMV>), \
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024); \
-        (void)raised;                                                                                  \
-        hipLaunchKernelGGL((gate_kernel<BF, NEV, TBV, GMV>), grid, block, smem, s, xp, wp, bias, finished, T, d, E,\
-                           EL, k, renormalize, expert_idx, expert_scale);                              \
-    } while (0)
-#define MOE_GATE_TB(BF, NEV)                                                                           \
-    do {                                                                                               \
-        if (tb == 16) MOE_GATE_LAUNCH(BF, NEV, 16, 1);                                                 \
-        else if (tb == 4) MOE_GATE_LAUNCH(BF, NEV, 4, 8);                                              \
-        else MOE_GATE_LAUNCH(BF, NEV, 1, 8);                                                           \
-    } while (0)
-    if (NE == 1 && tb == 32) MOE_GATE_LAUNCH(true, 1, 32, 1);
-    else if (NE == 1) { if (bf) MOE_GATE_TB(true, 1); else MOE_GATE_TB(false, 1); }
-    else if (NE == 2) { if (bf) MOE_GATE_TB(true, 2); else MOE_GATE_TB(false, 2); }
-    else { if (bf) MOE_GATE_TB(true, 4); else MOE_GATE_TB(false, 4); }
-#undef MOE_GATE_TB
-#undef MOE_GATE_LAUNCH
+    if (act_dtype == MOE_BF16) launch_gate<true>(xp, wp, bias, finished, T, d, E, k, renormalize, expert_idx, expert_scale, s);
+    else launch_gate<false>(xp, wp, bias, finished, T, d, E, k, renormalize, expert_idx, expert_scale, s);
     return check_launch("moe_gate_topk");
 }
