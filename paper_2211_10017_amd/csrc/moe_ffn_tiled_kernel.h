@@ -10,7 +10,7 @@
 #pragma once
 #include <type_traits>
 
-#include "moe_ffn_common.h"
+#include "moe_ffn_epilogue.h"
 
 namespace moe {
 
@@ -24,9 +24,11 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
 {
     constexpr int BM = 32 * TM;
     constexpr int NW = BITS == 4 ? 1 : 2;             // 16-byte loads per tile per 64-deep K step
-    __shared__ __align__(16) uint16_t lds_a[2][BM * kLdsRow];
-    __shared__ int32_t s_dst[BM];          // fused un-permute: destination row and gate scale of each row of the tile
-    __shared__ float s_scale[BM];
+    // two stages of rows; at the end the patches through which the wavefronts' results leave
+    constexpr int kStageBytes = 2 * BM * kLdsRow * 2, kPatches = 4 * kPatchBytes<16>;
+    __shared__ __align__(16) uint8_t lds_raw[kStageBytes > kPatches ? kStageBytes : kPatches];
+    uint16_t (*lds_a)[BM * kLdsRow] = reinterpret_cast<uint16_t (*)[BM * kLdsRow]>(lds_raw);
+    __shared__ TileRows<BM> tile_rows;
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: tile addresses stay scalar
     const int K = p.K, N = p.N;
@@ -35,17 +37,21 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     e = __builtin_amdgcn_readfirstlane(e), col = __builtin_amdgcn_readfirstlane(col);      // the same in every lane: kept in scalar registers
     row0 = __builtin_amdgcn_readfirstlane(row0), rows = __builtin_amdgcn_readfirstlane(rows);
 
-    if (p.out_dst && (int)threadIdx.x < rows) {       // read long before the epilogue; the K loop's barriers publish it
-        const int dst = p.out_dst[row0 + threadIdx.x];
-        s_dst[threadIdx.x] = dst;
-        s_scale[threadIdx.x] = p.out_scale[dst];
-    }
+    // what the rows need at the end is requested now; the tallest tile has no registers to carry it through the K loop
+    RowEntry<BM> entry;
+    entry.load(p, row0, rows);
+    if constexpr (TM == 4) entry.put(tile_rows);
     const int nk = K / 64;
     const int ntile0 = (col * 4 + wave) * kTN;         // first 32-channel tile of this wavefront
-    const int ntiles = N / 32;
-    bool tile_ok[kTN];
-#pragma unroll
-    for (int t = 0; t < kTN; ++t) tile_ok[t] = ntile0 + t < ntiles;
+    const bool tile_ok = ntile0 * 32 < N;              // N is a multiple of 64: both tiles exist or neither does
+    const int tile_c = tile_ok ? ntile0 : 0;
+    float cs_lane = 1.0f, bias_lane = 0.0f;            // channel factors: lane l brings channel l of the wavefront's 64
+    auto load_channels = [&]() {
+        const size_t n = (size_t)e * N + tile_c * 32 + lane;
+        if (SMODE == SCALE_CHANNEL) cs_lane = __half2float(p.scales[n]);
+        if (p.bias) bias_lane = __half2float(p.bias[n]);
+    };
+    if constexpr (TM < 4) load_channels();
 
     // ---- global addresses
     // A: thread loads 16 bytes = 8 K values of row (tid/8 + 32*pass)
@@ -65,15 +71,13 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     const uint4 *b_ptr[kTN];
 #pragma unroll
     for (int t = 0; t < kTN; ++t) {
-        const int nt = tile_ok[t] ? ntile0 + t : 0;
-        b_ptr[t] = reinterpret_cast<const uint4 *>(w_e + (size_t)nt * (K / frag_k(BITS)) * kFragBytes);   // wave-uniform
+        b_ptr[t] = reinterpret_cast<const uint4 *>(w_e + (size_t)(tile_c + t) * (K / frag_k(BITS)) * kFragBytes);   // wave-uniform
     }
     const int G = K / p.g;
     const __half *s_ptr[kTN];
 #pragma unroll
     for (int t = 0; t < kTN; ++t) {
-        const int nt = tile_ok[t] ? ntile0 + t : 0;
-        s_ptr[t] = p.scales + (size_t)e * G * N + nt * 32;              // wave-uniform
+        s_ptr[t] = p.scales + (size_t)e * G * N + (tile_c + t) * 32;              // wave-uniform
     }
 
     float16_t acc[TM][kTN];
@@ -286,64 +290,18 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     else k_loop(std::integral_constant<int, 1>{});
     wait_loads<0>();      // the last step's (unused) refill of the other stage must land before the block's LDS is given up
 
-    // ---- epilogue: scale (per channel), bias, activation, store.  acc[m][t][i] is row
-    // 32*m + 8*(i/4) + 4*(lane/32) + i%4 of the tile, channel lane%32 of tile t.
-    // Two channels leave per store: registers i and i+1 are two rows of one channel; a lane
-    // hands the row its neighbour (lane ^ 1, the next channel) keeps to that neighbour and gets the
-    // other row's value back, so the even lane stores channels (n, n+1) of the first row and the
-    // odd lane channels (n-1, n) of the second.
-    auto finish = [&](float a, int rl, float cs, float bias) {
-        float v = a * cs;
-        if (p.row_pow) v *= p.row_pow[row0 + min(rl, rows - 1)].y;     // rows that went in scaled by a power of two (bf16 rows)
-        v += bias;
-        v = activate(v, p.act);
-        if (p.out_dst) v *= s_scale[min(rl, rows - 1)];         // gate scale of the fused un-permute
-        return v;
-    };
-    auto store_tiles = [&](auto out_tag) {
-        using OT = decltype(out_tag);                            // float | _Float16 | uint16_t (bf16 bits)
-        OT *out = reinterpret_cast<OT *>(p.out);
-        // per-channel factors of the wavefront's two tiles first; then, row pair by row pair, both tiles:
-        // the two halves of a 128-byte line of the output leave back to back
-        float cs[kTN], bias[kTN];
+    // ---- epilogue: acc[m][t][i] is row 32*m + 8*(i/4) + 4*(lane/32) + i%4 of the tile, channel lane%32 of tile t
+    if constexpr (TM < 4) entry.put(tile_rows);
+    __syncthreads();                                   // every wavefront has left the stages
+    if (!tile_ok) return;
+    float cs[kTN], bias[kTN];
+    if constexpr (TM == 4) load_channels();
 #pragma unroll
-        for (int t = 0; t < kTN; ++t) {
-            const int n = (tile_ok[t] ? ntile0 + t : 0) * 32 + (lane & 31);       // clamped: always a channel of this expert
-            cs[t] = SMODE == SCALE_CHANNEL ? __half2float(p.scales[(size_t)e * N + n]) : SMODE == SCALE_GROUP_SPLIT ? 1.0f / 256.0f : 1.0f;
-            bias[t] = p.bias ? __half2float(p.bias[(size_t)e * N + n]) : 0.0f;
-        }
-#pragma unroll
-        for (int m = 0; m < TM; ++m) {
-#pragma unroll
-            for (int i = 0; i < 16; i += 2) {
-                const int rl = 32 * m + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);     // row of register i; i + 1 is the next row
-                const bool odd = lane & 1;
-                const int rs = rl + (odd ? 1 : 0);
-                OT *dst_row = out + (size_t)(p.out_dst ? s_dst[min(rs, rows - 1)] : row0 + rs) * N;
-#pragma unroll
-                for (int t = 0; t < kTN; ++t) {
-                    if (!tile_ok[t]) continue;
-                    const int n = (ntile0 + t) * 32 + (lane & 31);
-                    const float v0 = finish(acc[m][t][i], rl, cs[t], bias[t]), v1 = finish(acc[m][t][i + 1], rl + 1, cs[t], bias[t]);
-                    const float got = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-                                          0, __builtin_bit_cast(int, odd ? v0 : v1), 0xB1, 0xf, 0xf, false));   // quad_perm [1,0,3,2]
-                    const float lo = odd ? got : v0, hi = odd ? v1 : got;
-                    if (rs < rows) {
-                        OT *dst = dst_row + (n & ~1);
-                        if constexpr (std::is_same<OT, float>::value)
-                            *reinterpret_cast<float2 *>(dst) = make_float2(lo, hi);
-                        else if constexpr (std::is_same<OT, _Float16>::value)
-                            *reinterpret_cast<uint32_t *>(dst) = h2_bits(half2_t{(_Float16)lo, (_Float16)hi});
-                        else
-                            *reinterpret_cast<uint32_t *>(dst) = (uint32_t)to_bf16_rne(lo) | ((uint32_t)to_bf16_rne(hi) << 16);
-                    }
-                }
-            }
-        }
-    };
-    if (p.out_dtype == MOE_F32) store_tiles(float{});
-    else if (p.out_dtype == MOE_BF16) store_tiles(uint16_t{});
-    else store_tiles(_Float16{});
+    for (int t = 0; t < kTN; ++t) {
+        cs[t] = SMODE == SCALE_CHANNEL ? __shfl(cs_lane, 32 * t + (lane & 31)) : SMODE == SCALE_GROUP_SPLIT ? 1.0f / 256.0f : 1.0f;
+        bias[t] = __shfl(bias_lane, 32 * t + (lane & 31));
+    }
+    finish_tile<TM, 16, BM>(p, acc, tile_rows, cs, bias, rows, 0, ntile0 * 32, lds_raw + wave * kPatchBytes<16>);
 }
 
 template <int BITS, int SMODE>
