@@ -253,6 +253,10 @@ int moe_grouped_ffn_wq_routed(const void *x, int act_dtype, const int32_t *perm_
  */
 int moe_grouped_ffn_wq_gated_supported(int T, int k, int E, int d, int F, int bits, int group_size,
                                        int act_dtype);
+/* 1 when the gated call is also the faster way for these sizes (MoEExpertLayer asks this): on larger weights
+ * moe_permute + moe_grouped_ffn_wq + moe_combine stream faster than the two launches it runs there. */
+int moe_grouped_ffn_wq_gated_pays(int T, int k, int E, int d, int F, int bits, int group_size,
+                                  int act_dtype);
 int moe_grouped_ffn_wq_gated(const void *x, int act_dtype, const int32_t *expert_idx,
                              const float *expert_scale, int T, int k,
                              int E, int d, int F, int bits, int group_size, int activation,

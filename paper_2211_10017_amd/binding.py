@@ -22,7 +22,7 @@ EXPORTS = ["moe_last_error", "moe_last_ffn_kernels", "moe_device_info", "moe_abi
            "moe_permute_workspace_bytes", "moe_permute", "moe_grouped_ffn_wq_workspace_bytes",
            "moe_grouped_ffn_wq", "moe_combine", "moe_pack_fp16_experts", "moe_grouped_gemm_wq",
            "moe_grouped_ffn_wq_routed_supported", "moe_grouped_ffn_wq_routed",
-           "moe_grouped_ffn_wq_gated_supported", "moe_grouped_ffn_wq_gated",
+           "moe_grouped_ffn_wq_gated_supported", "moe_grouped_ffn_wq_gated_pays", "moe_grouped_ffn_wq_gated",
            "moe_grouped_ffn_wq_noalloc_max_bytes", "moe_grouped_ffn_wq_noalloc"]
 
 LAYER_MAX_EXPERTS = 256   # experts of a whole layer call: moe_gate_topk's limit (moe_permute: 1024, the FFN: 4096)
@@ -75,6 +75,8 @@ def load():
                                               vp, sz, vp]
     lib.moe_grouped_ffn_wq_gated_supported.restype = i
     lib.moe_grouped_ffn_wq_gated_supported.argtypes = [i, i, i, i, i, i, i, i]
+    lib.moe_grouped_ffn_wq_gated_pays.restype = i
+    lib.moe_grouped_ffn_wq_gated_pays.argtypes = [i, i, i, i, i, i, i, i]
     lib.moe_grouped_ffn_wq_gated.restype = i
     lib.moe_grouped_ffn_wq_gated.argtypes = [vp, i, vp, vp, i, i, i, i, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, i, vp, vp, vp,
                                              vp, sz, vp]
@@ -292,6 +294,11 @@ def moe_grouped_ffn_wq_routed(x, perm_src, k: int, expert_offsets, E: int, d: in
 def moe_grouped_ffn_wq_gated_supported(T: int, k: int, E: int, d: int, F: int, bits: int, group_size: int, act_dtype) -> int:
     """0: not taken; 1: permute + FFN; 2: expert_scale may be given as well (combine fused in)."""
     return int(load().moe_grouped_ffn_wq_gated_supported(T, k, E, d, F, bits, group_size, _DT[act_dtype]))
+
+
+def moe_grouped_ffn_wq_gated_pays(T: int, k: int, E: int, d: int, F: int, bits: int, group_size: int, act_dtype) -> bool:
+    """Whether the gated call is also the faster way for these sizes."""
+    return bool(load().moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, _DT[act_dtype]))
 
 
 def moe_grouped_ffn_wq_gated(x, expert_idx, E: int, d: int, F: int, bits: int, group_size: int, w1_packed, s1, w2_packed,

@@ -113,7 +113,11 @@ static GemmKernel choose_kernel(int R, int E, int max_rows, int K, int N, int bi
 static int run_gemm(moe::GemmArgs g, int bits, int smode, bool bf, int max_rows, hipStream_t s)
 {
     using namespace moe;
-    const GemmKernel kernel = choose_kernel(g.R, g.E, max_rows, g.K, g.N, bits, smode, bf);
+    GemmKernel kernel = choose_kernel(g.R, g.E, max_rows, g.K, g.N, bits, smode, bf);
+    // Without the permutation inside the launch the streaming kernels pay for at most one row per expert on average only: every
+    // further row group of an expert streams its weights again (64 tokens on 16 experts of 4096 x 16384: 4-bit 541 us per step
+    // against 230 in the row tiles, 8-bit 916 against 360).
+    if (!g.gate_idx && !g.out_add && g.R > g.E) kernel = GEMM_TILED;
     note_kernel(kernel == GEMM_STREAM_UNROLLED ? "stream_unrolled_kernel" : kernel == GEMM_STREAM_LOOP ? "stream_gemm_kernel" : "grouped_gemm_kernel");
     if (kernel == GEMM_STREAM_UNROLLED) return launch_stream_unrolled(g, bits, max_rows, s);
     if (g.gate_idx || g.out_add) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_gated: K=%d does not run in the straight-line kernel with these sizes", g.K);
@@ -351,6 +355,19 @@ static int gated_shapes(int T, int k, int E, int d, int F, int bits, int group_s
     // ... and fc2 as well, if it is to add its rows straight into the layer output
     const bool fc2 = choose_kernel(R, E, T, F, d, bits, SCALE_CHANNEL, false) == GEMM_STREAM_UNROLLED;
     return fc2 ? 2 : 1;
+}
+
+// Whether a layer should take the gated call where it is supported: yes for the decode kernel; with the streaming kernels
+// while a weight matrix's active experts are small enough for the saved launch to count (16.8 MB, 256 rows of 512 x 2048:
+// 20 us against 25 in permute + row tiles; 134 MB, 64 rows on 32 experts of 1024 x 4096 8-bit: 64 and 68), or for at most
+// one row per expert on average (16 tokens on 32 experts of 2048 x 8192 8-bit: 142 and 151); otherwise the row tiles
+// stream faster (64 tokens, 2048 x 8192: 4-bit 146 and 115, 8-bit 228 and 190).
+extern "C" int moe_grouped_ffn_wq_gated_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
+{
+    using namespace moe;
+    if (!gated_shapes(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
+    const int R = T * k;
+    return decode_ffn_supports(R, E, d, F, bits) || R <= E || (double)E * d * F * bits / 8 <= 150e6;
 }
 
 extern "C" int moe_grouped_ffn_wq_gated_supported(int T, int k, int E, int d, int F, int bits, int group_size,

@@ -72,6 +72,8 @@ void launch_tiled_4(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t
 void launch_tiled_4_exact(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);
 void launch_tiled_8(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);
 void launch_tiled_8_exact(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);
+void launch_ring_4(const GemmArgs &p, int smode, int bm, dim3 grid, hipStream_t s);
+void launch_ring_8(const GemmArgs &p, int smode, int bm, dim3 grid, hipStream_t s);
 int launch_stream_gemm(const GemmArgs &p, int bits, int smode, int max_rows, hipStream_t s);
 bool stream_gemm_supports(int K, int bits, int smode);
 int stream_gemm_fit_rows(int K);
@@ -203,10 +205,20 @@ __device__ inline void store_out(void *out, int dtype, size_t o, float v)
 // the first use of any).  The caller waits for it by hand with wait_loads<N>(), N = the loads
 // issued after it that may stay in flight: the counter retires loads in order, and the waits the
 // compiler places for its own loads can only be stricter for the ones it does not see.
+template <bool NT = false>
 __device__ inline void load_to_lds16(const void *src, uint16_t *dst)
 {
     const uint32_t l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst;
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(l) : "memory", "m0");
+    // (NT: non-temporal, for data that is read once)
+    if constexpr (NT) asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(src), "s"(l) : "memory", "m0");
+    else asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(l) : "memory", "m0");
+}
+
+// The same with 4 bytes per lane: lane l's bytes land at dst + 4 l.
+__device__ inline void load_to_lds4(const void *src, void *dst)
+{
+    const uint32_t l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(l) : "memory", "m0");
 }
 
 // s_waitcnt vmcnt(N) alone (the other counters' fields say "no wait").
@@ -259,6 +271,7 @@ __device__ inline void expert_range(const int32_t *offsets, int e, int R, int *l
     *hi = min(max(offsets[e + 1], l), R);
 }
 
+template <int UNIT = 32>
 __device__ inline bool find_item(const int32_t *offsets, int E, int R, int BM, int ncol, int wg,
                                  int *e_out, int *col, int *row0, int *rows)
 {
@@ -297,15 +310,15 @@ __device__ inline bool find_item(const int32_t *offsets, int E, int R, int BM, i
             const int local = (int)(item - (long)(base + excl) * ncol);
             const int c = local / t_e, mt = local % t_e;
             const int lo_s = __shfl(lo, src), hi_s = __shfl(hi, src);
-            // The expert's rows, in units of 32 (one MFMA row tile), are dealt evenly to its t_e
+            // The expert's rows, in units of UNIT = 32 (one MFMA row tile), are dealt evenly to its t_e
             // tiles: 270 rows become 96 + 96 + 78 rather than 128 + 128 + 14, the same matrix
             // work without a nearly empty tile that streams a whole weight block for 14 rows.
-            const int units = (hi_s - lo_s + 31) / 32, per = units / t_e, extra = units % t_e;
-            const int first = lo_s + 32 * (mt * per + min(mt, extra));
+            const int units = (hi_s - lo_s + UNIT - 1) / UNIT, per = units / t_e, extra = units % t_e;
+            const int first = lo_s + UNIT * (mt * per + min(mt, extra));
             *e_out = e0 + src;
             *col = c;
             *row0 = first;
-            *rows = min(32 * (per + (mt < extra ? 1 : 0)), hi_s - first);
+            *rows = min(UNIT * (per + (mt < extra ? 1 : 0)), hi_s - first);
             return true;
         }
         base += __shfl(incl, 63);

@@ -1,0 +1,270 @@
+// Grouped GEMM with fused dequantisation for launches with few rows per expert or few row tiles (Sec. 3.3,
+// Sec. 3.4): the packed weights, the group scales and the activation rows all go from memory straight
+// into a ring of LDS stages, several K steps ahead.
+//
+// Such a launch is bound by how many bytes it keeps in flight (few rows per expert: it streams weights), or, with
+// about one tile per compute unit, by the latency of what a lone wavefront per SIMD waits for.  Loads into
+// registers can be one or two steps ahead at most (moe_ffn_tiled_kernel.h); loads into LDS need no registers,
+// are counted by hand, and NST - 1 stages of them stay in flight.  The K range is split over WK groups of
+// wavefronts of the block, whose partial tiles meet in LDS at the end, added in the order of K: twice the blocks,
+// each with half the chain of K steps.
+//
+// Block: 2 x 2 wavefronts; wavefront (wc, kp) computes BM rows x 64 channels over the kp-th half of K.  A stage
+// holds, per K part, the rows' 64 K values (unpadded 128-byte rows, 16-byte chunks at position
+// chunk ^ ((row >> 1) & 7): conflict-free fragment reads), and per wavefront its two tiles' fragment
+// blocks and, for group scales, the 64 channels' scales of the step's group.
+//
+// Measured (64 tokens, 32 experts of 2048 x 8192, 4-bit, per step): 1 x 4 column wavefronts without a split 128 us, 2 x 4 (one
+// block per compute unit) 147, 2 x 2 with two blocks per compute unit 124, with three 115; weights loaded temporal instead of
+// non-temporal 154 (8-bit, two blocks: 190, temporal 237).  Rates: 64 tokens on 16 experts of 4096 x 16384, 8-bit, 2.1 GB in a step of
+// 351 us, 6.1 TB/s; in register-fed tiles 459 us.
+#pragma once
+#include <type_traits>
+
+#include "moe_ffn_epilogue.h"
+
+namespace moe {
+
+template <int BITS, int SMODE, int BM, int WC, int WK>
+struct RingShape {
+    static constexpr int NW = BITS == 4 ? 1 : 2;                    // fragment blocks per tile and 64-deep K step
+    static constexpr int TM = BM < 32 ? 1 : BM / 32;                // 32-row matrix tiles (of a 16-row block the upper half repeats the lower)
+    static constexpr int kWaves = WC * WK;
+    static constexpr bool GROUPED = SMODE != SCALE_CHANNEL;
+    static constexpr int kPartA = BM * 128;                         // bytes of one K part's rows in a stage
+    static constexpr int kWaveB = 2 * NW * kFragBytes + (GROUPED ? 256 : 0);
+    static constexpr int kStage = WK * kPartA + kWaves * kWaveB;
+    static constexpr int kReduce = WK > 1 ? kWaves * TM * 2 * 16 * 64 * 4 : 0;
+    // at the end the stages' space holds the partial tiles, then the patches of the tile end, and the row entries behind either
+    static constexpr int kRows = kReduce > kWaves * kPatchBytes<16 / WK> ? kReduce : kWaves * kPatchBytes<16 / WK>;
+    static constexpr int kEnd = kRows + (int)sizeof(TileRows<32 * TM>);
+    // LDS of a compute unit (160 KB): three blocks where a block's share still holds three stages, else two
+    static constexpr int kLimit = (BM > 32 || BITS == 8 ? 80 : 53) * 1024;
+    static constexpr int kFit = kLimit / kStage;
+    static constexpr int NST = kFit > 6 ? 6 : kFit;                 // stages
+    static constexpr int kLds = NST * kStage > kEnd ? NST * kStage : kEnd;
+    static_assert(NST >= 2 && kLds <= kLimit, "a stage in use and at least one in flight");
+};
+
+template <int BITS, int SMODE, int BM, int WC, int WK>
+__global__ __launch_bounds__(64 * WC * WK, 2) void grouped_gemm_ring_kernel(GemmArgs p)
+{
+    using S = RingShape<BITS, SMODE, BM, WC, WK>;
+    constexpr int TM = S::TM, NW = S::NW, NST = S::NST;
+    constexpr bool GROUPED = S::GROUPED, ACC = SMODE == SCALE_GROUP_ACC;
+    constexpr int D = NST - 1;                          // stages in flight
+    constexpr int NA = BM / 8 > WC ? BM / 8 / WC : 1;   // row loads per wavefront and stage (8 rows each)
+    constexpr int L = NA + 2 * NW + (GROUPED ? 1 : 0);  // loads per wavefront and stage
+    static_assert((D - 1) * L < 64, "the load counter has six bits");
+    extern __shared__ __align__(16) uint8_t lds[];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wc = wave % WC, kp = wave / WC;
+    const int K = p.K, N = p.N;
+    int e, col, row0, rows;
+    if (!find_item<(BM < 32 ? BM : 32)>(p.offsets, p.E, p.R, BM, (N + 64 * WC - 1) / (64 * WC), blockIdx.x, &e, &col, &row0, &rows)) return;
+    e = __builtin_amdgcn_readfirstlane(e), col = __builtin_amdgcn_readfirstlane(col);
+    row0 = __builtin_amdgcn_readfirstlane(row0), rows = __builtin_amdgcn_readfirstlane(rows);
+
+    RowEntry<32 * TM> entry;                                 // what the rows need at the end is requested now
+    entry.load(p, row0, rows);
+    // this wavefront's two 32-channel tiles (N is a multiple of 64: both exist or neither does)
+    const int tile_ok = (col * WC + wc) * 64 < N;
+    const int ntile0 = tile_ok ? (col * WC + wc) * 2 : 0;
+    float cs_lane = 1.0f, bias_lane = 0.0f;             // channel factors: lane l brings channel l of the wavefront's 64
+    if (!GROUPED) cs_lane = __half2float(p.scales[(size_t)e * N + ntile0 * 32 + lane]);
+    if (p.bias) bias_lane = __half2float(p.bias[(size_t)e * N + ntile0 * 32 + lane]);
+    // this wavefront's part of the K steps
+    const int nk = K / 64, per = (nk + WK - 1) / WK;
+    const int first = kp * per, mine = tile_ok ? min(max(nk - first, 0), per) : 0;
+
+    // ---- global addresses.  A load fills eight LDS rows; lane l brings chunk position l & 7 of row l >> 3,
+    // which holds K chunk (l & 7) ^ ((row >> 1) & 7).
+    const uint16_t *a_ptr[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int row = 8 * ((i * WC + wc) % (BM / 8)) + (lane >> 3);
+        const int r = row0 + min(row, rows - 1);                    // clamped: always a valid row
+        const int rs = p.a_src ? p.a_src[r] / p.a_div : r;          // gather fused into the loads
+        a_ptr[i] = p.a + (size_t)rs * K + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+    }
+    const uint8_t *b_ptr[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+        b_ptr[t] = p.wq + (size_t)e * packed_bytes_per_expert(K, N, BITS) + (size_t)(ntile0 + t) * (K / frag_k(BITS)) * kFragBytes + lane * 16;
+    const __half *s_ptr = p.scales + (size_t)e * (K / p.g) * N + ntile0 * 32 + (lane & 31) * 2;
+
+    // all loads of stage `slot`, for K step first + s of this part (past the end: the last step again)
+    auto issue = [&](int s, int slot) {
+        const int kb = min(first + s, nk - 1);
+        uint8_t *st = lds + slot * S::kStage;
+        uint8_t *sb = st + WK * S::kPartA + wave * S::kWaveB;
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+            load_to_lds16(a_ptr[i] + kb * 64, reinterpret_cast<uint16_t *>(st + kp * S::kPartA + (i * WC + wc) % (BM / 8) * 1024));
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+                load_to_lds16<TM == 1>(b_ptr[t] + (size_t)(kb * NW + w) * kFragBytes, reinterpret_cast<uint16_t *>(sb + (t * NW + w) * kFragBytes));
+        // (weights of blocks that hold an expert's rows in one tile, mostly, are read once: non-temporal)
+        if constexpr (GROUPED) load_to_lds4(s_ptr + (size_t)((kb * 64) / p.g) * N, sb + 2 * NW * kFragBytes);
+    };
+
+    float16_t acc[TM][2];
+#pragma unroll
+    for (int m = 0; m < TM; ++m)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[m][t][i] = 0.0f;
+
+    auto compute = [&](int slot, auto live_c) {
+        constexpr int LIVE = decltype(live_c)::value;               // row tiles of this block that hold rows
+        const uint8_t *st = lds + slot * S::kStage;
+        const uint16_t *sa = reinterpret_cast<const uint16_t *>(st + kp * S::kPartA);
+        const uint8_t *sb = st + WK * S::kPartA + wave * S::kWaveB;
+        uint32_t raw[2][NW * 4];
+        _Float16 sc[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(sb + (t * NW + w) * kFragBytes + lane * 16);
+                raw[t][4 * w + 0] = v.x; raw[t][4 * w + 1] = v.y; raw[t][4 * w + 2] = v.z; raw[t][4 * w + 3] = v.w;
+            }
+            if constexpr (GROUPED)
+                sc[t] = *reinterpret_cast<const _Float16 *>(sb + 2 * NW * kFragBytes + (t * 32 + (lane & 31)) * 2);
+        }
+        float16_t part[ACC ? TM : 1][2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            half8_t a[TM];
+#pragma unroll
+            for (int m = 0; m < TM; ++m)
+                if (m < LIVE) a[m] = *reinterpret_cast<const half8_t *>(sa + (32 * m + (lane & (BM < 32 ? BM - 1 : 31))) * 64 + 8 * ((2 * j + (lane >> 5)) ^ ((lane >> 1) & 7)));
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                uint32_t bw[4];
+                if (BITS == 4) dequant4(raw[t][j], bw);
+                else dequant8(raw[t][2 * j], raw[t][2 * j + 1], bw);
+                if constexpr (SMODE == SCALE_GROUP) {
+                    const half2_t s2 = {sc[t], sc[t]};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) bw[q] = h2_bits(bits_h2(bw[q]) * s2);
+                }
+#pragma unroll
+                for (int m = 0; m < TM; ++m) {
+                    if (m >= LIVE) continue;
+                    if constexpr (ACC) {
+                        float16_t c = part[m][t];
+                        if (j == 0)
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) c[i] = 0.0f;
+                        part[m][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[m], frag_from(bw), c, 0, 0, 0);
+                    } else {
+                        acc[m][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[m], frag_from(bw), acc[m][t], 0, 0, 0);
+                    }
+                }
+            }
+        }
+        if constexpr (ACC) {                            // exact codes went in: the step's sums are folded with the group's scale in fp32
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float sf = (float)sc[t];
+#pragma unroll
+                for (int m = 0; m < TM; ++m)
+                    if (m < LIVE)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) acc[m][t][i] = fmaf(part[m][t][i], sf, acc[m][t][i]);
+            }
+        }
+    };
+
+    // Stages issued and not yet used stay in flight; at the top of a step the wavefront waits for its own
+    // share of the step's stage (the loads of the `rem` stages after it may be outstanding: the counter is
+    // in order), and the barrier makes everyone's share visible and tells that everyone has left the
+    // stage before it, which is then refilled.
+#pragma unroll
+    for (int s = 0; s < D; ++s)
+        if (s < per) issue(s, s);
+    auto k_loop = [&](auto live_c) {
+        int slot = 0;
+        for (int s = 0; s < per; ++s) {
+            const int rem = min(per - 1 - s, D - 1);
+            if (rem == D - 1) wait_loads<(D - 1) * L>();
+            else if (D > 4 && rem == 3) wait_loads<(D > 4) * 3 * L>();
+            else if (D > 3 && rem == 2) wait_loads<(D > 3) * 2 * L>();
+            else if (D > 2 && rem == 1) wait_loads<(D > 2) * L>();
+            else wait_loads<0>();
+            __syncthreads();
+            if (s + D < per) issue(s + D, slot == 0 ? NST - 1 : slot - 1);
+            if (s < mine) compute(slot, live_c);
+            slot = slot + 1 == NST ? 0 : slot + 1;
+        }
+    };
+    static_assert(D <= 5, "the chain of waits above");
+    if (TM == 1 || rows > 32) k_loop(std::integral_constant<int, TM>{});
+    else k_loop(std::integral_constant<int, 1>{});
+
+    // ---- the K parts meet: every wavefront leaves its partial tiles in LDS and finishes registers
+    // [QN kp, QN kp + QN) of each tile of its channels
+    constexpr int QN = 16 / WK;
+    float cs[2], bias[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        cs[t] = __shfl(cs_lane, 32 * t + (lane & 31));
+        bias[t] = __shfl(bias_lane, 32 * t + (lane & 31));
+    }
+    __syncthreads();                                    // every wavefront is done with the ring
+    TileRows<32 * TM> &tile_rows = *reinterpret_cast<TileRows<32 * TM> *>(lds + S::kRows);
+    entry.put(tile_rows);
+    if constexpr (WK == 1) __syncthreads();
+    if constexpr (WK > 1) {
+        float *red = reinterpret_cast<float *>(lds);    // [wave][m][t][16][64]
+#pragma unroll
+        for (int m = 0; m < TM; ++m)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) red[((wave * TM + m) * 2 + t) * 1024 + i * 64 + lane] = acc[m][t][i];
+        __syncthreads();
+        float v[TM][2][QN];
+#pragma unroll
+        for (int m = 0; m < TM; ++m)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int q = 0; q < QN; ++q) {
+                    const float *src = red + ((wc * TM + m) * 2 + t) * 1024 + (kp * QN + q) * 64 + lane;
+                    float sum = src[0];
+#pragma unroll
+                    for (int w = 1; w < WK; ++w) sum += src[(size_t)w * WC * TM * 2 * 1024];
+                    v[m][t][q] = sum;
+                }
+        __syncthreads();                                // the partial tiles have been read
+        if (tile_ok) finish_tile<TM, QN, 32 * TM>(p, v, tile_rows, cs, bias, rows, 8 * (QN / 4) * kp, ntile0 * 32, lds + wave * kPatchBytes<QN>);
+    } else {
+        if (tile_ok) finish_tile<TM, 16, 32 * TM>(p, acc, tile_rows, cs, bias, rows, 0, ntile0 * 32, lds + wave * kPatchBytes<16>);
+    }
+}
+
+template <int BITS, int SMODE, int BM, int WC, int WK>
+static void launch_ring_shape(const GemmArgs &p, dim3 grid, hipStream_t s)
+{
+    using S = RingShape<BITS, SMODE, BM, WC, WK>;
+    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(&grouped_gemm_ring_kernel<BITS, SMODE, BM, WC, WK>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, S::kLds);
+    (void)raised;
+    hipLaunchKernelGGL((grouped_gemm_ring_kernel<BITS, SMODE, BM, WC, WK>), grid, dim3(64 * WC * WK), S::kLds, s, p);
+}
+
+template <int BITS, int SMODE>
+static void launch_ring_variants(const GemmArgs &p, int bm, dim3 grid, hipStream_t s)
+{
+    if (bm == 16) launch_ring_shape<BITS, SMODE, 16, 2, 2>(p, grid, s);
+    else if (bm == 32) launch_ring_shape<BITS, SMODE, 32, 2, 2>(p, grid, s);
+    else launch_ring_shape<BITS, SMODE, 64, 2, 2>(p, grid, s);
+}
+
+}  // namespace moe

@@ -4,10 +4,34 @@
 
 namespace moe {
 
+// Rows per block of the kernel with the LDS ring, or 0 where register-fed tiles do as well or better (steps of a layer, register-fed
+// tiles against the ring).  Few rows per expert: the launch streams weights, and what counts is how much of them is in flight.
+// 16-row blocks up to ten rows per expert on average: 64 tokens, two of 32 experts, group scales: 1024 x 4096 84 and 60 us, 2048 x 8192
+// 188 and 141; 64 experts of 4096 x 16384 816 and 797; 500 tokens on 128 experts of 1024 x 4096 8-bit 260 and 228.  With 4-bit
+// weights and more than 512 rows a busy expert's 16-row tiles unpack its weights too often (500 tokens, skewed, 128 experts of
+// 2048 x 8192: 443 and 488), so these take 32-row blocks.
+// 32-row blocks while the tiles alone do not fill the chip two to four times (240 tokens on 32 experts of 2048 x 8192: 201 and 154;
+// 1900 tokens on 128 of them: 578 and 671).  Beyond: only where 64-row tiles leave compute units without a block (fc2 of 500
+// tokens on 32 experts of 1024 x 4096, 126 tiles: 41 and 28 us; with 264 tiles of 2048 x 8192 98 and 103).
+static int ring_rows(const GemmArgs &p, int bits, int mean)
+{
+    const long experts = p.E < p.R ? p.E : p.R, ncol = (p.N + 255) / 256;
+    if (mean <= 10 && (bits == 8 || p.R <= 512)) return 16;
+    if (mean <= 32) return ((long)p.R / 32 + experts / 2) * ncol <= (mean <= 16 ? 1024 : 512) ? 32 : 0;
+    return ((long)p.R / 64 + experts / 2) * ncol <= 224 ? 64 : 0;
+}
+
 int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
 {
     // row-tile height from the mean rows per expert (the offsets themselves stay on the device)
     const int mean = (p.R + p.E - 1) / p.E;
+    if (const int bm = ring_rows(p, bits, mean)) {
+        const long slots = (long)p.R / bm + (p.E < p.R ? p.E : p.R);
+        const long wgs = (slots * ((p.N + 127) / 128) + kXcds - 1) / kXcds * kXcds;      // upper bound of the work items, whole rounds of XCDs
+        if (wgs > 0x7fffffffL) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq: %ld workgroups exceed one launch", wgs);
+        (bits == 4 ? launch_ring_4 : launch_ring_8)(p, smode, bm, dim3((unsigned)wgs), s);
+        return check_launch("moe_grouped_ffn_wq (gemm)");
+    }
     // 64-row tiles also for taller experts where a third block per CU pays more than halving the
     // dequantisation does: short K loops (the prologue and epilogue of a block then overlap the loops of
     // two others, not of one), and 8-bit weights up to 256 rows per expert (their 128-row tile has

@@ -54,7 +54,9 @@ class MoEExpertLayer:
         # the GEMMs instead of as copies of their own
         self.routed = bool(fuse_routing) and B.moe_grouped_ffn_wq_routed_supported(R, E, T, d, F, bits, group_size, act_dtype)
         # decode-sized batches: the permutation is rebuilt inside fc1 (no permute launch, no x_perm copy)
-        self.gated = B.moe_grouped_ffn_wq_gated_supported(T, k, E, d, F, bits, group_size, act_dtype) if fuse_routing else 0
+        self.gated = 0
+        if fuse_routing and B.moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype):
+            self.gated = B.moe_grouped_ffn_wq_gated_supported(T, k, E, d, F, bits, group_size, act_dtype)
 
     # -- offline: quantise one expert matrix from its fp32 master (which = 1 | 2) ------------
     def load_expert(self, which: int, e: int, w_fp32, q_canon_out=None):
