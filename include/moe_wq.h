@@ -221,6 +221,17 @@ int moe_grouped_ffn_wq_routed(const void *x, int act_dtype, const int32_t *perm_
                               int out_dtype, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * The same call for every size and for bf16 rows as well (k must divide R: row r of the sorted order is token
+ * perm_src[r] / k).  Both GEMMs run in row tiles whatever the sizes; bf16 tokens are converted once, not once per expert.
+ */
+int moe_grouped_ffn_wq_indexed(const void *x, int act_dtype, const int32_t *perm_src, int k,
+                               const float *expert_scale, const int32_t *expert_offsets, int R, int E,
+                               int max_rows_per_expert, int d, int F, int bits, int group_size,
+                               int activation, const void *w1_packed, const void *s1, const void *b1,
+                               const void *w2_packed, const void *s2, const void *b2, void *out,
+                               int out_dtype, void *workspace, size_t workspace_bytes, void *stream);
+
+/*
  * moe_permute and moe_grouped_ffn_wq in one call, for decode-sized batches (Sec. 3.3 steps 2 and
  * 3; the stable sort by expert is rebuilt inside the first GEMM).  fc1's blocks count the
  * assignments of their expert and of the experts before it from expert_idx, fetch their rows

@@ -21,7 +21,7 @@ _DT = {torch.float16: MOE_F16, torch.bfloat16: MOE_BF16, torch.float32: MOE_F32}
 EXPORTS = ["moe_last_error", "moe_last_ffn_kernels", "moe_device_info", "moe_abi_version", "moe_quantize_experts", "moe_gate_topk",
            "moe_permute_workspace_bytes", "moe_permute", "moe_grouped_ffn_wq_workspace_bytes",
            "moe_grouped_ffn_wq", "moe_combine", "moe_pack_fp16_experts", "moe_grouped_gemm_wq",
-           "moe_grouped_ffn_wq_routed_supported", "moe_grouped_ffn_wq_routed",
+           "moe_grouped_ffn_wq_routed_supported", "moe_grouped_ffn_wq_routed", "moe_grouped_ffn_wq_indexed",
            "moe_grouped_ffn_wq_gated_supported", "moe_grouped_ffn_wq_gated_pays", "moe_grouped_ffn_wq_gated",
            "moe_grouped_ffn_wq_noalloc_max_bytes", "moe_grouped_ffn_wq_noalloc"]
 
@@ -72,6 +72,9 @@ def load():
     lib.moe_grouped_ffn_wq_routed_supported.argtypes = [i, i, i, i, i, i, i, i]
     lib.moe_grouped_ffn_wq_routed.restype = i
     lib.moe_grouped_ffn_wq_routed.argtypes = [vp, i, vp, i, vp, vp, i, i, i, i, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, i,
+                                              vp, sz, vp]
+    lib.moe_grouped_ffn_wq_indexed.restype = i
+    lib.moe_grouped_ffn_wq_indexed.argtypes = [vp, i, vp, i, vp, vp, i, i, i, i, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, i,
                                               vp, sz, vp]
     lib.moe_grouped_ffn_wq_gated_supported.restype = i
     lib.moe_grouped_ffn_wq_gated_supported.argtypes = [i, i, i, i, i, i, i, i]

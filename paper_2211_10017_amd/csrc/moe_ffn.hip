@@ -14,32 +14,51 @@ namespace moe {
 // FP16 rows (straight from memory into LDS) and multiplies its output rows by pow.y = 2^p.  A value keeps its 8-bit significand unless it is more than 2^-28 below the row's largest, where FP16
 // runs out of exponent.  `out` may be `in`: a lane reads what it converts before it writes it, and the row's
 // largest magnitude is known before the first write.
+//
+// LANES lanes share a row (a wavefront, or a block of 256 for long rows) and hold it in registers, NV 16-byte vectors each,
+// between the search for its largest magnitude and the conversion: a row is read once.  (Read twice, with a wavefront per
+// row, the rows in flight on the chip were many times its L2s and the second read went to memory again: h of 16384 rows of
+// 16384, 262 us against 163.)  NV = 0: rows of any length, read twice.
+template <int LANES, int NV>
 __global__ __launch_bounds__(256) void rows_to_f16_kernel(const uint16_t *in, uint16_t *out, int R, int K, float2 *__restrict__ row_pow)
 {
-    const int lane = threadIdx.x & 63;
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= R) return;
+    __shared__ uint32_t s_max[4];
+    const int i0 = threadIdx.x % LANES;
+    const int r = blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
+    if (r >= R) return;                            // (with a row per block: the whole block)
     const uint4 *row = reinterpret_cast<const uint4 *>(in + (size_t)r * K);
     uint4 *dst = reinterpret_cast<uint4 *>(out + (size_t)r * K);
     uint32_t amax = 0;
-    for (int v = lane; v < K / 8; v += 64) {
-        const uint4 q = row[v];
+    auto largest = [&](const uint4 q) {
         const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             amax = max(amax, w[i] & 0x7fffu);
             amax = max(amax, (w[i] >> 16) & 0x7fffu);
         }
+    };
+    uint4 v[NV ? NV : 1];
+    if constexpr (NV > 0) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) v[j] = i0 + j * LANES < K / 8 ? row[i0 + j * LANES] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NV; ++j) largest(v[j]);
+    } else {
+        for (int i = i0; i < K / 8; i += LANES) largest(row[i]);
     }
     for (int off = 32; off > 0; off >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, off));
+    if constexpr (LANES > 64) {
+        if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = amax;
+        __syncthreads();
+        amax = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
+    }
     int ex = (int)(amax >> 7);                     // biased exponent of the largest magnitude
     if (ex == 255) ex = 141;                       // inf/nan rows: factor 1 (the result is nan anyway)
     int fe = 268 - ex;                             // biased exponent of 2^(14 - (ex - 127))
     fe = min(max(fe, 1), 253);
     const float down = __uint_as_float((uint32_t)fe << 23);
-    if (lane == 0) row_pow[r] = make_float2(down, __uint_as_float((uint32_t)(254 - fe) << 23));
-    for (int v = lane; v < K / 8; v += 64) {
-        const uint4 q = row[v];
+    if (i0 == 0) row_pow[r] = make_float2(down, __uint_as_float((uint32_t)(254 - fe) << 23));
+    auto convert = [&](const uint4 q) {
         const uint32_t w[4] = {q.x, q.y, q.z, q.w};
         uint32_t o[4];
 #pragma unroll
@@ -47,8 +66,24 @@ __global__ __launch_bounds__(256) void rows_to_f16_kernel(const uint16_t *in, ui
             const half2_t h = {(_Float16)(__uint_as_float(w[i] << 16) * down), (_Float16)(__uint_as_float(w[i] & 0xffff0000u) * down)};
             o[i] = h2_bits(h);
         }
-        dst[v] = make_uint4(o[0], o[1], o[2], o[3]);
+        return make_uint4(o[0], o[1], o[2], o[3]);
+    };
+    if constexpr (NV > 0) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            if (i0 + j * LANES < K / 8) dst[i0 + j * LANES] = convert(v[j]);
+    } else {
+        for (int i = i0; i < K / 8; i += LANES) dst[i] = convert(row[i]);
     }
+}
+
+static int rows_to_f16(const uint16_t *in, uint16_t *out, int R, int K, float2 *row_pow, hipStream_t s)
+{
+    if (K <= 64 * 8 * 2) hipLaunchKernelGGL((rows_to_f16_kernel<64, 2>), dim3((R + 3) / 4), dim3(256), 0, s, in, out, R, K, row_pow);
+    else if (K <= 64 * 8 * 8) hipLaunchKernelGGL((rows_to_f16_kernel<64, 8>), dim3((R + 3) / 4), dim3(256), 0, s, in, out, R, K, row_pow);
+    else if (K <= 256 * 8 * 8) hipLaunchKernelGGL((rows_to_f16_kernel<256, 8>), dim3(R), dim3(256), 0, s, in, out, R, K, row_pow);
+    else hipLaunchKernelGGL((rows_to_f16_kernel<64, 0>), dim3((R + 3) / 4), dim3(256), 0, s, in, out, R, K, row_pow);
+    return check_launch("moe_grouped_ffn_wq (bf16 rows to scaled FP16)");
 }
 
 struct FfnWorkspace {
@@ -110,14 +145,15 @@ static GemmKernel choose_kernel(int R, int E, int max_rows, int K, int N, int bi
 
 // bf: the rows were bf16 (they come in converted to scaled FP16, with their factors in g.row_pow, which only the
 // tiled kernel applies)
-static int run_gemm(moe::GemmArgs g, int bits, int smode, bool bf, int max_rows, hipStream_t s)
+// tiles_only: rows go through the routing index, which only the row tiles do
+static int run_gemm(moe::GemmArgs g, int bits, int smode, bool bf, bool tiles_only, int max_rows, hipStream_t s)
 {
     using namespace moe;
     GemmKernel kernel = choose_kernel(g.R, g.E, max_rows, g.K, g.N, bits, smode, bf);
     // Without the permutation inside the launch the streaming kernels pay for at most one row per expert on average only: every
     // further row group of an expert streams its weights again (64 tokens on 16 experts of 4096 x 16384: 4-bit 541 us per step
     // against 230 in the row tiles, 8-bit 916 against 360).
-    if (!g.gate_idx && !g.out_add && g.R > g.E) kernel = GEMM_TILED;
+    if (!g.gate_idx && !g.out_add && (g.R > g.E || tiles_only)) kernel = GEMM_TILED;
     note_kernel(kernel == GEMM_STREAM_UNROLLED ? "stream_unrolled_kernel" : kernel == GEMM_STREAM_LOOP ? "stream_gemm_kernel" : "grouped_gemm_kernel");
     if (kernel == GEMM_STREAM_UNROLLED) return launch_stream_unrolled(g, bits, max_rows, s);
     if (g.gate_idx || g.out_add) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_gated: K=%d does not run in the straight-line kernel with these sizes", g.K);
@@ -209,14 +245,14 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     }
     if (bf) {           // bf16 rows: converted to power-of-two scaled FP16 rows first, then the GEMM of FP16 rows
         uint16_t *x16 = (uint16_t *)(wsb + ws.x16_off);
-        hipLaunchKernelGGL(rows_to_f16_kernel, dim3((R + 3) / 4), dim3(256), 0, s, (const uint16_t *)x_perm, x16, R, d, pow_x);
-        int rc = check_launch("moe_grouped_ffn_wq (x to scaled FP16)");
+        // (through the routing index: every token's row once, R / k of them)
+        int rc = rows_to_f16((const uint16_t *)x_perm, x16, perm_src ? R / k : R, d, pow_x, s);
         if (rc) return rc;
         g1.a = x16;
     }
     // (groups of 128: exact codes, group sums folded in fp32; other group sizes: the two-term form)
     const int smode1 = !grouped ? SCALE_CHANNEL : !bf ? SCALE_GROUP : group_size == 128 ? SCALE_GROUP_ACC : SCALE_GROUP_SPLIT;
-    int rc = run_gemm(g1, bits, smode1, bf, max_rows, s);
+    int rc = run_gemm(g1, bits, smode1, bf, perm_src != nullptr, max_rows, s);
     if (rc) return rc;
 
     // fc2: y = h @ deq(W2) + b2
@@ -233,11 +269,10 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
         g2.out_dst = perm_src; g2.out_scale = expert_scale;
     }
     if (bf) {           // h, which fc1 rounded to bf16 (A13), in place
-        hipLaunchKernelGGL(rows_to_f16_kernel, dim3((R + 3) / 4), dim3(256), 0, s, (const uint16_t *)h, (uint16_t *)h, R, F, pow_h);
-        rc = check_launch("moe_grouped_ffn_wq (h to scaled FP16)");
+        rc = rows_to_f16((const uint16_t *)h, (uint16_t *)h, R, F, pow_h, s);
         if (rc) return rc;
     }
-    return run_gemm(g2, bits, grouped ? SCALE_GROUP : SCALE_CHANNEL, bf, max_rows, s);
+    return run_gemm(g2, bits, grouped ? SCALE_GROUP : SCALE_CHANNEL, bf, perm_src != nullptr, max_rows, s);
 }
 
 extern "C" int moe_grouped_ffn_wq(const void *x_perm, int act_dtype, const int32_t *expert_offsets, int R,
@@ -334,6 +369,24 @@ extern "C" int moe_grouped_ffn_wq_routed(const void *x, int act_dtype, const int
     if (!moe_grouped_ffn_wq_routed_supported(R, E, max_rows_per_expert, d, F, bits, group_size, act_dtype))
         return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_routed: these sizes run (partly) in the streaming kernels or in bf16, "
                                          "which take permuted rows only: use moe_permute + moe_grouped_ffn_wq + moe_combine");
+    return ffn_impl(x, act_dtype, expert_offsets, R, E, max_rows_per_expert, d, F, bits, group_size, activation, w1_packed, s1, b1,
+                    w2_packed, s2, b2, out, out_dtype, workspace, workspace_bytes, stream, perm_src, k, expert_scale);
+}
+
+// The routed call for every size and both row types: both GEMMs run in row tiles.
+extern "C" int moe_grouped_ffn_wq_indexed(const void *x, int act_dtype, const int32_t *perm_src, int k,
+                                          const float *expert_scale, const int32_t *expert_offsets, int R,
+                                          int E, int max_rows_per_expert, int d, int F, int bits,
+                                          int group_size, int activation, const void *w1_packed, const void *s1,
+                                          const void *b1, const void *w2_packed, const void *s2,
+                                          const void *b2, void *out, int out_dtype, void *workspace,
+                                          size_t workspace_bytes, void *stream)
+{
+    using namespace moe;
+    if (!perm_src) return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_indexed: perm_src must not be NULL");
+    if (k < 1 || k > 2 || R % k) return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_indexed: k must be 1 or 2 and divide R (k=%d, R=%d)", k, R);
+    if (expert_scale && k != 1)
+        return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_indexed: the fused un-permute needs k = 1 (one expert per token)");
     return ffn_impl(x, act_dtype, expert_offsets, R, E, max_rows_per_expert, d, F, bits, group_size, activation, w1_packed, s1, b1,
                     w2_packed, s2, b2, out, out_dtype, workspace, workspace_bytes, stream, perm_src, k, expert_scale);
 }

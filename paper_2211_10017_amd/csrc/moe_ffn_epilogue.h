@@ -34,7 +34,7 @@ struct RowEntry {
     {
         if ((int)threadIdx.x < BM) {
             const int r = row0 + min((int)threadIdx.x, rows - 1);
-            if (p.row_pow) pow = p.row_pow[r].y;
+            if (p.row_pow) pow = p.row_pow[p.a_src ? p.a_src[r] / p.a_div : r].y;     // (a row of A's: factors go with what was converted)
             dst = r;
             if (p.out_dst) {
                 dst = p.out_dst[r];

@@ -53,6 +53,10 @@ class MoEExpertLayer:
         # large batches: the row gather (and for k = 1 the un-permute and gate scale) run inside
         # the GEMMs instead of as copies of their own
         self.routed = bool(fuse_routing) and B.moe_grouped_ffn_wq_routed_supported(R, E, T, d, F, bits, group_size, act_dtype)
+        # ... and so for other sizes that run in row tiles, and for bf16 rows
+        self._ffn_call = "moe_grouped_ffn_wq_routed"
+        if not self.routed and fuse_routing and R > 0 and (act_dtype == torch.bfloat16 or R > E):
+            self.routed, self._ffn_call = True, "moe_grouped_ffn_wq_indexed"
         # decode-sized batches: the permutation is rebuilt inside fc1 (no permute launch, no x_perm copy)
         self.gated = 0
         if fuse_routing and B.moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype):
@@ -166,11 +170,11 @@ class MoEExpertLayer:
             permute = (lib.moe_permute, (p(self.expert_idx), None, dt, self.T, self.k, self.E, self.d, None,
                                          p(self.perm_src), p(self.inv_perm), p(self.expert_offsets), p(self.ws_permute),
                                          self.ws_permute.numel(), st), "moe_permute")
-            ffn = (lib.moe_grouped_ffn_wq_routed,
+            ffn = (getattr(lib, self._ffn_call),
                    (p(x), dt, p(self.perm_src), self.k, p(self.expert_scale) if scatter else None, p(self.expert_offsets),
                     self.R, self.E, self.T, self.d, self.F, self.bits, self.group_size, self.activation, p(self.w1_packed), p(self.s1),
                     p(self.b1), p(self.w2_packed), p(self.s2), p(self.b2), p(self.out) if scatter else p(self.y_perm),
-                    odt if scatter else ydt, p(self.ws_ffn), self.ws_ffn.numel(), st), "moe_grouped_ffn_wq_routed")
+                    odt if scatter else ydt, p(self.ws_ffn), self.ws_ffn.numel(), st), self._ffn_call)
             return [gate, permute, ffn] if scatter else [gate, permute, ffn, combine]
         permute = (lib.moe_permute, (p(self.expert_idx), p(x), dt, self.T, self.k, self.E, self.d, p(self.x_perm),
                                      p(self.perm_src), p(self.inv_perm), p(self.expert_offsets), p(self.ws_permute),

@@ -1,0 +1,67 @@
+"""Rows fetched through the routing index for every size and row type: the same bits as permuted copies give.  And the
+conversion of bf16 rows at the lengths where its form changes."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import MAX_ABS_TOL, REL_L2_TOL, error_metrics, to_dev
+from paper_2211_10017_amd import MoEExpertLayer
+from paper_2211_10017_amd import binding as B
+from test_gpu_ring import _case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,k,E,d,F,bits,g,act", [
+    (1, 2, 4, 1024, 512, 4, 0, torch.bfloat16), (64, 2, 32, 1024, 1024, 4, 0, torch.bfloat16), (40, 1, 8, 512, 768, 8, 0, torch.bfloat16),
+    (150, 2, 16, 768, 1536, 4, 128, torch.float16), (200, 2, 8, 1024, 2048, 8, 0, torch.float16), (700, 1, 4, 256, 4224, 4, 64, torch.bfloat16),
+    (2000, 2, 8, 192, 2048, 8, 0, torch.bfloat16), (3000, 2, 8, 128, 256, 4, 0, torch.bfloat16)])      # the last: index in two launches
+@pytest.mark.parametrize("prune", [False, True])
+def test_indexed_layer_equals_permuted_copies(T, k, E, d, F, bits, g, act, prune):
+    print(f"indexed T={T} k={k} E={E} d={d} F={F} bits={bits} g={g} {act} pruned={prune}", flush=True)
+    rng = np.random.default_rng(T + E + bits)
+    a = MoEExpertLayer(T, d, F, E, k, bits, g, act_dtype=act, y_dtype=torch.float32)
+    assert a.routed
+    wg = to_dev((rng.standard_normal((d, E)) * 0.05).astype(np.float32), act)
+    a.wg.copy_(wg)
+    for e in range(E):
+        a.load_expert(1, e, to_dev((rng.standard_normal((d, F)) * 0.05).astype(np.float32), torch.float32))
+        a.load_expert(2, e, to_dev((rng.standard_normal((F, d)) * 0.05).astype(np.float32), torch.float32))
+    b = MoEExpertLayer(T, d, F, E, k, bits, g, act_dtype=act, y_dtype=torch.float32, fuse_routing=False)
+    b.share_weights_from(a)
+    b.wg.copy_(wg)
+    span = 20 if act == torch.bfloat16 else 6           # rows of very different sizes; fp16 must hold 4 * 2^span and the h of such a row
+    x = to_dev((rng.standard_normal((T, d)) * 2.0 ** rng.integers(-span, span, (T, 1))).astype(np.float32), act)
+    fin = to_dev((rng.random(T) < 0.3).astype(np.uint8), torch.uint8) if prune else None
+    out_a, out_b = a.forward(x, fin), b.forward(x, fin)
+    torch.cuda.synchronize()
+    assert torch.equal(a.expert_idx, b.expert_idx) and torch.equal(a.perm_src, b.perm_src)
+    if T * k > E:
+        assert torch.equal(out_a, out_b)
+    else:           # the permuted call streams here when the rows are fp16 only, so both run row tiles
+        assert act == torch.bfloat16 and torch.equal(out_a, out_b)
+
+
+@pytest.mark.parametrize("K", [1024, 1088, 4096, 4160, 16384, 16448])       # two, eight 16-byte vectors per lane; a block per row; read twice
+def test_bf16_rows_of_every_length(K):
+    rows = [3, 6]
+    x, off, w, ((s1, p1), (s2, p2)), E, R = _case(rows, 64, K, 8, 0, "bf16", K)
+    y = B.moe_grouped_ffn_wq(x, to_dev(off, torch.int32), E, 64, K, 8, 0, p1, s1, p2, s2, y_dtype=torch.float32)
+    torch.cuda.synchronize()
+    (q1, o1), (q2, o2) = (oracle.quantize(m, 8, 0) for m in w)
+    want = oracle.grouped_ffn(x.float().cpu().numpy(), off, q1, o1, q2, o2, 0, oracle.BF16)
+    max_abs, rel = error_metrics(y.cpu().numpy(), want)
+    assert max_abs <= MAX_ABS_TOL * max(1.0, float(np.abs(want).max()) / 8) and rel <= REL_L2_TOL
+
+
+def test_indexed_refuses_what_does_not_fit():
+    f = ctypes.c_void_p(0x1000)
+    call = B.load().moe_grouped_ffn_wq_indexed
+    tail = (4, 0, 64, 64, 4, 0, 0, f, f, None, f, f, None, f, 0, f, 1 << 20, None)
+    assert call(f, 0, None, 1, None, f, 8, *tail) == 1          # no index
+    assert call(f, 0, f, 3, None, f, 9, *tail) == 1             # k = 3
+    assert call(f, 0, f, 2, None, f, 9, *tail) == 1             # odd number of rows with two experts per token
+    assert call(f, 0, f, 2, f, f, 8, *tail) == 1                # un-permute with two experts per token
