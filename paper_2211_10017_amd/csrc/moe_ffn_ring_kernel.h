@@ -119,7 +119,16 @@ __global__ __launch_bounds__(64 * WC * WK, 2) void grouped_gemm_ring_kernel(Gemm
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[m][t][i] = 0.0f;
 
-    auto compute = [&](int slot, auto live_c) {
+    float16_t part[ACC ? TM : 1][2];                    // sums of the current group
+    if constexpr (ACC)
+#pragma unroll
+        for (int m = 0; m < TM; ++m)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) part[m][t][i] = 0.0f;
+
+    auto compute = [&](int slot, bool last_of_group, auto live_c) {
         constexpr int LIVE = decltype(live_c)::value;               // row tiles of this block that hold rows
         const uint8_t *st = lds + slot * S::kStage;
         const uint16_t *sa = reinterpret_cast<const uint16_t *>(st + kp * S::kPartA);
@@ -136,7 +145,6 @@ __global__ __launch_bounds__(64 * WC * WK, 2) void grouped_gemm_ring_kernel(Gemm
             if constexpr (GROUPED)
                 sc[t] = *reinterpret_cast<const _Float16 *>(sb + 2 * NW * kFragBytes + (t * 32 + (lane & 31)) * 2);
         }
-        float16_t part[ACC ? TM : 1][2];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             half8_t a[TM];
@@ -157,26 +165,27 @@ __global__ __launch_bounds__(64 * WC * WK, 2) void grouped_gemm_ring_kernel(Gemm
                 for (int m = 0; m < TM; ++m) {
                     if (m >= LIVE) continue;
                     if constexpr (ACC) {
-                        float16_t c = part[m][t];
-                        if (j == 0)
-#pragma unroll
-                            for (int i = 0; i < 16; ++i) c[i] = 0.0f;
-                        part[m][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[m], frag_from(bw), c, 0, 0, 0);
+                        part[m][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[m], frag_from(bw), part[m][t], 0, 0, 0);
                     } else {
                         acc[m][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[m], frag_from(bw), acc[m][t], 0, 0, 0);
                     }
                 }
             }
         }
-        if constexpr (ACC) {                            // exact codes went in: the step's sums are folded with the group's scale in fp32
+        if constexpr (ACC) {        // exact codes went in: at the end of a group (or of this part of K) its sums are folded with the scale in fp32
+            if (last_of_group) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const float sf = (float)sc[t];
+                for (int t = 0; t < 2; ++t) {
+                    const float sf = (float)sc[t];
 #pragma unroll
-                for (int m = 0; m < TM; ++m)
-                    if (m < LIVE)
+                    for (int m = 0; m < TM; ++m)
+                        if (m < LIVE)
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) acc[m][t][i] = fmaf(part[m][t][i], sf, acc[m][t][i]);
+                            for (int i = 0; i < 16; ++i) {
+                                acc[m][t][i] = fmaf(part[m][t][i], sf, acc[m][t][i]);
+                                part[m][t][i] = 0.0f;
+                            }
+                }
             }
         }
     };
@@ -199,7 +208,7 @@ __global__ __launch_bounds__(64 * WC * WK, 2) void grouped_gemm_ring_kernel(Gemm
             else wait_loads<0>();
             __syncthreads();
             if (s + D < per) issue(s + D, slot == 0 ? NST - 1 : slot - 1);
-            if (s < mine) compute(slot, live_c);
+            if (s < mine) compute(slot, s + 1 == mine || (first + s + 1) * 64 % p.g == 0, live_c);
             slot = slot + 1 == NST ? 0 : slot + 1;
         }
     };
