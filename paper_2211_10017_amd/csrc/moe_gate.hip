@@ -138,6 +138,22 @@ __device__ inline void gate_static_for(F &&f)
     }
 }
 
+// Eight 16-bit values per lane, (x0, x1, y0, y1) and (z0, z1, w0, w1): value i of the first four is paired with value i of the
+// last four, and the 4 x 4 matrix of pairs over (row of sixteen lanes r, i) is transposed across the rows: q[s] of row r is then
+// pair r of row s.
+__device__ inline void transpose_quads(uint32_t x, uint32_t y, uint32_t z, uint32_t w, uint32_t (&q)[4])
+{
+    q[0] = __builtin_amdgcn_perm(z, x, 0x05040100u);
+    q[1] = __builtin_amdgcn_perm(z, x, 0x07060302u);
+    q[2] = __builtin_amdgcn_perm(w, y, 0x05040100u);
+    q[3] = __builtin_amdgcn_perm(w, y, 0x07060302u);
+    const auto a = __builtin_amdgcn_permlane16_swap(q[0], q[1], false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(q[2], q[3], false, false);
+    const auto c = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
+    const auto e = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
+    q[0] = c[0]; q[1] = e[0]; q[2] = c[1]; q[3] = e[1];
+}
+
 // The logits on the matrix cores.  v_mfma_f32_16x16x4_f32 adds its four products to the accumulator one after
 // the other, each with the rounding (and the subnormal numbers) of an fp32 fma, so a chain of them over ascending
 // features IS the contract's sequential partial sum, bit for bit, at twice the rate of v_fma_mix_f32 (256 flops
@@ -217,17 +233,7 @@ __global__ __launch_bounds__(256 * S) void gate_mfma_kernel(const uint16_t *__re
     // A lane's 16 bytes hold features 8 kk .. 8 kk + 7 of the group; quad n wants feature 4 n + kk.  Halves i and
     // 4 + i are paired (i = 0 .. 3), and the 4 x 4 matrix of pairs over (kk, i) is transposed across the four rows of
     // sixteen lanes: dword s then holds features 8 s + kk and 8 s + 4 + kk, the operands of quads 2 s and 2 s + 1.
-    auto spread = [&](u32x4 v, uint32_t (&q)[4]) __attribute__((always_inline)) {
-        q[0] = __builtin_amdgcn_perm(v.z, v.x, 0x05040100u);
-        q[1] = __builtin_amdgcn_perm(v.z, v.x, 0x07060302u);
-        q[2] = __builtin_amdgcn_perm(v.w, v.y, 0x05040100u);
-        q[3] = __builtin_amdgcn_perm(v.w, v.y, 0x07060302u);
-        const auto a = __builtin_amdgcn_permlane16_swap(q[0], q[1], false, false);
-        const auto b = __builtin_amdgcn_permlane16_swap(q[2], q[3], false, false);
-        const auto c = __builtin_amdgcn_permlane32_swap(a[0], b[0], false, false);
-        const auto e = __builtin_amdgcn_permlane32_swap(a[1], b[1], false, false);
-        q[0] = c[0]; q[1] = e[0]; q[2] = c[1]; q[3] = e[1];
-    };
+    auto spread = [&](u32x4 v, uint32_t (&q)[4]) __attribute__((always_inline)) { transpose_quads(v.x, v.y, v.z, v.w, q); };
     f4_t acc[TT][NB];
 #pragma unroll
     for (int t = 0; t < TT; ++t)
@@ -301,10 +307,12 @@ __global__ __launch_bounds__(256 * S) void gate_mfma_kernel(const uint16_t *__re
 
 // Few tokens and 33 to 64 experts: the same chains in v_mfma_f32_4x4x1_16b_f32, sixteen 4 x 4 x 1 products that make up
 // 4 tokens x 64 experts x 1 feature.  A block takes four tokens instead of sixteen, so the batch spreads over four times
-// as many compute units at the same rate of the matrix pipe; lane l supplies expert l's weight and token l & 3's feature, and
-// ends up with expert l's logits of the four tokens.  Per feature a wavefront loads one coalesced row of 64 weights straight into
-// the register it is used from (a ring of R octets of features).
-template <bool BF16, int R>
+// as many compute units at the same rate of the matrix pipe.  An octet of features is one 16-byte load of the tokens and two
+// 8-byte loads of the gate weight: lane (j, r) = (lane & 15, lane >> 4) brings experts 4 j .. 4 j + 3 of features r and 4 + r, and
+// the same 4 x 4 transposition that spreads the tokens' features above leaves it with expert 4 j + r of all eight.  (VEC; numbers
+// of experts that are no multiple of four: a lane per expert, one 2-byte load per feature.  One token, 64 experts, caches warm:
+// 8.5 -> 7.2 us at d = 1024, 12.9 -> 10.9 at 2048; several tokens within 2 %.)  A ring of R octets.
+template <bool BF16, int R, bool VEC>
 __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
                                                             const float *__restrict__ bias,
                                                             const uint8_t *__restrict__ finished, int T, int d, int E,
@@ -313,10 +321,12 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
 {
     typedef float f4_t __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     constexpr int NT = 4, ld = 64 + 4;
     __shared__ float part[4 * NT * ld];
     const int lane = threadIdx.x & 63;
     const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int own = VEC ? 4 * (lane & 15) + (lane >> 4) : lane;      // this lane's expert
     const int t0 = blockIdx.x * NT;
     const int nblk = (d + kGateBlk - 1) / kGateBlk;
     const int mine = p < nblk ? (nblk - p + 3) / 4 : 0;
@@ -325,14 +335,20 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
     const int rows = min(NT, T - t0);
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
-    const int x_off = min(lane & 3, rows - 1) * d * 2, w_off = min(lane, E - 1) * 2;
+    const int x_off = min(lane & 3, rows - 1) * d * 2;
+    const int w_off = VEC ? ((lane >> 4) * E + min(4 * (lane & 15), E - 4)) * 2 : min(own, E - 1) * 2;   // (experts clamped where they do not exist)
 
-    struct Octet { u32x4 x; uint16_t w[8]; } ring[R];
+    struct Octet { u32x4 x; uint32_t w[VEC ? 4 : 8]; } ring[R];
     auto load = [&](Octet &c, int q) __attribute__((always_inline)) {
         const int f = feature(q);
         c.x = __builtin_amdgcn_raw_buffer_load_b128(rx, x_off, f * 2, 0);
+        if constexpr (VEC) {
+            const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rw, w_off, f * E * 2, 0), b = __builtin_amdgcn_raw_buffer_load_b64(rw, w_off, (f + 4) * E * 2, 0);
+            c.w[0] = a.x; c.w[1] = a.y; c.w[2] = b.x; c.w[3] = b.y;
+        } else {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) c.w[u] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off, (f + u) * E * 2, 0);
+            for (int u = 0; u < 8; ++u) c.w[u] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off, (f + u) * E * 2, 0);
+        }
     };
     f4_t acc = {0.f, 0.f, 0.f, 0.f};
     struct Ops { float x[8], w[8]; };
@@ -341,7 +357,15 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
         for (int u = 0; u < 8; ++u) {
             const uint32_t v = u < 2 ? c.x.x : u < 4 ? c.x.y : u < 6 ? c.x.z : c.x.w;
             o.x[u] = act_to_float<BF16>((uint16_t)(v >> (16 * (u & 1))));
-            o.w[u] = act_to_float<BF16>(c.w[u]);
+        }
+        if constexpr (VEC) {
+            uint32_t q[4];
+            transpose_quads(c.w[0], c.w[1], c.w[2], c.w[3], q);     // dword u: features u and 4 + u of expert `own`
+#pragma unroll
+            for (int u = 0; u < 8; ++u) o.w[u] = act_to_float<BF16>((uint16_t)(q[u & 3] >> (16 * (u >> 2))));
+        } else {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) o.w[u] = act_to_float<BF16>((uint16_t)c.w[u]);
         }
     };
     auto multiply = [&](const Ops &o) __attribute__((always_inline)) {
@@ -377,9 +401,81 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
         }
     });
 #pragma unroll
-    for (int i = 0; i < NT; ++i) part[(p * NT + i) * ld + lane] = acc[i];
+    for (int i = 0; i < NT; ++i) part[(p * NT + i) * ld + own] = acc[i];
     __syncthreads();
     finish_tokens<1, 4>(part, NT, ld, t0, p, 4, bias, finished, T, E, k, renorm, expert_idx, expert_scale);
+}
+
+// Few tokens and 65 to 128 experts: two experts per lane and the partial sums as plain fp32 fused multiply-adds.  Up to
+// a token or two per compute unit the matrix instructions above work on rows and experts of one block alone, sixteen or four
+// tokens by all experts, and a compute unit's matrix pipe is the bound; here a block takes TB tokens, each feature costs a
+// wavefront 2 TB fused multiply-adds and one 4-byte load (a whole row of the gate weight), and R octets of features are in flight.
+// (T = 64, 128 experts, caches warm / cold: d = 1024 9.7 / 14.2 us against 14.8 / 18.2 on the matrix cores, d = 2048 15.6 / 22.3
+// against 23.7 / 27.4.)
+template <bool BF16, int TB, int R>
+__global__ __launch_bounds__(256) void gate_lanes_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
+                                                         const float *__restrict__ bias,
+                                                         const uint8_t *__restrict__ finished, int T, int d, int E,
+                                                         int k, int renorm, int32_t *__restrict__ expert_idx,
+                                                         float *__restrict__ expert_scale)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int NT = 4, ld = 128 + 4;                 // (finish_tokens takes four tokens; the ones past TB are not stored)
+    __shared__ float part[4 * NT * ld];
+    const int lane = threadIdx.x & 63;
+    const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = blockIdx.x * TB;
+    const int nblk = (d + kGateBlk - 1) / kGateBlk;
+    const int mine = p < nblk ? (nblk - p + 3) / 4 : 0;
+    const int nq = mine * 16 - (mine && (nblk - 1) % 4 == p ? (nblk * kGateBlk - d) / 8 : 0);     // octets of this partial sum
+    auto feature = [&](int q) { return min((p + 4 * (q >> 4)) * kGateBlk + (q & 15) * 8, d - 8); };   // clamped into the row
+    const int rows = min(TB, T - t0);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
+    const int w_off = min(2 * lane, E - 2) * 2;         // experts 2 lane, 2 lane + 1 (clamped where they do not exist)
+
+    struct Octet { u32x4 x[TB]; uint32_t w[8]; } ring[R];
+    auto load = [&](Octet &c, int q) __attribute__((always_inline)) {
+        const int f = feature(q);
+#pragma unroll
+        for (int b = 0; b < TB; ++b) c.x[b] = __builtin_amdgcn_raw_buffer_load_b128(rx, min(b, rows - 1) * d * 2, f * 2, 0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c.w[u] = __builtin_amdgcn_raw_buffer_load_b32(rw, w_off, (f + u) * E * 2, 0);
+    };
+    float acc[TB][2];
+#pragma unroll
+    for (int b = 0; b < TB; ++b) acc[b][0] = acc[b][1] = 0.0f;
+    auto multiply = [&](const Octet &c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int b = 0; b < TB; ++b) {
+                const float xf = act_to_float<BF16>((uint16_t)(c.x[b][u >> 1] >> (16 * (u & 1))));
+                acc[b][0] = fmaf(xf, act_to_float<BF16>((uint16_t)c.w[u]), acc[b][0]);
+                acc[b][1] = fmaf(xf, act_to_float<BF16>((uint16_t)(c.w[u] >> 16)), acc[b][1]);
+            }
+    };
+    gate_static_for<0, R>([&](auto o) { load(ring[decltype(o)::value], decltype(o)::value); });
+    int q0 = 0;
+    for (; q0 + R <= nq; q0 += R) {
+        gate_static_for<0, R>([&](auto oc) {
+            constexpr int o = decltype(oc)::value;
+            const Octet c = ring[o];
+            load(ring[o], q0 + o + R);                  // (past the end: in-bounds loads that are not used)
+            multiply(c);
+        });
+    }
+    gate_static_for<0, R - 1>([&](auto oc) {
+        constexpr int o = decltype(oc)::value;
+        if (q0 + o < nq) multiply(ring[o]);
+    });
+#pragma unroll
+    for (int b = 0; b < TB; ++b) {
+        part[(p * NT + b) * ld + 2 * lane] = acc[b][0];
+        part[(p * NT + b) * ld + 2 * lane + 1] = acc[b][1];
+    }
+    __syncthreads();
+    finish_tokens<2, 4>(part, NT, ld, t0, p, 4, bias, finished, min(T, t0 + TB), E, k, renorm, expert_idx, expert_scale);
 }
 
 template <bool BF16, int NB, int S, int TT, int R, bool VEC>
@@ -401,8 +497,18 @@ static void launch_gate(const uint16_t *x, const uint16_t *wg, const float *bias
     // 33 to 64 experts and up to four tokens per compute unit: four-token blocks.  (64 experts, T = 64: 10.0 against 12.7 us
     // for sixteen-token blocks at d = 1024, 25.8 against 28.0 us at d = 4096; T = 2048: 17.5 against 11.8 us.  Beyond 64
     // experts its one-row loads of the gate weight are the bound and it loses everywhere; up to 32 it idles half its lanes.)
+    // 33 to 64 experts and up to four tokens per compute unit: four-token blocks.  (64 experts, T = 64: 10.0 against 12.7 us
+    // for sixteen-token blocks at d = 1024, 25.8 against 28.0 us at d = 4096; T = 2048: 17.5 against 11.8 us.)
     if (E > 32 && E <= 64 && T <= 1024) {
-        hipLaunchKernelGGL((gate_quad_kernel<BF16, 8>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        if (E % 4) hipLaunchKernelGGL((gate_quad_kernel<BF16, 8, false>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        else hipLaunchKernelGGL((gate_quad_kernel<BF16, 8, true>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        return;
+    }
+    // 65 to 128 experts, up to two tokens per compute unit: a block per token, then per two (T = 500, d = 1024, caches warm: 13.8 us
+    // with one, 11.5 with two, 14.9 on the matrix cores)
+    if (E > 64 && E <= 128 && E % 2 == 0 && T <= 512) {
+        if (T <= 256) hipLaunchKernelGGL((gate_lanes_kernel<BF16, 1, 4>), dim3(T), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        else hipLaunchKernelGGL((gate_lanes_kernel<BF16, 2, 4>), dim3((T + 1) / 2), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
         return;
     }
     // Two row tiles per wavefront (one load and conversion of the gate weight for 32 tokens) once that still gives every
