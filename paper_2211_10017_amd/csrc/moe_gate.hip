@@ -4,7 +4,8 @@
 // fused multiply-adds, so the contract's sequential partial sums (128-element blocks of the feature axis dealt round-robin to
 // four sums) run on the matrix cores bit for bit: a wavefront owns one of the four partial sums for a tile of tokens and
 // experts, the four meet in LDS, and sixteen lanes finish a token.  Two tilings: gate_mfma_kernel (16 tokens x 16 experts
-// per instruction) and gate_quad_kernel (4 tokens x 64 experts).  T = 8192, d = 4096, 64 experts: 196 -> 48 us (bf16 208 ->
+// per instruction) and gate_quad_kernel (4 tokens x 64 experts); few tokens by more than 64 experts take the vector ALU
+// (gate_lanes_kernel).  T = 8192, d = 4096, 64 experts: 196 -> 48 us (bf16 208 ->
 // 47), T = 4096, d = 2048, 128 experts: 76 -> 28.6 us, T = 16384, d = 1024, 64 experts: 55 -> 32 us against multiply-adds in
 // the vector ALU with a lane per expert or per token; T = 64, d = 1024, 32 experts: 13 -> 9 us with cold caches.
 #include <math.h>
@@ -26,15 +27,21 @@ __device__ inline float act_to_float(uint16_t v)
     return __half2float(h);
 }
 
-// Value of the partner lane of butterfly step `off` within a row of sixteen lanes: quad permutes for 1 and 2, the half-row and
-// row mirrors for 4 and 8 (the same partner sets once the value is uniform over 4 resp. 8 lanes, which the earlier
-// steps have made it), all in the VALU's data-parallel primitives.  Used in ascending order of `off` by reductions
-// whose operation is commutative.
+// Value of the partner lane of butterfly step `off`: quad permutes for 1 and 2, the half-row and row mirrors for 4 and 8 (the same
+// partner sets once the value is uniform over 4 resp. 8 lanes, which the earlier steps have made it), all in the VALU's
+// data-parallel primitives, the steps across rows of sixteen lanes and halves of 32 the row and half swaps.  Used in ascending
+// order of `off` by reductions whose operation is commutative.
 template <int OFF, typename V>
 __device__ inline V butterfly_partner(V v)
 {
-    constexpr int CTRL = OFF == 1 ? 0xB1 : OFF == 2 ? 0x4E : OFF == 4 ? 0x141 : 0x140;    // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror, row_mirror
-    return __builtin_bit_cast(V, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+    const uint32_t b = __builtin_bit_cast(uint32_t, v);
+    if constexpr (OFF >= 16) {      // (a swap leaves the lower rows' resp. half's values in [0] of both sides and the upper ones' in [1])
+        const auto sw = OFF == 16 ? __builtin_amdgcn_permlane16_swap(b, b, false, false) : __builtin_amdgcn_permlane32_swap(b, b, false, false);
+        return __builtin_bit_cast(V, (threadIdx.x & OFF) ? sw[0] : sw[1]);
+    } else {
+        constexpr int CTRL = OFF == 1 ? 0xB1 : OFF == 2 ? 0x4E : OFF == 4 ? 0x141 : 0x140;    // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror, row_mirror
+        return __builtin_bit_cast(V, __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, false));
+    }
 }
 
 // The outputs of one token: its k chosen experts (logits selv, descending) and their gate probabilities, den = the sum of
@@ -64,24 +71,26 @@ __device__ inline void store_choice(int t, int T, int E, int k, int renorm, cons
     }
 }
 
-// Logits, top-k, softmax and the stores of the NT tokens of a block (a multiple of four) from the four partial sums in LDS,
-// part[p][token][ld].  Sixteen lanes finish a token, four tokens per wavefront at a time: lane (j, kk) of a wavefront holds
-// the logits of NB neighbouring experts (of each of S slices of 16 NB experts) of token kk, so a reduction is a few
-// comparisons in the lane and four data-parallel steps within the row of sixteen lanes.
-template <int S, int NB>
+// Logits, top-k, softmax and the stores of the NT tokens of a block (a multiple of 64 / LANES) from the four partial sums in LDS,
+// part[p][token][ld].  LANES lanes finish a token, 64 / LANES tokens per wavefront at a time: lane (j, kk) of a wavefront holds
+// the logits of NB neighbouring experts (of each of S slices of LANES NB experts) of token kk, so a reduction is a few
+// comparisons in the lane and four data-parallel steps within the row of sixteen lanes (six with a wavefront per token, which
+// blocks of few tokens and many experts take: a lane then has four logits instead of sixteen).
+template <int S, int NB, int LANES = 16>
 __device__ inline void finish_tokens(const float *part, int NT, int ld, int t0, int wave, int nwave,
                                      const float *__restrict__ bias, const uint8_t *__restrict__ finished, int T, int E,
                                      int k, int renorm, int32_t *__restrict__ expert_idx, float *__restrict__ expert_scale)
 {
-    const int j = threadIdx.x & 15, kk = (threadIdx.x >> 4) & 3;
-    for (int b0 = 4 * wave; b0 < NT; b0 += 4 * nwave) {
+    constexpr int TPW = 64 / LANES;                     // tokens per wavefront at a time
+    const int j = threadIdx.x % LANES, kk = threadIdx.x / LANES % TPW;
+    for (int b0 = TPW * wave; b0 < NT; b0 += TPW * nwave) {
         const int b = b0 + kk, t = t0 + b;
         float lg[S][NB];
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
             for (int q = 0; q < NB; ++q) {
-                const int e = (s * 16 + j) * NB + q;
+                const int e = (s * LANES + j) * NB + q;
                 const float *src = part + (size_t)b * ld + e;
                 float l = ((src[0] + src[(size_t)NT * ld]) + src[(size_t)2 * NT * ld]) + src[(size_t)3 * NT * ld];
                 if (bias) l = l + bias[min(e, E - 1)];
@@ -92,6 +101,10 @@ __device__ inline void finish_tokens(const float *part, int NT, int ld, int t0, 
             f(std::integral_constant<int, 2>{});
             f(std::integral_constant<int, 4>{});
             f(std::integral_constant<int, 8>{});
+            if constexpr (LANES == 64) {
+                f(std::integral_constant<int, 16>{});
+                f(std::integral_constant<int, 32>{});
+            }
         };
         // best (value, index) with ties to the lower index
         int sel[2] = {0, 0};
@@ -103,7 +116,7 @@ __device__ inline void finish_tokens(const float *part, int NT, int ld, int t0, 
             for (int s = 0; s < S; ++s)
 #pragma unroll
                 for (int q = 0; q < NB; ++q) {
-                    const int e = (s * 16 + j) * NB + q;
+                    const int e = (s * LANES + j) * NB + q;
                     const bool taken = r == 1 && e == sel[0];
                     if (e < E && !taken && (lg[s][q] > bv || be == 0x7fffffff)) { bv = lg[s][q]; be = e; }
                 }
@@ -122,7 +135,7 @@ __device__ inline void finish_tokens(const float *part, int NT, int ld, int t0, 
         for (int s = 0; s < S; ++s)
 #pragma unroll
             for (int q = 0; q < NB; ++q)
-                if ((s * 16 + j) * NB + q < E) den += expf(lg[s][q] - lmax);
+                if ((s * LANES + j) * NB + q < E) den += expf(lg[s][q] - lmax);
         steps([&](auto off) { den += butterfly_partner<decltype(off)::value>(den); });
         if (j == 0 && t < T) store_choice(t, T, E, k, renorm, sel, selv, den, finished, expert_idx, expert_scale);
     }
@@ -154,6 +167,13 @@ __device__ inline void transpose_quads(uint32_t x, uint32_t y, uint32_t z, uint3
     q[0] = c[0]; q[1] = e[0]; q[2] = c[1]; q[3] = e[1];
 }
 
+// Loads of the gate weight, whose rows are E values of two bytes: WIDE, all experts of a lane at once (E a multiple of their
+// number); PAIRS, two experts per 4-byte load (E even); ODD_PAIRS, the same for odd E, where every other row starts in the
+// middle of a dword: its dwords are read from one value earlier, one more of them, and shifted into place in registers.
+// (One 2-byte load per expert instead of pairs, d = 1024, caches warm: 4096 tokens, 129 / 250 / 255 experts 57 / 79 / 78 us against
+// 37 / 42 / 51; experts in lanes, 16 tokens, 255 experts 22.7 against 13.5.)
+enum GateLoads { WIDE, PAIRS, ODD_PAIRS };
+
 // The logits on the matrix cores.  v_mfma_f32_16x16x4_f32 adds its four products to the accumulator one after
 // the other, each with the rounding (and the subnormal numbers) of an fp32 fma, so a chain of them over ascending
 // features IS the contract's sequential partial sum, bit for bit, at twice the rate of v_fma_mix_f32 (256 flops
@@ -163,8 +183,8 @@ __device__ inline void transpose_quads(uint32_t x, uint32_t y, uint32_t z, uint3
 // feature 4 n + kk of token j and of NB neighbouring experts j NB ..: these sit side by side in the row of the gate
 // weight, so one load of 2 NB bytes feeds NB instructions, and nothing is staged through LDS.  A token's features
 // come 64 bytes at a time, 16 per lane, and change lanes in registers.  R groups of 32 features are in flight per
-// wavefront (a ring).
-template <bool BF16, int NB, int S, int TT, int R, bool VEC>
+// wavefront (a ring).  LOADS: how the gate weight's rows can be read, see GateLoads.
+template <bool BF16, int NB, int S, int TT, int R, GateLoads LOADS>
 __global__ __launch_bounds__(256 * S) void gate_mfma_kernel(const uint16_t *__restrict__ x,
                                                         const uint16_t *__restrict__ wg,
                                                         const float *__restrict__ bias,
@@ -200,10 +220,12 @@ __global__ __launch_bounds__(256 * S) void gate_mfma_kernel(const uint16_t *__re
 #pragma unroll
     for (int t = 0; t < TT; ++t) x_row[t] = min(16 * t + j, rows - 1) * d;
     const int e0 = slice * EP + j * NB;                 // this lane's experts e0 .. e0 + NB - 1 (clamped where they do not exist)
-    const int w_off = (kk * E + (VEC ? min(e0, E - NB) : 0)) * 2;
+    const int odd = LOADS == ODD_PAIRS ? kk & 1 : 0;    // this lane's rows start in the middle of a dword
+    const int w_off = (kk * E - odd + (LOADS == WIDE ? min(e0, E - NB) : 0)) * 2;
 
-    constexpr int WD = NB >= 2 ? NB / 2 : 1;            // dwords of one weight load
-    struct Group { u32x4 x[TT]; uint32_t w[8][WD]; } ring[R];
+    constexpr int WD = NB >= 2 ? NB / 2 : 1;            // dwords of a lane's weights for one feature
+    constexpr int WL = WD + (LOADS == ODD_PAIRS ? 1 : 0);
+    struct Group { u32x4 x[TT]; uint32_t w[8][WL]; } ring[R];
     auto load = [&](Group &c, int g) __attribute__((always_inline)) {
         const int f = (p + 4 * (g >> 2)) * kGateBlk + (g & 3) * 32;
         const int fl = min(f + 8 * kk, d - 8);
@@ -212,11 +234,10 @@ __global__ __launch_bounds__(256 * S) void gate_mfma_kernel(const uint16_t *__re
 #pragma unroll
         for (int n = 0; n < 8; ++n) {
             const int so = min(f + 4 * n, d - 4) * E * 2;
-            if constexpr (!VEC) {
+            if constexpr (LOADS != WIDE) {      // (clamped: at most one value into the next row, and none past the last one)
 #pragma unroll
-                for (int u = 0; u < WD; ++u)
-                    c.w[n][u] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off + 2 * min(e0 + 2 * u, E - 1), so, 0) |
-                                (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off + 2 * min(e0 + 2 * u + 1, E - 1), so, 0) << 16;
+                for (int u = 0; u < WL; ++u)
+                    c.w[n][u] = __builtin_amdgcn_raw_buffer_load_b32(rw, w_off + 2 * min(e0 + 2 * u, LOADS == PAIRS ? E - 2 : E - 1), so, 0);
             } else if constexpr (NB == 1) {
                 c.w[n][0] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off, so, 0);
             } else if constexpr (NB == 2) {
@@ -254,7 +275,11 @@ __global__ __launch_bounds__(256 * S) void gate_mfma_kernel(const uint16_t *__re
 #pragma unroll
         for (int n = 0; n < 8; ++n)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) o.w[n][b] = act_to_float<BF16>((uint16_t)(c.w[n][b >> 1] >> (16 * (b & 1))));
+            for (int u = 0; u < WD; ++u) {
+                const uint32_t w = LOADS == ODD_PAIRS ? __builtin_amdgcn_alignbit(c.w[n][u + WL - WD], c.w[n][u], 16 * odd) : c.w[n][u];
+#pragma unroll
+                for (int b = 2 * u; b < NB && b < 2 * u + 2; ++b) o.w[n][b] = act_to_float<BF16>((uint16_t)(w >> (16 * (b & 1))));
+            }
     };
     auto multiply = [&](const Ops &o, int n) __attribute__((always_inline)) {
 #pragma unroll
@@ -406,13 +431,13 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
     finish_tokens<1, 4>(part, NT, ld, t0, p, 4, bias, finished, T, E, k, renorm, expert_idx, expert_scale);
 }
 
-// Few tokens and 65 to 128 experts: two experts per lane and the partial sums as plain fp32 fused multiply-adds.  Up to
-// a token or two per compute unit the matrix instructions above work on rows and experts of one block alone, sixteen or four
-// tokens by all experts, and a compute unit's matrix pipe is the bound; here a block takes TB tokens, each feature costs a
-// wavefront 2 TB fused multiply-adds and one 4-byte load (a whole row of the gate weight), and R octets of features are in flight.
-// (T = 64, 128 experts, caches warm / cold: d = 1024 9.7 / 14.2 us against 14.8 / 18.2 on the matrix cores, d = 2048 15.6 / 22.3
-// against 23.7 / 27.4.)
-template <bool BF16, int TB, int R>
+// Few tokens and more than 32 experts: NE experts per lane and the partial sums as plain fp32 fused multiply-adds.  Up to a few
+// tokens per compute unit the matrix instructions above work on rows and experts of one block alone, sixteen or four tokens by all
+// experts, and a compute unit's matrix pipe is the bound; here a block takes TB tokens, each feature costs a wavefront
+// NE TB fused multiply-adds and one load of a row of the gate weight per VW experts of a lane, and R octets of features are in flight.
+// (Caches warm, 16 / 512 tokens, d = 1024: 128 experts 9.3 / 10.9 us, 127 9.5 / 12.5, 256 12.2 / 14.2, 255 13.5 / 18.1; on the matrix
+// cores 14.8 to 16 us with 64 to 512 tokens and 65 to 128 experts, 25 with 256, 51 with 255.)
+template <bool BF16, int NE, GateLoads LOADS, int TB, int R>
 __global__ __launch_bounds__(256) void gate_lanes_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
                                                          const float *__restrict__ bias,
                                                          const uint8_t *__restrict__ finished, int T, int d, int E,
@@ -420,7 +445,10 @@ __global__ __launch_bounds__(256) void gate_lanes_kernel(const uint16_t *__restr
                                                          float *__restrict__ expert_scale)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int NT = 4, ld = 128 + 4;                 // (finish_tokens takes four tokens; the ones past TB are not stored)
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    constexpr bool ODD = LOADS == ODD_PAIRS;
+    constexpr int VW = LOADS == WIDE ? NE : 2, NL = NE / VW;           // experts per load, loads per feature
+    constexpr int NT = NE <= 2 && TB < 4 ? 4 : TB, ld = 64 * NE + 4;   // (sixteen lanes per token: four tokens at a time, the ones past TB are not stored)
     __shared__ float part[4 * NT * ld];
     const int lane = threadIdx.x & 63;
     const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -432,61 +460,94 @@ __global__ __launch_bounds__(256) void gate_lanes_kernel(const uint16_t *__restr
     const int rows = min(TB, T - t0);
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
-    const int w_off = min(2 * lane, E - 2) * 2;         // experts 2 lane, 2 lane + 1 (clamped where they do not exist)
+    int w_off[NL];                                      // experts VW (64 s + lane) .. (clamped where they do not exist; odd E: at most one value into the next row)
+#pragma unroll
+    for (int s = 0; s < NL; ++s) w_off[s] = min(VW * (64 * s + lane), ODD ? E - 1 : E - VW) * 2;
 
-    struct Octet { u32x4 x[TB]; uint32_t w[8]; } ring[R];
+    struct Octet { u32x4 x[TB]; uint32_t w[8][NL][VW < 2 ? 1 : VW / 2]; } ring[R];
     auto load = [&](Octet &c, int q) __attribute__((always_inline)) {
         const int f = feature(q);
 #pragma unroll
         for (int b = 0; b < TB; ++b) c.x[b] = __builtin_amdgcn_raw_buffer_load_b128(rx, min(b, rows - 1) * d * 2, f * 2, 0);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) c.w[u] = __builtin_amdgcn_raw_buffer_load_b32(rw, w_off, (f + u) * E * 2, 0);
-    };
-    float acc[TB][2];
+        for (int u = 0; u < 8; ++u)
 #pragma unroll
-    for (int b = 0; b < TB; ++b) acc[b][0] = acc[b][1] = 0.0f;
+            for (int s = 0; s < NL; ++s) {
+                const int so = ((f + u) * E - (ODD ? u & 1 : 0)) * 2;
+                if constexpr (VW == 1) c.w[u][s][0] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off[s], so, 0);
+                else if constexpr (VW == 2) c.w[u][s][0] = __builtin_amdgcn_raw_buffer_load_b32(rw, w_off[s], so, 0);
+                else {
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rw, w_off[s], so, 0);
+                    c.w[u][s][0] = v.x; c.w[u][s][1] = v.y;
+                }
+            }
+    };
+    float acc[TB][NE];
+#pragma unroll
+    for (int b = 0; b < TB; ++b)
+#pragma unroll
+        for (int e = 0; e < NE; ++e) acc[b][e] = 0.0f;
     auto multiply = [&](const Octet &c) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
             for (int b = 0; b < TB; ++b) {
                 const float xf = act_to_float<BF16>((uint16_t)(c.x[b][u >> 1] >> (16 * (u & 1))));
-                acc[b][0] = fmaf(xf, act_to_float<BF16>((uint16_t)c.w[u]), acc[b][0]);
-                acc[b][1] = fmaf(xf, act_to_float<BF16>((uint16_t)(c.w[u] >> 16)), acc[b][1]);
+#pragma unroll
+                for (int e = 0; e < NE; ++e)
+                    acc[b][e] = fmaf(xf, act_to_float<BF16>((uint16_t)(c.w[u][e / VW][(e % VW) >> 1] >> (16 * (e % VW & 1)))), acc[b][e]);
             }
+    };
+    // odd E: a lane's dword of an odd feature holds the value before its first expert and that expert; the other one is the lower half
+    // of the next lane's dword (of lane 0's of the next slice in the last lane)
+    auto shift = [&](Octet &c) __attribute__((always_inline)) {
+        if constexpr (ODD) {
+#pragma unroll
+            for (int u = 1; u < 8; u += 2) {
+                uint32_t up[NL];
+#pragma unroll
+                for (int s = 0; s < NL; ++s) up[s] = __builtin_amdgcn_update_dpp(0, (int)c.w[u][s][0], 0x134, 0xf, 0xf, false);   // wave_rol:1
+#pragma unroll
+                for (int s = 0; s < NL; ++s)
+                    c.w[u][s][0] = __builtin_amdgcn_alignbit(s + 1 < NL && lane == 63 ? up[s + 1 < NL ? s + 1 : s] : up[s], c.w[u][s][0], 16);
+            }
+        }
     };
     gate_static_for<0, R>([&](auto o) { load(ring[decltype(o)::value], decltype(o)::value); });
     int q0 = 0;
     for (; q0 + R <= nq; q0 += R) {
         gate_static_for<0, R>([&](auto oc) {
             constexpr int o = decltype(oc)::value;
-            const Octet c = ring[o];
+            Octet c = ring[o];
             load(ring[o], q0 + o + R);                  // (past the end: in-bounds loads that are not used)
+            shift(c);
             multiply(c);
         });
     }
     gate_static_for<0, R - 1>([&](auto oc) {
         constexpr int o = decltype(oc)::value;
-        if (q0 + o < nq) multiply(ring[o]);
+        if (q0 + o < nq) {
+            shift(ring[o]);
+            multiply(ring[o]);
+        }
     });
 #pragma unroll
-    for (int b = 0; b < TB; ++b) {
-        part[(p * NT + b) * ld + 2 * lane] = acc[b][0];
-        part[(p * NT + b) * ld + 2 * lane + 1] = acc[b][1];
-    }
+    for (int b = 0; b < TB; ++b)
+#pragma unroll
+        for (int e = 0; e < NE; ++e) part[(p * NT + b) * ld + VW * (64 * (e / VW) + lane) + e % VW] = acc[b][e];
     __syncthreads();
-    finish_tokens<2, 4>(part, NT, ld, t0, p, 4, bias, finished, min(T, t0 + TB), E, k, renorm, expert_idx, expert_scale);
+    finish_tokens<NE == 2 ? 2 : 1, 4, NE <= 2 ? 16 : 64>(part, NT, ld, t0, p, 4, bias, finished, min(T, t0 + TB), E, k, renorm, expert_idx, expert_scale);
 }
 
-template <bool BF16, int NB, int S, int TT, int R, bool VEC>
+template <bool BF16, int NB, int S, int TT, int R, GateLoads LOADS>
 static void launch_gate_mfma(const uint16_t *x, const uint16_t *wg, const float *bias, const uint8_t *finished, int T, int d, int E,
                                  int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
 {
     const size_t smem = (size_t)4 * 16 * TT * (S * 16 * NB + 4) * sizeof(float);
-    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(&gate_mfma_kernel<BF16, NB, S, TT, R, VEC>),
+    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(&gate_mfma_kernel<BF16, NB, S, TT, R, LOADS>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
     (void)raised;
-    hipLaunchKernelGGL((gate_mfma_kernel<BF16, NB, S, TT, R, VEC>), dim3((T + 16 * TT - 1) / (16 * TT)), dim3(256 * S), smem, s, x, wg, bias,
+    hipLaunchKernelGGL((gate_mfma_kernel<BF16, NB, S, TT, R, LOADS>), dim3((T + 16 * TT - 1) / (16 * TT)), dim3(256 * S), smem, s, x, wg, bias,
                        finished, T, d, E, k, renorm, expert_idx, expert_scale);
 }
 
@@ -494,44 +555,70 @@ template <bool BF16>
 static void launch_gate(const uint16_t *x, const uint16_t *wg, const float *bias, const uint8_t *finished, int T, int d, int E,
                         int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
 {
-    // 33 to 64 experts and up to four tokens per compute unit: four-token blocks.  (64 experts, T = 64: 10.0 against 12.7 us
-    // for sixteen-token blocks at d = 1024, 25.8 against 28.0 us at d = 4096; T = 2048: 17.5 against 11.8 us.  Beyond 64
-    // experts its one-row loads of the gate weight are the bound and it loses everywhere; up to 32 it idles half its lanes.)
-    // 33 to 64 experts and up to four tokens per compute unit: four-token blocks.  (64 experts, T = 64: 10.0 against 12.7 us
-    // for sixteen-token blocks at d = 1024, 25.8 against 28.0 us at d = 4096; T = 2048: 17.5 against 11.8 us.)
+    const GateLoads pairs = E % 2 ? ODD_PAIRS : PAIRS;
+    // 33 to 64 experts and up to four tokens per compute unit: four-token blocks on the matrix cores.  (64 experts, T = 64: 10.0 against
+    // 12.7 us for sixteen-token blocks at d = 1024, 25.8 against 28.0 us at d = 4096; T = 2048: 17.5 against 11.8 us.)  FP16 tokens,
+    // more than one such block and up to a token per compute unit: a lane per expert.  (48 experts, T = 16: 8.4 against 9.4 us, 21.0
+    // against 25.1; T = 300: 12.3 against 9.6; one token 7.6 against 7.3; bf16 9.2 against 9.4, 26.5 against 25.2.)
     if (E > 32 && E <= 64 && T <= 1024) {
-        if (E % 4) hipLaunchKernelGGL((gate_quad_kernel<BF16, 8, false>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        if (!BF16 && T > 4 && T <= 256)
+            hipLaunchKernelGGL((gate_lanes_kernel<BF16, 1, WIDE, 1, 2>), dim3(T), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        else if (E % 4) hipLaunchKernelGGL((gate_quad_kernel<BF16, 8, false>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
         else hipLaunchKernelGGL((gate_quad_kernel<BF16, 8, true>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
         return;
     }
-    // 65 to 128 experts, up to two tokens per compute unit: a block per token, then per two (T = 500, d = 1024, caches warm: 13.8 us
-    // with one, 11.5 with two, 14.9 on the matrix cores)
-    if (E > 64 && E <= 128 && E % 2 == 0 && T <= 512) {
-        if (T <= 256) hipLaunchKernelGGL((gate_lanes_kernel<BF16, 1, 4>), dim3(T), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
-        else hipLaunchKernelGGL((gate_lanes_kernel<BF16, 2, 4>), dim3((T + 1) / 2), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+    // More than 64 experts: a block per token up to one per compute unit, then two, then four, as far as that is faster than the
+    // matrix cores (d = 1024, T = 1024, FP16, lanes / matrix cores: 127 experts 15.4 / 21.9 us, 128 13.9 / 14.9, 256 22.7 / 24.9; bf16 128
+    // experts 17.0 / 15.0; d = 4096 128 experts 48 / 42; T = 1500: 128 19.5 / 15.1, 255 33.2 / 51, 250 30 / 41, 256 32.5 / 25).
+    const int few = E > 128 ? (E % 8 ? 2048 : 1024) : E % 2 ? (d <= 1024 ? 2048 : 1024) : !BF16 && d <= 2048 ? 1024 : 512;
+    if (E > 64 && T <= few) {
+#define MOE_GATE_LANES(NE, LOADS, TB, R) \
+    hipLaunchKernelGGL((gate_lanes_kernel<BF16, NE, LOADS, TB, R>), dim3((T + TB - 1) / TB), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale)
+#define MOE_GATE_LANES_TB(NE, LOADS) \
+    do { \
+        constexpr int R = NE == 2 ? 3 : 2; \
+        if (T <= 256) MOE_GATE_LANES(NE, LOADS, 1, R); \
+        else if (T <= 512) MOE_GATE_LANES(NE, LOADS, 2, R); \
+        else MOE_GATE_LANES(NE, LOADS, 4, 2); \
+    } while (0)
+        if (E <= 128) {
+            if (pairs == PAIRS) MOE_GATE_LANES_TB(2, WIDE);
+            else MOE_GATE_LANES_TB(2, ODD_PAIRS);
+        } else {
+            if (E % 4 == 0) MOE_GATE_LANES_TB(4, WIDE);
+            else if (pairs == PAIRS) MOE_GATE_LANES_TB(4, PAIRS);
+            else MOE_GATE_LANES_TB(4, ODD_PAIRS);
+        }
+#undef MOE_GATE_LANES_TB
+#undef MOE_GATE_LANES
         return;
     }
     // Two row tiles per wavefront (one load and conversion of the gate weight for 32 tokens) once that still gives every
     // compute unit a block.  (T = 8192, d = 4096, 64 experts: 48.5 against 52 us; T = 4096: 45 against 30 us.)  With up to 16
     // experts the conversions of the tokens, not of the weights, are the larger part: one tile always.
     const bool two = (T + 31) / 32 >= 256;
-#define MOE_GATE_MFMA(NB, S, TT, R, VEC) launch_gate_mfma<BF16, NB, S, TT, R, VEC>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale, s)
-    if (E <= 16) MOE_GATE_MFMA(1, 1, 1, 8, true);
+#define MOE_GATE_MFMA(NB, S, TT, R, LOADS) launch_gate_mfma<BF16, NB, S, TT, R, LOADS>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale, s)
+    if (E <= 16) MOE_GATE_MFMA(1, 1, 1, 8, WIDE);
     else if (E <= 32) {
-        if (E % 2) MOE_GATE_MFMA(2, 1, 1, 4, false);
-        else if (two) MOE_GATE_MFMA(2, 1, 2, 4, true);
-        else MOE_GATE_MFMA(2, 1, 1, 8, true);
+        if (E % 2) MOE_GATE_MFMA(2, 1, 1, 4, ODD_PAIRS);
+        else if (two) MOE_GATE_MFMA(2, 1, 2, 4, WIDE);
+        else MOE_GATE_MFMA(2, 1, 1, 8, WIDE);
     } else if (E <= 64) {
-        if (E % 4) MOE_GATE_MFMA(4, 1, 1, 2, false);
-        else if (two) MOE_GATE_MFMA(4, 1, 2, 4, true);
-        else MOE_GATE_MFMA(4, 1, 1, 6, true);
+        if (E % 2) MOE_GATE_MFMA(4, 1, 1, 4, ODD_PAIRS);
+        else if (E % 4) MOE_GATE_MFMA(4, 1, 1, 4, PAIRS);
+        else if (two) MOE_GATE_MFMA(4, 1, 2, 4, WIDE);
+        else MOE_GATE_MFMA(4, 1, 1, 6, WIDE);
     } else if (E <= 128) {
-        if (E % 4) MOE_GATE_MFMA(4, 2, 1, 2, false);
-        else if (two) MOE_GATE_MFMA(4, 2, 2, 4, true);
-        else MOE_GATE_MFMA(4, 2, 1, 4, true);
+        if (E % 2) MOE_GATE_MFMA(4, 2, 1, 4, ODD_PAIRS);
+        else if (E % 4) MOE_GATE_MFMA(4, 2, 1, 4, PAIRS);
+        else if (two) MOE_GATE_MFMA(4, 2, 2, 4, WIDE);
+        else MOE_GATE_MFMA(4, 2, 1, 4, WIDE);
     } else {
-        if (E % 8) MOE_GATE_MFMA(8, 2, 1, 1, false);
-        else MOE_GATE_MFMA(8, 2, 1, 3, true);
+        if (E % 2 && two) MOE_GATE_MFMA(8, 2, 2, 1, ODD_PAIRS);
+        else if (E % 2) MOE_GATE_MFMA(8, 2, 1, 2, ODD_PAIRS);
+        else if (E % 8 && two) MOE_GATE_MFMA(8, 2, 2, 1, PAIRS);
+        else if (E % 8) MOE_GATE_MFMA(8, 2, 1, 3, PAIRS);
+        else MOE_GATE_MFMA(8, 2, 1, 3, WIDE);
     }
 #undef MOE_GATE_MFMA
 }
