@@ -12,12 +12,14 @@
 // Batch pruning (Sec. 3.5): an expert index equal to E marks a row of a finished sentence.  It is
 // one more key of the sort, the last one, so such rows end up behind every active row;
 // expert_offsets[E] is then the number of active rows, and pruned rows are not copied.
+#include <type_traits>
+
 #include "moe_common.h"
 
 namespace moe {
 
 constexpr int kPermMaxE = 1024;
-constexpr int kPermMaxIters = 16;        // steps of 64 assignments in a wave-chunk (perm_plan)
+constexpr int kPermFused = 4096;         // assignments that one launch takes (its blocks all sort them)
 
 __device__ inline uint64_t lanemask_lt() { return (1ull << (threadIdx.x & 63)) - 1ull; }
 
@@ -36,8 +38,8 @@ __device__ inline uint64_t match_key(int key, int key_bits)
 // assignments (cheap), keeps perm_src in LDS and then gathers its share of the rows; block 0
 // writes the index outputs.  Otherwise PHASE selects count (0) or rank (1), and the per-chunk
 // histograms travel through `hist` [nwc][E].
-// W: wavefronts of a block.
-template <bool FUSED, int PHASE, int W>
+// W: wavefronts of a block; ITERS: the most steps of 64 assignments of a wave-chunk.
+template <bool FUSED, int PHASE, int W, int ITERS>
 __global__ __launch_bounds__(64 * W) void permute_index_kernel(const int32_t *__restrict__ expert_idx,
                                                             int R, int NB, int iters, int nwc,
                                                             int key_bits, int32_t *__restrict__ hist,
@@ -59,9 +61,9 @@ __global__ __launch_bounds__(64 * W) void permute_index_kernel(const int32_t *__
 
     // The chunk's keys are requested together and kept for both passes over them: a load inside each step's chain of counting,
     // ranking and barriers would cost a memory latency per step and pass.
-    int keys[kPermMaxIters];
+    int keys[ITERS];
 #pragma unroll
-    for (int it = 0; it < kPermMaxIters; ++it) {
+    for (int it = 0; it < ITERS; ++it) {
         const int a = wc * CH + it * 64 + lane;
         if (it < iters) keys[it] = a < R ? min(max(expert_idx[a], 0), NB - 1) : -1;          // clamped: never out of range
     }
@@ -69,7 +71,7 @@ __global__ __launch_bounds__(64 * W) void permute_index_kernel(const int32_t *__
         for (int e = threadIdx.x; e < W * NB; e += 64 * W) sm[e] = 0;
         __syncthreads();
 #pragma unroll
-        for (int it = 0; it < kPermMaxIters; ++it)
+        for (int it = 0; it < ITERS; ++it)
             if (it < iters && keys[it] >= 0) atomicAdd(&cnt[keys[it]], 1);
         __syncthreads();
         if (!FUSED) {
@@ -132,7 +134,7 @@ __global__ __launch_bounds__(64 * W) void permute_index_kernel(const int32_t *__
 
     // rank: cnt[key] is the next free position of `key` for this wave-chunk
 #pragma unroll
-    for (int it = 0; it < kPermMaxIters; ++it) {
+    for (int it = 0; it < ITERS; ++it) {
         if (it >= iters) break;
         const int a = wc * CH + it * 64 + lane;
         const bool live = keys[it] >= 0;
@@ -184,21 +186,16 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint4 *__restric
     }
 }
 
-static void perm_plan(int R, int *iters, int *nblocks)
-{
-    // up to 4096 assignments: one block, one launch; beyond: 256 assignments per wavefront
-    if (R <= 256 * kPermMaxIters) { *iters = (R + 255) / 256; if (*iters < 1) *iters = 1; *nblocks = 1; }
-    else { *iters = 4; *nblocks = (R + 1023) / 1024; }
-}
+// one block's worth, one launch; beyond: 256 assignments per wavefront
+constexpr int kPermSteps = 4;
+static int perm_blocks(int R) { return R <= kPermFused ? 1 : (R + 256 * kPermSteps - 1) / (256 * kPermSteps); }
 
 }  // namespace moe
 
 extern "C" size_t moe_permute_workspace_bytes(int T, int k, int E)
 {
     if (T <= 0 || k <= 0 || E <= 0) return 16;
-    int iters, nblocks;
-    moe::perm_plan(T * k, &iters, &nblocks);
-    return moe::round_up((size_t)nblocks * 4 * (E + 1) * sizeof(int32_t), 256);
+    return moe::round_up((size_t)moe::perm_blocks(T * k) * 4 * (E + 1) * sizeof(int32_t), 256);
 }
 
 extern "C" int moe_permute(const int32_t *expert_idx, const void *x, int act_dtype, int T, int k, int E,
@@ -218,8 +215,7 @@ extern "C" int moe_permute(const int32_t *expert_idx, const void *x, int act_dty
     if ((long long)T * k > 0x7fffffffLL) return fail(MOE_ERR_INVALID_ARG, "moe_permute: T*k overflows int32");
     if (!aligned16(x) || !aligned16(x_perm)) return fail(MOE_ERR_INVALID_ARG, "moe_permute: x and x_perm must be 16-byte aligned");
     const int R = T * k;
-    int iters, nblocks;
-    perm_plan(R, &iters, &nblocks);
+    const int nblocks = perm_blocks(R);
     const size_t need = moe_permute_workspace_bytes(T, k, E);
     if (nblocks > 1 && (!workspace || workspace_bytes < need))
         return fail(MOE_ERR_WORKSPACE, "moe_permute: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
@@ -234,23 +230,27 @@ extern "C" int moe_permute(const int32_t *expert_idx, const void *x, int act_dty
         // index and gather in one launch: up to 64 blocks share the row copies
         int gb = x ? (R + 3) / 4 : 1;
         gb = gb < 1 ? 1 : gb > 64 ? 64 : gb;
-        // sixteen wavefronts where they share enough assignments and their counters fit: fewer steps in a row for each
-        // (index of 1994 assignments by 16 experts: 8.7 us in four wavefronts, 6.0 in sixteen)
-        if (R > 256 && NB <= 512) {
-            hipLaunchKernelGGL((permute_index_kernel<true, 0, 16>), dim3((gb + 3) / 4), dim3(1024), (size_t)17 * NB * sizeof(int32_t) + (size_t)R * sizeof(int32_t), s,
-                               expert_idx, R, NB, (R + 1023) / 1024, 16, key_bits, hist, perm_src, inv_perm, expert_offsets,
-                               (const uint4 *)x, k, row_vec, (uint4 *)x_perm);
-            return check_launch("moe_permute");
-        }
-        hipLaunchKernelGGL((permute_index_kernel<true, 0, 4>), dim3(gb), dim3(256), smem + (size_t)R * sizeof(int32_t), s,
-                           expert_idx, R, NB, iters, 4, key_bits, hist, perm_src, inv_perm, expert_offsets,
-                           (const uint4 *)x, k, row_vec, (uint4 *)x_perm);
+        // Four, eight or sixteen wavefronts per block, the fewest steps in a row for each that their start-up allows: up to 256, up to 512
+        // and more assignments (and at most eight where the counters of sixteen would not fit).  Index / index and copies of rows of 1024,
+        // 128 experts: 256 assignments 3.4 / 4.1 us in four wavefronts, 3.6 / 4.4 in eight, 4.0 / 5.2 in sixteen; 400 4.1 / 5.3, 3.7 / 4.5, 4.1 / 5.3;
+        // 2000 8.4 / 12.3, 5.8 / 8.2, 5.3 / 7.3 (in a quarter of the blocks 10.2); a step of 64 unrolled sixteen times for all sizes adds 0.15-0.3 us.
+        auto launch = [&](auto w_c, auto it_c) {
+            constexpr int W = decltype(w_c)::value, ITERS = decltype(it_c)::value;
+            const int steps = R > 64 * W ? (R + 64 * W - 1) / (64 * W) : 1;
+            hipLaunchKernelGGL((permute_index_kernel<true, 0, W, ITERS>), dim3(gb), dim3(64 * W), ((size_t)(W + 1) * NB + R) * sizeof(int32_t), s, expert_idx, R, NB, steps,
+                               W, key_bits, hist, perm_src, inv_perm, expert_offsets, (const uint4 *)x, k, row_vec, (uint4 *)x_perm);
+        };
+        using std::integral_constant;
+        if (R <= 256) launch(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+        else if (R <= 512) launch(integral_constant<int, 8>{}, integral_constant<int, 1>{});
+        else if (NB <= 512) launch(integral_constant<int, 16>{}, integral_constant<int, kPermFused / 1024>{});
+        else launch(integral_constant<int, 8>{}, integral_constant<int, kPermFused / 512>{});
         return check_launch("moe_permute");
     }
-    hipLaunchKernelGGL((permute_index_kernel<false, 0, 4>), dim3(nblocks), dim3(256), smem, s, expert_idx, R, NB, iters,
+    hipLaunchKernelGGL((permute_index_kernel<false, 0, 4, kPermSteps>), dim3(nblocks), dim3(256), smem, s, expert_idx, R, NB, kPermSteps,
                        nblocks * 4, key_bits, hist, perm_src, inv_perm, expert_offsets, (const uint4 *)nullptr, k,
                        row_vec, (uint4 *)nullptr);
-    hipLaunchKernelGGL((permute_index_kernel<false, 1, 4>), dim3(nblocks), dim3(256), smem, s, expert_idx, R, NB, iters,
+    hipLaunchKernelGGL((permute_index_kernel<false, 1, 4, kPermSteps>), dim3(nblocks), dim3(256), smem, s, expert_idx, R, NB, kPermSteps,
                        nblocks * 4, key_bits, hist, perm_src, inv_perm, expert_offsets, (const uint4 *)nullptr, k,
                        row_vec, (uint4 *)nullptr);
     int rc = check_launch("moe_permute (index)");

@@ -19,3 +19,12 @@ def test_gate_of_few_tokens_by_many_experts_is_spread_over_the_chip(act):
         (launch,) = call.launches
         assert call.rc == 0 and launch.kernel.startswith("gate_lanes_kernel"), (T, d, E, launch)
         assert launch.grid[0] == (T if T <= 256 else (T + 1) // 2)
+
+
+def test_permute_shares_its_work_by_the_number_of_assignments():
+    """One launch up to 4096 assignments: four, eight or sixteen wavefronts per block, and up to 64 blocks whatever their size where rows
+    are copied.  (2000 rows of 4096 copied by a quarter of the blocks: 29 us against 13.)"""
+    cases = [(1, 8, 4, 1), (256, 8, 4, 64), (257, 8, 8, 64), (512, 1000, 8, 64), (513, 8, 16, 64), (4096, 500, 16, 64), (4096, 1000, 8, 64)]
+    for (R, E, waves, blocks), copies, index in zip(cases, L.record([L.permute(R, 1, E, 1024) for R, E, _, _ in cases]), L.record([L.permute(R, 1, E) for R, E, _, _ in cases])):
+        assert [(p.block, p.grid[0]) for p in copies.launches] == [(64 * waves, blocks)], (R, E)
+        assert [(p.block, p.grid[0]) for p in index.launches] == [(64 * waves, 1)] and index.launches[0].shared <= 64 * 1024

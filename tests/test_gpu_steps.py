@@ -95,7 +95,10 @@ def test_gate_ties_and_equal_logits():
 
 # ------------------------------------------------------------------ permute
 @pytest.mark.parametrize("T,k,E,d", [(64, 2, 32, 1024), (1, 1, 4, 64), (300, 2, 13, 128), (4096, 1, 64, 64),
-                                      (5000, 2, 128, 64), (16384, 1, 64, 256), (4500, 1, 1, 64), (700, 2, 200, 72)])
+                                      (5000, 2, 128, 64), (16384, 1, 64, 256), (4500, 1, 1, 64), (700, 2, 200, 72),
+                                      # the edges between four, eight and sixteen wavefronts per block, and eight for many experts
+                                      (128, 2, 16, 64), (257, 1, 9, 72), (256, 2, 1000, 64), (513, 1, 30, 64), (1025, 1, 511, 64),
+                                      (600, 1, 512, 64), (2048, 2, 1023, 64), (4097, 1, 40, 64)])
 def test_permute_bit_exact(T, k, E, d):
     _say(f"permute T={T} k={k} E={E} d={d}")
     rng = np.random.default_rng(T + E)
