@@ -152,9 +152,9 @@ int moe_permute(const int32_t *expert_idx, const void *x, int act_dtype, int T, 
  *       knows one (T is one: a token visits an expert at most once); 0 = unknown (R is used).
  *       It takes part in the choice between the weight-streaming kernels (which need a bound
  *       <= 64, or a mean of at most 32 rows per expert with a bound of at most sixteen row
- *       groups, and are used while R / E says that the typical expert fits one row group, R <= 256,
- *       or there are too few experts to fill the chip with row tiles) and the tiled kernel, and
- *       it sizes the streaming launch, so it must be a true bound: rows of an expert beyond it
+ *       groups, and are used for each of the two GEMMs while they are the faster ones: R <= E, few
+ *       row groups of small weights in all, few experts, or experts of a few rows) and the row tiles,
+ *       and it sizes the streaming launch, so it must be a true bound: rows of an expert beyond it
  *       are not computed.
  *   w1_packed / w2_packed: q_packed from moe_quantize_experts for (E,d,F) / (E,F,d)
  *   s1 fp16 [E, d/g, F]; s2 fp16 [E, F/g, d]  (g = group_size, or K when group_size is 0)
@@ -197,8 +197,8 @@ int moe_grouped_ffn_wq_noalloc(const void *x_perm, int act_dtype, const int32_t 
                                const void *b2, void *y_perm, int y_dtype, void *stream);
 
 /*
- * moe_grouped_ffn_wq with the routing fused into the GEMMs, for batches large enough to run in
- * the tiled kernel: fc1 fetches row r from x[perm_src[r] / k] (no x_perm copy is needed:
+ * moe_grouped_ffn_wq with the routing fused into the GEMMs, for batches too large for the streaming
+ * kernels (moe_grouped_ffn_wq_indexed takes every size): fc1 fetches row r from x[perm_src[r] / k] (no x_perm copy is needed:
  * moe_permute may be called with x = x_perm = NULL), and, when expert_scale is given (k = 1
  * only, one expert per token), fc2 stores expert_scale[t] * y[r] straight into out[t],
  * t = perm_src[r], which replaces moe_combine.
@@ -207,7 +207,7 @@ int moe_grouped_ffn_wq_noalloc(const void *x_perm, int act_dtype, const int32_t 
  *   With pruned rows (Sec. 3.5) and expert_scale given, the rows of pruned tokens in out are
  *   not written: clear out first, or use moe_combine.
  * moe_grouped_ffn_wq_routed_supported returns 1 when a call with these sizes is taken (fp16
- * activations and row counts that run entirely in the tiled kernel); otherwise the call
+ * activations and row counts that no streaming kernel takes for either GEMM); otherwise the call
  * returns MOE_ERR_UNSUPPORTED and the un-fused sequence has to be used.  Workspace as for
  * moe_grouped_ffn_wq.
  */
@@ -223,7 +223,10 @@ int moe_grouped_ffn_wq_routed(const void *x, int act_dtype, const int32_t *perm_
 /*
  * The same call for every size and for bf16 rows as well (k must divide R: row r of the sorted order is token
  * perm_src[r] / k).  Both GEMMs run in row tiles whatever the sizes; bf16 tokens are converted once, not once per expert.
+ * moe_grouped_ffn_wq_indexed_pays returns 1 when it is also the faster way for these sizes (MoEExpertLayer asks this).
  */
+int moe_grouped_ffn_wq_indexed_pays(int R, int E, int max_rows_per_expert, int d, int F, int bits,
+                                    int group_size, int act_dtype);
 int moe_grouped_ffn_wq_indexed(const void *x, int act_dtype, const int32_t *perm_src, int k,
                                const float *expert_scale, const int32_t *expert_offsets, int R, int E,
                                int max_rows_per_expert, int d, int F, int bits, int group_size,

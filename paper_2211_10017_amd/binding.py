@@ -21,7 +21,7 @@ _DT = {torch.float16: MOE_F16, torch.bfloat16: MOE_BF16, torch.float32: MOE_F32}
 EXPORTS = ["moe_last_error", "moe_last_ffn_kernels", "moe_device_info", "moe_abi_version", "moe_quantize_experts", "moe_gate_topk",
            "moe_permute_workspace_bytes", "moe_permute", "moe_grouped_ffn_wq_workspace_bytes",
            "moe_grouped_ffn_wq", "moe_combine", "moe_pack_fp16_experts", "moe_grouped_gemm_wq",
-           "moe_grouped_ffn_wq_routed_supported", "moe_grouped_ffn_wq_routed", "moe_grouped_ffn_wq_indexed",
+           "moe_grouped_ffn_wq_routed_supported", "moe_grouped_ffn_wq_routed", "moe_grouped_ffn_wq_indexed", "moe_grouped_ffn_wq_indexed_pays",
            "moe_grouped_ffn_wq_gated_supported", "moe_grouped_ffn_wq_gated_pays", "moe_grouped_ffn_wq_gated",
            "moe_grouped_ffn_wq_noalloc_max_bytes", "moe_grouped_ffn_wq_noalloc"]
 
@@ -76,6 +76,8 @@ def load():
     lib.moe_grouped_ffn_wq_indexed.restype = i
     lib.moe_grouped_ffn_wq_indexed.argtypes = [vp, i, vp, i, vp, vp, i, i, i, i, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, i,
                                               vp, sz, vp]
+    lib.moe_grouped_ffn_wq_indexed_pays.restype = i
+    lib.moe_grouped_ffn_wq_indexed_pays.argtypes = [i, i, i, i, i, i, i, i]
     lib.moe_grouped_ffn_wq_gated_supported.restype = i
     lib.moe_grouped_ffn_wq_gated_supported.argtypes = [i, i, i, i, i, i, i, i]
     lib.moe_grouped_ffn_wq_gated_pays.restype = i
@@ -292,6 +294,11 @@ def moe_grouped_ffn_wq_routed(x, perm_src, k: int, expert_offsets, E: int, d: in
         _ptr(b2, torch.float16, "b2"), _ptr(out), _DT[out.dtype], _ptr(workspace), workspace.numel(), _stream())
     _check(rc, "moe_grouped_ffn_wq_routed")
     return out
+
+
+def moe_grouped_ffn_wq_indexed_pays(R: int, E: int, max_rows_per_expert: int, d: int, F: int, bits: int, group_size: int, act_dtype) -> bool:
+    """Whether fetching the rows through the routing index is the faster way for these sizes."""
+    return bool(load().moe_grouped_ffn_wq_indexed_pays(R, E, max_rows_per_expert, d, F, bits, group_size, _DT[act_dtype]))
 
 
 def moe_grouped_ffn_wq_gated_supported(T: int, k: int, E: int, d: int, F: int, bits: int, group_size: int, act_dtype) -> int:

@@ -117,8 +117,9 @@ extern "C" size_t moe_grouped_ffn_wq_workspace_bytes(int R, int d, int F, int E,
     return moe::ffn_workspace(R, d, F, act_dtype).total;
 }
 
-// Which kernel one GEMM of the FFN runs in, from what the host knows about the routed loads: an upper
-// bound on the rows of any expert and the mean rows per expert.
+// Which kernel can take one GEMM of the FFN, from what the host knows about the routed loads: an upper bound on the rows of any
+// expert and the mean rows per expert.  The gated call and the answers of the _supported queries follow this rule; a GEMM of
+// permuted rows runs in the streaming kernel it names only where that is the faster one as well (stream_pays).
 enum GemmKernel { GEMM_TILED, GEMM_STREAM_UNROLLED, GEMM_STREAM_LOOP };
 
 static GemmKernel choose_kernel(int R, int E, int max_rows, int K, int N, int bits, int smode, bool bf)
@@ -134,13 +135,42 @@ static GemmKernel choose_kernel(int R, int E, int max_rows, int K, int N, int bi
     // expert on average and at most sixteen groups ...
     const bool few = unrolled && mean <= 32 && max_rows <= 16 * fit;
     if (!(max_rows <= 64 || few)) return GEMM_TILED;
-    // ... and it pays while the typical expert is one row group (measured on 32 experts of 1024 x 4096:
-    // 34 us up to 8 rows per expert, 47 at 16, 69 at 24, against 49 us in row tiles at any of these), or
-    // the batch is decode-sized, or row tiles would leave most of the chip idle (one tile per expert and
-    // column block: 8 experts of 512 x 2048 stream in 16 us and take 30 us in 64 + 16 tiles).
+    // ... and, further, that the typical expert is one row group, the batch is decode-sized, or row tiles would leave most
+    // of the chip idle (one tile per expert and column block).
     const long tiles = (long)(E < R ? E : R) * ((N + 255) / 256);
     if (R <= 256 || mean <= fit || tiles < 128) return unrolled ? GEMM_STREAM_UNROLLED : GEMM_STREAM_LOOP;
     return GEMM_TILED;
+}
+
+// Whether one of the streaming kernels is the faster one for a GEMM that choose_kernel gives it, rows permuted beforehand.  A
+// streaming block takes one row group of an expert (`fit` rows) and one or two slabs of 32 channels and has its whole ring in flight
+// from the start; further row groups of the expert stream its weights again.  Row tiles read them once, but a launch of few
+// tiles waits for its chain of K steps.  So streaming pays
+//  - while all slabs of all row groups run at once, about 1280 of 4-bit or 1200 of 8-bit weights: 40 rows on 8 experts of
+//    1024 x 4096, 4-bit, 16.0 us a pair of GEMMs against 25.0 in row tiles, 256 rows 39 against 29; in the run-loop kernel 1300 of 4-bit
+//    or 650 of 8-bit weights, from N = 2048 on (32 experts of 1024 x 4096, 8-bit, 64 rows: its fc2 takes 5 us longer than row tiles),
+//  - for few tiles (64 rows on one expert of 2048 x 8192, 8-bit: 45 against 61 us, of 512 x 2048 11 against 22; on four of 2048 x 8192
+//    70 against 47, which the lines above leave to row tiles),
+//  - for experts of mostly well under one row group, 8-bit, or 4-bit with many tiles (200 rows on 128 experts of 1024 x 1024: 43
+//    against 54, 33 against 40).
+// (8681 GEMMs of such calls, even and skewed loads: row tiles for every R > E cost up to 88 % of a call, streaming wherever
+// choose_kernel allows it up to 68 %; this rule up to 13 %, or 28 % where the load is skewed, which it does not see.)
+static bool stream_pays(int R, int E, int K, int N, int bits, bool unrolled)
+{
+    using namespace moe;
+    if (R <= E) return true;
+    const long experts = E < R ? E : R, tiles = experts * ((N + 255) / 256);
+    const int fit = unrolled ? stream_unrolled_fit(K, R) : stream_gemm_fit_rows(K);
+    const long slabs = (experts + R / fit) * (N / 32);
+    if (unrolled) return slabs <= (bits == 4 ? 1280 : 1200) || tiles <= 40 || (8L * R <= 5L * fit * E && (bits == 8 || tiles > 448));
+    return (slabs * bits <= 4 * 1300 && N >= 2048) || (tiles <= 28 && R > 32L * E && R <= 16L * fit * E);
+}
+
+// The kernel of one GEMM whose rows come permuted.
+static GemmKernel four_call_kernel(int R, int E, int max_rows, int K, int N, int bits, int smode, bool bf)
+{
+    const GemmKernel kernel = choose_kernel(R, E, max_rows, K, N, bits, smode, bf);
+    return kernel == GEMM_TILED || stream_pays(R, E, K, N, bits, kernel == GEMM_STREAM_UNROLLED) ? kernel : GEMM_TILED;
 }
 
 // bf: the rows were bf16 (they come in converted to scaled FP16, with their factors in g.row_pow, which only the
@@ -149,11 +179,10 @@ static GemmKernel choose_kernel(int R, int E, int max_rows, int K, int N, int bi
 static int run_gemm(moe::GemmArgs g, int bits, int smode, bool bf, bool tiles_only, int max_rows, hipStream_t s)
 {
     using namespace moe;
-    GemmKernel kernel = choose_kernel(g.R, g.E, max_rows, g.K, g.N, bits, smode, bf);
-    // Without the permutation inside the launch the streaming kernels pay for at most one row per expert on average only: every
-    // further row group of an expert streams its weights again (64 tokens on 16 experts of 4096 x 16384: 4-bit 541 us per step
-    // against 230 in the row tiles, 8-bit 916 against 360).
-    if (!g.gate_idx && !g.out_add && (g.R > g.E || tiles_only)) kernel = GEMM_TILED;
+    // (the permutation inside the launch and the added rows of the gated call are built for the straight-line kernel only)
+    const GemmKernel kernel = tiles_only                ? GEMM_TILED
+                              : g.gate_idx || g.out_add ? choose_kernel(g.R, g.E, max_rows, g.K, g.N, bits, smode, bf)
+                                                        : four_call_kernel(g.R, g.E, max_rows, g.K, g.N, bits, smode, bf);
     note_kernel(kernel == GEMM_STREAM_UNROLLED ? "stream_unrolled_kernel" : kernel == GEMM_STREAM_LOOP ? "stream_gemm_kernel" : "grouped_gemm_kernel");
     if (kernel == GEMM_STREAM_UNROLLED) return launch_stream_unrolled(g, bits, max_rows, s);
     if (g.gate_idx || g.out_add) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_gated: K=%d does not run in the straight-line kernel with these sizes", g.K);
@@ -367,8 +396,8 @@ extern "C" int moe_grouped_ffn_wq_routed(const void *x, int act_dtype, const int
     if (expert_scale && k != 1)
         return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_routed: the fused un-permute needs k = 1 (one expert per token)");
     if (!moe_grouped_ffn_wq_routed_supported(R, E, max_rows_per_expert, d, F, bits, group_size, act_dtype))
-        return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_routed: these sizes run (partly) in the streaming kernels or in bf16, "
-                                         "which take permuted rows only: use moe_permute + moe_grouped_ffn_wq + moe_combine");
+        return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_routed: only fp16 batches too large for the streaming kernels are taken: use "
+                                         "moe_grouped_ffn_wq_indexed, or moe_permute + moe_grouped_ffn_wq + moe_combine");
     return ffn_impl(x, act_dtype, expert_offsets, R, E, max_rows_per_expert, d, F, bits, group_size, activation, w1_packed, s1, b1,
                     w2_packed, s2, b2, out, out_dtype, workspace, workspace_bytes, stream, perm_src, k, expert_scale);
 }
@@ -413,14 +442,28 @@ static int gated_shapes(int T, int k, int E, int d, int F, int bits, int group_s
 // Whether a layer should take the gated call where it is supported: yes for the decode kernel; with the streaming kernels
 // while a weight matrix's active experts are small enough for the saved launch to count (16.8 MB, 256 rows of 512 x 2048:
 // 20 us against 25 in permute + row tiles; 134 MB, 64 rows on 32 experts of 1024 x 4096 8-bit: 64 and 68), or for at most
-// one row per expert on average (16 tokens on 32 experts of 2048 x 8192 8-bit: 142 and 151); otherwise the row tiles
+// one row per expert on average (16 tokens on 32 experts of 2048 x 8192 8-bit: 142 and 151), two with 8-bit weights and two experts
+// per token (128 rows on 64 experts of 1024 x 4096 93 and 100, 192 on 128 of 1024 x 2048 88 and 106); otherwise the row tiles
 // stream faster (64 tokens, 2048 x 8192: 4-bit 146 and 115, 8-bit 228 and 190).
 extern "C" int moe_grouped_ffn_wq_gated_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
 {
     using namespace moe;
     if (!gated_shapes(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
     const int R = T * k;
-    return decode_ffn_supports(R, E, d, F, bits) || R <= E || (double)E * d * F * bits / 8 <= 150e6;
+    return decode_ffn_supports(R, E, d, F, bits) || R <= E || (bits == 8 && k == 2 && R <= 2 * E) || (double)E * d * F * bits / 8 <= 150e6;
+}
+
+// Whether a layer should take the indexed call: for bf16 rows, which run in row tiles anyway, and for more rows than experts where
+// fc2 runs in row tiles.  Where a streaming kernel is the better one for fc2, permuted copies cost less than row tiles there
+// (48 tokens, two of two experts of 2048 x 2048, 8-bit: 29 against 43 us a step).
+extern "C" int moe_grouped_ffn_wq_indexed_pays(int R, int E, int max_rows_per_expert, int d, int F, int bits, int group_size, int act_dtype)
+{
+    using namespace moe;
+    if (R <= 0 || E <= 0 || d <= 0 || F <= 0) return 0;
+    if (act_dtype == MOE_BF16) return 1;
+    const int max_rows = max_rows_per_expert > 0 && max_rows_per_expert < R ? max_rows_per_expert : R;
+    const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
+    return R > E && four_call_kernel(R, E, max_rows, F, d, bits, grouped ? SCALE_GROUP : SCALE_CHANNEL, false) == GEMM_TILED;
 }
 
 extern "C" int moe_grouped_ffn_wq_gated_supported(int T, int k, int E, int d, int F, int bits, int group_size,

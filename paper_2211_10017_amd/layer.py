@@ -55,7 +55,7 @@ class MoEExpertLayer:
         self.routed = bool(fuse_routing) and B.moe_grouped_ffn_wq_routed_supported(R, E, T, d, F, bits, group_size, act_dtype)
         # ... and so for other sizes that run in row tiles, and for bf16 rows
         self._ffn_call = "moe_grouped_ffn_wq_routed"
-        if not self.routed and fuse_routing and R > 0 and (act_dtype == torch.bfloat16 or R > E):
+        if not self.routed and fuse_routing and B.moe_grouped_ffn_wq_indexed_pays(R, E, T, d, F, bits, group_size, act_dtype):
             self.routed, self._ffn_call = True, "moe_grouped_ffn_wq_indexed"
         # decode-sized batches: the permutation is rebuilt inside fc1 (no permute launch, no x_perm copy)
         self.gated = 0

@@ -28,3 +28,30 @@ def test_permute_shares_its_work_by_the_number_of_assignments():
     for (R, E, waves, blocks), copies, index in zip(cases, L.record([L.permute(R, 1, E, 1024) for R, E, _, _ in cases]), L.record([L.permute(R, 1, E) for R, E, _, _ in cases])):
         assert [(p.block, p.grid[0]) for p in copies.launches] == [(64 * waves, blocks)], (R, E)
         assert [(p.block, p.grid[0]) for p in index.launches] == [(64 * waves, 1)] and index.launches[0].shared <= 64 * 1024
+
+
+def _kernels(call):
+    return [p.kernel.split("<")[0] for p in call.launches if not p.kernel.startswith("rows_to_f16")]
+
+
+def test_ffn_streams_where_streaming_is_the_faster_way():
+    """The pair of GEMMs of permuted rows, several rows per expert: the streaming kernels for few row groups in all, few experts
+    and small weights; row tiles where the experts' weights would be read more than once from memory or many tiles are there."""
+    u, s, ring = "stream_unrolled_kernel", "stream_gemm_kernel", "grouped_gemm_ring_kernel"
+    cases = [((40, 8, 1024, 4096, 4), [u, u]), ((40, 1, 1024, 4096, 4), [u, u]), ((64, 2, 512, 2048, 8), [u, u]), ((64, 1, 2048, 8192, 8), [u, s]),
+             ((8, 1, 2048, 8192, 4), [u, s]), ((128, 4, 1024, 1024, 8), [u, u]), ((200, 128, 512, 512, 8), [u, u]),
+             ((256, 16, 1024, 4096, 4), [ring, ring]), ((64, 32, 4096, 16384, 8), [ring, ring]), ((128, 32, 1024, 4096, 8), [u, ring]),
+             ((128, 16, 2048, 8192, 4), [u, ring]),
+             ((20, 32, 1024, 4096, 4), [u, u]), ((20, 32, 2048, 8192, 8), [u, s]), ((3, 4, 4096, 16384, 8), [s, s])]       # at most a row per expert: always
+    for (sizes, want), call in zip(cases, L.record([L.ffn(*c) for c, _ in cases])):
+        assert call.rc == 0 and _kernels(call) == want, (sizes, _kernels(call))
+
+
+def test_layers_fetch_through_the_index_where_fc2_runs_in_row_tiles():
+    lib = B.load()
+    pays = lambda R, E, T, d, F, bits, g=0, act=B.MOE_F16: lib.moe_grouped_ffn_wq_indexed_pays(R, E, T, d, F, bits, g, act)  # noqa: E731
+    assert pays(128, 32, 128, 1024, 4096, 8) and pays(384, 32, 192, 1024, 4096, 4) and pays(128, 64, 64, 4096, 16384, 4, 128)
+    assert not pays(96, 2, 48, 2048, 2048, 8) and not pays(20, 32, 20, 1024, 4096, 8) and not pays(0, 32, 0, 1024, 4096, 8)
+    assert pays(1, 32, 1, 1024, 4096, 8, 0, B.MOE_BF16)
+    gated = lib.moe_grouped_ffn_wq_gated_pays
+    assert gated(64, 2, 64, 1024, 4096, 8, 0, B.MOE_F16) and not gated(64, 2, 32, 2048, 8192, 4, 0, B.MOE_F16)
