@@ -7,17 +7,21 @@ namespace moe {
 // Rows per block of the kernel with the LDS ring, or 0 where register-fed tiles do as well or better (steps of a layer, register-fed
 // tiles against the ring).  Few rows per expert: the launch streams weights, and what counts is how much of them is in flight.
 // 16-row blocks up to ten rows per expert on average: 64 tokens, two of 32 experts, group scales: 1024 x 4096 84 and 60 us, 2048 x 8192
-// 188 and 141; 64 experts of 4096 x 16384 816 and 797; 500 tokens on 128 experts of 1024 x 4096 8-bit 260 and 228.  With 4-bit
-// weights and more than 512 rows a busy expert's 16-row tiles unpack its weights too often (500 tokens, skewed, 128 experts of
-// 2048 x 8192: 443 and 488), so these take 32-row blocks.
+// 188 and 141; 500 tokens on 128 experts of 1024 x 4096 8-bit 260 and 228.  With 4-bit weights, which cost more to unpack than to
+// read, only while there are too few tiles to hide that: 384 (a tile per expert and 256 channels), with one or two rows per expert
+// 512, and 1024 for long K loops.  (Shares of a call that the ring gains, fc1 / fc2: 192 to 256 tiles 3-27 / 5-38 %, 384 tiles -2 to 9 /
+// -3 to 19 %, 512 tiles and more than two rows per expert -7 to -3 / -6 to 2 %, skewed loads of 256 rows on 32 experts of 4096 x 16384, group
+// scales, -18 % of the call.)
 // 32-row blocks while the tiles alone do not fill the chip two to four times (240 tokens on 32 experts of 2048 x 8192: 201 and 154;
-// 1900 tokens on 128 of them: 578 and 671).  Beyond: only where 64-row tiles leave compute units without a block (fc2 of 500
+// 1900 tokens on 128 of them: 578 and 671), once with 8-bit weights and 29 to 32 rows per expert, where half of the experts take a second
+// block (1024 rows on 32 experts of 2048 x 8192: 237 and 267; 64 on two: 85 and 60).  Beyond: only where 64-row tiles leave compute units without a block (fc2 of 500
 // tokens on 32 experts of 1024 x 4096, 126 tiles: 41 and 28 us; with 264 tiles of 2048 x 8192 98 and 103).
 static int ring_rows(const GemmArgs &p, int bits, int mean)
 {
     const long experts = p.E < p.R ? p.E : p.R, ncol = (p.N + 255) / 256;
-    if (mean <= 10 && (bits == 8 || p.R <= 512)) return 16;
-    if (mean <= 32) return ((long)p.R / 32 + experts / 2) * ncol <= (mean <= 16 ? 1024 : 512) ? 32 : 0;
+    if (mean <= 10 && bits == 8) return 16;
+    if (mean <= 10 && p.R <= 512) return experts * ncol <= (mean > 2 ? 384 : p.K > 4096 ? 1024 : 512) ? 16 : 0;
+    if (mean <= 32) return ((long)p.R / 32 + experts / 2) * ncol <= (mean <= 16 ? 1024 : mean > 28 && bits == 8 ? 256 : 512) ? 32 : 0;
     return ((long)p.R / 64 + experts / 2) * ncol <= 224 ? 64 : 0;
 }
 

@@ -55,3 +55,24 @@ def test_layers_fetch_through_the_index_where_fc2_runs_in_row_tiles():
     assert pays(1, 32, 1, 1024, 4096, 8, 0, B.MOE_BF16)
     gated = lib.moe_grouped_ffn_wq_gated_pays
     assert gated(64, 2, 64, 1024, 4096, 8, 0, B.MOE_F16) and not gated(64, 2, 32, 2048, 8192, 4, 0, B.MOE_F16)
+
+
+def _rows_of_tiles(call):
+    """Rows per block of each GEMM in row tiles, negative in the register-fed kernel."""
+    out = []
+    for p in call.launches:
+        name, args = p.kernel.split("<")[0], p.kernel.split("<")[1].rstrip(">").split(", ")
+        if name == "grouped_gemm_ring_kernel":
+            out.append(int(args[2]))
+        elif name == "grouped_gemm_kernel":
+            out.append(-32 * int(args[2]))
+    return out
+
+
+def test_register_fed_tiles_where_the_ring_unpacks_too_often():
+    """4-bit weights, few rows per expert, many tiles; and 8-bit weights with 29 to 32 rows per expert."""
+    cases = [((64, 32, 1024, 4096, 4, 128), [16, 16]), ((256, 32, 2048, 8192, 4, 128), [-32, 16]), ((256, 32, 4096, 16384, 4, 128), [-32, -32]),
+             ((128, 64, 4096, 16384, 4, 128), [-32, 16]), ((512, 128, 1024, 4096, 4, 128), [-32, -32]), ((500, 128, 1024, 4096, 8, 128), [16, 16]),
+             ((1024, 32, 2048, 8192, 8, 128), [-32, -32]), ((64, 2, 2048, 8192, 8, 128), [32, 32]), ((384, 16, 1024, 4096, 8, 128), [32, 32])]
+    for (sizes, want), call in zip(cases, L.record([L.ffn(*c) for c, _ in cases])):
+        assert _rows_of_tiles(call) == want, (sizes, call.launches)
