@@ -60,7 +60,8 @@ enum { MOE_ACT_RELU = 0, MOE_ACT_GELU = 1 };
 const char *moe_last_error(void);
 
 /* Names of the GEMM kernels that the last moe_grouped_ffn_wq* call on this thread launched, fc1
- * first, separated by a blank ("" before the first call); for measurement reports. */
+ * first, separated by a blank ("" before the first call); for measurement reports.  Row tiles are
+ * grouped_gemm_kernel or, with their weights and rows in a ring in LDS, grouped_gemm_ring_kernel. */
 const char *moe_last_ffn_kernels(void);
 
 /* What the current device reports (HOST pointers, any may be NULL): compute units, engine and

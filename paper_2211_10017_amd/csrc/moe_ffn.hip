@@ -183,11 +183,11 @@ static int run_gemm(moe::GemmArgs g, int bits, int smode, bool bf, bool tiles_on
     const GemmKernel kernel = tiles_only                ? GEMM_TILED
                               : g.gate_idx || g.out_add ? choose_kernel(g.R, g.E, max_rows, g.K, g.N, bits, smode, bf)
                                                         : four_call_kernel(g.R, g.E, max_rows, g.K, g.N, bits, smode, bf);
-    note_kernel(kernel == GEMM_STREAM_UNROLLED ? "stream_unrolled_kernel" : kernel == GEMM_STREAM_LOOP ? "stream_gemm_kernel" : "grouped_gemm_kernel");
+    if (kernel != GEMM_TILED) note_kernel(kernel == GEMM_STREAM_UNROLLED ? "stream_unrolled_kernel" : "stream_gemm_kernel");
     if (kernel == GEMM_STREAM_UNROLLED) return launch_stream_unrolled(g, bits, max_rows, s);
     if (g.gate_idx || g.out_add) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_gated: K=%d does not run in the straight-line kernel with these sizes", g.K);
     if (kernel == GEMM_STREAM_LOOP) return launch_stream_gemm(g, bits, smode, max_rows, s);
-    // Everything else runs in the tiled kernel, experts with a handful of rows included: their tiles skip
+    // Everything else runs in row tiles, experts with a handful of rows included: their tiles skip
     // the row blocks that hold no rows and stream the weights as fast as the streaming kernel would
     // (sending them there in a launch of their own measured 2-25 % slower on skewed loads).
     return launch_tiled_gemm(g, bits, smode, s);

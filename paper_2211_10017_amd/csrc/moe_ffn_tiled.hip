@@ -29,7 +29,9 @@ int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
 {
     // row-tile height from the mean rows per expert (the offsets themselves stay on the device)
     const int mean = (p.R + p.E - 1) / p.E;
-    if (const int bm = ring_rows(p, bits, mean)) {
+    const int bm = ring_rows(p, bits, mean);
+    note_kernel(bm ? "grouped_gemm_ring_kernel" : "grouped_gemm_kernel");
+    if (bm) {
         const long slots = (long)p.R / bm + (p.E < p.R ? p.E : p.R);
         const long wgs = (slots * ((p.N + 127) / 128) + kXcds - 1) / kXcds * kXcds;      // upper bound of the work items, whole rounds of XCDs
         if (wgs > 0x7fffffffL) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq: %ld workgroups exceed one launch", wgs);

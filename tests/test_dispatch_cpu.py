@@ -76,3 +76,14 @@ def test_register_fed_tiles_where_the_ring_unpacks_too_often():
              ((1024, 32, 2048, 8192, 8, 128), [-32, -32]), ((64, 2, 2048, 8192, 8, 128), [32, 32]), ((384, 16, 1024, 4096, 8, 128), [32, 32])]
     for (sizes, want), call in zip(cases, L.record([L.ffn(*c) for c, _ in cases])):
         assert _rows_of_tiles(call) == want, (sizes, call.launches)
+
+
+def test_noted_kernels_are_the_ones_launched():
+    """moe_last_ffn_kernels names every GEMM kernel that the call launches, in order, the two kinds of row tiles told apart."""
+    cases = [L.ffn(64, 32, 1024, 4096, 8), L.ffn(2000, 8, 1024, 4096, 4), L.ffn(1024, 32, 2048, 8192, 8), L.ffn(250, 4, 512, 2048, 4, 128, B.MOE_BF16),
+             L.ffn(40, 1, 2048, 8192, 8), L.indexed(500, 32, 1, 1024, 4096, 4), L.indexed(9000, 16, 2, 1024, 2048, 4, 128, B.MOE_BF16)]
+    seen = set()
+    for call in L.record(cases):
+        assert call.rc == 0 and call.noted == " ".join(_kernels(call))
+        seen |= set(_kernels(call))
+    assert seen == {"stream_unrolled_kernel", "stream_gemm_kernel", "grouped_gemm_kernel", "grouped_gemm_ring_kernel"}

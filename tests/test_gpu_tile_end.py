@@ -31,7 +31,7 @@ def test_tile_end_matches_oracle_in_every_output_type(act, bits, g, activation, 
         y[dt] = B.moe_grouped_ffn_wq(x, to_dev(off, torch.int32), E, d, F, bits, g, p1, s1, p2, s2, b1=b1, b2=b2, y_dtype=dt,
                                      activation=activation)
         torch.cuda.synchronize()
-    assert B.load().moe_last_ffn_kernels().decode() == "grouped_gemm_kernel grouped_gemm_kernel"
+    assert B.load().moe_last_ffn_kernels().decode() == "grouped_gemm_ring_kernel grouped_gemm_ring_kernel"
     # the 16-bit outputs are the fp32 one, rounded to nearest even: bit for bit
     assert torch.equal(y[torch.float16], y[torch.float32].half()) and torch.equal(y[torch.bfloat16], y[torch.float32].bfloat16())
     q1, o1 = oracle.quantize(w1, bits, g)

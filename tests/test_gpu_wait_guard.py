@@ -62,6 +62,6 @@ def test_counted_waits_equal_waiting_for_all_loads(rows, d, F, bits, g, y_dt, x_
     _, s2, p2 = B.moe_quantize_experts(w2, bits, g, want_canon=False)
     plain, kernels = _ffn(B.load(), x, off, R, E, d, F, bits, g, p1, s1, p2, s2, y_dt)
     other, kernels2 = _ffn(ctypes.CDLL(WAITALL), x, off, R, E, d, F, bits, g, p1, s1, p2, s2, y_dt)
-    assert kernels == kernels2 == "grouped_gemm_kernel grouped_gemm_kernel"      # both GEMMs in the tiled kernel
+    assert kernels == kernels2 == "grouped_gemm_ring_kernel grouped_gemm_ring_kernel"
     assert torch.isfinite(plain.float()).all()
     assert torch.equal(plain, other)
