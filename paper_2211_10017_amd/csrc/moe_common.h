@@ -6,6 +6,8 @@
 #include <stdint.h>
 #include <stdio.h>
 
+#include <atomic>
+
 #include "moe_wq.h"
 
 namespace moe {
@@ -18,6 +20,18 @@ int fail(int code, const char *fmt, ...);
 int check_launch(const char *what);
 void reset_kernel_notes();
 void note_kernel(const char *name);
+
+// More than 64 KB of dynamic LDS has to be asked for once per kernel and device (a function's attributes are those of the
+// current device).  `raised`: one bit per device, a static of the launcher; asking twice, from two threads, does no harm.  A
+// refusal shows up as the launch's error.
+inline void raise_lds_limit(const void *kernel, int bytes, std::atomic<uint64_t> &raised)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return;
+    const uint64_t bit = dev < 64 ? 1ull << dev : 0;
+    if (raised.load(std::memory_order_relaxed) & bit) return;
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess) raised.fetch_or(bit, std::memory_order_relaxed);
+}
 
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }

@@ -262,9 +262,8 @@ template <int BITS, int SMODE, int BM, int WC, int WK>
 static void launch_ring_shape(const GemmArgs &p, dim3 grid, hipStream_t s)
 {
     using S = RingShape<BITS, SMODE, BM, WC, WK>;
-    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(&grouped_gemm_ring_kernel<BITS, SMODE, BM, WC, WK>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, S::kLds);
-    (void)raised;
+    static std::atomic<uint64_t> raised;
+    raise_lds_limit(reinterpret_cast<const void *>(&grouped_gemm_ring_kernel<BITS, SMODE, BM, WC, WK>), S::kLds, raised);
     hipLaunchKernelGGL((grouped_gemm_ring_kernel<BITS, SMODE, BM, WC, WK>), grid, dim3(64 * WC * WK), S::kLds, s, p);
 }
 

@@ -544,9 +544,8 @@ static void launch_gate_mfma(const uint16_t *x, const uint16_t *wg, const float 
                                  int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
 {
     const size_t smem = (size_t)4 * 16 * TT * (S * 16 * NB + 4) * sizeof(float);
-    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void *>(&gate_mfma_kernel<BF16, NB, S, TT, R, LOADS>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
-    (void)raised;
+    static std::atomic<uint64_t> raised;
+    raise_lds_limit(reinterpret_cast<const void *>(&gate_mfma_kernel<BF16, NB, S, TT, R, LOADS>), 144 * 1024, raised);
     hipLaunchKernelGGL((gate_mfma_kernel<BF16, NB, S, TT, R, LOADS>), dim3((T + 16 * TT - 1) / (16 * TT)), dim3(256 * S), smem, s, x, wg, bias,
                        finished, T, d, E, k, renorm, expert_idx, expert_scale);
 }

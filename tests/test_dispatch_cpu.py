@@ -87,3 +87,15 @@ def test_noted_kernels_are_the_ones_launched():
         assert call.rc == 0 and call.noted == " ".join(_kernels(call))
         seen |= set(_kernels(call))
     assert seen == {"stream_unrolled_kernel", "stream_gemm_kernel", "grouped_gemm_kernel", "grouped_gemm_ring_kernel"}
+
+
+def test_lds_limits_are_raised_on_every_device():
+    """A kernel that needs more than the default 64 KB of dynamic LDS asks for it once on each device that it runs on."""
+    calls = [L.gate(9000, 512, 256), L.ffn(592, 4, 256, 320, 8), L.ffn(40, 1, 2048, 8192, 8)]
+    rows = L.record([(*c, dev) for dev in (0, 1, 0, 5) for c in calls])
+    for i in range(len(calls)):
+        first, second, again, other = rows[i], rows[i + len(calls)], rows[i + 2 * len(calls)], rows[i + 3 * len(calls)]
+        big = {p.kernel for p in first.launches if p.shared > 64 * 1024}
+        assert big and big <= {k for k, _ in first.raised}
+        assert [k for k, _ in second.raised] == [k for k, _ in first.raised] == [k for k, _ in other.raised] and not again.raised
+        assert {d for _, d in second.raised} == {1} and {d for _, d in other.raised} == {5}
