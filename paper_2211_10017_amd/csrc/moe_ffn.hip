@@ -279,7 +279,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
         if (rc) return rc;
         g1.a = x16;
     }
-    // (groups of 128: exact codes, group sums folded in fp32; other group sizes: the two-term form)
+    // (groups of 128: exact codes, group sums folded in fp32; other group sizes: the two-term form, in the LDS ring exact codes as well)
     const int smode1 = !grouped ? SCALE_CHANNEL : !bf ? SCALE_GROUP : group_size == 128 ? SCALE_GROUP_ACC : SCALE_GROUP_SPLIT;
     int rc = run_gemm(g1, bits, smode1, bf, perm_src != nullptr, max_rows, s);
     if (rc) return rc;

@@ -1,4 +1,5 @@
-// Grouped GEMM kernels with an LDS ring for 4-bit weights.
+// Grouped GEMM kernels with an LDS ring for 4-bit weights.  The forms that keep group scales out of the FP16 weights are one here:
+// exact codes, sums folded once per group, for every group size (a multiple of the K step).
 #include "moe_ffn_ring_kernel.h"
 
 namespace moe {

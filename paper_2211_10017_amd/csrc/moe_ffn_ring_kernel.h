@@ -1,13 +1,14 @@
 // Grouped GEMM with fused dequantisation for launches with few rows per expert or few row tiles (Sec. 3.3,
 // Sec. 3.4): the packed weights, the group scales and the activation rows all go from memory straight
-// into a ring of LDS stages, several K steps ahead.
+// into a ring of two to four LDS stages, up to three K steps ahead.
 //
 // Such a launch is bound by how many bytes it keeps in flight (few rows per expert: it streams weights), or, with
 // about one tile per compute unit, by the latency of what a lone wavefront per SIMD waits for.  Loads into
 // registers can be one or two steps ahead at most (moe_ffn_tiled_kernel.h); loads into LDS need no registers,
-// are counted by hand, and NST - 1 stages of them stay in flight.  The K range is split over WK groups of
-// wavefronts of the block, whose partial tiles meet in LDS at the end, added in the order of K: twice the blocks,
-// each with half the chain of K steps.
+// are counted by hand, and NST - 1 stages of them stay in flight: three with 16-row blocks (two with 8-bit weights and group scales), two
+// with taller ones, one with 64-row blocks of 8-bit weights, whose stage is 32 KB of the 80 KB that two blocks per compute unit
+// leave each.  The K range is split over the two pairs of wavefronts of the block, whose partial tiles meet in LDS at the end, added
+// in the order of K: twice the blocks, each with half the chain of K steps.
 //
 // Block: 2 x 2 wavefronts; wavefront (wc, kp) computes BM rows x 64 channels over the kp-th half of K.  A stage
 // holds, per K part, the rows' 64 K values (unpadded 128-byte rows, 16-byte chunks at position
@@ -25,8 +26,9 @@
 
 namespace moe {
 
-template <int BITS, int SMODE, int BM, int WC, int WK>
+template <int BITS, int SMODE, int BM>
 struct RingShape {
+    static constexpr int WC = 2, WK = 2;                            // wavefronts along the channels and along K
     static constexpr int NW = BITS == 4 ? 1 : 2;                    // fragment blocks per tile and 64-deep K step
     static constexpr int TM = BM < 32 ? 1 : BM / 32;                // 32-row matrix tiles (of a 16-row block the upper half repeats the lower)
     static constexpr int kWaves = WC * WK;
@@ -34,23 +36,22 @@ struct RingShape {
     static constexpr int kPartA = BM * 128;                         // bytes of one K part's rows in a stage
     static constexpr int kWaveB = 2 * NW * kFragBytes + (GROUPED ? 256 : 0);
     static constexpr int kStage = WK * kPartA + kWaves * kWaveB;
-    static constexpr int kReduce = WK > 1 ? kWaves * TM * 2 * 16 * 64 * 4 : 0;
+    static constexpr int kReduce = kWaves * TM * 2 * 16 * 64 * 4;
     // at the end the stages' space holds the partial tiles, then the patches of the tile end, and the row entries behind either
     static constexpr int kRows = kReduce > kWaves * kPatchBytes<16 / WK> ? kReduce : kWaves * kPatchBytes<16 / WK>;
     static constexpr int kEnd = kRows + (int)sizeof(TileRows<32 * TM>);
     // LDS of a compute unit (160 KB): three blocks where a block's share still holds three stages, else two
     static constexpr int kLimit = (BM > 32 || BITS == 8 ? 80 : 53) * 1024;
-    static constexpr int kFit = kLimit / kStage;
-    static constexpr int NST = kFit > 6 ? 6 : kFit;                 // stages
+    static constexpr int NST = kLimit / kStage;                     // stages
     static constexpr int kLds = NST * kStage > kEnd ? NST * kStage : kEnd;
-    static_assert(NST >= 2 && kLds <= kLimit, "a stage in use and at least one in flight");
+    static_assert(NST >= 2 && NST <= 4 && kLds <= kLimit, "a stage in use and one to three in flight (the chain of waits)");
 };
 
-template <int BITS, int SMODE, int BM, int WC, int WK>
-__global__ __launch_bounds__(64 * WC * WK, 2) void grouped_gemm_ring_kernel(GemmArgs p)
+template <int BITS, int SMODE, int BM>
+__global__ __launch_bounds__(256, 2) void grouped_gemm_ring_kernel(GemmArgs p)
 {
-    using S = RingShape<BITS, SMODE, BM, WC, WK>;
-    constexpr int TM = S::TM, NW = S::NW, NST = S::NST;
+    using S = RingShape<BITS, SMODE, BM>;
+    constexpr int TM = S::TM, NW = S::NW, NST = S::NST, WC = S::WC, WK = S::WK;
     constexpr bool GROUPED = S::GROUPED, ACC = SMODE == SCALE_GROUP_ACC;
     constexpr int D = NST - 1;                          // stages in flight
     constexpr int NA = BM / 8 > WC ? BM / 8 / WC : 1;   // row loads per wavefront and stage (8 rows each)
@@ -202,8 +203,6 @@ __global__ __launch_bounds__(64 * WC * WK, 2) void grouped_gemm_ring_kernel(Gemm
         for (int s = 0; s < per; ++s) {
             const int rem = min(per - 1 - s, D - 1);
             if (rem == D - 1) wait_loads<(D - 1) * L>();
-            else if (D > 4 && rem == 3) wait_loads<(D > 4) * 3 * L>();
-            else if (D > 3 && rem == 2) wait_loads<(D > 3) * 2 * L>();
             else if (D > 2 && rem == 1) wait_loads<(D > 2) * L>();
             else wait_loads<0>();
             __syncthreads();
@@ -212,7 +211,6 @@ __global__ __launch_bounds__(64 * WC * WK, 2) void grouped_gemm_ring_kernel(Gemm
             slot = slot + 1 == NST ? 0 : slot + 1;
         }
     };
-    static_assert(D <= 5, "the chain of waits above");
     if (TM == 1 || rows > 32) k_loop(std::integral_constant<int, TM>{});
     else k_loop(std::integral_constant<int, 1>{});
 
@@ -228,51 +226,46 @@ __global__ __launch_bounds__(64 * WC * WK, 2) void grouped_gemm_ring_kernel(Gemm
     __syncthreads();                                    // every wavefront is done with the ring
     TileRows<32 * TM> &tile_rows = *reinterpret_cast<TileRows<32 * TM> *>(lds + S::kRows);
     entry.put(tile_rows);
-    if constexpr (WK == 1) __syncthreads();
-    if constexpr (WK > 1) {
-        float *red = reinterpret_cast<float *>(lds);    // [wave][m][t][16][64]
+    float *red = reinterpret_cast<float *>(lds);    // [wave][m][t][16][64]
 #pragma unroll
-        for (int m = 0; m < TM; ++m)
+    for (int m = 0; m < TM; ++m)
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) red[((wave * TM + m) * 2 + t) * 1024 + i * 64 + lane] = acc[m][t][i];
-        __syncthreads();
-        float v[TM][2][QN];
+            for (int i = 0; i < 16; ++i) red[((wave * TM + m) * 2 + t) * 1024 + i * 64 + lane] = acc[m][t][i];
+    __syncthreads();
+    float v[TM][2][QN];
 #pragma unroll
-        for (int m = 0; m < TM; ++m)
+    for (int m = 0; m < TM; ++m)
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int q = 0; q < QN; ++q) {
-                    const float *src = red + ((wc * TM + m) * 2 + t) * 1024 + (kp * QN + q) * 64 + lane;
-                    float sum = src[0];
+            for (int q = 0; q < QN; ++q) {
+                const float *src = red + ((wc * TM + m) * 2 + t) * 1024 + (kp * QN + q) * 64 + lane;
+                float sum = src[0];
 #pragma unroll
-                    for (int w = 1; w < WK; ++w) sum += src[(size_t)w * WC * TM * 2 * 1024];
-                    v[m][t][q] = sum;
-                }
-        __syncthreads();                                // the partial tiles have been read
-        if (tile_ok) finish_tile<TM, QN, 32 * TM>(p, v, tile_rows, cs, bias, rows, 8 * (QN / 4) * kp, ntile0 * 32, lds + wave * kPatchBytes<QN>);
-    } else {
-        if (tile_ok) finish_tile<TM, 16, 32 * TM>(p, acc, tile_rows, cs, bias, rows, 0, ntile0 * 32, lds + wave * kPatchBytes<16>);
-    }
+                for (int w = 1; w < WK; ++w) sum += src[(size_t)w * WC * TM * 2 * 1024];
+                v[m][t][q] = sum;
+            }
+    __syncthreads();                                // the partial tiles have been read
+    if (tile_ok) finish_tile<TM, QN, 32 * TM>(p, v, tile_rows, cs, bias, rows, 8 * (QN / 4) * kp, ntile0 * 32, lds + wave * kPatchBytes<QN>);
 }
 
-template <int BITS, int SMODE, int BM, int WC, int WK>
+template <int BITS, int SMODE, int BM>
 static void launch_ring_shape(const GemmArgs &p, dim3 grid, hipStream_t s)
 {
-    using S = RingShape<BITS, SMODE, BM, WC, WK>;
+    using S = RingShape<BITS, SMODE, BM>;
     static std::atomic<uint64_t> raised;
-    raise_lds_limit(reinterpret_cast<const void *>(&grouped_gemm_ring_kernel<BITS, SMODE, BM, WC, WK>), S::kLds, raised);
-    hipLaunchKernelGGL((grouped_gemm_ring_kernel<BITS, SMODE, BM, WC, WK>), grid, dim3(64 * WC * WK), S::kLds, s, p);
+    raise_lds_limit(reinterpret_cast<const void *>(&grouped_gemm_ring_kernel<BITS, SMODE, BM>), S::kLds, raised);
+    hipLaunchKernelGGL((grouped_gemm_ring_kernel<BITS, SMODE, BM>), grid, dim3(256), S::kLds, s, p);
 }
 
 template <int BITS, int SMODE>
 static void launch_ring_variants(const GemmArgs &p, int bm, dim3 grid, hipStream_t s)
 {
-    if (bm == 16) launch_ring_shape<BITS, SMODE, 16, 2, 2>(p, grid, s);
-    else if (bm == 32) launch_ring_shape<BITS, SMODE, 32, 2, 2>(p, grid, s);
-    else launch_ring_shape<BITS, SMODE, 64, 2, 2>(p, grid, s);
+    if (bm == 16) launch_ring_shape<BITS, SMODE, 16>(p, grid, s);
+    else if (bm == 32) launch_ring_shape<BITS, SMODE, 32>(p, grid, s);
+    else launch_ring_shape<BITS, SMODE, 64>(p, grid, s);
 }
 
 }  // namespace moe
