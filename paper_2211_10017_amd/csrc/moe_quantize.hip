@@ -82,7 +82,7 @@ __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const f
 
     // w / s, correctly rounded: with y = 1/s rounded to nearest and a quotient within one unit in the last place, one
     // residual step gives the correctly rounded quotient (Markstein); the first step makes it that accurate.  A scale of zero
-    // or infinity has codes of zero.
+    // has codes of zero, an infinite one as well, but for the infinite weights that it may come from (inf / inf: the lowest code).
     const bool finite = s <= 65504.0f;
     const float y = s != 0.0f && finite ? 1.0f / s : 0.0f, sd = finite ? s : 0.0f, lim = s != 0.0f ? (float)QMAX : 0.0f;
     auto code_of = [&](float x) __attribute__((always_inline)) {

@@ -1,6 +1,7 @@
 """Quantiser units at their edges: a unit shorter than, as long as and longer than the registers of the wavefronts that share it,
-units that do not fill a workgroup, both widths, with channels of zeros, of subnormal and of infinite scale.  Codes, scales
-and packed bytes are compared bit for bit; the packed bytes are unpacked on the host from the layout's definition."""
+units that do not fill a workgroup, both widths, with channels of zeros, of subnormal scales (some units and one unit in the last
+place), of a scale that rounds to zero and of infinite ones (from finite and from infinite weights).  Codes, scales and packed bytes
+are compared bit for bit; the packed bytes are unpacked on the host from the layout's definition."""
 import numpy as np
 import pytest
 import torch
@@ -33,11 +34,18 @@ def test_quantize_units_bit_exact(bits, g, E, K, N):
     rng = np.random.default_rng(K + N + bits)
     w = (rng.standard_normal((E, K, N)) * 0.02).astype(np.float32)
     w[0, :, 3] = 0.0
-    w[0, :, 5] *= np.float32(1e-6)                                  # subnormal scale
+    w[0, :, 4] *= np.float32(1e-3)                                  # subnormal scale
+    w[0, :, 5] = rng.integers(-2 * 7, 2 * 7 + 1, K) * np.float32(0.5) * np.float32(2.0 ** -24)      # the smallest one, with ties
+    w[0, 0::64, 5] = np.float32((2 ** (bits - 1) - 1) * 2.0 ** -24)
     w[0, :, 6] *= np.float32(1e-9)                                  # scale rounds to zero
+    w[0, :, 9] *= np.float32(1e9)                                   # infinite scale: codes of zero
+    w[0, 7, 10], w[0, K - 3, 10] = np.inf, -np.inf                  # ... from infinite weights, whose own code is the lowest
     w[E - 1, :, 8] = rng.integers(-2 * 7, 2 * 7 + 1, K) * np.float32(0.5) * np.float32(2.0 ** -6)      # ties
     w[E - 1, K // 2, 8] = np.float32((2 ** (bits - 1) - 1) * 2.0 ** -6)
     oq, os_ = oracle.quantize(w, bits, g)
+    oq[np.isinf(w)] = -(2 ** (bits - 1) - 1)                        # (inf / inf, which the oracle's C leaves undefined)
+    sc = os_.view(np.float16)[0]
+    assert (sc[:, [4, 5]] > 0).all() and (sc[:, [4, 5]] < 2.0 ** -14).all() and (sc[:, 6] == 0).all() and np.isinf(sc[:, 9]).all() and np.isinf(sc[[0, -1], 10]).all()
     canon, scales, packed = B.moe_quantize_experts(to_dev(w, torch.float32), bits, g)
     none, scales2, packed2 = B.moe_quantize_experts(to_dev(w, torch.float32), bits, g, want_canon=False)
     only, _, no_packed = B.moe_quantize_experts(to_dev(w, torch.float32), bits, g, want_packed=False)
