@@ -99,3 +99,46 @@ def test_lds_limits_are_raised_on_every_device():
         assert big and big <= {k for k, _ in first.raised}
         assert [k for k, _ in second.raised] == [k for k, _ in first.raised] == [k for k, _ in other.raised] and not again.raised
         assert {d for _, d in second.raised} == {1} and {d for _, d in other.raised} == {5}
+
+
+def test_every_form_of_the_row_tiles_is_in_the_two_build_comparison():
+    """The cases of test_gpu_wait_guard.py and test_gpu_ring.py run the kernels they say, and together every instance the library has."""
+    import torch
+
+    from test_gpu_ring import RING
+    from test_gpu_wait_guard import REGISTER_FED
+    fed = L.record([L.ffn(sum(c[0]), len(c[0]), *c[1:5], B._DT[c[5]]) for c in REGISTER_FED])
+    for case, call in zip(REGISTER_FED, fed):
+        assert [p.kernel for p in call.launches if p.kernel.startswith("grouped")][0] == case[6], case
+    ring = L.record([L.ffn(sum(c[0]), len(c[0]), *c[1:5], B._DT[{"f16": torch.float16, "bf16": torch.bfloat16}[c[5]]]) for c in RING])
+    ran = {p.kernel for call in fed + ring for p in call.launches}
+    modes, acc = (0, 1, 2), 3                      # per channel, per group, two-term; group sums
+    built = {f"grouped_gemm_kernel<{b}, {m}, {t}>" for b in (4, 8) for m in modes for t in (1, 2, 4)} | {f"grouped_gemm_kernel<{b}, {acc}, {t}>" for b in (4, 8) for t in (1, 2)}
+    built |= {f"grouped_gemm_ring_kernel<{b}, {m}, {bm}>" for b in (4, 8) for m in (0, 1, acc) for bm in (16, 32, 64)}
+    assert built <= ran, built - ran
+
+
+def test_the_oracle_comparisons_reach_every_kernel():
+    """Each GEMM kernel with its scale modes and tile heights is compared with the oracle, row by row, by some case of test_gpu_steps.py,
+    test_gpu_ring.py or test_gpu_tile_end.py."""
+    import test_gpu_ring
+    import test_gpu_steps
+    import test_gpu_tile_end
+
+    def params(test, i=0):
+        return test.pytestmark[i].args[1]
+    bf = {"f16": B.MOE_F16, "bf16": B.MOE_BF16}
+    calls = [L.ffn(sum(p[0]), len(p[0]), *p[1:5], bf[p[5]]) for p in params(test_gpu_steps.test_grouped_ffn_matches_oracle)]
+    calls += [L.ffn(sum(p[0]), len(p[0]), *p[1:4], bound=max(p[0])) for p in params(test_gpu_steps.test_grouped_ffn_with_a_row_bound_matches_oracle)]
+    calls += [L.ffn(sum(r[0]), len(r[0]), r[1], r[2], a[1], a[2], bf[a[0]]) for r in params(test_gpu_tile_end.test_tile_end_matches_oracle_in_every_output_type)
+              for a in params(test_gpu_tile_end.test_tile_end_matches_oracle_in_every_output_type, 1)]
+    ring = test_gpu_ring.test_ring_gemm_matches_oracle
+    calls += [L.ffn(sum(r), len(r), *df, a[1], a[2], bf[a[0]]) for r in params(ring, 2) for df in params(ring, 1) for a in params(ring, 0)]
+    launched = L.record(calls)
+    assert all(c.rc == 0 for c in launched)
+    ran = {p.kernel.split(", false")[0] for c in launched for p in c.launches}
+    fed = {f"grouped_gemm_kernel<{b}, {m}, {t}>" for b, m, t in [(4, 0, 1), (4, 2, 1), (8, 1, 1), (8, 3, 1), (8, 0, 2), (4, 1, 2), (8, 2, 2), (4, 3, 2), (4, 0, 4), (4, 1, 4),
+                                                                 (4, 2, 4), (8, 0, 4), (8, 1, 4), (8, 2, 4)]}
+    ring = {f"grouped_gemm_ring_kernel<{b}, {m}, {bm}>" for b, m in [(4, 0), (8, 0), (4, 1), (8, 1), (8, 3), (4, 3)] for bm in (16, 32, 64)}
+    stream = {"stream_gemm_kernel<4>", "stream_gemm_kernel<8>"} | {f"stream_unrolled_kernel<{b}, {kb}, {t}, {s}" for b in (4, 8) for kb, t, s in [(16, 1, 1), (32, 1, 1), (48, 1, 1), (64, 2, 4)]}
+    assert fed | ring | stream <= ran, (fed | ring | stream) - ran

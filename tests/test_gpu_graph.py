@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T,k,E,d,F,bits", [(64, 2, 32, 1024, 1024, 4),      # the decode kernel and its slice reduction
-                                            (48, 2, 16, 256, 512, 8)])       # gate, permute, streaming FFN, combine
+                                            (48, 2, 16, 256, 512, 8)])       # gate, permute, fc1 in row tiles, fc2 streaming, combine
 def test_layer_step_replays_from_a_graph(T, k, E, d, F, bits):
     print(f"graph replay T={T} k={k} E={E} d={d} F={F} bits={bits}", flush=True)
     rng = np.random.default_rng(5 + T)

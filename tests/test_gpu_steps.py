@@ -171,22 +171,32 @@ def _ffn_case(rows_per_expert, d, F, bits, g, act, y_dt, seed, with_bias=False, 
     ([9, 200, 0, 45], 256, 512, 4, 128, "bf16", torch.float32),
     ([64, 3], 128, 192, 8, 0, "bf16", torch.float32),
     ([150, 20], 256, 256, 4, 64, "bf16", torch.float32),
-    ([300, 70, 129], 256, 320, 8, 0, "f16", torch.float16),        # tallest 8-bit tiles (weights fetched one step ahead), rows dealt 96+96+96+12
+    ([300, 70, 129], 256, 320, 8, 0, "f16", torch.float16),        # several 64-row blocks per expert (the ring: few tiles)
     ([290, 131], 128, 192, 8, 0, "bf16", torch.float32),
-    ([270, 257, 1], 192, 256, 4, 0, "f16", torch.float32),          # balanced row tiles: 96+96+78 and 96+96+65
+    ([270, 257, 1], 192, 256, 4, 0, "f16", torch.float32),          # rows dealt evenly to an expert's blocks
     ([2, 11, 5], 256, 2048, 8, 0, "f16", torch.float16),            # fc2 splits K over the wavefronts, two channel tiles per block
-    # K above 2048 and many rows per expert: the 128-row tiles (shorter K loops and 8-bit weights up to 256 rows run 64-row tiles)
+    # K above 2048 and many rows per expert, few tiles: the ring's 64-row blocks over long K loops
     ([270, 257, 1], 2112, 2176, 4, 0, "f16", torch.float32),
-    ([300, 270, 259], 2112, 2176, 8, 0, "f16", torch.float16),      # tallest 8-bit tiles: weights fetched one step ahead
+    ([300, 270, 259], 2112, 2176, 8, 0, "f16", torch.float16),
     ([300, 280], 2112, 2176, 8, 64, "f16", torch.float32),
     ([290, 300], 2112, 2112, 8, 0, "bf16", torch.float32),
-    ([150, 120], 2112, 2112, 4, 64, "bf16", torch.float32),         # two-term group scales in 128-row tiles
-    # 4-bit weights, group scales, fp16 rows, K above 2048 in both GEMMs, more than 64 rows per expert on
-    # average: the 128-row tiles with a scale per group (the variant the largest workload's fp16 pass runs),
-    # every row compared; rows dealt 96+96+78, 96+96+65 and 96+34
+    ([150, 120], 2112, 2112, 4, 64, "bf16", torch.float32),
     ([270, 257, 130], 2112, 2176, 4, 64, "f16", torch.float16),
     ([270, 257, 130], 2176, 2304, 4, 128, "f16", torch.float32),
-    ([129, 288, 1, 256], 2304, 2176, 4, 128, "f16", torch.float16), # 128 + 1 rows; nine 32-row units in three tiles; one row; two full tiles
+    ([129, 288, 1, 256], 2304, 2176, 4, 128, "f16", torch.float16), # 128 + 1 rows; one row; two full tiles
+    # fc2 in the run-loop streaming kernel (fc1 in the straight-line one): one expert with many row groups, and at most a row per expert
+    ([40], 2048, 8192, 8, 0, "f16", torch.float32), ([9], 2048, 8192, 4, 0, "f16", torch.float32),
+    ([1, 0, 2, 0, 1], 512, 8192, 8, 0, "f16", torch.float32),
+    # so many tiles in fc1 that it runs register-fed ones: 32, 64 and 128 rows, per channel, per group, two-term group scales
+    # (bf16, groups of 64) and group sums (bf16, groups of 128; 128-row tiles are not built)
+    ([20] * 40 + [0, 33], 192, 2752, 4, 0, "f16", torch.float32), ([20] * 40 + [0, 33], 192, 2688, 8, 64, "f16", torch.float16),
+    ([20] * 40 + [0, 33], 192, 2688, 4, 64, "bf16", torch.float32), ([20] * 40 + [0, 33], 256, 2816, 8, 128, "bf16", torch.float32),
+    ([60, 50, 33, 5] * 4, 256, 3392, 8, 0, "f16", torch.float32), ([60, 50, 33, 5] * 4, 192, 3392, 4, 64, "f16", torch.float32),
+    ([60, 50, 33, 5] * 4, 192, 3392, 8, 64, "bf16", torch.float32), ([60, 50, 33, 5] * 4, 256, 3456, 4, 128, "bf16", torch.float32),
+    ([270, 257, 130, 20], 2112, 4736, 4, 0, "f16", torch.float32),  # rows dealt 96 + 96 + 78, 96 + 96 + 65 and 96 + 34
+    ([270, 257, 130, 20], 2176, 4736, 4, 64, "f16", torch.float32), ([270, 257, 130, 20], 2112, 4736, 4, 64, "bf16", torch.float32),
+    ([300, 290, 270], 2112, 4224, 8, 0, "f16", torch.float32),      # tallest 8-bit tiles: weights fetched one step ahead
+    ([300, 290, 270], 2112, 4224, 8, 64, "bf16", torch.float32),
 ])
 def test_grouped_ffn_matches_oracle(rows, d, F, bits, g, act, y_dt):
     _say(f"ffn rows={rows} d={d} F={F} bits={bits} g={g} {act} y={y_dt}")
@@ -228,12 +238,11 @@ def test_grouped_ffn_bf16_rows_of_any_magnitude(bits, g):
 
 
 @pytest.mark.parametrize("rows,d,F,bits", [
-    # a row bound of at most 64, but several row groups per expert and enough row tiles to fill the chip: the tiled kernel
+    # a row bound of at most 64, but several row groups per expert: row tiles
     ([40, 37, 44, 40, 1, 40, 39, 40, 64, 40, 33, 40], 1024, 4096, 4),
-    # fc1 in row tiles, fc2 (two column blocks: too few tiles) in the run-loop streaming kernel
     ([20] * 14, 512, 2560, 8),
-    # decode-sized: both GEMMs stream whatever the rows per expert
-    ([60, 64, 3], 1024, 4096, 4),
+    # few experts: both GEMMs stream whatever the rows per expert, in the straight-line kernel and (fc2 of the second) in the run-loop one
+    ([60, 64, 3], 1024, 4096, 4), ([60], 2048, 8192, 8),
 ])
 def test_grouped_ffn_with_a_row_bound_matches_oracle(rows, d, F, bits):
     _say(f"ffn with row bound rows={rows} d={d} F={F} bits={bits}")
@@ -258,8 +267,9 @@ def test_grouped_ffn_biases_few_rows():
 
 
 @pytest.mark.parametrize("rows,d,F,bits,g", [([5, 9], 1024, 4096, 4, 0),          # straight-line streaming kernels
-                                              ([7, 0, 16], 512, 8192, 8, 0),       # run-loop streaming kernel (fc2)
-                                              ([100, 260, 7], 256, 512, 4, 128)])  # tiled kernel, group scales
+                                              ([7, 0, 16], 512, 8192, 8, 0),       # fc2 in 16-row ring blocks over 128 K steps
+                                              ([1, 0, 2], 512, 8192, 8, 0),        # run-loop streaming kernel (fc2)
+                                              ([100, 260, 7], 256, 512, 4, 128)])  # row tiles, group scales
 def test_grouped_ffn_gelu(rows, d, F, bits, g):
     _say(f"ffn with GELU rows={rows} d={d} F={F} bits={bits} g={g}")
     got, want = _ffn_case(rows, d, F, bits, g, "f16", torch.float32, seed=9, with_bias=True, activation="gelu")
@@ -399,8 +409,10 @@ def test_grouped_gemm_matches_oracle(bits, native, K, N):
     (1500, 1, 4, 256, 512, 4, 128, torch.float32),
     # the fused un-permute storing 16-bit layer outputs
     (700, 1, 5, 128, 256, 4, 0, torch.float16), (650, 1, 3, 192, 320, 8, 0, torch.bfloat16),
-    # rows fetched through the routing index by the 128-row tiles with a scale per group (K above 2048, 4-bit)
-    (700, 1, 3, 2176, 2304, 4, 128, torch.float32), (400, 2, 3, 2112, 2176, 4, 64, torch.float32)])
+    # rows fetched through the routing index over long K loops (the ring's 64-row blocks)
+    (700, 1, 3, 2176, 2304, 4, 128, torch.float32), (400, 2, 3, 2112, 2176, 4, 64, torch.float32),
+    # ... by the register-fed 128-row tiles, and the un-permute in theirs
+    (700, 1, 3, 2176, 5504, 4, 128, torch.float32), (700, 1, 3, 5440, 2176, 4, 0, torch.float32)])
 def test_routed_ffn_matches_oracle(T, k, E, d, F, bits, g, o_dt):
     _say(f"routed ffn T={T} k={k} E={E} d={d} F={F} bits={bits} g={g} out={o_dt}")
     rng = np.random.default_rng(T + E + bits)

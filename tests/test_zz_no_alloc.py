@@ -46,7 +46,7 @@ def _run_both(c):
 
 def test_noalloc_ffn_equals_the_workspace_entry_point_on_two_calls_in_a_row():
     assert B.load().moe_grouped_ffn_wq_noalloc_max_bytes() == 8 << 20
-    big = _case([5, 0, 33, 1, 70, 9], 256, 1024, 4, 0, seed=21)       # tiled kernel, 118 rows of F = 1024
+    big = _case([5, 0, 33, 1, 70, 9], 256, 1024, 4, 0, seed=21)       # row tiles, 118 rows of F = 1024
     small = _case([3, 4, 0, 2], 1024, 2048, 4, 0, seed=22)            # decode-sized: the streaming kernels, 9 rows
     _run_both(big)
     _run_both(small)                                                   # h of the first call is still in the array
