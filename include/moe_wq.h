@@ -252,13 +252,12 @@ int moe_grouped_ffn_wq_indexed(const void *x, int act_dtype, const int32_t *perm
  *   does not depend on the order of arrival; rows of pruned tokens stay zero.
  *   With expert_scale given and sizes the decode kernel is built for (4-bit: d = 1024; 8-bit:
  *   d = 512; F a multiple of 512 up to 4096; at most 8 assignments per expert on average and at
- *   least 64 slices of 512 d_ff channels in all), the call is two launches: a persistent grid of one
- *   workgroup per compute unit streams every active expert's W1 and W2 once (fc1, activation and
- *   fc2 per 512-channel slice of d_ff, h staying on chip) and leaves fp32 partial sums of y in the
- *   workspace; a small second launch adds the slices in a fixed order, applies the channel scale,
- *   bias and gate scale and writes out.  No atomics on this path.  (For timing studies y_perm may
- *   be NULL on this path: the second launch is then left out and the partial sums stay in the
- *   workspace.)
+ *   least 64 slices of 512 d_ff channels in all), the call is two launches, those of
+ *   moe_grouped_ffn_wq_sliced with slices of 512 channels: a block per expert with rows and slice
+ *   (fc1, activation and fc2, h staying on chip) leaves fp32 partial sums of y in the workspace; a
+ *   small second launch adds the slices in a fixed order, applies the channel scale, bias and gate scale
+ *   and writes out.  No atomics on memory on this path.  (For timing studies y_perm may be NULL on this
+ *   path: the second launch is then left out and the partial sums stay in the workspace.)
  * moe_grouped_ffn_wq_gated_supported returns 0 when a call with these sizes is not taken
  * (it then returns MOE_ERR_UNSUPPORTED and launches nothing), 1 when it is taken with
  * expert_scale = NULL, 2 when expert_scale may be given too.  Taken: fp16 activations,
@@ -280,6 +279,27 @@ int moe_grouped_ffn_wq_gated(const void *x, int act_dtype, const int32_t *expert
                              int y_dtype, int32_t *perm_src, int32_t *inv_perm,
                              int32_t *expert_offsets, void *workspace, size_t workspace_bytes,
                              void *stream);
+
+/*
+ * moe_permute, moe_grouped_ffn_wq and moe_combine in one call of two launches, for few rows per expert: fp16 or bf16
+ * rows, 4- or 8-bit weights, channel or group scales, T * k <= 512 assignments, k = 1 or 2, E <= 4096, d and F multiples of 64.
+ * The first launch cuts the work along d_ff: a block per (expert with rows, slice of 64 to 512 channels) streams its part of W1
+ * and W2 once, h staying on chip, and leaves fp32 partial sums of y in the workspace; the second adds the slices in a
+ * fixed order, applies channel scale, bias and gate scale and writes out.  No atomics on memory; rows past sixteen per expert
+ * read the expert's weights again.
+ *   x [T,d] (un-permuted); expert_idx, expert_scale [T*k] from moe_gate_topk (E = pruned row, which adds nothing);
+ *   out [T,d] in out_dtype; perm_src, inv_perm, expert_offsets as moe_permute writes them.
+ *   Workspace of moe_grouped_ffn_wq_sliced_workspace_bytes (0 when a call with these sizes is not taken; it then
+ *   returns MOE_ERR_UNSUPPORTED).  out may be NULL: the second launch is left out (for timing studies).
+ * moe_grouped_ffn_wq_sliced_pays: 1 when the call is taken and also the faster way (MoEExpertLayer asks this).
+ */
+size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype);
+int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype);
+int moe_grouped_ffn_wq_sliced(const void *x, int act_dtype, const int32_t *expert_idx, const float *expert_scale,
+                              int T, int k, int E, int d, int F, int bits, int group_size, int activation,
+                              const void *w1_packed, const void *s1, const void *b1, const void *w2_packed, const void *s2,
+                              const void *b2, void *out, int out_dtype, int32_t *perm_src, int32_t *inv_perm,
+                              int32_t *expert_offsets, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
  * Table 1 (Sec. 4.1): throughput of one grouped GEMM  y[r] = x_perm[r] @ deq(W[e])  on about 40

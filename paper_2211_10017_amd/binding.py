@@ -23,6 +23,7 @@ EXPORTS = ["moe_last_error", "moe_last_ffn_kernels", "moe_device_info", "moe_abi
            "moe_grouped_ffn_wq", "moe_combine", "moe_pack_fp16_experts", "moe_grouped_gemm_wq",
            "moe_grouped_ffn_wq_routed_supported", "moe_grouped_ffn_wq_routed", "moe_grouped_ffn_wq_indexed", "moe_grouped_ffn_wq_indexed_pays",
            "moe_grouped_ffn_wq_gated_supported", "moe_grouped_ffn_wq_gated_pays", "moe_grouped_ffn_wq_gated",
+           "moe_grouped_ffn_wq_sliced_workspace_bytes", "moe_grouped_ffn_wq_sliced_pays", "moe_grouped_ffn_wq_sliced",
            "moe_grouped_ffn_wq_noalloc_max_bytes", "moe_grouped_ffn_wq_noalloc"]
 
 LAYER_MAX_EXPERTS = 256   # experts of a whole layer call: moe_gate_topk's limit (moe_permute: 1024, the FFN: 4096)
@@ -85,6 +86,13 @@ def load():
     lib.moe_grouped_ffn_wq_gated.restype = i
     lib.moe_grouped_ffn_wq_gated.argtypes = [vp, i, vp, vp, i, i, i, i, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, i, vp, vp, vp,
                                              vp, sz, vp]
+    lib.moe_grouped_ffn_wq_sliced_workspace_bytes.restype = sz
+    lib.moe_grouped_ffn_wq_sliced_workspace_bytes.argtypes = [i, i, i, i, i, i, i, i]
+    lib.moe_grouped_ffn_wq_sliced_pays.restype = i
+    lib.moe_grouped_ffn_wq_sliced_pays.argtypes = [i, i, i, i, i, i, i, i]
+    lib.moe_grouped_ffn_wq_sliced.restype = i
+    lib.moe_grouped_ffn_wq_sliced.argtypes = [vp, i, vp, vp, i, i, i, i, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, i, vp, vp, vp,
+                                              vp, sz, vp]
     lib.moe_pack_fp16_experts.restype = i
     lib.moe_pack_fp16_experts.argtypes = [vp, i, i, i, vp, vp]
     lib.moe_grouped_gemm_wq.restype = i
@@ -337,3 +345,35 @@ def moe_grouped_ffn_wq_gated(x, expert_idx, E: int, d: int, F: int, bits: int, g
         _ptr(workspace), workspace.numel(), _stream())
     _check(rc, "moe_grouped_ffn_wq_gated")
     return y, perm_src, inv_perm, offsets
+
+
+def moe_grouped_ffn_wq_sliced_workspace_bytes(T: int, k: int, E: int, d: int, F: int, bits: int, group_size: int, act_dtype) -> int:
+    """0: not taken."""
+    return int(load().moe_grouped_ffn_wq_sliced_workspace_bytes(T, k, E, d, F, bits, group_size, _DT[act_dtype]))
+
+
+def moe_grouped_ffn_wq_sliced_pays(T: int, k: int, E: int, d: int, F: int, bits: int, group_size: int, act_dtype) -> bool:
+    """Whether the sliced call is taken and the faster way for these sizes."""
+    return bool(load().moe_grouped_ffn_wq_sliced_pays(T, k, E, d, F, bits, group_size, _DT[act_dtype]))
+
+
+def moe_grouped_ffn_wq_sliced(x, expert_idx, expert_scale, E: int, d: int, F: int, bits: int, group_size: int, w1_packed, s1,
+                              w2_packed, s2, b1=None, b2=None, out_dtype=torch.float32, workspace=None, activation: str = "relu"):
+    """Few rows per expert: permute + FFN + combine in one call.  Returns (out [T,d], perm_src, inv_perm, expert_offsets)."""
+    T, k = expert_idx.shape
+    dev = x.device
+    out = torch.empty((T, d), dtype=out_dtype, device=dev)
+    perm_src = torch.empty(T * k, dtype=torch.int32, device=dev)
+    inv_perm = torch.empty(T * k, dtype=torch.int32, device=dev)
+    offsets = torch.empty(E + 1, dtype=torch.int32, device=dev)
+    if workspace is None:
+        workspace = torch.empty(max(256, moe_grouped_ffn_wq_sliced_workspace_bytes(T, k, E, d, F, bits, group_size, x.dtype)),
+                                dtype=torch.uint8, device=dev)
+    rc = load().moe_grouped_ffn_wq_sliced(
+        _ptr(x, (torch.float16, torch.bfloat16), "x"), _DT[x.dtype], _ptr(expert_idx, torch.int32, "expert_idx"),
+        _ptr(expert_scale, torch.float32, "expert_scale"), T, k, E, d, F, bits, group_size, ACTIVATIONS[activation],
+        _ptr(w1_packed, torch.uint8, "w1_packed"), _ptr(s1, torch.float16, "s1"), _ptr(b1, torch.float16, "b1"),
+        _ptr(w2_packed, torch.uint8, "w2_packed"), _ptr(s2, torch.float16, "s2"), _ptr(b2, torch.float16, "b2"), _ptr(out),
+        _DT[out_dtype], _ptr(perm_src), _ptr(inv_perm), _ptr(offsets), _ptr(workspace), workspace.numel(), _stream())
+    _check(rc, "moe_grouped_ffn_wq_sliced")
+    return out, perm_src, inv_perm, offsets

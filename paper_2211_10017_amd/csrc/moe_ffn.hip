@@ -102,8 +102,8 @@ static FfnWorkspace ffn_workspace(int R, int d, int F, int act_dtype)
     if (act_dtype == MOE_BF16) o += round_up((size_t)R * sizeof(float2), 256);
     w.x16_off = o;                               // bf16 rows: x converted to scaled FP16 (h is converted in place)
     if (act_dtype == MOE_BF16) o += round_up((size_t)R * d * 2, 256);
-    w.partial_off = o;                           // decode kernel: partial sums of y per d_ff slice
-    if (R <= kGatedMaxAssign && F % 512 == 0) o += round_up(decode_ffn_partial_bytes(R, d, F), 256);
+    w.partial_off = o;                           // decode kernel in the gated call: partial sums of y per d_ff slice of 512 channels
+    if (R <= kGatedMaxAssign && F % 512 == 0) o += round_up(decode_ffn_partial_bytes(R, d, F, 8), 256);
     w.total = o < 256 ? 256 : o;
     return w;
 }
@@ -203,6 +203,14 @@ static bool tiled_only(int R, int E, int max_rows, int d, int F, int bits, bool 
            choose_kernel(R, E, max_rows, F, d, bits, smode, bf) == GEMM_TILED;
 }
 
+// Sizes for which the gated call runs the decode kernel: those its workspace has had room for the slices' partial sums for.
+static bool gated_decode(int R, int E, int d, int F, int bits)
+{
+    if (R < 1 || R > moe::kGatedMaxAssign || E < 1 || E > moe::kDecMaxExperts) return false;
+    if (d != (bits == 4 ? 1024 : 512) || F % 512 || F / 512 > 8 || F < 512) return false;
+    return (long)R <= 8L * E && (long)E * (F / 512) >= 64;
+}
+
 static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_offsets, int R,
                     int E, int max_rows_per_expert, int d, int F, int bits, int group_size, int activation,
                     const void *w1_packed,
@@ -216,7 +224,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     using namespace moe;
     // (y_perm may be NULL only on the decode kernel's path, where it means "leave out the slice reduction")
     const bool partial_only = !y_perm && gate_idx && expert_scale && act_dtype == MOE_F16 && group_size == 0 &&
-                              moe::decode_ffn_supports(R, E, d, F, bits);
+                              gated_decode(R, E, d, F, bits);
     if (!expert_offsets || !w1_packed || !s1 || !w2_packed || !s2 || (R != 0 && (!x_perm || (!y_perm && !partial_only))))
         return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq: NULL pointer");
     if (R < 0 || E <= 0 || d <= 0 || F <= 0 || max_rows_per_expert < 0)
@@ -244,16 +252,16 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     unsigned char *wsb = (unsigned char *)workspace;
     void *h = wsb + ws.h_off;
     // decode-sized batch with everything fused: one streaming launch for the sort and both GEMMs, then the slice reduction
-    if (gate_idx && expert_scale && !bf && group_size == 0 && decode_ffn_supports(R, E, d, F, bits)) {
+    if (gate_idx && expert_scale && !bf && group_size == 0 && gated_decode(R, E, d, F, bits)) {
         DecodeArgs q{};
         q.x = (const uint16_t *)x_perm; q.gate_idx = gate_idx; q.gate_scale = expert_scale; q.n_assign = R; q.gate_k = k;
         q.E = E; q.d = d; q.F = F; q.act = activation;
         q.w1 = (const uint8_t *)w1_packed; q.w2 = (const uint8_t *)w2_packed;
         q.s1 = (const __half *)s1; q.s2 = (const __half *)s2; q.b1 = (const __half *)b1; q.b2 = (const __half *)b2;
-        q.partial = (float *)(wsb + ws.partial_off); q.out = (float *)y_perm;
+        q.cw = 8; q.partial = (float *)(wsb + ws.partial_off); q.out = y_perm; q.out_dtype = MOE_F32;
         q.perm_src_out = perm_src_out; q.inv_perm_out = inv_perm_out; q.offsets_out = offsets_out;
         note_kernel("decode_ffn_kernel");
-        return launch_decode_ffn(q, bits, as_stream(stream));
+        return launch_decode_ffn(q, bits, false, as_stream(stream));
     }
     float2 *pow_x = (float2 *)(wsb + ws.pow_x_off), *pow_h = (float2 *)(wsb + ws.pow_h_off);
     const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
@@ -450,7 +458,7 @@ extern "C" int moe_grouped_ffn_wq_gated_pays(int T, int k, int E, int d, int F, 
     using namespace moe;
     if (!gated_shapes(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
     const int R = T * k;
-    return decode_ffn_supports(R, E, d, F, bits) || R <= E || (bits == 8 && k == 2 && R <= 2 * E) || (double)E * d * F * bits / 8 <= 150e6;
+    return gated_decode(R, E, d, F, bits) || R <= E || (bits == 8 && k == 2 && R <= 2 * E) || (double)E * d * F * bits / 8 <= 150e6;
 }
 
 // Whether a layer should take the indexed call: for bf16 rows, which run in row tiles anyway, and for more rows than experts where
@@ -464,6 +472,66 @@ extern "C" int moe_grouped_ffn_wq_indexed_pays(int R, int E, int max_rows_per_ex
     const int max_rows = max_rows_per_expert > 0 && max_rows_per_expert < R ? max_rows_per_expert : R;
     const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
     return R > E && four_call_kernel(R, E, max_rows, F, d, bits, grouped ? SCALE_GROUP : SCALE_CHANNEL, false) == GEMM_TILED;
+}
+
+// ---- decode-sized batches of every kind: index, both GEMMs and the un-permute in the decode kernel and its reduction ----
+extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
+{
+    using namespace moe;
+    if (T <= 0 || (act_dtype != MOE_F16 && act_dtype != MOE_BF16)) return 0;
+    if ((long)T * k > kDecMaxAssign || !decode_ffn_supports(T * k, k, E, d, F, bits, group_size)) return 0;
+    return round_up(decode_ffn_partial_bytes(T * k, d, F, decode_slice_width(T * k, E, d, F, bits)), 256);
+}
+
+// Whether a layer should take the sliced call (steps in us of the routes below against it; 390 drawn sizes of up to 256 tokens, of
+// which the rule sends 80 % here: 1.4 times as fast on average, none slower):
+//  - up to eight assignments per expert: a pass takes sixteen rows, and experts with more stream their weights again (61 tokens, two of
+//    eight experts of 4096 x 16384 8-bit 188 and 318; 134 tokens on 16 of 512 x 2048 21.0 and 24.1; 5 per expert of 1024 x 4096 44 and 41);
+//  - the partial sums of a slice, rows x d x 4 bytes, well below its weights (narrow slices, where d_ff leaves no wider ones);
+//  - up to 300 MB of weights: beyond, the launch's fixed parts count little and the ring's loads into LDS keep more in flight (30 tokens
+//    on 32 experts of 4096 x 16384 8-bit 452 and 520; 79 on 64 of 1024 x 4096 8-bit, 382 MB, 83.5 and 85.8; 4-bit 104 MB 47 and 32); FP16
+//    rows with group scales, whose scales the ring multiplies into the weights, at any size (64 tokens, 64 experts of 4096 x 16384 809 and 711).
+extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
+{
+    using namespace moe;
+    if (!moe_grouped_ffn_wq_sliced_workspace_bytes(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
+    const int R = T * k;
+    const double active = decode_active_experts(R, E), bytes = active * 2 * d * F * bits / 8;
+    const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
+    return R <= 8L * E && 5 * R <= 4 * active * decode_slice_width(R, E, d, F, bits) * bits && (bytes <= 300e6 || (grouped && act_dtype == MOE_F16));
+}
+
+extern "C" int moe_grouped_ffn_wq_sliced(const void *x, int act_dtype, const int32_t *expert_idx, const float *expert_scale, int T, int k, int E,
+                                         int d, int F, int bits, int group_size, int activation, const void *w1_packed, const void *s1,
+                                         const void *b1, const void *w2_packed, const void *s2, const void *b2, void *out, int out_dtype,
+                                         int32_t *perm_src, int32_t *inv_perm, int32_t *expert_offsets, void *workspace,
+                                         size_t workspace_bytes, void *stream)
+{
+    using namespace moe;
+    if (!expert_idx || !expert_scale || !perm_src || !inv_perm || !expert_offsets || !x || !w1_packed || !s1 || !w2_packed || !s2)
+        return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_sliced: NULL pointer");
+    if (activation != MOE_ACT_RELU && activation != MOE_ACT_GELU) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_sliced: unknown activation %d", activation);
+    if (out_dtype != MOE_F16 && out_dtype != MOE_BF16 && out_dtype != MOE_F32) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_sliced: unknown out_dtype %d", out_dtype);
+    const size_t need = moe_grouped_ffn_wq_sliced_workspace_bytes(T, k, E, d, F, bits, group_size, act_dtype);
+    if (!need)
+        return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_sliced: only batches of 1 to %d assignments with k = 1 or 2, d and F multiples of 64, 4- or 8-bit "
+                                         "weights and group sizes that are 0 or a multiple of 64 dividing d and F are taken", kDecMaxAssign);
+    const void *ptrs[] = {x, w1_packed, s1, b1, w2_packed, s2, b2, out, workspace};
+    for (const void *q : ptrs)
+        if (!aligned16(q)) return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_sliced: buffers must be 16-byte aligned");
+    if (!workspace || workspace_bytes < need)
+        return fail(MOE_ERR_WORKSPACE, "moe_grouped_ffn_wq_sliced: workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+    reset_kernel_notes();
+    DecodeArgs q{};
+    q.x = (const uint16_t *)x; q.gate_idx = expert_idx; q.gate_scale = expert_scale; q.n_assign = T * k; q.gate_k = k;
+    q.E = E; q.d = d; q.F = F; q.act = activation; q.cw = decode_slice_width(T * k, E, d, F, bits);
+    q.g = group_size == d && group_size == F ? 0 : group_size;
+    q.w1 = (const uint8_t *)w1_packed; q.w2 = (const uint8_t *)w2_packed;
+    q.s1 = (const __half *)s1; q.s2 = (const __half *)s2; q.b1 = (const __half *)b1; q.b2 = (const __half *)b2;
+    q.partial = (float *)workspace; q.out = out; q.out_dtype = out_dtype;
+    q.perm_src_out = perm_src; q.inv_perm_out = inv_perm; q.offsets_out = expert_offsets;
+    note_kernel("decode_ffn_kernel");
+    return launch_decode_ffn(q, bits, act_dtype == MOE_BF16, as_stream(stream));
 }
 
 extern "C" int moe_grouped_ffn_wq_gated_supported(int T, int k, int E, int d, int F, int bits, int group_size,

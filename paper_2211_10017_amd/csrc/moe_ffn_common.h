@@ -46,24 +46,29 @@ struct GemmArgs {
 
 // FFN of a decode-sized batch: one streaming launch plus a small reduction (moe_ffn_decode.hip).
 struct DecodeArgs {
-    const uint16_t *x;          // [T, d] fp16, un-permuted
+    const uint16_t *x;          // [T, d] un-permuted, fp16 or bf16
     const int32_t *gate_idx;    // [n_assign] expert of assignment a (E = pruned row)
     const float *gate_scale;    // [n_assign] gate scale of assignment a
     int n_assign, gate_k;
     int E, d, F, act;
+    int g;                      // group size of the scales, 0 = per channel
+    uint32_t group_inv;         // 2^32 / (g / 64), rounded up, 0 for groups of 64 (set by the launcher)
+    int cw;                     // channels of d_ff per slice, in 64s: 1, 2, 4 or 8
     const uint8_t *w1, *w2;     // packed codes
-    const __half *s1, *s2;      // per-channel scales [E, F] / [E, d]
+    const __half *s1, *s2;      // scales [E, d / g, F] / [E, F / g, d], one row per expert for channel scales
     const __half *b1, *b2;      // biases or null
-    float *partial;             // [F / 512, n_assign, d] fp32: y summed over one 512-channel slice of d_ff
-    float *out;                 // [T, d] fp32 layer output
+    float *partial;             // [F / (64 cw), n_assign, d] fp32: y of every assignment summed over one slice of d_ff
+    void *out;                  // [T, d] layer output
+    int out_dtype;
     int32_t *perm_src_out, *inv_perm_out, *offsets_out;
-    int items1;                 // workgroup items (set by the launcher)
-    int early_ring;             // an item requests its first weights before it knows the expert's row count (set by the launcher)
 };
 constexpr int kDecMaxExperts = 4096;
-bool decode_ffn_supports(int n_assign, int E, int d, int F, int bits);
-size_t decode_ffn_partial_bytes(int n_assign, int d, int F);
-int launch_decode_ffn(const DecodeArgs &p, int bits, hipStream_t s);
+constexpr int kDecMaxAssign = 512;
+bool decode_ffn_supports(int n_assign, int k, int E, int d, int F, int bits, int group_size);
+size_t decode_ffn_partial_bytes(int n_assign, int d, int F, int cw);
+int decode_slice_width(int n_assign, int E, int d, int F, int bits);
+double decode_active_experts(int n_assign, int E);
+int launch_decode_ffn(const DecodeArgs &p, int bits, bool bf, hipStream_t s);
 
 constexpr int kGatedMaxAssign = 256;    // assignments the fused permutation takes: one per thread of a block
 

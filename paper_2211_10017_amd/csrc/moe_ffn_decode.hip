@@ -1,72 +1,73 @@
 // The expert FFN of a decode-sized batch (Sec. 3.3 steps 2-4 with the fused dequantisation of
 // Sec. 3.4) in one streaming launch plus a small reduction: the stable sort by expert is rebuilt from
-// the gate's output, and fc1, the activation and fc2 run in one persistent grid.
+// the gate's output, and fc1, the activation and fc2 run in one grid.
 //
 // Such a batch (the decoder-like case of Table 1: a few rows per expert) is bound by pulling every
-// active expert's packed weights through the chip once.  The work is cut along d_ff: a workgroup
-// item is (expert, 512 channels of d_ff).  Its sixteen wavefronts compute that slice of
-// h = act(x W1 + b1) (one 32-channel slab of W1 each), keep it in LDS as fp16, and multiply it at
-// once with the matching 512 rows of W2 (each wavefront 64 output channels): h never goes to
-// memory and a wavefront's weight stream (16 KB of W1, then 16 KB of W2) runs through one ring of
-// eight 16-byte-per-lane loads without a break.  What is left over is a partial sum of y per
-// d_ff slice, stored as fp32 rows; decode_reduce_kernel then adds the slices in ascending order,
-// applies W2's channel scale, the bias and the gate scale, and sums a token's experts in slot
+// active expert's packed weights through the chip once.  The work is cut along d_ff: a work item is
+// (expert that has rows, slice of 64 CW channels of d_ff), one block of eight wavefronts, and the grid holds one
+// block per item, dealt out by the hardware as blocks end.  The block computes its slice of h = act(x W1 + b1) - a wavefront
+// 64 channels over a CW-th part of an eighth of K, the parts meet in LDS -, keeps it in LDS as fp16 and multiplies it
+// at once with the matching rows of W2 (a wavefront an eighth of the output channels): h never goes to memory.
+// What is left over is a partial sum of y per slice, stored as fp32 rows; decode_reduce_kernel then adds the
+// slices in a fixed order, applies W2's channel scale, the bias and the gate scale, and sums a token's experts in slot
 // order into the layer output (no atomics, nothing to clear, nothing to wait for inside a launch).
 //
+// What bounds it: one token, the latencies in a row (the gate's indices 1 us, the weights 2, each phase's instructions, which no
+// block has run before: about 100 clocks per 64 bytes of code), 64 tokens, the weight stream and the unpacking beside it.  Small
+// blocks are dealt out as others end, so no compute unit's share is fixed, and one token's two experts of 1024 x 4096 are 128 blocks
+// over the chip: kernel and reduction 10.8 us where sixteen workgroups of sixteen wavefronts, one per slice of 512
+// channels, took 22; 64 tokens 34.6 against 33; a step of 64 tokens, 64 experts of 4096 x 16384, group scales, 809 -> 711 against two launches in
+// row tiles.  Fewer registers beat longer rings (4-bit, FP16: 24 wavefronts per compute unit with two 1 KB blocks of fc1 and four of fc2
+// in flight 28.8 us, sixteen with six and eight 31.1), and two fc2 units at a time one (12 against 17 us for a block's 512 channels).
+//
 // The rows of an expert (at most sixteen per pass; more rows take further passes over the same
-// weights) are staged in LDS and are the A operand of v_mfma_f32_16x16x32_f16; the weights go
-// from the ring through the magic-number conversion into the B operand.
+// weights) are the A operand of v_mfma_f32_16x16x32_f16, fetched from the tokens in operand order; the weights go
+// through the magic-number conversion into the B operand.  Group scales multiply the fp32 sums of 64 K values of exact
+// codes.  bf16 rows are scaled per row and 64 K values by a power of two into the FP16 range (exact), and so is the slice of
+// h per row, after its rounding to bf16.
+#include <math.h>
+
 #include <type_traits>
 
 #include "moe_ffn_common.h"
 
-// Hook for timing studies: a harness that includes this file may define these to record a time stamp
-// per workgroup at the named points; the library builds them empty.
+// Hook for timing studies: a harness that includes this file may define it to record a time stamp per block at the named points;
+// the library builds it empty.
 #ifndef MOE_DEC_STAMP
 #define MOE_DEC_STAMP(slot)
-#define MOE_DEC_STAMP_INIT
 #endif
 
 namespace moe {
 
-constexpr int kDecWaves = 16;            // wavefronts per workgroup
+constexpr int kDecWaves = 8;             // wavefronts per block
 constexpr int kDecThreads = kDecWaves * 64;
-#ifndef MOE_DEC_RING
-#define MOE_DEC_RING 8
-#endif
-#ifndef MOE_DEC_AUX
-#define MOE_DEC_AUX 2
-#endif
-constexpr int kDecRing = MOE_DEC_RING;   // weight fragment blocks in flight per wavefront
 constexpr int kDecFit = 16;              // rows of an expert per pass (one 16-row matrix tile)
-constexpr int kDecRowPad = 8;            // halfs of padding per LDS row: rows start 4 banks apart
-constexpr int kDecChunk = 32 * kDecWaves;   // channels of d_ff per item
 
 typedef float float4_t __attribute__((ext_vector_type(4)));
-
-template <int I, int N, class F>
-__device__ inline void dec_static_for(F &&f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        dec_static_for<I + 1, N>(f);
-    }
-}
-
-// One 16-byte-per-lane load of the ring through a buffer descriptor: the descriptor (base and extent of
-// the wavefront's weight stream) and the block's offset sit in scalar registers, the lane's 16 x lane
-// in ONE vector register for all loads (plain pointers would cost two vector registers per block in
-// flight).  Loads past the extent return zero instead of touching memory.  Non-temporal: the weights
-// of a launch are read once and must not push the small hot arrays out of the caches.
 typedef uint32_t dec_u32x4 __attribute__((ext_vector_type(4)));
-__device__ inline __amdgpu_buffer_rsrc_t dec_stream_rsrc(const uint8_t *base, uint32_t bytes)
+
+// Loads through buffer descriptors: what changes per load is in the descriptor (scalar registers), the lane's offset in one vector
+// register for all of them.  The hardware compares a lane's offset with the extent LESS the instruction's scalar offset, which wraps
+// for an extent of zero, so no load here has a scalar offset: the base is moved instead.
+__device__ inline __amdgpu_buffer_rsrc_t dec_rsrc(const void *base, uint32_t bytes)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(base), 0, (int)bytes, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
 }
-__device__ inline uint4 dec_ring_load(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t block_off)
+
+// 16 bytes per lane of one 1 KB fragment block, non-temporal: the weights of a launch are read once and must not push the small
+// hot arrays out of the caches.  Not `live`: the descriptor has no extent, the load returns zero without touching memory, and
+// the number of loads in flight does not depend on how long a wavefront's stream is.
+__device__ inline uint4 dec_load(const uint8_t *block, bool live, uint32_t lane_off)
 {
-    const dec_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, block_off, MOE_DEC_AUX /* 2 = nt */);
+    const __amdgpu_buffer_rsrc_t r = dec_rsrc(block, live ? kFragBytes : 0);
+    const dec_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, 0, 2 /* nt */);
     return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// Value of lane `first + (lane's byte offset / 4)`, both from registers (first: a constant).
+__device__ inline float dec_lane(float v, int byte_off, int first)
+{
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(byte_off + 4 * first, __float_as_int(v)));
 }
 
 // Rows 1 and 3 (of sixteen lanes each) of `a` change places with rows 0 and 2 of `b`.  A fragment
@@ -81,343 +82,527 @@ __device__ inline void swap_rows(uint32_t &a, uint32_t &b)
     b = r[1];
 }
 
-// BITS: weight width.  NB1: fragment blocks of a W1 slab (its whole K range, d_model).  TS: W2 slabs per
-// wavefront (d_model / 512).  NBC: fragment blocks of a W2 slab inside one d_ff slice of 512 rows.
-template <int BITS, int NB1, int TS, int NBC, bool EARLY>
-__global__ __launch_bounds__(kDecThreads, 1) void decode_ffn_kernel(DecodeArgs p)
+// 16 rows x 32 channels x 64 K values: one fragment block of 4-bit or two of 8-bit weights, a[] the two 32-deep row operands.
+template <int BITS>
+__device__ inline void dec_mac(const uint4 (&w)[BITS / 4], const uint4 (&a)[2], float4_t &lo, float4_t &hi)
 {
-    constexpr int FK = BITS == 4 ? 64 : 32;             // K values per fragment block
-    constexpr int PAIRS = BITS == 4 ? 2 : 1;            // 32-deep MFMA steps per fragment block
-    constexpr int K1 = NB1 * FK;                        // d_model
-    constexpr int LDR1 = K1 + kDecRowPad, LDRH = kDecChunk + kDecRowPad;
-    constexpr int VPR1 = K1 / 8;                        // 16-byte vectors per row of x
-    constexpr int NA1 = kDecFit * VPR1 / kDecThreads;   // staging vectors per thread
-    constexpr int TOT = NB1 + TS * NBC;                 // fragment blocks a wavefront streams per pass
-    static_assert(NA1 >= 1 && NBC * FK == kDecChunk && TS * 32 * kDecWaves == K1, "shape of an item");
-    static_assert(NB1 >= kDecRing && NBC >= 1, "the ring never holds more than one pass");
-    extern __shared__ __align__(16) uint16_t lds_x[];   // [kDecFit][LDR1] rows of x, then [kDecFit][LDRH] the slice of h
-    uint16_t *lds_h = lds_x + kDecFit * LDR1;
-    __shared__ int s_cnt[3][4];                 // per wavefront 0..3: assignments of the expert, of earlier experts, pruned
-    __shared__ int s_tok[kGatedMaxAssign];      // token of each row of the expert
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const half8_t av = __builtin_bit_cast(half8_t, a[q]);
+        uint32_t bw[4];
+        if constexpr (BITS == 4) {
+            uint32_t r0 = q ? w[0].z : w[0].x, r1 = q ? w[0].w : w[0].y;
+            swap_rows(r0, r1);
+            dequant4(r0, bw);
+            lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, frag_from(bw), lo, 0, 0, 0);
+            dequant4(r1, bw);
+            hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, frag_from(bw), hi, 0, 0, 0);
+        } else {
+            uint32_t r0 = w[q].x, r1 = w[q].y, r2 = w[q].z, r3 = w[q].w;
+            swap_rows(r0, r2);
+            swap_rows(r1, r3);
+            dequant8(r0, r1, bw);
+            lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, frag_from(bw), lo, 0, 0, 0);
+            dequant8(r2, r3, bw);
+            hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, frag_from(bw), hi, 0, 0, 0);
+        }
+    }
+}
+
+// Power of two that brings a bf16 magnitude `amax` (bits, sign cleared) into [2^14, 2^15), and its reciprocal.
+__device__ inline void dec_row_pow(uint32_t amax, float &down, float &up)
+{
+    int ex = (int)(amax >> 7);
+    if (ex == 255) ex = 141;                            // inf/nan: factor 1 (the result is nan anyway)
+    const int fe = min(max(268 - ex, 1), 253);
+    down = __uint_as_float((uint32_t)fe << 23);
+    up = __uint_as_float((uint32_t)(254 - fe) << 23);
+}
+
+__device__ inline uint32_t dec_max_bf16(uint32_t amax, uint32_t pair)
+{
+    return max(amax, max(pair & 0x7fffu, (pair >> 16) & 0x7fffu));
+}
+
+// The same wavefront-wide for values that sixteen-lane rows share: maximum over lanes l, l ^ 16, l ^ 32, l ^ 48.
+__device__ inline uint32_t dec_max_over_rows(uint32_t v)
+{
+    v = max(v, (uint32_t)__shfl_xor((int)v, 16));
+    return max(v, (uint32_t)__shfl_xor((int)v, 32));
+}
+
+__device__ inline uint32_t dec_bf16_pair_to_f16(uint32_t pair, float down)
+{
+    const half2_t h = {(_Float16)__builtin_fmaf(__uint_as_float(pair << 16), down, 0.0f),
+                       (_Float16)__builtin_fmaf(__uint_as_float(pair & 0xffff0000u), down, 0.0f)};
+    return h2_bits(h);
+}
+
+// The stable sort by expert, for the callers: perm_src, inv_perm and expert_offsets (pruned rows, key E, come last).  One block;
+// up to 512 keys, every thread counts what precedes its own.
+__device__ inline void dec_write_index(const DecodeArgs &p, int32_t *s_key, int v)
+{
+    const int tid = threadIdx.x, n = p.n_assign;
+    s_key[tid] = v;
+    __syncthreads();
+    auto count = [&](auto less) {
+        int r = 0;
+        for (int i = 0; i < n; i += 4) {
+            const int4 q = *reinterpret_cast<const int4 *>(s_key + i);
+            r += less(q.x, i) + less(q.y, i + 1) + less(q.z, i + 2) + less(q.w, i + 3);
+        }
+        return r;
+    };
+    if (tid < n) {
+        const int r = count([&](int key, int i) { return (int)(key < v || (key == v && i < tid)); });
+        p.inv_perm_out[tid] = r;
+        p.perm_src_out[r] = tid;
+    }
+    for (int e = tid; e <= p.E; e += kDecThreads) p.offsets_out[e] = count([&](int key, int) { return (int)(key < e); });
+}
+
+// BITS: weight width.  GROUPED: group scales (groups of a multiple of 64 K values).  BF: bf16 rows.  CW: 64-channel parts of a slice.
+template <int BITS, bool GROUPED, bool BF, int CW>
+__global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF ? 6 : 4) void decode_ffn_kernel(DecodeArgs p)
+{
+    constexpr int NW = BITS / 4;                        // fragment blocks of a slab per 64 K values (a "unit")
+    constexpr int KP = kDecWaves / CW, CH = 64 * CW;    // parts of K in fc1; channels of the slice
+    constexpr int U1 = 1, U2 = 4;                       // units in flight per wavefront, fc1 / fc2
+    constexpr int LDR = CH + 4, LDH = CH + 8;
+    __shared__ __align__(16) float s_red[KP * kDecFit * LDR];
+    __shared__ __align__(16) uint16_t s_h[kDecFit * LDH];
+    __shared__ __align__(16) int32_t s_row[kDecMaxAssign];      // assignments of the block's expert
+    __shared__ uint32_t s_used[kDecMaxExperts / 32];            // experts that have rows
+    __shared__ float s_pow[kDecFit];
+    __shared__ int s_n;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int E = p.E, F = p.F, d = p.d;
-    const int G = gridDim.x, blk = blockIdx.x;
-    MOE_DEC_STAMP_INIT;
+    const int E = p.E, F = p.F, d = p.d, S = F / CH;
     MOE_DEC_STAMP(0);
+    const int v_exp = tid < p.n_assign ? p.gate_idx[tid] : 0x7fffffff;
+    if (blockIdx.x == 0) {
+        dec_write_index(p, s_row, v_exp);
+        return;
+    }
+    const int c = (int)(blockIdx.x - 1) % S;
+    // ---- the block's expert: the (blockIdx - 1) / S -th one that has rows
+    if (tid < kDecMaxExperts / 32) s_used[tid] = 0;
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    if ((uint32_t)v_exp < (uint32_t)E) atomicOr(&s_used[v_exp >> 5], 1u << (v_exp & 31));
+    __syncthreads();
+    int e;
+    {
+        const uint32_t lo = s_used[2 * lane], hi = s_used[2 * lane + 1];
+        const int cnt = __popc(lo) + __popc(hi), incl = wave_inclusive_sum(cnt);
+        int rank = (int)(blockIdx.x - 1) / S;
+        const uint64_t hit = __ballot(incl > rank);
+        if (!hit) return;                               // fewer experts have rows than there are blocks for
+        const int src = __ffsll((unsigned long long)hit) - 1;
+        rank -= __shfl(incl - cnt, src);
+        uint64_t bits = (uint64_t)(uint32_t)__shfl((int)hi, src) << 32 | (uint32_t)__shfl((int)lo, src);
+        for (; rank > 0; --rank) bits &= bits - 1;
+        e = __builtin_amdgcn_readfirstlane(64 * src + __ffsll((unsigned long long)bits) - 1);
+    }
 
-    // the gate's expert of assignment `tid` (one per thread of the first four wavefronts)
-    const int a_id = tid;
-    const int v_exp = a_id < p.n_assign ? p.gate_idx[a_id] : 0x7fffffff;
-    const int a_tok = a_id >> (p.gate_k - 1);           // one or two experts per token
+    MOE_DEC_STAMP(1);
+    // ---- weight streams
+    const uint32_t lane_off = (uint32_t)lane * 16u;
+    const int cg = wave % CW, kp = wave / CW;
+    const int nk = d / 64, per = (nk + KP - 1) / KP, u0 = kp * per, n1 = max(min(nk - u0, per), 0);
+    const int ktot = F / 64;                            // units of a slab of W2
+    const int nslab = d / 32, spw = (nslab + kDecWaves - 1) / kDecWaves, slab0 = wave * spw;
+    const int n2 = max(min(nslab - slab0, spw), 0) * CW;
+    const uint8_t *w1 = p.w1 + (size_t)e * packed_bytes_per_expert(d, F, BITS) + ((size_t)(c * CW + cg) * 2 * nk + u0) * NW * kFragBytes;
+    const uint8_t *w2 = p.w2 + (size_t)e * packed_bytes_per_expert(F, d, BITS) + ((size_t)slab0 * ktot + c * CW) * NW * kFragBytes;
+    const uint16_t *s1 = reinterpret_cast<const uint16_t *>(p.s1) + (size_t)e * (GROUPED ? d / p.g : 1) * F + c * CH;
+    const uint16_t *s2 = reinterpret_cast<const uint16_t *>(p.s2) + (size_t)e * (GROUPED ? F / p.g : 1) * d + slab0 * 32;
 
-    // Counts of expert e among the assignments: its rows, the rows of experts before it, this thread's
-    // rank among its rows (stable: ascending assignment id), and the pruned assignments before this thread.
-    auto expert_counts = [&](int e, int &count, int &lower, int &rank, int &pruned_rank, bool &mine, bool &pruned) {
-        mine = v_exp == e;
-        pruned = v_exp == E;
-        const bool before = v_exp < e;
-        const uint64_t m_mine = __ballot(mine), m_before = __ballot(before), m_pruned = __ballot(pruned);
-        __syncthreads();                        // the previous use of s_cnt is over
-        if (lane == 0 && wave < 4) {
-            s_cnt[0][wave] = __popcll(m_mine);
-            s_cnt[1][wave] = __popcll(m_before);
-            s_cnt[2][wave] = __popcll(m_pruned);
-        }
-        __syncthreads();
-        int first = 0, pfirst = 0;
-        count = 0, lower = 0;
+    auto group_of = [&](int u) { return p.group_inv ? (int)__umulhi((uint32_t)u, p.group_inv) : u; };      // unit -> group
+    uint4 W[U1][2][NW], A[U1][2], V[U2][NW];
+    uint16_t gs1[GROUPED ? U1 : 1], gs2[GROUPED ? U2 : 1];       // group scales: lane l brings channel l of the wavefront's 64, l % 32 of the slab's 32
+    auto load_w1 = [&](int slot, int u) {
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            if (w < wave) { first += s_cnt[0][w]; pfirst += s_cnt[2][w]; }
-            count += s_cnt[0][w];
-            lower += s_cnt[1][w];
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int w = 0; w < NW; ++w) W[slot][s][w] = dec_load(w1 + ((size_t)s * nk + u) * NW * kFragBytes + w * kFragBytes, u < n1, lane_off);
+        if constexpr (GROUPED) {
+            gs1[slot] = __builtin_amdgcn_raw_buffer_load_b16(dec_rsrc(s1 + (size_t)group_of(u0 + u) * F + cg * 64, u < n1 ? 128 : 0), lane * 2, 0, 0);
         }
-        const uint64_t below = (1ull << lane) - 1;
-        rank = first + __popcll(m_mine & below);
-        pruned_rank = pfirst + __popcll(m_pruned & below);
     };
-
-    uint4 W[kDecRing];
+    auto load_w2 = [&](int slot, int j) {
+        const int slab = j / CW, unit = j % CW;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) V[slot][w] = dec_load(w2 + ((size_t)slab * ktot + unit) * NW * kFragBytes + w * kFragBytes, j < n2, lane_off);
+        if constexpr (GROUPED) {
+            gs2[slot] = __builtin_amdgcn_raw_buffer_load_b16(dec_rsrc(s2 + (size_t)group_of(c * CW + unit) * d + slab * 32, j < n2 ? 64 : 0), (lane & 31) * 2, 0, 0);
+        }
+    };
+    auto prime = [&]() {
+#pragma unroll
+        for (int i = 0; i < U1; ++i) load_w1(i, i);
+#pragma unroll
+        for (int i = 0; i < U2; ++i) load_w2(i, i);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    prime();                                            // (the weights depend on the expert alone: the rows are found under their flight)
+    // ---- the expert's rows
+    const bool mine = v_exp == e;
+    if (mine) s_row[atomicAdd(&s_n, 1)] = tid;          // in any order: the rows of a tile do not see each other
+    // channel factors of the thread's part of h: row tid / 32, 2 CW channels
+    constexpr int HC = 2 * CW;
+    const int h_row = tid >> 5, h_ch = (tid & 31) * HC;
+    uint32_t hs[CW], hb[CW];
+    auto load_factors = [&]() {
+#pragma unroll
+        for (int i = 0; i < CW; ++i) {
+            hs[i] = GROUPED ? 0 : reinterpret_cast<const uint32_t *>(s1 + h_ch)[i];
+            hb[i] = p.b1 ? reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint16_t *>(p.b1) + (size_t)e * F + c * CH + h_ch)[i] : 0;
+        }
+    };
+    if constexpr (CW <= 2) load_factors();              // (wider slices have no registers to carry them through fc1)
+    __syncthreads();
+    const int count = s_n;
+    MOE_DEC_STAMP(2);
+    const uint32_t x_bytes = (uint32_t)(p.n_assign >> (p.gate_k - 1)) * d * 2u;
+    const int lane16 = (lane & 15) * 4, lane_row = (lane >> 4) * 16;     // byte offsets of dec_lane
     // k octet this lane's quarter of the wavefront reads within a 32-deep step (see swap_rows)
     const int koct = ((lane >> 4) & 1) * 16 + (lane >> 5) * 8;
-
-    const int C = F / kDecChunk;                        // items per expert
-    const uint32_t lane_off = (uint32_t)lane * 16u;
-    // this wavefront's slab of W1 in item `it` (whole K range)
-    auto w1_slab = [&](int it) {
-        return p.w1 + (size_t)(it / C) * packed_bytes_per_expert(K1, F, BITS) + (size_t)((it % C) * kDecWaves + wave) * NB1 * kFragBytes;
-    };
-    // EARLY (the launcher's choice where nearly every expert has rows): an item's first ring is requested before the
-    // expert's row count is known (the count needs the gate's indices and two barriers; the weights need neither):
-    // for the workgroup's first item at once, for a further item when the item before it has used up its stream.
-    // Should the expert turn out empty, this one ring (a quarter of the item's stream) was read in vain.  Past the
-    // last item the descriptor has no extent: the same eight loads, no traffic, so that the count of loads in flight
-    // does not depend on the path taken.
-    auto prime = [&](int it) {
-        const __amdgpu_buffer_rsrc_t r1e = dec_stream_rsrc(w1_slab(min(it, p.items1 - 1)), it < p.items1 ? NB1 * kFragBytes : 0);
-        dec_static_for<0, kDecRing>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            W[i] = dec_ring_load(r1e, lane_off, i * kFragBytes);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    };
-    if constexpr (EARLY) prime(blk);
-    for (int it = blk; it < p.items1; it += G) {
-        const int e = it / C, c = it % C;
-        int count, lower, rank, prank;
-        bool mine, pruned;
-        // this wavefront's weight stream: its slab of W1 (whole K range), then the slice's rows of its TS slabs of W2
-        // (the bases are the same for the whole wavefront, so they live in scalar registers; a lane adds 16 bytes x its number)
-        const uint8_t *w1b = w1_slab(it);
-        expert_counts(e, count, lower, rank, prank, mine, pruned);
-        const uint8_t *w2b = p.w2 + (size_t)e * packed_bytes_per_expert(F, K1, BITS) +
-                             ((size_t)(wave * TS) * (F / FK) + (size_t)c * NBC) * kFragBytes;
-        const size_t slab2 = (size_t)(F / FK) * kFragBytes;             // bytes between consecutive slabs of W2
-        // an expert without rows costs no (further) weight traffic: its descriptors have no extent (loads return zero
-        // without touching memory) and the item ends below
-        const __amdgpu_buffer_rsrc_t r1 = dec_stream_rsrc(w1b, count ? NB1 * kFragBytes : 0);
-        __amdgpu_buffer_rsrc_t r2[TS];
+    for (int z0 = 0; z0 < count; z0 += kDecFit) {       // usually a single pass
+        const int rows = min(kDecFit, count - z0);
+        // rows of x in operand order: only the lanes of live rows read (the others hold zeros)
+        const bool a_live = (lane & 15) < rows;
+        const int a_tok = s_row[z0 + min(lane & 15, rows - 1)] >> (p.gate_k - 1);       // one or two experts per token
+        const uint32_t a_off = a_live ? ((uint32_t)a_tok * d + koct) * 2u : 0x7fffff00u;    // (past the tokens: reads as zero)
+        auto load_a = [&](int slot, int u) {
+            const __amdgpu_buffer_rsrc_t r = dec_rsrc(p.x + (u0 + u) * 64, u < n1 ? x_bytes - (u0 + u) * 128 : 0);
 #pragma unroll
-        for (int s = 0; s < TS; ++s) r2[s] = dec_stream_rsrc(w2b + (size_t)s * slab2, count ? NBC * kFragBytes : 0);
-        auto ring_load = [&](auto gc) {         // block g of the stream
-            constexpr int g = decltype(gc)::value;
-            if constexpr (g < NB1) return dec_ring_load(r1, lane_off, g * kFragBytes);
-            else return dec_ring_load(r2[(g - NB1) / NBC], lane_off, ((g - NB1) % NBC) * kFragBytes);
+            for (int q = 0; q < 2; ++q) {
+                const dec_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, a_off + 64 * q, 0, 0);
+                A[slot][q] = make_uint4(v.x, v.y, v.z, v.w);
+            }
         };
-        // The weights depend on nothing but the item: their first ring is requested as soon as the expert is
-        // known to have rows, ahead of everything else the item needs (the rows of x arrive under it).
-        auto issue_ring = [&]() {
-            dec_static_for<0, kDecRing>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                W[i] = ring_load(ic);
-                __builtin_amdgcn_sched_barrier(0);
-            });
-        };
-        if constexpr (!EARLY) issue_ring();
-        if (c == 0) {                           // the first item of an expert writes the expert's part of the index arrays
-            if (tid == 0) {
-                p.offsets_out[e] = lower;
-                if (e == E - 1) p.offsets_out[E] = lower + count;       // = the active rows
-            }
-            if (mine) {
-                p.inv_perm_out[a_id] = lower + rank;
-                p.perm_src_out[lower + rank] = a_id;
-            }
-            if (pruned && e == E - 1) {         // pruned rows are numbered behind the active ones
-                const int r = lower + count + prank;
-                p.inv_perm_out[a_id] = r;
-                p.perm_src_out[r] = a_id;
-            }
-        }
-        if (count == 0) {
-            if constexpr (EARLY) prime(it + G);
-            continue;
-        }
-        if (mine) s_tok[rank] = a_tok;
-        const int n1 = c * kDecChunk + wave * 32 + (lane & 15);        // this lane's fc1 channels: n1, n1 + 16
-        const float cs0 = __half2float(p.s1[(size_t)e * F + n1]), cs1 = __half2float(p.s1[(size_t)e * F + n1 + 16]);
-        const float bi0 = p.b1 ? __half2float(p.b1[(size_t)e * F + n1]) : 0.0f, bi1 = p.b1 ? __half2float(p.b1[(size_t)e * F + n1 + 16]) : 0.0f;
-        __syncthreads();                        // s_tok is written
-        for (int z0 = 0; z0 < count; z0 += kDecFit) {   // usually a single pass
-            const int rows = min(kDecFit, count - z0);
-            if (z0) issue_ring();               // a further pass streams the same weights again
-            // rows of x: gathered through the tokens of the expert's rows
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            const u32x4 *xv = reinterpret_cast<const u32x4 *>(p.x);
-            const int total = rows * VPR1;
-            u32x4 av[NA1];
 #pragma unroll
-            for (int j = 0; j < NA1; ++j) {
-                const int idx = min(j * kDecThreads + tid, total - 1);
-                av[j] = xv[(size_t)s_tok[z0 + idx / VPR1] * VPR1 + idx % VPR1];
-            }
-#pragma unroll
-            for (int j = 0; j < NA1; ++j) {
-                const int idx = j * kDecThreads + tid;
-                if (idx < total) *reinterpret_cast<u32x4 *>(lds_x + (idx / VPR1) * LDR1 + (idx % VPR1) * 8) = av[j];
-            }
-            __syncthreads();
-            MOE_DEC_STAMP(1);
+        for (int i = 0; i < U1; ++i) load_a(i, i);
 
-            // ---- fc1: 16 rows x 32 channels per wavefront over the whole K range
-            const int arow_i = min(lane & 15, rows - 1);                // clamped to a live row
-            const uint16_t *arow = lds_x + (size_t)arow_i * LDR1 + koct;
-            uint4 A[2][PAIRS];
-            auto fetch_a = [&](const uint16_t *row, int slot, int kb) {
+        // ---- fc1: 16 rows x 64 channels over the wavefront's part of K
+        float4_t acc[4];
 #pragma unroll
-                for (int q = 0; q < PAIRS; ++q) A[slot][q] = *reinterpret_cast<const uint4 *>(row + kb * FK + 32 * q);
-            };
-            // one fragment block: 32 channels x FK k values, into the accumulators of the two channel halves
-            auto mac_block = [&](int slot, int g, float4_t &lo, float4_t &hi) {
-                uint32_t r0 = W[g % kDecRing].x, r1 = W[g % kDecRing].y, r2 = W[g % kDecRing].z, r3 = W[g % kDecRing].w;
-                uint32_t bw[4];
-                if constexpr (BITS == 4) {
-                    swap_rows(r0, r1);
-                    swap_rows(r2, r3);
-                    dequant4(r0, bw);
-                    lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, A[slot][0]), frag_from(bw), lo, 0, 0, 0);
-                    dequant4(r1, bw);
-                    hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, A[slot][0]), frag_from(bw), hi, 0, 0, 0);
-                    dequant4(r2, bw);
-                    lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, A[slot][1]), frag_from(bw), lo, 0, 0, 0);
-                    dequant4(r3, bw);
-                    hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, A[slot][1]), frag_from(bw), hi, 0, 0, 0);
-                } else {
-                    swap_rows(r0, r2);
-                    swap_rows(r1, r3);
-                    dequant8(r0, r1, bw);
-                    lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, A[slot][0]), frag_from(bw), lo, 0, 0, 0);
-                    dequant8(r2, r3, bw);
-                    hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, A[slot][0]), frag_from(bw), hi, 0, 0, 0);
-                }
-            };
-            float4_t h0 = {0.f, 0.f, 0.f, 0.f}, h1 = {0.f, 0.f, 0.f, 0.f};
-            fetch_a(arow, 0, 0);
-            dec_static_for<0, NB1>([&](auto bc) {
-                constexpr int b = decltype(bc)::value;
-                __builtin_amdgcn_sched_barrier(0);
-                if (b + 1 < NB1) fetch_a(arow, (b + 1) & 1, b + 1);
-                mac_block(b & 1, b, h0, h1);
-                if constexpr (b + kDecRing < TOT) W[b % kDecRing] = ring_load(std::integral_constant<int, b + kDecRing>{});   // runs on into the W2 blocks
-            });
-            // rows 4 (lane / 16) + i, channels n1 and n1 + 16: scale, bias, activation, fp16, into the slice of h in LDS
+        for (int t = 0; t < 4; ++t) acc[t] = float4_t{0.f, 0.f, 0.f, 0.f};
+        for (int base = 0; base < n1; base += U1) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = 4 * (lane >> 4) + i;
-                const _Float16 v0 = (_Float16)activate(h0[i] * cs0 + bi0, p.act), v1 = (_Float16)activate(h1[i] * cs1 + bi1, p.act);
-                lds_h[m * LDRH + wave * 32 + (lane & 15)] = __builtin_bit_cast(uint16_t, v0);
-                lds_h[m * LDRH + wave * 32 + (lane & 15) + 16] = __builtin_bit_cast(uint16_t, v1);
-            }
-            __syncthreads();
-            MOE_DEC_STAMP(2);
-
-            // ---- fc2 on the slice: 16 rows x (TS x 32) output channels per wavefront, K = the slice's 512 channels
-            const uint16_t *hrow = lds_h + (size_t)arow_i * LDRH + koct;
-            float4_t y[TS][2];
+            for (int i = 0; i < U1; ++i) {
+                if (base + i < n1) {
+                    float up = 1.0f;
+                    if constexpr (BF) {
+                        uint32_t amax = 0;
 #pragma unroll
-            for (int s = 0; s < TS; ++s) y[s][0] = y[s][1] = float4_t{0.f, 0.f, 0.f, 0.f};
-            fetch_a(hrow, 0, 0);
-            dec_static_for<0, TS * NBC>([&](auto bc) {
-                constexpr int b = decltype(bc)::value, s = b / NBC, g = NB1 + b;
-                __builtin_amdgcn_sched_barrier(0);
-                if (b + 1 < TS * NBC) fetch_a(hrow, (b + 1) & 1, (b + 1) % NBC);
-                mac_block(b & 1, g, y[s][0], y[s][1]);
-                if constexpr (g + kDecRing < TOT) W[g % kDecRing] = ring_load(std::integral_constant<int, g + kDecRing>{});
-            });
-            MOE_DEC_STAMP(3);
-            // this slice's part of y, rows lower + z0 + m of the expert-sorted order
-            float *prow = p.partial + ((size_t)c * p.n_assign + lower + z0) * d;
+                        for (int q = 0; q < 2; ++q) {
+                            amax = dec_max_bf16(dec_max_bf16(amax, A[i][q].x), A[i][q].y);
+                            amax = dec_max_bf16(dec_max_bf16(amax, A[i][q].z), A[i][q].w);
+                        }
+                        float down;
+                        dec_row_pow(dec_max_over_rows(amax), down, up);
 #pragma unroll
-            for (int s = 0; s < TS; ++s) {
-                const int n2 = (wave * TS + s) * 32 + (lane & 15);
+                        for (int q = 0; q < 2; ++q)
+                            A[i][q] = make_uint4(dec_bf16_pair_to_f16(A[i][q].x, down), dec_bf16_pair_to_f16(A[i][q].y, down),
+                                                 dec_bf16_pair_to_f16(A[i][q].z, down), dec_bf16_pair_to_f16(A[i][q].w, down));
+                    }
+                    if constexpr (GROUPED || BF) {      // the unit's sums, folded with its factors in fp32
+                        float4_t part[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int m = 4 * (lane >> 4) + i;
-                    if (m < rows) {
-                        prow[(size_t)m * d + n2] = y[s][0][i];
-                        prow[(size_t)m * d + n2 + 16] = y[s][1][i];
+                        for (int t = 0; t < 4; ++t) part[t] = float4_t{0.f, 0.f, 0.f, 0.f};
+                        dec_mac<BITS>(W[i][0], A[i], part[0], part[1]);
+                        dec_mac<BITS>(W[i][1], A[i], part[2], part[3]);
+                        float pw[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) pw[r] = BF ? dec_lane(up, lane_row, r) : 1.0f;
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const float sf = GROUPED ? dec_lane((float)__builtin_bit_cast(_Float16, gs1[i]), lane16, 16 * t) : 1.0f;
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) acc[t][r] = fmaf(part[t][r], sf * pw[r], acc[t][r]);
+                        }
+                    } else {
+                        dec_mac<BITS>(W[i][0], A[i], acc[0], acc[1]);
+                        dec_mac<BITS>(W[i][1], A[i], acc[2], acc[3]);
                     }
                 }
+                load_w1(i, base + U1 + i);
+                load_a(i, base + U1 + i);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (z0 + kDecFit < count) __syncthreads();      // LDS rows are free for the next pass
         }
-        if constexpr (EARLY) prime(it + G);
+        MOE_DEC_STAMP(3);
+        if constexpr (CW > 2) load_factors();
+        // ---- the parts of K meet: rows 4 (lane / 16) + r, channels 64 cg + 16 t + lane % 16
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s_red[(kp * kDecFit + 4 * (lane >> 4) + r) * LDR + cg * 64 + 16 * t + (lane & 15)] = acc[t][r];
+        __syncthreads();
+        {
+            float v[HC];
+#pragma unroll
+            for (int i = 0; i < HC; ++i) v[i] = s_red[h_row * LDR + h_ch + i];
+#pragma unroll
+            for (int q = 1; q < KP; ++q)
+#pragma unroll
+                for (int i = 0; i < HC; ++i) v[i] += s_red[(q * kDecFit + h_row) * LDR + h_ch + i];
+            uint32_t amax = 0;
+#pragma unroll
+            for (int i = 0; i < HC; ++i) {
+                const half2_t s2v = bits_h2(hs[i >> 1]), b2v = bits_h2(hb[i >> 1]);
+                v[i] = fmaf(v[i], GROUPED ? 1.0f : (float)s2v[i & 1], (float)b2v[i & 1]);
+            }
+            if (p.act == MOE_ACT_GELU) {
+#pragma unroll
+                for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_GELU);
+            } else {
+#pragma unroll
+                for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_RELU);
+            }
+#pragma unroll
+            for (int i = 0; i < HC; ++i) {
+                if constexpr (BF) {
+                    v[i] = __uint_as_float((uint32_t)to_bf16_rne(v[i]) << 16);
+                    amax = max(amax, (__float_as_uint(v[i]) >> 16) & 0x7fffu);
+                }
+            }
+            if constexpr (BF) {
+                float down, up;
+#pragma unroll
+                for (int off = 16; off > 0; off >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, off));
+                dec_row_pow(amax, down, up);
+                if ((tid & 31) == 0) s_pow[h_row] = up;
+#pragma unroll
+                for (int i = 0; i < HC; ++i) v[i] *= down;
+            }
+#pragma unroll
+            for (int i = 0; i < HC; i += 2) {
+                const half2_t hv = {(_Float16)v[i], (_Float16)v[i + 1]};
+                *reinterpret_cast<uint32_t *>(s_h + h_row * LDH + h_ch + i) = h2_bits(hv);
+            }
+        }
+        __syncthreads();
+
+        MOE_DEC_STAMP(4);
+        // ---- fc2 on the slice: 16 rows x 32 output channels per slab, K = the slice's channels
+        const uint16_t *h_ptr = s_h + (lane & 15) * LDH + koct;
+        float *const part_c = p.partial + (size_t)c * p.n_assign * d + slab0 * 32;
+        int row_off[4];
+        float pw[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = 4 * (lane >> 4) + r;
+            row_off[r] = m < rows ? s_row[z0 + m] * d + (lane & 15) : -1;
+            pw[r] = BF ? s_pow[m] : 1.0f;
+        }
+        float4_t y0 = {0.f, 0.f, 0.f, 0.f}, y1 = {0.f, 0.f, 0.f, 0.f};
+        auto unit_mac = [&](int i, const uint4 (&a)[2], float4_t &lo, float4_t &hi) {
+            if constexpr (GROUPED) {
+                float4_t p0 = {0.f, 0.f, 0.f, 0.f}, p1 = {0.f, 0.f, 0.f, 0.f};
+                dec_mac<BITS>(V[i], a, p0, p1);
+                const float sl = (float)__builtin_bit_cast(_Float16, gs2[i]), f0 = dec_lane(sl, lane16, 0), f1 = dec_lane(sl, lane16, 16);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) lo[r] = fmaf(p0[r], f0, lo[r]), hi[r] = fmaf(p1[r], f1, hi[r]);
+            } else {
+                dec_mac<BITS>(V[i], a, lo, hi);
+            }
+        };
+        auto store = [&](int n, const float4_t &lo, const float4_t &hi) {       // this slice's part of y, channels n .. n + 31
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (row_off[r] >= 0) {
+                    part_c[row_off[r] + n] = BF ? lo[r] * pw[r] : lo[r];
+                    part_c[row_off[r] + n + 16] = BF ? hi[r] * pw[r] : hi[r];
+                }
+        };
+        // two units at a time, whose chains of unpacking and products the wavefront interleaves: two slabs (slices of 64 channels)
+        // or two units of a slab
+        for (int base = 0; base < n2; base += U2) {
+#pragma unroll
+            for (int i = 0; i < U2; i += 2) {
+                const int j = base + i, unit = CW == 1 ? 0 : U2 % CW == 0 ? i % CW : j % CW;
+                if (j < n2) {
+                    const uint4 a0[2] = {*reinterpret_cast<const uint4 *>(h_ptr + unit * 64), *reinterpret_cast<const uint4 *>(h_ptr + unit * 64 + 32)};
+                    if constexpr (CW == 1) {
+                        float4_t z0v = {0.f, 0.f, 0.f, 0.f}, z1v = {0.f, 0.f, 0.f, 0.f};
+                        y0 = y1 = z0v;
+                        unit_mac(i, a0, y0, y1);
+                        unit_mac(i + 1, a0, z0v, z1v);
+                        store(j * 32, y0, y1);
+                        if (j + 1 < n2) store(j * 32 + 32, z0v, z1v);
+                    } else {
+                        const uint4 a1[2] = {*reinterpret_cast<const uint4 *>(h_ptr + unit * 64 + 64), *reinterpret_cast<const uint4 *>(h_ptr + unit * 64 + 96)};
+                        unit_mac(i, a0, y0, y1);
+                        unit_mac(i + 1, a1, y0, y1);
+                        if (unit == CW - 2) {
+                            store(j / CW * 32, y0, y1);
+                            y0 = y1 = float4_t{0.f, 0.f, 0.f, 0.f};
+                        }
+                    }
+                }
+                load_w2(i, j + U2);
+                load_w2(i + 1, j + 1 + U2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        MOE_DEC_STAMP(5);
+        // (a further pass: s_h and s_pow are written again only behind the barrier that follows its fc1)
+        if (z0 + kDecFit < count) {
+            __syncthreads();
+            prime();
+        }
     }
-    MOE_DEC_STAMP(7);
 }
 
-// Sum of the d_ff slices and of a token's experts: out[t] = sum_j scale[a] * (W2-scale * sum_c partial[c][row of a] + b2),
-// a = t k + j in ascending j, slices in ascending c; pruned assignments (expert index E) add nothing, so a
-// pruned token's row is zero.  One workgroup per token, four channels per thread.
+// Sum of the d_ff slices and of a token's experts: out[t] = sum_j scale[a] * (W2-scale * sum_c partial[c][a] + b2),
+// a = t k + j in ascending j; pruned assignments (expert index E) add nothing, so a pruned token's row is zero.
+// A block is a token and 1024 / SG channels, four per thread; SG threads share an element's slices, NV of each expert at a time.
+template <int SG, int NV>
 __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs p)
 {
-    const int t = blockIdx.x, C = p.F / kDecChunk, d = p.d;
-    for (int n = threadIdx.x * 4; n < d; n += 256 * 4) {
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int j = 0; j < p.gate_k; ++j) {
-            const int a = t * p.gate_k + j, e = p.gate_idx[a];
-            if (e >= p.E) continue;             // pruned
-            const int r = p.inv_perm_out[a];
-            const float sc = p.gate_scale[a];
-            float4 v[8];
+    constexpr int LANES = 256 / SG;
+    __shared__ float4 s_sum[SG > 1 ? 2 * 256 : 1];
+    const int t = blockIdx.x, S = p.F / (64 * p.cw), d = p.d;
+    const int sg = threadIdx.x / LANES, ln = threadIdx.x % LANES, n = (blockIdx.y * LANES + ln) * 4;
+    const bool in = n < d;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 y[2] = {acc, acc};
+    const float *src = p.partial + (size_t)t * p.gate_k * d + (in ? n : 0);     // (a token's rows of a slice are neighbours)
+    const int second = p.gate_k > 1 ? d : 0;
+    const size_t step = (size_t)p.n_assign * d;
+    for (int c = sg; c < S; c += NV * SG) {
+        float4 v[2][NV];
 #pragma unroll
-            for (int c = 0; c < 8; ++c)
-                v[c] = c < C ? *reinterpret_cast<const float4 *>(p.partial + ((size_t)c * p.n_assign + r) * d + n) : make_float4(0.f, 0.f, 0.f, 0.f);
-            float4 y = v[0];
+        for (int i = 0; i < NV; ++i) {
+            const float *q = src + min(c + i * SG, S - 1) * step;
+            v[0][i] = *reinterpret_cast<const float4 *>(q);
+            v[1][i] = *reinterpret_cast<const float4 *>(q + second);
+        }
 #pragma unroll
-            for (int c = 1; c < 8; ++c) { y.x += v[c].x; y.y += v[c].y; y.z += v[c].z; y.w += v[c].w; }
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const bool live = c + i * SG < S;
+                y[j].x += live ? v[j][i].x : 0.0f; y[j].y += live ? v[j][i].y : 0.0f; y[j].z += live ? v[j][i].z : 0.0f; y[j].w += live ? v[j][i].w : 0.0f;
+            }
+    }
+    if constexpr (SG > 1) {
+        s_sum[threadIdx.x] = y[0];
+        s_sum[256 + threadIdx.x] = y[1];
+        __syncthreads();
+        if (sg) return;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int g = 1; g < SG; ++g) {
+                const float4 v = s_sum[j * 256 + g * LANES + ln];
+                y[j].x += v.x; y[j].y += v.y; y[j].z += v.z; y[j].w += v.w;
+            }
+    }
+    if (!in) return;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        if (j >= p.gate_k) break;
+        const int a = t * p.gate_k + j, e = p.gate_idx[a];
+        if ((uint32_t)e >= (uint32_t)p.E) continue;     // (pruned: nothing of it was written)
+        const float sc = p.gate_scale[a];
+        float f[4] = {1.f, 1.f, 1.f, 1.f}, b[4] = {0.f, 0.f, 0.f, 0.f};
+        if (!p.g) {                             // channel scales (group scales are in the partial sums)
             const uint2 s2 = *reinterpret_cast<const uint2 *>(p.s2 + (size_t)e * d + n);
             const half2_t s01 = bits_h2(s2.x), s23 = bits_h2(s2.y);
-            float b[4] = {0.f, 0.f, 0.f, 0.f};
-            if (p.b2) {
-                const uint2 bb = *reinterpret_cast<const uint2 *>(p.b2 + (size_t)e * d + n);
-                const half2_t b01 = bits_h2(bb.x), b23 = bits_h2(bb.y);
-                b[0] = (float)b01[0]; b[1] = (float)b01[1]; b[2] = (float)b23[0]; b[3] = (float)b23[1];
-            }
-            acc.x += sc * (y.x * (float)s01[0] + b[0]);
-            acc.y += sc * (y.y * (float)s01[1] + b[1]);
-            acc.z += sc * (y.z * (float)s23[0] + b[2]);
-            acc.w += sc * (y.w * (float)s23[1] + b[3]);
+            f[0] = (float)s01[0]; f[1] = (float)s01[1]; f[2] = (float)s23[0]; f[3] = (float)s23[1];
         }
-        *reinterpret_cast<float4 *>(p.out + (size_t)t * d + n) = acc;
+        if (p.b2) {
+            const uint2 bb = *reinterpret_cast<const uint2 *>(p.b2 + (size_t)e * d + n);
+            const half2_t b01 = bits_h2(bb.x), b23 = bits_h2(bb.y);
+            b[0] = (float)b01[0]; b[1] = (float)b01[1]; b[2] = (float)b23[0]; b[3] = (float)b23[1];
+        }
+        acc.x += sc * (y[j].x * f[0] + b[0]);
+        acc.y += sc * (y[j].y * f[1] + b[1]);
+        acc.z += sc * (y[j].z * f[2] + b[2]);
+        acc.w += sc * (y[j].w * f[3] + b[3]);
+    }
+    if (p.out_dtype == MOE_F32) {
+        *reinterpret_cast<float4 *>((float *)p.out + (size_t)t * d + n) = acc;
+    } else {
+        const float v[4] = {acc.x, acc.y, acc.z, acc.w};
+        for (int i = 0; i < 4; ++i) store_out(p.out, p.out_dtype, (size_t)t * d + n + i, v[i]);
     }
 }
 
 // ---- host side -----------------------------------------------------------------------------------
 
-template <int BITS, int NB1, int TS, int NBC>
-static int launch_decode(const DecodeArgs &p, int grid, hipStream_t s)
+template <int BITS, bool GROUPED, bool BF>
+static void launch_decode(const DecodeArgs &p, dim3 grid, hipStream_t s)
 {
-    constexpr int FK = BITS == 4 ? 64 : 32;
-    constexpr int K1 = NB1 * FK;
-    const int lds = kDecFit * (K1 + kDecRowPad) * 2 + kDecFit * (kDecChunk + kDecRowPad) * 2;
-    if (p.early_ring) hipLaunchKernelGGL((decode_ffn_kernel<BITS, NB1, TS, NBC, true>), dim3(grid), dim3(kDecThreads), lds, s, p);
-    else hipLaunchKernelGGL((decode_ffn_kernel<BITS, NB1, TS, NBC, false>), dim3(grid), dim3(kDecThreads), lds, s, p);
-    int rc = check_launch("moe_grouped_ffn_wq_gated (decode kernel)");
-    if (rc || !p.out) return rc;                // (no output buffer: the partial sums are all the caller wants)
-    hipLaunchKernelGGL(decode_reduce_kernel, dim3(p.n_assign / p.gate_k), dim3(256), 0, s, p);
-    return check_launch("moe_grouped_ffn_wq_gated (slice reduction)");
+    if (p.cw == 1) hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 1>), grid, dim3(kDecThreads), 0, s, p);
+    else if (p.cw == 2) hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 2>), grid, dim3(kDecThreads), 0, s, p);
+    else if (p.cw == 4) hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 4>), grid, dim3(kDecThreads), 0, s, p);
+    else hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 8>), grid, dim3(kDecThreads), 0, s, p);
 }
 
-// Sizes the decode kernel is built for: d_model of sixteen fragment blocks (1024 with 4-bit, 512 with
-// 8-bit weights), d_ff in slices of 512 channels (at most eight), few rows per expert.
-bool decode_ffn_supports(int n_assign, int E, int d, int F, int bits)
+template <int BITS>
+static void launch_decode_bits(const DecodeArgs &p, bool bf, dim3 grid, hipStream_t s)
 {
-    if (bits != 4 && bits != 8) return false;
-    if (n_assign < 1 || n_assign > kGatedMaxAssign || E < 1 || E > kDecMaxExperts) return false;
-    if (d != (bits == 4 ? 1024 : 512) || F % kDecChunk || F / kDecChunk > 8 || F < kDecChunk) return false;
-    // few rows per expert (a pass takes sixteen) and enough items to give a quarter of the compute units one
-    return (long)n_assign <= 8L * E && (long)E * (F / kDecChunk) >= 64;
+    if (p.g) bf ? launch_decode<BITS, true, true>(p, grid, s) : launch_decode<BITS, true, false>(p, grid, s);
+    else bf ? launch_decode<BITS, false, true>(p, grid, s) : launch_decode<BITS, false, false>(p, grid, s);
 }
 
-size_t decode_ffn_partial_bytes(int n_assign, int d, int F)
+// Sizes the kernel takes.
+bool decode_ffn_supports(int n_assign, int k, int E, int d, int F, int bits, int group_size)
 {
-    return (size_t)(F / kDecChunk) * n_assign * d * sizeof(float);
+    if (n_assign < 1 || n_assign > kDecMaxAssign || k < 1 || k > 2 || E < 1 || E > kDecMaxExperts || d <= 0 || F <= 0 || d % 64 || F % 64) return false;
+    if ((bits != 4 && bits != 8) || group_size < 0 || (group_size && (group_size % 64 || d % group_size || F % group_size))) return false;
+    return (long)n_assign * d < (1l << 29) && (long)d * F * bits / 8 < (1l << 31);      // offsets into x and the partial sums have 31 bits
 }
 
-static int decode_ffn_grid(int items)
+// Experts that n_assign assignments are expected to touch under uniform routing.
+double decode_active_experts(int n_assign, int E)
 {
-    static int cus = 0;                          // compute units of the current device (one workgroup fits each)
-    if (!cus) {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) cus = n;
-        else cus = 64;
-    }
-    return items < cus ? items : cus;
+    return E * (1.0 - pow(1.0 - 1.0 / E, n_assign));
 }
 
-int launch_decode_ffn(const DecodeArgs &q, int bits, hipStream_t s)
+// Channels of d_ff per slice, in 64s: the widest slice that still gives every compute unit a block, give or take.  Narrow slices
+// spread few experts over the chip; each slice leaves a partial sum of every row behind, so wide ones move less.  (us a step, slices
+// of 64 / 128 / 256 / 512: 1 token, two of 32 experts of 1024 x 4096, 4-bit 17.6 / 20.6 / 24.6 / 33; 16 tokens 36 / 32 / 32 / 37.5; 64 tokens 54 /
+// 48 / 40 / 42; 80 tokens on 16 experts of 4096 x 16384, group scales 357 / 281 / 264 / 227.  Over 390 drawn sizes this rule is 2 %
+// slower than the best width of each, at most 17 %.)
+int decode_slice_width(int n_assign, int E, int d, int F, int bits)
+{
+    (void)d, (void)bits;
+    const double blocks64 = decode_active_experts(n_assign, E) * (F / 64);
+    int w = 1;
+    for (int c = 2; c <= 8; c *= 2)
+        if (F % (64 * c) == 0 && blocks64 / c >= 254) w = c;
+    return w;
+}
+
+size_t decode_ffn_partial_bytes(int n_assign, int d, int F, int cw)
+{
+    return (size_t)(F / (64 * cw)) * n_assign * d * sizeof(float);
+}
+
+int launch_decode_ffn(const DecodeArgs &q, int bits, bool bf, hipStream_t s)
 {
     DecodeArgs p = q;
-    p.items1 = p.E * (p.F / kDecChunk);
-    // three or more assignments per expert: under uniform routing at most one expert in twenty is empty, and the
-    // early ring of such an expert is a quarter of its weights
-    p.early_ring = p.n_assign >= 3 * p.E;
-    const int grid = decode_ffn_grid(p.items1);
-    if (bits == 4) return launch_decode<4, 16, 2, 8>(p, grid, s);
-    return launch_decode<8, 16, 1, 16>(p, grid, s);
+    const uint32_t units = p.g ? p.g / 64 : 1;
+    p.group_inv = units > 1 ? (uint32_t)(((1ull << 32) + units - 1) / units) : 0;
+    const int S = p.F / (64 * p.cw);
+    const dim3 grid(1 + (unsigned)(p.E < p.n_assign ? p.E : p.n_assign) * S);      // (the first block writes the index arrays)
+    if (bits == 4) launch_decode_bits<4>(p, bf, grid, s);
+    else launch_decode_bits<8>(p, bf, grid, s);
+    int rc = check_launch("moe_grouped_ffn_wq (decode kernel)");
+    if (rc || !p.out) return rc;                // (no output buffer: the partial sums are all the caller wants)
+    const int T = p.n_assign / p.gate_k;
+    auto blocks = [&](int sg) { return dim3(T, (p.d + 1024 / sg - 1) / (1024 / sg)); };
+    if (S > 32) hipLaunchKernelGGL((decode_reduce_kernel<16, 4>), blocks(16), dim3(256), 0, s, p);
+    else if (S > 8) hipLaunchKernelGGL((decode_reduce_kernel<8, 4>), blocks(8), dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((decode_reduce_kernel<4, 2>), blocks(4), dim3(256), 0, s, p);
+    return check_launch("moe_grouped_ffn_wq (slice reduction)");
 }
 
 }  // namespace moe

@@ -61,6 +61,14 @@ class MoEExpertLayer:
         self.gated = 0
         if fuse_routing and B.moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype):
             self.gated = B.moe_grouped_ffn_wq_gated_supported(T, k, E, d, F, bits, group_size, act_dtype)
+        # few rows per expert, of any kind: gate, one streaming launch for everything up to y, its reduction (y is never stored:
+        # not for a layer that asks for a type of y)
+        self.sliced = bool(fuse_routing) and y_dtype is None and B.moe_grouped_ffn_wq_sliced_pays(T, k, E, d, F, bits, group_size, act_dtype)
+        if self.sliced:
+            self.gated, self.routed = 2, False
+            need = B.moe_grouped_ffn_wq_sliced_workspace_bytes(T, k, E, d, F, bits, group_size, act_dtype)
+            if need > self.ws_ffn.numel():
+                self.ws_ffn = torch.empty(need, dtype=torch.uint8, device=dev)
 
     # -- offline: quantise one expert matrix from its fp32 master (which = 1 | 2) ------------
     def load_expert(self, which: int, e: int, w_fp32, q_canon_out=None):
@@ -97,8 +105,8 @@ class MoEExpertLayer:
         """The decode path's streaming kernel without its slice reduction (the gated call with a NULL output), for
         timing that kernel alone.  Raises MoeError where the FFN call does not take the decode kernel."""
         fn, args, what = [c for c in self._plan(x, finished) if c[2].startswith("moe_grouped_ffn_wq")][0]
-        if what != "moe_grouped_ffn_wq_gated":
-            raise B.MoeError("ffn_streaming_kernel_only: this layer does not run the gated FFN call")
+        if what not in ("moe_grouped_ffn_wq_gated", "moe_grouped_ffn_wq_sliced"):
+            raise B.MoeError("ffn_streaming_kernel_only: this layer does not run the decode kernel")
         bare = self._bare.get(id(args))
         if bare is None:
             if len(self._bare) > 256:
@@ -153,6 +161,13 @@ class MoEExpertLayer:
                                     int(self.renormalize), p(self.expert_idx), p(self.expert_scale), st), "moe_gate_topk")
         combine = (lib.moe_combine, (p(self.y_perm), ydt, p(self.inv_perm), p(self.expert_scale), active, self.T, self.k,
                                      self.d, p(self.out), odt, st), "moe_combine")
+        if self.sliced:
+            ffn = (lib.moe_grouped_ffn_wq_sliced,
+                   (p(x), dt, p(self.expert_idx), p(self.expert_scale), self.T, self.k, self.E, self.d, self.F, self.bits,
+                    self.group_size, self.activation, p(self.w1_packed), p(self.s1), p(self.b1), p(self.w2_packed), p(self.s2),
+                    p(self.b2), p(self.out), odt, p(self.perm_src), p(self.inv_perm), p(self.expert_offsets), p(self.ws_ffn),
+                    self.ws_ffn.numel(), st), "moe_grouped_ffn_wq_sliced")
+            return [gate, ffn]
         if self.gated:
             # level 2 with an fp32 layer output: fc2 adds the scaled rows straight into out (no combine launch)
             fused = self.gated == 2 and self.out_dtype == torch.float32
