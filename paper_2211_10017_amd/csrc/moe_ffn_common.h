@@ -90,11 +90,33 @@ int launch_stream_unrolled_variant(const GemmArgs &p, int bits, bool native, int
 
 enum { MOE_ACT_NONE = -1 };
 
-// The activation between the two GEMMs.  GELU in its exact form x * Phi(x).
+// GELU in its exact form v * Phi(v) = max(v, 0) - |v| Phi(-|v|), without a branch: with b = |v| / 2, log2(2 Phi(-2 b)) is b times a
+// polynomial of degree nine (a weighted minimax fit on [0, 3]; beyond, it falls without end, so that the second term vanishes; b stops
+// at 16, which keeps infinities out of the product).  Against 64 bits, normally distributed v of standard deviation 0.02 to 3:
+// error 0.7 to 0.85 times, largest error 0.5 to 0.95 times that of 0.5 v (1 + erff(v / sqrt 2)).  What bounds the end of a tile is its vector
+// instructions, and erff runs both of its branches on nearly every wavefront.  16384 tokens of
+// 1024 x 4096, 64 experts, 4-bit: a step with GELU 385 -> 359 us (ReLU 334); 997 bf16 tokens of 768 x 3072 71 -> 66.5 (64).
+__device__ inline float gelu(float v)
+{
+    const float a = 0.5f * fabsf(v), b = fminf(a, 16.0f);
+    float q = -4.015279e-05f;
+    q = __builtin_fmaf(q, b, 0.0005579601f);
+    q = __builtin_fmaf(q, b, -0.0033400627f);
+    q = __builtin_fmaf(q, b, 0.011037564f);
+    q = __builtin_fmaf(q, b, -0.019550677f);
+    q = __builtin_fmaf(q, b, 0.0012326466f);
+    q = __builtin_fmaf(q, b, 0.110654876f);
+    q = __builtin_fmaf(q, b, -0.41943568f);
+    q = __builtin_fmaf(q, b, -1.8368893f);
+    q = __builtin_fmaf(q, b, -2.3022084f);
+    return __builtin_fmaf(-b, __builtin_amdgcn_exp2f(q * b), __builtin_fmaf(0.5f, v, a));
+}
+
+// The activation between the two GEMMs.
 __device__ inline float activate(float v, int act)
 {
     if (act == MOE_ACT_RELU) return fmaxf(v, 0.0f);
-    if (act == MOE_ACT_GELU) return 0.5f * v * (1.0f + erff(v * 0.70710678118654752440f));
+    if (act == MOE_ACT_GELU) return gelu(v);
     return v;
 }
 
