@@ -4,8 +4,8 @@
 // fused multiply-adds, so the contract's sequential partial sums (128-element blocks of the feature axis dealt round-robin to
 // four sums) run on the matrix cores bit for bit: a wavefront owns one of the four partial sums for a tile of tokens and
 // experts, the four meet in LDS, and sixteen lanes finish a token.  Two tilings: gate_mfma_kernel (16 tokens x 16 experts
-// per instruction) and gate_quad_kernel (4 tokens x 64 experts); few tokens by more than 64 experts take the vector ALU
-// (gate_lanes_kernel).  T = 8192, d = 4096, 64 experts: 196 -> 48 us (bf16 208 ->
+// per instruction) and gate_quad_kernel (4 tokens x 64 experts); few tokens take the vector ALU with a lane per expert or several
+// experts per lane (gate_token_kernel, gate_lanes_kernel).  T = 8192, d = 4096, 64 experts: 196 -> 48 us (bf16 208 ->
 // 47), T = 4096, d = 2048, 128 experts: 76 -> 28.6 us, T = 16384, d = 1024, 64 experts: 55 -> 32 us against multiply-adds in
 // the vector ALU with a lane per expert or per token; T = 64, d = 1024, 32 experts: 13 -> 9 us with cold caches.
 #include <math.h>
@@ -62,8 +62,8 @@ __device__ inline void store_choice(int t, int T, int E, int k, int renorm, cons
         expert_scale[t] = 1.0f / den;
     } else {
         const float e2 = expf(selv[1] - selv[0]);
-        float s0 = 1.0f / den, s1 = e2 / den;
-        if (renorm) { s0 = 1.0f / (1.0f + e2); s1 = e2 / (1.0f + e2); }
+        if (renorm) den = 1.0f + e2;
+        const float s0 = 1.0f / den, s1 = e2 / den;
         expert_idx[2 * t] = sel[0];
         expert_idx[2 * t + 1] = sel[1];
         expert_scale[2 * t] = s0;
@@ -129,14 +129,17 @@ __device__ inline void finish_tokens(const float *part, int NT, int ld, int t0, 
             sel[r] = be;
             selv[r] = bv;
         }
-        const float lmax = selv[0];
-        float den = 0.0f;
+        float den = 1.0f;
+        if (k == 1 || !renorm) {                        // (two experts renormalised: their own two terms are all there is to it)
+            const float lmax = selv[0];
+            den = 0.0f;
 #pragma unroll
-        for (int s = 0; s < S; ++s)
+            for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int q = 0; q < NB; ++q)
-                if ((s * LANES + j) * NB + q < E) den += expf(lg[s][q] - lmax);
-        steps([&](auto off) { den += butterfly_partner<decltype(off)::value>(den); });
+                for (int q = 0; q < NB; ++q)
+                    if ((s * LANES + j) * NB + q < E) den += expf(lg[s][q] - lmax);
+            steps([&](auto off) { den += butterfly_partner<decltype(off)::value>(den); });
+        }
         if (j == 0 && t < T) store_choice(t, T, E, k, renorm, sel, selv, den, finished, expert_idx, expert_scale);
     }
 }
@@ -539,6 +542,94 @@ __global__ __launch_bounds__(256) void gate_lanes_kernel(const uint16_t *__restr
     finish_tokens<NE == 2 ? 2 : 1, 4, NE <= 2 ? 16 : 64>(part, NT, ld, t0, p, 4, bias, finished, min(T, t0 + TB), E, k, renorm, expert_idx, expert_scale);
 }
 
+// Few tokens by 17 to 64 experts, E a multiple of eight: a lane per expert, EP = 32 or 64 lanes per token, 64 / EP tokens per block, plain fp32
+// multiply-adds.  The block takes 512 features at a time (128 of each partial sum): the gate weight's part of them goes through
+// LDS, eight features of an expert side by side, so that an octet of a chain is one 16-byte read of weights and one of the token.
+// What bounds so small a launch is its latencies in a row: the code (about 100 clocks per 64 bytes that a compute unit has not run
+// before, hence one rolled loop), the loads (all of a chunk's at once, 16 bytes each, the next chunk's under this one's chains) and the chains
+// themselves, 8 clocks per feature of a partial sum.
+template <bool BF16, int EP>
+__global__ __launch_bounds__(256) void gate_token_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
+                                                         const float *__restrict__ bias,
+                                                         const uint8_t *__restrict__ finished, int T, int d, int E,
+                                                         int k, int renorm, int32_t *__restrict__ expert_idx,
+                                                         float *__restrict__ expert_scale)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int NT = 64 / EP, OCT = 64;               // tokens of the block, octets of a chunk
+    constexpr int SB = EP == 64 ? 2 : 1;                // 8 x 8 blocks of the gate weight per thread and chunk
+    constexpr int ld = EP + 4;
+    __shared__ u32x4 s_w[OCT * EP], s_x[NT * OCT];
+    float *part = reinterpret_cast<float *>(s_w);       // at the end: [4][4][ld]
+    static_assert(16 * ld * 4 <= OCT * EP * 16, "the partial sums fit where the weights were");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int p = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t0 = blockIdx.x * NT, rows = min(NT, T - t0);
+    const int groups = E >> 3;
+    int w_off[SB], oc[SB], eg[SB];
+#pragma unroll
+    for (int b = 0; b < SB; ++b) {
+        const int id = tid + 256 * b;
+        oc[b] = id / groups, eg[b] = id - oc[b] * groups;
+        w_off[b] = (oc[b] * 8 * E + eg[b] * 8) * 2;
+    }
+    const int x_off = (min(tid >> 6, rows - 1) * d + (tid & 63) * 8) * 2;
+    u32x4 W[SB][8], X;
+    // (extents end with the buffers: what lies past the last feature reads as zero or as the next token's, and is not used)
+    auto load = [&](int c) {
+        const int left = max(d - c * 512, 0);
+        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg + (size_t)c * 512 * E), 0, left * E * 2, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d + c * 512), 0, left ? (rows * d - c * 512) * 2 : 0, 0x00020000);
+#pragma unroll
+        for (int b = 0; b < SB; ++b)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) W[b][i] = __builtin_amdgcn_raw_buffer_load_b128(rw, w_off[b] + i * E * 2, 0, 0);
+        if (tid < NT * OCT) X = __builtin_amdgcn_raw_buffer_load_b128(rx, x_off, 0, 0);
+    };
+    load(0);
+    const int e = lane % EP, sub = lane / EP, ec = min(e, E - 1);
+    // (an expert's slot within its eight: turned by the number of the eight, so that neighbouring threads' writes spread over the banks)
+    const u32x4 *w_ptr = s_w + p * 16 * E + (ec & ~7) + ((ec & 7) ^ ((ec >> 3) & 7)), *x_ptr = s_x + sub * OCT + p * 16;
+    float acc = 0.0f;
+    for (int c = 0; c * 512 < d; ++c) {
+#pragma unroll
+        for (int b = 0; b < SB; ++b)
+            if (oc[b] < OCT) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    u32x4 v;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] = __builtin_amdgcn_perm(W[b][2 * q + 1][j >> 1], W[b][2 * q][j >> 1], j & 1 ? 0x07060302u : 0x05040100u);
+                    s_w[oc[b] * E + eg[b] * 8 + (j ^ (eg[b] & 7))] = v;
+                }
+            }
+        if (tid < NT * OCT) s_x[tid] = X;
+        __syncthreads();
+        load(c + 1);
+        const int n = min(max((d - (4 * c + p) * kGateBlk) >> 3, 0), 16);      // octets of this partial sum's block
+        auto octet = [&](u32x4 xv, u32x4 wv) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                acc = fmaf(act_to_float<BF16>((uint16_t)xv[q]), act_to_float<BF16>((uint16_t)wv[q]), acc);
+                acc = fmaf(act_to_float<BF16>((uint16_t)(xv[q] >> 16)), act_to_float<BF16>((uint16_t)(wv[q] >> 16)), acc);
+            }
+        };
+        int o = 0;
+        for (; o + 4 <= n; o += 4) {
+            u32x4 xv[4], wv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) xv[i] = x_ptr[o + i], wv[i] = w_ptr[(o + i) * E];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) octet(xv[i], wv[i]);
+        }
+        for (; o < n; ++o) octet(x_ptr[o], w_ptr[o * E]);
+        __syncthreads();
+    }
+    part[(p * 4 + sub) * ld + e] = acc;
+    __syncthreads();
+    finish_tokens<1, EP / 16>(part, 4, ld, t0, p, 4, bias, finished, min(T, t0 + NT), E, k, renorm, expert_idx, expert_scale);
+}
+
 template <bool BF16, int NB, int S, int TT, int R, GateLoads LOADS>
 static void launch_gate_mfma(const uint16_t *x, const uint16_t *wg, const float *bias, const uint8_t *finished, int T, int d, int E,
                                  int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
@@ -555,7 +646,16 @@ static void launch_gate(const uint16_t *x, const uint16_t *wg, const float *bias
                         int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
 {
     const GateLoads pairs = E % 2 ? ODD_PAIRS : PAIRS;
-    // 33 to 64 experts and up to four tokens per compute unit: four-token blocks on the matrix cores.  (64 experts, T = 64: 10.0 against
+    // 17 to 64 experts, a multiple of eight, while the blocks of one or two tokens find a compute unit each: a lane per expert with the gate
+    // weight in LDS, against the forms below.  (Caches warm, d = 1024, FP16: 32 experts, 1 / 64 / 512 tokens 5.9 / 6.4 / 6.5 -> 4.7 / 5.0 / 5.3 us,
+    // 700 6.6 / 6.2, 1500 6.7 / 7.3; 64 experts, 1 / 64 / 256 tokens 6.9 / 8.2 / 8.5 -> 6.0 / 6.5 / 6.7, 700 9.3 / 12.5; 64 tokens, 64
+    // experts, d = 4096 21.0 -> 16.2, bf16 24.8 -> 18.5.  Up to 16 experts it gains nothing below d = 1024 and loses beyond.)
+    if (E > 16 && E <= 64 && E % 8 == 0 && T <= (E <= 32 ? 512 : 256)) {
+        if (E <= 32) hipLaunchKernelGGL((gate_token_kernel<BF16, 32>), dim3((T + 1) / 2), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        else hipLaunchKernelGGL((gate_token_kernel<BF16, 64>), dim3(T), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        return;
+    }
+    // 33 to 64 experts else and up to four tokens per compute unit: four-token blocks on the matrix cores.  (64 experts, T = 64: 10.0 against
     // 12.7 us for sixteen-token blocks at d = 1024, 25.8 against 28.0 us at d = 4096; T = 2048: 17.5 against 11.8 us.)  FP16 tokens,
     // more than one such block and up to a token per compute unit: a lane per expert.  (48 experts, T = 16: 8.4 against 9.4 us, 21.0
     // against 25.1; T = 300: 12.3 against 9.6; one token 7.6 against 7.3; bf16 9.2 against 9.4, 26.5 against 25.2.)
@@ -601,7 +701,7 @@ static void launch_gate(const uint16_t *x, const uint16_t *wg, const float *bias
     else if (E <= 32) {
         if (E % 2) MOE_GATE_MFMA(2, 1, 1, 4, ODD_PAIRS);
         else if (two) MOE_GATE_MFMA(2, 1, 2, 4, WIDE);
-        else MOE_GATE_MFMA(2, 1, 1, 8, WIDE);
+        else MOE_GATE_MFMA(2, 1, 1, 4, WIDE);
     } else if (E <= 64) {
         if (E % 2) MOE_GATE_MFMA(4, 1, 1, 4, ODD_PAIRS);
         else if (E % 4) MOE_GATE_MFMA(4, 1, 1, 4, PAIRS);
