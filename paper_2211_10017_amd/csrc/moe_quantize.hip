@@ -1,6 +1,8 @@
 // moe_quantize_experts: symmetric range-based weight quantisation (Sec. 3.4) producing the
 // interchange codes, the fp16 scales and the pre-shuffled offset-binary layout (Sec. 3.4.1)
 // that the grouped FFN kernels stream.
+#include <type_traits>
+
 #include "moe_common.h"
 
 namespace moe {
@@ -10,9 +12,11 @@ namespace moe {
 // the channel whose codes are lane l's 16 bytes of the packed block: it reads 128-byte row segments (two rows per
 // instruction) and stores 1 KB per block.  What bounds it is reading the fp32 masters, so they are read once: 128 rows per
 // wavefront stay in registers between the search for the largest magnitude and the conversion, and only rows
-// beyond WU x 128 are read a second time.  (32 experts of 1024 x 4096, 4-bit: 332 -> 141 us, 4.3 TB/s; 4096 x 1024:
-// 940 -> 174 us.)
-template <int BITS, int WU, bool CANON>
+// beyond WU x 128 are read a second time.  A compute unit has room for two blocks, so what a block takes to convert is time in which
+// little is being read: the codes are put together by fp32 multiply-adds, and masters that no cache holds and that are read once
+// (NT) are loaded non-temporal.  (32 experts of 1024 x 4096, 4-bit: 332 us with two reads in strips, 143 with shifts and plain loads, 129 with
+// multiply-adds, 122 with both, 5.0 TB/s; 8-bit 147 -> 134; groups of 128 124 -> 108; 4096 x 1024, which is read twice: 174 -> 171.)
+template <int BITS, int WU, bool CANON, bool NT>
 __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const float *__restrict__ w, int K, int N, int g,
                                                                          long units, int8_t *__restrict__ q_canon,
                                                                          __half *__restrict__ scales,
@@ -45,7 +49,7 @@ __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const f
 #pragma unroll
         for (int j = 0; j < J; ++j)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[j][i] = p[(size_t)(16 * j + i) * N];
+            for (int i = 0; i < 8; ++i) v[j][i] = NT ? __builtin_nontemporal_load(p + (size_t)(16 * j + i) * N) : p[(size_t)(16 * j + i) * N];
     };
     auto largest = [&](const float (&v)[J][8], float m) __attribute__((always_inline)) {
 #pragma unroll
@@ -85,36 +89,43 @@ __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const f
     // has codes of zero, an infinite one as well, but for the infinite weights that it may come from (inf / inf: the lowest code).
     const bool finite = s <= 65504.0f;
     const float y = s != 0.0f && finite ? 1.0f / s : 0.0f, sd = finite ? s : 0.0f, lim = s != 0.0f ? (float)QMAX : 0.0f;
-    auto code_of = [&](float x) __attribute__((always_inline)) {
+    auto code_of = [&](float x) __attribute__((always_inline)) -> float {
         float q = x * y;
         q = fmaf(fmaf(-q, sd, x), y, q);
         q = fmaf(fmaf(-q, sd, x), y, q);
-        return (int)fminf(fmaxf(rintf(q), -lim), lim);
+        return __builtin_amdgcn_fmed3f(rintf(q), -lim, lim);
     };
     auto convert = [&](int b, const float (&v)[J][8]) __attribute__((always_inline)) {
         uint32_t word[4];
-        int code[J][8];
+        float fc[J][8];
 #pragma unroll
         for (int j = 0; j < J; ++j)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) code[j][i] = code_of(v[j][i]);
+            for (int i = 0; i < 8; ++i) fc[j][i] = code_of(v[j][i]);
+        // codes are put together as sums of fp32 numbers below 2^24, which are exact: fewer steps than shifts of each
         if (BITS == 4) {
 #pragma unroll
-            for (int j = 0; j < J; ++j) {
-                uint32_t x = 0;
+            for (int j = 0; j < J; ++j) {       // nibble positions 0,4,1,5,2,6,3,7: even codes in the lower half, odd ones in the upper
+                float h[2];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) x |= (uint32_t)(code[j][i] + 8) << (4 * ((i >> 1) + 4 * (i & 1)));      // nibble positions 0,4,1,5,2,6,3,7
-                word[j] = x;
+                for (int o = 0; o < 2; ++o) h[o] = fmaf(fc[j][6 + o], 4096.0f, fmaf(fc[j][4 + o], 256.0f, fmaf(fc[j][2 + o], 16.0f, fc[j][o] + 34952.0f)));
+                word[j] = (uint32_t)h[0] | (uint32_t)h[1] << 16;
             }
         } else {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                uint32_t x = 0;
+                float h[2];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) x |= (uint32_t)(code[q >> 1][4 * (q & 1) + i] + 128) << (8 * i);
-                word[q] = x;
+                for (int o = 0; o < 2; ++o) h[o] = fmaf(fc[q >> 1][4 * (q & 1) + 2 * o + 1], 256.0f, fc[q >> 1][4 * (q & 1) + 2 * o] + 32896.0f);
+                word[q] = (uint32_t)h[0] | (uint32_t)h[1] << 16;
             }
         }
+        int code[CANON ? J : 1][8];
+        if constexpr (CANON)
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) code[j][i] = (int)fc[j][i];
         const int kb = gi * nblk + b;
         if (q_packed)
             *reinterpret_cast<uint4 *>(q_packed + (size_t)e * packed_bytes_per_expert(K, N, BITS) + ((size_t)nb * (K / FK) + kb) * kFragBytes +
@@ -159,10 +170,15 @@ static void launch_quantize(const float *w, int E, int K, int N, int g, void *q_
     constexpr int UPB = (WU == 16 ? 16 : 8) / WU;
     const long units = (long)E * (K / g) * (N / 32);
     const dim3 grid((unsigned)((units + UPB - 1) / UPB)), block(WU == 16 ? 1024 : 512);
-    if (q_canon)
-        hipLaunchKernelGGL((quantize_kernel<BITS, WU, true>), grid, block, 0, s, w, K, N, g, units, (int8_t *)q_canon, (__half *)scales, (uint8_t *)q_packed);
-    else
-        hipLaunchKernelGGL((quantize_kernel<BITS, WU, false>), grid, block, 0, s, w, K, N, g, units, (int8_t *)nullptr, (__half *)scales, (uint8_t *)q_packed);
+    // masters larger than the L2s together, units that the registers hold (a second read finds part of its rows in the last-level cache: 4096 x
+    // 1024 171 us plain, 184 non-temporal; one expert of 1024 x 4096 just written 7.8 and 8.5)
+    const bool nt = (size_t)E * K * N >= (size_t)16 << 20 && g <= WU * 128;
+    auto launch = [&](auto canon, auto once) {
+        hipLaunchKernelGGL((quantize_kernel<BITS, WU, decltype(canon)::value, decltype(once)::value>), grid, block, 0, s, w, K, N, g, units, (int8_t *)q_canon,
+                           (__half *)scales, (uint8_t *)q_packed);
+    };
+    if (q_canon) nt ? launch(std::true_type{}, std::true_type{}) : launch(std::true_type{}, std::false_type{});
+    else nt ? launch(std::false_type{}, std::true_type{}) : launch(std::false_type{}, std::false_type{});
 }
 
 // Wavefronts per unit: the fewest whose registers hold the unit (128 rows each), sixteen for the longest.

@@ -56,3 +56,17 @@ def test_quantize_units_bit_exact(bits, g, E, K, N):
     assert np.array_equal(scales.cpu().numpy().view(np.uint16), os_) and torch.equal(scales, scales2)
     assert torch.equal(packed, packed2)
     assert np.array_equal(_unpack(packed.cpu().numpy(), E, K, N, bits), oq)
+
+
+@pytest.mark.parametrize("bits,g,E,K,N", [(4, 0, 17, 1024, 1024), (8, 128, 9, 768, 2560), (4, 0, 4, 2048, 2080), (8, 0, 2, 4096, 2112)])
+def test_large_masters_give_the_bytes_of_their_experts(bits, g, E, K, N):
+    """Masters of more than 64 MB are loaded non-temporal where the registers hold a unit: expert by expert they are not."""
+    print(f"quantize large bits={bits} g={g} E={E} K={K} N={N}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(K + N)
+    w = torch.randn((E, K, N), generator=gen, device="cuda") * 0.02
+    canon, scales, packed = B.moe_quantize_experts(w, bits, g)
+    packed2 = B.moe_quantize_experts(w, bits, g, want_canon=False)[2]
+    for e in range(E):
+        c, s, p = B.moe_quantize_experts(w[e:e + 1].contiguous(), bits, g)
+        assert torch.equal(canon[e], c[0]) and torch.equal(scales[e], s[0]) and torch.equal(packed.view(E, -1)[e], p.view(-1))
+    assert torch.equal(packed, packed2)
