@@ -480,16 +480,23 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
     using namespace moe;
     if (T <= 0 || (act_dtype != MOE_F16 && act_dtype != MOE_BF16)) return 0;
     if ((long)T * k > kDecMaxAssign || !decode_ffn_supports(T * k, k, E, d, F, bits, group_size)) return 0;
-    return round_up(decode_ffn_partial_bytes(T * k, d, F, decode_slice_width(T * k, E, d, F, bits)), 256);
+    return round_up(decode_ffn_partial_bytes(T * k, d, F, decode_slice_width(T * k, E, F)), 256);
 }
 
 // Whether a layer should take the sliced call (steps in us of the routes below against it; 390 drawn sizes of up to 256 tokens, of
 // which the rule sends 80 % here: 1.4 times as fast on average, none slower):
 //  - up to eight assignments per expert: a pass takes sixteen rows, and experts with more stream their weights again (61 tokens, two of
-//    eight experts of 4096 x 16384 8-bit 188 and 318; 134 tokens on 16 of 512 x 2048 21.0 and 24.1; 5 per expert of 1024 x 4096 44 and 41);
+//    eight experts of 4096 x 16384 8-bit 188 and 318; 134 tokens on 16 of 512 x 2048 21.0 and 24.1; 5 per expert of 1024 x 4096 44 and 41).
+//    FP16 rows on 4-bit codes, whose passes then take thirty-two: up to sixteen, 150 MB of weights and a d_ff of twice d (192 tokens,
+//    two of 32 experts of 1024 x 4096 51.6 and 45.2, 144 on 16 39.7 and 32.0; 242 tokens, two of 32 of 2048 x 8192 130 and 143; 191 of 1536 x
+//    2048 42.6 and 43.5), with group scales twelve, 110 MB and four times d (71 tokens, two of 16 of 1024 x 4096 48.0 and 36.9; 154, two of 32
+//    51.6 and 52.3; 96, two of 16 of 2048 x 4096 55 and 58), but not where one and a bit blocks per compute unit would keep some busy
+//    twice as long as others (250 tokens, two of 60 of 1536 x 1280, 300 blocks, 54.5 and 58.3);
 //  - the partial sums of a slice, rows x d x 4 bytes, well below its weights (narrow slices, where d_ff leaves no wider ones);
 //  - up to 300 MB of weights: beyond, the launch's fixed parts count little and the ring's loads into LDS keep more in flight (30 tokens
-//    on 32 experts of 4096 x 16384 8-bit 452 and 520; 79 on 64 of 1024 x 4096 8-bit, 382 MB, 83.5 and 85.8; 4-bit 104 MB 47 and 32); FP16
+//    on 32 experts of 4096 x 16384 8-bit 452 and 520; 79 on 64 of 1024 x 4096 8-bit, 382 MB, 83.5 and 85.8; 4-bit 104 MB 47 and 32), and
+//    180 MB for FP16 rows on 8-bit codes with channel scales where the gated call streams (28 / 40 / 60 / 100 / 200 tokens on 32 of 1024 x
+//    4096 44.8 / 43.5 / 50.0 / 55.3 / 59.7 and 43.2 / 45.6 / 49.9 / 55.2 / 63.8); FP16
 //    rows with group scales, whose scales the ring multiplies into the weights, at any size (64 tokens, 64 experts of 4096 x 16384 809 and 711).
 extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
 {
@@ -497,8 +504,16 @@ extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F,
     if (!moe_grouped_ffn_wq_sliced_workspace_bytes(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
     const int R = T * k;
     const double active = decode_active_experts(R, E), bytes = active * 2 * d * F * bits / 8;
-    const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
-    return R <= 8L * E && 5 * R <= 4 * active * decode_slice_width(R, E, d, F, bits) * bits && (bytes <= 300e6 || (grouped && act_dtype == MOE_F16));
+    const bool grouped = group_size != 0 && !(group_size == d && group_size == F), f16 = act_dtype == MOE_F16;
+    const int cw = decode_slice_width(R, E, F);
+    const double blocks = active * (F / 64) / cw;
+    if (5 * R > 4 * active * cw * bits) return 0;
+    if (R > 8L * E) {
+        const bool fits = grouped ? R <= 12L * E && F >= 4 * d && bytes <= 110e6 : R <= 16L * E && F >= 2 * d && bytes <= 150e6;
+        return f16 && bits == 4 && fits && (blocks <= 260 || blocks > 400);
+    }
+    if (bits == 8 && f16 && !grouped && R > E && bytes > 180e6 && (double)E * d * F <= 150e6) return 0;
+    return bytes <= 300e6 || (grouped && f16);
 }
 
 extern "C" int moe_grouped_ffn_wq_sliced(const void *x, int act_dtype, const int32_t *expert_idx, const float *expert_scale, int T, int k, int E,
@@ -524,7 +539,7 @@ extern "C" int moe_grouped_ffn_wq_sliced(const void *x, int act_dtype, const int
     reset_kernel_notes();
     DecodeArgs q{};
     q.x = (const uint16_t *)x; q.gate_idx = expert_idx; q.gate_scale = expert_scale; q.n_assign = T * k; q.gate_k = k;
-    q.E = E; q.d = d; q.F = F; q.act = activation; q.cw = decode_slice_width(T * k, E, d, F, bits);
+    q.E = E; q.d = d; q.F = F; q.act = activation; q.cw = decode_slice_width(T * k, E, F);
     q.g = group_size == d && group_size == F ? 0 : group_size;
     q.w1 = (const uint8_t *)w1_packed; q.w2 = (const uint8_t *)w2_packed;
     q.s1 = (const __half *)s1; q.s2 = (const __half *)s2; q.b1 = (const __half *)b1; q.b2 = (const __half *)b2;

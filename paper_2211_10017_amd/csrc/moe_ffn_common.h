@@ -54,6 +54,7 @@ struct DecodeArgs {
     int g;                      // group size of the scales, 0 = per channel
     uint32_t group_inv;         // 2^32 / (g / 64), rounded up, 0 for groups of 64 (set by the launcher)
     int cw;                     // channels of d_ff per slice, in 64s: 1, 2, 4 or 8
+    int row_tiles;              // sixteens of rows per pass: 1 or 2 (set by the launcher)
     const uint8_t *w1, *w2;     // packed codes
     const __half *s1, *s2;      // scales [E, d / g, F] / [E, F / g, d], one row per expert for channel scales
     const __half *b1, *b2;      // biases or null
@@ -66,7 +67,7 @@ constexpr int kDecMaxExperts = 4096;
 constexpr int kDecMaxAssign = 512;
 bool decode_ffn_supports(int n_assign, int k, int E, int d, int F, int bits, int group_size);
 size_t decode_ffn_partial_bytes(int n_assign, int d, int F, int cw);
-int decode_slice_width(int n_assign, int E, int d, int F, int bits);
+int decode_slice_width(int n_assign, int E, int F);
 double decode_active_experts(int n_assign, int E);
 int launch_decode_ffn(const DecodeArgs &p, int bits, bool bf, hipStream_t s);
 

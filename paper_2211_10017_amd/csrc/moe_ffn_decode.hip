@@ -20,8 +20,8 @@
 // row tiles.  Fewer registers beat longer rings (4-bit, FP16: 24 wavefronts per compute unit with two 1 KB blocks of fc1 and four of fc2
 // in flight 28.8 us, sixteen with six and eight 31.1), and two fc2 units at a time one (12 against 17 us for a block's 512 channels).
 //
-// The rows of an expert (at most sixteen per pass; more rows take further passes over the same
-// weights) are the A operand of v_mfma_f32_16x16x32_f16, fetched from the tokens in operand order; the weights go
+// The rows of an expert (at most sixteen per pass, thirty-two where experts are expected to have more than eight; more rows take
+// further passes over the same weights) are the A operand of v_mfma_f32_16x16x32_f16, fetched from the tokens in operand order; the weights go
 // through the magic-number conversion into the B operand.  Group scales multiply the fp32 sums of 64 K values of exact
 // codes.  bf16 rows are scaled per row and 64 K values by a power of two into the FP16 range (exact), and so is the slice of
 // h per row, after its rounding to bf16.
@@ -82,29 +82,33 @@ __device__ inline void swap_rows(uint32_t &a, uint32_t &b)
     b = r[1];
 }
 
-// 16 rows x 32 channels x 64 K values: one fragment block of 4-bit or two of 8-bit weights, a[] the two 32-deep row operands.
-template <int BITS>
-__device__ inline void dec_mac(const uint4 (&w)[BITS / 4], const uint4 (&a)[2], float4_t &lo, float4_t &hi)
+// RT x 16 rows x 32 channels x 64 K values: one fragment block of 4-bit or two of 8-bit weights, a[] the two 32-deep operands of
+// each sixteen rows.
+template <int BITS, int RT>
+__device__ inline void dec_mac(const uint4 (&w)[BITS / 4], const uint4 (&a)[RT][2], float4_t (&lo)[RT], float4_t (&hi)[RT])
 {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        const half8_t av = __builtin_bit_cast(half8_t, a[q]);
+        auto products = [&](const uint32_t (&bw)[4], float4_t (&acc)[RT]) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a[rt][q]), frag_from(bw), acc[rt], 0, 0, 0);
+        };
         uint32_t bw[4];
         if constexpr (BITS == 4) {
             uint32_t r0 = q ? w[0].z : w[0].x, r1 = q ? w[0].w : w[0].y;
             swap_rows(r0, r1);
             dequant4(r0, bw);
-            lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, frag_from(bw), lo, 0, 0, 0);
+            products(bw, lo);
             dequant4(r1, bw);
-            hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, frag_from(bw), hi, 0, 0, 0);
+            products(bw, hi);
         } else {
             uint32_t r0 = w[q].x, r1 = w[q].y, r2 = w[q].z, r3 = w[q].w;
             swap_rows(r0, r2);
             swap_rows(r1, r3);
             dequant8(r0, r1, bw);
-            lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, frag_from(bw), lo, 0, 0, 0);
+            products(bw, lo);
             dequant8(r2, r3, bw);
-            hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, frag_from(bw), hi, 0, 0, 0);
+            products(bw, hi);
         }
     }
 }
@@ -162,18 +166,20 @@ __device__ inline void dec_write_index(const DecodeArgs &p, int32_t *s_key, int 
 }
 
 // BITS: weight width.  GROUPED: group scales (groups of a multiple of 64 K values).  BF: bf16 rows.  CW: 64-channel parts of a slice.
-template <int BITS, bool GROUPED, bool BF, int CW>
-__global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF ? 6 : 4) void decode_ffn_kernel(DecodeArgs p)
+// RT: sixteens of rows per pass.
+template <int BITS, bool GROUPED, bool BF, int CW, int RT>
+__global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF && RT == 1 ? 6 : 4) void decode_ffn_kernel(DecodeArgs p)
 {
     constexpr int NW = BITS / 4;                        // fragment blocks of a slab per 64 K values (a "unit")
     constexpr int KP = kDecWaves / CW, CH = 64 * CW;    // parts of K in fc1; channels of the slice
-    constexpr int U1 = 1, U2 = 4;                       // units in flight per wavefront, fc1 / fc2
+    constexpr int U2 = RT > 1 && GROUPED ? 2 : 4;           // units of fc2 in flight per wavefront (and one of fc1)
+    constexpr int FIT = kDecFit * RT;
     constexpr int LDR = CH + 4, LDH = CH + 8;
     __shared__ __align__(16) float s_red[KP * kDecFit * LDR];
-    __shared__ __align__(16) uint16_t s_h[kDecFit * LDH];
+    __shared__ __align__(16) uint16_t s_h[FIT * LDH];
     __shared__ __align__(16) int32_t s_row[kDecMaxAssign];      // assignments of the block's expert
     __shared__ uint32_t s_used[kDecMaxExperts / 32];            // experts that have rows
-    __shared__ float s_pow[kDecFit];
+    __shared__ float s_pow[FIT];
     __shared__ int s_n;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -220,16 +226,14 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF ? 6 : 4) 
     const uint16_t *s2 = reinterpret_cast<const uint16_t *>(p.s2) + (size_t)e * (GROUPED ? F / p.g : 1) * d + slab0 * 32;
 
     auto group_of = [&](int u) { return p.group_inv ? (int)__umulhi((uint32_t)u, p.group_inv) : u; };      // unit -> group
-    uint4 W[U1][2][NW], A[U1][2], V[U2][NW];
-    uint16_t gs1[GROUPED ? U1 : 1], gs2[GROUPED ? U2 : 1];       // group scales: lane l brings channel l of the wavefront's 64, l % 32 of the slab's 32
-    auto load_w1 = [&](int slot, int u) {
+    uint4 W[2][NW], A[RT][2], V[U2][NW];
+    uint16_t gs1, gs2[GROUPED ? U2 : 1];        // group scales: lane l brings channel l of the wavefront's 64, l % 32 of the slab's 32
+    auto load_w1 = [&](int u) {
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int w = 0; w < NW; ++w) W[slot][s][w] = dec_load(w1 + ((size_t)s * nk + u) * NW * kFragBytes + w * kFragBytes, u < n1, lane_off);
-        if constexpr (GROUPED) {
-            gs1[slot] = __builtin_amdgcn_raw_buffer_load_b16(dec_rsrc(s1 + (size_t)group_of(u0 + u) * F + cg * 64, u < n1 ? 128 : 0), lane * 2, 0, 0);
-        }
+            for (int w = 0; w < NW; ++w) W[s][w] = dec_load(w1 + ((size_t)s * nk + u) * NW * kFragBytes + w * kFragBytes, u < n1, lane_off);
+        if constexpr (GROUPED) gs1 = __builtin_amdgcn_raw_buffer_load_b16(dec_rsrc(s1 + (size_t)group_of(u0 + u) * F + cg * 64, u < n1 ? 128 : 0), lane * 2, 0, 0);
     };
     auto load_w2 = [&](int slot, int j) {
         const int slab = j / CW, unit = j % CW;
@@ -240,8 +244,7 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF ? 6 : 4) 
         }
     };
     auto prime = [&]() {
-#pragma unroll
-        for (int i = 0; i < U1; ++i) load_w1(i, i);
+        load_w1(0);
 #pragma unroll
         for (int i = 0; i < U2; ++i) load_w2(i, i);
         __builtin_amdgcn_sched_barrier(0);
@@ -269,80 +272,92 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF ? 6 : 4) 
     const int lane16 = (lane & 15) * 4, lane_row = (lane >> 4) * 16;     // byte offsets of dec_lane
     // k octet this lane's quarter of the wavefront reads within a 32-deep step (see swap_rows)
     const int koct = ((lane >> 4) & 1) * 16 + (lane >> 5) * 8;
-    for (int z0 = 0; z0 < count; z0 += kDecFit) {       // usually a single pass
-        const int rows = min(kDecFit, count - z0);
-        // rows of x in operand order: only the lanes of live rows read (the others hold zeros)
-        const bool a_live = (lane & 15) < rows;
-        const int a_tok = s_row[z0 + min(lane & 15, rows - 1)] >> (p.gate_k - 1);       // one or two experts per token
-        const uint32_t a_off = a_live ? ((uint32_t)a_tok * d + koct) * 2u : 0x7fffff00u;    // (past the tokens: reads as zero)
-        auto load_a = [&](int slot, int u) {
+    for (int z0 = 0; z0 < count; z0 += FIT) {           // usually a single pass
+        const int rows = min(FIT, count - z0);
+        // rows of x in operand order: only the lanes of live rows read (the others are past the tokens, which reads as zero)
+        uint32_t a_off[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            const int m = 16 * rt + (lane & 15), tok = s_row[z0 + min(m, rows - 1)] >> (p.gate_k - 1);      // one or two experts per token
+            a_off[rt] = m < rows ? ((uint32_t)tok * d + koct) * 2u : 0x7fffff00u;
+        }
+        auto load_a = [&](int u) {
             const __amdgpu_buffer_rsrc_t r = dec_rsrc(p.x + (u0 + u) * 64, u < n1 ? x_bytes - (u0 + u) * 128 : 0);
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const dec_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, a_off + 64 * q, 0, 0);
-                A[slot][q] = make_uint4(v.x, v.y, v.z, v.w);
-            }
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const dec_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, a_off[rt] + 64 * q, 0, 0);
+                    A[rt][q] = make_uint4(v.x, v.y, v.z, v.w);
+                }
+        };
+        load_a(0);
+
+        // ---- fc1: the rows x 64 channels over the wavefront's part of K
+        float4_t acc[4][RT];
+        auto clear = [&](float4_t (&t)[RT]) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) t[rt] = float4_t{0.f, 0.f, 0.f, 0.f};
         };
 #pragma unroll
-        for (int i = 0; i < U1; ++i) load_a(i, i);
-
-        // ---- fc1: 16 rows x 64 channels over the wavefront's part of K
-        float4_t acc[4];
+        for (int t = 0; t < 4; ++t) clear(acc[t]);
+        for (int u = 0; u < n1; ++u) {
+            float up[RT];
+            if constexpr (BF) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t] = float4_t{0.f, 0.f, 0.f, 0.f};
-        for (int base = 0; base < n1; base += U1) {
+                for (int rt = 0; rt < RT; ++rt) {
+                    uint32_t amax = 0;
 #pragma unroll
-            for (int i = 0; i < U1; ++i) {
-                if (base + i < n1) {
-                    float up = 1.0f;
-                    if constexpr (BF) {
-                        uint32_t amax = 0;
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            amax = dec_max_bf16(dec_max_bf16(amax, A[i][q].x), A[i][q].y);
-                            amax = dec_max_bf16(dec_max_bf16(amax, A[i][q].z), A[i][q].w);
-                        }
-                        float down;
-                        dec_row_pow(dec_max_over_rows(amax), down, up);
-#pragma unroll
-                        for (int q = 0; q < 2; ++q)
-                            A[i][q] = make_uint4(dec_bf16_pair_to_f16(A[i][q].x, down), dec_bf16_pair_to_f16(A[i][q].y, down),
-                                                 dec_bf16_pair_to_f16(A[i][q].z, down), dec_bf16_pair_to_f16(A[i][q].w, down));
+                    for (int q = 0; q < 2; ++q) {
+                        amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].x), A[rt][q].y);
+                        amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].z), A[rt][q].w);
                     }
-                    if constexpr (GROUPED || BF) {      // the unit's sums, folded with its factors in fp32
-                        float4_t part[4];
+                    float down;
+                    dec_row_pow(dec_max_over_rows(amax), down, up[rt]);
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) part[t] = float4_t{0.f, 0.f, 0.f, 0.f};
-                        dec_mac<BITS>(W[i][0], A[i], part[0], part[1]);
-                        dec_mac<BITS>(W[i][1], A[i], part[2], part[3]);
-                        float pw[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) pw[r] = BF ? dec_lane(up, lane_row, r) : 1.0f;
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            const float sf = GROUPED ? dec_lane((float)__builtin_bit_cast(_Float16, gs1[i]), lane16, 16 * t) : 1.0f;
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) acc[t][r] = fmaf(part[t][r], sf * pw[r], acc[t][r]);
-                        }
-                    } else {
-                        dec_mac<BITS>(W[i][0], A[i], acc[0], acc[1]);
-                        dec_mac<BITS>(W[i][1], A[i], acc[2], acc[3]);
-                    }
+                    for (int q = 0; q < 2; ++q)
+                        A[rt][q] = make_uint4(dec_bf16_pair_to_f16(A[rt][q].x, down), dec_bf16_pair_to_f16(A[rt][q].y, down),
+                                              dec_bf16_pair_to_f16(A[rt][q].z, down), dec_bf16_pair_to_f16(A[rt][q].w, down));
                 }
-                load_w1(i, base + U1 + i);
-                load_a(i, base + U1 + i);
-                __builtin_amdgcn_sched_barrier(0);
             }
+            if constexpr (GROUPED || BF) {              // the unit's sums, folded with its factors in fp32
+#pragma unroll
+                for (int t = 0; t < 4; t += 2) {        // (one slab, then the other)
+                    float4_t part[2][RT];
+                    clear(part[0]), clear(part[1]);
+                    dec_mac<BITS, RT>(W[t / 2], A, part[0], part[1]);
+                    float sf[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) sf[i] = GROUPED ? dec_lane((float)__builtin_bit_cast(_Float16, gs1), lane16, 16 * (t + i)) : 1.0f;
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float pw = BF ? dec_lane(up[rt], lane_row, r) : 1.0f;
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) acc[t + i][rt][r] = fmaf(part[i][rt][r], sf[i] * pw, acc[t + i][rt][r]);
+                        }
+                    if (RT > 1) __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                dec_mac<BITS, RT>(W[0], A, acc[0], acc[1]);
+                dec_mac<BITS, RT>(W[1], A, acc[2], acc[3]);
+            }
+            load_w1(u + 1);
+            load_a(u + 1);
+            __builtin_amdgcn_sched_barrier(0);
         }
         MOE_DEC_STAMP(3);
         if constexpr (CW > 2) load_factors();
-        // ---- the parts of K meet: rows 4 (lane / 16) + r, channels 64 cg + 16 t + lane % 16
+        // ---- the parts of K meet, sixteen rows at a time: rows 16 rt + 4 (lane / 16) + r, channels 64 cg + 16 t + lane % 16
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int rt = 0; rt < RT; ++rt) {
+            if (rt) __syncthreads();                    // the sixteen rows before have been read
 #pragma unroll
-            for (int r = 0; r < 4; ++r) s_red[(kp * kDecFit + 4 * (lane >> 4) + r) * LDR + cg * 64 + 16 * t + (lane & 15)] = acc[t][r];
-        __syncthreads();
-        {
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s_red[(kp * kDecFit + 4 * (lane >> 4) + r) * LDR + cg * 64 + 16 * t + (lane & 15)] = acc[t][rt][r];
+            __syncthreads();
             float v[HC];
 #pragma unroll
             for (int i = 0; i < HC; ++i) v[i] = s_red[h_row * LDR + h_ch + i];
@@ -363,61 +378,73 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF ? 6 : 4) 
 #pragma unroll
                 for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_RELU);
             }
-#pragma unroll
-            for (int i = 0; i < HC; ++i) {
-                if constexpr (BF) {
-                    v[i] = __uint_as_float((uint32_t)to_bf16_rne(v[i]) << 16);
-                    amax = max(amax, (__float_as_uint(v[i]) >> 16) & 0x7fffu);
-                }
-            }
             if constexpr (BF) {
                 float down, up;
 #pragma unroll
+                for (int i = 0; i < HC; ++i) {
+                    v[i] = __uint_as_float((uint32_t)to_bf16_rne(v[i]) << 16);
+                    amax = max(amax, (__float_as_uint(v[i]) >> 16) & 0x7fffu);
+                }
+#pragma unroll
                 for (int off = 16; off > 0; off >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, off));
                 dec_row_pow(amax, down, up);
-                if ((tid & 31) == 0) s_pow[h_row] = up;
+                if ((tid & 31) == 0) s_pow[16 * rt + h_row] = up;
 #pragma unroll
                 for (int i = 0; i < HC; ++i) v[i] *= down;
             }
 #pragma unroll
             for (int i = 0; i < HC; i += 2) {
                 const half2_t hv = {(_Float16)v[i], (_Float16)v[i + 1]};
-                *reinterpret_cast<uint32_t *>(s_h + h_row * LDH + h_ch + i) = h2_bits(hv);
+                *reinterpret_cast<uint32_t *>(s_h + (16 * rt + h_row) * LDH + h_ch + i) = h2_bits(hv);
             }
         }
         __syncthreads();
 
         MOE_DEC_STAMP(4);
-        // ---- fc2 on the slice: 16 rows x 32 output channels per slab, K = the slice's channels
+        // ---- fc2 on the slice: the rows x 32 output channels per slab, K = the slice's channels
         const uint16_t *h_ptr = s_h + (lane & 15) * LDH + koct;
         float *const part_c = p.partial + (size_t)c * p.n_assign * d + slab0 * 32;
-        int row_off[4];
-        float pw[4];
+        int row_off[RT][4];
+        float pw[RT][4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int m = 4 * (lane >> 4) + r;
-            row_off[r] = m < rows ? s_row[z0 + m] * d + (lane & 15) : -1;
-            pw[r] = BF ? s_pow[m] : 1.0f;
-        }
-        float4_t y0 = {0.f, 0.f, 0.f, 0.f}, y1 = {0.f, 0.f, 0.f, 0.f};
-        auto unit_mac = [&](int i, const uint4 (&a)[2], float4_t &lo, float4_t &hi) {
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = 16 * rt + 4 * (lane >> 4) + r;
+                row_off[rt][r] = m < rows ? s_row[z0 + m] * d + (lane & 15) : -1;
+                pw[rt][r] = BF ? s_pow[m] : 1.0f;
+            }
+        float4_t y0[RT], y1[RT];
+        clear(y0), clear(y1);
+        auto read_h = [&](int unit, uint4 (&a)[RT][2]) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) a[rt][q] = *reinterpret_cast<const uint4 *>(h_ptr + 16 * rt * LDH + unit * 64 + 32 * q);
+        };
+        auto unit_mac = [&](int i, const uint4 (&a)[RT][2], float4_t (&lo)[RT], float4_t (&hi)[RT]) {
             if constexpr (GROUPED) {
-                float4_t p0 = {0.f, 0.f, 0.f, 0.f}, p1 = {0.f, 0.f, 0.f, 0.f};
-                dec_mac<BITS>(V[i], a, p0, p1);
+                float4_t p0[RT], p1[RT];
+                clear(p0), clear(p1);
+                dec_mac<BITS, RT>(V[i], a, p0, p1);
                 const float sl = (float)__builtin_bit_cast(_Float16, gs2[i]), f0 = dec_lane(sl, lane16, 0), f1 = dec_lane(sl, lane16, 16);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) lo[r] = fmaf(p0[r], f0, lo[r]), hi[r] = fmaf(p1[r], f1, hi[r]);
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) lo[rt][r] = fmaf(p0[rt][r], f0, lo[rt][r]), hi[rt][r] = fmaf(p1[rt][r], f1, hi[rt][r]);
             } else {
-                dec_mac<BITS>(V[i], a, lo, hi);
+                dec_mac<BITS, RT>(V[i], a, lo, hi);
             }
         };
-        auto store = [&](int n, const float4_t &lo, const float4_t &hi) {       // this slice's part of y, channels n .. n + 31
+        auto store = [&](int n, const float4_t (&lo)[RT], const float4_t (&hi)[RT]) {       // this slice's part of y, channels n .. n + 31
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (row_off[r] >= 0) {
-                    part_c[row_off[r] + n] = BF ? lo[r] * pw[r] : lo[r];
-                    part_c[row_off[r] + n + 16] = BF ? hi[r] * pw[r] : hi[r];
-                }
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (row_off[rt][r] >= 0) {
+                        part_c[row_off[rt][r] + n] = BF ? lo[rt][r] * pw[rt][r] : lo[rt][r];
+                        part_c[row_off[rt][r] + n + 16] = BF ? hi[rt][r] * pw[rt][r] : hi[rt][r];
+                    }
         };
         // two units at a time, whose chains of unpacking and products the wavefront interleaves: two slabs (slices of 64 channels)
         // or two units of a slab
@@ -426,21 +453,23 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF ? 6 : 4) 
             for (int i = 0; i < U2; i += 2) {
                 const int j = base + i, unit = CW == 1 ? 0 : U2 % CW == 0 ? i % CW : j % CW;
                 if (j < n2) {
-                    const uint4 a0[2] = {*reinterpret_cast<const uint4 *>(h_ptr + unit * 64), *reinterpret_cast<const uint4 *>(h_ptr + unit * 64 + 32)};
+                    uint4 a0[RT][2];
+                    read_h(unit, a0);
                     if constexpr (CW == 1) {
-                        float4_t z0v = {0.f, 0.f, 0.f, 0.f}, z1v = {0.f, 0.f, 0.f, 0.f};
-                        y0 = y1 = z0v;
+                        float4_t z0v[RT], z1v[RT];
+                        clear(y0), clear(y1), clear(z0v), clear(z1v);
                         unit_mac(i, a0, y0, y1);
                         unit_mac(i + 1, a0, z0v, z1v);
                         store(j * 32, y0, y1);
                         if (j + 1 < n2) store(j * 32 + 32, z0v, z1v);
                     } else {
-                        const uint4 a1[2] = {*reinterpret_cast<const uint4 *>(h_ptr + unit * 64 + 64), *reinterpret_cast<const uint4 *>(h_ptr + unit * 64 + 96)};
+                        uint4 a1[RT][2];
+                        read_h(unit + 1, a1);
                         unit_mac(i, a0, y0, y1);
                         unit_mac(i + 1, a1, y0, y1);
                         if (unit == CW - 2) {
                             store(j / CW * 32, y0, y1);
-                            y0 = y1 = float4_t{0.f, 0.f, 0.f, 0.f};
+                            clear(y0), clear(y1);
                         }
                     }
                 }
@@ -451,7 +480,7 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF ? 6 : 4) 
         }
         MOE_DEC_STAMP(5);
         // (a further pass: s_h and s_pow are written again only behind the barrier that follows its fc1)
-        if (z0 + kDecFit < count) {
+        if (z0 + FIT < count) {
             __syncthreads();
             prime();
         }
@@ -536,13 +565,21 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs p)
 
 // ---- host side -----------------------------------------------------------------------------------
 
+template <int BITS, bool GROUPED, bool BF, int RT>
+static void launch_decode_rows(const DecodeArgs &p, dim3 grid, hipStream_t s)
+{
+    if (p.cw == 1) hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 1, RT>), grid, dim3(kDecThreads), 0, s, p);
+    else if (p.cw == 2) hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 2, RT>), grid, dim3(kDecThreads), 0, s, p);
+    else if (p.cw == 4) hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 4, RT>), grid, dim3(kDecThreads), 0, s, p);
+    else hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 8, RT>), grid, dim3(kDecThreads), 0, s, p);
+}
+
 template <int BITS, bool GROUPED, bool BF>
 static void launch_decode(const DecodeArgs &p, dim3 grid, hipStream_t s)
 {
-    if (p.cw == 1) hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 1>), grid, dim3(kDecThreads), 0, s, p);
-    else if (p.cw == 2) hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 2>), grid, dim3(kDecThreads), 0, s, p);
-    else if (p.cw == 4) hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 4>), grid, dim3(kDecThreads), 0, s, p);
-    else hipLaunchKernelGGL((decode_ffn_kernel<BITS, GROUPED, BF, 8>), grid, dim3(kDecThreads), 0, s, p);
+    if constexpr (BITS == 4 && !BF)
+        if (p.row_tiles > 1) return launch_decode_rows<BITS, GROUPED, BF, 2>(p, grid, s);
+    launch_decode_rows<BITS, GROUPED, BF, 1>(p, grid, s);
 }
 
 template <int BITS>
@@ -571,9 +608,8 @@ double decode_active_experts(int n_assign, int E)
 // of 64 / 128 / 256 / 512: 1 token, two of 32 experts of 1024 x 4096, 4-bit 17.6 / 20.6 / 24.6 / 33; 16 tokens 36 / 32 / 32 / 37.5; 64 tokens 54 /
 // 48 / 40 / 42; 80 tokens on 16 experts of 4096 x 16384, group scales 357 / 281 / 264 / 227.  Over 390 drawn sizes this rule is 2 %
 // slower than the best width of each, at most 17 %.)
-int decode_slice_width(int n_assign, int E, int d, int F, int bits)
+int decode_slice_width(int n_assign, int E, int F)
 {
-    (void)d, (void)bits;
     const double blocks64 = decode_active_experts(n_assign, E) * (F / 64);
     int w = 1;
     for (int c = 2; c <= 8; c *= 2)
@@ -590,6 +626,9 @@ int launch_decode_ffn(const DecodeArgs &q, int bits, bool bf, hipStream_t s)
 {
     DecodeArgs p = q;
     const uint32_t units = p.g ? p.g / 64 : 1;
+    // two sixteens of rows per pass where experts are expected to have more than eight, FP16 rows on 4-bit codes: with fewer the second
+    // sixteen's products are idle, with wider codes or rows it takes the registers that loads in flight need
+    p.row_tiles = p.n_assign > 8 * p.E && bits == 4 && !bf ? 2 : 1;
     p.group_inv = units > 1 ? (uint32_t)(((1ull << 32) + units - 1) / units) : 0;
     const int S = p.F / (64 * p.cw);
     const dim3 grid(1 + (unsigned)(p.E < p.n_assign ? p.E : p.n_assign) * S);      // (the first block writes the index arrays)

@@ -26,8 +26,21 @@ def _routing(loads, T, k, E, rng):
 @pytest.mark.parametrize("d,F", [(64, 64), (64, 320), (192, 1152), (768, 512), (1088, 1024), (2176, 640)])
 @pytest.mark.parametrize("act,bits,g", [("f16", 4, 0), ("f16", 8, 0), ("f16", 4, 64), ("f16", 8, 64), ("bf16", 4, 0), ("bf16", 8, 0), ("bf16", 4, 64),
                                         ("bf16", 8, 64)])
-@pytest.mark.parametrize("T,k,E,load", [(1, 1, 3, -1), (5, 2, 70, -1), (40, 2, 6, 33)])        # 33 rows: three passes of one expert
+@pytest.mark.parametrize("T,k,E,load", [(1, 1, 3, -1), (5, 2, 70, -1), (17, 2, 6, 17), (40, 2, 6, 33)])      # 17, 33 rows: two passes of sixteen, of 32
 def test_sliced_ffn_matches_oracle(d, F, act, bits, g, T, k, E, load):
+    _check(d, F, act, bits, g, T, k, E, load)
+
+
+# slices of 128, 256 and 512 channels, one and two sixteens of rows per pass
+@pytest.mark.parametrize("d,F", [(192, 1024), (64, 2048), (128, 4096)])
+@pytest.mark.parametrize("act,bits,g", [("f16", 4, 0), ("f16", 8, 0), ("f16", 4, 64), ("bf16", 8, 0), ("bf16", 4, 64)])
+@pytest.mark.parametrize("T", [60, 150])
+def test_wide_slices_match_oracle(d, F, act, bits, g, T):
+    assert B.moe_grouped_ffn_wq_sliced_workspace_bytes(T, 2, 34, d, F, bits, g, TORCH_DT[act]) == T * 2 * d * 4 * 8       # eight slices
+    _check(d, F, act, bits, g, T, 2, 34, 20 if T == 60 else 45)
+
+
+def _check(d, F, act, bits, g, T, k, E, load):
     print(f"sliced T={T} k={k} E={E} d={d} F={F} {act} bits={bits} g={g}", flush=True)
     rng = np.random.default_rng(d + F + bits + T)
     x = to_dev(rng.standard_normal((T, d)).astype(np.float32), TORCH_DT[act])
