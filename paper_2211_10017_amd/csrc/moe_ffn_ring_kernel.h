@@ -7,7 +7,7 @@
 // registers can be one or two steps ahead at most (moe_ffn_tiled_kernel.h); loads into LDS need no registers,
 // are counted by hand, and NST - 1 stages of them stay in flight: three with 16-row blocks (two with 8-bit weights and group scales), two
 // with taller ones, one with 64-row blocks of 8-bit weights, whose stage is 32 KB of the 80 KB that two blocks per compute unit
-// leave each.  The K range is split over the two pairs of wavefronts of the block, whose partial tiles meet in LDS at the end, added
+// leave each (three or four where a block has the compute unit to itself, see ring_long).  The K range is split over the two pairs of wavefronts of the block, whose partial tiles meet in LDS at the end, added
 // in the order of K: twice the blocks, each with half the chain of K steps.
 //
 // Block: 2 x 2 wavefronts; wavefront (wc, kp) computes BM rows x 64 channels over the kp-th half of K.  A stage
@@ -43,20 +43,24 @@ struct RingShape {
     // LDS of a compute unit (160 KB): three blocks where a block's share still holds three stages, else two
     static constexpr int kLimit = (BM > 32 || BITS == 8 ? 80 : 53) * 1024;
     static constexpr int NST = kLimit / kStage;                     // stages
-    static constexpr int kLds = NST * kStage > kEnd ? NST * kStage : kEnd;
-    static_assert(NST >= 2 && NST <= 4 && kLds <= kLimit, "a stage in use and one to three in flight (the chain of waits)");
+    static constexpr int kLds(int stages) { return stages * kStage > kEnd ? stages * kStage : kEnd; }
+    static_assert(NST >= 2 && NST <= 4 && kLds(NST) <= kLimit, "a stage in use and one to three in flight (the chain of waits)");
+    // 64-row blocks of 8-bit weights, with one stage in flight, may take all of a compute unit's LDS instead (p.ring_stages)
+    static constexpr bool kLong = BITS == 8 && BM > 32;
+    static constexpr int kMost = kLong ? 160 * 1024 / kStage : NST;
+    static_assert(!kLong || (NST == 2 && kMost >= 4 && kMost <= 5 && kLds(kMost) <= 160 * 1024), "up to four in flight (the chain of waits)");
 };
 
 template <int BITS, int SMODE, int BM>
 __global__ __launch_bounds__(256, 2) void grouped_gemm_ring_kernel(GemmArgs p)
 {
     using S = RingShape<BITS, SMODE, BM>;
-    constexpr int TM = S::TM, NW = S::NW, NST = S::NST, WC = S::WC, WK = S::WK;
+    constexpr int TM = S::TM, NW = S::NW, WC = S::WC, WK = S::WK;
     constexpr bool GROUPED = S::GROUPED, ACC = SMODE == SCALE_GROUP_ACC;
-    constexpr int D = NST - 1;                          // stages in flight
+    const int NST = S::kLong ? p.ring_stages : S::NST, D = NST - 1;     // stages, and those in flight
     constexpr int NA = BM / 8 > WC ? BM / 8 / WC : 1;   // row loads per wavefront and stage (8 rows each)
     constexpr int L = NA + 2 * NW + (GROUPED ? 1 : 0);  // loads per wavefront and stage
-    static_assert((D - 1) * L < 64, "the load counter has six bits");
+    static_assert((S::kMost - 2) * L < 64, "the load counter has six bits");
     extern __shared__ __align__(16) uint8_t lds[];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -196,15 +200,23 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_ring_kernel(GemmArgs p)
     // in order), and the barrier makes everyone's share visible and tells that everyone has left the
     // stage before it, which is then refilled.
 #pragma unroll
-    for (int s = 0; s < D; ++s)
-        if (s < per) issue(s, s);
+    for (int s = 0; s < S::kMost - 1; ++s)
+        if (s < D && s < per) issue(s, s);
     auto k_loop = [&](auto live_c) {
         int slot = 0;
         for (int s = 0; s < per; ++s) {
             const int rem = min(per - 1 - s, D - 1);
-            if (rem == D - 1) wait_loads<(D - 1) * L>();
-            else if (D > 2 && rem == 1) wait_loads<(D > 2) * L>();
-            else wait_loads<0>();
+            if constexpr (S::kLong) {
+                if (rem == 0) wait_loads<0>();
+                else if (rem == 3) wait_loads<3 * L>();
+                else if (rem == 2) wait_loads<2 * L>();
+                else wait_loads<L>();
+            } else {
+                constexpr int D = S::NST - 1;
+                if (rem == D - 1) wait_loads<(D - 1) * L>();
+                else if (D > 2 && rem == 1) wait_loads<(D > 2) * L>();
+                else wait_loads<0>();
+            }
             __syncthreads();
             if (s + D < per) issue(s + D, slot == 0 ? NST - 1 : slot - 1);
             if (s < mine) compute(slot, s + 1 == mine || (first + s + 1) * 64 % p.g == 0, live_c);
@@ -256,8 +268,10 @@ static void launch_ring_shape(const GemmArgs &p, dim3 grid, hipStream_t s)
 {
     using S = RingShape<BITS, SMODE, BM>;
     static std::atomic<uint64_t> raised;
-    raise_lds_limit(reinterpret_cast<const void *>(&grouped_gemm_ring_kernel<BITS, SMODE, BM>), S::kLds, raised);
-    hipLaunchKernelGGL((grouped_gemm_ring_kernel<BITS, SMODE, BM>), grid, dim3(256), S::kLds, s, p);
+    raise_lds_limit(reinterpret_cast<const void *>(&grouped_gemm_ring_kernel<BITS, SMODE, BM>), S::kLds(S::kMost), raised);
+    GemmArgs q = p;
+    q.ring_stages = p.ring_long ? S::kMost : S::NST;
+    hipLaunchKernelGGL((grouped_gemm_ring_kernel<BITS, SMODE, BM>), grid, dim3(256), S::kLds(q.ring_stages), s, q);
 }
 
 template <int BITS, int SMODE>

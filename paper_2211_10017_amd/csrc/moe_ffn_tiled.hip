@@ -25,6 +25,17 @@ static int ring_rows(const GemmArgs &p, int bits, int mean)
     return ((long)p.R / 64 + experts / 2) * ncol <= 224 ? 64 : 0;
 }
 
+// Whether 64-row blocks of 8-bit weights take the whole LDS of a compute unit for their ring: typical row counts make no more blocks
+// than compute units, and the weights are many enough to come from memory, whose latency one stage in flight does not cover (25
+// layers of 18 MB and more 1.00 to 1.10 times as fast a step: 1000 FP16 tokens on 16 experts of 1088 x 4352 76.2 -> 69.5 us, 100 on one of
+// 4096 x 16384 161 -> 150, 997 bf16 tokens, two of 16 of 768 x 3072, fc2 31.9 -> 27.3; below, 0.92 to 1.0 times: 300 tokens, two of 8 of
+// 512 x 2048 36.1 -> 38.4).
+static bool ring_long(const GemmArgs &p, int bm)
+{
+    const long tiles = ((long)p.R / bm + (p.E < p.R ? p.E : p.R) / 2) * ((p.N + 127) / 128);
+    return tiles <= 240 && (long)p.E * p.K * p.N >= 18000000l;
+}
+
 int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
 {
     // row-tile height from the mean rows per expert (the offsets themselves stay on the device)
@@ -35,7 +46,9 @@ int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
         const long slots = (long)p.R / bm + (p.E < p.R ? p.E : p.R);
         const long wgs = (slots * ((p.N + 127) / 128) + kXcds - 1) / kXcds * kXcds;      // upper bound of the work items, whole rounds of XCDs
         if (wgs > 0x7fffffffL) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq: %ld workgroups exceed one launch", wgs);
-        (bits == 4 ? launch_ring_4 : launch_ring_8)(p, smode, bm, dim3((unsigned)wgs), s);
+        GemmArgs q = p;
+        q.ring_long = ring_long(p, bm);
+        (bits == 4 ? launch_ring_4 : launch_ring_8)(q, smode, bm, dim3((unsigned)wgs), s);
         return check_launch("moe_grouped_ffn_wq (gemm)");
     }
     // 64-row tiles also for taller experts where a third block per CU pays more than halving the

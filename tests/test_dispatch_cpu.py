@@ -142,3 +142,12 @@ def test_the_oracle_comparisons_reach_every_kernel():
     ring = {f"grouped_gemm_ring_kernel<{b}, {m}, {bm}>" for b, m in [(4, 0), (8, 0), (4, 1), (8, 1), (8, 3), (4, 3)] for bm in (16, 32, 64)}
     stream = {"stream_gemm_kernel<4>", "stream_gemm_kernel<8>"} | {f"stream_unrolled_kernel<{b}, {kb}, {t}, {s}" for b in (4, 8) for kb, t, s in [(16, 1, 1), (32, 1, 1), (48, 1, 1), (64, 2, 4)]}
     assert fed | ring | stream <= ran, (fed | ring | stream) - ran
+
+
+def test_long_rings_where_a_64_row_tile_has_its_compute_unit_to_itself():
+    """8-bit weights of 18 MB and more and up to 240 tiles, as typical row counts make them."""
+    cases = [((2000, 16, 3072, 768, 8), True), ((2000, 16, 3072, 768, 8, 128), True), ((600, 8, 768, 3072, 8, 128), False), ((600, 8, 512, 2048, 8, 64), False),
+             ((2000, 16, 3072, 768, 4), False)]
+    for (sizes, want), call in zip(cases, L.record([L.ffn(*c) for c, _ in cases])):
+        ring = [p for p in call.launches if p.kernel.startswith("grouped_gemm_ring") and p.kernel.endswith("64>")]
+        assert ring and (ring[0].shared > 80 * 1024) is want, (sizes, call.launches)

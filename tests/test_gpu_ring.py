@@ -42,6 +42,14 @@ def test_ring_gemm_matches_oracle(rows, d, F, act, bits, g):
     assert max_abs <= MAX_ABS_TOL and rel <= REL_L2_TOL
 
 
+# 64-row tiles of 18 MB of 8-bit weights, one per compute unit at most: the longest ring, over odd and even numbers of K steps
+@pytest.mark.parametrize("rows,d,F", [([70, 33, 64, 129, 5, 0, 96, 40], 1216, 1984), ([50] * 32, 320, 1792)])
+@pytest.mark.parametrize("act,g", [("f16", 64), ("bf16", 64), ("bf16", 0)])
+def test_long_rings_match_oracle_and_the_build_that_waits_for_all_loads(rows, d, F, act, g):
+    test_ring_gemm_matches_oracle(rows, d, F, act, 8, g)
+    test_counted_waits_equal_waiting_for_all_loads(rows, d, F, 8, g, act)
+
+
 RING = [
     ([3, 9, 0, 17, 1], 1088, 704, 4, 0, "f16"), ([3, 9, 0, 17, 1], 1152, 1088, 8, 0, "f16"),            # ring, 16-row blocks
     ([3, 9, 0, 17, 1], 1152, 640, 4, 128, "f16"), ([3, 9, 0, 17, 1], 1152, 640, 4, 128, "bf16"),
