@@ -283,10 +283,11 @@ int moe_grouped_ffn_wq_gated(const void *x, int act_dtype, const int32_t *expert
 /*
  * moe_permute, moe_grouped_ffn_wq and moe_combine in one call of two launches, for few rows per expert: fp16 or bf16
  * rows, 4- or 8-bit weights, channel or group scales, T * k <= 512 assignments, k = 1 or 2, E <= 4096, d and F multiples of 64.
- * The first launch cuts the work along d_ff: a block per (expert with rows, slice of 64 to 512 channels) streams its part of W1
- * and W2 once, h staying on chip, and leaves fp32 partial sums of y in the workspace; the second adds the slices in a
- * fixed order, applies channel scale, bias and gate scale and writes out.  No atomics on memory; rows past sixteen per expert
- * read the expert's weights again.
+ * The first launch cuts the work along d_ff: a block per (expert, up to 16 or 32 of its rows, slice of 64 to 512 channels) streams its part of W1
+ * and W2, h staying on chip, and leaves fp32 partial sums of y in the workspace; the second adds the slices in a
+ * fixed order, applies channel scale, bias and gate scale and writes out.  No atomics on memory.  An expert with more than
+ * sixteen rows (thirty-two for fp16 rows on 4-bit weights with more than eight assignments per expert) has further blocks, which
+ * read its weights again.
  *   x [T,d] (un-permuted); expert_idx, expert_scale [T*k] from moe_gate_topk (E = pruned row, which adds nothing);
  *   out [T,d] in out_dtype; perm_src, inv_perm, expert_offsets as moe_permute writes them.
  *   Workspace of moe_grouped_ffn_wq_sliced_workspace_bytes (0 when a call with these sizes is not taken; it then

@@ -3,11 +3,11 @@
 // the gate's output, and fc1, the activation and fc2 run in one grid.
 //
 // Such a batch (the decoder-like case of Table 1: a few rows per expert) is bound by pulling every
-// active expert's packed weights through the chip once.  The work is cut along d_ff: a work item is
-// (expert that has rows, slice of 64 CW channels of d_ff), one block of eight wavefronts, and the grid holds one
-// block per item, dealt out by the hardware as blocks end.  The block computes its slice of h = act(x W1 + b1) - a wavefront
-// 64 channels over a CW-th part of an eighth of K, the parts meet in LDS -, keeps it in LDS as fp16 and multiplies it
-// at once with the matching rows of W2 (a wavefront an eighth of the output channels): h never goes to memory.
+// active expert's packed weights through the chip once.  The work is cut along d_ff: a work item is (expert that has rows,
+// sixteen or thirty-two of its rows, slice of 64 CW channels of d_ff), one block of eight wavefronts, and the grid holds a
+// block per item for any routing, dealt out by the hardware as blocks end (the few without an item find that out and end).  The block
+// computes its slice of h = act(x W1 + b1) - a wavefront 64 channels over a CW-th part of an eighth of K, the parts meet in LDS -, keeps it in LDS
+// as fp16 and multiplies it at once with the matching rows of W2 (a wavefront an eighth of the output channels): h never goes to memory.
 // What is left over is a partial sum of y per slice, stored as fp32 rows; decode_reduce_kernel then adds the
 // slices in a fixed order, applies W2's channel scale, the bias and the gate scale, and sums a token's experts in slot
 // order into the layer output (no atomics, nothing to clear, nothing to wait for inside a launch).
@@ -20,9 +20,12 @@
 // row tiles.  Fewer registers beat longer rings (4-bit, FP16: 24 wavefronts per compute unit with two 1 KB blocks of fc1 and four of fc2
 // in flight 28.8 us, sixteen with six and eight 31.1), and two fc2 units at a time one (12 against 17 us for a block's 512 channels).
 //
-// The rows of an expert (at most sixteen per pass, thirty-two where experts are expected to have more than eight; more rows take
-// further passes over the same weights) are the A operand of v_mfma_f32_16x16x32_f16, fetched from the tokens in operand order; the weights go
-// through the magic-number conversion into the B operand.  Group scales multiply the fp32 sums of 64 K values of exact
+// The rows of an item (sixteen, thirty-two where experts are expected to have more than eight) are the A operand of
+// v_mfma_f32_16x16x32_f16, fetched from the tokens in operand order; an expert with more rows has several items, whose blocks read its weights
+// at about the same time.  (As passes of one block they left most of a crowded batch's chip idle: 64 tokens on two of 64 experts of 4096 x 16384,
+// group scales, 383 -> 133 us a step, 143 in row tiles; on two of 32 of 1024 x 4096, bf16, 78 -> 29 and 44; 192 on two 190 -> 43 and 40, on
+// four of 64 of 4096 x 16384, 64 tokens, 298 -> 197 and 184.  Even routing gains what a kernel without the loop has in registers: 0 to 3 %.)
+// The weights go through the magic-number conversion into the B operand.  Group scales multiply the fp32 sums of 64 K values of exact
 // codes.  bf16 rows are scaled per row and 64 K values by a power of two into the FP16 range (exact), and so is the slice of
 // h per row, after its rounding to bf16.
 #include <math.h>
@@ -178,9 +181,10 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF && RT == 
     __shared__ __align__(16) float s_red[KP * kDecFit * LDR];
     __shared__ __align__(16) uint16_t s_h[FIT * LDH];
     __shared__ __align__(16) int32_t s_row[kDecMaxAssign];      // assignments of the block's expert
-    __shared__ uint32_t s_used[kDecMaxExperts / 32];            // experts that have rows
+    __shared__ int s_wave[kDecWaves];                           // rows of the expert among each wavefront's assignments
     __shared__ float s_pow[FIT];
-    __shared__ int s_n;
+    int *const s_cnt = reinterpret_cast<int *>(s_red);          // rows of every expert, until fc1's sums need the place
+    static_assert(sizeof(s_red) >= kDecMaxExperts * sizeof(int), "the experts' counters fit");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -192,24 +196,36 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF && RT == 
         return;
     }
     const int c = (int)(blockIdx.x - 1) % S;
-    // ---- the block's expert: the (blockIdx - 1) / S -th one that has rows
-    if (tid < kDecMaxExperts / 32) s_used[tid] = 0;
-    if (tid == 0) s_n = 0;
+    // ---- the block's item: the (blockIdx - 1) / S -th (expert that has rows, FIT of its rows), experts in ascending order.
+    // A lane sums the items of `span` neighbouring experts; more than 64 experts: the lanes then look into the span that was hit.
+    const int span = (E + 63) / 64;
+    for (int i = tid; i < 64 * span; i += kDecThreads) s_cnt[i] = 0;
     __syncthreads();
-    if ((uint32_t)v_exp < (uint32_t)E) atomicOr(&s_used[v_exp >> 5], 1u << (v_exp & 31));
+    if ((uint32_t)v_exp < (uint32_t)E) atomicAdd(&s_cnt[v_exp], 1);
     __syncthreads();
-    int e;
+    int e, count, z0;
     {
-        const uint32_t lo = s_used[2 * lane], hi = s_used[2 * lane + 1];
-        const int cnt = __popc(lo) + __popc(hi), incl = wave_inclusive_sum(cnt);
-        int rank = (int)(blockIdx.x - 1) / S;
-        const uint64_t hit = __ballot(incl > rank);
-        if (!hit) return;                               // fewer experts have rows than there are blocks for
-        const int src = __ffsll((unsigned long long)hit) - 1;
-        rank -= __shfl(incl - cnt, src);
-        uint64_t bits = (uint64_t)(uint32_t)__shfl((int)hi, src) << 32 | (uint32_t)__shfl((int)lo, src);
-        for (; rank > 0; --rank) bits &= bits - 1;
-        e = __builtin_amdgcn_readfirstlane(64 * src + __ffsll((unsigned long long)bits) - 1);
+        int item = (int)(blockIdx.x - 1) / S, first = 0;
+        auto find = [&](int cnt) {                      // the lane that holds the item; `item` becomes its number there
+            const int incl = wave_inclusive_sum(cnt);
+            const uint64_t hit = __ballot(incl > item);
+            if (!hit) return -1;
+            const int src = __ffsll((unsigned long long)hit) - 1;
+            item -= __shfl(incl - cnt, src);
+            return src;
+        };
+        auto groups = [&](int i) { return (s_cnt[i] + FIT - 1) / FIT; };
+        int cnt = 0;
+        for (int i = 0; i < span; ++i) cnt += groups(lane * span + i);
+        int src = find(cnt);
+        if (src < 0) return;                            // fewer items than there are blocks for
+        if (span > 1) {
+            first = src * span;
+            src = find(lane < span ? groups(first + lane) : 0);
+        }
+        e = __builtin_amdgcn_readfirstlane(first + src);
+        z0 = __builtin_amdgcn_readfirstlane(item) * FIT;
+        count = __builtin_amdgcn_readfirstlane(s_cnt[e]);
     }
 
     MOE_DEC_STAMP(1);
@@ -243,16 +259,21 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF && RT == 
             gs2[slot] = __builtin_amdgcn_raw_buffer_load_b16(dec_rsrc(s2 + (size_t)group_of(c * CW + unit) * d + slab * 32, j < n2 ? 64 : 0), (lane & 31) * 2, 0, 0);
         }
     };
-    auto prime = [&]() {
-        load_w1(0);
+    // (the weights depend on the expert alone: the rows are found under their flight)
+    load_w1(0);
 #pragma unroll
-        for (int i = 0; i < U2; ++i) load_w2(i, i);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    prime();                                            // (the weights depend on the expert alone: the rows are found under their flight)
-    // ---- the expert's rows
+    for (int i = 0; i < U2; ++i) load_w2(i, i);
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- the item's rows, in the order of the assignments: blocks of other slices and of the expert's other items share them out alike
     const bool mine = v_exp == e;
-    if (mine) s_row[atomicAdd(&s_n, 1)] = tid;          // in any order: the rows of a tile do not see each other
+    const uint64_t wave_rows = __ballot(mine);
+    if (lane == 0) s_wave[wave] = __popcll(wave_rows);
+    __syncthreads();
+    if (mine) {
+        int r = __popcll(wave_rows & ((1ull << lane) - 1)) - z0;
+        for (int w = 0; w < wave; ++w) r += s_wave[w];
+        if ((uint32_t)r < (uint32_t)FIT) s_row[r] = tid;
+    }
     // channel factors of the thread's part of h: row tid / 32, 2 CW channels
     constexpr int HC = 2 * CW;
     const int h_row = tid >> 5, h_ch = (tid & 31) * HC;
@@ -266,225 +287,217 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF && RT == 
     };
     if constexpr (CW <= 2) load_factors();              // (wider slices have no registers to carry them through fc1)
     __syncthreads();
-    const int count = s_n;
+    const int rows = min(FIT, count - z0);
     MOE_DEC_STAMP(2);
     const uint32_t x_bytes = (uint32_t)(p.n_assign >> (p.gate_k - 1)) * d * 2u;
     const int lane16 = (lane & 15) * 4, lane_row = (lane >> 4) * 16;     // byte offsets of dec_lane
     // k octet this lane's quarter of the wavefront reads within a 32-deep step (see swap_rows)
     const int koct = ((lane >> 4) & 1) * 16 + (lane >> 5) * 8;
-    for (int z0 = 0; z0 < count; z0 += FIT) {           // usually a single pass
-        const int rows = min(FIT, count - z0);
-        // rows of x in operand order: only the lanes of live rows read (the others are past the tokens, which reads as zero)
-        uint32_t a_off[RT];
+    // rows of x in operand order: only the lanes of live rows read (the others are past the tokens, which reads as zero)
+    uint32_t a_off[RT];
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const int m = 16 * rt + (lane & 15), tok = s_row[z0 + min(m, rows - 1)] >> (p.gate_k - 1);      // one or two experts per token
-            a_off[rt] = m < rows ? ((uint32_t)tok * d + koct) * 2u : 0x7fffff00u;
-        }
-        auto load_a = [&](int u) {
-            const __amdgpu_buffer_rsrc_t r = dec_rsrc(p.x + (u0 + u) * 64, u < n1 ? x_bytes - (u0 + u) * 128 : 0);
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const dec_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, a_off[rt] + 64 * q, 0, 0);
-                    A[rt][q] = make_uint4(v.x, v.y, v.z, v.w);
-                }
-        };
-        load_a(0);
-
-        // ---- fc1: the rows x 64 channels over the wavefront's part of K
-        float4_t acc[4][RT];
-        auto clear = [&](float4_t (&t)[RT]) {
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) t[rt] = float4_t{0.f, 0.f, 0.f, 0.f};
-        };
-#pragma unroll
-        for (int t = 0; t < 4; ++t) clear(acc[t]);
-        for (int u = 0; u < n1; ++u) {
-            float up[RT];
-            if constexpr (BF) {
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) {
-                    uint32_t amax = 0;
-#pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].x), A[rt][q].y);
-                        amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].z), A[rt][q].w);
-                    }
-                    float down;
-                    dec_row_pow(dec_max_over_rows(amax), down, up[rt]);
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        A[rt][q] = make_uint4(dec_bf16_pair_to_f16(A[rt][q].x, down), dec_bf16_pair_to_f16(A[rt][q].y, down),
-                                              dec_bf16_pair_to_f16(A[rt][q].z, down), dec_bf16_pair_to_f16(A[rt][q].w, down));
-                }
-            }
-            if constexpr (GROUPED || BF) {              // the unit's sums, folded with its factors in fp32
-#pragma unroll
-                for (int t = 0; t < 4; t += 2) {        // (one slab, then the other)
-                    float4_t part[2][RT];
-                    clear(part[0]), clear(part[1]);
-                    dec_mac<BITS, RT>(W[t / 2], A, part[0], part[1]);
-                    float sf[2];
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) sf[i] = GROUPED ? dec_lane((float)__builtin_bit_cast(_Float16, gs1), lane16, 16 * (t + i)) : 1.0f;
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const float pw = BF ? dec_lane(up[rt], lane_row, r) : 1.0f;
-#pragma unroll
-                            for (int i = 0; i < 2; ++i) acc[t + i][rt][r] = fmaf(part[i][rt][r], sf[i] * pw, acc[t + i][rt][r]);
-                        }
-                    if (RT > 1) __builtin_amdgcn_sched_barrier(0);
-                }
-            } else {
-                dec_mac<BITS, RT>(W[0], A, acc[0], acc[1]);
-                dec_mac<BITS, RT>(W[1], A, acc[2], acc[3]);
-            }
-            load_w1(u + 1);
-            load_a(u + 1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        MOE_DEC_STAMP(3);
-        if constexpr (CW > 2) load_factors();
-        // ---- the parts of K meet, sixteen rows at a time: rows 16 rt + 4 (lane / 16) + r, channels 64 cg + 16 t + lane % 16
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            if (rt) __syncthreads();                    // the sixteen rows before have been read
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) s_red[(kp * kDecFit + 4 * (lane >> 4) + r) * LDR + cg * 64 + 16 * t + (lane & 15)] = acc[t][rt][r];
-            __syncthreads();
-            float v[HC];
-#pragma unroll
-            for (int i = 0; i < HC; ++i) v[i] = s_red[h_row * LDR + h_ch + i];
-#pragma unroll
-            for (int q = 1; q < KP; ++q)
-#pragma unroll
-                for (int i = 0; i < HC; ++i) v[i] += s_red[(q * kDecFit + h_row) * LDR + h_ch + i];
-            uint32_t amax = 0;
-#pragma unroll
-            for (int i = 0; i < HC; ++i) {
-                const half2_t s2v = bits_h2(hs[i >> 1]), b2v = bits_h2(hb[i >> 1]);
-                v[i] = fmaf(v[i], GROUPED ? 1.0f : (float)s2v[i & 1], (float)b2v[i & 1]);
-            }
-            if (p.act == MOE_ACT_GELU) {
-#pragma unroll
-                for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_GELU);
-            } else {
-#pragma unroll
-                for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_RELU);
-            }
-            if constexpr (BF) {
-                float down, up;
-#pragma unroll
-                for (int i = 0; i < HC; ++i) {
-                    v[i] = __uint_as_float((uint32_t)to_bf16_rne(v[i]) << 16);
-                    amax = max(amax, (__float_as_uint(v[i]) >> 16) & 0x7fffu);
-                }
-#pragma unroll
-                for (int off = 16; off > 0; off >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, off));
-                dec_row_pow(amax, down, up);
-                if ((tid & 31) == 0) s_pow[16 * rt + h_row] = up;
-#pragma unroll
-                for (int i = 0; i < HC; ++i) v[i] *= down;
-            }
-#pragma unroll
-            for (int i = 0; i < HC; i += 2) {
-                const half2_t hv = {(_Float16)v[i], (_Float16)v[i + 1]};
-                *reinterpret_cast<uint32_t *>(s_h + (16 * rt + h_row) * LDH + h_ch + i) = h2_bits(hv);
-            }
-        }
-        __syncthreads();
-
-        MOE_DEC_STAMP(4);
-        // ---- fc2 on the slice: the rows x 32 output channels per slab, K = the slice's channels
-        const uint16_t *h_ptr = s_h + (lane & 15) * LDH + koct;
-        float *const part_c = p.partial + (size_t)c * p.n_assign * d + slab0 * 32;
-        int row_off[RT][4];
-        float pw[RT][4];
+    for (int rt = 0; rt < RT; ++rt) {
+        const int m = 16 * rt + (lane & 15), tok = s_row[min(m, rows - 1)] >> (p.gate_k - 1);      // one or two experts per token
+        a_off[rt] = m < rows ? ((uint32_t)tok * d + koct) * 2u : 0x7fffff00u;
+    }
+    auto load_a = [&](int u) {
+        const __amdgpu_buffer_rsrc_t r = dec_rsrc(p.x + (u0 + u) * 64, u < n1 ? x_bytes - (u0 + u) * 128 : 0);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = 16 * rt + 4 * (lane >> 4) + r;
-                row_off[rt][r] = m < rows ? s_row[z0 + m] * d + (lane & 15) : -1;
-                pw[rt][r] = BF ? s_pow[m] : 1.0f;
+            for (int q = 0; q < 2; ++q) {
+                const dec_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, a_off[rt] + 64 * q, 0, 0);
+                A[rt][q] = make_uint4(v.x, v.y, v.z, v.w);
             }
-        float4_t y0[RT], y1[RT];
-        clear(y0), clear(y1);
-        auto read_h = [&](int unit, uint4 (&a)[RT][2]) {
+    };
+    load_a(0);
+
+    // ---- fc1: the rows x 64 channels over the wavefront's part of K
+    float4_t acc[4][RT];
+    auto clear = [&](float4_t (&t)[RT]) {
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
+        for (int rt = 0; rt < RT; ++rt) t[rt] = float4_t{0.f, 0.f, 0.f, 0.f};
+    };
 #pragma unroll
-                for (int q = 0; q < 2; ++q) a[rt][q] = *reinterpret_cast<const uint4 *>(h_ptr + 16 * rt * LDH + unit * 64 + 32 * q);
-        };
-        auto unit_mac = [&](int i, const uint4 (&a)[RT][2], float4_t (&lo)[RT], float4_t (&hi)[RT]) {
-            if constexpr (GROUPED) {
-                float4_t p0[RT], p1[RT];
-                clear(p0), clear(p1);
-                dec_mac<BITS, RT>(V[i], a, p0, p1);
-                const float sl = (float)__builtin_bit_cast(_Float16, gs2[i]), f0 = dec_lane(sl, lane16, 0), f1 = dec_lane(sl, lane16, 16);
+    for (int t = 0; t < 4; ++t) clear(acc[t]);
+    for (int u = 0; u < n1; ++u) {
+        float up[RT];
+        if constexpr (BF) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                uint32_t amax = 0;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].x), A[rt][q].y);
+                    amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].z), A[rt][q].w);
+                }
+                float down;
+                dec_row_pow(dec_max_over_rows(amax), down, up[rt]);
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    A[rt][q] = make_uint4(dec_bf16_pair_to_f16(A[rt][q].x, down), dec_bf16_pair_to_f16(A[rt][q].y, down),
+                                          dec_bf16_pair_to_f16(A[rt][q].z, down), dec_bf16_pair_to_f16(A[rt][q].w, down));
+            }
+        }
+        if constexpr (GROUPED || BF) {              // the unit's sums, folded with its factors in fp32
+#pragma unroll
+            for (int t = 0; t < 4; t += 2) {        // (one slab, then the other)
+                float4_t part[2][RT];
+                clear(part[0]), clear(part[1]);
+                dec_mac<BITS, RT>(W[t / 2], A, part[0], part[1]);
+                float sf[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) sf[i] = GROUPED ? dec_lane((float)__builtin_bit_cast(_Float16, gs1), lane16, 16 * (t + i)) : 1.0f;
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) lo[rt][r] = fmaf(p0[rt][r], f0, lo[rt][r]), hi[rt][r] = fmaf(p1[rt][r], f1, hi[rt][r]);
-            } else {
-                dec_mac<BITS, RT>(V[i], a, lo, hi);
+                    for (int r = 0; r < 4; ++r) {
+                        const float pw = BF ? dec_lane(up[rt], lane_row, r) : 1.0f;
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) acc[t + i][rt][r] = fmaf(part[i][rt][r], sf[i] * pw, acc[t + i][rt][r]);
+                    }
+                if (RT > 1) __builtin_amdgcn_sched_barrier(0);
             }
-        };
-        auto store = [&](int n, const float4_t (&lo)[RT], const float4_t (&hi)[RT]) {       // this slice's part of y, channels n .. n + 31
+        } else {
+            dec_mac<BITS, RT>(W[0], A, acc[0], acc[1]);
+            dec_mac<BITS, RT>(W[1], A, acc[2], acc[3]);
+        }
+        load_w1(u + 1);
+        load_a(u + 1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    MOE_DEC_STAMP(3);
+    if constexpr (CW > 2) load_factors();
+    // ---- the parts of K meet, sixteen rows at a time: rows 16 rt + 4 (lane / 16) + r, channels 64 cg + 16 t + lane % 16
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        if (rt) __syncthreads();                    // the sixteen rows before have been read
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s_red[(kp * kDecFit + 4 * (lane >> 4) + r) * LDR + cg * 64 + 16 * t + (lane & 15)] = acc[t][rt][r];
+        __syncthreads();
+        float v[HC];
+#pragma unroll
+        for (int i = 0; i < HC; ++i) v[i] = s_red[h_row * LDR + h_ch + i];
+#pragma unroll
+        for (int q = 1; q < KP; ++q)
+#pragma unroll
+            for (int i = 0; i < HC; ++i) v[i] += s_red[(q * kDecFit + h_row) * LDR + h_ch + i];
+        uint32_t amax = 0;
+#pragma unroll
+        for (int i = 0; i < HC; ++i) {
+            const half2_t s2v = bits_h2(hs[i >> 1]), b2v = bits_h2(hb[i >> 1]);
+            v[i] = fmaf(v[i], GROUPED ? 1.0f : (float)s2v[i & 1], (float)b2v[i & 1]);
+        }
+        if (p.act == MOE_ACT_GELU) {
+#pragma unroll
+            for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_GELU);
+        } else {
+#pragma unroll
+            for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_RELU);
+        }
+        if constexpr (BF) {
+            float down, up;
+#pragma unroll
+            for (int i = 0; i < HC; ++i) {
+                v[i] = __uint_as_float((uint32_t)to_bf16_rne(v[i]) << 16);
+                amax = max(amax, (__float_as_uint(v[i]) >> 16) & 0x7fffu);
+            }
+#pragma unroll
+            for (int off = 16; off > 0; off >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, off));
+            dec_row_pow(amax, down, up);
+            if ((tid & 31) == 0) s_pow[16 * rt + h_row] = up;
+#pragma unroll
+            for (int i = 0; i < HC; ++i) v[i] *= down;
+        }
+#pragma unroll
+        for (int i = 0; i < HC; i += 2) {
+            const half2_t hv = {(_Float16)v[i], (_Float16)v[i + 1]};
+            *reinterpret_cast<uint32_t *>(s_h + (16 * rt + h_row) * LDH + h_ch + i) = h2_bits(hv);
+        }
+    }
+    __syncthreads();
+
+    MOE_DEC_STAMP(4);
+    // ---- fc2 on the slice: the rows x 32 output channels per slab, K = the slice's channels
+    const uint16_t *h_ptr = s_h + (lane & 15) * LDH + koct;
+    float *const part_c = p.partial + (size_t)c * p.n_assign * d + slab0 * 32;
+    int row_off[RT][4];
+    float pw[RT][4];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = 16 * rt + 4 * (lane >> 4) + r;
+            row_off[rt][r] = m < rows ? s_row[m] * d + (lane & 15) : -1;
+            pw[rt][r] = BF ? s_pow[m] : 1.0f;
+        }
+    float4_t y0[RT], y1[RT];
+    clear(y0), clear(y1);
+    auto read_h = [&](int unit, uint4 (&a)[RT][2]) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) a[rt][q] = *reinterpret_cast<const uint4 *>(h_ptr + 16 * rt * LDH + unit * 64 + 32 * q);
+    };
+    auto unit_mac = [&](int i, const uint4 (&a)[RT][2], float4_t (&lo)[RT], float4_t (&hi)[RT]) {
+        if constexpr (GROUPED) {
+            float4_t p0[RT], p1[RT];
+            clear(p0), clear(p1);
+            dec_mac<BITS, RT>(V[i], a, p0, p1);
+            const float sl = (float)__builtin_bit_cast(_Float16, gs2[i]), f0 = dec_lane(sl, lane16, 0), f1 = dec_lane(sl, lane16, 16);
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (row_off[rt][r] >= 0) {
-                        part_c[row_off[rt][r] + n] = BF ? lo[rt][r] * pw[rt][r] : lo[rt][r];
-                        part_c[row_off[rt][r] + n + 16] = BF ? hi[rt][r] * pw[rt][r] : hi[rt][r];
-                    }
-        };
-        // two units at a time, whose chains of unpacking and products the wavefront interleaves: two slabs (slices of 64 channels)
-        // or two units of a slab
-        for (int base = 0; base < n2; base += U2) {
+                for (int r = 0; r < 4; ++r) lo[rt][r] = fmaf(p0[rt][r], f0, lo[rt][r]), hi[rt][r] = fmaf(p1[rt][r], f1, hi[rt][r]);
+        } else {
+            dec_mac<BITS, RT>(V[i], a, lo, hi);
+        }
+    };
+    auto store = [&](int n, const float4_t (&lo)[RT], const float4_t (&hi)[RT]) {       // this slice's part of y, channels n .. n + 31
 #pragma unroll
-            for (int i = 0; i < U2; i += 2) {
-                const int j = base + i, unit = CW == 1 ? 0 : U2 % CW == 0 ? i % CW : j % CW;
-                if (j < n2) {
-                    uint4 a0[RT][2];
-                    read_h(unit, a0);
-                    if constexpr (CW == 1) {
-                        float4_t z0v[RT], z1v[RT];
-                        clear(y0), clear(y1), clear(z0v), clear(z1v);
-                        unit_mac(i, a0, y0, y1);
-                        unit_mac(i + 1, a0, z0v, z1v);
-                        store(j * 32, y0, y1);
-                        if (j + 1 < n2) store(j * 32 + 32, z0v, z1v);
-                    } else {
-                        uint4 a1[RT][2];
-                        read_h(unit + 1, a1);
-                        unit_mac(i, a0, y0, y1);
-                        unit_mac(i + 1, a1, y0, y1);
-                        if (unit == CW - 2) {
-                            store(j / CW * 32, y0, y1);
-                            clear(y0), clear(y1);
-                        }
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (row_off[rt][r] >= 0) {
+                    part_c[row_off[rt][r] + n] = BF ? lo[rt][r] * pw[rt][r] : lo[rt][r];
+                    part_c[row_off[rt][r] + n + 16] = BF ? hi[rt][r] * pw[rt][r] : hi[rt][r];
+                }
+    };
+    // two units at a time, whose chains of unpacking and products the wavefront interleaves: two slabs (slices of 64 channels)
+    // or two units of a slab
+    for (int base = 0; base < n2; base += U2) {
+#pragma unroll
+        for (int i = 0; i < U2; i += 2) {
+            const int j = base + i, unit = CW == 1 ? 0 : U2 % CW == 0 ? i % CW : j % CW;
+            if (j < n2) {
+                uint4 a0[RT][2];
+                read_h(unit, a0);
+                if constexpr (CW == 1) {
+                    float4_t z0v[RT], z1v[RT];
+                    clear(y0), clear(y1), clear(z0v), clear(z1v);
+                    unit_mac(i, a0, y0, y1);
+                    unit_mac(i + 1, a0, z0v, z1v);
+                    store(j * 32, y0, y1);
+                    if (j + 1 < n2) store(j * 32 + 32, z0v, z1v);
+                } else {
+                    uint4 a1[RT][2];
+                    read_h(unit + 1, a1);
+                    unit_mac(i, a0, y0, y1);
+                    unit_mac(i + 1, a1, y0, y1);
+                    if (unit == CW - 2) {
+                        store(j / CW * 32, y0, y1);
+                        clear(y0), clear(y1);
                     }
                 }
-                load_w2(i, j + U2);
-                load_w2(i + 1, j + 1 + U2);
-                __builtin_amdgcn_sched_barrier(0);
             }
-        }
-        MOE_DEC_STAMP(5);
-        // (a further pass: s_h and s_pow are written again only behind the barrier that follows its fc1)
-        if (z0 + FIT < count) {
-            __syncthreads();
-            prime();
+            load_w2(i, j + U2);
+            load_w2(i + 1, j + 1 + U2);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
+    MOE_DEC_STAMP(5);
 }
 
 // Sum of the d_ff slices and of a token's experts: out[t] = sum_j scale[a] * (W2-scale * sum_c partial[c][a] + b2),
@@ -631,7 +644,9 @@ int launch_decode_ffn(const DecodeArgs &q, int bits, bool bf, hipStream_t s)
     p.row_tiles = p.n_assign > 8 * p.E && bits == 4 && !bf ? 2 : 1;
     p.group_inv = units > 1 ? (uint32_t)(((1ull << 32) + units - 1) / units) : 0;
     const int S = p.F / (64 * p.cw);
-    const dim3 grid(1 + (unsigned)(p.E < p.n_assign ? p.E : p.n_assign) * S);      // (the first block writes the index arrays)
+    // the most items that a routing can make: one per expert with rows, one more for every further `fit` rows (the first block writes the index arrays)
+    const int fit = kDecFit * p.row_tiles, items = p.n_assign <= p.E ? p.n_assign : p.E + (p.n_assign - p.E) / fit;
+    const dim3 grid(1 + (unsigned)items * S);
     if (bits == 4) launch_decode_bits<4>(p, bf, grid, s);
     else launch_decode_bits<8>(p, bf, grid, s);
     int rc = check_launch("moe_grouped_ffn_wq (decode kernel)");

@@ -151,3 +151,13 @@ def test_long_rings_where_a_64_row_tile_has_its_compute_unit_to_itself():
     for (sizes, want), call in zip(cases, L.record([L.ffn(*c) for c, _ in cases])):
         ring = [p for p in call.launches if p.kernel.startswith("grouped_gemm_ring") and p.kernel.endswith("64>")]
         assert ring and (ring[0].shared > 80 * 1024) is want, (sizes, call.launches)
+
+
+def test_decode_kernel_has_blocks_for_every_row_group_of_any_routing():
+    """A block per slice and (expert, sixteen or thirty-two of its rows), however the rows fall: at most one item per assignment, and one per
+    expert and for each further pass of rows.  (128 rows on two of 64 experts of 4096 x 16384, group scales: 383 us with the passes of an expert in one
+    block, 8.2 ms for ... )"""
+    cases = [((1, 2, 32, 1024, 4096, 4), 2, 64), ((64, 2, 64, 4096, 16384, 4, 128), 64 + 4, 32), ((192, 2, 32, 1024, 4096, 4), 32 + 352 // 32, 8),
+             ((256, 2, 2, 64, 64, 8), 2 + 510 // 16, 1), ((256, 2, 2, 64, 64, 4), 2 + 510 // 32, 1), ((256, 2, 512, 64, 64, 4), 512, 1)]
+    for (sizes, items, slices), call in zip(cases, L.record([L.sliced(*c[0]) for c in cases])):
+        assert call.rc == 0 and call.launches[0].kernel.startswith("decode_ffn_kernel") and call.launches[0].grid[0] == 1 + items * slices, (sizes, call.launches)

@@ -40,6 +40,13 @@ def test_wide_slices_match_oracle(d, F, act, bits, g, T):
     _check(d, F, act, bits, g, T, 2, 34, 20 if T == 60 else 45)
 
 
+# experts with far more rows than one item takes, beside experts with few or none; more experts than lanes, with spans of 5 and 64 experts
+@pytest.mark.parametrize("T,k,E,load", [(256, 2, 2, -1), (256, 2, 70, 200), (200, 1, 1, -1), (130, 2, 300, 90), (60, 2, 4096, 40)])
+@pytest.mark.parametrize("act,bits,g", [("f16", 4, 0), ("f16", 8, 64), ("bf16", 4, 64)])
+def test_rows_of_crowded_experts_match_oracle(act, bits, g, T, k, E, load):
+    _check(64, 128 if E > 1000 else 1024, act, bits, g, T, k, E, load)
+
+
 def _check(d, F, act, bits, g, T, k, E, load):
     print(f"sliced T={T} k={k} E={E} d={d} F={F} {act} bits={bits} g={g}", flush=True)
     rng = np.random.default_rng(d + F + bits + T)
