@@ -164,8 +164,8 @@ int moe_permute(const int32_t *expert_idx, const void *x, int act_dtype, int T, 
  * Requires d % 64 == 0, F % 64 == 0, bits in {4,8}, group_size 0 or a multiple of 64 dividing
  * both d and F.
  * Workspace: h (R * F elements of act_dtype), for bf16 rows their per-row factors and x_perm converted to
- * scaled FP16 (R * d elements), and for decode-sized batches (R <= 256) the partial sums
- * moe_grouped_ffn_wq_gated keeps (F / 512 x R x d fp32).
+ * scaled FP16 (R * d elements); at the sizes of moe_grouped_ffn_wq_gated's decode kernel room for its partial sums too
+ * (R x d fp32 per slice of d_ff).
  */
 size_t moe_grouped_ffn_wq_workspace_bytes(int R, int d, int F, int E, int act_dtype);
 int moe_grouped_ffn_wq(const void *x_perm, int act_dtype, const int32_t *expert_offsets, int R,
@@ -183,7 +183,7 @@ int moe_grouped_ffn_wq(const void *x_perm, int act_dtype, const int32_t *expert_
  * moe_grouped_ffn_wq_noalloc_max_bytes() = 8 MiB inside the library's own device memory, which
  * every GPU the library is used on holds until the process ends.  The call allocates and frees
  * nothing (its first call on a device looks up the array's address, nothing more).
- *   Sizes whose moe_grouped_ffn_wq_workspace_bytes(R, d, F, E, act_dtype) exceeds the array are
+ *   Sizes that need more of it than the array holds are
  *   refused with MOE_ERR_WORKSPACE before anything is launched (decode-sized batches fit: 128 rows
  *   of F = 4096 take 1 MiB; R * F <= 4 Mi elements of fp16 in general).
  *   All calls on one GPU share that GPU's array, which keeps the last call's h: nothing in it has
@@ -253,7 +253,8 @@ int moe_grouped_ffn_wq_indexed(const void *x, int act_dtype, const int32_t *perm
  *   With expert_scale given and sizes the decode kernel is built for (4-bit: d = 1024; 8-bit:
  *   d = 512; F a multiple of 512 up to 4096; at most 8 assignments per expert on average and at
  *   least 64 slices of 512 d_ff channels in all), the call is two launches, those of
- *   moe_grouped_ffn_wq_sliced with slices of 512 channels: a block per expert with rows and slice
+ *   moe_grouped_ffn_wq_sliced (a workspace too small for the slices it would take makes them wider, up to 512
+ *   channels): a block per expert, sixteen or thirty-two of its rows and slice
  *   (fc1, activation and fc2, h staying on chip) leaves fp32 partial sums of y in the workspace; a
  *   small second launch adds the slices in a fixed order, applies the channel scale, bias and gate scale
  *   and writes out.  No atomics on memory on this path.  (For timing studies y_perm may be NULL on this

@@ -86,11 +86,22 @@ static int rows_to_f16(const uint16_t *in, uint16_t *out, int R, int K, float2 *
     return check_launch("moe_grouped_ffn_wq (bf16 rows to scaled FP16)");
 }
 
+// Sizes for which the gated call runs the decode kernel instead of two streaming launches: the ones it was measured to be the faster way
+// for in this call (one K range per weight width; other sizes have moe_grouped_ffn_wq_sliced, which takes any).
+static bool gated_decode(int R, int E, int d, int F, int bits)
+{
+    if (R < 1 || R > kGatedMaxAssign || E < 1 || E > kDecMaxExperts) return false;
+    if (d != (bits == 4 ? 1024 : 512) || F % 512 || F / 512 > 8 || F < 512) return false;
+    return (long)R <= 8L * E && (long)E * (F / 512) >= 64;
+}
+
 struct FfnWorkspace {
-    size_t h_off, pow_x_off, pow_h_off, x16_off, partial_off, total;
+    size_t h_off, pow_x_off, pow_h_off, x16_off;
+    size_t own;             // what the two GEMMs need
+    size_t total;           // with the decode kernel's partial sums of y, which that kernel keeps at the start of the workspace
 };
 
-static FfnWorkspace ffn_workspace(int R, int d, int F, int act_dtype)
+static FfnWorkspace ffn_workspace(int R, int E, int d, int F, int act_dtype)
 {
     FfnWorkspace w;
     size_t o = 0;
@@ -102,9 +113,8 @@ static FfnWorkspace ffn_workspace(int R, int d, int F, int act_dtype)
     if (act_dtype == MOE_BF16) o += round_up((size_t)R * sizeof(float2), 256);
     w.x16_off = o;                               // bf16 rows: x converted to scaled FP16 (h is converted in place)
     if (act_dtype == MOE_BF16) o += round_up((size_t)R * d * 2, 256);
-    w.partial_off = o;                           // decode kernel in the gated call: partial sums of y per d_ff slice of 512 channels
-    if (R <= kGatedMaxAssign && F % 512 == 0) o += round_up(decode_ffn_partial_bytes(R, d, F, 8), 256);
-    w.total = o < 256 ? 256 : o;
+    w.own = w.total = o < 256 ? 256 : o;
+    if (gated_decode(R, E, d, F, 4) || gated_decode(R, E, d, F, 8)) w.total += round_up(decode_ffn_partial_bytes(R, d, F, decode_slice_width(R, E, F)), 256);
     return w;
 }
 
@@ -112,9 +122,8 @@ static FfnWorkspace ffn_workspace(int R, int d, int F, int act_dtype)
 
 extern "C" size_t moe_grouped_ffn_wq_workspace_bytes(int R, int d, int F, int E, int act_dtype)
 {
-    (void)E;
     if (R <= 0 || d <= 0 || F <= 0) return 256;
-    return moe::ffn_workspace(R, d, F, act_dtype).total;
+    return moe::ffn_workspace(R, E, d, F, act_dtype).total;
 }
 
 // Which kernel can take one GEMM of the FFN, from what the host knows about the routed loads: an upper bound on the rows of any
@@ -203,14 +212,6 @@ static bool tiled_only(int R, int E, int max_rows, int d, int F, int bits, bool 
            choose_kernel(R, E, max_rows, F, d, bits, smode, bf) == GEMM_TILED;
 }
 
-// Sizes for which the gated call runs the decode kernel: those its workspace has had room for the slices' partial sums for.
-static bool gated_decode(int R, int E, int d, int F, int bits)
-{
-    if (R < 1 || R > moe::kGatedMaxAssign || E < 1 || E > moe::kDecMaxExperts) return false;
-    if (d != (bits == 4 ? 1024 : 512) || F % 512 || F / 512 > 8 || F < 512) return false;
-    return (long)R <= 8L * E && (long)E * (F / 512) >= 64;
-}
-
 static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_offsets, int R,
                     int E, int max_rows_per_expert, int d, int F, int bits, int group_size, int activation,
                     const void *w1_packed,
@@ -222,9 +223,9 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
                     int32_t *offsets_out = nullptr)
 {
     using namespace moe;
-    // (y_perm may be NULL only on the decode kernel's path, where it means "leave out the slice reduction")
-    const bool partial_only = !y_perm && gate_idx && expert_scale && act_dtype == MOE_F16 && group_size == 0 &&
-                              gated_decode(R, E, d, F, bits);
+    // decode-sized batch with everything fused: one streaming launch for the sort and both GEMMs, then the slice reduction
+    const bool decode = gate_idx && expert_scale && act_dtype == MOE_F16 && group_size == 0 && gated_decode(R, E, d, F, bits);
+    const bool partial_only = !y_perm && decode;        // (on that path NULL means "leave out the slice reduction")
     if (!expert_offsets || !w1_packed || !s1 || !w2_packed || !s2 || (R != 0 && (!x_perm || (!y_perm && !partial_only))))
         return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq: NULL pointer");
     if (R < 0 || E <= 0 || d <= 0 || F <= 0 || max_rows_per_expert < 0)
@@ -240,9 +241,10 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     const void *ptrs[] = {x_perm, w1_packed, s1, b1, w2_packed, s2, b2, y_perm, workspace};
     for (const void *q : ptrs)
         if (!aligned16(q)) return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq: buffers must be 16-byte aligned");
-    const FfnWorkspace ws = ffn_workspace(R, d, F, act_dtype);
-    if (!workspace || workspace_bytes < ws.total)
-        return fail(MOE_ERR_WORKSPACE, "moe_grouped_ffn_wq: workspace of %zu bytes needed, %zu given", ws.total, workspace_bytes);
+    const FfnWorkspace ws = ffn_workspace(R, E, d, F, act_dtype);
+    const size_t least = decode ? decode_ffn_partial_bytes(R, d, F, 8) : ws.own;
+    if (!workspace || workspace_bytes < least)
+        return fail(MOE_ERR_WORKSPACE, "moe_grouped_ffn_wq: workspace of %zu bytes needed, %zu given", least, workspace_bytes);
     reset_kernel_notes();
     if (R == 0) return MOE_OK;
 
@@ -251,17 +253,19 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     const int max_rows = max_rows_per_expert > 0 && max_rows_per_expert < R ? max_rows_per_expert : R;
     unsigned char *wsb = (unsigned char *)workspace;
     void *h = wsb + ws.h_off;
-    // decode-sized batch with everything fused: one streaming launch for the sort and both GEMMs, then the slice reduction
-    if (gate_idx && expert_scale && !bf && group_size == 0 && gated_decode(R, E, d, F, bits)) {
+    if (decode) {
+        // (a workspace asked for with more rows may hold fewer slices than this batch would take: they are then wider)
+        int cw = decode_slice_width(R, E, F);
+        while (cw < 8 && decode_ffn_partial_bytes(R, d, F, cw) > workspace_bytes) cw *= 2;
         DecodeArgs q{};
         q.x = (const uint16_t *)x_perm; q.gate_idx = gate_idx; q.gate_scale = expert_scale; q.n_assign = R; q.gate_k = k;
         q.E = E; q.d = d; q.F = F; q.act = activation;
         q.w1 = (const uint8_t *)w1_packed; q.w2 = (const uint8_t *)w2_packed;
         q.s1 = (const __half *)s1; q.s2 = (const __half *)s2; q.b1 = (const __half *)b1; q.b2 = (const __half *)b2;
-        q.cw = 8; q.partial = (float *)(wsb + ws.partial_off); q.out = y_perm; q.out_dtype = MOE_F32;
+        q.cw = cw; q.partial = (float *)wsb; q.out = y_perm; q.out_dtype = MOE_F32;
         q.perm_src_out = perm_src_out; q.inv_perm_out = inv_perm_out; q.offsets_out = offsets_out;
         note_kernel("decode_ffn_kernel");
-        return launch_decode_ffn(q, bits, false, as_stream(stream));
+        return launch_decode_ffn(q, bits, false, s);
     }
     float2 *pow_x = (float2 *)(wsb + ws.pow_x_off), *pow_h = (float2 *)(wsb + ws.pow_h_off);
     const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
@@ -367,7 +371,7 @@ extern "C" int moe_grouped_ffn_wq_noalloc(const void *x_perm, int act_dtype, con
 {
     using namespace moe;
     if (R > 0 && d > 0 && F > 0) {
-        const size_t need = moe_grouped_ffn_wq_workspace_bytes(R, d, F, E, act_dtype);
+        const size_t need = ffn_workspace(R, E, d, F, act_dtype).own;
         if (need > kScratchBytes)
             return fail(MOE_ERR_WORKSPACE, "moe_grouped_ffn_wq_noalloc: R=%d rows of F=%d need %zu bytes of scratch, the built-in "
                                            "array holds %zu: use moe_grouped_ffn_wq with a workspace", R, F, need, kScratchBytes);

@@ -25,7 +25,7 @@ rec = ctypes.CDLL(shim, mode=ctypes.RTLD_GLOBAL)
 rec.recorder_take.restype = ctypes.c_char_p
 lib = ctypes.CDLL(lib_path)
 lib.moe_last_ffn_kernels.restype = ctypes.c_char_p
-conv = lambda a: ctypes.c_void_p(0x10000) if a == "ptr" else ctypes.c_void_p(None) if a is None else ctypes.c_size_t(a) if a >= 1 << 31 else ctypes.c_int(a)
+conv = lambda a: ctypes.c_void_p(0x10000) if a == "ptr" else ctypes.c_void_p(None) if a is None else ctypes.c_size_t(a[0]) if isinstance(a, list) else ctypes.c_size_t(a) if a >= 1 << 31 else ctypes.c_int(a)
 out = []
 for name, device, args in json.load(sys.stdin):
     rec.recorder_device(device)
@@ -85,3 +85,7 @@ def indexed(R, E, k, d, F, bits, g=0, act=B.MOE_F16, bound=0, scale=False):
 
 def sliced(T, k, E, d, F, bits, g=0, act=B.MOE_F16, out=B.MOE_F32):
     return "moe_grouped_ffn_wq_sliced", [P, act, P, P, T, k, E, d, F, bits, g, 0, P, P, None, P, P, None, P, out, P, P, P, P, _SIZE, None]
+
+
+def gated(T, k, E, d, F, bits, scale=True, workspace=_SIZE):
+    return "moe_grouped_ffn_wq_gated", [P, B.MOE_F16, P, P if scale else None, T, k, E, d, F, bits, 0, 0, P, P, None, P, P, None, P, B.MOE_F32, P, P, P, P, [workspace], None]

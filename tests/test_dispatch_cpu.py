@@ -161,3 +161,21 @@ def test_decode_kernel_has_blocks_for_every_row_group_of_any_routing():
              ((256, 2, 2, 64, 64, 8), 2 + 510 // 16, 1), ((256, 2, 2, 64, 64, 4), 2 + 510 // 32, 1), ((256, 2, 512, 64, 64, 4), 512, 1)]
     for (sizes, items, slices), call in zip(cases, L.record([L.sliced(*c[0]) for c in cases])):
         assert call.rc == 0 and call.launches[0].kernel.startswith("decode_ffn_kernel") and call.launches[0].grid[0] == 1 + items * slices, (sizes, call.launches)
+
+
+def test_gated_call_cuts_d_ff_as_the_sliced_call_does():
+    """The decode kernel in the gated call: slices as wide as the batch asks for, wider where the workspace holds no more, the workspace
+    query large enough for them, and no room for partial sums where that kernel does not run."""
+    lib = B.load()
+    sizes = [(1, 2, 32, 1024, 4096, 4), (4, 2, 32, 1024, 4096, 4), (16, 2, 32, 1024, 4096, 4), (64, 2, 32, 1024, 4096, 4), (128, 2, 64, 1024, 4096, 4),
+             (60, 1, 8, 1024, 4096, 4), (1, 1, 16, 512, 2048, 8), (128, 2, 128, 512, 2048, 8), (100, 1, 64, 1024, 1024, 4)]
+    query = lambda T, k, E, d, F: lib.moe_grouped_ffn_wq_workspace_bytes(T * k, d, F, E, B.MOE_F16)  # noqa: E731
+    own, sliced, tight = (L.record(c) for c in ([L.gated(*s, workspace=query(*s[:5])) for s in sizes], [L.sliced(*s) for s in sizes],
+                                                [L.gated(*s, workspace=max(s[4] // 512 * s[0] * s[1] * s[3] * 4, 1 << 16)) for s in sizes]))
+    for s, a, b, c in zip(sizes, own, sliced, tight):
+        assert a.rc == b.rc == 0 and a.launches == b.launches and a.launches[0].kernel.startswith("decode_ffn_kernel"), (s, a.launches, b.launches)
+        assert c.rc == 0 and c.launches[0].grid[0] <= a.launches[0].grid[0]
+    assert tight[3].launches[0].kernel == "decode_ffn_kernel<4, false, false, 8, 1>" != own[3].launches[0].kernel
+    assert L.record([L.gated(*sizes[3], workspace=8 * 128 * 1024 * 4 - 1)])[0].rc == 3
+    assert query(128, 2, 64, 4096, 16384) == 256 * 16384 * 2              # h and nothing else
+    assert L.record([("moe_grouped_ffn_wq_noalloc", [*L.ffn(120, 15, 1024, 4096, 4)[1][:-3], None])])[0].rc == 0    # (8 MiB hold its h, not the slices)
