@@ -496,7 +496,9 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
 //    2048 42.6 and 43.5), with group scales twelve, 110 MB and four times d (71 tokens, two of 16 of 1024 x 4096 48.0 and 36.9; 154, two of 32
 //    51.6 and 52.3; 96, two of 16 of 2048 x 4096 55 and 58), but not where one and a bit blocks per compute unit would keep some busy
 //    twice as long as others (250 tokens, two of 60 of 1536 x 1280, 300 blocks, 54.5 and 58.3);
-//  - the partial sums of a slice, rows x d x 4 bytes, well below its weights (narrow slices, where d_ff leaves no wider ones);
+//  - the partial sums of a slice, rows x d x 4 bytes, well below its weights, and no thousands of slices of 64 channels, where d_ff leaves no
+//    wider ones: a block's start then costs more than its few weights (218 tokens on 115 of 256 x 5312, group scales, 8100 blocks, 65 and 101;
+//    139 on 131 of 640 x 4544, 6100, 81 and 110; 178 on 80 of 384 x 3392, 3800, 40 and 44; 43 on 71 of 448 x 6720, 3400, 17 % faster);
 //  - up to 300 MB of weights: beyond, the launch's fixed parts count little and the ring's loads into LDS keep more in flight (30 tokens
 //    on 32 experts of 4096 x 16384 8-bit 452 and 520; 79 on 64 of 1024 x 4096 8-bit, 382 MB, 83.5 and 85.8; 4-bit 104 MB 47 and 32), and
 //    180 MB for FP16 rows on 8-bit codes with channel scales where the gated call streams (28 / 40 / 60 / 100 / 200 tokens on 32 of 1024 x
@@ -511,7 +513,7 @@ extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F,
     const bool grouped = group_size != 0 && !(group_size == d && group_size == F), f16 = act_dtype == MOE_F16;
     const int cw = decode_slice_width(R, E, F);
     const double blocks = active * (F / 64) / cw;
-    if (5 * R > 4 * active * cw * bits) return 0;
+    if (5 * R > 4 * active * cw * bits || (cw == 1 && blocks > 3600)) return 0;
     if (R > 8L * E) {
         const bool fits = grouped ? R <= 12L * E && F >= 4 * d && bytes <= 110e6 : R <= 16L * E && F >= 2 * d && bytes <= 150e6;
         return f16 && bits == 4 && fits && (blocks <= 260 || blocks > 400);

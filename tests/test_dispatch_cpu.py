@@ -179,3 +179,13 @@ def test_gated_call_cuts_d_ff_as_the_sliced_call_does():
     assert L.record([L.gated(*sizes[3], workspace=8 * 128 * 1024 * 4 - 1)])[0].rc == 3
     assert query(128, 2, 64, 4096, 16384) == 256 * 16384 * 2              # h and nothing else
     assert L.record([("moe_grouped_ffn_wq_noalloc", [*L.ffn(120, 15, 1024, 4096, 4)[1][:-3], None])])[0].rc == 0    # (8 MiB hold its h, not the slices)
+
+
+def _pays(T, k, E, d, F, bits, g=0, act=B.MOE_F16):
+    return B.load().moe_grouped_ffn_wq_sliced_pays(T, k, E, d, F, bits, g, act)
+
+
+def test_layers_are_not_cut_into_thousands_of_narrow_slices():
+    assert not _pays(218, 1, 115, 256, 5312, 4, 64) and not _pays(139, 1, 131, 640, 4544, 4, 64) and not _pays(71, 2, 232, 576, 5952, 4, 0, B.MOE_BF16)
+    assert not _pays(184, 2, 167, 1024, 4800, 8, 64)
+    assert _pays(43, 1, 71, 448, 6720, 4) and _pays(236, 2, 78, 64, 7552, 8, 0, B.MOE_BF16) and _pays(218, 1, 115, 256, 5120, 4, 64)
