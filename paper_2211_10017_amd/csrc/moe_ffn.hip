@@ -500,10 +500,13 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
 //    wider ones: a block's start then costs more than its few weights (218 tokens on 115 of 256 x 5312, group scales, 8100 blocks, 65 and 101;
 //    139 on 131 of 640 x 4544, 6100, 81 and 110; 178 on 80 of 384 x 3392, 3800, 40 and 44; 43 on 71 of 448 x 6720, 3400, 17 % faster);
 //  - up to 300 MB of weights: beyond, the launch's fixed parts count little and the ring's loads into LDS keep more in flight (30 tokens
-//    on 32 experts of 4096 x 16384 8-bit 452 and 520; 79 on 64 of 1024 x 4096 8-bit, 382 MB, 83.5 and 85.8; 4-bit 104 MB 47 and 32), and
-//    180 MB for FP16 rows on 8-bit codes with channel scales where the gated call streams (28 / 40 / 60 / 100 / 200 tokens on 32 of 1024 x
-//    4096 44.8 / 43.5 / 50.0 / 55.3 / 59.7 and 43.2 / 45.6 / 49.9 / 55.2 / 63.8); FP16
-//    rows with group scales, whose scales the ring multiplies into the weights, at any size (64 tokens, 64 experts of 4096 x 16384 809 and 711).
+//    on 32 experts of 4096 x 16384 8-bit 457 and 486; 240 on 55 of 4096 x 4096 8-bit, 1.5 GB, 257 and 299);
+//  - FP16 rows on 8-bit codes with channel scales, more rows than experts: not from 140 MB on where the routes below stream and rows are long
+//    enough for that to go well (40 / 60 / 100 / 128 tokens, two of 32 of 1024 x 4096 53.6 / 56.4 / 58.5 / 59.2 and 53.5 / 57.3 / 67.6 / 69.0;
+//    120 on 22 of 2048 x 1536 49 and 54; but 512 x 4096, 128 on 64, 63 and 56), from 180 MB on not for the longest rows (64 tokens on 8 of 4096 x
+//    4096 65 and 85), and fewer narrow slices (100 tokens, two of 67 of 512 x 2112, 2100 slices, 41 and 50).  Where row tiles run
+//    below, sliced at any of these sizes (60 tokens, two of 32 of 1088 x 4096 74 and 57, of 960 x 4096 61 and 52; 160, two of 128 of 512 x 2048 63 and 53);
+//  - FP16 rows with group scales, whose scales the ring multiplies into the weights, at any size (64 tokens, 64 experts of 4096 x 16384 809 and 711).
 extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
 {
     using namespace moe;
@@ -518,7 +521,12 @@ extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F,
         const bool fits = grouped ? R <= 12L * E && F >= 4 * d && bytes <= 110e6 : R <= 16L * E && F >= 2 * d && bytes <= 150e6;
         return f16 && bits == 4 && fits && (blocks <= 260 || blocks > 400);
     }
-    if (bits == 8 && f16 && !grouped && R > E && bytes > 180e6 && (double)E * d * F <= 150e6) return 0;
+    if (bits == 8 && f16 && !grouped && R > E) {
+        const bool streams = moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype) ||
+                             !(moe_grouped_ffn_wq_routed_supported(R, E, T, d, F, bits, group_size, act_dtype) ||
+                               moe_grouped_ffn_wq_indexed_pays(R, E, T, d, F, bits, group_size, act_dtype));
+        if ((streams && d >= 1024 && bytes > 140e6) || (d >= 4096 && bytes > 180e6) || (cw == 1 && blocks > 1250)) return 0;
+    }
     return bytes <= 300e6 || (grouped && f16);
 }
 

@@ -189,3 +189,12 @@ def test_layers_are_not_cut_into_thousands_of_narrow_slices():
     assert not _pays(218, 1, 115, 256, 5312, 4, 64) and not _pays(139, 1, 131, 640, 4544, 4, 64) and not _pays(71, 2, 232, 576, 5952, 4, 0, B.MOE_BF16)
     assert not _pays(184, 2, 167, 1024, 4800, 8, 64)
     assert _pays(43, 1, 71, 448, 6720, 4) and _pays(236, 2, 78, 64, 7552, 8, 0, B.MOE_BF16) and _pays(218, 1, 115, 256, 5120, 4, 64)
+
+
+def test_eight_bit_layers_are_sliced_unless_the_route_below_streams():
+    """FP16 rows, channel scales, 140 to 300 MB of active weights: what decides is which kernel the layer would run otherwise."""
+    assert all(_pays(*c, 8) for c in [(40, 2, 32, 1088, 4096), (60, 2, 32, 1088, 4096), (60, 2, 32, 960, 4096), (128, 2, 32, 960, 4096), (160, 2, 128, 512, 2048),
+                                      (256, 2, 96, 512, 2560), (150, 2, 60, 768, 3072), (128, 2, 64, 512, 4096), (35, 1, 7, 2048, 8192)])
+    assert not any(_pays(*c, 8) for c in [(40, 2, 32, 1024, 4096), (100, 1, 32, 1024, 4096), (128, 2, 32, 1024, 4096), (100, 1, 24, 2048, 2048),
+                                          (64, 1, 8, 4096, 4096), (100, 2, 67, 512, 2112), (38, 2, 42, 1024, 2048)])
+    assert _pays(28, 1, 32, 1024, 4096, 8) and _pays(40, 2, 32, 1024, 4096, 4) and _pays(40, 2, 32, 1024, 4096, 8, 0, B.MOE_BF16)
