@@ -506,12 +506,15 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
 //    120 on 22 of 2048 x 1536 49 and 54; but 512 x 4096, 128 on 64, 63 and 56), from 180 MB on not for the longest rows (64 tokens on 8 of 4096 x
 //    4096 65 and 85), and fewer narrow slices (100 tokens, two of 67 of 512 x 2112, 2100 slices, 41 and 50).  Where row tiles run
 //    below, sliced at any of these sizes (60 tokens, two of 32 of 1088 x 4096 74 and 57, of 960 x 4096 61 and 52; 160, two of 128 of 512 x 2048 63 and 53);
-//  - FP16 rows with group scales, whose scales the ring multiplies into the weights, at any size (64 tokens, 64 experts of 4096 x 16384 809 and 711).
+//  - FP16 rows with group scales, whose scales the ring multiplies into the weights, at any size (64 tokens, 64 experts of 4096 x 16384 809 and 711);
+//  - wherever the gated call would run the decode kernel: it is the same one (128 tokens, two of 128 experts of 1024 x 4096, 460 MB, 104 in
+//    either call, 131 to 141 in row tiles; 60 on 8 22, where two streaming launches take 26).
 extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
 {
     using namespace moe;
     if (!moe_grouped_ffn_wq_sliced_workspace_bytes(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
     const int R = T * k;
+    if (gated_shapes(T, k, E, d, F, bits, group_size, act_dtype) == 2 && group_size == 0 && gated_decode(R, E, d, F, bits)) return 1;
     const double active = decode_active_experts(R, E), bytes = active * 2 * d * F * bits / 8;
     const bool grouped = group_size != 0 && !(group_size == d && group_size == F), f16 = act_dtype == MOE_F16;
     const int cw = decode_slice_width(R, E, F);

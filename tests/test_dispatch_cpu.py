@@ -198,3 +198,11 @@ def test_eight_bit_layers_are_sliced_unless_the_route_below_streams():
     assert not any(_pays(*c, 8) for c in [(40, 2, 32, 1024, 4096), (100, 1, 32, 1024, 4096), (128, 2, 32, 1024, 4096), (100, 1, 24, 2048, 2048),
                                           (64, 1, 8, 4096, 4096), (100, 2, 67, 512, 2112), (38, 2, 42, 1024, 2048)])
     assert _pays(28, 1, 32, 1024, 4096, 8) and _pays(40, 2, 32, 1024, 4096, 4) and _pays(40, 2, 32, 1024, 4096, 8, 0, B.MOE_BF16)
+
+
+def test_both_calls_answer_alike_for_the_decode_kernel():
+    """Where the gated call runs the decode kernel a layer takes the sliced call, whose launches are the same."""
+    sizes = [(128, 2, 128, 1024, 4096, 4), (100, 2, 128, 1024, 4096, 4), (64, 2, 256, 1024, 4096, 4), (60, 1, 8, 1024, 4096, 4), (128, 2, 128, 512, 2048, 8),
+             (64, 2, 32, 1024, 4096, 4), (128, 1, 16, 1024, 4096, 4), (128, 2, 256, 512, 2048, 8)]
+    for s, a, b in zip(sizes, L.record([L.gated(*s) for s in sizes]), L.record([L.sliced(*s) for s in sizes])):
+        assert a.launches[0].kernel.startswith("decode_ffn_kernel") and a.launches == b.launches and _pays(*s), s
