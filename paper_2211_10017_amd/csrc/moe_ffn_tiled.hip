@@ -1,5 +1,7 @@
 // Host side of the LDS-tiled grouped GEMM: tile height, grid size, and the hand-over to the
 // translation unit that holds the kernels of the weight width and activation dtype asked for.
+#include <math.h>
+
 #include "moe_ffn_common.h"
 
 namespace moe {
@@ -25,15 +27,26 @@ static int ring_rows(const GemmArgs &p, int bits, int mean)
     return ((long)p.R / 64 + experts / 2) * ncol <= 224 ? 64 : 0;
 }
 
-// Whether 64-row blocks of 8-bit weights take the whole LDS of a compute unit for their ring: typical row counts make no more blocks
-// than compute units, and the weights are many enough to come from memory, whose latency one stage in flight does not cover (25
-// layers of 18 MB and more 1.00 to 1.10 times as fast a step: 1000 FP16 tokens on 16 experts of 1088 x 4352 76.2 -> 69.5 us, 100 on one of
-// 4096 x 16384 161 -> 150, 997 bf16 tokens, two of 16 of 768 x 3072, fc2 31.9 -> 27.3; below, 0.92 to 1.0 times: 300 tokens, two of 8 of
-// 512 x 2048 36.1 -> 38.4).
+// Row tiles that R rows make on E experts under uniform routing, an expert's rows taken as normally distributed.
+static double expected_row_tiles(long R, long E, int bm)
+{
+    const double mean = (double)R / E, sd = sqrt(mean * (1.0 - 1.0 / E));
+    double tiles = floor(fmax(mean - 4 * sd, 0.0) / bm);       // (that all experts fill)
+    for (double first = tiles * bm; first < mean + 4 * sd; first += bm)
+        tiles += sd > 0 ? 0.5 * erfc((first + 0.5 - mean) / (sd * M_SQRT2)) : 1.0;
+    return tiles * E;
+}
+
+// Whether 64-row blocks of 8-bit weights take the whole LDS of a compute unit for their ring: uniform routing makes no more blocks
+// than compute units, and the weights are many enough to come from memory, whose latency one stage in flight does not cover.
+// A block more than that and the launch takes two rounds where two blocks per compute unit took one.  (244 GEMMs in 130 drawn layers: up to 250
+// expected blocks 1 to 15 % of a step gained, five 1 % lost; from 256 on 4 to 22 % lost, two equal; the blocks of a lone expert are known.  300 tokens on 4 experts of 1280 x
+// 5120: fc1, 307 blocks, 8 us lost of 64, fc2, 77, 5 gained; 100 on one of 5120 x 20480, 320 and 80 blocks, 18 lost and 25 gained of 197; 997 bf16 tokens, two
+// of 16 of 768 x 3072, fc2, 227 blocks, 31.9 -> 27.3.  Below 18 MB of weights 0.92 to 1.0 times as fast a step: 300 tokens, two of 8 of 512 x
+// 2048 36.1 -> 38.4.)
 static bool ring_long(const GemmArgs &p, int bm)
 {
-    const long tiles = ((long)p.R / bm + (p.E < p.R ? p.E : p.R) / 2) * ((p.N + 127) / 128);
-    return tiles <= 240 && (long)p.E * p.K * p.N >= 18000000l;
+    return (long)p.E * p.K * p.N >= 18000000l && expected_row_tiles(p.R, p.E, bm) * ((p.N + 127) / 128) <= (p.E > 1 ? 250 : 256);
 }
 
 int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
@@ -47,7 +60,7 @@ int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
         const long wgs = (slots * ((p.N + 127) / 128) + kXcds - 1) / kXcds * kXcds;      // upper bound of the work items, whole rounds of XCDs
         if (wgs > 0x7fffffffL) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq: %ld workgroups exceed one launch", wgs);
         GemmArgs q = p;
-        q.ring_long = ring_long(p, bm);
+        q.ring_long = bits == 8 && bm == 64 && ring_long(p, bm);
         (bits == 4 ? launch_ring_4 : launch_ring_8)(q, smode, bm, dim3((unsigned)wgs), s);
         return check_launch("moe_grouped_ffn_wq (gemm)");
     }

@@ -206,3 +206,12 @@ def test_both_calls_answer_alike_for_the_decode_kernel():
              (64, 2, 32, 1024, 4096, 4), (128, 1, 16, 1024, 4096, 4), (128, 2, 256, 512, 2048, 8)]
     for s, a, b in zip(sizes, L.record([L.gated(*s) for s in sizes]), L.record([L.sliced(*s) for s in sizes])):
         assert a.launches[0].kernel.startswith("decode_ffn_kernel") and a.launches == b.launches and _pays(*s), s
+
+
+def test_long_rings_only_where_one_round_of_blocks_is_expected():
+    """64-row tiles as uniform routing makes them: 65 to 90 rows per expert are two tiles nearly everywhere."""
+    cases = [((300, 4, 1280, 5120, 8), [False, True]), ((100, 1, 5120, 20480, 8), [False, True]), ((150, 2, 1280, 10240, 8), [False, True]),
+             ((340, 4, 1280, 5120, 8), [False, True]), ((1994, 16, 768, 3072, 8), [False, True]), ((64, 1, 4096, 16384, 8), [True, True]), ((65, 1, 4096, 16384, 8), [True, True]), ((65, 1, 4096, 16448, 8), [False, True]),
+             ((714, 26, 896, 2368, 8, 64), [False, False]), ((2046, 18, 7296, 832, 8, 64), [False, False]), ((722, 14, 3648, 1984, 8), [True, False])]
+    for (sizes, want), call in zip(cases, L.record([L.ffn(*c) for c, _ in cases])):
+        assert [p.shared > 80 * 1024 for p in call.launches if not p.kernel.startswith("rows")] == want, (sizes, call.launches)
