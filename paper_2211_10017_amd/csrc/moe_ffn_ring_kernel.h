@@ -45,22 +45,22 @@ struct RingShape {
     static constexpr int NST = kLimit / kStage;                     // stages
     static constexpr int kLds(int stages) { return stages * kStage > kEnd ? stages * kStage : kEnd; }
     static_assert(NST >= 2 && NST <= 4 && kLds(NST) <= kLimit, "a stage in use and one to three in flight (the chain of waits)");
-    // 64-row blocks of 8-bit weights, with one stage in flight, may take all of a compute unit's LDS instead (p.ring_stages)
+    // 64-row blocks of 8-bit weights, with one stage in flight, may take all of a compute unit's LDS instead (grouped_gemm_ring_long_kernel)
     static constexpr bool kLong = BITS == 8 && BM > 32;
     static constexpr int kMost = kLong ? 160 * 1024 / kStage : NST;
     static_assert(!kLong || (NST == 2 && kMost >= 4 && kMost <= 5 && kLds(kMost) <= 160 * 1024), "up to four in flight (the chain of waits)");
 };
 
-template <int BITS, int SMODE, int BM>
-__global__ __launch_bounds__(256, 2) void grouped_gemm_ring_kernel(GemmArgs p)
+template <int BITS, int SMODE, int BM, int NST>
+__device__ __forceinline__ void ring_gemm(const GemmArgs &p)
 {
     using S = RingShape<BITS, SMODE, BM>;
     constexpr int TM = S::TM, NW = S::NW, WC = S::WC, WK = S::WK;
     constexpr bool GROUPED = S::GROUPED, ACC = SMODE == SCALE_GROUP_ACC;
-    const int NST = S::kLong ? p.ring_stages : S::NST, D = NST - 1;     // stages, and those in flight
+    constexpr int D = NST - 1;                          // stages in flight, of NST
     constexpr int NA = BM / 8 > WC ? BM / 8 / WC : 1;   // row loads per wavefront and stage (8 rows each)
     constexpr int L = NA + 2 * NW + (GROUPED ? 1 : 0);  // loads per wavefront and stage
-    static_assert((S::kMost - 2) * L < 64, "the load counter has six bits");
+    static_assert((D - 1) * L < 64, "the load counter has six bits");
     extern __shared__ __align__(16) uint8_t lds[];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -200,23 +200,16 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_ring_kernel(GemmArgs p)
     // in order), and the barrier makes everyone's share visible and tells that everyone has left the
     // stage before it, which is then refilled.
 #pragma unroll
-    for (int s = 0; s < S::kMost - 1; ++s)
-        if (s < D && s < per) issue(s, s);
+    for (int s = 0; s < D; ++s)
+        if (s < per) issue(s, s);
     auto k_loop = [&](auto live_c) {
         int slot = 0;
         for (int s = 0; s < per; ++s) {
             const int rem = min(per - 1 - s, D - 1);
-            if constexpr (S::kLong) {
-                if (rem == 0) wait_loads<0>();
-                else if (rem == 3) wait_loads<3 * L>();
-                else if (rem == 2) wait_loads<2 * L>();
-                else wait_loads<L>();
-            } else {
-                constexpr int D = S::NST - 1;
-                if (rem == D - 1) wait_loads<(D - 1) * L>();
-                else if (D > 2 && rem == 1) wait_loads<(D > 2) * L>();
-                else wait_loads<0>();
-            }
+            if (rem == D - 1) wait_loads<(D - 1) * L>();
+            else if (D > 3 && rem == 2) wait_loads<(D > 3) * 2 * L>();
+            else if (D > 2 && rem == 1) wait_loads<(D > 2) * L>();
+            else wait_loads<0>();
             __syncthreads();
             if (s + D < per) issue(s + D, slot == 0 ? NST - 1 : slot - 1);
             if (s < mine) compute(slot, s + 1 == mine || (first + s + 1) * 64 % p.g == 0, live_c);
@@ -263,15 +256,35 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_ring_kernel(GemmArgs p)
     if (tile_ok) finish_tile<TM, QN, 32 * TM>(p, v, tile_rows, cs, bias, rows, 8 * (QN / 4) * kp, ntile0 * 32, lds + wave * kPatchBytes<QN>);
 }
 
+// The number of stages is a constant of the kernel: as an argument of one kernel for both it cost the shorter ring with group scales 1 to 3 %
+// (590 tokens, two of 5 experts of 1600 x 11456, 175 us a step and 169).
+template <int BITS, int SMODE, int BM>
+__global__ __launch_bounds__(256, 2) void grouped_gemm_ring_kernel(GemmArgs p)
+{
+    ring_gemm<BITS, SMODE, BM, RingShape<BITS, SMODE, BM>::NST>(p);
+}
+
+template <int BITS, int SMODE, int BM>
+__global__ __launch_bounds__(256, 2) void grouped_gemm_ring_long_kernel(GemmArgs p)
+{
+    ring_gemm<BITS, SMODE, BM, RingShape<BITS, SMODE, BM>::kMost>(p);
+}
+
 template <int BITS, int SMODE, int BM>
 static void launch_ring_shape(const GemmArgs &p, dim3 grid, hipStream_t s)
 {
     using S = RingShape<BITS, SMODE, BM>;
+    if constexpr (S::kLong) {
+        if (p.ring_long) {
+            static std::atomic<uint64_t> raised;
+            raise_lds_limit(reinterpret_cast<const void *>(&grouped_gemm_ring_long_kernel<BITS, SMODE, BM>), S::kLds(S::kMost), raised);
+            hipLaunchKernelGGL((grouped_gemm_ring_long_kernel<BITS, SMODE, BM>), grid, dim3(256), S::kLds(S::kMost), s, p);
+            return;
+        }
+    }
     static std::atomic<uint64_t> raised;
-    raise_lds_limit(reinterpret_cast<const void *>(&grouped_gemm_ring_kernel<BITS, SMODE, BM>), S::kLds(S::kMost), raised);
-    GemmArgs q = p;
-    q.ring_stages = p.ring_long ? S::kMost : S::NST;
-    hipLaunchKernelGGL((grouped_gemm_ring_kernel<BITS, SMODE, BM>), grid, dim3(256), S::kLds(q.ring_stages), s, q);
+    raise_lds_limit(reinterpret_cast<const void *>(&grouped_gemm_ring_kernel<BITS, SMODE, BM>), S::kLds(S::NST), raised);
+    hipLaunchKernelGGL((grouped_gemm_ring_kernel<BITS, SMODE, BM>), grid, dim3(256), S::kLds(S::NST), s, p);
 }
 
 template <int BITS, int SMODE>

@@ -215,3 +215,12 @@ def test_long_rings_only_where_one_round_of_blocks_is_expected():
              ((714, 26, 896, 2368, 8, 64), [False, False]), ((2046, 18, 7296, 832, 8, 64), [False, False]), ((722, 14, 3648, 1984, 8), [True, False])]
     for (sizes, want), call in zip(cases, L.record([L.ffn(*c) for c, _ in cases])):
         assert [p.shared > 80 * 1024 for p in call.launches if not p.kernel.startswith("rows")] == want, (sizes, call.launches)
+        assert [p.kernel.startswith("grouped_gemm_ring_long") for p in call.launches if not p.kernel.startswith("rows")] == want      # its depth is a constant
+
+
+def test_the_oracle_comparisons_reach_every_long_ring():
+    import test_gpu_ring
+    act = {"f16": B.MOE_F16, "bf16": B.MOE_BF16}
+    (m_act, m_rows) = test_gpu_ring.test_long_rings_match_oracle_and_the_build_that_waits_for_all_loads.pytestmark
+    ran = {p.kernel for rows, d, F in m_rows.args[1] for a, g in m_act.args[1] for p in L.record([L.ffn(sum(rows), len(rows), d, F, 8, g, act[a])])[0].launches}
+    assert {f"grouped_gemm_ring_long_kernel<8, {m}, 64>" for m in (0, 1, 3)} <= ran, ran
