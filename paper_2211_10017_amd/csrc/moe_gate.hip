@@ -655,10 +655,11 @@ static void launch_gate(const uint16_t *x, const uint16_t *wg, const float *bias
         else hipLaunchKernelGGL((gate_token_kernel<BF16, 64>), dim3(T), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
         return;
     }
-    // 33 to 64 experts else and up to four tokens per compute unit: four-token blocks on the matrix cores.  (64 experts, T = 64: 10.0 against
-    // 12.7 us for sixteen-token blocks at d = 1024, 25.8 against 28.0 us at d = 4096; T = 2048: 17.5 against 11.8 us.)  FP16 tokens,
-    // more than one such block and up to a token per compute unit: a lane per expert.  (48 experts, T = 16: 8.4 against 9.4 us, 21.0
-    // against 25.1; T = 300: 12.3 against 9.6; one token 7.6 against 7.3; bf16 9.2 against 9.4, 26.5 against 25.2.)
+    // 33 to 64 experts else (no multiple of eight, or more tokens) and up to four tokens per compute unit: four-token blocks on the matrix
+    // cores; FP16 tokens, more than one such block and up to a token per compute unit: a lane per expert.  (Lane per expert / four-token /
+    // sixteen-token blocks, warm, 36 to 60 experts, d = 1024: T = 1 7.4 / 7.1 / 9.5 us, 64 8.4 / 9.2 / 9.9, 300 11.9 / 9.2 / 10.2, 1000 20.5 / 9.3 / 10.1,
+    // 2000 37 / 15.9 / 10.1; d = 4096, T = 64 21.0 / 24.9 / 25.3; bf16 27.6 / 24.9 / 25.3.  Odd numbers of experts: one token 7.4 / 8.3 / 11.3,
+    // 2000 37 / 15.8 / 12.2.)
     if (E > 32 && E <= 64 && T <= 1024) {
         if (!BF16 && T > 4 && T <= 256)
             hipLaunchKernelGGL((gate_lanes_kernel<BF16, 1, WIDE, 1, 2>), dim3(T), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);

@@ -224,3 +224,24 @@ def test_the_oracle_comparisons_reach_every_long_ring():
     (m_act, m_rows) = test_gpu_ring.test_long_rings_match_oracle_and_the_build_that_waits_for_all_loads.pytestmark
     ran = {p.kernel for rows, d, F in m_rows.args[1] for a, g in m_act.args[1] for p in L.record([L.ffn(sum(rows), len(rows), d, F, 8, g, act[a])])[0].launches}
     assert {f"grouped_gemm_ring_long_kernel<8, {m}, 64>" for m in (0, 1, 3)} <= ran, ran
+
+
+def test_the_oracle_comparisons_reach_every_form_of_the_decode_kernel():
+    """Weight width, kind of scales, row type, slice width and sixteens of rows of the decode kernel, and the three reductions."""
+    import test_gpu_sliced as t
+
+    bf = {"f16": B.MOE_F16, "bf16": B.MOE_BF16}
+    marks = lambda f: [m.args[1] for m in f.pytestmark]  # noqa: E731
+    (loads, acts, sizes), (ts, wide_acts, wide), (rows, few) = (marks(f) for f in (t.test_sliced_ffn_matches_oracle, t.test_wide_slices_match_oracle,
+                                                                                   t.test_few_rows_over_few_and_many_slices_match_oracle))
+    calls = [L.sliced(T, k, E, d, F, b, g, bf[a]) for T, k, E, _ in loads for a, b, g in acts for d, F in sizes]
+    calls += [L.sliced(T, 2, 34, d, F, b, g, bf[a]) for T in ts for a, b, g in wide_acts for d, F in wide]
+    calls += [L.sliced(T, k, 5, d, F, 4) for T, k in rows for d, F in few]
+    ran = {p.kernel for c in L.record(calls) for p in c.launches}
+    flag = ("false", "true")
+    built = {f"decode_ffn_kernel<{b}, {flag[g]}, {flag[f]}, {cw}, {rt}>" for b in (4, 8) for g in (0, 1) for f in (0, 1) for cw in (1, 2, 4, 8) for rt in (1, 2)
+             if rt == 1 or (b == 4 and not f)}
+    built |= {"decode_reduce_kernel<16, 4>", "decode_reduce_kernel<8, 4>", "decode_reduce_kernel<4, 2>"}
+    assert built <= ran, built - ran
+    reduced = {c.launches[1].kernel for c in L.record([L.sliced(T, k, 5, d, F, 4) for T, k in rows for d, F in few])}
+    assert len(reduced) == 3

@@ -1,5 +1,6 @@
 """The gate's form for few tokens by 17 to 64 experts (a lane per expert, the weight in LDS 512 features at a time): short and odd
-feature counts, partly filled eights of experts' lanes, odd numbers of tokens, the largest batches it takes.  Bit for bit."""
+feature counts, partly filled eights of experts' lanes, odd numbers of tokens, the largest batches it takes.  The chosen experts are the
+oracle's; the logits are, bit for bit, those of the matrix-core form, whose order of additions is the contract's."""
 import numpy as np
 import pytest
 import torch
@@ -30,3 +31,11 @@ def test_gate_with_the_weight_in_lds_bit_exact(T, d, E, act):
         torch.cuda.synchronize()
         assert np.array_equal(gi.cpu().numpy(), oi)
         assert np.allclose(gs.cpu().numpy(), osc, rtol=1e-5, atol=1e-9)
+    # a batch too large for this form: renormalised scales of two experts come from their two logits alone
+    n = -(-1100 // T)
+    (call,) = L.record([L.gate(T * n, d, E, B._DT[TORCH_DT[act]])])
+    assert call.launches[0].kernel.startswith("gate_mfma_kernel")
+    bi, bs = B.moe_gate_topk(x.repeat(n, 1), wg, to_dev(bias, torch.float32), 2, True)
+    si, ss = B.moe_gate_topk(x, wg, to_dev(bias, torch.float32), 2, True)
+    torch.cuda.synchronize()
+    assert torch.equal(si.repeat(n, 1), bi) and torch.equal(ss.repeat(n, 1), bs)

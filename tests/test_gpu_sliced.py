@@ -15,10 +15,10 @@ pytestmark = pytest.mark.gpu
 
 
 def _routing(loads, T, k, E, rng):
-    """Expert of every assignment, distinct per token; -1 in `loads` means uniform, else the first expert takes that many tokens."""
-    idx = np.stack([rng.choice(E, size=k, replace=False) for _ in range(T)]).astype(np.int32)
-    if loads > 0:
-        idx[:loads] = np.stack([np.concatenate([[0], 1 + rng.choice(E - 1, size=k - 1, replace=False)]) if k > 1 else [0] for _ in range(loads)])
+    """Expert of every assignment, distinct per token: uniform for -1, else the first expert takes that many tokens and no others."""
+    first = min(max(loads, 0), T)
+    idx = np.stack([rng.choice(E, size=k, replace=False) if loads < 0 else 1 + rng.choice(E - 1, size=k, replace=False) for _ in range(T)]).astype(np.int32)
+    idx[:first, 0] = 0
     return idx
 
 
@@ -26,18 +26,34 @@ def _routing(loads, T, k, E, rng):
 @pytest.mark.parametrize("d,F", [(64, 64), (64, 320), (192, 1152), (768, 512), (1088, 1024), (2176, 640)])
 @pytest.mark.parametrize("act,bits,g", [("f16", 4, 0), ("f16", 8, 0), ("f16", 4, 64), ("f16", 8, 64), ("bf16", 4, 0), ("bf16", 8, 0), ("bf16", 4, 64),
                                         ("bf16", 8, 64)])
-@pytest.mark.parametrize("T,k,E,load", [(1, 1, 3, -1), (5, 2, 70, -1), (17, 2, 6, 17), (40, 2, 6, 33)])      # 17, 33 rows: two passes of sixteen, of 32
+@pytest.mark.parametrize("T,k,E,load", [(1, 1, 3, -1), (5, 2, 70, -1), (18, 2, 6, 17), (40, 2, 6, 33)])      # 17, 33 rows: one more than an item takes
 def test_sliced_ffn_matches_oracle(d, F, act, bits, g, T, k, E, load):
     _check(d, F, act, bits, g, T, k, E, load)
 
 
 # slices of 128, 256 and 512 channels, one and two sixteens of rows per pass
 @pytest.mark.parametrize("d,F", [(192, 1024), (64, 2048), (128, 4096)])
-@pytest.mark.parametrize("act,bits,g", [("f16", 4, 0), ("f16", 8, 0), ("f16", 4, 64), ("bf16", 8, 0), ("bf16", 4, 64)])
+@pytest.mark.parametrize("act,bits,g", [("f16", 4, 0), ("f16", 8, 0), ("f16", 4, 64), ("f16", 8, 64), ("bf16", 4, 0), ("bf16", 8, 0), ("bf16", 4, 64),
+                                        ("bf16", 8, 64)])
 @pytest.mark.parametrize("T", [60, 150])
 def test_wide_slices_match_oracle(d, F, act, bits, g, T):
     assert B.moe_grouped_ffn_wq_sliced_workspace_bytes(T, 2, 34, d, F, bits, g, TORCH_DT[act]) == T * 2 * d * 4 * 8       # eight slices
     _check(d, F, act, bits, g, T, 2, 34, 20 if T == 60 else 45)
+
+
+# groups of two and three units, one and two sixteens of rows per item
+@pytest.mark.parametrize("d,F,g", [(256, 1152, 128), (384, 1152, 192), (1152, 384, 192)])
+@pytest.mark.parametrize("act,bits", [("f16", 4), ("f16", 8), ("bf16", 4)])
+@pytest.mark.parametrize("T,E", [(30, 12), (90, 12)])
+def test_longer_groups_match_oracle(act, bits, d, F, g, T, E):
+    _check(d, F, act, bits, g, T, 2, E, 20)
+
+
+# the reduction by the number of slices: up to 8, up to 32, more
+@pytest.mark.parametrize("d,F", [(64, 512), (320, 576), (1088, 2048), (64, 2112), (1024, 4096), (1088, 4160)])
+@pytest.mark.parametrize("T,k", [(1, 2), (3, 1)])
+def test_few_rows_over_few_and_many_slices_match_oracle(d, F, T, k):
+    _check(d, F, "f16", 4, 0, T, k, 5, -1)
 
 
 # experts with far more rows than one item takes, beside experts with few or none; more experts than lanes, with spans of 5 and 64 experts
@@ -56,7 +72,7 @@ def _check(d, F, act, bits, g, T, k, E, load):
     (q1, o1), (q2, o2) = (oracle.quantize(m, bits, g) for m in w)
     idx = _routing(load, T, k, E, rng)
     if T > 4:
-        idx[3] = E                                               # a pruned token
+        idx[T - 1] = E                                           # a pruned token, none of the loaded ones
     scale = rng.uniform(0.1, 1.0, (T, k)).astype(np.float32)
     ob1, ob2 = ((rng.standard_normal((E, n)) * 0.1).astype(np.float16).astype(np.float32) for n in (F, d))
     bias = T != 5
@@ -64,6 +80,7 @@ def _check(d, F, act, bits, g, T, k, E, load):
     gelu = T == 40
     perm_src, inv_perm, off = oracle.permute(idx, E)
     active = int(off[E])
+    assert load < 0 or int(off[1]) == min(load, T - 1)
     y = np.zeros((T * k, d), dtype=np.float32)
     y[:active] = oracle.grouped_ffn(oracle.gather_rows(x.float().cpu().numpy(), perm_src[:active], k), off, q1, o1, q2, o2, g, ORC_DT[act],
                                     ob1 if bias else None, ob2 if bias else None, activation=int(gelu))

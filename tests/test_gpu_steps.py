@@ -527,14 +527,13 @@ def _routing(kind, T, k, E, rng):
 
 @pytest.mark.parametrize("T,k,E,d,F,bits,kind,extras", [
     (64, 2, 32, 1024, 4096, 4, "uniform", ""),                  # the decode workload's shape
-    (64, 2, 32, 1024, 4096, 4, "one_hot_expert", ""),           # 64 rows in one expert: four passes; the rest one or two rows
+    (64, 2, 32, 1024, 4096, 4, "one_hot_expert", ""),           # 64 rows in one expert: four blocks per slice; the rest one or two rows
     (30, 2, 32, 1024, 4096, 4, "few_experts", "pruned"),        # 27 experts without rows, pruned tokens
-    (64, 2, 32, 1024, 4096, 4, "few_experts", "pruned"),        # the same with four assignments per expert: the weights are requested
-                                                                # before the row counts are known, for 27 experts in vain
-    (128, 2, 80, 1024, 2048, 4, "uniform", ""),                 # early requests and 320 items: some workgroups take two
+    (64, 2, 32, 1024, 4096, 4, "few_experts", "pruned"),        # the same with four assignments per expert: two blocks per slice and expert
+    (128, 2, 80, 1024, 2048, 4, "uniform", ""),                 # more experts than lanes
     (64, 2, 32, 512, 2048, 8, "uniform", "bias gelu"),          # 8-bit weights, biases, GELU
     (1, 1, 64, 1024, 1024, 4, "uniform", ""),                   # a single row
-    (128, 2, 136, 1024, 1024, 4, "uniform", ""),                # 272 items: some workgroups take two
+    (128, 2, 136, 1024, 1024, 4, "uniform", ""),                # three experts per lane
     (50, 1, 16, 1024, 2048, 4, "one_hot_expert", "bias")])      # one expert per token, all fifty rows in one expert
 def test_decode_ffn_matches_oracle(T, k, E, d, F, bits, kind, extras):
     """Decode-sized batches with the gate scale fused in: one streaming launch (sort, fc1, activation, fc2 per
