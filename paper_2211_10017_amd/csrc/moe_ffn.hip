@@ -487,11 +487,11 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
     return round_up(decode_ffn_partial_bytes(T * k, d, F, decode_slice_width(T * k, E, F)), 256);
 }
 
-// Whether a layer should take the sliced call (steps in us of the routes below against it; 390 drawn sizes of up to 256 tokens, of
-// which the rule sends 80 % here: 1.4 times as fast on average, none slower):
-//  - up to eight assignments per expert: a pass takes sixteen rows, and experts with more stream their weights again (61 tokens, two of
+// Whether a layer should take the sliced call (steps in us of the routes below against it, uniform routing; of 700 sizes, most of them drawn where this
+// rule is in doubt, it takes two thirds, 1.36 times as fast on average; 22 of them are 2 to 13 % slower):
+//  - up to eight assignments per expert: a block takes sixteen rows, and experts with more stream their weights again (61 tokens, two of
 //    eight experts of 4096 x 16384 8-bit 188 and 318; 134 tokens on 16 of 512 x 2048 21.0 and 24.1; 5 per expert of 1024 x 4096 44 and 41).
-//    FP16 rows on 4-bit codes, whose passes then take thirty-two: up to sixteen, 150 MB of weights and a d_ff of twice d (192 tokens,
+//    FP16 rows on 4-bit codes, whose blocks then take thirty-two: up to sixteen, 150 MB of weights and a d_ff of twice d (192 tokens,
 //    two of 32 experts of 1024 x 4096 51.6 and 45.2, 144 on 16 39.7 and 32.0; 242 tokens, two of 32 of 2048 x 8192 130 and 143; 191 of 1536 x
 //    2048 42.6 and 43.5), with group scales twelve, 110 MB and four times d (71 tokens, two of 16 of 1024 x 4096 48.0 and 36.9; 154, two of 32
 //    51.6 and 52.3; 96, two of 16 of 2048 x 4096 55 and 58), but not where one and a bit blocks per compute unit would keep some busy
@@ -506,7 +506,7 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
 //    120 on 22 of 2048 x 1536 49 and 54; but 512 x 4096, 128 on 64, 63 and 56), from 180 MB on not for the longest rows (64 tokens on 8 of 4096 x
 //    4096 65 and 85), and fewer narrow slices (100 tokens, two of 67 of 512 x 2112, 2100 slices, 41 and 50).  Where row tiles run
 //    below, sliced at any of these sizes (60 tokens, two of 32 of 1088 x 4096 74 and 57, of 960 x 4096 61 and 52; 160, two of 128 of 512 x 2048 63 and 53);
-//  - FP16 rows with group scales, whose scales the ring multiplies into the weights, at any size (64 tokens, 64 experts of 4096 x 16384 809 and 711);
+//  - FP16 rows with group scales, whose scales the ring multiplies into the weights, at any size (64 tokens, 64 experts of 4096 x 16384 803 and 732);
 //  - wherever the gated call would run the decode kernel: it is the same one (128 tokens, two of 128 experts of 1024 x 4096, 460 MB, 104 in
 //    either call, 131 to 141 in row tiles; 60 on 8 22, where two streaming launches take 26).
 extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)

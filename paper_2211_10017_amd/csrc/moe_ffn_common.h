@@ -55,7 +55,7 @@ struct DecodeArgs {
     int g;                      // group size of the scales, 0 = per channel
     uint32_t group_inv;         // 2^32 / (g / 64), rounded up, 0 for groups of 64 (set by the launcher)
     int cw;                     // channels of d_ff per slice, in 64s: 1, 2, 4 or 8
-    int row_tiles;              // sixteens of rows per pass: 1 or 2 (set by the launcher)
+    int row_tiles;              // sixteens of rows per item: 1 or 2 (set by the launcher)
     const uint8_t *w1, *w2;     // packed codes
     const __half *s1, *s2;      // scales [E, d / g, F] / [E, F / g, d], one row per expert for channel scales
     const __half *b1, *b2;      // biases or null

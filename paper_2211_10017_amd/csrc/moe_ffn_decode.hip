@@ -16,7 +16,7 @@
 // block has run before: about 100 clocks per 64 bytes of code), 64 tokens, the weight stream and the unpacking beside it.  Small
 // blocks are dealt out as others end, so no compute unit's share is fixed, and one token's two experts of 1024 x 4096 are 128 blocks
 // over the chip: kernel and reduction 10.8 us where sixteen workgroups of sixteen wavefronts, one per slice of 512
-// channels, took 22; 64 tokens 34.6 against 33; a step of 64 tokens, 64 experts of 4096 x 16384, group scales, 809 -> 711 against two launches in
+// channels, took 22; 64 tokens 34.6 against 33; a step of 64 tokens, 64 experts of 4096 x 16384, group scales, 803 -> 732 against two launches in
 // row tiles.  Fewer registers beat longer rings (4-bit, FP16: 24 wavefronts per compute unit with two 1 KB blocks of fc1 and four of fc2
 // in flight 28.8 us, sixteen with six and eight 31.1), and two fc2 units at a time one (12 against 17 us for a block's 512 channels).
 //
@@ -44,7 +44,7 @@ namespace moe {
 
 constexpr int kDecWaves = 8;             // wavefronts per block
 constexpr int kDecThreads = kDecWaves * 64;
-constexpr int kDecFit = 16;              // rows of an expert per pass (one 16-row matrix tile)
+constexpr int kDecFit = 16;              // rows of an item (one 16-row matrix tile)
 
 typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t dec_u32x4 __attribute__((ext_vector_type(4)));
@@ -169,7 +169,7 @@ __device__ inline void dec_write_index(const DecodeArgs &p, int32_t *s_key, int 
 }
 
 // BITS: weight width.  GROUPED: group scales (groups of a multiple of 64 K values).  BF: bf16 rows.  CW: 64-channel parts of a slice.
-// RT: sixteens of rows per pass.
+// RT: sixteens of rows per item.
 template <int BITS, bool GROUPED, bool BF, int CW, int RT>
 __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF && RT == 1 ? 6 : 4) void decode_ffn_kernel(DecodeArgs p)
 {
@@ -618,8 +618,8 @@ double decode_active_experts(int n_assign, int E)
 
 // Channels of d_ff per slice, in 64s: the widest slice that still gives every compute unit a block, give or take.  Narrow slices
 // spread few experts over the chip; each slice leaves a partial sum of every row behind, so wide ones move less.  (us a step, slices
-// of 64 / 128 / 256 / 512: 1 token, two of 32 experts of 1024 x 4096, 4-bit 17.6 / 20.6 / 24.6 / 33; 16 tokens 36 / 32 / 32 / 37.5; 64 tokens 54 /
-// 48 / 40 / 42; 80 tokens on 16 experts of 4096 x 16384, group scales 357 / 281 / 264 / 227.  Over 390 drawn sizes this rule is 2 %
+// of 64 / 128 / 256 / 512: 1 token, two of 32 experts of 1024 x 4096, 4-bit 15.2 / 17.8 / 22.4 / 31.2; 16 tokens 31.5 / 30.7 / 30.5 / 34.6; 64 tokens 49.4 /
+// 42.4 / 35.4 / 38.0; 80 tokens on 16 experts of 4096 x 16384, group scales 357 / 281 / 264 / 227.  Over 390 drawn sizes this rule is 2 %
 // slower than the best width of each, at most 17 %.)
 int decode_slice_width(int n_assign, int E, int F)
 {
@@ -639,7 +639,7 @@ int launch_decode_ffn(const DecodeArgs &q, int bits, bool bf, hipStream_t s)
 {
     DecodeArgs p = q;
     const uint32_t units = p.g ? p.g / 64 : 1;
-    // two sixteens of rows per pass where experts are expected to have more than eight, FP16 rows on 4-bit codes: with fewer the second
+    // two sixteens of rows per item where experts are expected to have more than eight, FP16 rows on 4-bit codes: with fewer the second
     // sixteen's products are idle, with wider codes or rows it takes the registers that loads in flight need
     p.row_tiles = p.n_assign > 8 * p.E && bits == 4 && !bf ? 2 : 1;
     p.group_inv = units > 1 ? (uint32_t)(((1ull << 32) + units - 1) / units) : 0;

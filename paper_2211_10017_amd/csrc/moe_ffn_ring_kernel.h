@@ -1,13 +1,13 @@
 // Grouped GEMM with fused dequantisation for launches with few rows per expert or few row tiles (Sec. 3.3,
 // Sec. 3.4): the packed weights, the group scales and the activation rows all go from memory straight
-// into a ring of two to four LDS stages, up to three K steps ahead.
+// into a ring of two to five LDS stages, up to four K steps ahead.
 //
 // Such a launch is bound by how many bytes it keeps in flight (few rows per expert: it streams weights), or, with
 // about one tile per compute unit, by the latency of what a lone wavefront per SIMD waits for.  Loads into
 // registers can be one or two steps ahead at most (moe_ffn_tiled_kernel.h); loads into LDS need no registers,
 // are counted by hand, and NST - 1 stages of them stay in flight: three with 16-row blocks (two with 8-bit weights and group scales), two
 // with taller ones, one with 64-row blocks of 8-bit weights, whose stage is 32 KB of the 80 KB that two blocks per compute unit
-// leave each (three or four where a block has the compute unit to itself, see ring_long).  The K range is split over the two pairs of wavefronts of the block, whose partial tiles meet in LDS at the end, added
+// leave each (three or four in the long kernel, where a block has the compute unit to itself, see ring_long).  The K range is split over the two pairs of wavefronts of the block, whose partial tiles meet in LDS at the end, added
 // in the order of K: twice the blocks, each with half the chain of K steps.
 //
 // Block: 2 x 2 wavefronts; wavefront (wc, kp) computes BM rows x 64 channels over the kp-th half of K.  A stage
