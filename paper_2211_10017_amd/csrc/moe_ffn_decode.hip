@@ -25,6 +25,8 @@
 // at about the same time.  (As passes of one block they left most of a crowded batch's chip idle: 64 tokens on two of 64 experts of 4096 x 16384,
 // group scales, 383 -> 133 us a step, 143 in row tiles; on two of 32 of 1024 x 4096, bf16, 78 -> 29 and 44; 192 on two 190 -> 43 and 40, on
 // four of 64 of 4096 x 16384, 64 tokens, 298 -> 197 and 184.  Even routing gains what a kernel without the loop has in registers: 0 to 3 %.)
+// Where items may have thirty-two rows those of up to sixteen run the code for sixteen: half the products, more of fc2 in flight (192 tokens,
+// two of 32 of 1024 x 4096, a third of them ended 43.1 -> 41.6, none 43.7 and 43.9; 71, two of 16, group scales 32.7 -> 28.0).
 // The weights go through the magic-number conversion into the B operand.  Group scales multiply the fp32 sums of 64 K values of exact
 // codes.  bf16 rows are scaled per row and 64 K values by a power of two into the FP16 range (exact), and so is the slice of
 // h per row, after its rounding to bf16.
@@ -169,14 +171,13 @@ __device__ inline void dec_write_index(const DecodeArgs &p, int32_t *s_key, int 
 }
 
 // BITS: weight width.  GROUPED: group scales (groups of a multiple of 64 K values).  BF: bf16 rows.  CW: 64-channel parts of a slice.
-// RT: sixteens of rows per item.
-template <int BITS, bool GROUPED, bool BF, int CW, int RT>
-__global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF && RT == 1 ? 6 : 4) void decode_ffn_kernel(DecodeArgs p)
+// MOST: sixteens of rows per item at most; with two, items of up to sixteen rows run the code for one.
+template <int BITS, bool GROUPED, bool BF, int CW, int MOST>
+__global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF && MOST == 1 ? 6 : 4) void decode_ffn_kernel(DecodeArgs p)
 {
     constexpr int NW = BITS / 4;                        // fragment blocks of a slab per 64 K values (a "unit")
     constexpr int KP = kDecWaves / CW, CH = 64 * CW;    // parts of K in fc1; channels of the slice
-    constexpr int U2 = RT > 1 && GROUPED ? 2 : 4;           // units of fc2 in flight per wavefront (and one of fc1)
-    constexpr int FIT = kDecFit * RT;
+    constexpr int FIT = kDecFit * MOST;
     constexpr int LDR = CH + 4, LDH = CH + 8;
     __shared__ __align__(16) float s_red[KP * kDecFit * LDR];
     __shared__ __align__(16) uint16_t s_h[FIT * LDH];
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF && RT == 
     __syncthreads();
     if ((uint32_t)v_exp < (uint32_t)E) atomicAdd(&s_cnt[v_exp], 1);
     __syncthreads();
-    int e, count, z0;
+    int e, rows, z0;
     {
         int item = (int)(blockIdx.x - 1) / S, first = 0;
         auto find = [&](int cnt) {                      // the lane that holds the item; `item` becomes its number there
@@ -225,279 +226,284 @@ __global__ __launch_bounds__(kDecThreads, BITS == 4 && !GROUPED && !BF && RT == 
         }
         e = __builtin_amdgcn_readfirstlane(first + src);
         z0 = __builtin_amdgcn_readfirstlane(item) * FIT;
-        count = __builtin_amdgcn_readfirstlane(s_cnt[e]);
+        rows = min(FIT, __builtin_amdgcn_readfirstlane(s_cnt[e]) - z0);
     }
 
     MOE_DEC_STAMP(1);
-    // ---- weight streams
-    const uint32_t lane_off = (uint32_t)lane * 16u;
-    const int cg = wave % CW, kp = wave / CW;
-    const int nk = d / 64, per = (nk + KP - 1) / KP, u0 = kp * per, n1 = max(min(nk - u0, per), 0);
-    const int ktot = F / 64;                            // units of a slab of W2
-    const int nslab = d / 32, spw = (nslab + kDecWaves - 1) / kDecWaves, slab0 = wave * spw;
-    const int n2 = max(min(nslab - slab0, spw), 0) * CW;
-    const uint8_t *w1 = p.w1 + (size_t)e * packed_bytes_per_expert(d, F, BITS) + ((size_t)(c * CW + cg) * 2 * nk + u0) * NW * kFragBytes;
-    const uint8_t *w2 = p.w2 + (size_t)e * packed_bytes_per_expert(F, d, BITS) + ((size_t)slab0 * ktot + c * CW) * NW * kFragBytes;
-    const uint16_t *s1 = reinterpret_cast<const uint16_t *>(p.s1) + (size_t)e * (GROUPED ? d / p.g : 1) * F + c * CH;
-    const uint16_t *s2 = reinterpret_cast<const uint16_t *>(p.s2) + (size_t)e * (GROUPED ? F / p.g : 1) * d + slab0 * 32;
+    auto run = [&](auto rt_c) __attribute__((always_inline)) {
+        constexpr int RT = decltype(rt_c)::value;           // sixteens of rows of this item
+        constexpr int U2 = RT > 1 && GROUPED ? 2 : 4;       // units of fc2 in flight per wavefront (and one of fc1)
+        // ---- weight streams
+        const uint32_t lane_off = (uint32_t)lane * 16u;
+        const int cg = wave % CW, kp = wave / CW;
+        const int nk = d / 64, per = (nk + KP - 1) / KP, u0 = kp * per, n1 = max(min(nk - u0, per), 0);
+        const int ktot = F / 64;                            // units of a slab of W2
+        const int nslab = d / 32, spw = (nslab + kDecWaves - 1) / kDecWaves, slab0 = wave * spw;
+        const int n2 = max(min(nslab - slab0, spw), 0) * CW;
+        const uint8_t *w1 = p.w1 + (size_t)e * packed_bytes_per_expert(d, F, BITS) + ((size_t)(c * CW + cg) * 2 * nk + u0) * NW * kFragBytes;
+        const uint8_t *w2 = p.w2 + (size_t)e * packed_bytes_per_expert(F, d, BITS) + ((size_t)slab0 * ktot + c * CW) * NW * kFragBytes;
+        const uint16_t *s1 = reinterpret_cast<const uint16_t *>(p.s1) + (size_t)e * (GROUPED ? d / p.g : 1) * F + c * CH;
+        const uint16_t *s2 = reinterpret_cast<const uint16_t *>(p.s2) + (size_t)e * (GROUPED ? F / p.g : 1) * d + slab0 * 32;
 
-    auto group_of = [&](int u) { return p.group_inv ? (int)__umulhi((uint32_t)u, p.group_inv) : u; };      // unit -> group
-    uint4 W[2][NW], A[RT][2], V[U2][NW];
-    uint16_t gs1, gs2[GROUPED ? U2 : 1];        // group scales: lane l brings channel l of the wavefront's 64, l % 32 of the slab's 32
-    auto load_w1 = [&](int u) {
+        auto group_of = [&](int u) { return p.group_inv ? (int)__umulhi((uint32_t)u, p.group_inv) : u; };      // unit -> group
+        uint4 W[2][NW], A[RT][2], V[U2][NW];
+        uint16_t gs1, gs2[GROUPED ? U2 : 1];        // group scales: lane l brings channel l of the wavefront's 64, l % 32 of the slab's 32
+        auto load_w1 = [&](int u) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+            for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int w = 0; w < NW; ++w) W[s][w] = dec_load(w1 + ((size_t)s * nk + u) * NW * kFragBytes + w * kFragBytes, u < n1, lane_off);
-        if constexpr (GROUPED) gs1 = __builtin_amdgcn_raw_buffer_load_b16(dec_rsrc(s1 + (size_t)group_of(u0 + u) * F + cg * 64, u < n1 ? 128 : 0), lane * 2, 0, 0);
-    };
-    auto load_w2 = [&](int slot, int j) {
-        const int slab = j / CW, unit = j % CW;
+                for (int w = 0; w < NW; ++w) W[s][w] = dec_load(w1 + ((size_t)s * nk + u) * NW * kFragBytes + w * kFragBytes, u < n1, lane_off);
+            if constexpr (GROUPED) gs1 = __builtin_amdgcn_raw_buffer_load_b16(dec_rsrc(s1 + (size_t)group_of(u0 + u) * F + cg * 64, u < n1 ? 128 : 0), lane * 2, 0, 0);
+        };
+        auto load_w2 = [&](int slot, int j) {
+            const int slab = j / CW, unit = j % CW;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) V[slot][w] = dec_load(w2 + ((size_t)slab * ktot + unit) * NW * kFragBytes + w * kFragBytes, j < n2, lane_off);
-        if constexpr (GROUPED) {
-            gs2[slot] = __builtin_amdgcn_raw_buffer_load_b16(dec_rsrc(s2 + (size_t)group_of(c * CW + unit) * d + slab * 32, j < n2 ? 64 : 0), (lane & 31) * 2, 0, 0);
-        }
-    };
-    // (the weights depend on the expert alone: the rows are found under their flight)
-    load_w1(0);
-#pragma unroll
-    for (int i = 0; i < U2; ++i) load_w2(i, i);
-    __builtin_amdgcn_sched_barrier(0);
-    // ---- the item's rows, in the order of the assignments: blocks of other slices and of the expert's other items share them out alike
-    const bool mine = v_exp == e;
-    const uint64_t wave_rows = __ballot(mine);
-    if (lane == 0) s_wave[wave] = __popcll(wave_rows);
-    __syncthreads();
-    if (mine) {
-        int r = __popcll(wave_rows & ((1ull << lane) - 1)) - z0;
-        for (int w = 0; w < wave; ++w) r += s_wave[w];
-        if ((uint32_t)r < (uint32_t)FIT) s_row[r] = tid;
-    }
-    // channel factors of the thread's part of h: row tid / 32, 2 CW channels
-    constexpr int HC = 2 * CW;
-    const int h_row = tid >> 5, h_ch = (tid & 31) * HC;
-    uint32_t hs[CW], hb[CW];
-    auto load_factors = [&]() {
-#pragma unroll
-        for (int i = 0; i < CW; ++i) {
-            hs[i] = GROUPED ? 0 : reinterpret_cast<const uint32_t *>(s1 + h_ch)[i];
-            hb[i] = p.b1 ? reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint16_t *>(p.b1) + (size_t)e * F + c * CH + h_ch)[i] : 0;
-        }
-    };
-    if constexpr (CW <= 2) load_factors();              // (wider slices have no registers to carry them through fc1)
-    __syncthreads();
-    const int rows = min(FIT, count - z0);
-    MOE_DEC_STAMP(2);
-    const uint32_t x_bytes = (uint32_t)(p.n_assign >> (p.gate_k - 1)) * d * 2u;
-    const int lane16 = (lane & 15) * 4, lane_row = (lane >> 4) * 16;     // byte offsets of dec_lane
-    // k octet this lane's quarter of the wavefront reads within a 32-deep step (see swap_rows)
-    const int koct = ((lane >> 4) & 1) * 16 + (lane >> 5) * 8;
-    // rows of x in operand order: only the lanes of live rows read (the others are past the tokens, which reads as zero)
-    uint32_t a_off[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const int m = 16 * rt + (lane & 15), tok = s_row[min(m, rows - 1)] >> (p.gate_k - 1);      // one or two experts per token
-        a_off[rt] = m < rows ? ((uint32_t)tok * d + koct) * 2u : 0x7fffff00u;
-    }
-    auto load_a = [&](int u) {
-        const __amdgpu_buffer_rsrc_t r = dec_rsrc(p.x + (u0 + u) * 64, u < n1 ? x_bytes - (u0 + u) * 128 : 0);
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const dec_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, a_off[rt] + 64 * q, 0, 0);
-                A[rt][q] = make_uint4(v.x, v.y, v.z, v.w);
+            for (int w = 0; w < NW; ++w) V[slot][w] = dec_load(w2 + ((size_t)slab * ktot + unit) * NW * kFragBytes + w * kFragBytes, j < n2, lane_off);
+            if constexpr (GROUPED) {
+                gs2[slot] = __builtin_amdgcn_raw_buffer_load_b16(dec_rsrc(s2 + (size_t)group_of(c * CW + unit) * d + slab * 32, j < n2 ? 64 : 0), (lane & 31) * 2, 0, 0);
             }
-    };
-    load_a(0);
-
-    // ---- fc1: the rows x 64 channels over the wavefront's part of K
-    float4_t acc[4][RT];
-    auto clear = [&](float4_t (&t)[RT]) {
+        };
+        // (the weights depend on the expert alone: the rows are found under their flight)
+        load_w1(0);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) t[rt] = float4_t{0.f, 0.f, 0.f, 0.f};
-    };
-#pragma unroll
-    for (int t = 0; t < 4; ++t) clear(acc[t]);
-    for (int u = 0; u < n1; ++u) {
-        float up[RT];
-        if constexpr (BF) {
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                uint32_t amax = 0;
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].x), A[rt][q].y);
-                    amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].z), A[rt][q].w);
-                }
-                float down;
-                dec_row_pow(dec_max_over_rows(amax), down, up[rt]);
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    A[rt][q] = make_uint4(dec_bf16_pair_to_f16(A[rt][q].x, down), dec_bf16_pair_to_f16(A[rt][q].y, down),
-                                          dec_bf16_pair_to_f16(A[rt][q].z, down), dec_bf16_pair_to_f16(A[rt][q].w, down));
-            }
-        }
-        if constexpr (GROUPED || BF) {              // the unit's sums, folded with its factors in fp32
-#pragma unroll
-            for (int t = 0; t < 4; t += 2) {        // (one slab, then the other)
-                float4_t part[2][RT];
-                clear(part[0]), clear(part[1]);
-                dec_mac<BITS, RT>(W[t / 2], A, part[0], part[1]);
-                float sf[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) sf[i] = GROUPED ? dec_lane((float)__builtin_bit_cast(_Float16, gs1), lane16, 16 * (t + i)) : 1.0f;
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float pw = BF ? dec_lane(up[rt], lane_row, r) : 1.0f;
-#pragma unroll
-                        for (int i = 0; i < 2; ++i) acc[t + i][rt][r] = fmaf(part[i][rt][r], sf[i] * pw, acc[t + i][rt][r]);
-                    }
-                if (RT > 1) __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-            dec_mac<BITS, RT>(W[0], A, acc[0], acc[1]);
-            dec_mac<BITS, RT>(W[1], A, acc[2], acc[3]);
-        }
-        load_w1(u + 1);
-        load_a(u + 1);
+        for (int i = 0; i < U2; ++i) load_w2(i, i);
         __builtin_amdgcn_sched_barrier(0);
-    }
-    MOE_DEC_STAMP(3);
-    if constexpr (CW > 2) load_factors();
-    // ---- the parts of K meet, sixteen rows at a time: rows 16 rt + 4 (lane / 16) + r, channels 64 cg + 16 t + lane % 16
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        if (rt) __syncthreads();                    // the sixteen rows before have been read
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) s_red[(kp * kDecFit + 4 * (lane >> 4) + r) * LDR + cg * 64 + 16 * t + (lane & 15)] = acc[t][rt][r];
+        // ---- the item's rows, in the order of the assignments: blocks of other slices and of the expert's other items share them out alike
+        const bool mine = v_exp == e;
+        const uint64_t wave_rows = __ballot(mine);
+        if (lane == 0) s_wave[wave] = __popcll(wave_rows);
         __syncthreads();
-        float v[HC];
-#pragma unroll
-        for (int i = 0; i < HC; ++i) v[i] = s_red[h_row * LDR + h_ch + i];
-#pragma unroll
-        for (int q = 1; q < KP; ++q)
-#pragma unroll
-            for (int i = 0; i < HC; ++i) v[i] += s_red[(q * kDecFit + h_row) * LDR + h_ch + i];
-        uint32_t amax = 0;
-#pragma unroll
-        for (int i = 0; i < HC; ++i) {
-            const half2_t s2v = bits_h2(hs[i >> 1]), b2v = bits_h2(hb[i >> 1]);
-            v[i] = fmaf(v[i], GROUPED ? 1.0f : (float)s2v[i & 1], (float)b2v[i & 1]);
+        if (mine) {
+            int r = __popcll(wave_rows & ((1ull << lane) - 1)) - z0;
+            for (int w = 0; w < wave; ++w) r += s_wave[w];
+            if ((uint32_t)r < (uint32_t)FIT) s_row[r] = tid;
         }
-        if (p.act == MOE_ACT_GELU) {
+        // channel factors of the thread's part of h: row tid / 32, 2 CW channels
+        constexpr int HC = 2 * CW;
+        const int h_row = tid >> 5, h_ch = (tid & 31) * HC;
+        uint32_t hs[CW], hb[CW];
+        auto load_factors = [&]() {
 #pragma unroll
-            for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_GELU);
-        } else {
-#pragma unroll
-            for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_RELU);
-        }
-        if constexpr (BF) {
-            float down, up;
-#pragma unroll
-            for (int i = 0; i < HC; ++i) {
-                v[i] = __uint_as_float((uint32_t)to_bf16_rne(v[i]) << 16);
-                amax = max(amax, (__float_as_uint(v[i]) >> 16) & 0x7fffu);
+            for (int i = 0; i < CW; ++i) {
+                hs[i] = GROUPED ? 0 : reinterpret_cast<const uint32_t *>(s1 + h_ch)[i];
+                hb[i] = p.b1 ? reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint16_t *>(p.b1) + (size_t)e * F + c * CH + h_ch)[i] : 0;
             }
+        };
+        if constexpr (CW <= 2) load_factors();              // (wider slices have no registers to carry them through fc1)
+        __syncthreads();
+        MOE_DEC_STAMP(2);
+        const uint32_t x_bytes = (uint32_t)(p.n_assign >> (p.gate_k - 1)) * d * 2u;
+        const int lane16 = (lane & 15) * 4, lane_row = (lane >> 4) * 16;     // byte offsets of dec_lane
+        // k octet this lane's quarter of the wavefront reads within a 32-deep step (see swap_rows)
+        const int koct = ((lane >> 4) & 1) * 16 + (lane >> 5) * 8;
+        // rows of x in operand order: only the lanes of live rows read (the others are past the tokens, which reads as zero)
+        uint32_t a_off[RT];
 #pragma unroll
-            for (int off = 16; off > 0; off >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, off));
-            dec_row_pow(amax, down, up);
-            if ((tid & 31) == 0) s_pow[16 * rt + h_row] = up;
-#pragma unroll
-            for (int i = 0; i < HC; ++i) v[i] *= down;
+        for (int rt = 0; rt < RT; ++rt) {
+            const int m = 16 * rt + (lane & 15), tok = s_row[min(m, rows - 1)] >> (p.gate_k - 1);      // one or two experts per token
+            a_off[rt] = m < rows ? ((uint32_t)tok * d + koct) * 2u : 0x7fffff00u;
         }
-#pragma unroll
-        for (int i = 0; i < HC; i += 2) {
-            const half2_t hv = {(_Float16)v[i], (_Float16)v[i + 1]};
-            *reinterpret_cast<uint32_t *>(s_h + (16 * rt + h_row) * LDH + h_ch + i) = h2_bits(hv);
-        }
-    }
-    __syncthreads();
-
-    MOE_DEC_STAMP(4);
-    // ---- fc2 on the slice: the rows x 32 output channels per slab, K = the slice's channels
-    const uint16_t *h_ptr = s_h + (lane & 15) * LDH + koct;
-    float *const part_c = p.partial + (size_t)c * p.n_assign * d + slab0 * 32;
-    int row_off[RT][4];
-    float pw[RT][4];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int m = 16 * rt + 4 * (lane >> 4) + r;
-            row_off[rt][r] = m < rows ? s_row[m] * d + (lane & 15) : -1;
-            pw[rt][r] = BF ? s_pow[m] : 1.0f;
-        }
-    float4_t y0[RT], y1[RT];
-    clear(y0), clear(y1);
-    auto read_h = [&](int unit, uint4 (&a)[RT][2]) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) a[rt][q] = *reinterpret_cast<const uint4 *>(h_ptr + 16 * rt * LDH + unit * 64 + 32 * q);
-    };
-    auto unit_mac = [&](int i, const uint4 (&a)[RT][2], float4_t (&lo)[RT], float4_t (&hi)[RT]) {
-        if constexpr (GROUPED) {
-            float4_t p0[RT], p1[RT];
-            clear(p0), clear(p1);
-            dec_mac<BITS, RT>(V[i], a, p0, p1);
-            const float sl = (float)__builtin_bit_cast(_Float16, gs2[i]), f0 = dec_lane(sl, lane16, 0), f1 = dec_lane(sl, lane16, 16);
+        auto load_a = [&](int u) {
+            const __amdgpu_buffer_rsrc_t r = dec_rsrc(p.x + (u0 + u) * 64, u < n1 ? x_bytes - (u0 + u) * 128 : 0);
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) lo[rt][r] = fmaf(p0[rt][r], f0, lo[rt][r]), hi[rt][r] = fmaf(p1[rt][r], f1, hi[rt][r]);
-        } else {
-            dec_mac<BITS, RT>(V[i], a, lo, hi);
+                for (int q = 0; q < 2; ++q) {
+                    const dec_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, a_off[rt] + 64 * q, 0, 0);
+                    A[rt][q] = make_uint4(v.x, v.y, v.z, v.w);
+                }
+        };
+        load_a(0);
+
+        // ---- fc1: the rows x 64 channels over the wavefront's part of K
+        float4_t acc[4][RT];
+        auto clear = [&](float4_t (&t)[RT]) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) t[rt] = float4_t{0.f, 0.f, 0.f, 0.f};
+        };
+#pragma unroll
+        for (int t = 0; t < 4; ++t) clear(acc[t]);
+        for (int u = 0; u < n1; ++u) {
+            float up[RT];
+            if constexpr (BF) {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    uint32_t amax = 0;
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].x), A[rt][q].y);
+                        amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].z), A[rt][q].w);
+                    }
+                    float down;
+                    dec_row_pow(dec_max_over_rows(amax), down, up[rt]);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        A[rt][q] = make_uint4(dec_bf16_pair_to_f16(A[rt][q].x, down), dec_bf16_pair_to_f16(A[rt][q].y, down),
+                                              dec_bf16_pair_to_f16(A[rt][q].z, down), dec_bf16_pair_to_f16(A[rt][q].w, down));
+                }
+            }
+            if constexpr (GROUPED || BF) {              // the unit's sums, folded with its factors in fp32
+#pragma unroll
+                for (int t = 0; t < 4; t += 2) {        // (one slab, then the other)
+                    float4_t part[2][RT];
+                    clear(part[0]), clear(part[1]);
+                    dec_mac<BITS, RT>(W[t / 2], A, part[0], part[1]);
+                    float sf[2];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) sf[i] = GROUPED ? dec_lane((float)__builtin_bit_cast(_Float16, gs1), lane16, 16 * (t + i)) : 1.0f;
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float pw = BF ? dec_lane(up[rt], lane_row, r) : 1.0f;
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) acc[t + i][rt][r] = fmaf(part[i][rt][r], sf[i] * pw, acc[t + i][rt][r]);
+                        }
+                    if (RT > 1) __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                dec_mac<BITS, RT>(W[0], A, acc[0], acc[1]);
+                dec_mac<BITS, RT>(W[1], A, acc[2], acc[3]);
+            }
+            load_w1(u + 1);
+            load_a(u + 1);
+            __builtin_amdgcn_sched_barrier(0);
         }
-    };
-    auto store = [&](int n, const float4_t (&lo)[RT], const float4_t (&hi)[RT]) {       // this slice's part of y, channels n .. n + 31
+        MOE_DEC_STAMP(3);
+        if constexpr (CW > 2) load_factors();
+        // ---- the parts of K meet, sixteen rows at a time: rows 16 rt + 4 (lane / 16) + r, channels 64 cg + 16 t + lane % 16
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            if (rt) __syncthreads();                    // the sixteen rows before have been read
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s_red[(kp * kDecFit + 4 * (lane >> 4) + r) * LDR + cg * 64 + 16 * t + (lane & 15)] = acc[t][rt][r];
+            __syncthreads();
+            float v[HC];
+#pragma unroll
+            for (int i = 0; i < HC; ++i) v[i] = s_red[h_row * LDR + h_ch + i];
+#pragma unroll
+            for (int q = 1; q < KP; ++q)
+#pragma unroll
+                for (int i = 0; i < HC; ++i) v[i] += s_red[(q * kDecFit + h_row) * LDR + h_ch + i];
+            uint32_t amax = 0;
+#pragma unroll
+            for (int i = 0; i < HC; ++i) {
+                const half2_t s2v = bits_h2(hs[i >> 1]), b2v = bits_h2(hb[i >> 1]);
+                v[i] = fmaf(v[i], GROUPED ? 1.0f : (float)s2v[i & 1], (float)b2v[i & 1]);
+            }
+            if (p.act == MOE_ACT_GELU) {
+#pragma unroll
+                for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_GELU);
+            } else {
+#pragma unroll
+                for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_RELU);
+            }
+            if constexpr (BF) {
+                float down, up;
+#pragma unroll
+                for (int i = 0; i < HC; ++i) {
+                    v[i] = __uint_as_float((uint32_t)to_bf16_rne(v[i]) << 16);
+                    amax = max(amax, (__float_as_uint(v[i]) >> 16) & 0x7fffu);
+                }
+#pragma unroll
+                for (int off = 16; off > 0; off >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, off));
+                dec_row_pow(amax, down, up);
+                if ((tid & 31) == 0) s_pow[16 * rt + h_row] = up;
+#pragma unroll
+                for (int i = 0; i < HC; ++i) v[i] *= down;
+            }
+#pragma unroll
+            for (int i = 0; i < HC; i += 2) {
+                const half2_t hv = {(_Float16)v[i], (_Float16)v[i + 1]};
+                *reinterpret_cast<uint32_t *>(s_h + (16 * rt + h_row) * LDH + h_ch + i) = h2_bits(hv);
+            }
+        }
+        __syncthreads();
+
+        MOE_DEC_STAMP(4);
+        // ---- fc2 on the slice: the rows x 32 output channels per slab, K = the slice's channels
+        const uint16_t *h_ptr = s_h + (lane & 15) * LDH + koct;
+        float *const part_c = p.partial + (size_t)c * p.n_assign * d + slab0 * 32;
+        int row_off[RT][4];
+        float pw[RT][4];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (row_off[rt][r] >= 0) {
-                    part_c[row_off[rt][r] + n] = BF ? lo[rt][r] * pw[rt][r] : lo[rt][r];
-                    part_c[row_off[rt][r] + n + 16] = BF ? hi[rt][r] * pw[rt][r] : hi[rt][r];
-                }
-    };
-    // two units at a time, whose chains of unpacking and products the wavefront interleaves: two slabs (slices of 64 channels)
-    // or two units of a slab
-    for (int base = 0; base < n2; base += U2) {
+            for (int r = 0; r < 4; ++r) {
+                const int m = 16 * rt + 4 * (lane >> 4) + r;
+                row_off[rt][r] = m < rows ? s_row[m] * d + (lane & 15) : -1;
+                pw[rt][r] = BF ? s_pow[m] : 1.0f;
+            }
+        float4_t y0[RT], y1[RT];
+        clear(y0), clear(y1);
+        auto read_h = [&](int unit, uint4 (&a)[RT][2]) {
 #pragma unroll
-        for (int i = 0; i < U2; i += 2) {
-            const int j = base + i, unit = CW == 1 ? 0 : U2 % CW == 0 ? i % CW : j % CW;
-            if (j < n2) {
-                uint4 a0[RT][2];
-                read_h(unit, a0);
-                if constexpr (CW == 1) {
-                    float4_t z0v[RT], z1v[RT];
-                    clear(y0), clear(y1), clear(z0v), clear(z1v);
-                    unit_mac(i, a0, y0, y1);
-                    unit_mac(i + 1, a0, z0v, z1v);
-                    store(j * 32, y0, y1);
-                    if (j + 1 < n2) store(j * 32 + 32, z0v, z1v);
-                } else {
-                    uint4 a1[RT][2];
-                    read_h(unit + 1, a1);
-                    unit_mac(i, a0, y0, y1);
-                    unit_mac(i + 1, a1, y0, y1);
-                    if (unit == CW - 2) {
-                        store(j / CW * 32, y0, y1);
-                        clear(y0), clear(y1);
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) a[rt][q] = *reinterpret_cast<const uint4 *>(h_ptr + 16 * rt * LDH + unit * 64 + 32 * q);
+        };
+        auto unit_mac = [&](int i, const uint4 (&a)[RT][2], float4_t (&lo)[RT], float4_t (&hi)[RT]) {
+            if constexpr (GROUPED) {
+                float4_t p0[RT], p1[RT];
+                clear(p0), clear(p1);
+                dec_mac<BITS, RT>(V[i], a, p0, p1);
+                const float sl = (float)__builtin_bit_cast(_Float16, gs2[i]), f0 = dec_lane(sl, lane16, 0), f1 = dec_lane(sl, lane16, 16);
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) lo[rt][r] = fmaf(p0[rt][r], f0, lo[rt][r]), hi[rt][r] = fmaf(p1[rt][r], f1, hi[rt][r]);
+            } else {
+                dec_mac<BITS, RT>(V[i], a, lo, hi);
+            }
+        };
+        auto store = [&](int n, const float4_t (&lo)[RT], const float4_t (&hi)[RT]) {       // this slice's part of y, channels n .. n + 31
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (row_off[rt][r] >= 0) {
+                        part_c[row_off[rt][r] + n] = BF ? lo[rt][r] * pw[rt][r] : lo[rt][r];
+                        part_c[row_off[rt][r] + n + 16] = BF ? hi[rt][r] * pw[rt][r] : hi[rt][r];
+                    }
+        };
+        // two units at a time, whose chains of unpacking and products the wavefront interleaves: two slabs (slices of 64 channels)
+        // or two units of a slab
+        for (int base = 0; base < n2; base += U2) {
+#pragma unroll
+            for (int i = 0; i < U2; i += 2) {
+                const int j = base + i, unit = CW == 1 ? 0 : U2 % CW == 0 ? i % CW : j % CW;
+                if (j < n2) {
+                    uint4 a0[RT][2];
+                    read_h(unit, a0);
+                    if constexpr (CW == 1) {
+                        float4_t z0v[RT], z1v[RT];
+                        clear(y0), clear(y1), clear(z0v), clear(z1v);
+                        unit_mac(i, a0, y0, y1);
+                        unit_mac(i + 1, a0, z0v, z1v);
+                        store(j * 32, y0, y1);
+                        if (j + 1 < n2) store(j * 32 + 32, z0v, z1v);
+                    } else {
+                        uint4 a1[RT][2];
+                        read_h(unit + 1, a1);
+                        unit_mac(i, a0, y0, y1);
+                        unit_mac(i + 1, a1, y0, y1);
+                        if (unit == CW - 2) {
+                            store(j / CW * 32, y0, y1);
+                            clear(y0), clear(y1);
+                        }
                     }
                 }
+                load_w2(i, j + U2);
+                load_w2(i + 1, j + 1 + U2);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            load_w2(i, j + U2);
-            load_w2(i + 1, j + 1 + U2);
-            __builtin_amdgcn_sched_barrier(0);
         }
-    }
-    MOE_DEC_STAMP(5);
+        MOE_DEC_STAMP(5);
+    };
+    if (MOST > 1 && rows > kDecFit) run(std::integral_constant<int, MOST>{});
+    else run(std::integral_constant<int, 1>{});
 }
 
 // Sum of the d_ff slices and of a token's experts: out[t] = sum_j scale[a] * (W2-scale * sum_c partial[c][a] + b2),
