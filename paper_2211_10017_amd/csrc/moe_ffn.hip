@@ -506,7 +506,11 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
 //    120 on 22 of 2048 x 1536 49 and 54; but 512 x 4096, 128 on 64, 63 and 56), from 180 MB on not for the longest rows (64 tokens on 8 of 4096 x
 //    4096 65 and 85), and fewer narrow slices (100 tokens, two of 67 of 512 x 2112, 2100 slices, 41 and 50).  Where row tiles run
 //    below, sliced at any of these sizes (60 tokens, two of 32 of 1088 x 4096 74 and 57, of 960 x 4096 61 and 52; 160, two of 128 of 512 x 2048 63 and 53);
-//  - FP16 rows with group scales, whose scales the ring multiplies into the weights, at any size (64 tokens, 64 experts of 4096 x 16384 803 and 732);
+//  - FP16 rows with group scales, whose scales the ring multiplies into the weights, beyond 300 MB too (64 tokens, 64 experts of 4096 x 16384 803 and 732),
+//    but experts of more than 30 MB only up to five rows each: there little is left to gain (256 tokens, two of 64 of 4096 x 8192 480 and 459, 192
+//    482 and 439, 128 477 and 422; of 2048 x 8192 259 and 230) and crowded routing, whose blocks read an expert's weights for every sixteen rows, loses most (256 on two of
+//    4096 x 8192 137 and 214, 192 130 and 188, 128 115 and 127, on eight 195 and 297, 160 and 221, 150 and 188, by a gate of graded popularity
+//    391 and 420, 327 and 362, 258 and 288);
 //  - wherever the gated call would run the decode kernel: it is the same one (128 tokens, two of 128 experts of 1024 x 4096, 460 MB, 104 in
 //    either call, 131 to 141 in row tiles; 60 on 8 22, where two streaming launches take 26).
 extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
@@ -530,7 +534,7 @@ extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F,
                                moe_grouped_ffn_wq_indexed_pays(R, E, T, d, F, bits, group_size, act_dtype));
         if ((streams && d >= 1024 && bytes > 140e6) || (d >= 4096 && bytes > 180e6) || (cw == 1 && blocks > 1250)) return 0;
     }
-    return bytes <= 300e6 || (grouped && f16);
+    return bytes <= 300e6 || (grouped && f16 && (R <= 5L * E || (double)d * F * bits <= 120e6));
 }
 
 extern "C" int moe_grouped_ffn_wq_sliced(const void *x, int act_dtype, const int32_t *expert_idx, const float *expert_scale, int T, int k, int E,

@@ -245,3 +245,9 @@ def test_the_oracle_comparisons_reach_every_form_of_the_decode_kernel():
     assert built <= ran, built - ran
     reduced = {c.launches[1].kernel for c in L.record([L.sliced(T, k, 5, d, F, 4) for T, k in rows for d, F in few])}
     assert len(reduced) == 3
+
+
+def test_large_group_scaled_experts_with_many_rows_stay_in_row_tiles():
+    """Crowded routing would read their weights for every sixteen rows."""
+    assert not _pays(256, 2, 64, 4096, 8192, 4, 128) and not _pays(256, 2, 64, 4096, 16384, 4, 128) and not _pays(192, 2, 64, 4096, 8192, 4, 128)
+    assert _pays(160, 2, 64, 4096, 8192, 4, 128) and _pays(64, 2, 64, 4096, 16384, 4, 128) and _pays(256, 2, 64, 2048, 8192, 4, 128)
