@@ -46,7 +46,7 @@ enum {
     MOE_OK = 0,
     MOE_ERR_INVALID_ARG = 1,   /* null pointer, non-positive or misaligned dimension, k > E ... */
     MOE_ERR_UNSUPPORTED = 2,   /* bits not in {4,8}, unknown dtype, E above the supported range */
-    MOE_ERR_WORKSPACE = 3,     /* workspace missing or smaller than the query says */
+    MOE_ERR_WORKSPACE = 3,     /* workspace missing or too small (what the query says is enough) */
     MOE_ERR_HIP = 4            /* a launch failed (hipGetLastError) */
 };
 
