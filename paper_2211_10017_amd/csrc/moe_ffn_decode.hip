@@ -517,19 +517,45 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs p)
     const int t = blockIdx.x, S = p.F / (64 * p.cw), d = p.d;
     const int sg = threadIdx.x / LANES, ln = threadIdx.x % LANES, n = (blockIdx.y * LANES + ln) * 4;
     const bool in = n < d;
+    // the token's experts and what their rows of W2 are scaled with are requested with the slices: found after their sum they are two more
+    // trips to memory in a row
+    const int J = p.gate_k > 1 ? 2 : 1;
+    int e[2];
+    float sc[2];
+    uint2 s2[2], b2[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        e[j] = p.gate_idx[t * J + min(j, J - 1)];
+        sc[j] = p.gate_scale[t * J + min(j, J - 1)];
+    }
+    auto load_factors = [&]() {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (j >= J || (uint32_t)e[j] >= (uint32_t)p.E) e[j] = -1;      // (pruned: nothing of it was written)
+            s2[j] = make_uint2(0x3c003c00u, 0x3c003c00u), b2[j] = make_uint2(0, 0);
+            if (sg == 0 && in && e[j] >= 0) {
+                if (!p.g) s2[j] = *reinterpret_cast<const uint2 *>(p.s2 + (size_t)e[j] * d + n);       // (group scales are in the partial sums)
+                if (p.b2) b2[j] = *reinterpret_cast<const uint2 *>(p.b2 + (size_t)e[j] * d + n);
+            }
+        }
+    };
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float4 y[2] = {acc, acc};
     const float *src = p.partial + (size_t)t * p.gate_k * d + (in ? n : 0);     // (a token's rows of a slice are neighbours)
     const int second = p.gate_k > 1 ? d : 0;
     const size_t step = (size_t)p.n_assign * d;
-    for (int c = sg; c < S; c += NV * SG) {
+    for (int c = sg; c - sg < S; c += NV * SG) {
         float4 v[2][NV];
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const float *q = src + min(c + i * SG, S - 1) * step;
-            v[0][i] = *reinterpret_cast<const float4 *>(q);
-            v[1][i] = *reinterpret_cast<const float4 *>(q + second);
+            v[0][i] = v[1][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (c - sg + i * SG < S) {                  // (the same for the whole block)
+                const float *q = src + min(c + i * SG, S - 1) * step;
+                v[0][i] = *reinterpret_cast<const float4 *>(q);
+                v[1][i] = *reinterpret_cast<const float4 *>(q + second);
+            }
         }
+        if (c == sg) load_factors();
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -554,25 +580,12 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs p)
     if (!in) return;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        if (j >= p.gate_k) break;
-        const int a = t * p.gate_k + j, e = p.gate_idx[a];
-        if ((uint32_t)e >= (uint32_t)p.E) continue;     // (pruned: nothing of it was written)
-        const float sc = p.gate_scale[a];
-        float f[4] = {1.f, 1.f, 1.f, 1.f}, b[4] = {0.f, 0.f, 0.f, 0.f};
-        if (!p.g) {                             // channel scales (group scales are in the partial sums)
-            const uint2 s2 = *reinterpret_cast<const uint2 *>(p.s2 + (size_t)e * d + n);
-            const half2_t s01 = bits_h2(s2.x), s23 = bits_h2(s2.y);
-            f[0] = (float)s01[0]; f[1] = (float)s01[1]; f[2] = (float)s23[0]; f[3] = (float)s23[1];
-        }
-        if (p.b2) {
-            const uint2 bb = *reinterpret_cast<const uint2 *>(p.b2 + (size_t)e * d + n);
-            const half2_t b01 = bits_h2(bb.x), b23 = bits_h2(bb.y);
-            b[0] = (float)b01[0]; b[1] = (float)b01[1]; b[2] = (float)b23[0]; b[3] = (float)b23[1];
-        }
-        acc.x += sc * (y[j].x * f[0] + b[0]);
-        acc.y += sc * (y[j].y * f[1] + b[1]);
-        acc.z += sc * (y[j].z * f[2] + b[2]);
-        acc.w += sc * (y[j].w * f[3] + b[3]);
+        if (e[j] < 0) continue;
+        const half2_t s01 = bits_h2(s2[j].x), s23 = bits_h2(s2[j].y), b01 = bits_h2(b2[j].x), b23 = bits_h2(b2[j].y);
+        acc.x += sc[j] * (y[j].x * (float)s01[0] + (float)b01[0]);
+        acc.y += sc[j] * (y[j].y * (float)s01[1] + (float)b01[1]);
+        acc.z += sc[j] * (y[j].z * (float)s23[0] + (float)b23[0]);
+        acc.w += sc[j] * (y[j].w * (float)s23[1] + (float)b23[1]);
     }
     if (p.out_dtype == MOE_F32) {
         *reinterpret_cast<float4 *>((float *)p.out + (size_t)t * d + n) = acc;
