@@ -151,8 +151,9 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     // previous step) and tells that every wavefront has left the other stage, which is then
     // refilled at the end of the step, when its rows have had time to arrive; the arrival of
     // the rows is not waited for in front of a barrier.
-    auto k_step = [&](int kb, auto slot_c, auto live_c) {
+    auto k_step = [&](int kb, auto slot_c, auto live_c, auto window_c) {
         constexpr int SL = decltype(slot_c)::value;      // = kb & 1: LDS stage and weight register set
+        constexpr bool WINDOW = decltype(window_c)::value;
         constexpr int LIVE = decltype(live_c)::value;    // row tiles of this block that hold rows
         uint16_t *stage = lds_a[SL];
         // this wavefront's share of the stage has landed once only the weight refills issued after
@@ -186,9 +187,17 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
         };
 
         // unpack + convert one 16-deep step of weight fragments in registers
+        ScaledCodes<BITS> factors[kTN];
+        if constexpr (WINDOW)
+#pragma unroll
+            for (int t = 0; t < kTN; ++t) factors[t] = ScaledCodes<BITS>(sc[t]);
         auto dequant_step = [&](int j, uint32_t (&bw)[kTN][4], uint32_t (&bl)[kTN][4]) {
 #pragma unroll
             for (int t = 0; t < kTN; ++t) {
+                if constexpr (WINDOW) {
+                    factors[t].convert(raw[t] + j * NW, bw[t]);
+                    continue;
+                }
                 if (BITS == 4) dequant4(raw[t][j], bw[t]);
                 else dequant8(raw[t][2 * j], raw[t][2 * j + 1], bw[t]);
                 if (SMODE == SCALE_GROUP) {
@@ -271,23 +280,61 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
             }
         }
     };
+    // Group scales with the multiply and the subtraction of the code's offset in one instruction (ScaledCodes): an accumulator
+    // column, which is a lane's channel, is kept in units of a power of two that brings the channel's first scale to the middle
+    // of what that conversion takes, and a wavefront that meets a scale outside of it goes on in the general loop.
+    constexpr bool WINDOWED = SMODE == SCALE_GROUP && PF == 2;
+    int unit[kTN] = {};
     // The K loop exists once per number of live row tiles (the last tile of an expert usually
     // holds few rows): a run-time test inside the loop would cut the MFMA stream into pieces.
-    auto k_loop = [&](auto live_c) {
-        for (int kb = 0; kb < nk; kb += 2) {
+    // Returns the K step that it stopped at.
+    auto k_loop = [&](int kb, auto live_c, auto window_c) {
+        for (; kb < nk; kb += 2) {
             take(std::integral_constant<int, 0>{});
             if constexpr (PF == 2) take(std::integral_constant<int, PF - 1>{});
-            k_step(kb, std::integral_constant<int, 0>{}, live_c);
+            if constexpr (decltype(window_c)::value) {
+                bool in = true;
+#pragma unroll
+                for (int s = 0; s < PF; ++s)
+#pragma unroll
+                    for (int t = 0; t < kTN; ++t) {
+                        sc2[s][t] = __builtin_amdgcn_ldexph(sc2[s][t], unit[t]);
+                        in &= scale_in_window(sc2[s][t]);
+                    }
+                if (!__all(in)) break;
+            }
+            k_step(kb, std::integral_constant<int, 0>{}, live_c, window_c);
             if (kb + 1 < nk) {
                 if constexpr (PF == 1) take(std::integral_constant<int, 0>{});
-                k_step(kb + 1, std::integral_constant<int, 1>{}, live_c);
+                k_step(kb + 1, std::integral_constant<int, 1>{}, live_c, window_c);
             }
         }
+        return kb;
     };
-    if (TM == 1 || live == TM) k_loop(std::integral_constant<int, TM>{});
-    else if (TM >= 4 && live == 3) k_loop(std::integral_constant<int, 3>{});
-    else if (TM >= 2 && live == 2) k_loop(std::integral_constant<int, 2>{});
-    else k_loop(std::integral_constant<int, 1>{});
+    const std::integral_constant<bool, WINDOWED> windowed;
+    int kb = 0;
+    if constexpr (WINDOWED)
+#pragma unroll
+        for (int t = 0; t < kTN; ++t) unit[t] = window_unit(gs[0][t]);
+    if (TM == 1 || live == TM) kb = k_loop(kb, std::integral_constant<int, TM>{}, windowed);
+    else if (TM >= 4 && live == 3) kb = k_loop(kb, std::integral_constant<int, 3>{}, windowed);
+    else if (TM >= 2 && live == 2) kb = k_loop(kb, std::integral_constant<int, 2>{}, windowed);
+    else kb = k_loop(kb, std::integral_constant<int, 1>{}, windowed);
+    if constexpr (WINDOWED) {
+        if (kb < nk) {                                 // (row tiles that hold no rows come along: what is read for them is never stored)
+#pragma unroll
+            for (int m = 0; m < TM; ++m)
+#pragma unroll
+                for (int t = 0; t < kTN; ++t) {
+                    const float back = __builtin_ldexpf(1.0f, kWindowShift - unit[t]);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[m][t][i] *= back;
+                }
+#pragma unroll
+            for (int t = 0; t < kTN; ++t) unit[t] = kWindowShift;
+            k_loop(kb, std::integral_constant<int, TM>{}, std::false_type{});
+        }
+    }
     wait_loads<0>();      // the last step's (unused) refill of the other stage must land before the block's LDS is given up
 
     // ---- epilogue: acc[m][t][i] is row 32*m + 8*(i/4) + 4*(lane/32) + i%4 of the tile, channel lane%32 of tile t
@@ -298,7 +345,8 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     if constexpr (TM == 4) load_channels();
 #pragma unroll
     for (int t = 0; t < kTN; ++t) {
-        cs[t] = SMODE == SCALE_CHANNEL ? __shfl(cs_lane, 32 * t + (lane & 31)) : SMODE == SCALE_GROUP_SPLIT ? 1.0f / 256.0f : 1.0f;
+        cs[t] = SMODE == SCALE_CHANNEL ? __shfl(cs_lane, 32 * t + (lane & 31)) : SMODE == SCALE_GROUP_SPLIT ? 1.0f / 256.0f
+              : WINDOWED ? __builtin_ldexpf(1.0f, kWindowShift - unit[t]) : 1.0f;
         bias[t] = __shfl(bias_lane, 32 * t + (lane & 31));
     }
     finish_tile<TM, 16, BM>(p, acc, tile_rows, cs, bias, rows, 0, ntile0 * 32, lds_raw + wave * kPatchBytes<16>);
