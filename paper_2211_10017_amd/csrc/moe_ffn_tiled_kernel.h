@@ -93,6 +93,10 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     // scale in fp32.  Exact like the two-term form, at half its MFMA count; needs the registers of a
     // second accumulator set, so it is built for row tiles of at most 64 rows.
     constexpr bool ACC = SMODE == SCALE_GROUP_ACC;
+    // 4-bit codes that go in unscaled are taken the same way, as q 2^-9 (2^24 itself is no FP16 number), which the factor at the end makes up for:
+    // two-operand masks instead of v_and_or_b32 with three registers.  4096 bf16 tokens, two of 16 experts of 2048 x 8192, a step 554 -> 552 us, 16384 of
+    // 1024 x 4096 557 -> 555; bf16 with groups of 128, 4096 x 16384, 4601 -> 4583.
+    constexpr bool EXACT4 = BITS == 4 && (SMODE == SCALE_CHANNEL || ACC);
     static_assert(!ACC || TM <= 2, "two accumulator sets fit for TM <= 2 only");
     float16_t accg[ACC ? TM : 1][kTN];
 
@@ -188,13 +192,13 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
 
         // unpack + convert one 16-deep step of weight fragments in registers
         ScaledCodes<BITS> factors[kTN];
-        if constexpr (WINDOW)
+        if constexpr (WINDOW || EXACT4)
 #pragma unroll
-            for (int t = 0; t < kTN; ++t) factors[t] = ScaledCodes<BITS>(sc[t]);
+            for (int t = 0; t < kTN; ++t) factors[t] = ScaledCodes<BITS>(EXACT4 ? (_Float16)32768.0f : sc[t]);
         auto dequant_step = [&](int j, uint32_t (&bw)[kTN][4], uint32_t (&bl)[kTN][4]) {
 #pragma unroll
             for (int t = 0; t < kTN; ++t) {
-                if constexpr (WINDOW) {
+                if constexpr (WINDOW || EXACT4) {
                     factors[t].convert(raw[t] + j * NW, bw[t]);
                     continue;
                 }
@@ -271,7 +275,7 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
         if constexpr (ACC && SL == 1) {                 // end of the group: acc += scale * accg
 #pragma unroll
             for (int t = 0; t < kTN; ++t) {
-                const float sf = (float)sc[t];
+                const float sf = (float)sc[t] * (EXACT4 ? 512.0f : 1.0f);
 #pragma unroll
                 for (int m = 0; m < TM; ++m)
                     if (m < LIVE)
@@ -345,7 +349,7 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     if constexpr (TM == 4) load_channels();
 #pragma unroll
     for (int t = 0; t < kTN; ++t) {
-        cs[t] = SMODE == SCALE_CHANNEL ? __shfl(cs_lane, 32 * t + (lane & 31)) : SMODE == SCALE_GROUP_SPLIT ? 1.0f / 256.0f
+        cs[t] = SMODE == SCALE_CHANNEL ? __shfl(cs_lane, 32 * t + (lane & 31)) * (EXACT4 ? 512.0f : 1.0f) : SMODE == SCALE_GROUP_SPLIT ? 1.0f / 256.0f
               : WINDOWED ? __builtin_ldexpf(1.0f, kWindowShift - unit[t]) : 1.0f;
         bias[t] = __shfl(bias_lane, 32 * t + (lane & 31));
     }
