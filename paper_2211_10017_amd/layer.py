@@ -136,7 +136,7 @@ class MoEExpertLayer:
         opt = lambda t: 0 if t is None else t.data_ptr()  # noqa: E731
         key = (x.data_ptr(), opt(finished), self.w1_packed.data_ptr(), self.w2_packed.data_ptr(), self.s1.data_ptr(),
                self.s2.data_ptr(), self.wg.data_ptr(), opt(self.gate_bias), opt(self.b1), opt(self.b2),
-               torch.cuda.current_stream().cuda_stream)
+               B.current_stream_handle())
         calls = self._plans.get(key)
         if calls is None:
             calls = self._plans[key] = self._marshal(x, finished, key[-1])
