@@ -274,7 +274,8 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     // activations and group scales the weights go in as an exact two-term FP16 sum, because h
     // is rounded to 8 bits afterwards and a 2^-11 weight rounding would show through.
     GemmArgs g1{};
-    g1.a = (const uint16_t *)x_perm; g1.row_pow = bf ? pow_x : nullptr; g1.offsets = expert_offsets;
+    const bool convert = bf && (grouped || !bf16_codes_pay(R, perm_src ? R / k : R, E, d, F, bits));
+    g1.a = (const uint16_t *)x_perm; g1.a_bf16 = bf && !convert; g1.row_pow = convert ? pow_x : nullptr; g1.offsets = expert_offsets;
     g1.wq = (const uint8_t *)w1_packed; g1.scales = (const __half *)s1; g1.bias = (const __half *)b1;
     g1.out = h; g1.E = E; g1.R = R; g1.K = d; g1.N = F; g1.g = grouped ? group_size : d;
     g1.out_dtype = act_dtype; g1.act = activation;
@@ -284,7 +285,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
         g1.perm_src_out = perm_src_out; g1.inv_perm_out = inv_perm_out; g1.offsets_out = offsets_out;
         if (expert_scale) { g1.zero_out = (float *)y_perm; g1.zero_count = (long)(R / k) * d; }   // fc2 adds into it
     }
-    if (bf) {           // bf16 rows: converted to power-of-two scaled FP16 rows first, then the GEMM of FP16 rows
+    if (convert) {      // bf16 rows of group-scaled or large layers: converted to power-of-two scaled FP16 rows first, then the GEMM of FP16 rows
         uint16_t *x16 = (uint16_t *)(wsb + ws.x16_off);
         // (through the routing index: every token's row once, R / k of them)
         int rc = rows_to_f16((const uint16_t *)x_perm, x16, perm_src ? R / k : R, d, pow_x, s);
@@ -298,7 +299,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
 
     // fc2: y = h @ deq(W2) + b2
     GemmArgs g2 = g1;
-    g2.a = (const uint16_t *)h; g2.row_pow = bf ? pow_h : nullptr;
+    g2.a = (const uint16_t *)h; g2.row_pow = convert ? pow_h : nullptr;
     g2.wq = (const uint8_t *)w2_packed; g2.scales = (const __half *)s2; g2.bias = (const __half *)b2;
     g2.out = y_perm; g2.K = F; g2.N = d; g2.g = grouped ? group_size : F;
     g2.out_dtype = y_dtype; g2.act = MOE_ACT_NONE;
@@ -309,7 +310,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     } else if (expert_scale) {
         g2.out_dst = perm_src; g2.out_scale = expert_scale;
     }
-    if (bf) {           // h, which fc1 rounded to bf16 (A13), in place
+    if (convert) {      // h, which fc1 rounded to bf16 (A13), in place
         rc = rows_to_f16((const uint16_t *)h, (uint16_t *)h, R, F, pow_h, s);
         if (rc) return rc;
     }

@@ -13,7 +13,8 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 enum { SCALE_CHANNEL = 0, SCALE_GROUP = 1, SCALE_GROUP_SPLIT = 2, SCALE_GROUP_ACC = 3 };
 
 struct GemmArgs {
-    const uint16_t *a;        // [R, K] fp16 bit patterns (rows that were bf16 come converted, scaled by 2^-p per row)
+    const uint16_t *a;        // [R, K] fp16 bit patterns (rows that were bf16 come converted, scaled by 2^-p per row, or as they are: a_bf16)
+    int a_bf16;               // row tiles, channel scales: the rows are bf16 and meet the codes, exact in bf16, in bf16 matrix instructions
     const float2 *row_pow;    // null, or per row (2^-p, 2^p): the tiled kernel multiplies its output rows by 2^p
     const int32_t *offsets;   // [E+1]
     const uint8_t *wq;        // packed codes, [E] x packed_bytes_per_expert
@@ -75,6 +76,7 @@ int launch_decode_ffn(const DecodeArgs &p, int bits, bool bf, hipStream_t s);
 constexpr int kGatedMaxAssign = 256;    // assignments the fused permutation takes: one per thread of a block
 
 int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s);
+bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits);
 void launch_tiled_4(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);
 void launch_tiled_4_exact(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);
 void launch_tiled_8(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);
@@ -223,6 +225,29 @@ struct ScaledCodes {
     }
 };
 
+// Eight codes as exact bf16 numbers, for rows that come as bf16: q for 8-bit codes, 16 q for 4-bit ones (a signed byte whose upper four bits are
+// the code).  There is no packed bf16 arithmetic, so every code is converted on its own, 14 or 15 instructions for eight instead of 8 or 9;
+// what that saves is a pass over the rows of x and of h to bring them to scaled FP16, a launch and a read and write each.
+template <int BITS>
+__device__ inline void codes_to_bf16(const uint32_t *w, uint32_t out[4])
+{
+    uint32_t v[2];
+    if constexpr (BITS == 4) {
+        v[0] = ((w[0] << 4) & 0xf0f0f0f0u) ^ 0x80808080u;      // codes 0, 4, 1, 5
+        v[1] = (w[0] & 0xf0f0f0f0u) ^ 0x80808080u;             // codes 2, 6, 3, 7
+    } else {
+        v[0] = w[0] ^ 0x80808080u;
+        v[1] = w[1] ^ 0x80808080u;
+    }
+    auto value = [&](int q, int byte) { return __float_as_uint((float)(int8_t)(v[q] >> (8 * byte))); };
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t lo = BITS == 4 ? value(q & 1, q >> 1) : value(q >> 1, 2 * (q & 1));
+        const uint32_t hi = BITS == 4 ? value(q & 1, 2 + (q >> 1)) : value(q >> 1, 2 * (q & 1) + 1);
+        out[q] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+    }
+}
+
 // The same conversions with the chip's integer-to-float instructions instead of the magic
 // number (the variant Sec. 3.4.1 measured as too slow on its hardware): extract the code, convert
 // to fp32, remove the offset, round to FP16.  Exact, like the magic-number route.
@@ -255,6 +280,16 @@ __device__ inline half8_t frag_from(const uint32_t w[4])
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
     u4 v = {w[0], w[1], w[2], w[3]};
     return __builtin_bit_cast(half8_t, v);
+}
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+
+// 32 rows x 32 channels x 16 K values of FP16 or bf16 operands
+template <bool BF16>
+__device__ inline float16_t tile_product(half8_t a, half8_t b, float16_t c)
+{
+    if constexpr (BF16) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
 __device__ inline uint16_t to_bf16_rne(float f)

@@ -133,8 +133,9 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) part[m][t][i] = 0.0f;
 
-    auto compute = [&](int slot, bool last_of_group, auto live_c) {
+    auto compute = [&](int slot, bool last_of_group, auto live_c, auto bf_c) {
         constexpr int LIVE = decltype(live_c)::value;               // row tiles of this block that hold rows
+        constexpr bool BF = decltype(bf_c)::value;                  // bf16 rows, channel scales
         const uint8_t *st = lds + slot * S::kStage;
         const uint16_t *sa = reinterpret_cast<const uint16_t *>(st + kp * S::kPartA);
         const uint8_t *sb = st + WK * S::kPartA + wave * S::kWaveB;
@@ -159,7 +160,8 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 uint32_t bw[4];
-                if (BITS == 4) dequant4(raw[t][j], bw);
+                if constexpr (BF) codes_to_bf16<BITS>(raw[t] + j * NW, bw);
+                else if (BITS == 4) dequant4(raw[t][j], bw);
                 else dequant8(raw[t][2 * j], raw[t][2 * j + 1], bw);
                 if constexpr (SMODE == SCALE_GROUP) {
                     const half2_t s2 = {sc[t], sc[t]};
@@ -172,7 +174,7 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
                     if constexpr (ACC) {
                         part[m][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[m], frag_from(bw), part[m][t], 0, 0, 0);
                     } else {
-                        acc[m][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[m], frag_from(bw), acc[m][t], 0, 0, 0);
+                        acc[m][t] = tile_product<BF>(a[m], frag_from(bw), acc[m][t]);
                     }
                 }
             }
@@ -202,7 +204,7 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
 #pragma unroll
     for (int s = 0; s < D; ++s)
         if (s < per) issue(s, s);
-    auto k_loop = [&](auto live_c) {
+    auto k_loop = [&](auto live_c, auto bf_c) {
         int slot = 0;
         for (int s = 0; s < per; ++s) {
             const int rem = min(per - 1 - s, D - 1);
@@ -212,12 +214,16 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
             else wait_loads<0>();
             __syncthreads();
             if (s + D < per) issue(s + D, slot == 0 ? NST - 1 : slot - 1);
-            if (s < mine) compute(slot, s + 1 == mine || (first + s + 1) * 64 % p.g == 0, live_c);
+            if (s < mine) compute(slot, s + 1 == mine || (first + s + 1) * 64 % p.g == 0, live_c, bf_c);
             slot = slot + 1 == NST ? 0 : slot + 1;
         }
     };
-    if (TM == 1 || rows > 32) k_loop(std::integral_constant<int, TM>{});
-    else k_loop(std::integral_constant<int, 1>{});
+    auto part_of_k = [&](auto bf_c) {
+        if (TM == 1 || rows > 32) k_loop(std::integral_constant<int, TM>{}, bf_c);
+        else k_loop(std::integral_constant<int, 1>{}, bf_c);
+    };
+    if (!GROUPED && p.a_bf16) part_of_k(std::integral_constant<bool, !GROUPED>{});
+    else part_of_k(std::false_type{});
 
     // ---- the K parts meet: every wavefront leaves its partial tiles in LDS and finishes registers
     // [QN kp, QN kp + QN) of each tile of its channels
@@ -225,7 +231,7 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
     float cs[2], bias[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        cs[t] = __shfl(cs_lane, 32 * t + (lane & 31));
+        cs[t] = __shfl(cs_lane, 32 * t + (lane & 31)) * (BITS == 4 && p.a_bf16 ? 1.0f / 16.0f : 1.0f);      // (4-bit codes go in as 16 q)
         bias[t] = __shfl(bias_lane, 32 * t + (lane & 31));
     }
     __syncthreads();                                    // every wavefront is done with the ring

@@ -49,6 +49,37 @@ static bool ring_long(const GemmArgs &p, int bm)
     return (long)p.E * p.K * p.N >= 18000000l && expected_row_tiles(p.R, p.E, bm) * ((p.N + 127) / 128) <= (p.E > 1 ? 250 : 256);
 }
 
+// 32-row tiles of a register-fed block.
+// 64-row tiles also for taller experts where a third block per CU pays more than halving the
+// dequantisation does: short K loops (the prologue and epilogue of a block then overlap the loops of
+// two others, not of one), and 8-bit weights up to 256 rows per expert (their 128-row tile has
+// registers for one set of weights in flight only)
+static int tile_height(const GemmArgs &p, int bits, int mean)
+{
+    return mean <= 32 ? 1 : (mean <= 64 || p.K <= 2048 || (bits == 8 && mean <= 256)) ? 2 : 4;
+}
+
+// Whether bf16 rows of a channel-scaled layer meet bf16 codes as they are (codes_to_bf16) instead of being converted to scaled FP16 ahead of
+// each GEMM.  Converting costs two launches, 8 us, and reads and writes x and h at 5 TB/s; bf16 codes cost six vector instructions more for eight
+// of them, 22 us per 1e9 over the chip, every time a row tile converts them, of which about 0.8 shows, with 8-bit weights, whose launches read twice
+// as much, 0.45.  (us a step, converted / as they are.  1000 tokens, one of 64 experts of 512 x 2048 45.1 / 39.7; 997, two of 16 of 768 x 3072, 8-bit, 70.2 / 65.5; 16384, one of
+// 64 of 1024 x 4096 380 / 338; 5000, two of 128 333 / 317; 4096, two of 16 of 2048 x 8192 576 / 567, 8-bit 687 / 658; 2500, two of 64, 8-bit 706 / 699.  Left to the
+// conversion: 1000, two of 32 of 2048 x 8192 240 / 251, 2500, two of 64 536 / 553; 2000, two of 16 of 4096 x 16384, 8-bit 1353 / 1388, 8192, two of 64 4091 / 4099.)
+bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits)
+{
+    GemmArgs p{};
+    p.E = E, p.R = R;
+    const int mean = (R + E - 1) / E;
+    double codes = 0;
+    for (int fc = 0; fc < 2; ++fc) {
+        p.K = fc ? F : d, p.N = fc ? d : F;
+        const int ring = ring_rows(p, bits, mean);
+        codes += expected_row_tiles(R, E, ring ? ring : 32 * tile_height(p, bits, mean)) * p.K * p.N;
+    }
+    const double moved = 4.0 * ((double)R * F + (double)tokens * d);
+    return codes * 22e-9 * (bits == 8 ? 0.45 : 0.8) <= 8.0 + moved / 5e6;
+}
+
 int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
 {
     // row-tile height from the mean rows per expert (the offsets themselves stay on the device)
@@ -64,11 +95,7 @@ int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
         (bits == 4 ? launch_ring_4 : launch_ring_8)(q, smode, bm, dim3((unsigned)wgs), s);
         return check_launch("moe_grouped_ffn_wq (gemm)");
     }
-    // 64-row tiles also for taller experts where a third block per CU pays more than halving the
-    // dequantisation does: short K loops (the prologue and epilogue of a block then overlap the loops of
-    // two others, not of one), and 8-bit weights up to 256 rows per expert (their 128-row tile has
-    // registers for one set of weights in flight only)
-    int tm = mean <= 32 ? 1 : (mean <= 64 || p.K <= 2048 || (bits == 8 && mean <= 256)) ? 2 : 4;
+    int tm = tile_height(p, bits, mean);
     if (smode == SCALE_GROUP_ACC && tm > 2) tm = 2;
     const long most = p.R;                                      // experts that can hold rows
     const long ncol = (p.N + 255) / 256;
