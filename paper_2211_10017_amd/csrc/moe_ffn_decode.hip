@@ -28,8 +28,9 @@
 // Where items may have thirty-two rows those of up to sixteen run the code for sixteen: half the products, more of fc2 in flight (192 tokens,
 // two of 32 of 1024 x 4096, a third of them ended 43.1 -> 41.6, none 43.7 and 43.9; 71, two of 16, group scales 32.7 -> 28.0).
 // The weights go through the magic-number conversion into the B operand.  Group scales multiply the fp32 sums of 64 K values of exact
-// codes.  bf16 rows are scaled per row and 64 K values by a power of two into the FP16 range (exact), and so is the slice of
-// h per row, after its rounding to bf16.
+// codes.  bf16 rows, and the slice of h rounded to bf16, are operands as they are: the codes are exact in bf16 too (codes_to_bf16).  (Scaled per row and 64
+// K values to FP16 before, with searches for each row's largest: 64 tokens, two of 32 of 1024 x 4096 39.9 -> 39.0 us a step, 100, two of 32 of 512 x 2048 20.9 -> 20.2,
+// 20, two of 32 of 2048 x 8192 118 -> 114; same bits.)
 #include <math.h>
 
 #include <type_traits>
@@ -89,62 +90,42 @@ __device__ inline void swap_rows(uint32_t &a, uint32_t &b)
 
 // RT x 16 rows x 32 channels x 64 K values: one fragment block of 4-bit or two of 8-bit weights, a[] the two 32-deep operands of
 // each sixteen rows.
-template <int BITS, int RT>
+template <int BITS, int RT, bool BF16>
 __device__ inline void dec_mac(const uint4 (&w)[BITS / 4], const uint4 (&a)[RT][2], float4_t (&lo)[RT], float4_t (&hi)[RT])
 {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         auto products = [&](const uint32_t (&bw)[4], float4_t (&acc)[RT]) {
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a[rt][q]), frag_from(bw), acc[rt], 0, 0, 0);
+            for (int rt = 0; rt < RT; ++rt) {
+                if constexpr (BF16) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a[rt][q]), __builtin_bit_cast(bf16x8_t, frag_from(bw)), acc[rt], 0, 0, 0);
+                else acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a[rt][q]), frag_from(bw), acc[rt], 0, 0, 0);
+            }
         };
         uint32_t bw[4];
+        auto convert = [&](uint32_t c0, uint32_t c1) {
+            const uint32_t c[2] = {c0, c1};
+            if constexpr (BF16) codes_to_bf16<BITS>(c, bw);
+            else if constexpr (BITS == 4) dequant4(c0, bw);
+            else dequant8(c0, c1, bw);
+        };
         if constexpr (BITS == 4) {
             uint32_t r0 = q ? w[0].z : w[0].x, r1 = q ? w[0].w : w[0].y;
             swap_rows(r0, r1);
-            dequant4(r0, bw);
+            convert(r0, 0);
             products(bw, lo);
-            dequant4(r1, bw);
+            convert(r1, 0);
             products(bw, hi);
         } else {
             uint32_t r0 = w[q].x, r1 = w[q].y, r2 = w[q].z, r3 = w[q].w;
             swap_rows(r0, r2);
             swap_rows(r1, r3);
-            dequant8(r0, r1, bw);
+            convert(r0, r1);
             products(bw, lo);
-            dequant8(r2, r3, bw);
+            convert(r2, r3);
             products(bw, hi);
         }
     }
-}
-
-// Power of two that brings a bf16 magnitude `amax` (bits, sign cleared) into [2^14, 2^15), and its reciprocal.
-__device__ inline void dec_row_pow(uint32_t amax, float &down, float &up)
-{
-    int ex = (int)(amax >> 7);
-    if (ex == 255) ex = 141;                            // inf/nan: factor 1 (the result is nan anyway)
-    const int fe = min(max(268 - ex, 1), 253);
-    down = __uint_as_float((uint32_t)fe << 23);
-    up = __uint_as_float((uint32_t)(254 - fe) << 23);
-}
-
-__device__ inline uint32_t dec_max_bf16(uint32_t amax, uint32_t pair)
-{
-    return max(amax, max(pair & 0x7fffu, (pair >> 16) & 0x7fffu));
-}
-
-// The same wavefront-wide for values that sixteen-lane rows share: maximum over lanes l, l ^ 16, l ^ 32, l ^ 48.
-__device__ inline uint32_t dec_max_over_rows(uint32_t v)
-{
-    v = max(v, (uint32_t)__shfl_xor((int)v, 16));
-    return max(v, (uint32_t)__shfl_xor((int)v, 32));
-}
-
-__device__ inline uint32_t dec_bf16_pair_to_f16(uint32_t pair, float down)
-{
-    const half2_t h = {(_Float16)__builtin_fmaf(__uint_as_float(pair << 16), down, 0.0f),
-                       (_Float16)__builtin_fmaf(__uint_as_float(pair & 0xffff0000u), down, 0.0f)};
-    return h2_bits(h);
 }
 
 // The stable sort by expert, for the callers: perm_src, inv_perm and expert_offsets (pruned rows, key E, come last).  One block;
@@ -179,11 +160,11 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && !BF && MOST == 1 && (BITS 
     constexpr int KP = kDecWaves / CW, CH = 64 * CW;    // parts of K in fc1; channels of the slice
     constexpr int FIT = kDecFit * MOST;
     constexpr int LDR = CH + 4, LDH = CH + 8;
+    constexpr float UNIT = BF && BITS == 4 ? 0.0625f : 1.0f;             // (4-bit codes are 16 q in bf16)
     __shared__ __align__(16) float s_red[KP * kDecFit * LDR];
     __shared__ __align__(16) uint16_t s_h[FIT * LDH];
     __shared__ __align__(16) int32_t s_row[kDecMaxAssign];      // assignments of the block's expert
     __shared__ int s_wave[kDecWaves];                           // rows of the expert among each wavefront's assignments
-    __shared__ float s_pow[FIT];
     int *const s_cnt = reinterpret_cast<int *>(s_red);          // rows of every expert, until fc1's sums need the place
     static_assert(sizeof(s_red) >= kDecMaxExperts * sizeof(int), "the experts' counters fit");
 
@@ -295,7 +276,7 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && !BF && MOST == 1 && (BITS 
         __syncthreads();
         MOE_DEC_STAMP(2);
         const uint32_t x_bytes = (uint32_t)(p.n_assign >> (p.gate_k - 1)) * d * 2u;
-        const int lane16 = (lane & 15) * 4, lane_row = (lane >> 4) * 16;     // byte offsets of dec_lane
+        const int lane16 = (lane & 15) * 4;     // byte offset of dec_lane
         // k octet this lane's quarter of the wavefront reads within a 32-deep step (see swap_rows)
         const int koct = ((lane >> 4) & 1) * 16 + (lane >> 5) * 8;
         // rows of x in operand order: only the lanes of live rows read (the others are past the tokens, which reads as zero)
@@ -326,46 +307,26 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && !BF && MOST == 1 && (BITS 
 #pragma unroll
         for (int t = 0; t < 4; ++t) clear(acc[t]);
         for (int u = 0; u < n1; ++u) {
-            float up[RT];
-            if constexpr (BF) {
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) {
-                    uint32_t amax = 0;
-#pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].x), A[rt][q].y);
-                        amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].z), A[rt][q].w);
-                    }
-                    float down;
-                    dec_row_pow(dec_max_over_rows(amax), down, up[rt]);
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        A[rt][q] = make_uint4(dec_bf16_pair_to_f16(A[rt][q].x, down), dec_bf16_pair_to_f16(A[rt][q].y, down),
-                                              dec_bf16_pair_to_f16(A[rt][q].z, down), dec_bf16_pair_to_f16(A[rt][q].w, down));
-                }
-            }
-            if constexpr (GROUPED || BF) {              // the unit's sums, folded with its factors in fp32
+            if constexpr (GROUPED || BF) {              // the unit's sums, folded with the group's scale in fp32 (bf16: short sums, as h keeps few bits)
 #pragma unroll
                 for (int t = 0; t < 4; t += 2) {        // (one slab, then the other)
                     float4_t part[2][RT];
                     clear(part[0]), clear(part[1]);
-                    dec_mac<BITS, RT>(W[t / 2], A, part[0], part[1]);
+                    dec_mac<BITS, RT, BF>(W[t / 2], A, part[0], part[1]);
                     float sf[2];
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) sf[i] = GROUPED ? dec_lane((float)__builtin_bit_cast(_Float16, gs1), lane16, 16 * (t + i)) : 1.0f;
+                    for (int i = 0; i < 2; ++i) sf[i] = GROUPED ? dec_lane((float)__builtin_bit_cast(_Float16, gs1) * UNIT, lane16, 16 * (t + i)) : 1.0f;
 #pragma unroll
                     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const float pw = BF ? dec_lane(up[rt], lane_row, r) : 1.0f;
+                        for (int r = 0; r < 4; ++r)
 #pragma unroll
-                            for (int i = 0; i < 2; ++i) acc[t + i][rt][r] = fmaf(part[i][rt][r], sf[i] * pw, acc[t + i][rt][r]);
-                        }
+                            for (int i = 0; i < 2; ++i) acc[t + i][rt][r] = GROUPED ? fmaf(part[i][rt][r], sf[i], acc[t + i][rt][r]) : part[i][rt][r] + acc[t + i][rt][r];
                     if (RT > 1) __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
-                dec_mac<BITS, RT>(W[0], A, acc[0], acc[1]);
-                dec_mac<BITS, RT>(W[1], A, acc[2], acc[3]);
+                dec_mac<BITS, RT, false>(W[0], A, acc[0], acc[1]);
+                dec_mac<BITS, RT, false>(W[1], A, acc[2], acc[3]);
             }
             load_w1(u + 1);
             load_a(u + 1);
@@ -389,11 +350,10 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && !BF && MOST == 1 && (BITS 
             for (int q = 1; q < KP; ++q)
 #pragma unroll
                 for (int i = 0; i < HC; ++i) v[i] += s_red[(q * kDecFit + h_row) * LDR + h_ch + i];
-            uint32_t amax = 0;
 #pragma unroll
             for (int i = 0; i < HC; ++i) {
                 const half2_t s2v = bits_h2(hs[i >> 1]), b2v = bits_h2(hb[i >> 1]);
-                v[i] = fmaf(v[i], GROUPED ? 1.0f : (float)s2v[i & 1], (float)b2v[i & 1]);
+                v[i] = fmaf(v[i], GROUPED ? 1.0f : (float)s2v[i & 1] * UNIT, (float)b2v[i & 1]);
             }
             if (p.act == MOE_ACT_GELU) {
 #pragma unroll
@@ -402,24 +362,10 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && !BF && MOST == 1 && (BITS 
 #pragma unroll
                 for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_RELU);
             }
-            if constexpr (BF) {
-                float down, up;
-#pragma unroll
-                for (int i = 0; i < HC; ++i) {
-                    v[i] = __uint_as_float((uint32_t)to_bf16_rne(v[i]) << 16);
-                    amax = max(amax, (__float_as_uint(v[i]) >> 16) & 0x7fffu);
-                }
-#pragma unroll
-                for (int off = 16; off > 0; off >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, off));
-                dec_row_pow(amax, down, up);
-                if ((tid & 31) == 0) s_pow[16 * rt + h_row] = up;
-#pragma unroll
-                for (int i = 0; i < HC; ++i) v[i] *= down;
-            }
 #pragma unroll
             for (int i = 0; i < HC; i += 2) {
                 const half2_t hv = {(_Float16)v[i], (_Float16)v[i + 1]};
-                *reinterpret_cast<uint32_t *>(s_h + (16 * rt + h_row) * LDH + h_ch + i) = h2_bits(hv);
+                *reinterpret_cast<uint32_t *>(s_h + (16 * rt + h_row) * LDH + h_ch + i) = BF ? to_bf16_rne(v[i]) | (uint32_t)to_bf16_rne(v[i + 1]) << 16 : h2_bits(hv);
             }
         }
         __syncthreads();
@@ -429,14 +375,12 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && !BF && MOST == 1 && (BITS 
         const uint16_t *h_ptr = s_h + (lane & 15) * LDH + koct;
         float *const part_c = p.partial + (size_t)c * p.n_assign * d + slab0 * 32;
         int row_off[RT][4];
-        float pw[RT][4];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = 16 * rt + 4 * (lane >> 4) + r;
                 row_off[rt][r] = m < rows ? s_row[m] * d + (lane & 15) : -1;
-                pw[rt][r] = BF ? s_pow[m] : 1.0f;
             }
         float4_t y0[RT], y1[RT];
         clear(y0), clear(y1);
@@ -450,14 +394,14 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && !BF && MOST == 1 && (BITS 
             if constexpr (GROUPED) {
                 float4_t p0[RT], p1[RT];
                 clear(p0), clear(p1);
-                dec_mac<BITS, RT>(V[i], a, p0, p1);
-                const float sl = (float)__builtin_bit_cast(_Float16, gs2[i]), f0 = dec_lane(sl, lane16, 0), f1 = dec_lane(sl, lane16, 16);
+                dec_mac<BITS, RT, BF>(V[i], a, p0, p1);
+                const float sl = (float)__builtin_bit_cast(_Float16, gs2[i]) * UNIT, f0 = dec_lane(sl, lane16, 0), f1 = dec_lane(sl, lane16, 16);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) lo[rt][r] = fmaf(p0[rt][r], f0, lo[rt][r]), hi[rt][r] = fmaf(p1[rt][r], f1, hi[rt][r]);
             } else {
-                dec_mac<BITS, RT>(V[i], a, lo, hi);
+                dec_mac<BITS, RT, BF>(V[i], a, lo, hi);
             }
         };
         auto store = [&](int n, const float4_t (&lo)[RT], const float4_t (&hi)[RT]) {       // this slice's part of y, channels n .. n + 31
@@ -466,8 +410,8 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && !BF && MOST == 1 && (BITS 
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (row_off[rt][r] >= 0) {
-                        part_c[row_off[rt][r] + n] = BF ? lo[rt][r] * pw[rt][r] : lo[rt][r];
-                        part_c[row_off[rt][r] + n + 16] = BF ? hi[rt][r] * pw[rt][r] : hi[rt][r];
+                        part_c[row_off[rt][r] + n] = GROUPED ? lo[rt][r] : lo[rt][r] * UNIT;
+                        part_c[row_off[rt][r] + n + 16] = GROUPED ? hi[rt][r] : hi[rt][r] * UNIT;
                     }
         };
         // two units at a time, whose chains of unpacking and products the wavefront interleaves: two slabs (slices of 64 channels)
