@@ -154,7 +154,7 @@ __device__ inline void dec_write_index(const DecodeArgs &p, int32_t *s_key, int 
 // BITS: weight width.  GROUPED: group scales (groups of a multiple of 64 K values).  BF: bf16 rows.  CW: 64-channel parts of a slice.
 // MOST: sixteens of rows per item at most; with two, items of up to sixteen rows run the code for one.
 template <int BITS, bool GROUPED, bool BF, int CW, int MOST>
-__global__ __launch_bounds__(kDecThreads, !GROUPED && !BF && MOST == 1 && (BITS == 4 || CW > 1) ? 6 : 4) void decode_ffn_kernel(DecodeArgs p)
+__global__ __launch_bounds__(kDecThreads, !GROUPED && MOST == 1 && (BITS == 4 || CW > 1) ? 6 : 4) void decode_ffn_kernel(DecodeArgs p)
 {
     constexpr int NW = BITS / 4;                        // fragment blocks of a slab per 64 K values (a "unit")
     constexpr int KP = kDecWaves / CW, CH = 64 * CW;    // parts of K in fc1; channels of the slice
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && !BF && MOST == 1 && (BITS 
         constexpr int RT = decltype(rt_c)::value;           // sixteens of rows of this item
         // units of fc2 in flight per wavefront (and one of fc1); two of 8-bit weights leave room for a third block per compute unit (20 tokens, one of
         // 32 experts of 1024 x 4096, a step 30.3 -> 28.8 us; for slices of 64 channels, few blocks at all, 15.8 and 15.9, four)
-        constexpr int U2 = (RT > 1 && GROUPED) || (BITS == 8 && !GROUPED && !BF && CW > 1) ? 2 : 4;
+        constexpr int U2 = (RT > 1 && GROUPED) || (BITS == 8 && !GROUPED && CW > 1) ? 2 : 4;
         // ---- weight streams
         const uint32_t lane_off = (uint32_t)lane * 16u;
         const int cg = wave % CW, kp = wave / CW;
