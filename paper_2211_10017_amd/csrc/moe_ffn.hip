@@ -492,7 +492,7 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
 // rule is in doubt, it takes two thirds, 1.36 times as fast on average; 22 of them are 2 to 13 % slower):
 //  - up to eight assignments per expert: a block takes sixteen rows, and experts with more stream their weights again (61 tokens, two of
 //    eight experts of 4096 x 16384 8-bit 188 and 318; 134 tokens on 16 of 512 x 2048 21.0 and 24.1; 5 per expert of 1024 x 4096 44 and 41).
-//    FP16 rows on 4-bit codes, whose blocks then take thirty-two: up to sixteen, 150 MB of weights and a d_ff of twice d (192 tokens,
+//    Rows on 4-bit codes, whose blocks then take thirty-two: up to sixteen, 150 MB of weights and a d_ff of twice d (192 tokens,
 //    two of 32 experts of 1024 x 4096 51.6 and 45.2, 144 on 16 39.7 and 32.0; 242 tokens, two of 32 of 2048 x 8192 130 and 143; 191 of 1536 x
 //    2048 42.6 and 43.5), with group scales twelve, 110 MB and four times d (71 tokens, two of 16 of 1024 x 4096 48.0 and 36.9; 154, two of 32
 //    51.6 and 52.3; 96, two of 16 of 2048 x 4096 55 and 58), but not where one and a bit blocks per compute unit would keep some busy
@@ -527,7 +527,7 @@ extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F,
     if (5 * R > 4 * active * cw * bits || (cw == 1 && blocks > 3600)) return 0;
     if (R > 8L * E) {
         const bool fits = grouped ? R <= 12L * E && F >= 4 * d && bytes <= 110e6 : R <= 16L * E && F >= 2 * d && bytes <= 150e6;
-        return f16 && bits == 4 && fits && (blocks <= 260 || blocks > 400);
+        return bits == 4 && fits && (blocks <= 260 || blocks > 400);
     }
     if (bits == 8 && f16 && !grouped && R > E) {
         const bool streams = moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype) ||

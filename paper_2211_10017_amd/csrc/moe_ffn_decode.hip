@@ -555,7 +555,7 @@ static void launch_decode_rows(const DecodeArgs &p, dim3 grid, hipStream_t s)
 template <int BITS, bool GROUPED, bool BF>
 static void launch_decode(const DecodeArgs &p, dim3 grid, hipStream_t s)
 {
-    if constexpr (BITS == 4 && !BF)
+    if constexpr (BITS == 4)
         if (p.row_tiles > 1) return launch_decode_rows<BITS, GROUPED, BF, 2>(p, grid, s);
     launch_decode_rows<BITS, GROUPED, BF, 1>(p, grid, s);
 }
@@ -604,9 +604,9 @@ int launch_decode_ffn(const DecodeArgs &q, int bits, bool bf, hipStream_t s)
 {
     DecodeArgs p = q;
     const uint32_t units = p.g ? p.g / 64 : 1;
-    // two sixteens of rows per item where experts are expected to have more than eight, FP16 rows on 4-bit codes: with fewer the second
-    // sixteen's products are idle, with wider codes or rows it takes the registers that loads in flight need
-    p.row_tiles = p.n_assign > 8 * p.E && bits == 4 && !bf ? 2 : 1;
+    // two sixteens of rows per item where experts are expected to have more than eight, 4-bit codes: with fewer the second
+    // sixteen's products are idle, with wider codes it takes the registers that loads in flight need
+    p.row_tiles = p.n_assign > 8 * p.E && bits == 4 ? 2 : 1;
     p.group_inv = units > 1 ? (uint32_t)(((1ull << 32) + units - 1) / units) : 0;
     const int S = p.F / (64 * p.cw);
     // the most items that a routing can make: one per expert with rows, one more for every further `fit` rows (the first block writes the index arrays)
