@@ -225,26 +225,31 @@ struct ScaledCodes {
     }
 };
 
-// Eight codes as exact bf16 numbers, for rows that come as bf16: q for 8-bit codes, 16 q for 4-bit ones (a signed byte whose upper four bits are
-// the code).  There is no packed bf16 arithmetic, so every code is converted on its own, 14 or 15 instructions for eight instead of 8 or 9;
-// what that saves is a pass over the rows of x and of h to bring them to scaled FP16, a launch and a read and write each.
+// Eight codes as exact bf16 numbers q 2^-16, for rows that come as bf16.  A code that stands in a half by itself is Y 2^-24 (see ScaledCodes), or Y 2^-20,
+// and one mixed multiply-add makes (Y - 2^(B-1)) 2^-16 of it in FP32; there is no packed bf16 arithmetic, so every code is converted on its own,
+// 16 or 17 instructions for eight instead of 8 or 9.  What that saves is a pass over the rows of x and of h to bring them to scaled FP16, a launch and a
+// read and write each.
+// 2^-16: products of bf16 numbers, whole multiples of 2^-133, with the codes are whole multiples of 2^-149, FP32's smallest number, so the sums of rows of any size
+// are as exact as those of rows around one, and they overflow from 2^144 on in units of the code: with scales of 2^-16 and more, only where the result does.
+constexpr float kBf16CodeUnit = 65536.0f;
 template <int BITS>
 __device__ inline void codes_to_bf16(const uint32_t *w, uint32_t out[4])
 {
-    uint32_t v[2];
+    constexpr float LO = 0x1p24f / kBf16CodeUnit, HI = 0x1p20f / kBf16CodeUnit, OFF = (BITS == 4 ? -8.0f : -128.0f) / kBf16CodeUnit;
+    auto pair = [&](uint32_t y, float unit) {
+        const half2_t v = bits_h2(y);
+        const float lo = __builtin_fmaf((float)v[0], unit, OFF), hi = __builtin_fmaf((float)v[1], unit, OFF);
+        return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+    };
     if constexpr (BITS == 4) {
-        v[0] = ((w[0] << 4) & 0xf0f0f0f0u) ^ 0x80808080u;      // codes 0, 4, 1, 5
-        v[1] = (w[0] & 0xf0f0f0f0u) ^ 0x80808080u;             // codes 2, 6, 3, 7
+        const uint32_t x = w[0], x8 = x >> 8;
+        out[0] = pair(x & 0x000f000fu, LO);
+        out[1] = pair(x & 0x00f000f0u, HI);
+        out[2] = pair(x8 & 0x000f000fu, LO);
+        out[3] = pair(x8 & 0x00f000f0u, HI);
     } else {
-        v[0] = w[0] ^ 0x80808080u;
-        v[1] = w[1] ^ 0x80808080u;
-    }
-    auto value = [&](int q, int byte) { return __float_as_uint((float)(int8_t)(v[q] >> (8 * byte))); };
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t lo = BITS == 4 ? value(q & 1, q >> 1) : value(q >> 1, 2 * (q & 1));
-        const uint32_t hi = BITS == 4 ? value(q & 1, 2 + (q >> 1)) : value(q >> 1, 2 * (q & 1) + 1);
-        out[q] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+        for (int q = 0; q < 4; ++q) out[q] = pair(__builtin_amdgcn_perm(0u, w[q >> 1], q & 1 ? 0x0c030c02u : 0x0c010c00u), LO);
     }
 }
 

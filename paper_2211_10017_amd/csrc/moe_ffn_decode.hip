@@ -28,9 +28,11 @@
 // Where items may have thirty-two rows those of up to sixteen run the code for sixteen: half the products, more of fc2 in flight (192 tokens,
 // two of 32 of 1024 x 4096, a third of them ended 43.1 -> 41.6, none 43.7 and 43.9; 71, two of 16, group scales 32.7 -> 28.0).
 // The weights go through the magic-number conversion into the B operand.  Group scales multiply the fp32 sums of 64 K values of exact
-// codes.  bf16 rows, and the slice of h rounded to bf16, are operands as they are: the codes are exact in bf16 too (codes_to_bf16).  (Scaled per row and 64
-// K values to FP16 before, with searches for each row's largest: 64 tokens, two of 32 of 1024 x 4096 39.9 -> 39.0 us a step, 100, two of 32 of 512 x 2048 20.9 -> 20.2,
-// 20, two of 32 of 2048 x 8192 118 -> 114; same bits.)
+// codes.  bf16 rows, and the slice of h rounded to bf16, are operands as they are, the codes being exact in bf16 too (codes_to_bf16).  Where rows
+// come sixteen at a time and meet group scales they are scaled per row and 64 K values by a power of two into the FP16 range (exact) instead, and so is the slice of h per row, after its
+// rounding to bf16: the unpacking of the codes then costs less than the searches for each row's largest.  (us a step, scaled / as they are: 64 tokens, two of 32 experts of
+// 1024 x 4096, group scales 41.8 / 43.1, 16 37.9 / 38.6; channel scales 40.7 / 40.7; 20, two of 32 of 2048 x 8192 113.7 / 109.3, 40, two of 16 of 768 x 3072 25.7 / 25.0, 20, one
+// of 32 of 1024 x 4096, 8-bit, 36.2 / 34.0; same bits.)
 #include <math.h>
 
 #include <type_traits>
@@ -128,6 +130,35 @@ __device__ inline void dec_mac(const uint4 (&w)[BITS / 4], const uint4 (&a)[RT][
     }
 }
 
+// Power of two that brings a bf16 magnitude `amax` (bits, sign cleared) into [2^14, 2^15), and its reciprocal.
+__device__ inline void dec_row_pow(uint32_t amax, float &down, float &up)
+{
+    int ex = (int)(amax >> 7);
+    if (ex == 255) ex = 141;                            // inf/nan: factor 1 (the result is nan anyway)
+    const int fe = min(max(268 - ex, 1), 253);
+    down = __uint_as_float((uint32_t)fe << 23);
+    up = __uint_as_float((uint32_t)(254 - fe) << 23);
+}
+
+__device__ inline uint32_t dec_max_bf16(uint32_t amax, uint32_t pair)
+{
+    return max(amax, max(pair & 0x7fffu, (pair >> 16) & 0x7fffu));
+}
+
+// The same wavefront-wide for values that sixteen-lane rows share: maximum over lanes l, l ^ 16, l ^ 32, l ^ 48.
+__device__ inline uint32_t dec_max_over_rows(uint32_t v)
+{
+    v = max(v, (uint32_t)__shfl_xor((int)v, 16));
+    return max(v, (uint32_t)__shfl_xor((int)v, 32));
+}
+
+__device__ inline uint32_t dec_bf16_pair_to_f16(uint32_t pair, float down)
+{
+    const half2_t h = {(_Float16)__builtin_fmaf(__uint_as_float(pair << 16), down, 0.0f),
+                       (_Float16)__builtin_fmaf(__uint_as_float(pair & 0xffff0000u), down, 0.0f)};
+    return h2_bits(h);
+}
+
 // The stable sort by expert, for the callers: perm_src, inv_perm and expert_offsets (pruned rows, key E, come last).  One block;
 // up to 512 keys, every thread counts what precedes its own.
 __device__ inline void dec_write_index(const DecodeArgs &p, int32_t *s_key, int v)
@@ -160,11 +191,14 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && MOST == 1 && (BITS == 4 ||
     constexpr int KP = kDecWaves / CW, CH = 64 * CW;    // parts of K in fc1; channels of the slice
     constexpr int FIT = kDecFit * MOST;
     constexpr int LDR = CH + 4, LDH = CH + 8;
-    constexpr float UNIT = BF && BITS == 4 ? 0.0625f : 1.0f;             // (4-bit codes are 16 q in bf16)
+    // How bf16 rows meet the codes: as they are, or (group scales, one sixteen of rows per item) scaled to FP16
+    constexpr bool SCALED = BF && GROUPED && MOST == 1, CODES = BF && !SCALED;
+    constexpr float UNIT = CODES ? kBf16CodeUnit : 1.0f;                 // (bf16 codes are q / kBf16CodeUnit)
     __shared__ __align__(16) float s_red[KP * kDecFit * LDR];
     __shared__ __align__(16) uint16_t s_h[FIT * LDH];
     __shared__ __align__(16) int32_t s_row[kDecMaxAssign];      // assignments of the block's expert
     __shared__ int s_wave[kDecWaves];                           // rows of the expert among each wavefront's assignments
+    __shared__ float s_pow[SCALED ? FIT : 1];
     int *const s_cnt = reinterpret_cast<int *>(s_red);          // rows of every expert, until fc1's sums need the place
     static_assert(sizeof(s_red) >= kDecMaxExperts * sizeof(int), "the experts' counters fit");
 
@@ -276,7 +310,7 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && MOST == 1 && (BITS == 4 ||
         __syncthreads();
         MOE_DEC_STAMP(2);
         const uint32_t x_bytes = (uint32_t)(p.n_assign >> (p.gate_k - 1)) * d * 2u;
-        const int lane16 = (lane & 15) * 4;     // byte offset of dec_lane
+        const int lane16 = (lane & 15) * 4, lane_row = (lane >> 4) * 16;     // byte offsets of dec_lane
         // k octet this lane's quarter of the wavefront reads within a 32-deep step (see swap_rows)
         const int koct = ((lane >> 4) & 1) * 16 + (lane >> 5) * 8;
         // rows of x in operand order: only the lanes of live rows read (the others are past the tokens, which reads as zero)
@@ -307,21 +341,41 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && MOST == 1 && (BITS == 4 ||
 #pragma unroll
         for (int t = 0; t < 4; ++t) clear(acc[t]);
         for (int u = 0; u < n1; ++u) {
+            float up[RT];
+            if constexpr (SCALED) {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    uint32_t amax = 0;
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].x), A[rt][q].y);
+                        amax = dec_max_bf16(dec_max_bf16(amax, A[rt][q].z), A[rt][q].w);
+                    }
+                    float down;
+                    dec_row_pow(dec_max_over_rows(amax), down, up[rt]);
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        A[rt][q] = make_uint4(dec_bf16_pair_to_f16(A[rt][q].x, down), dec_bf16_pair_to_f16(A[rt][q].y, down),
+                                              dec_bf16_pair_to_f16(A[rt][q].z, down), dec_bf16_pair_to_f16(A[rt][q].w, down));
+                }
+            }
             if constexpr (GROUPED || BF) {              // the unit's sums, folded with the group's scale in fp32 (bf16: short sums, as h keeps few bits)
 #pragma unroll
                 for (int t = 0; t < 4; t += 2) {        // (one slab, then the other)
                     float4_t part[2][RT];
                     clear(part[0]), clear(part[1]);
-                    dec_mac<BITS, RT, BF>(W[t / 2], A, part[0], part[1]);
+                    dec_mac<BITS, RT, CODES>(W[t / 2], A, part[0], part[1]);
                     float sf[2];
 #pragma unroll
                     for (int i = 0; i < 2; ++i) sf[i] = GROUPED ? dec_lane((float)__builtin_bit_cast(_Float16, gs1) * UNIT, lane16, 16 * (t + i)) : 1.0f;
 #pragma unroll
                     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
+                        for (int r = 0; r < 4; ++r) {
+                            const float pw = SCALED ? dec_lane(up[rt], lane_row, r) : 1.0f;
 #pragma unroll
-                            for (int i = 0; i < 2; ++i) acc[t + i][rt][r] = GROUPED ? fmaf(part[i][rt][r], sf[i], acc[t + i][rt][r]) : part[i][rt][r] + acc[t + i][rt][r];
+                            for (int i = 0; i < 2; ++i) acc[t + i][rt][r] = GROUPED ? fmaf(part[i][rt][r], sf[i] * pw, acc[t + i][rt][r]) : part[i][rt][r] + acc[t + i][rt][r];
+                        }
                     if (RT > 1) __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
@@ -362,10 +416,25 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && MOST == 1 && (BITS == 4 ||
 #pragma unroll
                 for (int i = 0; i < HC; ++i) v[i] = activate(v[i], MOE_ACT_RELU);
             }
+            if constexpr (SCALED) {
+                uint32_t amax = 0;
+                float down, up;
+#pragma unroll
+                for (int i = 0; i < HC; ++i) {
+                    v[i] = __uint_as_float((uint32_t)to_bf16_rne(v[i]) << 16);
+                    amax = max(amax, (__float_as_uint(v[i]) >> 16) & 0x7fffu);
+                }
+#pragma unroll
+                for (int off = 16; off > 0; off >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, off));
+                dec_row_pow(amax, down, up);
+                if ((tid & 31) == 0) s_pow[16 * rt + h_row] = up;
+#pragma unroll
+                for (int i = 0; i < HC; ++i) v[i] *= down;
+            }
 #pragma unroll
             for (int i = 0; i < HC; i += 2) {
                 const half2_t hv = {(_Float16)v[i], (_Float16)v[i + 1]};
-                *reinterpret_cast<uint32_t *>(s_h + (16 * rt + h_row) * LDH + h_ch + i) = BF ? to_bf16_rne(v[i]) | (uint32_t)to_bf16_rne(v[i + 1]) << 16 : h2_bits(hv);
+                *reinterpret_cast<uint32_t *>(s_h + (16 * rt + h_row) * LDH + h_ch + i) = CODES ? to_bf16_rne(v[i]) | (uint32_t)to_bf16_rne(v[i + 1]) << 16 : h2_bits(hv);
             }
         }
         __syncthreads();
@@ -375,12 +444,14 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && MOST == 1 && (BITS == 4 ||
         const uint16_t *h_ptr = s_h + (lane & 15) * LDH + koct;
         float *const part_c = p.partial + (size_t)c * p.n_assign * d + slab0 * 32;
         int row_off[RT][4];
+        float pw[RT][4];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = 16 * rt + 4 * (lane >> 4) + r;
                 row_off[rt][r] = m < rows ? s_row[m] * d + (lane & 15) : -1;
+                pw[rt][r] = SCALED ? s_pow[m] : 1.0f;
             }
         float4_t y0[RT], y1[RT];
         clear(y0), clear(y1);
@@ -394,14 +465,14 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && MOST == 1 && (BITS == 4 ||
             if constexpr (GROUPED) {
                 float4_t p0[RT], p1[RT];
                 clear(p0), clear(p1);
-                dec_mac<BITS, RT, BF>(V[i], a, p0, p1);
+                dec_mac<BITS, RT, CODES>(V[i], a, p0, p1);
                 const float sl = (float)__builtin_bit_cast(_Float16, gs2[i]) * UNIT, f0 = dec_lane(sl, lane16, 0), f1 = dec_lane(sl, lane16, 16);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) lo[rt][r] = fmaf(p0[rt][r], f0, lo[rt][r]), hi[rt][r] = fmaf(p1[rt][r], f1, hi[rt][r]);
             } else {
-                dec_mac<BITS, RT, BF>(V[i], a, lo, hi);
+                dec_mac<BITS, RT, CODES>(V[i], a, lo, hi);
             }
         };
         auto store = [&](int n, const float4_t (&lo)[RT], const float4_t (&hi)[RT]) {       // this slice's part of y, channels n .. n + 31
@@ -410,8 +481,8 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && MOST == 1 && (BITS == 4 ||
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (row_off[rt][r] >= 0) {
-                        part_c[row_off[rt][r] + n] = GROUPED ? lo[rt][r] : lo[rt][r] * UNIT;
-                        part_c[row_off[rt][r] + n + 16] = GROUPED ? hi[rt][r] : hi[rt][r] * UNIT;
+                        part_c[row_off[rt][r] + n] = SCALED ? lo[rt][r] * pw[rt][r] : lo[rt][r];
+                        part_c[row_off[rt][r] + n + 16] = SCALED ? hi[rt][r] * pw[rt][r] : hi[rt][r];
                     }
         };
         // two units at a time, whose chains of unpacking and products the wavefront interleaves: two slabs (slices of 64 channels)
@@ -455,8 +526,9 @@ __global__ __launch_bounds__(kDecThreads, !GROUPED && MOST == 1 && (BITS == 4 ||
 // Sum of the d_ff slices and of a token's experts: out[t] = sum_j scale[a] * (W2-scale * sum_c partial[c][a] + b2),
 // a = t k + j in ascending j; pruned assignments (expert index E) add nothing, so a pruned token's row is zero.
 // A block is a token and 1024 / SG channels, four per thread; SG threads share an element's slices, NV of each expert at a time.
-template <int SG, int NV>
-__global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs p)
+// CODES: the partial sums are in units of bf16 codes (bf16 rows, channel scales).
+template <int SG, int NV, bool CODES>
+__device__ __forceinline__ void decode_reduce(const DecodeArgs &p)
 {
     constexpr int LANES = 256 / SG;
     __shared__ float4 s_sum[SG > 1 ? 2 * 256 : 1];
@@ -528,10 +600,11 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs p)
     for (int j = 0; j < 2; ++j) {
         if (e[j] < 0) continue;
         const half2_t s01 = bits_h2(s2[j].x), s23 = bits_h2(s2[j].y), b01 = bits_h2(b2[j].x), b23 = bits_h2(b2[j].y);
-        acc.x += sc[j] * (y[j].x * (float)s01[0] + (float)b01[0]);
-        acc.y += sc[j] * (y[j].y * (float)s01[1] + (float)b01[1]);
-        acc.z += sc[j] * (y[j].z * (float)s23[0] + (float)b23[0]);
-        acc.w += sc[j] * (y[j].w * (float)s23[1] + (float)b23[1]);
+        constexpr float unit = CODES ? kBf16CodeUnit : 1.0f;
+        acc.x += sc[j] * (y[j].x * ((float)s01[0] * unit) + (float)b01[0]);
+        acc.y += sc[j] * (y[j].y * ((float)s01[1] * unit) + (float)b01[1]);
+        acc.z += sc[j] * (y[j].z * ((float)s23[0] * unit) + (float)b23[0]);
+        acc.w += sc[j] * (y[j].w * ((float)s23[1] * unit) + (float)b23[1]);
     }
     if (p.out_dtype == MOE_F32) {
         *reinterpret_cast<float4 *>((float *)p.out + (size_t)t * d + n) = acc;
@@ -541,7 +614,27 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs p)
     }
 }
 
+template <int SG, int NV>
+__global__ __launch_bounds__(256) void decode_reduce_kernel(DecodeArgs p)
+{
+    decode_reduce<SG, NV, false>(p);
+}
+
+template <int SG, int NV>
+__global__ __launch_bounds__(256) void decode_reduce_codes_kernel(DecodeArgs p)
+{
+    decode_reduce<SG, NV, true>(p);
+}
+
 // ---- host side -----------------------------------------------------------------------------------
+
+template <int SG, int NV>
+static void launch_reduce(const DecodeArgs &p, bool codes, hipStream_t s)
+{
+    const dim3 grid(p.n_assign / p.gate_k, (p.d + 1024 / SG - 1) / (1024 / SG));
+    if (codes) hipLaunchKernelGGL((decode_reduce_codes_kernel<SG, NV>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((decode_reduce_kernel<SG, NV>), grid, dim3(256), 0, s, p);
+}
 
 template <int BITS, bool GROUPED, bool BF, int RT>
 static void launch_decode_rows(const DecodeArgs &p, dim3 grid, hipStream_t s)
@@ -616,11 +709,10 @@ int launch_decode_ffn(const DecodeArgs &q, int bits, bool bf, hipStream_t s)
     else launch_decode_bits<8>(p, bf, grid, s);
     int rc = check_launch("moe_grouped_ffn_wq (decode kernel)");
     if (rc || !p.out) return rc;                // (no output buffer: the partial sums are all the caller wants)
-    const int T = p.n_assign / p.gate_k;
-    auto blocks = [&](int sg) { return dim3(T, (p.d + 1024 / sg - 1) / (1024 / sg)); };
-    if (S > 32) hipLaunchKernelGGL((decode_reduce_kernel<16, 4>), blocks(16), dim3(256), 0, s, p);
-    else if (S > 8) hipLaunchKernelGGL((decode_reduce_kernel<8, 4>), blocks(8), dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((decode_reduce_kernel<4, 2>), blocks(4), dim3(256), 0, s, p);
+    const bool codes = bf && !p.g;
+    if (S > 32) launch_reduce<16, 4>(p, codes, s);
+    else if (S > 8) launch_reduce<8, 4>(p, codes, s);
+    else launch_reduce<4, 2>(p, codes, s);
     return check_launch("moe_grouped_ffn_wq (slice reduction)");
 }
 

@@ -231,7 +231,7 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
     float cs[2], bias[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        cs[t] = __shfl(cs_lane, 32 * t + (lane & 31)) * (BITS == 4 && p.a_bf16 ? 1.0f / 16.0f : 1.0f);      // (4-bit codes go in as 16 q)
+        cs[t] = __shfl(cs_lane, 32 * t + (lane & 31)) * (p.a_bf16 ? kBf16CodeUnit : 1.0f);      // (bf16 codes go in as q / kBf16CodeUnit)
         bias[t] = __shfl(bias_lane, 32 * t + (lane & 31));
     }
     __syncthreads();                                    // every wavefront is done with the ring

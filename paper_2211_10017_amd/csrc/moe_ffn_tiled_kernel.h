@@ -352,7 +352,7 @@ __device__ __forceinline__ void tiled_gemm(const GemmArgs &p)
     __syncthreads();                                   // every wavefront has left the stages
     if (!tile_ok) return;
     float cs[kTN], bias[kTN];
-    const float unit_cs = EXACT4 ? 512.0f : BF && BITS == 4 ? 1.0f / 16.0f : 1.0f;      // unscaled codes went in as q / unit_cs
+    const float unit_cs = EXACT4 ? 512.0f : BF ? kBf16CodeUnit : 1.0f;      // unscaled codes went in as q / unit_cs
     if constexpr (TM == 4) load_channels();
 #pragma unroll
     for (int t = 0; t < kTN; ++t) {

@@ -240,11 +240,14 @@ def test_the_oracle_comparisons_reach_every_form_of_the_decode_kernel():
     ran = {p.kernel for c in L.record(calls) for p in c.launches}
     flag = ("false", "true")
     built = {f"decode_ffn_kernel<{b}, {flag[g]}, {flag[f]}, {cw}, {rt}>" for b in (4, 8) for g in (0, 1) for f in (0, 1) for cw in (1, 2, 4, 8) for rt in (1, 2)
-             if rt == 1 or (b == 4 and not f)}
+             if rt == 1 or b == 4}
     built |= {"decode_reduce_kernel<16, 4>", "decode_reduce_kernel<8, 4>", "decode_reduce_kernel<4, 2>"}
     assert built <= ran, built - ran
     reduced = {c.launches[1].kernel for c in L.record([L.sliced(T, k, 5, d, F, 4) for T, k in rows for d, F in few])}
     assert len(reduced) == 3
+    (few_bf16,) = marks(t.test_few_bf16_rows_over_few_and_many_slices_match_oracle)
+    codes = {c.launches[1].kernel for c in L.record([L.sliced(3, 2, 5, d, F, b, 0, B.MOE_BF16) for d, F, b in few_bf16])}
+    assert codes == {k.replace("reduce", "reduce_codes") for k in reduced}
 
 
 def test_large_group_scaled_experts_with_many_rows_stay_in_row_tiles():

@@ -1,7 +1,10 @@
 """bf16 rows of channel-scaled layers that meet bf16 codes as they are: every kernel with row tiles against the oracle."""
+import numpy as np
 import pytest
+import torch
 
 import launches as L
+from helpers import to_dev
 from paper_2211_10017_amd import binding as B
 
 # rows per expert, d, F, bits: 16-, 32- and 64-row blocks of the ring, the long ring, register-fed tiles of 32, 64 and 128 rows; partly filled tiles
@@ -33,3 +36,55 @@ def test_conversion_where_matrix_work_is_the_larger_part():
 def test_bf16_codes_match_oracle(rows, d, F, bits):
     from test_gpu_ring import test_ring_gemm_matches_oracle as check
     check(rows, d, F, "bf16", bits, 0)
+
+
+def _masters(rng, E, d, F, bits, g):
+    w = [(rng.standard_normal((E, *s)) * 0.05).astype(np.float32) for s in ((d, F), (F, d))]
+    return [B.moe_quantize_experts(to_dev(m, torch.float32), bits, g, want_canon=False)[1:] for m in w]
+
+
+# Without biases the layer commutes with powers of two: rows of any size give the same bits, scaled, as long as x, h and y stay in range (unscaled they are
+# below 2^4; at 2^-100 the few elements of h below 2^-26 lose bits that bf16 does not have)
+SCALES = [2.0 ** k for k in (-100, -60, 60, 100, 115, 119, 123)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,d,F,bits", CASES + [([3, 9, 0, 17, 1], 1088, 704, 4), ([20, 40, 0, 33], 1088, 704, 4), ([60, 70, 1, 64], 1088, 704, 4)])
+def test_row_tiles_take_rows_of_any_size(rows, d, F, bits):
+    print(f"bf16 row sizes rows={rows[:5]} d={d} F={F} bits={bits}", flush=True)
+    rng = np.random.default_rng(d + F + bits)
+    E, off = len(rows), to_dev(np.concatenate([[0], np.cumsum(rows)]).astype(np.int32), torch.int32)
+    (s1, p1), (s2, p2) = _masters(rng, E, d, F, bits, 0)
+    x = to_dev(rng.standard_normal((sum(rows), d)).astype(np.float32), torch.bfloat16)
+    ffn = lambda v: B.moe_grouped_ffn_wq(v, off, E, d, F, bits, 0, p1, s1, p2, s2, y_dtype=torch.float32).double()  # noqa: E731
+    _compare_scaled(ffn, x)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,E,d,F,bits,g", [(40, 6, 192, 576, 4, 0), (40, 6, 192, 576, 8, 0), (40, 6, 192, 576, 4, 64), (40, 6, 192, 576, 8, 64), (90, 12, 256, 4096, 4, 0),
+                                            (90, 12, 256, 4096, 8, 0), (90, 12, 256, 4096, 4, 128), (250, 8, 128, 2048, 4, 0), (250, 8, 128, 2048, 4, 64),
+                                            (3, 5, 64, 2112, 4, 0), (3, 5, 1088, 576, 8, 0)])
+def test_the_decode_kernel_takes_rows_of_any_size(T, E, d, F, bits, g):
+    print(f"bf16 row sizes T={T} E={E} d={d} F={F} bits={bits} g={g}", flush=True)
+    rng = np.random.default_rng(T + d + F + bits)
+    (s1, p1), (s2, p2) = _masters(rng, E, d, F, bits, g)
+    x = to_dev(rng.standard_normal((T, d)).astype(np.float32), torch.bfloat16)
+    idx, one = to_dev(rng.integers(0, E, (T, 1)).astype(np.int32), torch.int32), torch.ones((T, 1), device="cuda")
+    _compare_scaled(lambda v: B.moe_grouped_ffn_wq_sliced(v, idx, one, E, d, F, bits, g, p1, s1, p2, s2)[0].double(), x)
+
+
+def _compare_scaled(ffn, x):
+    want, size = ffn(x), torch.ones((len(x), 1), device="cuda", dtype=torch.float64)
+    for i, s in enumerate(SCALES):
+        size[i::len(SCALES)] = s                      # rows of very different sizes side by side
+    got = ffn((x.double() * size).to(torch.bfloat16)) / size
+    assert torch.isfinite(got).all() and (want.norm(dim=1) > 0).all()
+    small = size[:, 0] < 2.0 ** -90
+    assert torch.equal(got[~small], want[~small])
+    assert ((got - want).norm(dim=1) <= 1e-6 * want.norm(dim=1)).all()
+    # close to the smallest normal numbers h has units of 2^-133, 2^-13 unscaled: half of one lost in elements whose root mean square is 2^-2 at least, 2^-12; x
+    # loses as much in its small elements; twice that for rows of few large elements
+    tiny = ffn((x.double() * 2.0 ** -120).to(torch.bfloat16)) * 2.0 ** 120
+    lost = ((tiny - want).norm(dim=1) / want.norm(dim=1)).max()
+    print(f"   lost at 2^-120: {float(lost):.2e}", flush=True)
+    assert lost <= 2.0 ** -10

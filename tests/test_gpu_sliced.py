@@ -56,6 +56,12 @@ def test_few_rows_over_few_and_many_slices_match_oracle(d, F, T, k):
     _check(d, F, "f16", 4, 0, T, k, 5, -1)
 
 
+# ... of partial sums in units of bf16 codes
+@pytest.mark.parametrize("d,F,bits", [(64, 512, 4), (320, 576, 8), (1088, 2048, 4), (64, 2112, 4), (1088, 4160, 8)])
+def test_few_bf16_rows_over_few_and_many_slices_match_oracle(d, F, bits):
+    _check(d, F, "bf16", bits, 0, 3, 2, 5, -1)
+
+
 # experts with far more rows than one item takes, beside experts with few or none; more experts than lanes, with spans of 5 and 64 experts
 @pytest.mark.parametrize("T,k,E,load", [(256, 2, 2, -1), (256, 2, 70, 200), (200, 1, 1, -1), (130, 2, 300, 90), (60, 2, 4096, 40)])
 @pytest.mark.parametrize("act,bits,g", [("f16", 4, 0), ("f16", 8, 64), ("bf16", 4, 64)])
