@@ -182,8 +182,8 @@ static GemmKernel four_call_kernel(int R, int E, int max_rows, int K, int N, int
     return kernel == GEMM_TILED || stream_pays(R, E, K, N, bits, kernel == GEMM_STREAM_UNROLLED) ? kernel : GEMM_TILED;
 }
 
-// bf: the rows were bf16 (they come in converted to scaled FP16, with their factors in g.row_pow, which only the
-// tiled kernel applies)
+// bf: the rows were bf16 (they come in as they are, smode SCALE_CHANNEL_BF16, or converted to scaled FP16, with their factors in
+// g.row_pow; only the row tiles take either)
 // tiles_only: rows go through the routing index, which only the row tiles do
 static int run_gemm(moe::GemmArgs g, int bits, int smode, bool bf, bool tiles_only, int max_rows, hipStream_t s)
 {
@@ -275,7 +275,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     // is rounded to 8 bits afterwards and a 2^-11 weight rounding would show through.
     GemmArgs g1{};
     const bool convert = bf && (grouped || !bf16_codes_pay(R, perm_src ? R / k : R, E, d, F, bits));
-    g1.a = (const uint16_t *)x_perm; g1.a_bf16 = bf && !convert; g1.row_pow = convert ? pow_x : nullptr; g1.offsets = expert_offsets;
+    g1.a = (const uint16_t *)x_perm; g1.row_pow = convert ? pow_x : nullptr; g1.offsets = expert_offsets;
     g1.wq = (const uint8_t *)w1_packed; g1.scales = (const __half *)s1; g1.bias = (const __half *)b1;
     g1.out = h; g1.E = E; g1.R = R; g1.K = d; g1.N = F; g1.g = grouped ? group_size : d;
     g1.out_dtype = act_dtype; g1.act = activation;
@@ -293,7 +293,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
         g1.a = x16;
     }
     // (groups of 128: exact codes, group sums folded in fp32; other group sizes: the two-term form, in the LDS ring exact codes as well)
-    const int smode1 = !grouped ? SCALE_CHANNEL : !bf ? SCALE_GROUP : group_size == 128 ? SCALE_GROUP_ACC : SCALE_GROUP_SPLIT;
+    const int channel = bf && !convert ? SCALE_CHANNEL_BF16 : SCALE_CHANNEL, smode1 = !grouped ? channel : !bf ? SCALE_GROUP : group_size == 128 ? SCALE_GROUP_ACC : SCALE_GROUP_SPLIT;
     int rc = run_gemm(g1, bits, smode1, bf, perm_src != nullptr, max_rows, s);
     if (rc) return rc;
 
@@ -314,7 +314,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
         rc = rows_to_f16((const uint16_t *)h, (uint16_t *)h, R, F, pow_h, s);
         if (rc) return rc;
     }
-    return run_gemm(g2, bits, grouped ? SCALE_GROUP : SCALE_CHANNEL, bf, perm_src != nullptr, max_rows, s);
+    return run_gemm(g2, bits, grouped ? SCALE_GROUP : channel, bf, perm_src != nullptr, max_rows, s);
 }
 
 extern "C" int moe_grouped_ffn_wq(const void *x_perm, int act_dtype, const int32_t *expert_offsets, int R,

@@ -10,11 +10,12 @@ typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
-enum { SCALE_CHANNEL = 0, SCALE_GROUP = 1, SCALE_GROUP_SPLIT = 2, SCALE_GROUP_ACC = 3 };
+// SCALE_CHANNEL_BF16: the rows are bf16 and meet the codes, exact in bf16, in bf16 matrix instructions.
+enum { SCALE_CHANNEL = 0, SCALE_GROUP = 1, SCALE_GROUP_SPLIT = 2, SCALE_GROUP_ACC = 3, SCALE_CHANNEL_BF16 = 4 };
+constexpr bool channel_scales(int smode) { return smode == SCALE_CHANNEL || smode == SCALE_CHANNEL_BF16; }
 
 struct GemmArgs {
-    const uint16_t *a;        // [R, K] fp16 bit patterns (rows that were bf16 come converted, scaled by 2^-p per row, or as they are: a_bf16)
-    int a_bf16;               // row tiles, channel scales: the rows are bf16 and meet the codes, exact in bf16, in bf16 matrix instructions
+    const uint16_t *a;        // [R, K] fp16 bit patterns (rows that were bf16 come converted, scaled by 2^-p per row, or, SCALE_CHANNEL_BF16, as they are)
     const float2 *row_pow;    // null, or per row (2^-p, 2^p): the tiled kernel multiplies its output rows by 2^p
     const int32_t *offsets;   // [E+1]
     const uint8_t *wq;        // packed codes, [E] x packed_bytes_per_expert

@@ -6,6 +6,7 @@ namespace moe {
 void launch_ring_8(const GemmArgs &p, int smode, int bm, dim3 grid, hipStream_t s)
 {
     if (smode == SCALE_CHANNEL) launch_ring_variants<8, SCALE_CHANNEL>(p, bm, grid, s);
+    else if (smode == SCALE_CHANNEL_BF16) launch_ring_variants<8, SCALE_CHANNEL_BF16>(p, bm, grid, s);
     else if (smode == SCALE_GROUP) launch_ring_variants<8, SCALE_GROUP>(p, bm, grid, s);
     else launch_ring_variants<8, SCALE_GROUP_ACC>(p, bm, grid, s);
 }

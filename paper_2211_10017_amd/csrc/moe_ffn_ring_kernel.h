@@ -32,7 +32,7 @@ struct RingShape {
     static constexpr int NW = BITS == 4 ? 1 : 2;                    // fragment blocks per tile and 64-deep K step
     static constexpr int TM = BM < 32 ? 1 : BM / 32;                // 32-row matrix tiles (of a 16-row block the upper half repeats the lower)
     static constexpr int kWaves = WC * WK;
-    static constexpr bool GROUPED = SMODE != SCALE_CHANNEL;
+    static constexpr bool GROUPED = !channel_scales(SMODE);
     static constexpr int kPartA = BM * 128;                         // bytes of one K part's rows in a stage
     static constexpr int kWaveB = 2 * NW * kFragBytes + (GROUPED ? 256 : 0);
     static constexpr int kStage = WK * kPartA + kWaves * kWaveB;
@@ -56,7 +56,7 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
 {
     using S = RingShape<BITS, SMODE, BM>;
     constexpr int TM = S::TM, NW = S::NW, WC = S::WC, WK = S::WK;
-    constexpr bool GROUPED = S::GROUPED, ACC = SMODE == SCALE_GROUP_ACC;
+    constexpr bool GROUPED = S::GROUPED, ACC = SMODE == SCALE_GROUP_ACC, BF = SMODE == SCALE_CHANNEL_BF16;
     constexpr int D = NST - 1;                          // stages in flight, of NST
     constexpr int NA = BM / 8 > WC ? BM / 8 / WC : 1;   // row loads per wavefront and stage (8 rows each)
     constexpr int L = NA + 2 * NW + (GROUPED ? 1 : 0);  // loads per wavefront and stage
@@ -133,9 +133,8 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) part[m][t][i] = 0.0f;
 
-    auto compute = [&](int slot, bool last_of_group, auto live_c, auto bf_c) {
+    auto compute = [&](int slot, bool last_of_group, auto live_c) {
         constexpr int LIVE = decltype(live_c)::value;               // row tiles of this block that hold rows
-        constexpr bool BF = decltype(bf_c)::value;                  // bf16 rows, channel scales
         const uint8_t *st = lds + slot * S::kStage;
         const uint16_t *sa = reinterpret_cast<const uint16_t *>(st + kp * S::kPartA);
         const uint8_t *sb = st + WK * S::kPartA + wave * S::kWaveB;
@@ -204,7 +203,7 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
 #pragma unroll
     for (int s = 0; s < D; ++s)
         if (s < per) issue(s, s);
-    auto k_loop = [&](auto live_c, auto bf_c) {
+    auto k_loop = [&](auto live_c) {
         int slot = 0;
         for (int s = 0; s < per; ++s) {
             const int rem = min(per - 1 - s, D - 1);
@@ -214,16 +213,12 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
             else wait_loads<0>();
             __syncthreads();
             if (s + D < per) issue(s + D, slot == 0 ? NST - 1 : slot - 1);
-            if (s < mine) compute(slot, s + 1 == mine || (first + s + 1) * 64 % p.g == 0, live_c, bf_c);
+            if (s < mine) compute(slot, s + 1 == mine || (first + s + 1) * 64 % p.g == 0, live_c);
             slot = slot + 1 == NST ? 0 : slot + 1;
         }
     };
-    auto part_of_k = [&](auto bf_c) {
-        if (TM == 1 || rows > 32) k_loop(std::integral_constant<int, TM>{}, bf_c);
-        else k_loop(std::integral_constant<int, 1>{}, bf_c);
-    };
-    if (!GROUPED && p.a_bf16) part_of_k(std::integral_constant<bool, !GROUPED>{});
-    else part_of_k(std::false_type{});
+    if (TM == 1 || rows > 32) k_loop(std::integral_constant<int, TM>{});
+    else k_loop(std::integral_constant<int, 1>{});
 
     // ---- the K parts meet: every wavefront leaves its partial tiles in LDS and finishes registers
     // [QN kp, QN kp + QN) of each tile of its channels
@@ -231,7 +226,7 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
     float cs[2], bias[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        cs[t] = __shfl(cs_lane, 32 * t + (lane & 31)) * (p.a_bf16 ? kBf16CodeUnit : 1.0f);      // (bf16 codes go in as q / kBf16CodeUnit)
+        cs[t] = __shfl(cs_lane, 32 * t + (lane & 31)) * (BF ? kBf16CodeUnit : 1.0f);      // (bf16 codes go in as q / kBf16CodeUnit)
         bias[t] = __shfl(bias_lane, 32 * t + (lane & 31));
     }
     __syncthreads();                                    // every wavefront is done with the ring
@@ -262,6 +257,8 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
     if (tile_ok) finish_tile<TM, QN, 32 * TM>(p, v, tile_rows, cs, bias, rows, 8 * (QN / 4) * kp, ntile0 * 32, lds + wave * kPatchBytes<QN>);
 }
 
+// So are the rows' type and the codes': with a loop for bf16 beside the one for FP16 in a kernel a launch of 40 rows of 8-bit experts, whose code no block
+// has run before, took longer (a step of 40 tokens, one of 32 of 1024 x 4096, 47.6 us in one, 47.2 apart; 997 bf16 tokens of 768 x 3072 62.6 and 62.1).
 // The number of stages is a constant of the kernel: as an argument of one kernel for both it cost the shorter ring with group scales 1 to 3 %
 // (590 tokens, two of 5 experts of 1600 x 11456, 175 us a step and 169).
 template <int BITS, int SMODE, int BM>

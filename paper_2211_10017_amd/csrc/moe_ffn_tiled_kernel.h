@@ -19,11 +19,12 @@ constexpr int kLdsRow = 64;              // halfs per LDS row: one K step, no pa
                                          // fragment reads conflict-free and keeps a wavefront's 64 chunks contiguous
 constexpr int kTN = 2;                   // 32-channel tiles per wavefront
 
-// BF: the rows are bf16 and meet bf16 codes (channel scales)
-template <int BITS, int SMODE, int TM, bool BF>
-__device__ __forceinline__ void tiled_gemm(const GemmArgs &p)
+// (bf16 rows that meet bf16 codes are a scale mode, not a branch: both loops in one kernel take 194 registers for 64-row tiles of 8-bit weights, two wavefronts per
+// SIMD, each by itself 162 to 164, three; 4096 tokens, two of 128 experts of 2048 x 8192, skewed, a step 1145 us in one, 1116 apart)
+template <int BITS, int SMODE, int TM>
+__global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
 {
-    static_assert(!BF || SMODE == SCALE_CHANNEL, "group scales go into FP16 weights");
+    constexpr bool BF = SMODE == SCALE_CHANNEL_BF16;
     constexpr int BM = 32 * TM;
     constexpr int NW = BITS == 4 ? 1 : 2;             // 16-byte loads per tile per 64-deep K step
     // two stages of rows; at the end the patches through which the wavefronts' results leave
@@ -50,7 +51,7 @@ __device__ __forceinline__ void tiled_gemm(const GemmArgs &p)
     float cs_lane = 1.0f, bias_lane = 0.0f;            // channel factors: lane l brings channel l of the wavefront's 64
     auto load_channels = [&]() {
         const size_t n = (size_t)e * N + tile_c * 32 + lane;
-        if (SMODE == SCALE_CHANNEL) cs_lane = __half2float(p.scales[n]);
+        if (channel_scales(SMODE)) cs_lane = __half2float(p.scales[n]);
         if (p.bias) bias_lane = __half2float(p.bias[n]);
     };
     if constexpr (TM < 4) load_channels();
@@ -98,7 +99,7 @@ __device__ __forceinline__ void tiled_gemm(const GemmArgs &p)
     // 4-bit codes that go in unscaled are taken the same way, as q 2^-9 (2^24 itself is no FP16 number), which the factor at the end makes up for:
     // two-operand masks instead of v_and_or_b32 with three registers.  4096 bf16 tokens, two of 16 experts of 2048 x 8192, a step 554 -> 552 us, 16384 of
     // 1024 x 4096 557 -> 555; bf16 with groups of 128, 4096 x 16384, 4601 -> 4583.
-    constexpr bool EXACT4 = !BF && BITS == 4 && (SMODE == SCALE_CHANNEL || ACC);
+    constexpr bool EXACT4 = BITS == 4 && (SMODE == SCALE_CHANNEL || ACC);
     static_assert(!ACC || TM <= 2, "two accumulator sets fit for TM <= 2 only");
     float16_t accg[ACC ? TM : 1][kTN];
 
@@ -109,7 +110,7 @@ __device__ __forceinline__ void tiled_gemm(const GemmArgs &p)
     constexpr int PF = (BITS == 8 && TM == 4) ? 1 : 2;
     // The rows (16 bits each; group-scaled layers get bf16 rows converted, see rows_to_f16_kernel) go from global memory straight into
     // the LDS stage: no staging registers, no LDS write instructions.
-    constexpr int LB = kTN * NW + (SMODE != SCALE_CHANNEL ? kTN : 0);   // loads of one load_b()
+    constexpr int LB = kTN * NW + (channel_scales(SMODE) ? 0 : kTN);   // loads of one load_b()
     auto dma_a = [&](int kb, uint16_t *stage, int m) {
         load_to_lds16(a_ptr[m] + kb * 64, stage + (32 * m + 8 * wave) * kLdsRow);
     };
@@ -121,7 +122,7 @@ __device__ __forceinline__ void tiled_gemm(const GemmArgs &p)
         for (int t = 0; t < kTN; ++t) {
 #pragma unroll
             for (int w = 0; w < NW; ++w) gb[WS][t][w] = (b_ptr[t] + (size_t)(kb * NW + w) * 64)[lane];
-            if (SMODE != SCALE_CHANNEL)
+            if (!channel_scales(SMODE))
                 gs[WS][t] = __builtin_bit_cast(_Float16, (s_ptr[t] + (size_t)((kb * 64) / p.g) * N)[lane & 31]);
         }
     };
@@ -356,48 +357,19 @@ __device__ __forceinline__ void tiled_gemm(const GemmArgs &p)
     if constexpr (TM == 4) load_channels();
 #pragma unroll
     for (int t = 0; t < kTN; ++t) {
-        cs[t] = SMODE == SCALE_CHANNEL ? __shfl(cs_lane, 32 * t + (lane & 31)) * unit_cs : SMODE == SCALE_GROUP_SPLIT ? 1.0f / 256.0f
+        cs[t] = channel_scales(SMODE) ? __shfl(cs_lane, 32 * t + (lane & 31)) * unit_cs : SMODE == SCALE_GROUP_SPLIT ? 1.0f / 256.0f
               : WINDOWED ? __builtin_ldexpf(1.0f, kWindowShift - unit[t]) : 1.0f;
         bias[t] = __shfl(bias_lane, 32 * t + (lane & 31));
     }
     finish_tile<TM, 16, BM>(p, acc, tile_rows, cs, bias, rows, 0, ntile0 * 32, lds_raw + wave * kPatchBytes<16>);
 }
 
-template <int BITS, int SMODE, int TM>
-__global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
-{
-    tiled_gemm<BITS, SMODE, TM, false>(p);
-}
-
-// The same for bf16 rows, as a kernel of its own: both loops in one take 194 registers for 64-row tiles of 8-bit weights, two wavefronts per SIMD,
-// each by itself 162 to 164, three (4096 tokens, two of 128 experts of 2048 x 8192, skewed, a step 1145 us in one, 1116 apart).
-struct Bf16GemmArgs : GemmArgs {};
-template <int BITS, int SMODE, int TM>
-__global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(Bf16GemmArgs p)
-{
-    tiled_gemm<BITS, SMODE, TM, true>(p);
-}
-
-template <int BITS, int SMODE, int TM>
-static void launch_fp16(const GemmArgs &p, dim3 grid, hipStream_t s)
-{
-    void (*kernel)(GemmArgs) = grouped_gemm_kernel<BITS, SMODE, TM>;
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, p);
-}
-
-template <int BITS, int TM>
-static void launch_bf16(const GemmArgs &p, dim3 grid, hipStream_t s)
-{
-    void (*kernel)(Bf16GemmArgs) = grouped_gemm_kernel<BITS, SCALE_CHANNEL, TM>;
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, Bf16GemmArgs{p});
-}
-
 template <int BITS, int SMODE>
 static void launch_tm(const GemmArgs &p, int tm, dim3 grid, hipStream_t s)
 {
-    if (tm == 1) launch_fp16<BITS, SMODE, 1>(p, grid, s);
-    else if (tm == 2) launch_fp16<BITS, SMODE, 2>(p, grid, s);
-    else launch_fp16<BITS, SMODE, 4>(p, grid, s);
+    if (tm == 1) hipLaunchKernelGGL((grouped_gemm_kernel<BITS, SMODE, 1>), grid, dim3(256), 0, s, p);
+    else if (tm == 2) hipLaunchKernelGGL((grouped_gemm_kernel<BITS, SMODE, 2>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((grouped_gemm_kernel<BITS, SMODE, 4>), grid, dim3(256), 0, s, p);
 }
 
 // All kernels of one weight width and one kind of scale mode (one translation unit each, so that they
@@ -406,12 +378,12 @@ template <int BITS, bool EXACT>
 static void launch_tiled_variants(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s)
 {
     if constexpr (!EXACT) {
-        if (smode == SCALE_CHANNEL && p.a_bf16) (tm == 1 ? launch_bf16<BITS, 1> : tm == 2 ? launch_bf16<BITS, 2> : launch_bf16<BITS, 4>)(p, grid, s);
+        if (smode == SCALE_CHANNEL_BF16) launch_tm<BITS, SCALE_CHANNEL_BF16>(p, tm, grid, s);
         else if (smode == SCALE_CHANNEL) launch_tm<BITS, SCALE_CHANNEL>(p, tm, grid, s);
         else launch_tm<BITS, SCALE_GROUP>(p, tm, grid, s);
     } else if (smode == SCALE_GROUP_ACC) {                 // row tiles of at most 64 rows
-        if (tm == 1) launch_fp16<BITS, SCALE_GROUP_ACC, 1>(p, grid, s);
-        else launch_fp16<BITS, SCALE_GROUP_ACC, 2>(p, grid, s);
+        if (tm == 1) hipLaunchKernelGGL((grouped_gemm_kernel<BITS, SCALE_GROUP_ACC, 1>), grid, dim3(256), 0, s, p);
+        else hipLaunchKernelGGL((grouped_gemm_kernel<BITS, SCALE_GROUP_ACC, 2>), grid, dim3(256), 0, s, p);
     } else {
         launch_tm<BITS, SCALE_GROUP_SPLIT>(p, tm, grid, s);
     }

@@ -112,9 +112,9 @@ def test_every_form_of_the_row_tiles_is_in_the_two_build_comparison():
         assert [p.kernel for p in call.launches if p.kernel.startswith("grouped")][0] == case[6], case
     ring = L.record([L.ffn(sum(c[0]), len(c[0]), *c[1:5], B._DT[{"f16": torch.float16, "bf16": torch.bfloat16}[c[5]]]) for c in RING])
     ran = {p.kernel for call in fed + ring for p in call.launches}
-    modes, acc = (0, 1, 2), 3                      # per channel, per group, two-term; group sums
+    modes, acc = (0, 1, 2, 4), 3                   # per channel, per group, two-term, per channel with bf16 rows; group sums
     built = {f"grouped_gemm_kernel<{b}, {m}, {t}>" for b in (4, 8) for m in modes for t in (1, 2, 4)} | {f"grouped_gemm_kernel<{b}, {acc}, {t}>" for b in (4, 8) for t in (1, 2)}
-    built |= {f"grouped_gemm_ring_kernel<{b}, {m}, {bm}>" for b in (4, 8) for m in (0, 1, acc) for bm in (16, 32, 64)}
+    built |= {f"grouped_gemm_ring_kernel<{b}, {m}, {bm}>" for b in (4, 8) for m in (0, 1, acc, 4) for bm in (16, 32, 64)}
     assert built <= ran, built - ran
 
 
@@ -223,7 +223,7 @@ def test_the_oracle_comparisons_reach_every_long_ring():
     act = {"f16": B.MOE_F16, "bf16": B.MOE_BF16}
     (m_act, m_rows) = test_gpu_ring.test_long_rings_match_oracle_and_the_build_that_waits_for_all_loads.pytestmark
     ran = {p.kernel for rows, d, F in m_rows.args[1] for a, g in m_act.args[1] for p in L.record([L.ffn(sum(rows), len(rows), d, F, 8, g, act[a])])[0].launches}
-    assert {f"grouped_gemm_ring_long_kernel<8, {m}, 64>" for m in (0, 1, 3)} <= ran, ran
+    assert {f"grouped_gemm_ring_long_kernel<8, {m}, 64>" for m in (0, 1, 3, 4)} <= ran, ran
 
 
 def test_the_oracle_comparisons_reach_every_form_of_the_decode_kernel():

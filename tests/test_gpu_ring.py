@@ -44,7 +44,7 @@ def test_ring_gemm_matches_oracle(rows, d, F, act, bits, g):
 
 # 64-row tiles of 18 MB of 8-bit weights, one per compute unit at most: the longest ring, over odd and even numbers of K steps
 @pytest.mark.parametrize("rows,d,F", [([70, 33, 64, 129, 5, 0, 96, 40], 1216, 1984), ([50] * 32, 320, 1792)])
-@pytest.mark.parametrize("act,g", [("f16", 64), ("bf16", 64), ("bf16", 0)])
+@pytest.mark.parametrize("act,g", [("f16", 64), ("bf16", 64), ("bf16", 0), ("f16", 0)])
 def test_long_rings_match_oracle_and_the_build_that_waits_for_all_loads(rows, d, F, act, g):
     test_ring_gemm_matches_oracle(rows, d, F, act, 8, g)
     test_counted_waits_equal_waiting_for_all_loads(rows, d, F, 8, g, act)
@@ -60,7 +60,10 @@ RING = [
     ([270, 257, 130, 20], 2112, 4416, 4, 0, "f16"), ([270, 257, 130, 20], 2176, 4480, 4, 64, "f16"),
     ([300, 290, 270], 2112, 5440, 8, 0, "f16"), ([270, 257, 130, 20], 2176, 4480, 4, 128, "bf16"),
     ([3, 9, 0, 17, 1], 1152, 640, 8, 128, "bf16"), ([20, 40, 0, 33], 1152, 640, 4, 128, "bf16"),        # the remaining forms of both scale modes
-    ([20, 40, 0, 33], 1088, 704, 8, 0, "f16"), ([60, 70, 1, 64], 1152, 640, 8, 128, "bf16")]
+    ([20, 40, 0, 33], 1088, 704, 8, 0, "f16"), ([60, 70, 1, 64], 1152, 640, 8, 128, "bf16"),
+    ([3, 9, 0, 17, 1], 1088, 704, 4, 0, "bf16"), ([3, 9, 0, 17, 1], 1152, 1088, 8, 0, "bf16"),          # bf16 rows and codes: 16-, 32- and 64-row blocks
+    ([20, 40, 0, 33], 1088, 704, 4, 0, "bf16"), ([20, 40, 0, 33], 1152, 640, 8, 0, "bf16"),
+    ([60, 70, 1, 64], 1088, 704, 4, 0, "bf16"), ([60, 50, 33, 5] * 4, 192, 3072, 8, 0, "f16")]
 
 
 @pytest.mark.parametrize("rows,d,F,bits,g,act", RING)

@@ -1,4 +1,4 @@
-"""The grouped GEMMs with row tiles send their activation rows (fp16, or bf16 converted to scaled fp16 beforehand), and the kernel with the LDS ring
+"""The grouped GEMMs with row tiles send their activation rows (fp16, bf16, or bf16 converted to scaled fp16 beforehand), and the kernel with the LDS ring
 its weights as well, from global memory straight into LDS and wait for them with a hand-counted `s_waitcnt vmcnt(n)`, n = the loads issued after them.  The library is
 built a second time (libmoe_wq_waitall.so) with every such wait replaced by a wait for ALL loads, which
 needs no counting.  If a compiler change ever merged, split or reordered one of the counted loads, the
@@ -77,7 +77,7 @@ REGISTER_FED = [
     (_T32, 256, 2816, 4, 128, _F16, "grouped_gemm_kernel<4, 1, 1>"), (_T32, 192, 2688, 8, 64, _F16, "grouped_gemm_kernel<8, 1, 1>"),
     (_T32, 192, 2688, 4, 64, _BF16, "grouped_gemm_kernel<4, 2, 1>"), (_T32, 256, 2688, 8, 64, _BF16, "grouped_gemm_kernel<8, 2, 1>"),
     (_T32, 384, 2816, 4, 128, _BF16, "grouped_gemm_kernel<4, 3, 1>"), (_T32, 256, 2816, 8, 128, _BF16, "grouped_gemm_kernel<8, 3, 1>"),
-    (_T64, 256, 3392, 4, 0, _F16, "grouped_gemm_kernel<4, 0, 2>"), (_T64, 192, 3392, 8, 0, _BF16, "grouped_gemm_kernel<8, 0, 2>"),
+    (_T64, 256, 3392, 4, 0, _F16, "grouped_gemm_kernel<4, 0, 2>"), (_T64, 192, 3392, 8, 0, _F16, "grouped_gemm_kernel<8, 0, 2>"),
     (_T64, 192, 3392, 4, 64, _F16, "grouped_gemm_kernel<4, 1, 2>"), (_T64, 256, 3456, 8, 128, _F16, "grouped_gemm_kernel<8, 1, 2>"),
     (_T64, 256, 3392, 4, 64, _BF16, "grouped_gemm_kernel<4, 2, 2>"), (_T64, 192, 3392, 8, 64, _BF16, "grouped_gemm_kernel<8, 2, 2>"),
     (_T64, 256, 3456, 4, 128, _BF16, "grouped_gemm_kernel<4, 3, 2>"), (_T64, 384, 3456, 8, 128, _BF16, "grouped_gemm_kernel<8, 3, 2>"),
@@ -85,7 +85,10 @@ REGISTER_FED = [
     (_T128, 2176, 4736, 4, 64, _F16, "grouped_gemm_kernel<4, 1, 4>"), ([300, 290, 270], 2112, 4224, 8, 64, _F16, "grouped_gemm_kernel<8, 1, 4>"),
     (_T128, 2112, 4736, 4, 64, _BF16, "grouped_gemm_kernel<4, 2, 4>"), ([300, 290, 270], 2176, 4224, 8, 64, _BF16, "grouped_gemm_kernel<8, 2, 4>"),
     (_T128, 2176, 4864, 4, 128, _BF16, "grouped_gemm_kernel<4, 3, 2>"),                     # group sums stay on 64-row tiles
-    (_T128, 2112, 4736, 4, 0, _BF16, "grouped_gemm_kernel<4, 0, 4>")]
+    # bf16 rows and codes
+    (_T32, 192, 2752, 4, 0, _BF16, "grouped_gemm_kernel<4, 4, 1>"), (_T32, 256, 2752, 8, 0, _BF16, "grouped_gemm_kernel<8, 4, 1>"),
+    (_T64, 256, 3392, 4, 0, _BF16, "grouped_gemm_kernel<4, 4, 2>"), (_T64, 192, 3392, 8, 0, _BF16, "grouped_gemm_kernel<8, 4, 2>"),
+    (_T128, 2112, 4736, 4, 0, _BF16, "grouped_gemm_kernel<4, 4, 4>"), ([300, 290, 270], 2176, 4224, 8, 0, _BF16, "grouped_gemm_kernel<8, 4, 4>")]
 
 
 @pytest.mark.parametrize("rows,d,F,bits,g,x_dt,fc1", REGISTER_FED)
