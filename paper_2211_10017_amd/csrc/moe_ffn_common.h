@@ -182,10 +182,10 @@ __device__ inline void dequant8(uint32_t w0, uint32_t w1, uint32_t out[4])
     out[3] = h2_bits(bits_h2(__builtin_amdgcn_perm(magic, w1, 0x04030402u)) - sub);
 }
 
-// Codes times their group's scale in one instruction after the unpacking.  FP16 numbers below 2^-13 are whole multiples of 2^-24, bits and
+// 4-bit codes times their group's scale in one instruction after the unpacking.  FP16 numbers below 2^-13 are whole multiples of 2^-24, bits and
 // value in proportion, so a code Y that stands in the low bits of a half by itself is the number Y 2^-24 (2^-20 four bits up), and
-// Y 2^-24 * (2^24 s) - 2^(B-1) s is (Y - 2^(B-1)) s with one rounding, as code times scale is: 2^(B-1) s is exact, where 1032 s, what the
-// 0x6400 form would take off, is not.  4-bit codes cost 9 instructions per eight instead of 13, 8-bit ones 8 instead of 12.
+// Y 2^-24 * (2^24 s) - 8 s is (Y - 8) s with one rounding, as code times scale is: 8 s is exact, where 1032 s, what the
+// 0x6400 form would take off, is not.  9 instructions per eight codes instead of 13.
 // 2^24 s has to be an FP16 number and s itself a normal one: the caller scales s by a power of two per channel, 2^unit = 2^24 / 2^t,
 // which the accumulator column is then in units of, and takes only what `scale_in_window` accepts.
 // What bounds a tile of many rows is the power of matrix and conversion work together.  A step of 8192 tokens, two of 64 experts of
@@ -199,7 +199,6 @@ __device__ inline bool scale_in_window(_Float16 m)        // 2^10 <= m < infinit
 // Brings s to [2^13, 2^14): room for a factor of 4 up and of 8 down.
 __device__ inline int window_unit(_Float16 s) { return 14 - __builtin_amdgcn_frexp_exph(s); }
 
-template <int BITS>
 struct ScaledCodes {
     half2_t lo, hi, off;
     ScaledCodes() = default;
@@ -207,22 +206,16 @@ struct ScaledCodes {
     {
         lo = half2_t{m, m};
         hi = lo * half2_t{(_Float16)0.0625f, (_Float16)0.0625f};
-        const _Float16 o = (_Float16)(BITS == 4 ? -0x1p-21f : -0x1p-17f);
-        off = lo * half2_t{o, o};
+        off = lo * half2_t{(_Float16)-0x1p-21f, (_Float16)-0x1p-21f};
     }
-    __device__ inline void convert(const uint32_t *w, uint32_t out[4]) const
+    __device__ inline void convert(uint32_t x, uint32_t out[4]) const
     {
         auto fma2 = [&](uint32_t y, half2_t f) { return h2_bits(__builtin_elementwise_fma(bits_h2(y), f, off)); };
-        if constexpr (BITS == 4) {
-            const uint32_t x = w[0], x8 = x >> 8;
-            out[0] = fma2(x & 0x000f000fu, lo);
-            out[1] = fma2(x & 0x00f000f0u, hi);
-            out[2] = fma2(x8 & 0x000f000fu, lo);
-            out[3] = fma2(x8 & 0x00f000f0u, hi);
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) out[q] = fma2(__builtin_amdgcn_perm(0u, w[q >> 1], q & 1 ? 0x0c030c02u : 0x0c010c00u), lo);
-        }
+        const uint32_t x8 = x >> 8;
+        out[0] = fma2(x & 0x000f000fu, lo);
+        out[1] = fma2(x & 0x00f000f0u, hi);
+        out[2] = fma2(x8 & 0x000f000fu, lo);
+        out[3] = fma2(x8 & 0x00f000f0u, hi);
     }
 };
 

@@ -194,10 +194,10 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
         };
 
         // unpack + convert one 16-deep step of weight fragments in registers
-        ScaledCodes<BITS> factors[kTN];
+        ScaledCodes factors[kTN];
         if constexpr (WINDOW || EXACT4)
 #pragma unroll
-            for (int t = 0; t < kTN; ++t) factors[t] = ScaledCodes<BITS>(EXACT4 ? (_Float16)32768.0f : sc[t]);
+            for (int t = 0; t < kTN; ++t) factors[t] = ScaledCodes(EXACT4 ? (_Float16)32768.0f : sc[t]);
         auto dequant_step = [&](int j, uint32_t (&bw)[kTN][4], uint32_t (&bl)[kTN][4]) {
 #pragma unroll
             for (int t = 0; t < kTN; ++t) {
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
                     continue;
                 }
                 if constexpr (WINDOW || EXACT4) {
-                    factors[t].convert(raw[t] + j * NW, bw[t]);
+                    factors[t].convert(raw[t][j], bw[t]);
                     continue;
                 }
                 if (BITS == 4) dequant4(raw[t][j], bw[t]);
@@ -294,7 +294,10 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     // Group scales with the multiply and the subtraction of the code's offset in one instruction (ScaledCodes): an accumulator
     // column, which is a lane's channel, is kept in units of a power of two that brings the channel's first scale to the middle
     // of what that conversion takes, and a wavefront that meets a scale outside of it goes on in the general loop.
-    constexpr bool WINDOWED = SMODE == SCALE_GROUP && PF == 2;
+    // (4-bit codes only: for 8-bit ones, which save as many instructions, it takes the 32-row tile's fourth wavefront per SIMD, 140 registers for 128,
+    // and gains nothing.  us a step with / without, groups of 128: 4000 tokens, one of 128 experts of 1024 x 4096 262.7 / 262.6, 8000 350.4 / 350.4, 3000, one of 64 of
+    // 2048 x 8192 511.9 / 510.9.)
+    constexpr bool WINDOWED = SMODE == SCALE_GROUP && BITS == 4;
     int unit[kTN] = {};
     // The K loop exists once per number of live row tiles (the last tile of an expert usually
     // holds few rows): a run-time test inside the loop would cut the MFMA stream into pieces.

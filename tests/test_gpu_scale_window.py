@@ -35,7 +35,7 @@ def _dequantised(canon, scales, bits, g):
     return (q.half() * scales.repeat_interleave(g, dim=1)).double()          # (rounded once, as the kernels take it)
 
 
-# 32-, 64- and 128-row tiles (tallest 8-bit tile: general loop only); odd and even numbers of K steps; one and two K steps per group
+# 32-, 64- and 128-row tiles (8-bit codes: general loop only); odd and even numbers of K steps; one and two K steps per group
 @pytest.mark.parametrize("E,rows,d,g", [(256, (20, 40), 512, 64), (64, (70, 130), 512, 128), (64, (33, 150), 576, 64), (8, (280, 330), 2112, 64),
                                         (8, (290, 390), 2176, 128)])
 @pytest.mark.parametrize("bits", [4, 8])
