@@ -1,11 +1,14 @@
 """Group scales in the row-tile kernels: a wavefront takes code times scale in one fused operation as long as its channels' scales stay
 within a window around their first, and goes on in the general loop from the first that does not."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 from helpers import to_dev
 from paper_2211_10017_amd import binding as B
+from test_gpu_wait_guard import WAITALL, _ffn
 
 pytestmark = pytest.mark.gpu
 
@@ -61,3 +64,22 @@ def test_scales_in_and_out_of_the_window(E, rows, d, g, bits):
         # scale of one group of K / g is off by more than that in a channel by itself.
         err = (y[lo:hi].double() - want).norm(dim=0)
         assert (err <= 2.0 ** -10 * want.norm(dim=0) + 1e-12).all(), (e, int((err / (want.norm(dim=0) + 1e-12)).argmax()))
+
+
+@pytest.mark.parametrize("E,rows,d,g", [(256, (20, 40), 512, 64), (64, (70, 130), 512, 128), (64, (33, 150), 576, 64), (8, (280, 330), 2112, 64),
+                                        (8, (290, 390), 2176, 128)])
+def test_counted_waits_where_wavefronts_leave_the_window(E, rows, d, g):
+    """The general loop entered in the middle of K, by some of a block's wavefronts: both builds of the library (counted waits / waits for all loads) bit for bit."""
+    print(f"scale window, wait guard E={E} rows={rows} d={d} g={g}", flush=True)
+    rng = np.random.default_rng(E + d + g)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(E + d)
+    off = np.concatenate([[0], np.cumsum(rng.integers(*rows, E))]).astype(np.int32)
+    R = int(off[-1])
+    x = torch.randn((R, d), generator=gen, device="cuda").half()
+    (s1, p1), (s2, p2) = (B.moe_quantize_experts(_masters(gen, E, d, d, g), 4, g, want_canon=False)[1:] for _ in range(2))
+    off = to_dev(off, torch.int32)
+    plain, kernels = _ffn(B.load(), x, off, R, E, d, d, 4, g, p1, s1, p2, s2, torch.float32)
+    other, kernels2 = _ffn(ctypes.CDLL(WAITALL), x, off, R, E, d, d, 4, g, p1, s1, p2, s2, torch.float32)
+    assert kernels == kernels2 == "grouped_gemm_kernel grouped_gemm_kernel"
+    assert torch.isfinite(plain).all() and torch.equal(plain, other)
