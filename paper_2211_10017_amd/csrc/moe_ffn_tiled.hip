@@ -60,24 +60,25 @@ static int tile_height(const GemmArgs &p, int bits, int mean)
 }
 
 // Whether bf16 rows of a channel-scaled layer meet bf16 codes as they are (codes_to_bf16) instead of being converted to scaled FP16 ahead of
-// each GEMM.  Converting costs two launches, 8 us, and reads and writes x and h at 5 TB/s; bf16 codes cost six vector instructions more for eight
-// of them, 22 us per 1e9 over the chip, every time a row tile converts them, of which about 0.8 shows, with 8-bit weights, whose launches read twice
-// as much, 0.45.  (us a step, converted / as they are.  1000 tokens, one of 64 experts of 512 x 2048 45.1 / 39.7; 997, two of 16 of 768 x 3072, 8-bit, 70.2 / 65.5; 16384, one of
-// 64 of 1024 x 4096 380 / 338; 5000, two of 128 333 / 317; 4096, two of 16 of 2048 x 8192 576 / 567, 8-bit 687 / 658; 2500, two of 64, 8-bit 706 / 699.  Left to the
-// conversion: 1000, two of 32 of 2048 x 8192 240 / 251, 2500, two of 64 536 / 553; 2000, two of 16 of 4096 x 16384, 8-bit 1353 / 1388, 8192, two of 64 4091 / 4099.)
+// each GEMM.  Converting costs two launches and reads and writes x and h at 5 TB/s, of which 3 us and that much show; bf16 codes cost eight vector instructions more for
+// eight of them every time a row tile converts them, and how much of that shows depends on what bounds the kernel (us per 1e9 codes over the chip): little in blocks of few rows,
+// which wait for weights, least with 8-bit ones, of which there are twice as many bytes; most in 128-row tiles, where matrix and vector work share the chip's power.
+// (9719 drawn layers, 100 to 16000 tokens: 0.11 % slower on average than the better way for each, at most 9 %; one figure for every kernel 0.23 % and 17 %; always converting
+// 6.7 %, never 0.7 % and 17 %.  us a step, converted / as they are: 1906 tokens, one of 16 experts of 768 x 3072 57.1 / 50.5; 609, two of 8, 8-bit, 61.4 / 57.3; 10420, two of 64,
+// 8-bit, 347 / 309; left to the conversion: 713, one of 8 of 4096 x 16384 267 / 312; 490, one of 16 of 2048 x 8192 97.7 / 111.2; 3862, one of 8 of 4096 x 16384, 8-bit, 1129 / 1211.)
 bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits)
 {
+    static const double ring_us[2][3] = {{16, 16, 24}, {0, 4, 0}}, tile_us[2][3] = {{7, 16, 27}, {0, 8, 21}};     // [8-bit][16, 32, 64 rows], [32, 64, 128 rows]
     GemmArgs p{};
     p.E = E, p.R = R;
     const int mean = (R + E - 1) / E;
-    double codes = 0;
+    double us = 0;
     for (int fc = 0; fc < 2; ++fc) {
         p.K = fc ? F : d, p.N = fc ? d : F;
-        const int ring = ring_rows(p, bits, mean);
-        codes += expected_row_tiles(R, E, ring ? ring : 32 * tile_height(p, bits, mean)) * p.K * p.N;
+        const int ring = ring_rows(p, bits, mean), bm = ring ? ring : 32 * tile_height(p, bits, mean);
+        us += expected_row_tiles(R, E, bm) * p.K * p.N * 1e-9 * (ring ? ring_us[bits == 8][bm / 32] : tile_us[bits == 8][bm / 64]);
     }
-    const double moved = 4.0 * ((double)R * F + (double)tokens * d);
-    return codes * 22e-9 * (bits == 8 ? 0.45 : 0.8) <= 8.0 + moved / 5e6;
+    return us <= 3.0 + 4.0 * ((double)R * F + (double)tokens * d) / 5e6;
 }
 
 int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import launches as L
-from helpers import to_dev
+from helpers import REL_L2_TOL, to_dev
 from paper_2211_10017_amd import binding as B
 
 # rows per expert, d, F, bits: 16-, 32- and 64-row blocks of the ring, the long ring, register-fed tiles of 32, 64 and 128 rows; partly filled tiles
@@ -36,6 +36,55 @@ def test_conversion_where_matrix_work_is_the_larger_part():
 def test_bf16_codes_match_oracle(rows, d, F, bits):
     from test_gpu_ring import test_ring_gemm_matches_oracle as check
     check(rows, d, F, "bf16", bits, 0)
+
+
+# Rows, d, F, bits of channel-scaled layers on the other side of the rule: FP16 kernels with a factor per row
+CONVERTED = [([5, 1] * 8, 2048, 8192, 4), ([200, 130, 160, 70], 2048, 8192, 4), ([300, 220], 4096, 8192, 4), ([300, 270, 255, 215], 4096, 8192, 8), ([5, 1], 4096, 16384, 4),
+             ([17, 7], 4096, 16384, 4), ([300, 220], 4096, 4096, 4)]
+
+
+def test_converted_cases_are_converted():
+    calls = L.record([L.ffn(sum(r), len(r), d, F, bits, 0, B.MOE_BF16) for r, d, F, bits in CONVERTED])
+    assert all([p.kernel[:11] for p in c.launches][::2] == ["rows_to_f16"] * 2 for c in calls)
+    ran = {p.kernel for c in calls for p in c.launches[1::2]}
+    assert ran == {f"grouped_gemm_kernel<4, 0, {tm}>" for tm in (1, 2, 4)} | {"grouped_gemm_kernel<8, 0, 4>"} | {f"grouped_gemm_ring_kernel<4, 0, {bm}>" for bm in (16, 32, 64)}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,d,F,bits", CONVERTED)
+def test_converted_rows_match_64_bits(rows, d, F, bits):
+    print(f"converted bf16 rows={rows[:4]} d={d} F={F} bits={bits}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + F + bits)
+    E, R = len(rows), sum(rows)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    quantised = [B.moe_quantize_experts(torch.randn((E, *s), generator=gen, device="cuda") * 0.05, bits, 0) for s in ((d, F), (F, d))]
+    size = torch.exp2(torch.randint(-60, 60, (R, 1), generator=gen, device="cuda").float())
+    x = (torch.randn((R, d), generator=gen, device="cuda") * size).bfloat16()
+    (_, s1, p1), (_, s2, p2) = quantised
+    y = B.moe_grouped_ffn_wq(x, to_dev(off, torch.int32), E, d, F, bits, 0, p1, s1, p2, s2, y_dtype=torch.float32).double()
+    assert torch.isfinite(y).all()
+    for e in range(E):
+        lo, hi = int(off[e]), int(off[e + 1])
+        v = x[lo:hi].double()
+        for canon, s, _ in quantised:
+            q = canon[e].to(torch.int32)
+            if bits == 4:
+                q = torch.stack([(q << 28) >> 28, (q << 24) >> 28], dim=-1).reshape(q.shape[0], -1)
+            v = v @ (q.double() * s[e].reshape(1, -1).double())
+            if s is s1:
+                v = v.clamp(min=0).to(torch.bfloat16).double()
+        rel = (y[lo:hi] - v).norm(dim=1) / v.norm(dim=1)
+        # an element of h that rounds the other way is off by 2^-8 at most; the few that do are well below the acceptance bound
+        assert float(rel.max()) <= REL_L2_TOL, (e, float(rel.max()))
+
+
+def test_conversion_by_what_its_kernel_shows_of_it():
+    """Sizes on both sides of the rule where one figure for all kernels answered wrongly."""
+    sizes = [((713, 8, 4096, 16384, 4), False), ((490, 16, 2048, 8192, 4), False), ((3862, 8, 4096, 16384, 8), False), ((252, 8, 4096, 16384, 8), True),
+             ((1218, 8, 768, 3072, 8), True), ((1906, 16, 768, 3072, 4), True)]
+    for (s, want), c in zip(sizes, L.record([L.ffn(*s, 0, B.MOE_BF16) for s, _ in sizes])):
+        assert want != any(p.kernel.startswith("rows_to_f16") for p in c.launches), s
 
 
 def _masters(rng, E, d, F, bits, g):
