@@ -254,3 +254,11 @@ def test_large_group_scaled_experts_with_many_rows_stay_in_row_tiles():
     """Crowded routing would read their weights for every sixteen rows."""
     assert not _pays(256, 2, 64, 4096, 8192, 4, 128) and not _pays(256, 2, 64, 4096, 16384, 4, 128) and not _pays(192, 2, 64, 4096, 8192, 4, 128)
     assert _pays(160, 2, 64, 4096, 8192, 4, 128) and _pays(64, 2, 64, 4096, 16384, 4, 128) and _pays(256, 2, 64, 2048, 8192, 4, 128)
+
+
+def test_the_conversion_of_bf16_rows_is_compared_in_every_form():
+    """Each row length of test_gpu_indexed.py runs the form that it stands for, in calls that convert."""
+    from test_gpu_indexed import LENGTHS
+    converted = L.record([L.ffn(9, 2, 64, K, 8, 64, B.MOE_BF16) for K, _ in LENGTHS])
+    assert [c.launches[2].kernel for c in converted] == [f"rows_to_f16_kernel<{256 if 4096 < K <= 16384 else 64}, {nv}>" for K, nv in LENGTHS]
+    assert not any(p.kernel.startswith("rows_to_f16") for c in L.record([L.ffn(9, 2, 64, K, 8, 0, B.MOE_BF16) for K, _ in LENGTHS]) for p in c.launches)

@@ -45,14 +45,18 @@ def test_indexed_layer_equals_permuted_copies(T, k, E, d, F, bits, g, act, prune
         assert act == torch.bfloat16 and torch.equal(out_a, out_b)
 
 
-@pytest.mark.parametrize("K", [1024, 1088, 4096, 4160, 16384, 16448])       # two, eight 16-byte vectors per lane; a block per row; read twice
-def test_bf16_rows_of_every_length(K):
+LENGTHS = [(1024, 2), (1088, 8), (4096, 8), (4160, 8), (16384, 8), (16448, 0)]       # two, eight 16-byte vectors per lane; a block per row; read twice
+
+
+@pytest.mark.parametrize("g", [0, 64])          # as they are; converted (test_dispatch_cpu.py: by which form)
+@pytest.mark.parametrize("K", [K for K, _ in LENGTHS])
+def test_bf16_rows_of_every_length(K, g):
     rows = [3, 6]
-    x, off, w, ((s1, p1), (s2, p2)), E, R = _case(rows, 64, K, 8, 0, "bf16", K)
-    y = B.moe_grouped_ffn_wq(x, to_dev(off, torch.int32), E, 64, K, 8, 0, p1, s1, p2, s2, y_dtype=torch.float32)
+    x, off, w, ((s1, p1), (s2, p2)), E, R = _case(rows, 64, K, 8, g, "bf16", K)
+    y = B.moe_grouped_ffn_wq(x, to_dev(off, torch.int32), E, 64, K, 8, g, p1, s1, p2, s2, y_dtype=torch.float32)
     torch.cuda.synchronize()
-    (q1, o1), (q2, o2) = (oracle.quantize(m, 8, 0) for m in w)
-    want = oracle.grouped_ffn(x.float().cpu().numpy(), off, q1, o1, q2, o2, 0, oracle.BF16)
+    (q1, o1), (q2, o2) = (oracle.quantize(m, 8, g) for m in w)
+    want = oracle.grouped_ffn(x.float().cpu().numpy(), off, q1, o1, q2, o2, g, oracle.BF16)
     max_abs, rel = error_metrics(y.cpu().numpy(), want)
     assert max_abs <= MAX_ABS_TOL * max(1.0, float(np.abs(want).max()) / 8) and rel <= REL_L2_TOL
 
