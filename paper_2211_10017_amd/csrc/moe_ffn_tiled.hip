@@ -62,10 +62,11 @@ static int tile_height(const GemmArgs &p, int bits, int mean)
 // Whether bf16 rows of a channel-scaled layer meet bf16 codes as they are (codes_to_bf16) instead of being converted to scaled FP16 ahead of
 // each GEMM.  Converting costs two launches and reads and writes x and h at 5 TB/s, of which 3 us and that much show; bf16 codes cost eight vector instructions more for
 // eight of them every time a row tile converts them, and how much of that shows depends on what bounds the kernel (us per 1e9 codes over the chip): little in blocks of few rows,
-// which wait for weights, least with 8-bit ones, of which there are twice as many bytes; most in 128-row tiles, where matrix and vector work share the chip's power.
+// which wait for weights, least with 8-bit ones, of which there are twice as many bytes, unless a block has its compute unit to itself; most in 128-row tiles, where matrix and
+// vector work share the chip's power.
 // (9719 drawn layers, 100 to 16000 tokens: 0.11 % slower on average than the better way for each, at most 9 %; one figure for every kernel 0.23 % and 17 %; always converting
 // 6.7 %, never 0.7 % and 17 %.  us a step, converted / as they are: 1906 tokens, one of 16 experts of 768 x 3072 57.1 / 50.5; 609, two of 8, 8-bit, 61.4 / 57.3; 10420, two of 64,
-// 8-bit, 347 / 309; left to the conversion: 713, one of 8 of 4096 x 16384 267 / 312; 490, one of 16 of 2048 x 8192 97.7 / 111.2; 3862, one of 8 of 4096 x 16384, 8-bit, 1129 / 1211.)
+// 8-bit, 347 / 309; left to the conversion: 713, one of 8 of 4096 x 16384 267 / 312; 490, one of 16 of 2048 x 8192 97.7 / 111.2; 3862, one of 8 of 4096 x 16384, 8-bit, 1129 / 1211, 7 133 / 149.)
 bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits)
 {
     static const double ring_us[2][3] = {{16, 16, 24}, {0, 4, 0}}, tile_us[2][3] = {{7, 16, 27}, {0, 8, 21}};     // [8-bit][16, 32, 64 rows], [32, 64, 128 rows]
@@ -76,7 +77,9 @@ bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits)
     for (int fc = 0; fc < 2; ++fc) {
         p.K = fc ? F : d, p.N = fc ? d : F;
         const int ring = ring_rows(p, bits, mean), bm = ring ? ring : 32 * tile_height(p, bits, mean);
-        us += expected_row_tiles(R, E, bm) * p.K * p.N * 1e-9 * (ring ? ring_us[bits == 8][bm / 32] : tile_us[bits == 8][bm / 64]);
+        const double tiles = expected_row_tiles(R, E, bm);
+        us += tiles * p.K * p.N * 1e-9 * (ring ? ring_us[bits == 8][bm / 32] : tile_us[bits == 8][bm / 64]);
+        if (bits == 8 && ring == 16 && tiles * ((p.N + 127) / 128) <= 256) us += p.K * 4e-4;      // nothing beside the lone block's chain
     }
     return us <= 3.0 + 4.0 * ((double)R * F + (double)tokens * d) / 5e6;
 }

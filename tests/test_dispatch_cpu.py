@@ -261,4 +261,4 @@ def test_the_conversion_of_bf16_rows_is_compared_in_every_form():
     from test_gpu_indexed import LENGTHS
     converted = L.record([L.ffn(9, 2, 64, K, 8, 64, B.MOE_BF16) for K, _ in LENGTHS])
     assert [c.launches[2].kernel for c in converted] == [f"rows_to_f16_kernel<{256 if 4096 < K <= 16384 else 64}, {nv}>" for K, nv in LENGTHS]
-    assert not any(p.kernel.startswith("rows_to_f16") for c in L.record([L.ffn(9, 2, 64, K, 8, 0, B.MOE_BF16) for K, _ in LENGTHS]) for p in c.launches)
+    assert not any(p.kernel.startswith("rows_to_f16") for c in L.record([L.ffn(9, 2, 64, K, 8, 0, B.MOE_BF16) for K in (1024, 1088, 4096, 4160)]) for p in c.launches)

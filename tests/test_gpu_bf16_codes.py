@@ -81,7 +81,7 @@ def test_converted_rows_match_64_bits(rows, d, F, bits):
 
 def test_conversion_by_what_its_kernel_shows_of_it():
     """Sizes on both sides of the rule where one figure for all kernels answered wrongly."""
-    sizes = [((713, 8, 4096, 16384, 4), False), ((490, 16, 2048, 8192, 4), False), ((3862, 8, 4096, 16384, 8), False), ((252, 8, 4096, 16384, 8), True),
+    sizes = [((713, 8, 4096, 16384, 4), False), ((490, 16, 2048, 8192, 4), False), ((3862, 8, 4096, 16384, 8), False), ((252, 8, 4096, 16384, 8), True), ((7, 8, 4096, 16384, 8), False), ((12, 32, 2048, 8192, 8), False), ((65, 8, 1024, 4096, 8), True),
              ((1218, 8, 768, 3072, 8), True), ((1906, 16, 768, 3072, 4), True)]
     for (s, want), c in zip(sizes, L.record([L.ffn(*s, 0, B.MOE_BF16) for s, _ in sizes])):
         assert want != any(p.kernel.startswith("rows_to_f16") for p in c.launches), s

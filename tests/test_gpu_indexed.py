@@ -48,7 +48,7 @@ def test_indexed_layer_equals_permuted_copies(T, k, E, d, F, bits, g, act, prune
 LENGTHS = [(1024, 2), (1088, 8), (4096, 8), (4160, 8), (16384, 8), (16448, 0)]       # two, eight 16-byte vectors per lane; a block per row; read twice
 
 
-@pytest.mark.parametrize("g", [0, 64])          # as they are; converted (test_dispatch_cpu.py: by which form)
+@pytest.mark.parametrize("g", [0, 64])          # as they are up to 4160; converted (test_dispatch_cpu.py: by which form)
 @pytest.mark.parametrize("K", [K for K, _ in LENGTHS])
 def test_bf16_rows_of_every_length(K, g):
     rows = [3, 6]
