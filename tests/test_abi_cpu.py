@@ -124,3 +124,14 @@ def test_layer_level_limits_are_checked_before_anything_is_allocated(lib):
     for d, F in ((96, 128), (64, 100), (0, 128)):
         with pytest.raises(binding.MoeError, match="multiples of 64"):
             MoEExpertLayer(16, d, F, 8, 1, 4, device="cpu")
+
+
+def test_the_stream_handle_does_without_torchs_private_functions(monkeypatch):
+    class Stream:
+        cuda_stream = 42
+
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: Stream)
+    for missing in ("_raw_stream", "_raw_device"):
+        with monkeypatch.context() as m:
+            m.setattr(binding, missing, None)
+            assert binding.current_stream_handle() == 42

@@ -43,3 +43,10 @@ def test_layer_step_replays_from_a_graph(T, k, E, d, F, bits):
             torch.cuda.synchronize()
             assert torch.equal(layer.out, want), f"replay differs from the eager call ({kernels})"
     print(f"   6 replays bit-identical to the eager calls ({kernels})", flush=True)
+
+
+def test_the_stream_handle_is_the_current_streams():
+    side = torch.cuda.Stream()
+    for stream in (torch.cuda.current_stream(), side):
+        with torch.cuda.stream(stream):
+            assert B.current_stream_handle() == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
