@@ -223,7 +223,7 @@ int moe_grouped_ffn_wq_routed(const void *x, int act_dtype, const int32_t *perm_
 
 /*
  * The same call for every size and for bf16 rows as well (k must divide R: row r of the sorted order is token
- * perm_src[r] / k).  Both GEMMs run in row tiles whatever the sizes; bf16 tokens are converted once, not once per expert.
+ * perm_src[r] / k).  Both GEMMs run in row tiles whatever the sizes; bf16 tokens, where they are converted, are once, not once per expert.
  * moe_grouped_ffn_wq_indexed_pays returns 1 when it is also the faster way for these sizes (MoEExpertLayer asks this).
  */
 int moe_grouped_ffn_wq_indexed_pays(int R, int E, int max_rows_per_expert, int d, int F, int bits,

@@ -488,32 +488,34 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
     return round_up(decode_ffn_partial_bytes(T * k, d, F, decode_slice_width(T * k, E, F)), 256);
 }
 
-// Whether a layer should take the sliced call (steps in us of the routes below against it, uniform routing; of 700 sizes, most of them drawn where this
-// rule is in doubt, it takes two thirds, 1.36 times as fast on average; 22 of them are 2 to 13 % slower):
+// Whether a layer should take the sliced call (steps in us of the routes below against it, uniform routing; of 13898 drawn sizes of 4 to 512 assignments
+// it takes 9964, 1.40 times as fast on average; 263 of them, most with up to one row per expert, are 2 to 41 % slower; 2319 of those it leaves would be 1.35 times
+// as fast):
 //  - up to eight assignments per expert: a block takes sixteen rows, and experts with more stream their weights again (61 tokens, two of
-//    eight experts of 4096 x 16384 8-bit 188 and 318; 134 tokens on 16 of 512 x 2048 21.0 and 24.1; 5 per expert of 1024 x 4096 44 and 41).
+//    eight experts of 4096 x 16384 8-bit 182 and 320; 5 per expert of 1024 x 4096 8-bit 57 and 61).
 //    Rows on 4-bit codes, whose blocks then take thirty-two: up to sixteen, 150 MB of weights and a d_ff of twice d (192 tokens,
-//    two of 32 experts of 1024 x 4096 51.6 and 45.2, 144 on 16 39.7 and 32.0; 242 tokens, two of 32 of 2048 x 8192 130 and 143; 191 of 1536 x
-//    2048 42.6 and 43.5), with group scales twelve, 110 MB and four times d (71 tokens, two of 16 of 1024 x 4096 48.0 and 36.9; 154, two of 32
-//    51.6 and 52.3; 96, two of 16 of 2048 x 4096 55 and 58), but not where one and a bit blocks per compute unit would keep some busy
-//    twice as long as others (250 tokens, two of 60 of 1536 x 1280, 300 blocks, 54.5 and 58.3);
+//    two of 32 experts of 1024 x 4096 48.1 and 43.1, bf16 52.9 and 50.5; 242 tokens, two of 32 of 2048 x 8192 122 and 138; 191 of 1536 x
+//    2048 40.7 and 41.2; left out 144, two of 16 of 1024 x 4096, 40.0 and 33.9, bf16 44.3 and 38.2), with group scales twelve, 110 MB and four times d (71 tokens, two of 16 of
+//    1024 x 4096 42.6 and 28.1, bf16 48.5 and 32.1; 96, two of 16 of 2048 x 4096 51.0 and 52.5; left out 154, two of 32 of 1024 x 4096, 53.7 and 45.9), but not where one and a
+//    bit blocks per compute unit would keep some busy twice as long as others (250 tokens, two of 60 of 1536 x 1280, 300 blocks, 53.6 and 52.4);
 //  - the partial sums of a slice, rows x d x 4 bytes, well below its weights, and no thousands of slices of 64 channels, where d_ff leaves no
-//    wider ones: a block's start then costs more than its few weights (218 tokens on 115 of 256 x 5312, group scales, 8100 blocks, 65 and 101;
-//    139 on 131 of 640 x 4544, 6100, 81 and 110; 178 on 80 of 384 x 3392, 3800, 40 and 44; 43 on 71 of 448 x 6720, 3400, 17 % faster);
+//    wider ones: a block's start then costs more than its few weights (218 tokens on 115 of 256 x 5312, group scales, 8100 blocks, 58 and 97;
+//    139 on 131 of 640 x 4544, 6100, 81 and 113; 178 on 80 of 384 x 3392, 3800, 40 and 45; 43 on 71 of 448 x 6720, 3400, 48 and 40; small layers lose by the
+//    first line what they would gain: 134 on 16 of 512 x 2048 25.7 and 15.7);
 //  - up to 300 MB of weights: beyond, the launch's fixed parts count little and the ring's loads into LDS keep more in flight (30 tokens
-//    on 32 experts of 4096 x 16384 8-bit 457 and 486; 240 on 55 of 4096 x 4096 8-bit, 1.5 GB, 257 and 299);
+//    on 32 experts of 4096 x 16384 8-bit 398 and 388; 240 on 55 of 4096 x 4096 8-bit, 1.8 GB, 314 and 370);
 //  - FP16 rows on 8-bit codes with channel scales, more rows than experts: not from 140 MB on where the routes below stream and rows are long
-//    enough for that to go well (40 / 60 / 100 / 128 tokens, two of 32 of 1024 x 4096 53.6 / 56.4 / 58.5 / 59.2 and 53.5 / 57.3 / 67.6 / 69.0;
-//    120 on 22 of 2048 x 1536 49 and 54; but 512 x 4096, 128 on 64, 63 and 56), from 180 MB on not for the longest rows (64 tokens on 8 of 4096 x
-//    4096 65 and 85), and fewer narrow slices (100 tokens, two of 67 of 512 x 2112, 2100 slices, 41 and 50).  Where row tiles run
-//    below, sliced at any of these sizes (60 tokens, two of 32 of 1088 x 4096 74 and 57, of 960 x 4096 61 and 52; 160, two of 128 of 512 x 2048 63 and 53);
-//  - FP16 rows with group scales, whose scales the ring multiplies into the weights, beyond 300 MB too (64 tokens, 64 experts of 4096 x 16384 803 and 732),
-//    but experts of more than 30 MB only up to five rows each: there little is left to gain (256 tokens, two of 64 of 4096 x 8192 480 and 459, 192
-//    482 and 439, 128 477 and 422; of 2048 x 8192 259 and 230) and crowded routing, whose blocks read an expert's weights for every sixteen rows, loses most (256 on two of
+//    enough for that to go well (40 / 60 / 100 / 128 tokens, two of 32 of 1024 x 4096 55.0 / 55.2 / 58.4 / 62.8 and 54.2 / 55.5 / 65.9 / 72.6;
+//    40, one of 32, 44.5 and 45.6; 120, two of 22 of 2048 x 1536 52 and 60; but 512 x 4096, 128, two of 64, 61 and 55), from 180 MB on not for the longest rows (64 tokens on 8 of 4096 x
+//    4096 63 and 84), and fewer narrow slices (100 tokens, two of 67 of 512 x 2112, 2100 slices, 44 and 49).  Where row tiles run
+//    below, sliced at any of these sizes (60 tokens, two of 32 of 1088 x 4096 72 and 56, of 960 x 4096 58 and 49; 160, two of 128 of 512 x 2048 62 and 52);
+//  - FP16 rows with group scales, whose scales the ring multiplies into the weights, beyond 300 MB too (64 tokens, 64 experts of 4096 x 16384 755 and 703),
+//    but experts of more than 30 MB only up to five rows each: there little is left to gain (256 tokens, two of 64 of 4096 x 8192 445 and 445, 192
+//    442 and 431, 128 436 and 419; of 2048 x 8192 237 and 242) and crowded routing, whose blocks read an expert's weights for every sixteen rows, loses most (256 on two of
 //    4096 x 8192 137 and 214, 192 130 and 188, 128 115 and 127, on eight 195 and 297, 160 and 221, 150 and 188, by a gate of graded popularity
 //    391 and 420, 327 and 362, 258 and 288);
 //  - wherever the gated call would run the decode kernel: it is the same one (128 tokens, two of 128 experts of 1024 x 4096, 460 MB, 104 in
-//    either call, 131 to 141 in row tiles; 60 on 8 22, where two streaming launches take 26).
+//    either call; 60 on 8 21).
 extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
 {
     using namespace moe;

@@ -7,7 +7,7 @@
 // sixteen or thirty-two of its rows, slice of 64 CW channels of d_ff), one block of eight wavefronts, and the grid holds a
 // block per item for any routing, dealt out by the hardware as blocks end (the few without an item find that out and end).  The block
 // computes its slice of h = act(x W1 + b1) - a wavefront 64 channels over a CW-th part of an eighth of K, the parts meet in LDS -, keeps it in LDS
-// as fp16 and multiplies it at once with the matching rows of W2 (a wavefront an eighth of the output channels): h never goes to memory.
+// in the rows' type and multiplies it at once with the matching rows of W2 (a wavefront an eighth of the output channels): h never goes to memory.
 // What is left over is a partial sum of y per slice, stored as fp32 rows; decode_reduce_kernel then adds the
 // slices in a fixed order, applies W2's channel scale, the bias and the gate scale, and sums a token's experts in slot
 // order into the layer output (no atomics, nothing to clear, nothing to wait for inside a launch).

@@ -97,8 +97,8 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     // second accumulator set, so it is built for row tiles of at most 64 rows.
     constexpr bool ACC = SMODE == SCALE_GROUP_ACC;
     // 4-bit codes that go in unscaled are taken the same way, as q 2^-9 (2^24 itself is no FP16 number), which the factor at the end makes up for:
-    // two-operand masks instead of v_and_or_b32 with three registers.  4096 bf16 tokens, two of 16 experts of 2048 x 8192, a step 554 -> 552 us, 16384 of
-    // 1024 x 4096 557 -> 555; bf16 with groups of 128, 4096 x 16384, 4601 -> 4583.
+    // two-operand masks instead of v_and_or_b32 with three registers.  4096 FP16 tokens, two of 16 experts of 2048 x 8192, a step 501 -> 498 us, 16384, one of 64 of
+    // 1024 x 4096 326.3 -> 325.3; 8192 bf16 tokens, two of 64 of 4096 x 16384, which are converted, 3859 and 3859, with groups of 128 4563 -> 4534.
     constexpr bool EXACT4 = BITS == 4 && (SMODE == SCALE_CHANNEL || ACC);
     static_assert(!ACC || TM <= 2, "two accumulator sets fit for TM <= 2 only");
     float16_t accg[ACC ? TM : 1][kTN];
