@@ -236,6 +236,24 @@ int moe_grouped_ffn_wq_indexed(const void *x, int act_dtype, const int32_t *perm
                                int out_dtype, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * moe_permute (index only) and moe_grouped_ffn_wq_indexed in one call, for up to 4096 assignments and 1024 experts: the blocks of the first GEMM
+ * sort the gate's output for themselves (Sec. 3.3 steps 2 and 3) and write the index arrays on the way, so the index is no launch of its own.
+ *   x [T,d] (un-permuted); expert_idx [T*k] from moe_gate_topk (E = pruned row; other entries outside [0,E] are treated as
+ *   0 or E); expert_scale [T] fp32 (k = 1 only) or NULL, and out, as for moe_grouped_ffn_wq_indexed: [T,d] when expert_scale
+ *   is given, where the rows of pruned tokens are not written, else y_perm [T*k,d]; perm_src, inv_perm,
+ *   expert_offsets as moe_permute writes them; workspace as for moe_grouped_ffn_wq with R = T*k.
+ * moe_grouped_ffn_wq_unsorted_supported returns 1 when a call with these sizes is taken; it otherwise returns MOE_ERR_UNSUPPORTED.
+ * moe_grouped_ffn_wq_unsorted_pays: 1 when it is also the faster way than the two calls (MoEExpertLayer asks this).
+ */
+int moe_grouped_ffn_wq_unsorted_supported(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype);
+int moe_grouped_ffn_wq_unsorted_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype);
+int moe_grouped_ffn_wq_unsorted(const void *x, int act_dtype, const int32_t *expert_idx, const float *expert_scale,
+                                int T, int k, int E, int d, int F, int bits, int group_size, int activation,
+                                const void *w1_packed, const void *s1, const void *b1, const void *w2_packed, const void *s2,
+                                const void *b2, void *out, int out_dtype, int32_t *perm_src, int32_t *inv_perm,
+                                int32_t *expert_offsets, void *workspace, size_t workspace_bytes, void *stream);
+
+/*
  * moe_permute and moe_grouped_ffn_wq in one call, for decode-sized batches (Sec. 3.3 steps 2 and
  * 3; the stable sort by expert is rebuilt inside the first GEMM).  fc1's blocks count the
  * assignments of their expert and of the experts before it from expert_idx, fetch their rows

@@ -22,6 +22,7 @@ EXPORTS = ["moe_last_error", "moe_last_ffn_kernels", "moe_device_info", "moe_abi
            "moe_permute_workspace_bytes", "moe_permute", "moe_grouped_ffn_wq_workspace_bytes",
            "moe_grouped_ffn_wq", "moe_combine", "moe_pack_fp16_experts", "moe_grouped_gemm_wq",
            "moe_grouped_ffn_wq_routed_supported", "moe_grouped_ffn_wq_routed", "moe_grouped_ffn_wq_indexed", "moe_grouped_ffn_wq_indexed_pays",
+           "moe_grouped_ffn_wq_unsorted_supported", "moe_grouped_ffn_wq_unsorted_pays", "moe_grouped_ffn_wq_unsorted",
            "moe_grouped_ffn_wq_gated_supported", "moe_grouped_ffn_wq_gated_pays", "moe_grouped_ffn_wq_gated",
            "moe_grouped_ffn_wq_sliced_workspace_bytes", "moe_grouped_ffn_wq_sliced_pays", "moe_grouped_ffn_wq_sliced",
            "moe_grouped_ffn_wq_noalloc_max_bytes", "moe_grouped_ffn_wq_noalloc"]
@@ -79,6 +80,13 @@ def load():
                                               vp, sz, vp]
     lib.moe_grouped_ffn_wq_indexed_pays.restype = i
     lib.moe_grouped_ffn_wq_indexed_pays.argtypes = [i, i, i, i, i, i, i, i]
+    lib.moe_grouped_ffn_wq_unsorted_supported.restype = i
+    lib.moe_grouped_ffn_wq_unsorted_supported.argtypes = [i, i, i, i, i, i, i, i]
+    lib.moe_grouped_ffn_wq_unsorted_pays.restype = i
+    lib.moe_grouped_ffn_wq_unsorted_pays.argtypes = [i, i, i, i, i, i, i, i]
+    lib.moe_grouped_ffn_wq_unsorted.restype = i
+    lib.moe_grouped_ffn_wq_unsorted.argtypes = [vp, i, vp, vp, i, i, i, i, i, i, i, i, vp, vp, vp, vp, vp, vp, vp, i, vp, vp, vp,
+                                                vp, sz, vp]
     lib.moe_grouped_ffn_wq_gated_supported.restype = i
     lib.moe_grouped_ffn_wq_gated_supported.argtypes = [i, i, i, i, i, i, i, i]
     lib.moe_grouped_ffn_wq_gated_pays.restype = i
@@ -319,6 +327,33 @@ def moe_grouped_ffn_wq_routed(x, perm_src, k: int, expert_offsets, E: int, d: in
 def moe_grouped_ffn_wq_indexed_pays(R: int, E: int, max_rows_per_expert: int, d: int, F: int, bits: int, group_size: int, act_dtype) -> bool:
     """Whether fetching the rows through the routing index is the faster way for these sizes."""
     return bool(load().moe_grouped_ffn_wq_indexed_pays(R, E, max_rows_per_expert, d, F, bits, group_size, _DT[act_dtype]))
+
+
+def moe_grouped_ffn_wq_unsorted_pays(T: int, k: int, E: int, d: int, F: int, bits: int, group_size: int, act_dtype) -> bool:
+    """Whether the unsorted call is taken and the faster way for these sizes."""
+    return bool(load().moe_grouped_ffn_wq_unsorted_pays(T, k, E, d, F, bits, group_size, _DT[act_dtype]))
+
+
+def moe_grouped_ffn_wq_unsorted(x, expert_idx, E: int, d: int, F: int, bits: int, group_size: int, w1_packed, s1, w2_packed, s2,
+                                b1=None, b2=None, expert_scale=None, out_dtype=None, workspace=None, activation: str = "relu"):
+    """Index and FFN in row tiles in one call.  Returns (y_perm [R,d] or, with expert_scale, out [T,d], perm_src, inv_perm, expert_offsets)."""
+    T, k = expert_idx.shape
+    R = T * k
+    dev = x.device
+    out = torch.empty((T if expert_scale is not None else R, d), dtype=out_dtype or x.dtype, device=dev)
+    perm_src = torch.empty(R, dtype=torch.int32, device=dev)
+    inv_perm = torch.empty(R, dtype=torch.int32, device=dev)
+    offsets = torch.empty(E + 1, dtype=torch.int32, device=dev)
+    if workspace is None:
+        workspace = torch.empty(moe_grouped_ffn_wq_workspace_bytes(R, d, F, E, x.dtype), dtype=torch.uint8, device=dev)
+    rc = load().moe_grouped_ffn_wq_unsorted(
+        _ptr(x, (torch.float16, torch.bfloat16), "x"), _DT[x.dtype], _ptr(expert_idx, torch.int32, "expert_idx"),
+        _ptr(expert_scale, torch.float32, "expert_scale"), T, k, E, d, F, bits, group_size, ACTIVATIONS[activation],
+        _ptr(w1_packed, torch.uint8, "w1_packed"), _ptr(s1, torch.float16, "s1"), _ptr(b1, torch.float16, "b1"),
+        _ptr(w2_packed, torch.uint8, "w2_packed"), _ptr(s2, torch.float16, "s2"), _ptr(b2, torch.float16, "b2"), _ptr(out),
+        _DT[out.dtype], _ptr(perm_src), _ptr(inv_perm), _ptr(offsets), _ptr(workspace), workspace.numel(), _stream())
+    _check(rc, "moe_grouped_ffn_wq_unsorted")
+    return out, perm_src, inv_perm, offsets
 
 
 def moe_grouped_ffn_wq_gated_supported(T: int, k: int, E: int, d: int, F: int, bits: int, group_size: int, act_dtype) -> int:

@@ -194,7 +194,7 @@ static int run_gemm(moe::GemmArgs g, int bits, int smode, bool bf, bool tiles_on
                                                         : four_call_kernel(g.R, g.E, max_rows, g.K, g.N, bits, smode, bf);
     if (kernel != GEMM_TILED) note_kernel(kernel == GEMM_STREAM_UNROLLED ? "stream_unrolled_kernel" : "stream_gemm_kernel");
     if (kernel == GEMM_STREAM_UNROLLED) return launch_stream_unrolled(g, bits, max_rows, s);
-    if (g.gate_idx || g.out_add) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_gated: K=%d does not run in the straight-line kernel with these sizes", g.K);
+    if (!tiles_only && (g.gate_idx || g.out_add)) return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_gated: K=%d does not run in the straight-line kernel with these sizes", g.K);
     if (kernel == GEMM_STREAM_LOOP) return launch_stream_gemm(g, bits, smode, max_rows, s);
     // Everything else runs in row tiles, experts with a handful of rows included: their tiles skip
     // the row blocks that hold no rows and stream the weights as fast as the streaming kernel would
@@ -220,11 +220,11 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
                     size_t workspace_bytes, void *stream,
                     const int32_t *perm_src, int k, const float *expert_scale,
                     const int32_t *gate_idx = nullptr, int32_t *perm_src_out = nullptr, int32_t *inv_perm_out = nullptr,
-                    int32_t *offsets_out = nullptr)
+                    int32_t *offsets_out = nullptr, bool unsorted = false)
 {
     using namespace moe;
     // decode-sized batch with everything fused: one streaming launch for the sort and both GEMMs, then the slice reduction
-    const bool decode = gate_idx && expert_scale && act_dtype == MOE_F16 && group_size == 0 && gated_decode(R, E, d, F, bits);
+    const bool decode = gate_idx && !unsorted && expert_scale && act_dtype == MOE_F16 && group_size == 0 && gated_decode(R, E, d, F, bits);
     const bool partial_only = !y_perm && decode;        // (on that path NULL means "leave out the slice reduction")
     if (!expert_offsets || !w1_packed || !s1 || !w2_packed || !s2 || (R != 0 && (!x_perm || (!y_perm && !partial_only))))
         return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq: NULL pointer");
@@ -274,7 +274,9 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     // activations and group scales the weights go in as an exact two-term FP16 sum, because h
     // is rounded to 8 bits afterwards and a 2^-11 weight rounding would show through.
     GemmArgs g1{};
-    const bool convert = bf && (grouped || !bf16_codes_pay(R, perm_src ? R / k : R, E, d, F, bits));
+    const bool tiles_only = perm_src || unsorted;
+    const int tokens = tiles_only ? R / k : R;                  // rows of x
+    const bool convert = bf && (grouped || !bf16_codes_pay(R, tokens, E, d, F, bits));
     g1.a = (const uint16_t *)x_perm; g1.row_pow = convert ? pow_x : nullptr; g1.offsets = expert_offsets;
     g1.wq = (const uint8_t *)w1_packed; g1.scales = (const __half *)s1; g1.bias = (const __half *)b1;
     g1.out = h; g1.E = E; g1.R = R; g1.K = d; g1.N = F; g1.g = grouped ? group_size : d;
@@ -283,18 +285,18 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     if (gate_idx) {     // decode-sized: fc1 rebuilds the permutation from the gate's output and writes the index arrays
         g1.gate_idx = gate_idx; g1.n_assign = R; g1.gate_k = k;
         g1.perm_src_out = perm_src_out; g1.inv_perm_out = inv_perm_out; g1.offsets_out = offsets_out;
-        if (expert_scale) { g1.zero_out = (float *)y_perm; g1.zero_count = (long)(R / k) * d; }   // fc2 adds into it
+        if (expert_scale && !unsorted) { g1.zero_out = (float *)y_perm; g1.zero_count = (long)(R / k) * d; }   // fc2 adds into it
     }
     if (convert) {      // bf16 rows of group-scaled or large layers: converted to power-of-two scaled FP16 rows first, then the GEMM of FP16 rows
         uint16_t *x16 = (uint16_t *)(wsb + ws.x16_off);
         // (through the routing index: every token's row once, R / k of them)
-        int rc = rows_to_f16((const uint16_t *)x_perm, x16, perm_src ? R / k : R, d, pow_x, s);
+        int rc = rows_to_f16((const uint16_t *)x_perm, x16, tokens, d, pow_x, s);
         if (rc) return rc;
         g1.a = x16;
     }
     // (groups of 128: exact codes, group sums folded in fp32; other group sizes: the two-term form, in the LDS ring exact codes as well)
     const int channel = bf && !convert ? SCALE_CHANNEL_BF16 : SCALE_CHANNEL, smode1 = !grouped ? channel : !bf ? SCALE_GROUP : group_size == 128 ? SCALE_GROUP_ACC : SCALE_GROUP_SPLIT;
-    int rc = run_gemm(g1, bits, smode1, bf, perm_src != nullptr, max_rows, s);
+    int rc = run_gemm(g1, bits, smode1, bf, tiles_only, max_rows, s);
     if (rc) return rc;
 
     // fc2: y = h @ deq(W2) + b2
@@ -305,16 +307,16 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     g2.out_dtype = y_dtype; g2.act = MOE_ACT_NONE;
     g2.a_src = nullptr;
     g2.gate_idx = nullptr; g2.zero_out = nullptr;
-    if (gate_idx && expert_scale) {     // un-permute fused into fc2: fc1 clears out, fc2 adds scale * y into the tokens' rows
+    if (gate_idx && expert_scale && !unsorted) {     // un-permute fused into fc2: fc1 clears out, fc2 adds scale * y into the tokens' rows
         g2.out_dst = perm_src_out; g2.out_scale = expert_scale; g2.out_add = 1; g2.out_div = k;
     } else if (expert_scale) {
-        g2.out_dst = perm_src; g2.out_scale = expert_scale;
+        g2.out_dst = unsorted ? perm_src_out : perm_src; g2.out_scale = expert_scale;
     }
     if (convert) {      // h, which fc1 rounded to bf16 (A13), in place
         rc = rows_to_f16((const uint16_t *)h, (uint16_t *)h, R, F, pow_h, s);
         if (rc) return rc;
     }
-    return run_gemm(g2, bits, grouped ? SCALE_GROUP : channel, bf, perm_src != nullptr, max_rows, s);
+    return run_gemm(g2, bits, grouped ? SCALE_GROUP : channel, bf, tiles_only, max_rows, s);
 }
 
 extern "C" int moe_grouped_ffn_wq(const void *x_perm, int act_dtype, const int32_t *expert_offsets, int R,
@@ -431,6 +433,47 @@ extern "C" int moe_grouped_ffn_wq_indexed(const void *x, int act_dtype, const in
         return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_indexed: the fused un-permute needs k = 1 (one expert per token)");
     return ffn_impl(x, act_dtype, expert_offsets, R, E, max_rows_per_expert, d, F, bits, group_size, activation, w1_packed, s1, b1,
                     w2_packed, s2, b2, out, out_dtype, workspace, workspace_bytes, stream, perm_src, k, expert_scale);
+}
+
+// moe_permute's index and moe_grouped_ffn_wq_indexed in one call: fc1's row tiles sort for themselves (find_unsorted_item).
+extern "C" int moe_grouped_ffn_wq_unsorted_supported(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
+{
+    using namespace moe;
+    if (T <= 0 || k < 1 || k > 2 || E <= 0 || E > kUnsortedMaxExperts || (long)T * k > kUnsortedMaxAssign || d <= 0 || F <= 0 || d % 64 || F % 64) return 0;
+    if ((bits != 4 && bits != 8) || group_size < 0 || (group_size && (group_size % 64 || d % group_size || F % group_size))) return 0;
+    return act_dtype == MOE_F16 || act_dtype == MOE_BF16;
+}
+
+// Whether a layer that takes the indexed call should take this one: the launch that it saves is 2 to 3.5 us, and every round of fc1's blocks pays for
+// sorting, the more the more assignments there are.  us a step, with the index in a launch / in fc1, by fc1's blocks per compute unit: 62 tokens, one of 8 experts of 512 x
+// 2048 8-bit (0.5) 30.6 / 28.7; 683, two of 32 of 512 x 2048 (1.0) 35.4 / 32.3; 1270, two of 16 of 1024 x 4096 8-bit (3.0) 87.2 / 83.9; 1555, one of 8 of 2048 x 8192
+// 8-bit (3.6) 158.1 / 158.6; few assignments, 31, two of 64 of 2048 x 8192 (5.5) 173.1 / 170.8; 107, two (7.5) 217.9 / 217.3; left out 1215, two of 64 of 2048 x 8192 (8)
+// 292 / 295; 387, two of 128 of 1024 x 4096 8-bit (15.8) 207 / 212.
+extern "C" int moe_grouped_ffn_wq_unsorted_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
+{
+    using namespace moe;
+    if (!moe_grouped_ffn_wq_unsorted_supported(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
+    GemmArgs g{};
+    g.R = T * k, g.E = E, g.K = d, g.N = F;
+    const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
+    return row_tile_blocks(g, bits, grouped && act_dtype == MOE_BF16 && group_size == 128 ? SCALE_GROUP_ACC : SCALE_CHANNEL) <= 256 * (g.R <= 512 ? 8 : 3.5);
+}
+
+extern "C" int moe_grouped_ffn_wq_unsorted(const void *x, int act_dtype, const int32_t *expert_idx, const float *expert_scale, int T, int k, int E,
+                                           int d, int F, int bits, int group_size, int activation, const void *w1_packed, const void *s1,
+                                           const void *b1, const void *w2_packed, const void *s2, const void *b2, void *out, int out_dtype,
+                                           int32_t *perm_src, int32_t *inv_perm, int32_t *expert_offsets, void *workspace,
+                                           size_t workspace_bytes, void *stream)
+{
+    using namespace moe;
+    if (!expert_idx || !perm_src || !inv_perm || !expert_offsets) return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_unsorted: NULL pointer");
+    if (!moe_grouped_ffn_wq_unsorted_supported(T, k, E, d, F, bits, group_size, act_dtype))
+        return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_unsorted: only 1 to %d assignments of fp16 or bf16 rows to at most %d experts with k = 1 or 2, d and F "
+                                         "multiples of 64, 4- or 8-bit weights and group sizes that are 0 or a multiple of 64 dividing d and F are taken",
+                    kUnsortedMaxAssign, kUnsortedMaxExperts);
+    if (expert_scale && k != 1) return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_unsorted: the fused un-permute needs k = 1 (one expert per token)");
+    return ffn_impl(x, act_dtype, expert_offsets, T * k, E, T, d, F, bits, group_size, activation, w1_packed, s1, b1, w2_packed, s2, b2, out, out_dtype,
+                    workspace, workspace_bytes, stream, nullptr, k, expert_scale, expert_idx, perm_src, inv_perm, expert_offsets, true);
 }
 
 // Decode-sized batches: moe_permute and moe_grouped_ffn_wq in one call.  fc1 runs in the straight-line

@@ -32,9 +32,9 @@ struct GemmArgs {
     int a_div;
     const int32_t *out_dst;   // [R] or null: row r of the result goes to out[out_dst[r]], times out_scale[out_dst[r]]
     const float *out_scale;
-    // straight-line streaming kernel only (decode-sized batches): the permutation is rebuilt from the
+    // straight-line streaming kernel (decode-sized batches) and row tiles: the permutation is rebuilt from the
     // gate's output inside the launch.  gate_idx[a] is the expert of assignment a (E = pruned row),
-    // row a / gate_k of `a` is its token; the first block of every expert writes the index arrays.
+    // row a / gate_k of `a` is its token; the first block of every expert (or row tile) writes the index arrays.
     const int32_t *gate_idx;  // [n_assign] or null
     int n_assign, gate_k;
     int32_t *perm_src_out, *inv_perm_out, *offsets_out;
@@ -75,8 +75,10 @@ double decode_active_experts(int n_assign, int E);
 int launch_decode_ffn(const DecodeArgs &p, int bits, bool bf, hipStream_t s);
 
 constexpr int kGatedMaxAssign = 256;    // assignments the fused permutation takes: one per thread of a block
+constexpr int kUnsortedMaxAssign = 4096, kUnsortedMaxExperts = 1024;    // of row tiles that sort for themselves: sixteen keys per thread
 
 int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s);
+double row_tile_blocks(const GemmArgs &p, int bits, int smode);
 bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits);
 void launch_tiled_4(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);
 void launch_tiled_4_exact(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);
@@ -431,6 +433,86 @@ __device__ inline bool find_item(const int32_t *offsets, int E, int R, int BM, i
         base += __shfl(incl, 63);
     }
     return false;
+}
+
+// LDS of find_unsorted_item: rows of every expert and where they begin, matches per 64 assignments, the assignments of the tile's rows.
+struct IndexScratch {
+    int32_t cnt[kUnsortedMaxExperts + 1], off[kUnsortedMaxExperts + 1], match[kUnsortedMaxAssign / 64], row[128];
+};
+
+// find_item for a launch of 256-thread blocks that has no index yet: every block counts the gate's output, which gives it the
+// offsets and its item, and ranks the item's expert, which gives it the assignments of its rows (s.row).  The blocks of a tile's first column write
+// perm_src and inv_perm for the tile's rows, block 0 the offsets and the pruned rows, as moe_permute does.
+// What bounds a small batch is its chain of launches, and the index as one of its own is the link that does least.  Here it costs barriers and
+// code that no block has run before, so each step over 256 assignments ends the loops that are done with them all.
+template <int UNIT = 32>
+__device__ inline bool find_unsorted_item(const GemmArgs &p, int BM, int ncol, IndexScratch &s, int *e_out, int *col, int *row0, int *rows)
+{
+    constexpr int STEPS = kUnsortedMaxAssign / 256;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = p.n_assign, E = p.E;
+    int key[STEPS];
+#pragma unroll
+    for (int j = 0; j < STEPS; ++j) {
+        if (256 * j >= n) break;
+        key[j] = p.gate_idx[min(256 * j + tid, n - 1)];
+    }
+    for (int i = tid; i <= E; i += 256) s.cnt[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < STEPS; ++j) {
+        if (256 * j >= n) break;
+        const bool live = 256 * j + tid < n;
+        key[j] = live ? min(max(key[j], 0), E) : -1;
+        if (live) atomicAdd(&s.cnt[key[j]], 1);
+    }
+    __syncthreads();
+    for (int e0 = 0, carry = 0; e0 <= E; e0 += 64) {            // (every wavefront writes the same for itself: no barrier)
+        const int c = e0 + lane <= E ? s.cnt[e0 + lane] : 0, incl = wave_inclusive_sum(c);
+        if (e0 + lane <= E) s.off[e0 + lane] = carry + incl - c;
+        carry += __shfl(incl, 63);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // f(assignment, its place among those of expert `target`)
+    auto ranks = [&](int target, auto f) {
+#pragma unroll
+        for (int j = 0; j < STEPS; ++j) {
+            if (256 * j >= n) break;
+            const uint64_t m = __ballot(key[j] == target);
+            if (lane == 0) s.match[4 * j + wave] = __popcll(m);
+        }
+        __syncthreads();
+        const int c = 64 * lane < n + 255 - (n + 255) % 256 ? s.match[lane] : 0, before = wave_inclusive_sum(c) - c;
+#pragma unroll
+        for (int j = 0; j < STEPS; ++j) {
+            if (256 * j >= n) break;
+            const bool hit = key[j] == target;
+            const uint64_t m = __ballot(hit);
+            const int r = __shfl(before, 4 * j + wave) + __popcll(m & ((1ull << lane) - 1));
+            if (hit) f(256 * j + tid, r);
+        }
+        __syncthreads();
+    };
+    if (blockIdx.x == 0) {
+        for (int i = tid; i <= E; i += 256) p.offsets_out[i] = s.off[i];
+        const int active = s.off[E];
+        if (active < n) ranks(E, [&](int a, int r) { p.perm_src_out[active + r] = a, p.inv_perm_out[a] = active + r; });
+    }
+    if (!find_item<UNIT>(s.off, E, n, BM, ncol, blockIdx.x, e_out, col, row0, rows)) return false;
+    const int first = *row0 - s.off[*e_out];
+    ranks(*e_out, [&](int a, int r) {
+        if (r < first || r >= first + *rows) return;
+        s.row[r - first] = a;
+        if (*col == 0) p.perm_src_out[*row0 + r - first] = a, p.inv_perm_out[a] = *row0 + r - first;
+    });
+    return true;
+}
+
+// Row of `a` that row i of a block's tile is.
+__device__ inline int source_row(const GemmArgs &p, const IndexScratch &s, int row0, int i)
+{
+    if (p.gate_idx) return s.row[i] >> (p.gate_k - 1);              // one or two experts per token
+    return p.a_src ? p.a_src[row0 + i] / p.a_div : row0 + i;        // (a_src: gather fused into the loads)
 }
 
 }  // namespace moe

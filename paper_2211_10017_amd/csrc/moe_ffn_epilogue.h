@@ -30,11 +30,11 @@ template <int BM>
 struct RowEntry {
     float pow = 1.0f, scale = 1.0f;
     int32_t dst = 0;
-    __device__ inline void load(const GemmArgs &p, int row0, int rows)
+    __device__ inline void load(const GemmArgs &p, const IndexScratch &s, int row0, int rows)
     {
         if ((int)threadIdx.x < BM) {
-            const int r = row0 + min((int)threadIdx.x, rows - 1);
-            if (p.row_pow) pow = p.row_pow[p.a_src ? p.a_src[r] / p.a_div : r].y;     // (a row of A's: factors go with what was converted)
+            const int i = min((int)threadIdx.x, rows - 1), r = row0 + i;
+            if (p.row_pow) pow = p.row_pow[source_row(p, s, row0, i)].y;     // (a row of A's: factors go with what was converted)
             dst = r;
             if (p.out_dst) {
                 dst = p.out_dst[r];

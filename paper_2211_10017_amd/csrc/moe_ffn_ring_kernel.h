@@ -67,12 +67,18 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
     const int wc = wave % WC, kp = wave / WC;
     const int K = p.K, N = p.N;
     int e, col, row0, rows;
-    if (!find_item<(BM < 32 ? BM : 32)>(p.offsets, p.E, p.R, BM, (N + 64 * WC - 1) / (64 * WC), blockIdx.x, &e, &col, &row0, &rows)) return;
+    constexpr int UNIT = BM < 32 ? BM : 32;
+    // (scratch of the index: the last stage, which is filled behind the first barrier)
+    static_assert(S::kStage >= (int)sizeof(IndexScratch), "the index's scratch fits");
+    IndexScratch &index = *reinterpret_cast<IndexScratch *>(lds + (NST - 1) * S::kStage);
+    const int ncol = (N + 64 * WC - 1) / (64 * WC);
+    if (!(p.gate_idx ? find_unsorted_item<UNIT>(p, BM, ncol, index, &e, &col, &row0, &rows)
+                     : find_item<UNIT>(p.offsets, p.E, p.R, BM, ncol, blockIdx.x, &e, &col, &row0, &rows))) return;
     e = __builtin_amdgcn_readfirstlane(e), col = __builtin_amdgcn_readfirstlane(col);
     row0 = __builtin_amdgcn_readfirstlane(row0), rows = __builtin_amdgcn_readfirstlane(rows);
 
     RowEntry<32 * TM> entry;                                 // what the rows need at the end is requested now
-    entry.load(p, row0, rows);
+    entry.load(p, index, row0, rows);
     // this wavefront's two 32-channel tiles (N is a multiple of 64: both exist or neither does)
     const int tile_ok = (col * WC + wc) * 64 < N;
     const int ntile0 = tile_ok ? (col * WC + wc) * 2 : 0;
@@ -89,9 +95,7 @@ __device__ __forceinline__ void ring_gemm(const GemmArgs &p)
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
         const int row = 8 * ((i * WC + wc) % (BM / 8)) + (lane >> 3);
-        const int r = row0 + min(row, rows - 1);                    // clamped: always a valid row
-        const int rs = p.a_src ? p.a_src[r] / p.a_div : r;          // gather fused into the loads
-        a_ptr[i] = p.a + (size_t)rs * K + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+        a_ptr[i] = p.a + (size_t)source_row(p, index, row0, min(row, rows - 1)) * K + ((lane & 7) ^ ((row >> 1) & 7)) * 8;      // clamped: always a valid row
     }
     const uint8_t *b_ptr[2];
 #pragma unroll

@@ -84,6 +84,14 @@ bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits)
     return us <= 3.0 + 4.0 * ((double)R * F + (double)tokens * d) / 5e6;
 }
 
+// Blocks that hold rows when launch_tiled_gemm takes this GEMM, under uniform routing.
+double row_tile_blocks(const GemmArgs &p, int bits, int smode)
+{
+    const int mean = (p.R + p.E - 1) / p.E, ring = ring_rows(p, bits, mean), tm = tile_height(p, bits, mean);
+    if (ring) return expected_row_tiles(p.R, p.E, ring) * ((p.N + 127) / 128);
+    return expected_row_tiles(p.R, p.E, 32 * (smode == SCALE_GROUP_ACC && tm > 2 ? 2 : tm)) * ((p.N + 255) / 256);
+}
+
 int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
 {
     // row-tile height from the mean rows per expert (the offsets themselves stay on the device)

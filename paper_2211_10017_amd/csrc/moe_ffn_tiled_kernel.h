@@ -22,7 +22,7 @@ constexpr int kTN = 2;                   // 32-channel tiles per wavefront
 // (bf16 rows that meet bf16 codes are a scale mode, not a branch: both loops in one kernel take 194 registers for 64-row tiles of 8-bit weights, two wavefronts per
 // SIMD, each by itself 162 to 164, three; 4096 tokens, two of 128 experts of 2048 x 8192, skewed, a step 1145 us in one, 1116 apart)
 template <int BITS, int SMODE, int TM>
-__global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
+__global__ __launch_bounds__(256, TM == 1 && !(SMODE == SCALE_GROUP_ACC || SMODE == SCALE_GROUP_SPLIT) ? 4 : 2) void grouped_gemm_kernel(GemmArgs p)
 {
     constexpr bool BF = SMODE == SCALE_CHANNEL_BF16;
     constexpr int BM = 32 * TM;
@@ -36,13 +36,17 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: tile addresses stay scalar
     const int K = p.K, N = p.N;
     int e, col, row0, rows;
-    if (!find_item(p.offsets, p.E, p.R, 32 * p.tile_units, (N + 255) / 256, blockIdx.x, &e, &col, &row0, &rows)) return;
+    // (scratch of the index: behind the first stage, which is filled while other wavefronts still read their rows' assignments)
+    static_assert(sizeof(lds_raw) >= kStageBytes / 2 + sizeof(IndexScratch), "the index's scratch fits");
+    IndexScratch &index = *reinterpret_cast<IndexScratch *>(lds_raw + kStageBytes / 2);
+    if (!(p.gate_idx ? find_unsorted_item(p, 32 * p.tile_units, (N + 255) / 256, index, &e, &col, &row0, &rows)
+                     : find_item(p.offsets, p.E, p.R, 32 * p.tile_units, (N + 255) / 256, blockIdx.x, &e, &col, &row0, &rows))) return;
     e = __builtin_amdgcn_readfirstlane(e), col = __builtin_amdgcn_readfirstlane(col);      // the same in every lane: kept in scalar registers
     row0 = __builtin_amdgcn_readfirstlane(row0), rows = __builtin_amdgcn_readfirstlane(rows);
 
     // what the rows need at the end is requested now; the tallest tile has no registers to carry it through the K loop
     RowEntry<BM> entry;
-    entry.load(p, row0, rows);
+    entry.load(p, index, row0, rows);
     if constexpr (TM == 4) entry.put(tile_rows);
     const int nk = K / 64;
     const int ntile0 = (col * 4 + wave) * kTN;         // first 32-channel tile of this wavefront
@@ -65,9 +69,7 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_kernel(GemmArgs p)
     const uint16_t *a_ptr[TM];
 #pragma unroll
     for (int m = 0; m < TM; ++m) {
-        const int r = row0 + min(a_row + 32 * m, rows - 1);      // clamped: always a valid row
-        const int rs = p.a_src ? p.a_src[r] / p.a_div : r;       // gather fused into the A loads
-        a_ptr[m] = p.a + (size_t)rs * K + a_seg;
+        a_ptr[m] = p.a + (size_t)source_row(p, index, row0, min(a_row + 32 * m, rows - 1)) * K + a_seg;      // clamped: always a valid row
     }
     // B: fragment blocks of tile t are contiguous along K
     const uint8_t *w_e = p.wq + (size_t)e * packed_bytes_per_expert(K, N, BITS);

@@ -83,6 +83,10 @@ def indexed(R, E, k, d, F, bits, g=0, act=B.MOE_F16, bound=0, scale=False):
     return "moe_grouped_ffn_wq_indexed", [P, act, P, k, P if scale else None, P, R, E, bound, d, F, bits, g, 0, P, P, None, P, P, None, P, B.MOE_F32, P, _SIZE, None]
 
 
+def unsorted(T, k, E, d, F, bits, g=0, act=B.MOE_F16, scale=False, idx=P):
+    return "moe_grouped_ffn_wq_unsorted", [P, act, idx, P if scale else None, T, k, E, d, F, bits, g, 0, P, P, None, P, P, None, P, B.MOE_F32, P, P, P, P, _SIZE, None]
+
+
 def sliced(T, k, E, d, F, bits, g=0, act=B.MOE_F16, out=B.MOE_F32):
     return "moe_grouped_ffn_wq_sliced", [P, act, P, P, T, k, E, d, F, bits, g, 0, P, P, None, P, P, None, P, out, P, P, P, P, _SIZE, None]
 

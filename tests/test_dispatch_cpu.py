@@ -262,3 +262,21 @@ def test_the_conversion_of_bf16_rows_is_compared_in_every_form():
     converted = L.record([L.ffn(9, 2, 64, K, 8, 64, B.MOE_BF16) for K, _ in LENGTHS])
     assert [c.launches[2].kernel for c in converted] == [f"rows_to_f16_kernel<{256 if 4096 < K <= 16384 else 64}, {nv}>" for K, nv in LENGTHS]
     assert not any(p.kernel.startswith("rows_to_f16") for c in L.record([L.ffn(9, 2, 64, K, 8, 0, B.MOE_BF16) for K in (1024, 1088, 4096, 4160)]) for p in c.launches)
+
+
+def test_the_unsorted_call_launches_what_the_indexed_call_does():
+    """The same launches in the same order, for every form that it takes; what it does not take is refused; and it pays only where few blocks sort."""
+    import itertools
+    forms = [(T, k, E, d, F, bits, g, act, k == 1) for (T, k, E), (d, F), bits, g, act in itertools.product(
+        [(1, 1, 1), (3, 2, 8), (64, 2, 32), (257, 1, 65), (2048, 2, 16), (4096, 1, 1024)], [(64, 128), (512, 2048), (4096, 1024)], (4, 8), (0, 64, 128), (B.MOE_F16, B.MOE_BF16))
+        if not (g == 128 and d == 64)]
+    here, there = L.record([L.unsorted(*f) for f in forms]), L.record([L.indexed(f[0] * f[1], f[2], f[1], *f[3:8], f[0], f[8]) for f in forms])
+    for f, a, b in zip(forms, here, there):
+        assert a.rc == b.rc == 0 and a.launches == b.launches and a.noted == b.noted, f
+    refused = [L.unsorted(2049, 2, 8, 64, 64, 4), L.unsorted(4097, 1, 8, 64, 64, 4), L.unsorted(8, 1, 1025, 64, 64, 4), L.unsorted(0, 1, 8, 64, 64, 4), L.unsorted(8, 3, 8, 64, 64, 4),
+               L.unsorted(8, 2, 8, 64, 64, 4, scale=True), L.unsorted(8, 1, 8, 96, 64, 4), L.unsorted(8, 1, 8, 64, 64, 5), L.unsorted(8, 1, 8, 64, 64, 4, 128),
+               L.unsorted(8, 1, 8, 64, 64, 4, idx=None), L.unsorted(8, 1, 8, 64, 64, 4, act=B.MOE_F32)]
+    assert all(c.rc in (1, 2) and not c.launches for c in L.record(refused))
+    pays = lambda *a: B.load().moe_grouped_ffn_wq_unsorted_pays(*a)  # noqa: E731
+    assert pays(683, 2, 32, 512, 2048, 4, 0, B.MOE_F16) and pays(1270, 2, 16, 1024, 4096, 8, 0, B.MOE_F16) and pays(31, 2, 64, 2048, 8192, 4, 128, B.MOE_BF16)
+    assert not pays(1215, 2, 64, 2048, 8192, 4, 0, B.MOE_F16) and not pays(387, 2, 128, 1024, 4096, 8, 0, B.MOE_F16) and not pays(4097, 1, 8, 512, 2048, 4, 0, B.MOE_F16)
