@@ -16,7 +16,11 @@ namespace moe {
 // little is being read: the codes are put together by fp32 multiply-adds, and masters that no cache holds and that are read once
 // (NT) are loaded non-temporal.  (32 experts of 1024 x 4096, 4-bit: 332 us with two reads in strips, 143 with shifts and plain loads, 129 with
 // multiply-adds, 122 with both, 5.0 TB/s; 8-bit 147 -> 134; groups of 128 124 -> 108; 4096 x 1024, which is read twice: 174 -> 171.)
-template <int BITS, int WU, bool CANON, bool NT>
+//
+// CH: channels of a unit.  Long units (per-channel scales of more than 2048 rows) of a few slabs leave compute units idle and are read twice: there a
+// slab is cut into units of sixteen or eight channels, PARTS of them, and a wavefront takes that many blocks of rows side by side, so the same registers hold
+// two or four times the rows.  A row segment is then 64 or 32 bytes, which is slower per byte: only where it fills the chip (see quantize_channels).
+template <int BITS, int WU, bool CANON, bool NT, int CH>
 __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const float *__restrict__ w, int K, int N, int g,
                                                                          long units, int8_t *__restrict__ q_canon,
                                                                          __half *__restrict__ scales,
@@ -27,25 +31,31 @@ __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const f
     constexpr int J = FK / 16;                          // octets of rows per lane and block
     constexpr int FB = 128 / FK;                        // blocks a wavefront keeps
     constexpr int UPB = (WU == 16 ? 16 : 8) / WU;       // units per workgroup
-    __shared__ float s_amax[UPB][WU][32];
+    constexpr int PARTS = 32 / CH;                      // units of a slab, and blocks of rows side by side in a wavefront
+    __shared__ float s_amax[UPB][WU][CH];
     __shared__ __align__(16) uint8_t s_canon[CANON ? UPB * WU : 1][CANON ? FK * 32 * BITS / 8 : 16];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int sub = wave / WU, wu = wave % WU;
-    const int nl = lane & 31, half = lane >> 5;
+    const int nl = lane % CH, half = lane / CH & 1, side = lane / (2 * CH);
     const int nslab = N / 32, G = K / g;
-    const long unit = (long)blockIdx.x * UPB + sub;     // [expert][group][slab]: neighbouring workgroups read neighbouring columns
+    // [expert][group][slab]: neighbouring workgroups read neighbouring columns; the parts of a slab, which share its lines, run side by
+    // side on one XCD
+    const long unit = PARTS == 1 ? (long)blockIdx.x * UPB + sub : (long)(blockIdx.x / (8 * PARTS)) * 8 + blockIdx.x % 8;
+    const int part = PARTS == 1 ? 0 : blockIdx.x / 8 % PARTS;
     const bool live = unit < units;
     const long u = live ? unit : units - 1;
     const int nb = (int)(u % nslab), gi = (int)(u / nslab % G);
     const long e = u / nslab / G;
-    const int n = nb * 32 + nl;
+    const int n = nb * 32 + part * CH + nl;
     const int nblk = g / FK;                            // fragment blocks of the unit
+    const int nrun = (nblk + PARTS - 1) / PARTS;        // runs of PARTS blocks, of which a lane has one
+    auto block_of = [&](int r) { return PARTS == 1 ? r : min(r * PARTS + side, nblk - 1); };      // (past the last one: that one again)
     const float *base = w + ((size_t)e * K + (size_t)gi * g) * N + n;
 
-    // rows FK b + 16 j + 8 half + i of the unit
-    auto fetch = [&](int b, float (&v)[J][8]) __attribute__((always_inline)) {
-        const float *p = base + (size_t)(b * FK + 8 * half) * N;
+    // rows FK b + 16 j + 8 half + i of the unit, b the lane's block of run r
+    auto fetch = [&](int r, float (&v)[J][8]) __attribute__((always_inline)) {
+        const float *p = base + (size_t)(block_of(r) * FK + 8 * half) * N;
 #pragma unroll
         for (int j = 0; j < J; ++j)
 #pragma unroll
@@ -62,18 +72,19 @@ __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const f
     float amax = 0.0f;
 #pragma unroll
     for (int f = 0; f < FB; ++f)
-        if (f * WU + wu < nblk) fetch(f * WU + wu, keep[f]);
+        if (f * WU + wu < nrun) fetch(f * WU + wu, keep[f]);
 #pragma unroll
     for (int f = 0; f < FB; ++f)
-        if (f * WU + wu < nblk) amax = largest(keep[f], amax);
-    for (int b = FB * WU + wu; b < nblk; b += WU) {
+        if (f * WU + wu < nrun) amax = largest(keep[f], amax);
+    for (int r = FB * WU + wu; r < nrun; r += WU) {
         float v[J][8];
-        fetch(b, v);
+        fetch(r, v);
         amax = largest(v, amax);
     }
-    amax = fmaxf(amax, __shfl_xor(amax, 32));
+#pragma unroll
+    for (int off = CH; off < 64; off *= 2) amax = fmaxf(amax, __shfl_xor(amax, off));
     if (WU > 1) {
-        if (half == 0) s_amax[sub][wu][nl] = amax;
+        if (lane < CH) s_amax[sub][wu][nl] = amax;
         __syncthreads();
         amax = s_amax[sub][0][nl];
 #pragma unroll
@@ -82,7 +93,7 @@ __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const f
     if (!live) return;                                  // (no barrier follows)
     const __half sh = __float2half_rn(amax / (float)QMAX);   // IEEE divide, round to nearest even
     const float s = __half2float(sh);
-    if (wu == 0 && half == 0) scales[((size_t)e * G + gi) * N + n] = sh;
+    if (wu == 0 && lane < CH) scales[((size_t)e * G + gi) * N + n] = sh;
 
     // w / s, correctly rounded: with y = 1/s rounded to nearest and a quotient within one unit in the last place, one
     // residual step gives the correctly rounded quotient (Markstein); the first step makes it that accurate.  A scale of zero
@@ -95,7 +106,7 @@ __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const f
         q = fmaf(fmaf(-q, sd, x), y, q);
         return __builtin_amdgcn_fmed3f(rintf(q), -lim, lim);
     };
-    auto convert = [&](int b, const float (&v)[J][8]) __attribute__((always_inline)) {
+    auto convert = [&](int r, const float (&v)[J][8]) __attribute__((always_inline)) {
         uint32_t word[4];
         float fc[J][8];
 #pragma unroll
@@ -126,60 +137,75 @@ __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const f
             for (int j = 0; j < J; ++j)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) code[j][i] = (int)fc[j][i];
-        const int kb = gi * nblk + b;
-        if (q_packed)
+        const int kb = gi * nblk + block_of(r);
+        if (q_packed && (PARTS == 1 || r * PARTS + side < nblk))
             *reinterpret_cast<uint4 *>(q_packed + (size_t)e * packed_bytes_per_expert(K, N, BITS) + ((size_t)nb * (K / FK) + kb) * kFragBytes +
-                                       lane * 16) = make_uint4(word[0], word[1], word[2], word[3]);
+                                       (half * 32 + part * CH + nl) * 16) = make_uint4(word[0], word[1], word[2], word[3]);
         if constexpr (CANON) {
             // the block's rows meet in the wavefront's own piece of LDS (served in order: no barrier) and leave 16 bytes per lane
+            constexpr int ROW = CH * BITS / 8;          // bytes of a row
             uint8_t *tile = s_canon[sub * WU + wu];
 #pragma unroll
             for (int j = 0; j < J; ++j)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const int row = 16 * j + 8 * half + i;
+                    const int row = side * FK + 16 * j + 8 * half + i;
                     if (BITS == 8) {
-                        tile[row * 32 + nl] = (uint8_t)code[j][i];
+                        tile[row * ROW + nl] = (uint8_t)code[j][i];
                     } else {
                         const int other = __builtin_amdgcn_update_dpp(0, code[j][i], 0xB1, 0xf, 0xf, false);     // the neighbouring channel's code
-                        if (!(lane & 1)) tile[row * 16 + (nl >> 1)] = (uint8_t)((code[j][i] & 0xf) | ((other & 0xf) << 4));
+                        if (!(lane & 1)) tile[row * ROW + (nl >> 1)] = (uint8_t)((code[j][i] & 0xf) | ((other & 0xf) << 4));
                     }
                 }
-            constexpr int VPR = BITS == 8 ? 2 : 1;      // 16-byte vectors per row
-            const int row = lane / VPR;
             __builtin_amdgcn_wave_barrier();
-            const uint4 v = *reinterpret_cast<const uint4 *>(tile + lane * 16);
-            *reinterpret_cast<uint4 *>(reinterpret_cast<uint8_t *>(q_canon) + (((size_t)e * K + (size_t)kb * FK + row) * N + nb * 32) * BITS / 8 +
-                                       (lane % VPR) * 16) = v;
+            auto leave = [&](auto vec, int at) __attribute__((always_inline)) {      // the tile's bytes from `at` on, a piece of one row
+                const int row = at / ROW;
+                if (PARTS > 1 && r * PARTS * FK + row >= g) return;                  // (the rows of a last block that is there again)
+                *reinterpret_cast<decltype(vec) *>(reinterpret_cast<uint8_t *>(q_canon) +
+                                                   (((size_t)e * K + (size_t)gi * g + (size_t)r * PARTS * FK + row) * N + nb * 32 + part * CH) * BITS / 8 + at % ROW) =
+                    *reinterpret_cast<const decltype(vec) *>(tile + at);
+            };
+            if constexpr (ROW >= 16) leave(uint4{}, lane * 16);
+            else if constexpr (ROW == 8) leave(uint2{}, lane * 8), leave(uint2{}, 512 + lane * 8);
+            else
+#pragma unroll
+                for (int i = 0; i < 4; ++i) leave(uint32_t{}, 256 * i + lane * 4);
             __builtin_amdgcn_wave_barrier();
         }
     };
 #pragma unroll
     for (int f = 0; f < FB; ++f)
-        if (f * WU + wu < nblk) convert(f * WU + wu, keep[f]);
-    for (int b = FB * WU + wu; b < nblk; b += WU) {
+        if (f * WU + wu < nrun) convert(f * WU + wu, keep[f]);
+    for (int r = FB * WU + wu; r < nrun; r += WU) {
         float v[J][8];
-        fetch(b, v);
-        convert(b, v);
+        fetch(r, v);
+        convert(r, v);
     }
 }
 
-template <int BITS, int WU>
+template <int BITS, int WU, int CH = 32>
 static void launch_quantize(const float *w, int E, int K, int N, int g, void *q_canon, void *scales, void *q_packed, hipStream_t s)
 {
     constexpr int UPB = (WU == 16 ? 16 : 8) / WU;
     const long units = (long)E * (K / g) * (N / 32);
-    const dim3 grid((unsigned)((units + UPB - 1) / UPB)), block(WU == 16 ? 1024 : 512);
+    static_assert(CH == 32 || UPB == 1, "parts of a slab are workgroups");
+    const dim3 grid((unsigned)(CH == 32 ? (units + UPB - 1) / UPB : (units + 7) / 8 * 8 * (32 / CH))), block(WU == 16 ? 1024 : 512);
     // masters larger than the L2s together, units that the registers hold (a second read finds part of its rows in the last-level cache: 4096 x
     // 1024 171 us plain, 184 non-temporal; one expert of 1024 x 4096 just written 7.8 and 8.5)
-    const bool nt = (size_t)E * K * N >= (size_t)16 << 20 && g <= WU * 128;
+    const bool nt = CH == 32 && (size_t)E * K * N >= (size_t)16 << 20 && g <= WU * 128;      // (parts share lines)
     auto launch = [&](auto canon, auto once) {
-        hipLaunchKernelGGL((quantize_kernel<BITS, WU, decltype(canon)::value, decltype(once)::value>), grid, block, 0, s, w, K, N, g, units, (int8_t *)q_canon,
+        hipLaunchKernelGGL((quantize_kernel<BITS, WU, decltype(canon)::value, decltype(once)::value, CH>), grid, block, 0, s, w, K, N, g, units, (int8_t *)q_canon,
                            (__half *)scales, (uint8_t *)q_packed);
     };
     if (q_canon) nt ? launch(std::true_type{}, std::true_type{}) : launch(std::true_type{}, std::false_type{});
     else nt ? launch(std::false_type{}, std::true_type{}) : launch(std::false_type{}, std::false_type{});
 }
+
+// Channels of a unit of more than 2048 rows: all of a slab while the slabs fill half of the compute units or more, else as few as leave a compute unit to
+// each block.  us, units of 32 / 16 / 8 channels: one expert of 4096 x 1024, 4-bit (32 slabs) 17.9 / 12.8 / 11.0, 8-bit 18.3 / 13.4 / 10.9, of 8192 x 2048 (64)
+// 37.5 / 29.0 / 22.0, of 16384 x 4096 (128) 125 / 103 / 149; four of 4096 x 1024 (128) 23.3 / 18.6 / 22.2, two of 8192 x 2048 (128) 57 / 48 / 66; eight of 3072 x 768
+// (192) 21.8 / 23.3 / 26.7, 32 of 4096 x 1024 (1024) 174 / 183 / 257.
+static int quantize_channels(long slabs) { return slabs <= 64 ? 8 : slabs <= 128 ? 16 : 32; }
 
 // Wavefronts per unit: the fewest whose registers hold the unit (128 rows each), sixteen for the longest.
 template <int BITS>
@@ -188,7 +214,12 @@ static void launch_quantize_bits(const float *w, int E, int K, int N, int g, voi
     if (g <= 128) launch_quantize<BITS, 1>(w, E, K, N, g, q_canon, scales, q_packed, s);
     else if (g <= 512) launch_quantize<BITS, 4>(w, E, K, N, g, q_canon, scales, q_packed, s);
     else if (g <= 1024) launch_quantize<BITS, 8>(w, E, K, N, g, q_canon, scales, q_packed, s);
-    else launch_quantize<BITS, 16>(w, E, K, N, g, q_canon, scales, q_packed, s);
+    else {
+        const int ch = g <= 2048 ? 32 : quantize_channels((long)E * (K / g) * (N / 32));
+        if (ch == 32) launch_quantize<BITS, 16>(w, E, K, N, g, q_canon, scales, q_packed, s);
+        else if (ch == 16) launch_quantize<BITS, 16, 16>(w, E, K, N, g, q_canon, scales, q_packed, s);
+        else launch_quantize<BITS, 16, 8>(w, E, K, N, g, q_canon, scales, q_packed, s);
+    }
 }
 
 // Unquantised fp16 weights in the fragment layout (one MFMA step, 16 K values, per 1 KB block):

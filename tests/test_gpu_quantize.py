@@ -58,6 +58,14 @@ def test_quantize_units_bit_exact(bits, g, E, K, N):
     assert np.array_equal(_unpack(packed.cpu().numpy(), E, K, N, bits), oq)
 
 
+# Units of more than 2048 rows of sixteen (more than 64 slabs) and of eight channels: rows that fill two or four blocks of a wavefront, and a last run of one, two
+# or three of them; as many rows as the registers hold and more (read twice); a last group of eight slabs that is not full
+@pytest.mark.parametrize("bits,g,E,K,N", [(4, 0, 1, 2112, 96), (8, 0, 1, 2176, 32), (4, 0, 1, 2304, 2112), (8, 0, 3, 2240, 704), (4, 0, 1, 8256, 64), (8, 0, 1, 8256, 32),
+                                          (4, 4160, 1, 8320, 1056), (8, 2176, 2, 4352, 32)])
+def test_parts_of_slabs_bit_exact(bits, g, E, K, N):
+    test_quantize_units_bit_exact(bits, g, E, K, N)
+
+
 @pytest.mark.parametrize("bits,g,E,K,N", [(4, 0, 17, 1024, 1024), (8, 128, 9, 768, 2560), (4, 0, 4, 2048, 2080), (8, 0, 2, 4096, 2112)])
 def test_large_masters_give_the_bytes_of_their_experts(bits, g, E, K, N):
     """Masters of more than 64 MB are loaded non-temporal where the registers hold a unit: expert by expert they are not."""
