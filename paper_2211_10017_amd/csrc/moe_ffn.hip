@@ -531,9 +531,31 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
     return round_up(decode_ffn_partial_bytes(T * k, d, F, decode_slice_width(T * k, E, F)), 256);
 }
 
+// Few experts or small ones, beyond what moe_grouped_ffn_wq_sliced_pays lists: the launches of the other routes are most of their step there, and nearly every
+// expert's rows are one item (sixteen rows, thirty-two with 4-bit weights and more than eight rows per expert), so no weights are read twice:
+// `over`, the items that a touched expert is expected to make, may be 1.6, with more than 100 MB of weights 1.1, anything up to 17 MB.  (us a step, the best
+// other route / sliced: 40 rows on 8 experts of 512 x 2048, bf16 28.9 / 14.4, 141 on 16 of 768 x 3072, groups of 128, 31.6 / 24.4, 149 on 8 of 1024 x 4096 32.0 / 27.3, 186 on 8 of
+// 2048 x 8192, bf16 65.3 / 55.6; left out 226 on 8 of 2048 x 8192, over = 1.2, 70 / 85, 476 on 8 of 768 x 3072, 2.2, 35 / 47.)
+//  - FP16 rows on 8-bit codes with channel scales, which stream well elsewhere: over up to 1.25 and 100 MB, or at most a row per expert and 430 MB (12 on 32 of 2048 x
+//    8192 65 / 54; 7 on 32 of 4096 x 16384, 750 MB, 134 / 160).
+//  - all others up to 500 MB, with experts of up to 17 MB 600 (229 rows on 128 of 768 x 3072, 8-bit bf16, 97 / 77; 230 on 32 of 2048 x 8192, groups of 128, bf16 154 / 134);
+//    FP16 rows on 4-bit codes with channel scales up to 1200 MB while there are at most 1.6 rows per expert (22 on 16 of 4096 x 16384, 814 MB, 180 / 155; bf16
+//    11 on 64, 683 MB, 171 / 202).
+// Slices of 64 channels up to 520 blocks, as far as these were measured.
+// (402 drawn sizes that the rules before left out: this takes 182 of them, a step 1.23 times as fast on average, two of them 3 and 4 % slower.)
+static bool sliced_small(int R, int E, int d, int F, int bits, bool grouped, bool f16, double active, double bytes, bool narrow)
+{
+    using namespace moe;
+    if (narrow) return false;
+    const double expert = 2.0 * d * F * bits / 8, over = R <= E ? 1.0 : expected_row_tiles(R, E, R > 8L * E && bits == 4 ? 32 : 16) / active;
+    if (f16 && bits == 8 && !grouped) return over <= (bytes > 100e6 ? 1.1 : 1.25) && (bytes <= 100e6 || (R <= E && bytes <= 430e6));
+    if (bytes > 17e6 && over > (bytes > 100e6 ? 1.1 : 1.6)) return false;
+    return bytes <= (expert <= 17e6 ? 600e6 : 500e6) || (f16 && bits == 4 && !grouped && 5L * R <= 8L * E && bytes <= 1200e6);
+}
+
 // Whether a layer should take the sliced call (steps in us of the routes below against it, uniform routing; of 13898 drawn sizes of 4 to 512 assignments
-// it takes 9964, 1.40 times as fast on average; 263 of them, most with up to one row per expert, are 2 to 41 % slower; 2319 of those it leaves would be 1.35 times
-// as fast):
+// it takes 9964, 1.40 times as fast on average; 263 of them, most with up to one row per expert, are 2 to 41 % slower; sliced_small takes in what these lines
+// leave of small and few experts):
 //  - up to eight assignments per expert: a block takes sixteen rows, and experts with more stream their weights again (61 tokens, two of
 //    eight experts of 4096 x 16384 8-bit 182 and 320; 5 per expert of 1024 x 4096 8-bit 57 and 61).
 //    Rows on 4-bit codes, whose blocks then take thirty-two: up to sixteen, 150 MB of weights and a d_ff of twice d (192 tokens,
@@ -569,7 +591,9 @@ extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F,
     const bool grouped = group_size != 0 && !(group_size == d && group_size == F), f16 = act_dtype == MOE_F16;
     const int cw = decode_slice_width(R, E, F);
     const double blocks = active * (F / 64) / cw;
-    if (5 * R > 4 * active * cw * bits || (cw == 1 && blocks > 3600)) return 0;
+    if (cw == 1 && blocks > 3600) return 0;
+    if (sliced_small(R, E, d, F, bits, grouped, f16, active, bytes, cw == 1 && blocks > 520)) return 1;
+    if (5 * R > 4 * active * cw * bits) return 0;
     if (R > 8L * E) {
         const bool fits = grouped ? R <= 12L * E && F >= 4 * d && bytes <= 110e6 : R <= 16L * E && F >= 2 * d && bytes <= 150e6;
         return bits == 4 && fits && (blocks <= 260 || blocks > 400);

@@ -28,7 +28,7 @@ static int ring_rows(const GemmArgs &p, int bits, int mean)
 }
 
 // Row tiles that R rows make on E experts under uniform routing, an expert's rows taken as normally distributed.
-static double expected_row_tiles(long R, long E, int bm)
+double expected_row_tiles(long R, long E, int bm)
 {
     const double mean = (double)R / E, sd = sqrt(mean * (1.0 - 1.0 / E));
     double tiles = floor(fmax(mean - 4 * sd, 0.0) / bm);       // (that all experts fill)

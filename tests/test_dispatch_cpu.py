@@ -280,3 +280,11 @@ def test_the_unsorted_call_launches_what_the_indexed_call_does():
     pays = lambda *a: B.load().moe_grouped_ffn_wq_unsorted_pays(*a)  # noqa: E731
     assert pays(683, 2, 32, 512, 2048, 4, 0, B.MOE_F16) and pays(1270, 2, 16, 1024, 4096, 8, 0, B.MOE_F16) and pays(31, 2, 64, 2048, 8192, 4, 128, B.MOE_BF16)
     assert not pays(1215, 2, 64, 2048, 8192, 4, 0, B.MOE_F16) and not pays(387, 2, 128, 1024, 4096, 8, 0, B.MOE_F16) and not pays(4097, 1, 8, 512, 2048, 4, 0, B.MOE_F16)
+
+
+def test_small_and_few_experts_are_sliced_up_to_about_one_block_each():
+    bf = B.MOE_BF16
+    assert _pays(20, 2, 8, 512, 2048, 4, 0, bf) and _pays(141, 1, 16, 768, 3072, 4, 128) and _pays(149, 1, 8, 1024, 4096, 4) and _pays(82, 1, 8, 512, 2048, 8, 0, bf)
+    assert _pays(229, 1, 128, 768, 3072, 8, 0, bf) and _pays(11, 2, 16, 4096, 16384, 4) and _pays(12, 1, 32, 2048, 8192, 8)
+    assert not any(_pays(*c) for c in [(256, 1, 8, 512, 2048, 8), (113, 2, 8, 2048, 8192, 4), (238, 2, 8, 768, 3072, 4), (7, 1, 32, 4096, 16384, 8), (11, 1, 64, 4096, 16384, 4, 0, bf),
+                                       (133, 1, 8, 4096, 16384, 8), (99, 2, 32, 4096, 16384, 4)])
