@@ -242,6 +242,7 @@ int moe_grouped_ffn_wq_indexed(const void *x, int act_dtype, const int32_t *perm
  *   0 or E); expert_scale [T] fp32 (k = 1 only) or NULL, and out, as for moe_grouped_ffn_wq_indexed: [T,d] when expert_scale
  *   is given, where the rows of pruned tokens are not written, else y_perm [T*k,d]; perm_src, inv_perm,
  *   expert_offsets as moe_permute writes them; workspace as for moe_grouped_ffn_wq with R = T*k.
+ * (Sizes that moe_grouped_ffn_wq_gated takes at level 1 and that it pays for run fc1 in its streaming kernel, the others both GEMMs in row tiles.)
  * moe_grouped_ffn_wq_unsorted_supported returns 1 when a call with these sizes is taken; it otherwise returns MOE_ERR_UNSUPPORTED.
  * moe_grouped_ffn_wq_unsorted_pays: 1 when it is also the faster way than the two calls (MoEExpertLayer asks this).
  */

@@ -220,7 +220,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
                     size_t workspace_bytes, void *stream,
                     const int32_t *perm_src, int k, const float *expert_scale,
                     const int32_t *gate_idx = nullptr, int32_t *perm_src_out = nullptr, int32_t *inv_perm_out = nullptr,
-                    int32_t *offsets_out = nullptr, bool unsorted = false)
+                    int32_t *offsets_out = nullptr, bool unsorted = false, bool stream_fc1 = false)
 {
     using namespace moe;
     // decode-sized batch with everything fused: one streaming launch for the sort and both GEMMs, then the slice reduction
@@ -296,7 +296,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     }
     // (groups of 128: exact codes, group sums folded in fp32; other group sizes: the two-term form, in the LDS ring exact codes as well)
     const int channel = bf && !convert ? SCALE_CHANNEL_BF16 : SCALE_CHANNEL, smode1 = !grouped ? channel : !bf ? SCALE_GROUP : group_size == 128 ? SCALE_GROUP_ACC : SCALE_GROUP_SPLIT;
-    int rc = run_gemm(g1, bits, smode1, bf, tiles_only, max_rows, s);
+    int rc = run_gemm(g1, bits, smode1, bf, tiles_only && !stream_fc1, max_rows, s);
     if (rc) return rc;
 
     // fc2: y = h @ deq(W2) + b2
@@ -435,47 +435,6 @@ extern "C" int moe_grouped_ffn_wq_indexed(const void *x, int act_dtype, const in
                     w2_packed, s2, b2, out, out_dtype, workspace, workspace_bytes, stream, perm_src, k, expert_scale);
 }
 
-// moe_permute's index and moe_grouped_ffn_wq_indexed in one call: fc1's row tiles sort for themselves (find_unsorted_item).
-extern "C" int moe_grouped_ffn_wq_unsorted_supported(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
-{
-    using namespace moe;
-    if (T <= 0 || k < 1 || k > 2 || E <= 0 || E > kUnsortedMaxExperts || (long)T * k > kUnsortedMaxAssign || d <= 0 || F <= 0 || d % 64 || F % 64) return 0;
-    if ((bits != 4 && bits != 8) || group_size < 0 || (group_size && (group_size % 64 || d % group_size || F % group_size))) return 0;
-    return act_dtype == MOE_F16 || act_dtype == MOE_BF16;
-}
-
-// Whether a layer that takes the indexed call should take this one: the launch that it saves is 2 to 3.5 us, and every round of fc1's blocks pays for
-// sorting, the more the more assignments there are.  us a step, with the index in a launch / in fc1, by fc1's blocks per compute unit: 62 tokens, one of 8 experts of 512 x
-// 2048 8-bit (0.5) 30.6 / 28.7; 683, two of 32 of 512 x 2048 (1.0) 35.4 / 32.3; 1270, two of 16 of 1024 x 4096 8-bit (3.0) 87.2 / 83.9; 1555, one of 8 of 2048 x 8192
-// 8-bit (3.6) 158.1 / 158.6; few assignments, 31, two of 64 of 2048 x 8192 (5.5) 173.1 / 170.8; 107, two (7.5) 217.9 / 217.3; left out 1215, two of 64 of 2048 x 8192 (8)
-// 292 / 295; 387, two of 128 of 1024 x 4096 8-bit (15.8) 207 / 212.
-extern "C" int moe_grouped_ffn_wq_unsorted_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
-{
-    using namespace moe;
-    if (!moe_grouped_ffn_wq_unsorted_supported(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
-    GemmArgs g{};
-    g.R = T * k, g.E = E, g.K = d, g.N = F;
-    const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
-    return row_tile_blocks(g, bits, grouped && act_dtype == MOE_BF16 && group_size == 128 ? SCALE_GROUP_ACC : SCALE_CHANNEL) <= 256 * (g.R <= 512 ? 8 : 3.5);
-}
-
-extern "C" int moe_grouped_ffn_wq_unsorted(const void *x, int act_dtype, const int32_t *expert_idx, const float *expert_scale, int T, int k, int E,
-                                           int d, int F, int bits, int group_size, int activation, const void *w1_packed, const void *s1,
-                                           const void *b1, const void *w2_packed, const void *s2, const void *b2, void *out, int out_dtype,
-                                           int32_t *perm_src, int32_t *inv_perm, int32_t *expert_offsets, void *workspace,
-                                           size_t workspace_bytes, void *stream)
-{
-    using namespace moe;
-    if (!expert_idx || !perm_src || !inv_perm || !expert_offsets) return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_unsorted: NULL pointer");
-    if (!moe_grouped_ffn_wq_unsorted_supported(T, k, E, d, F, bits, group_size, act_dtype))
-        return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_unsorted: only 1 to %d assignments of fp16 or bf16 rows to at most %d experts with k = 1 or 2, d and F "
-                                         "multiples of 64, 4- or 8-bit weights and group sizes that are 0 or a multiple of 64 dividing d and F are taken",
-                    kUnsortedMaxAssign, kUnsortedMaxExperts);
-    if (expert_scale && k != 1) return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_unsorted: the fused un-permute needs k = 1 (one expert per token)");
-    return ffn_impl(x, act_dtype, expert_offsets, T * k, E, T, d, F, bits, group_size, activation, w1_packed, s1, b1, w2_packed, s2, b2, out, out_dtype,
-                    workspace, workspace_bytes, stream, nullptr, k, expert_scale, expert_idx, perm_src, inv_perm, expert_offsets, true);
-}
-
 // Decode-sized batches: moe_permute and moe_grouped_ffn_wq in one call.  fc1 runs in the straight-line
 // streaming kernel, whose blocks rebuild the permutation from the gate's expert indices, fetch their
 // rows from the tokens and write perm_src / inv_perm / expert_offsets on the way; fc2 and moe_combine
@@ -507,6 +466,59 @@ extern "C" int moe_grouped_ffn_wq_gated_pays(int T, int k, int E, int d, int F, 
     if (!gated_shapes(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
     const int R = T * k;
     return gated_decode(R, E, d, F, bits) || R <= E || (bits == 8 && k == 2 && R <= 2 * E) || (double)E * d * F * bits / 8 <= 150e6;
+}
+
+// moe_permute's index and moe_grouped_ffn_wq_indexed in one call: fc1's row tiles sort for themselves (find_unsorted_item).
+extern "C" int moe_grouped_ffn_wq_unsorted_supported(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
+{
+    using namespace moe;
+    if (T <= 0 || k < 1 || k > 2 || E <= 0 || E > kUnsortedMaxExperts || (long)T * k > kUnsortedMaxAssign || d <= 0 || F <= 0 || d % 64 || F % 64) return 0;
+    if ((bits != 4 && bits != 8) || group_size < 0 || (group_size && (group_size % 64 || d % group_size || F % group_size))) return 0;
+    return act_dtype == MOE_F16 || act_dtype == MOE_BF16;
+}
+
+// ... or, for the batches whose fc1 the gated call would run in the streaming kernel and whose fc2 runs in row tiles, that kernel, which sorts for itself as well.
+static bool unsorted_streams(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
+{
+    using namespace moe;
+    return gated_shapes(T, k, E, d, F, bits, group_size, act_dtype) == 1 && moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype) &&
+           four_call_kernel(T * k, E, T, F, d, bits, SCALE_CHANNEL, false) == GEMM_TILED;
+}
+
+// Whether a layer that takes the indexed call should take this one: the launch that it saves is 2 to 3.5 us, and every round of fc1's blocks pays for
+// sorting, the more the more assignments there are.  us a step, with the index in a launch / in fc1, by fc1's blocks per compute unit: 62 tokens, one of 8 experts of 512 x
+// 2048 8-bit (0.5) 30.6 / 28.7; 683, two of 32 of 512 x 2048 (1.0) 35.4 / 32.3; 1270, two of 16 of 1024 x 4096 8-bit (3.0) 87.2 / 83.9; 1555, one of 8 of 2048 x 8192
+// 8-bit (3.6) 158.1 / 158.6; few assignments, 31, two of 64 of 2048 x 8192 (5.5) 173.1 / 170.8; 107, two (7.5) 217.9 / 217.3; left out 1215, two of 64 of 2048 x 8192 (8)
+// 292 / 295; 387, two of 128 of 1024 x 4096 8-bit (15.8) 207 / 212.
+extern "C" int moe_grouped_ffn_wq_unsorted_pays(int T, int k, int E, int d, int F, int bits, int group_size, int act_dtype)
+{
+    using namespace moe;
+    if (!moe_grouped_ffn_wq_unsorted_supported(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
+    // one expert per token, fc1 streaming: fc2 stores the output, where the gated call leaves it to moe_combine (40 tokens, one of 32 experts of 1024 x 4096, 8-bit,
+    // 46.0 / 43.8 us a step; 200, one of 8, 39.7 / 37.9)
+    if (moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype)) return k == 1 && unsorted_streams(T, k, E, d, F, bits, group_size, act_dtype);
+    GemmArgs g{};
+    g.R = T * k, g.E = E, g.K = d, g.N = F;
+    const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
+    return row_tile_blocks(g, bits, grouped && act_dtype == MOE_BF16 && group_size == 128 ? SCALE_GROUP_ACC : SCALE_CHANNEL) <= 256 * (g.R <= 512 ? 8 : 3.5);
+}
+
+extern "C" int moe_grouped_ffn_wq_unsorted(const void *x, int act_dtype, const int32_t *expert_idx, const float *expert_scale, int T, int k, int E,
+                                           int d, int F, int bits, int group_size, int activation, const void *w1_packed, const void *s1,
+                                           const void *b1, const void *w2_packed, const void *s2, const void *b2, void *out, int out_dtype,
+                                           int32_t *perm_src, int32_t *inv_perm, int32_t *expert_offsets, void *workspace,
+                                           size_t workspace_bytes, void *stream)
+{
+    using namespace moe;
+    if (!expert_idx || !perm_src || !inv_perm || !expert_offsets) return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_unsorted: NULL pointer");
+    if (!moe_grouped_ffn_wq_unsorted_supported(T, k, E, d, F, bits, group_size, act_dtype))
+        return fail(MOE_ERR_UNSUPPORTED, "moe_grouped_ffn_wq_unsorted: only 1 to %d assignments of fp16 or bf16 rows to at most %d experts with k = 1 or 2, d and F "
+                                         "multiples of 64, 4- or 8-bit weights and group sizes that are 0 or a multiple of 64 dividing d and F are taken",
+                    kUnsortedMaxAssign, kUnsortedMaxExperts);
+    if (expert_scale && k != 1) return fail(MOE_ERR_INVALID_ARG, "moe_grouped_ffn_wq_unsorted: the fused un-permute needs k = 1 (one expert per token)");
+    return ffn_impl(x, act_dtype, expert_offsets, T * k, E, T, d, F, bits, group_size, activation, w1_packed, s1, b1, w2_packed, s2, b2, out, out_dtype,
+                    workspace, workspace_bytes, stream, nullptr, k, expert_scale, expert_idx, perm_src, inv_perm, expert_offsets, true,
+                    unsorted_streams(T, k, E, d, F, bits, group_size, act_dtype));
 }
 
 // Whether a layer should take the indexed call: for bf16 rows, which run in row tiles anyway, and for more rows than experts where

@@ -57,12 +57,13 @@ class MoEExpertLayer:
         self._ffn_call = "moe_grouped_ffn_wq_routed"
         if not self.routed and fuse_routing and B.moe_grouped_ffn_wq_indexed_pays(R, E, T, d, F, bits, group_size, act_dtype):
             self.routed, self._ffn_call = True, "moe_grouped_ffn_wq_indexed"
-        # ... and in small batches fc1's row tiles sort for themselves
-        self.unsorted = self.routed and B.moe_grouped_ffn_wq_unsorted_pays(T, k, E, d, F, bits, group_size, act_dtype)
         # decode-sized batches: the permutation is rebuilt inside fc1 (no permute launch, no x_perm copy)
         self.gated = 0
         if fuse_routing and B.moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype):
             self.gated = B.moe_grouped_ffn_wq_gated_supported(T, k, E, d, F, bits, group_size, act_dtype)
+        # ... and in small batches fc1 sorts for itself (of a layer that takes the gated call with one expert per token, and stores the output in fc2: y is
+        # never stored then either)
+        self.unsorted = (self.gated == 1 and y_dtype is None if self.gated else self.routed) and B.moe_grouped_ffn_wq_unsorted_pays(T, k, E, d, F, bits, group_size, act_dtype)
         # few rows per expert, of any kind: gate, one streaming launch for everything up to y, its reduction (y is never stored:
         # not for a layer that asks for a type of y)
         self.sliced = bool(fuse_routing) and y_dtype is None and B.moe_grouped_ffn_wq_sliced_pays(T, k, E, d, F, bits, group_size, act_dtype)
@@ -170,6 +171,14 @@ class MoEExpertLayer:
                     p(self.b2), p(self.out), odt, p(self.perm_src), p(self.inv_perm), p(self.expert_offsets), p(self.ws_ffn),
                     self.ws_ffn.numel(), st), "moe_grouped_ffn_wq_sliced")
             return [gate, ffn]
+        scatter = self.k == 1 and finished is None
+        if self.unsorted and (scatter or not self.gated):
+            ffn = (lib.moe_grouped_ffn_wq_unsorted,
+                   (p(x), dt, p(self.expert_idx), p(self.expert_scale) if scatter else None, self.T, self.k, self.E, self.d, self.F, self.bits,
+                    self.group_size, self.activation, p(self.w1_packed), p(self.s1), p(self.b1), p(self.w2_packed), p(self.s2), p(self.b2),
+                    p(self.out) if scatter else p(self.y_perm), odt if scatter else ydt, p(self.perm_src), p(self.inv_perm),
+                    p(self.expert_offsets), p(self.ws_ffn), self.ws_ffn.numel(), st), "moe_grouped_ffn_wq_unsorted")
+            return [gate, ffn] if scatter else [gate, ffn, combine]
         if self.gated:
             # level 2 with an fp32 layer output: fc2 adds the scaled rows straight into out (no combine launch)
             fused = self.gated == 2 and self.out_dtype == torch.float32
@@ -183,14 +192,6 @@ class MoEExpertLayer:
         if self.routed:
             # index only (no x_perm copy); fc1 gathers, and fc2 scatters when there is one expert per
             # token and no pruned row (a pruned token's output row would stay unwritten)
-            scatter = self.k == 1 and finished is None
-            if self.unsorted:
-                ffn = (lib.moe_grouped_ffn_wq_unsorted,
-                       (p(x), dt, p(self.expert_idx), p(self.expert_scale) if scatter else None, self.T, self.k, self.E, self.d, self.F, self.bits,
-                        self.group_size, self.activation, p(self.w1_packed), p(self.s1), p(self.b1), p(self.w2_packed), p(self.s2), p(self.b2),
-                        p(self.out) if scatter else p(self.y_perm), odt if scatter else ydt, p(self.perm_src), p(self.inv_perm),
-                        p(self.expert_offsets), p(self.ws_ffn), self.ws_ffn.numel(), st), "moe_grouped_ffn_wq_unsorted")
-                return [gate, ffn] if scatter else [gate, ffn, combine]
             permute = (lib.moe_permute, (p(self.expert_idx), None, dt, self.T, self.k, self.E, self.d, None,
                                          p(self.perm_src), p(self.inv_perm), p(self.expert_offsets), p(self.ws_permute),
                                          self.ws_permute.numel(), st), "moe_permute")

@@ -288,3 +288,13 @@ def test_small_and_few_experts_are_sliced_up_to_about_one_block_each():
     assert _pays(229, 1, 128, 768, 3072, 8, 0, bf) and _pays(11, 2, 16, 4096, 16384, 4) and _pays(12, 1, 32, 2048, 8192, 8)
     assert not any(_pays(*c) for c in [(256, 1, 8, 512, 2048, 8), (113, 2, 8, 2048, 8192, 4), (238, 2, 8, 768, 3072, 4), (7, 1, 32, 4096, 16384, 8), (11, 1, 64, 4096, 16384, 4, 0, bf),
                                        (133, 1, 8, 4096, 16384, 8), (99, 2, 32, 4096, 16384, 4)])
+
+
+def test_the_unsorted_call_streams_fc1_where_the_gated_call_does():
+    """Level 1 of the gated call, where it pays: the same launches, fc2 in row tiles; a layer takes it with one expert per token."""
+    lib = B.load()
+    sizes = [(40, 1, 32, 1024, 4096, 8), (200, 1, 8, 1024, 4096, 8), (40, 1, 8, 512, 2112, 8), (100, 2, 12, 512, 2112, 8)]
+    for s, a, b in zip(sizes, L.record([L.unsorted(*s) for s in sizes]), L.record([L.gated(*s, scale=False) for s in sizes])):
+        assert a.rc == b.rc == 0 and a.launches == b.launches and _kernels(a)[0] == "stream_unrolled_kernel", (s, a.launches)
+        assert bool(lib.moe_grouped_ffn_wq_unsorted_pays(*s, 0, B.MOE_F16)) == (s[1] == 1)
+    assert not lib.moe_grouped_ffn_wq_unsorted_pays(256, 1, 8, 512, 2048, 8, 0, B.MOE_F16)      # level 2: everything fused in the gated call

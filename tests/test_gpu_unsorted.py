@@ -57,3 +57,29 @@ def test_unsorted_call_equals_permute_and_the_indexed_call(T, k, E, d, F, bits, 
     active = int(off[E])
     rows = src[:active].long() if k == 1 else slice(0, active)          # what is written: the active tokens' rows, or the active sorted rows
     assert torch.equal(y[rows], want[rows]) and bool(torch.isfinite(y[rows]).all())
+
+
+@pytest.mark.parametrize("T,k,E,d,F,bits", [(40, 1, 8, 512, 2112, 8), (1, 1, 3, 1024, 2112, 4), (256, 1, 16, 1024, 1088, 4), (100, 2, 12, 512, 2112, 8), (37, 2, 40, 2048, 1088, 4)])
+@pytest.mark.parametrize("prune", [False, True])
+def test_unsorted_call_that_streams_fc1_equals_the_gated_call(T, k, E, d, F, bits, prune):
+    """Where the gated call runs fc1 in the streaming kernel and fc2 in row tiles: its bits, and with the un-permute those times the gate's scale."""
+    print(f"unsorted, streaming T={T} k={k} E={E} d={d} F={F} bits={bits} pruned={prune}", flush=True)
+    assert B.moe_grouped_ffn_wq_gated_supported(T, k, E, d, F, bits, 0, torch.float16) == 1 and B.moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, 0, torch.float16)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T + E)
+    (s1, p1), (s2, p2) = _weights(gen, E, d, F, bits, 0), _weights(gen, E, F, d, bits, 0)
+    x = torch.randn((T, d), generator=gen, device="cuda").half()
+    idx = torch.randint(0, E, (T, k), generator=gen, device="cuda", dtype=torch.int32)
+    if prune:
+        idx[torch.rand(T, generator=gen, device="cuda") < 0.4] = E
+    want = B.moe_grouped_ffn_wq_gated(x, idx, E, d, F, bits, 0, p1, s1, p2, s2, y_dtype=torch.float32)
+    assert B.load().moe_last_ffn_kernels().decode().startswith("stream_unrolled_kernel grouped_gemm")
+    got = B.moe_grouped_ffn_wq_unsorted(x, idx, E, d, F, bits, 0, p1, s1, p2, s2, out_dtype=torch.float32)
+    assert B.load().moe_last_ffn_kernels().decode().startswith("stream_unrolled_kernel grouped_gemm")
+    active = int(want[3][E])
+    assert all(torch.equal(a, b) for a, b in zip(got[1:], want[1:])) and torch.equal(got[0][:active], want[0][:active])
+    if k == 1:
+        scale = torch.rand((T, 1), generator=gen, device="cuda")
+        out = B.moe_grouped_ffn_wq_unsorted(x, idx, E, d, F, bits, 0, p1, s1, p2, s2, expert_scale=scale, out_dtype=torch.float32)[0]
+        rows = want[1][:active].long()
+        assert torch.equal(out[rows], want[0][:active] * scale[rows])
