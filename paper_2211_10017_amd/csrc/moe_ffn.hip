@@ -281,7 +281,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     g1.wq = (const uint8_t *)w1_packed; g1.scales = (const __half *)s1; g1.bias = (const __half *)b1;
     g1.out = h; g1.E = E; g1.R = R; g1.K = d; g1.N = F; g1.g = grouped ? group_size : d;
     g1.out_dtype = act_dtype; g1.act = activation;
-    g1.a_src = perm_src; g1.a_div = k;
+    g1.a_src = perm_src; g1.a_div = k; g1.indexed = tiles_only;
     if (gate_idx) {     // decode-sized: fc1 rebuilds the permutation from the gate's output and writes the index arrays
         g1.gate_idx = gate_idx; g1.n_assign = R; g1.gate_k = k;
         g1.perm_src_out = perm_src_out; g1.inv_perm_out = inv_perm_out; g1.offsets_out = offsets_out;
@@ -498,7 +498,7 @@ extern "C" int moe_grouped_ffn_wq_unsorted_pays(int T, int k, int E, int d, int 
     // 46.0 / 43.8 us a step; 200, one of 8, 39.7 / 37.9)
     if (moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype)) return k == 1 && unsorted_streams(T, k, E, d, F, bits, group_size, act_dtype);
     GemmArgs g{};
-    g.R = T * k, g.E = E, g.K = d, g.N = F;
+    g.R = T * k, g.E = E, g.K = d, g.N = F, g.indexed = 1;
     const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
     return row_tile_blocks(g, bits, grouped && act_dtype == MOE_BF16 && group_size == 128 ? SCALE_GROUP_ACC : SCALE_CHANNEL) <= 256 * (g.R <= 512 ? 8 : 3.5);
 }

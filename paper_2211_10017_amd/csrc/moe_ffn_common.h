@@ -26,6 +26,7 @@ struct GemmArgs {
     int out_dtype;
     int act;                  // MOE_ACT_NONE (plain GEMM) | MOE_ACT_RELU | MOE_ACT_GELU applied after the bias
     int tile_units;           // tiled kernel: row tiles of at most 32 * tile_units rows (set by the launcher)
+    int indexed;              // of a call whose rows come through the routing index: both its GEMMs run in row tiles
     int ring_long;            // ring kernel: whether a block may have its compute unit's LDS to itself (set by the launcher)
     // tiled kernel only: rows fetched / stored through the routing index instead of a permuted copy
     const int32_t *a_src;     // [R] or null: row r of A is a[a_src[r] / a_div]

@@ -27,6 +27,8 @@ static int ring_rows(const GemmArgs &p, int bits, int mean)
     return ((long)p.R / 64 + experts / 2) * ncol <= 224 ? 64 : 0;
 }
 
+constexpr long kLongRingWeights = 18000000l;        // the fewest 8-bit weights for ring_long
+
 // Row tiles that R rows make on E experts under uniform routing, an expert's rows taken as normally distributed.
 double expected_row_tiles(long R, long E, int bm)
 {
@@ -35,6 +37,27 @@ double expected_row_tiles(long R, long E, int bm)
     for (double first = tiles * bm; first < mean + 4 * sd; first += bm)
         tiles += sd > 0 ? 0.5 * erfc((first + 0.5 - mean) / (sd * M_SQRT2)) : 1.0;
     return tiles * E;
+}
+
+// ring_rows for rows fetched through the routing index, as layers do (its own lines were drawn with permuted copies), of eight experts and more, by the
+// tiles that uniform routing makes (350 drawn layers, both GEMMs in every form: 49 of 710 GEMMs change, 44 of them by more than 2 % of the step, 7 % on
+// average, none to the worse; us a step below):
+//  - K up to 1024, where a block's start and end are most of it and the ring is hardly full before it ends: register-fed tiles from 0.9 of 32 rows per
+//    compute unit on, with 8-bit weights between 0.8 and 1.8 and 11 to 64 rows per expert.  (fc1 of 446 tokens, two of 64 experts of 768 x 3072, 62 -> 53;
+//    470, one of 16 of 1024 x 4096, 46 -> 38; 783, one of 16 of 512 x 2048 with groups of 128, 34 -> 32.5; 8-bit, 705, one of 32 of 768 x 3072, 53.6 -> 49.6;
+//    left out 382, one of 8 of 768 x 3072, 0.7 tiles, 35 and 34.5.)
+//  - longer K in 64-row blocks: 32-row ones up to one of them per compute unit (fc2 of 382 tokens, one of 8 of 3072 x 768, 34.7 -> 31.6; 735, 38.5 -> 35.3; 1318, one
+//    of 8 of 2048 x 512, fc1 in tiles as well, 31.9 -> 28.7; at 1.4 blocks, 74 rows on each of 32 of 2048 x 512, 38 -> 40), unless ring_long takes those of 64.
+//  - up to eight rows per expert of 4-bit weights in 32-row blocks, from 3.9 of these per compute unit on: tiles, which unpack as much for twice the columns
+//    (fc2 of 420 tokens, two of 128 experts of 4096 x 1024, 152 -> 138).
+static int ring_rows_for(const GemmArgs &p, int bits, int mean)
+{
+    const int ring = ring_rows(p, bits, mean);
+    if (!ring || p.E < 8 || !p.indexed) return ring;
+    const double tiles = expected_row_tiles(p.R, p.E, 32), fed = tiles * ((p.N + 255) / 256) / 256, blocks = tiles * ((p.N + 127) / 128) / 256;
+    if (p.K <= 1024) return (bits == 4 ? fed >= 0.9 : mean > 10 && mean <= 64 && fed >= 0.8 && fed <= 1.8) ? 0 : ring;
+    if (ring == 64 && blocks <= 1.0 && !(bits == 8 && (long)p.E * p.K * p.N >= kLongRingWeights)) return 32;
+    return ring == 32 && bits == 4 && mean <= 8 && blocks >= 3.9 ? 0 : ring;
 }
 
 // Whether 64-row blocks of 8-bit weights take the whole LDS of a compute unit for their ring: uniform routing makes no more blocks
@@ -46,7 +69,7 @@ double expected_row_tiles(long R, long E, int bm)
 // 2048 36.1 -> 38.4.)
 static bool ring_long(const GemmArgs &p, int bm)
 {
-    return (long)p.E * p.K * p.N >= 18000000l && expected_row_tiles(p.R, p.E, bm) * ((p.N + 127) / 128) <= (p.E > 1 ? 250 : 256);
+    return (long)p.E * p.K * p.N >= kLongRingWeights && expected_row_tiles(p.R, p.E, bm) * ((p.N + 127) / 128) <= (p.E > 1 ? 250 : 256);
 }
 
 // 32-row tiles of a register-fed block.
@@ -57,6 +80,12 @@ static bool ring_long(const GemmArgs &p, int bm)
 static int tile_height(const GemmArgs &p, int bits, int mean)
 {
     return mean <= 32 ? 1 : (mean <= 64 || p.K <= 2048 || (bits == 8 && mean <= 256)) ? 2 : 4;
+}
+
+// ... and of one that takes the ring's place (ring_rows_for): there are few tiles
+static int tile_height_for(const GemmArgs &p, int bits, int mean)
+{
+    return p.indexed && mean <= 100 && ring_rows(p, bits, mean) ? 1 : tile_height(p, bits, mean);
 }
 
 // Whether bf16 rows of a channel-scaled layer meet bf16 codes as they are (codes_to_bf16) instead of being converted to scaled FP16 ahead of
@@ -87,7 +116,7 @@ bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits)
 // Blocks that hold rows when launch_tiled_gemm takes this GEMM, under uniform routing.
 double row_tile_blocks(const GemmArgs &p, int bits, int smode)
 {
-    const int mean = (p.R + p.E - 1) / p.E, ring = ring_rows(p, bits, mean), tm = tile_height(p, bits, mean);
+    const int mean = (p.R + p.E - 1) / p.E, ring = ring_rows_for(p, bits, mean), tm = tile_height_for(p, bits, mean);
     if (ring) return expected_row_tiles(p.R, p.E, ring) * ((p.N + 127) / 128);
     return expected_row_tiles(p.R, p.E, 32 * (smode == SCALE_GROUP_ACC && tm > 2 ? 2 : tm)) * ((p.N + 255) / 256);
 }
@@ -96,7 +125,7 @@ int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
 {
     // row-tile height from the mean rows per expert (the offsets themselves stay on the device)
     const int mean = (p.R + p.E - 1) / p.E;
-    const int bm = ring_rows(p, bits, mean);
+    const int bm = ring_rows_for(p, bits, mean);
     note_kernel(bm ? "grouped_gemm_ring_kernel" : "grouped_gemm_kernel");
     if (bm) {
         const long slots = (long)p.R / bm + (p.E < p.R ? p.E : p.R);
@@ -107,7 +136,7 @@ int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
         (bits == 4 ? launch_ring_4 : launch_ring_8)(q, smode, bm, dim3((unsigned)wgs), s);
         return check_launch("moe_grouped_ffn_wq (gemm)");
     }
-    int tm = tile_height(p, bits, mean);
+    int tm = tile_height_for(p, bits, mean);
     if (smode == SCALE_GROUP_ACC && tm > 2) tm = 2;
     const long most = p.R;                                      // experts that can hold rows
     const long ncol = (p.N + 255) / 256;

@@ -298,3 +298,15 @@ def test_the_unsorted_call_streams_fc1_where_the_gated_call_does():
         assert a.rc == b.rc == 0 and a.launches == b.launches and _kernels(a)[0] == "stream_unrolled_kernel", (s, a.launches)
         assert bool(lib.moe_grouped_ffn_wq_unsorted_pays(*s, 0, B.MOE_F16)) == (s[1] == 1)
     assert not lib.moe_grouped_ffn_wq_unsorted_pays(256, 1, 8, 512, 2048, 8, 0, B.MOE_F16)      # level 2: everything fused in the gated call
+
+
+def test_layers_of_eight_experts_and_more_leave_the_ring_by_their_expected_tiles():
+    """Rows through the routing index: short K in register-fed tiles once these fill most of the chip, long K of few 64-row blocks in 32-row ones, and
+    what lies on the other side of each line as with permuted copies."""
+    cases = [((892, 64, 2, 768, 3072, 4), [-32, 32]), ((470, 16, 1, 1024, 4096, 4), [-32, 32]), ((783, 16, 1, 512, 2048, 4, 128), [-32, 32]), ((705, 32, 1, 768, 3072, 8), [-32, 32]),
+             ((382, 8, 1, 768, 3072, 4), [64, 32]), ((1318, 8, 2, 512, 2048, 4), [-64, 32]), ((840, 128, 2, 1024, 4096, 4), [-32, -32]), ((2368, 32, 1, 512, 2048, 4), [-64, 64]),
+             ((320, 4, 1, 768, 3072, 4), [64, 64]), ((1000, 8, 2, 768, 3072, 8), [-64])]       # (the last: fc2 in the long ring)
+    from test_gpu_indexed import TAKEN
+    cases += TAKEN
+    for (sizes, want), call in zip(cases, L.record([L.indexed(*c) for c, _ in cases])):
+        assert call.rc == 0 and _rows_of_tiles(call) == want, (sizes, call.launches)

@@ -1,4 +1,4 @@
-"""Rows fetched through the routing index for every size and row type: the same bits as permuted copies give.  And the
+"""Rows fetched through the routing index for every size and row type: the same bits as permuted copies give in the same tiles.  And the
 conversion of bf16 rows at the lengths where its form changes."""
 import ctypes
 
@@ -58,6 +58,34 @@ def test_bf16_rows_of_every_length(K, g):
     (q1, o1), (q2, o2) = (oracle.quantize(m, 8, g) for m in w)
     want = oracle.grouped_ffn(x.float().cpu().numpy(), off, q1, o1, q2, o2, g, oracle.BF16)
     max_abs, rel = error_metrics(y.cpu().numpy(), want)
+    assert max_abs <= MAX_ABS_TOL * max(1.0, float(np.abs(want).max()) / 8) and rel <= REL_L2_TOL
+
+
+# (assignments, experts, k, d, F, bits[, g]) whose tiles a layer takes otherwise than permuted copies would, and the rows per block of fc1 and fc2
+# (test_dispatch_cpu.py), negative in register-fed tiles
+TAKEN = [((800, 8, 1, 64, 2112, 4), [-32, 32]), ((1318, 8, 2, 64, 2112, 4, 64), [-64, 32]), ((1280, 32, 2, 64, 1088, 8), [-32, 32]),
+         ((640, 128, 1, 1024, 1088, 4), [-32, -32])]
+
+
+@pytest.mark.parametrize("load", ["even", "one", "pruned"])
+@pytest.mark.parametrize("sizes,tiles", TAKEN)
+def test_tiles_of_indexed_rows_match_oracle(sizes, tiles, load):
+    R, E, k, d, F, bits, g = (*sizes, 0)[:7]
+    print(f"indexed tiles {sizes} {load}", flush=True)
+    x, _, w, ((s1, p1), (s2, p2)), _, _ = _case([1] * E, d, F, bits, g, "f16", R)
+    rng, T = np.random.default_rng(R), R // k
+    x = to_dev(rng.standard_normal((T, d)).astype(np.float32), torch.float16)
+    idx = np.stack([(np.arange(T) + j * 3) % (1 if load == "one" and j == 0 else E) for j in range(k)], 1).astype(np.int32)
+    if load == "pruned":
+        idx[rng.random(T) < 0.3] = E
+    y, src, _, off = B.moe_grouped_ffn_wq_unsorted(x, to_dev(idx, torch.int32), E, d, F, bits, g, p1, s1, p2, s2, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    off, src = off.cpu().numpy(), src.cpu().numpy()
+    (q1, o1), (q2, o2) = (oracle.quantize(m, bits, g) for m in w)
+    rows = src[:off[E]] // k
+    want = oracle.grouped_ffn(x.float().cpu().numpy()[rows], off, q1, o1, q2, o2, g, oracle.F16)
+    max_abs, rel = error_metrics(y.cpu().numpy()[:off[E]], want)
+    print(f"   max_abs={max_abs:.3e} rel_l2={rel:.3e}", flush=True)
     assert max_abs <= MAX_ABS_TOL * max(1.0, float(np.abs(want).max()) / 8) and rel <= REL_L2_TOL
 
 
