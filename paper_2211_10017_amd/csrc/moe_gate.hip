@@ -5,7 +5,7 @@
 // four sums) run on the matrix cores bit for bit: a wavefront owns one of the four partial sums for a tile of tokens and
 // experts, the four meet in LDS, and sixteen lanes finish a token.  Two tilings: gate_mfma_kernel (16 tokens x 16 experts
 // per instruction) and gate_quad_kernel (4 tokens x 64 experts); few tokens take the vector ALU with a lane per expert or several
-// experts per lane (gate_token_kernel, gate_lanes_kernel).  T = 8192, d = 4096, 64 experts: 196 -> 48 us (bf16 208 ->
+// experts per lane (gate_token_kernel, gate_lanes_kernel and their other forms).  T = 8192, d = 4096, 64 experts: 196 -> 48 us (bf16 208 ->
 // 47), T = 4096, d = 2048, 128 experts: 76 -> 28.6 us, T = 16384, d = 1024, 64 experts: 55 -> 32 us against multiply-adds in
 // the vector ALU with a lane per expert or per token; T = 64, d = 1024, 32 experts: 13 -> 9 us with cold caches.
 #include <math.h>
@@ -335,12 +335,9 @@ __global__ __launch_bounds__(256 * S) void gate_mfma_kernel(const uint16_t *__re
 
 // Few tokens and 33 to 64 experts: the same chains in v_mfma_f32_4x4x1_16b_f32, sixteen 4 x 4 x 1 products that make up
 // 4 tokens x 64 experts x 1 feature.  A block takes four tokens instead of sixteen, so the batch spreads over four times
-// as many compute units at the same rate of the matrix pipe.  An octet of features is one 16-byte load of the tokens and two
-// 8-byte loads of the gate weight: lane (j, r) = (lane & 15, lane >> 4) brings experts 4 j .. 4 j + 3 of features r and 4 + r, and
-// the same 4 x 4 transposition that spreads the tokens' features above leaves it with expert 4 j + r of all eight.  (VEC; numbers
-// of experts that are no multiple of four: a lane per expert, one 2-byte load per feature.  One token, 64 experts, caches warm:
-// 8.5 -> 7.2 us at d = 1024, 12.9 -> 10.9 at 2048; several tokens within 2 %.)  A ring of R octets.
-template <bool BF16, int R, bool VEC>
+// as many compute units at the same rate of the matrix pipe.  A lane per expert, one 2-byte load per feature (numbers of experts that
+// are no multiple of four; the others take gate_token_kernel).  A ring of R octets.
+template <bool BF16, int R>
 __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
                                                             const float *__restrict__ bias,
                                                             const uint8_t *__restrict__ finished, int T, int d, int E,
@@ -349,12 +346,10 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
 {
     typedef float f4_t __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     constexpr int NT = 4, ld = 64 + 4;
     __shared__ float part[4 * NT * ld];
     const int lane = threadIdx.x & 63;
     const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int own = VEC ? 4 * (lane & 15) + (lane >> 4) : lane;      // this lane's expert
     const int t0 = blockIdx.x * NT;
     const int nblk = (d + kGateBlk - 1) / kGateBlk;
     const int mine = p < nblk ? (nblk - p + 3) / 4 : 0;
@@ -364,19 +359,14 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
     const int x_off = min(lane & 3, rows - 1) * d * 2;
-    const int w_off = VEC ? ((lane >> 4) * E + min(4 * (lane & 15), E - 4)) * 2 : min(own, E - 1) * 2;   // (experts clamped where they do not exist)
+    const int w_off = min(lane, E - 1) * 2;             // (experts clamped where they do not exist)
 
-    struct Octet { u32x4 x; uint32_t w[VEC ? 4 : 8]; } ring[R];
+    struct Octet { u32x4 x; uint32_t w[8]; } ring[R];
     auto load = [&](Octet &c, int q) __attribute__((always_inline)) {
         const int f = feature(q);
         c.x = __builtin_amdgcn_raw_buffer_load_b128(rx, x_off, f * 2, 0);
-        if constexpr (VEC) {
-            const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rw, w_off, f * E * 2, 0), b = __builtin_amdgcn_raw_buffer_load_b64(rw, w_off, (f + 4) * E * 2, 0);
-            c.w[0] = a.x; c.w[1] = a.y; c.w[2] = b.x; c.w[3] = b.y;
-        } else {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) c.w[u] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off, (f + u) * E * 2, 0);
-        }
+        for (int u = 0; u < 8; ++u) c.w[u] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off, (f + u) * E * 2, 0);
     };
     f4_t acc = {0.f, 0.f, 0.f, 0.f};
     struct Ops { float x[8], w[8]; };
@@ -386,15 +376,8 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
             const uint32_t v = u < 2 ? c.x.x : u < 4 ? c.x.y : u < 6 ? c.x.z : c.x.w;
             o.x[u] = act_to_float<BF16>((uint16_t)(v >> (16 * (u & 1))));
         }
-        if constexpr (VEC) {
-            uint32_t q[4];
-            transpose_quads(c.w[0], c.w[1], c.w[2], c.w[3], q);     // dword u: features u and 4 + u of expert `own`
 #pragma unroll
-            for (int u = 0; u < 8; ++u) o.w[u] = act_to_float<BF16>((uint16_t)(q[u & 3] >> (16 * (u >> 2))));
-        } else {
-#pragma unroll
-            for (int u = 0; u < 8; ++u) o.w[u] = act_to_float<BF16>((uint16_t)c.w[u]);
-        }
+        for (int u = 0; u < 8; ++u) o.w[u] = act_to_float<BF16>((uint16_t)c.w[u]);
     };
     auto multiply = [&](const Ops &o) __attribute__((always_inline)) {
 #pragma unroll
@@ -429,7 +412,7 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
         }
     });
 #pragma unroll
-    for (int i = 0; i < NT; ++i) part[(p * NT + i) * ld + own] = acc[i];
+    for (int i = 0; i < NT; ++i) part[(p * NT + i) * ld + lane] = acc[i];
     __syncthreads();
     finish_tokens<1, 4>(part, NT, ld, t0, p, 4, bias, finished, T, E, k, renorm, expert_idx, expert_scale);
 }
@@ -542,22 +525,21 @@ __global__ __launch_bounds__(256) void gate_lanes_kernel(const uint16_t *__restr
     finish_tokens<NE == 2 ? 2 : 1, 4, NE <= 2 ? 16 : 64>(part, NT, ld, t0, p, 4, bias, finished, min(T, t0 + TB), E, k, renorm, expert_idx, expert_scale);
 }
 
-// Few tokens by 17 to 64 experts, E a multiple of eight: a lane per expert, EP = 32 or 64 lanes per token, 64 / EP tokens per block, plain fp32
+// Few tokens by 24 or 32 experts and up to 1024 features: a lane per expert, 32 lanes per token, two tokens per block, plain fp32
 // multiply-adds.  The block takes 512 features at a time (128 of each partial sum): the gate weight's part of them goes through
 // LDS, eight features of an expert side by side, so that an octet of a chain is one 16-byte read of weights and one of the token.
 // What bounds so small a launch is its latencies in a row: the code (about 100 clocks per 64 bytes that a compute unit has not run
 // before, hence one rolled loop), the loads (all of a chunk's at once, 16 bytes each, the next chunk's under this one's chains) and the chains
 // themselves, 8 clocks per feature of a partial sum.
-template <bool BF16, int EP>
-__global__ __launch_bounds__(256) void gate_token_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
+template <bool BF16>
+__global__ __launch_bounds__(256) void gate_token_kernel_lds(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
                                                          const float *__restrict__ bias,
                                                          const uint8_t *__restrict__ finished, int T, int d, int E,
                                                          int k, int renorm, int32_t *__restrict__ expert_idx,
                                                          float *__restrict__ expert_scale)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int NT = 64 / EP, OCT = 64;               // tokens of the block, octets of a chunk
-    constexpr int SB = EP == 64 ? 2 : 1;                // 8 x 8 blocks of the gate weight per thread and chunk
+    constexpr int EP = 32, NT = 64 / EP, OCT = 64;      // tokens of the block, octets of a chunk
     constexpr int ld = EP + 4;
     __shared__ u32x4 s_w[OCT * EP], s_x[NT * OCT];
     float *part = reinterpret_cast<float *>(s_w);       // at the end: [4][4][ld]
@@ -566,24 +548,16 @@ __global__ __launch_bounds__(256) void gate_token_kernel(const uint16_t *__restr
     const int p = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int t0 = blockIdx.x * NT, rows = min(NT, T - t0);
     const int groups = E >> 3;
-    int w_off[SB], oc[SB], eg[SB];
-#pragma unroll
-    for (int b = 0; b < SB; ++b) {
-        const int id = tid + 256 * b;
-        oc[b] = id / groups, eg[b] = id - oc[b] * groups;
-        w_off[b] = (oc[b] * 8 * E + eg[b] * 8) * 2;
-    }
+    const int oc = tid / groups, eg = tid - oc * groups, w_off = (oc * 8 * E + eg * 8) * 2;      // this thread's 8 x 8 block of a chunk
     const int x_off = (min(tid >> 6, rows - 1) * d + (tid & 63) * 8) * 2;
-    u32x4 W[SB][8], X;
+    u32x4 W[8], X;
     // (extents end with the buffers: what lies past the last feature reads as zero or as the next token's, and is not used)
     auto load = [&](int c) {
         const int left = max(d - c * 512, 0);
         const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg + (size_t)c * 512 * E), 0, left * E * 2, 0x00020000);
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d + c * 512), 0, left ? (rows * d - c * 512) * 2 : 0, 0x00020000);
 #pragma unroll
-        for (int b = 0; b < SB; ++b)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) W[b][i] = __builtin_amdgcn_raw_buffer_load_b128(rw, w_off[b] + i * E * 2, 0, 0);
+        for (int i = 0; i < 8; ++i) W[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, w_off + i * E * 2, 0, 0);
         if (tid < NT * OCT) X = __builtin_amdgcn_raw_buffer_load_b128(rx, x_off, 0, 0);
     };
     load(0);
@@ -592,17 +566,15 @@ __global__ __launch_bounds__(256) void gate_token_kernel(const uint16_t *__restr
     const u32x4 *w_ptr = s_w + p * 16 * E + (ec & ~7) + ((ec & 7) ^ ((ec >> 3) & 7)), *x_ptr = s_x + sub * OCT + p * 16;
     float acc = 0.0f;
     for (int c = 0; c * 512 < d; ++c) {
+        if (oc < OCT) {
 #pragma unroll
-        for (int b = 0; b < SB; ++b)
-            if (oc[b] < OCT) {
+            for (int j = 0; j < 8; ++j) {
+                u32x4 v;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    u32x4 v;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = __builtin_amdgcn_perm(W[b][2 * q + 1][j >> 1], W[b][2 * q][j >> 1], j & 1 ? 0x07060302u : 0x05040100u);
-                    s_w[oc[b] * E + eg[b] * 8 + (j ^ (eg[b] & 7))] = v;
-                }
+                for (int q = 0; q < 4; ++q) v[q] = __builtin_amdgcn_perm(W[2 * q + 1][j >> 1], W[2 * q][j >> 1], j & 1 ? 0x07060302u : 0x05040100u);
+                s_w[oc * E + eg * 8 + (j ^ (eg & 7))] = v;
             }
+        }
         if (tid < NT * OCT) s_x[tid] = X;
         __syncthreads();
         load(c + 1);
@@ -630,6 +602,197 @@ __global__ __launch_bounds__(256) void gate_token_kernel(const uint16_t *__restr
     finish_tokens<1, EP / 16>(part, 4, ld, t0, p, 4, bias, finished, min(T, t0 + NT), E, k, renorm, expert_idx, expert_scale);
 }
 
+// Few tokens, E a multiple of four up to 128: a lane per expert (two with more than 64), plain fp32 multiply-adds, the gate weight
+// from memory straight into registers.  A lane (j, r) brings experts 4 j .. 4 j + 3 of features r and 4 + r in two 8-byte loads, and the 4 x 4
+// transposition that spreads the tokens' features above leaves it with expert 4 j + r of an octet of features; with fewer than 64 experts the sixteen
+// j of a row repeat them for SUB tokens.  TW tokens per lane, so a block takes SUB TW.  Each wavefront keeps its own partial sum's features of
+// the tokens in LDS (bf16 as fp32, which saves a conversion per lane and feature), so it waits for nobody before the end.
+// What bounds it is the chain, 8 clocks per feature and one wavefront per SIMD: the transposition of the next octet, its loads and the reads of the tokens are
+// dealt out one by one into the gaps between the additions (in the other order, spread / additions / loads, 3 % slower), and an octet still takes 130 clocks for
+// the 64 of its chain, the swaps issuing at half rate.  R octets in flight: with 4, warm launches are 0.2 us shorter and layers' steps, whose gate weight comes from memory, 0.3 % longer; with
+// 16, 1.8 % longer.  (Against the gate weight through LDS with two barriers per 512 features, 64 experts, d = 4096: 1.6 us of those each, of which the additions are 0.4.)
+template <bool BF16, int EP, int TW, int R = 8>
+__device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg, const float *__restrict__ bias,
+                                            const uint8_t *__restrict__ finished, int T, int d, int E, int k, int renorm,
+                                            int32_t *__restrict__ expert_idx, float *__restrict__ expert_scale)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef float f4_t __attribute__((ext_vector_type(4)));
+    constexpr int EW = EP > 64 ? 2 : 1, JL = EP / EW / 4, SUB = 16 / JL, NT = TW * SUB;
+    constexpr int ld = EP + 4, NTP = NT < 4 ? 4 : NT;   // (four tokens finish at a time, those past NT are not stored)
+    constexpr int XV = BF16 ? 2 : 1;                    // 16-byte words of an octet of a token
+    constexpr int XP = 2;                               // passes of 64 octets of the tokens that are requested ahead of the weights
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *part = reinterpret_cast<float *>(smem);      // [4][NTP][ld]
+    const int lane = threadIdx.x & 63;
+    const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = lane & (JL - 1), sub = (lane & 15) / JL, r = lane >> 4;
+    const int t0 = blockIdx.x * NT, rows = min(NT, T - t0);
+    const int nblk = (d + kGateBlk - 1) / kGateBlk;
+    const int full = max((d / kGateBlk - p + 3) / 4, 0);                                // whole 128-feature blocks of this partial sum
+    const int rest = (nblk - 1) % 4 == p ? (d % kGateBlk) / 8 : 0, nq = full * 16 + rest;      // octets of the last, short one, and in all
+    u32x4 *s_x = reinterpret_cast<u32x4 *>(smem + 4 * NTP * ld * 4) + (size_t)p * ((nblk + 3) / 4 * 16 + 2) * NT * XV;    // [octet][token]; two octets are read past the end
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
+    int w_off[EW][2];                                   // features r, 4 + r
+#pragma unroll
+    for (int s = 0; s < EW; ++s) {
+        w_off[s][0] = (r * E + min(64 * s + 4 * j, E - 4)) * 2;         // (experts clamped where they do not exist)
+        w_off[s][1] = w_off[s][0] + 8 * E;
+    }
+
+    auto x_load = [&](int q, int b) __attribute__((always_inline)) {
+        return __builtin_amdgcn_raw_buffer_load_b128(rx, (min(b, rows - 1) * d + min((p + 4 * (q >> 4)) * kGateBlk + (q & 15) * 8, d - 8)) * 2, 0, 0);
+    };
+    auto x_store = [&](int q, int b, u32x4 v) __attribute__((always_inline)) {
+        if (q >= nq) return;
+        if constexpr (BF16) {
+            s_x[(q * NT + b) * 2] = u32x4{v.x << 16, v.x & 0xffff0000u, v.y << 16, v.y & 0xffff0000u};
+            s_x[(q * NT + b) * 2 + 1] = u32x4{v.z << 16, v.z & 0xffff0000u, v.w << 16, v.w & 0xffff0000u};
+        } else {
+            s_x[q * NT + b] = v;
+        }
+    };
+    struct Raw { uint32_t w[EW][4]; } ring[R];
+    auto load = [&](Raw &c, int so) __attribute__((always_inline)) {        // so: bytes of the octet's first row
+#pragma unroll
+        for (int s = 0; s < EW; ++s) {
+            const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rw, w_off[s][0], so, 0), b = __builtin_amdgcn_raw_buffer_load_b64(rw, w_off[s][1], so, 0);
+            c.w[s][0] = a.x; c.w[s][1] = a.y; c.w[s][2] = b.x; c.w[s][3] = b.y;
+        }
+    };
+    // one of the eight instructions that spread an octet (transpose_quads)
+    struct Spread { uint32_t q[EW][4]; };
+    auto spread = [&](const Raw &c, Spread &v, auto ic) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value;
+#pragma unroll
+        for (int s = 0; s < EW; ++s) {
+            uint32_t(&q)[4] = v.q[s];
+            if constexpr (i < 4) {
+                q[i] = __builtin_amdgcn_perm(c.w[s][2 + (i >> 1)], c.w[s][i >> 1], i & 1 ? 0x07060302u : 0x05040100u);
+            } else if constexpr (i < 6) {
+                const auto a = __builtin_amdgcn_permlane16_swap(q[2 * i - 8], q[2 * i - 7], false, false);
+                q[2 * i - 8] = a[0]; q[2 * i - 7] = a[1];
+            } else {
+                const auto a = __builtin_amdgcn_permlane32_swap(q[i - 6], q[i - 4], false, false);
+                q[i - 6] = a[0]; q[i - 4] = a[1];
+            }
+        }
+    };
+    // after the swaps: dword 0, 1, 2, 3 holds features (0, 4), (1, 5), (2, 6), (3, 7)
+    float acc[TW][EW];
+#pragma unroll
+    for (int w = 0; w < TW; ++w)
+#pragma unroll
+        for (int s = 0; s < EW; ++s) acc[w][s] = 0.0f;
+    struct Tok { u32x4 v[TW][XV]; };
+    auto x_read = [&](Tok &t, int q) __attribute__((always_inline)) {
+#pragma unroll
+        for (int w = 0; w < TW; ++w)
+#pragma unroll
+            for (int h = 0; h < XV; ++h) t.v[w][h] = s_x[(q * NT + w * SUB + sub) * XV + h];
+    };
+    auto feature = [&](const Tok &t, const Spread &v, auto uc) __attribute__((always_inline)) {
+        constexpr int u = decltype(uc)::value;
+#pragma unroll
+        for (int w = 0; w < TW; ++w) {
+            const float xf = BF16 ? __uint_as_float(t.v[w][XV == 2 ? u >> 2 : 0][u & 3]) : act_to_float<false>((uint16_t)(t.v[w][0][u >> 1] >> (16 * (u & 1))));
+#pragma unroll
+            for (int s = 0; s < EW; ++s) acc[w][s] = fmaf(xf, act_to_float<BF16>((uint16_t)(v.q[s][u & 3] >> (16 * (u >> 2)))), acc[w][s]);
+        }
+    };
+    u32x4 xv[XP][NT];
+#pragma unroll
+    for (int i = 0; i < XP; ++i)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) xv[i][b] = x_load(lane + 64 * i, b);
+    __builtin_amdgcn_sched_barrier(0);
+    const int step = 16 * E, turn = 4 * kGateBlk * E * 2, first = p * kGateBlk * E * 2;   // bytes of an octet of rows, between this partial sum's blocks, before the first of them
+    if (full)
+        gate_static_for<0, R>([&](auto o) {
+            load(ring[decltype(o)::value], first + decltype(o)::value * step);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+#pragma unroll
+    for (int i = 0; i < XP; ++i)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) x_store(lane + 64 * i, b, xv[i][b]);
+    for (int q = lane + 64 * XP; q < nq; q += 64)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) x_store(q, b, x_load(q, b));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+    if (full) {
+        Tok tok[4];
+        Spread sp[2];
+        x_read(tok[0], 0);
+        x_read(tok[1], 1);
+        gate_static_for<0, 8>([&](auto i) { spread(ring[0], sp[0], i); });
+        int ahead = R == 16 ? first + min(1, full - 1) * turn : first + R * step;       // the octet R past the one at hand
+        load(ring[0], ahead);
+        // an octet's features one after the other (8 clocks each, what a chain of additions takes), an instruction of the next octet's spread in each gap
+        for (int b = 0; b < full; ++b) {
+            gate_static_for<0, 16>([&](auto oc) {
+                constexpr int o = decltype(oc)::value;
+                auto spr = [&](auto i) __attribute__((always_inline)) { spread(ring[(o + 1) % R], sp[(o + 1) & 1], i); };
+                gate_static_for<0, 8>([&](auto u) {
+                    constexpr int i = decltype(u)::value;
+                    feature(tok[o & 3], sp[o & 1], u);
+                    if constexpr (i == 0) {
+                        spr(std::integral_constant<int, 0>{});
+                        spr(std::integral_constant<int, 1>{});
+                    } else if constexpr (i == 1) {
+                        spr(std::integral_constant<int, 2>{});
+                        x_read(tok[(o + 2) & 3], b * 16 + o + 2);
+                    } else if constexpr (i == 5) {      // the octet o + 1 + R: in this block or the next (the last block again where there is none)
+                        constexpr int n = o + 1 + R;
+                        if constexpr (n % 16 == 0) ahead = first + min(b + n / 16, full - 1) * turn;
+                        else ahead += step;
+                        load(ring[(o + 1) % R], ahead);
+                    } else {
+                        spr(std::integral_constant<int, i == 2 ? 3 : i < 5 ? i + 1 : i>{});
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            });
+        }
+    }
+    for (int o = 0; o < rest; ++o) {
+        Raw c;
+        Spread v;
+        Tok t;
+        load(c, ((p + 4 * full) * kGateBlk + o * 8) * E * 2);
+        x_read(t, full * 16 + o);
+        gate_static_for<0, 8>([&](auto i) { spread(c, v, i); });
+        gate_static_for<0, 8>([&](auto u) { feature(t, v, u); });
+    }
+#pragma unroll
+    for (int w = 0; w < TW; ++w)
+#pragma unroll
+        for (int s = 0; s < EW; ++s) part[(p * NTP + w * SUB + sub) * ld + 64 * s + 4 * j + r] = acc[w][s];
+    __syncthreads();
+    finish_tokens<EW, EP / EW / 16>(part, NTP, ld, t0, p, 4, bias, finished, min(T, t0 + NT), E, k, renorm, expert_idx, expert_scale);
+}
+
+template <bool BF16, int EP, int TW>      // up to 64 experts
+__global__ __launch_bounds__(256) void gate_token_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg, const float *__restrict__ bias,
+                                                         const uint8_t *__restrict__ finished, int T, int d, int E, int k, int renorm,
+                                                         int32_t *__restrict__ expert_idx, float *__restrict__ expert_scale)
+{
+    gate_chains<BF16, EP, TW>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+}
+
+template <bool BF16, int TW>              // up to 128
+__global__ __launch_bounds__(256) void gate_lanes_kernel_wide(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg, const float *__restrict__ bias,
+                                                              const uint8_t *__restrict__ finished, int T, int d, int E, int k, int renorm,
+                                                              int32_t *__restrict__ expert_idx, float *__restrict__ expert_scale)
+{
+    gate_chains<BF16, 128, TW>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+}
+
 template <bool BF16, int NB, int S, int TT, int R, GateLoads LOADS>
 static void launch_gate_mfma(const uint16_t *x, const uint16_t *wg, const float *bias, const uint8_t *finished, int T, int d, int E,
                                  int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
@@ -641,33 +804,67 @@ static void launch_gate_mfma(const uint16_t *x, const uint16_t *wg, const float 
                        finished, T, d, E, k, renorm, expert_idx, expert_scale);
 }
 
+// False where a block's tokens have too many features for the LDS (fewer tokens per lane are tried first).
+template <bool BF16, int EP, int TW>
+static bool launch_gate_chains(const uint16_t *x, const uint16_t *wg, const float *bias, const uint8_t *finished, int T, int d, int E,
+                              int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
+{
+    constexpr int NT = TW * (EP < 64 ? 64 / EP : 1), NTP = NT < 4 ? 4 : NT;
+    const size_t smem = (size_t)4 * NTP * (EP + 4) * sizeof(float) + (size_t)4 * ((d + 511) / 512 * 16 + 2) * NT * (BF16 ? 32 : 16);
+    if (smem > 152 * 1024) {
+        if constexpr (TW > 1) return launch_gate_chains<BF16, EP, TW / 2>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale, s);
+        return false;
+    }
+    auto launch = [&](auto kernel) {
+        static std::atomic<uint64_t> raised;
+        raise_lds_limit(reinterpret_cast<const void *>(kernel), 152 * 1024, raised);
+        hipLaunchKernelGGL(kernel, dim3((T + NT - 1) / NT), dim3(256), smem, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+    };
+    if constexpr (EP > 64) launch(&gate_lanes_kernel_wide<BF16, TW>);
+    else launch(&gate_token_kernel<BF16, EP, TW>);
+    return true;
+}
+
 template <bool BF16>
 static void launch_gate(const uint16_t *x, const uint16_t *wg, const float *bias, const uint8_t *finished, int T, int d, int E,
                         int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
 {
     const GateLoads pairs = E % 2 ? ODD_PAIRS : PAIRS;
-    // 17 to 64 experts, a multiple of eight, while the blocks of one or two tokens find a compute unit each: a lane per expert with the gate
-    // weight in LDS, against the forms below.  (Caches warm, d = 1024, FP16: 32 experts, 1 / 64 / 512 tokens 5.9 / 6.4 / 6.5 -> 4.7 / 5.0 / 5.3 us,
-    // 700 6.6 / 6.2, 1500 6.7 / 7.3; 64 experts, 1 / 64 / 256 tokens 6.9 / 8.2 / 8.5 -> 6.0 / 6.5 / 6.7, 700 9.3 / 12.5; 64 tokens, 64
-    // experts, d = 4096 21.0 -> 16.2, bf16 24.8 -> 18.5.  Up to 16 experts it gains nothing below d = 1024 and loses beyond.)
-    if (E > 16 && E <= 64 && E % 8 == 0 && T <= (E <= 32 ? 512 : 256)) {
-        if (E <= 32) hipLaunchKernelGGL((gate_token_kernel<BF16, 32>), dim3((T + 1) / 2), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
-        else hipLaunchKernelGGL((gate_token_kernel<BF16, 64>), dim3(T), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+    // 24 or 32 experts, up to 1024 features, while the blocks of two tokens find a compute unit each: a lane per expert with the gate
+    // weight in LDS, against the matrix cores.  (Caches warm, d = 1024, FP16: 32 experts, 1 / 64 / 512 tokens 5.9 / 6.4 / 6.5 -> 4.7 / 5.0 / 5.3 us,
+    // 700 6.6 / 6.2, 1500 6.7 / 7.3.  Against the chains from memory below: d = 512 3.6 / 3.8, 1024 4.8 / 4.8, 2048 7.1 / 6.6, 4096 11.6 / 10.1.)
+    if (E > 16 && E <= 32 && E % 8 == 0 && T <= 512 && d <= 1024) {
+        hipLaunchKernelGGL((gate_token_kernel_lds<BF16>), dim3((T + 1) / 2), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
         return;
     }
-    // 33 to 64 experts else (no multiple of eight, or more tokens) and up to four tokens per compute unit: four-token blocks on the matrix
+    // Else a multiple of four experts up to 128, while the blocks' tokens are few: chains from memory, more tokens per lane rather than more than a block
+    // per compute unit (64 experts, d = 4096, 512 tokens, one / two per lane 17.9 / 12.4 us).  (us, caches warm, before -> after, d = 512 / 1024 / 2048 / 4096: FP16, 16 experts on
+    // the matrix cores, 1 to 1024 tokens 4.1 / 5.3 / 7.3 / 11.3 -> 3.7 / 4.6 / 6.3 / 10.1; 64 experts, 64 tokens, weights in LDS 4.5 / 6.2 / 9.3 / 15.8 -> 4.0 / 4.9 / 6.6 / 10.2, 1024 tokens, four-token
+    // blocks 6.5 / 9.0 / 14.5 / 24.7 -> 5.0 / 6.7 / 9.9 / 17.5; 128 experts, 64 tokens, gate_lanes_kernel 5.9 / 8.4 / 13.2 / 22.1 -> 5.8 / 7.4 / 10.9 / 17.9, 1024 tokens 8.5 / 13.1 / 22.9 / 41.4 ->
+    // 7.4 / 10.5 / 17.2 / 30.3; bf16 64 tokens, 64 experts 4.8 / 6.9 / 10.6 / 18.0 -> 4.2 / 5.5 / 7.6 / 12.2.  Not: bf16 on up to 16 experts 5.2 / 5.4 at d = 1024 and 11.2 / 13.3 at 4096, and
+    // 513 to 1024 bf16 tokens on up to 32 6.0 / 6.2 and 15.5 / 16.1, whose conversions the matrix cores share out over sixteen tokens; 2048 tokens on 64 experts, d = 4096, 25 / 28.)
+    if (E % 4 == 0 && E <= 128 && T <= 1024) {
+#define MOE_GATE_CHAINS(EP, TW) launch_gate_chains<BF16, EP, TW>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale, s)
+        bool done = false;
+        if (E > 64) done = T <= 256 ? MOE_GATE_CHAINS(128, 1) : T <= 512 ? MOE_GATE_CHAINS(128, 2) : MOE_GATE_CHAINS(128, 4);
+        else if (E > 32) done = T <= 256 ? MOE_GATE_CHAINS(64, 1) : T <= 512 ? MOE_GATE_CHAINS(64, 2) : MOE_GATE_CHAINS(64, 4);
+        else if (E > 16 && T <= 512) done = MOE_GATE_CHAINS(32, 1);
+        else if constexpr (!BF16) done = E > 16 ? MOE_GATE_CHAINS(32, 2) : MOE_GATE_CHAINS(16, 1);
+#undef MOE_GATE_CHAINS
+        if (done) return;
+    }
+    // 33 to 64 experts, no multiple of four, and up to four tokens per compute unit: four-token blocks on the matrix
     // cores; FP16 tokens, more than one such block and up to a token per compute unit: a lane per expert.  (Lane per expert / four-token /
-    // sixteen-token blocks, warm, 36 to 60 experts, d = 1024: T = 1 7.4 / 7.1 / 9.5 us, 64 8.4 / 9.2 / 9.9, 300 11.9 / 9.2 / 10.2, 1000 20.5 / 9.3 / 10.1,
+    // sixteen-token blocks, warm, 36 to 60 experts, d = 1024: T = 64 8.4 / 9.2 / 9.9 us, 300 11.9 / 9.2 / 10.2, 1000 20.5 / 9.3 / 10.1,
     // 2000 37 / 15.9 / 10.1; d = 4096, T = 64 21.0 / 24.9 / 25.3; bf16 27.6 / 24.9 / 25.3.  Odd numbers of experts: one token 7.4 / 8.3 / 11.3,
     // 2000 37 / 15.8 / 12.2.)
-    if (E > 32 && E <= 64 && T <= 1024) {
+    if (E > 32 && E <= 64 && E % 4 && T <= 1024) {
         if (!BF16 && T > 4 && T <= 256)
             hipLaunchKernelGGL((gate_lanes_kernel<BF16, 1, WIDE, 1, 2>), dim3(T), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
-        else if (E % 4) hipLaunchKernelGGL((gate_quad_kernel<BF16, 8, false>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
-        else hipLaunchKernelGGL((gate_quad_kernel<BF16, 8, true>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        else hipLaunchKernelGGL((gate_quad_kernel<BF16, 8>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
         return;
     }
-    // More than 64 experts: a block per token up to one per compute unit, then two, then four, as far as that is faster than the
+    // More than 64 experts else: a block per token up to one per compute unit, then two, then four, as far as that is faster than the
     // matrix cores (d = 1024, T = 1024, FP16, lanes / matrix cores: 127 experts 15.4 / 21.9 us, 128 13.9 / 14.9, 256 22.7 / 24.9; bf16 128
     // experts 17.0 / 15.0; d = 4096 128 experts 48 / 42; T = 1500: 128 19.5 / 15.1, 255 33.2 / 51, 250 30 / 41, 256 32.5 / 25).
     const int few = E > 128 ? (E % 8 ? 2048 : 1024) : E % 2 ? (d <= 1024 ? 2048 : 1024) : !BF16 && d <= 2048 ? 1024 : 512;

@@ -1,0 +1,37 @@
+"""The gate's chains from memory, a lane per expert or two: features short of, at and past whole blocks of 128 and of the four partial sums (some with
+none), experts that leave lanes empty, every number of tokens per lane at its edges, and rows too long for the LDS."""
+import numpy as np
+import pytest
+import torch
+
+import launches as L
+import oracle
+from helpers import TORCH_DT, to_dev
+from paper_2211_10017_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,d,E", [(1, 8, 4), (5, 128, 8), (1024, 136, 12), (7, 1160, 16), (3, 4224, 16),
+                                   (1, 120, 20), (9, 520, 28), (512, 1152, 32), (513, 640, 24), (1023, 72, 32),
+                                   (1, 72, 36), (256, 512, 64), (257, 904, 52), (512, 1032, 60), (513, 4104, 64), (1024, 264, 44),
+                                   (1, 64, 68), (255, 1536, 128), (259, 776, 100), (515, 392, 124),
+                                   (4, 4352, 64), (514, 10248, 64), (6, 20488, 8)])
+@pytest.mark.parametrize("act", ["f16", "bf16"])
+def test_gate_chains_bit_exact(T, d, E, act):
+    print(f"gate chains T={T} d={d} E={E} {act}", flush=True)
+    (call,) = L.record([L.gate(T, d, E, B._DT[TORCH_DT[act]])])
+    name = call.launches[0].kernel
+    if d < 20000 and (act == "f16" or E > 16 and (E > 32 or T <= 512)):
+        assert name.startswith("gate_lanes_kernel_wide<" if E > 64 else "gate_token_kernel<"), name
+    rng = np.random.default_rng(T + d + E)
+    x = to_dev(rng.standard_normal((T, d)).astype(np.float32), TORCH_DT[act])
+    wg = to_dev((rng.standard_normal((d, E)) * 0.05).astype(np.float32), TORCH_DT[act])
+    bias = (rng.standard_normal(E) * 0.05).astype(np.float32)
+    fin = (rng.random(T) < 0.2).astype(np.uint8)
+    for k, renorm in ((1, True), (2, True), (2, False)):
+        oi, osc = oracle.gate(x.float().cpu().numpy(), wg.float().cpu().numpy(), bias, k, renorm, finished=fin)
+        gi, gs = B.moe_gate_topk(x, wg, to_dev(bias, torch.float32), k, renorm, finished=to_dev(fin, torch.uint8))
+        torch.cuda.synchronize()
+        assert np.array_equal(gi.cpu().numpy(), oi)
+        assert np.allclose(gs.cpu().numpy(), osc, rtol=1e-5, atol=1e-9)         # (expf)
