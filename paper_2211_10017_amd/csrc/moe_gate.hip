@@ -7,7 +7,7 @@
 // per instruction) and gate_quad_kernel (4 tokens x 64 experts); few tokens take the vector ALU with a lane per expert or several
 // experts per lane (gate_token_kernel, gate_lanes_kernel and their other forms).  T = 8192, d = 4096, 64 experts: 196 -> 48 us (bf16 208 ->
 // 47), T = 4096, d = 2048, 128 experts: 76 -> 28.6 us, T = 16384, d = 1024, 64 experts: 55 -> 32 us against multiply-adds in
-// the vector ALU with a lane per expert or per token; T = 64, d = 1024, 32 experts: 13 -> 9 us with cold caches.
+// the vector ALU with a lane per expert or per token.
 #include <math.h>
 
 #include <type_traits>
@@ -525,92 +525,160 @@ __global__ __launch_bounds__(256) void gate_lanes_kernel(const uint16_t *__restr
     finish_tokens<NE == 2 ? 2 : 1, 4, NE <= 2 ? 16 : 64>(part, NT, ld, t0, p, 4, bias, finished, min(T, t0 + TB), E, k, renorm, expert_idx, expert_scale);
 }
 
-// Few tokens by 24 or 32 experts and up to 1024 features: a lane per expert, 32 lanes per token, two tokens per block, plain fp32
-// multiply-adds.  The block takes 512 features at a time (128 of each partial sum): the gate weight's part of them goes through
-// LDS, eight features of an expert side by side, so that an octet of a chain is one 16-byte read of weights and one of the token.
-// What bounds so small a launch is its latencies in a row: the code (about 100 clocks per 64 bytes that a compute unit has not run
-// before, hence one rolled loop), the loads (all of a chunk's at once, 16 bytes each, the next chunk's under this one's chains) and the chains
-// themselves, 8 clocks per feature of a partial sum.
-template <bool BF16>
-__global__ __launch_bounds__(256) void gate_token_kernel_lds(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
-                                                         const float *__restrict__ bias,
-                                                         const uint8_t *__restrict__ finished, int T, int d, int E,
-                                                         int k, int renorm, int32_t *__restrict__ expert_idx,
-                                                         float *__restrict__ expert_scale)
+// Few tokens, E a multiple of four up to 32: a lane per expert, SUB tokens side by side, TW of them per lane, plain fp32 multiply-adds, the gate weight through
+// LDS as it lies in memory: each wavefront copies its own partial sum's rows 64 features at a time (two chunks in LDS, two more on the way), and the transposing
+// read gives a lane four features of its expert.  What bounds it are instructions, of which a wavefront alone on its SIMD issues one in 4.4 clocks: an octet of features
+// takes eight multiply-adds, a wait state after each whose sum the next one adds to, two reads of weights, one of the token.  (115 clocks an octet.  With FP16 tokens as
+// fp32 in LDS, which spares wait states, the reads bound: d = 4096, 16 experts 8.6 -> 10.6 us.  Transposing in registers as below: 10.1.  For 64 experts writes and reads
+// of LDS meet the other three wavefronts': 10.9 against 10.1.)  A wavefront waits for nobody before the end.
+template <bool BF16, int EP, int TW>
+__device__ __forceinline__ void gate_rows(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg, const float *__restrict__ bias,
+                                          const uint8_t *__restrict__ finished, int T, int d, int E, int k, int renorm,
+                                          int32_t *__restrict__ expert_idx, float *__restrict__ expert_scale)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int EP = 32, NT = 64 / EP, OCT = 64;      // tokens of the block, octets of a chunk
-    constexpr int ld = EP + 4;
-    __shared__ u32x4 s_w[OCT * EP], s_x[NT * OCT];
-    float *part = reinterpret_cast<float *>(s_w);       // at the end: [4][4][ld]
-    static_assert(16 * ld * 4 <= OCT * EP * 16, "the partial sums fit where the weights were");
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int p = __builtin_amdgcn_readfirstlane(tid >> 6);
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    constexpr int SUB = 64 / EP, NT = TW * SUB;
+    constexpr int ld = EP + 4, NTP = NT < 4 ? 4 : NT;   // (four tokens finish at a time, those past NT are not stored)
+    constexpr int XV = BF16 ? 2 : 1;                    // 16-byte words of an octet of a token
+    constexpr int XP = 2;                               // passes of 64 octets of the tokens that are requested ahead of the weights
+    constexpr int CW = EP * 8, LD = EP / 8;             // 16-byte words of a chunk (64 features), loads of it per lane
+    static_assert(LD <= 6, "a chunk is written before its first octet is read");
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63;
+    const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    u32x4 *s_w = reinterpret_cast<u32x4 *>(smem) + (size_t)p * 2 * CW;                   // two chunks of this wavefront's
+    float *part = reinterpret_cast<float *>(smem + 8 * CW * 16);                         // [4][NTP][ld]
+    const int e = lane % EP, sub = lane / EP;           // this lane's expert and token
     const int t0 = blockIdx.x * NT, rows = min(NT, T - t0);
-    const int groups = E >> 3;
-    const int oc = tid / groups, eg = tid - oc * groups, w_off = (oc * 8 * E + eg * 8) * 2;      // this thread's 8 x 8 block of a chunk
-    const int x_off = (min(tid >> 6, rows - 1) * d + (tid & 63) * 8) * 2;
-    u32x4 W[8], X;
-    // (extents end with the buffers: what lies past the last feature reads as zero or as the next token's, and is not used)
-    auto load = [&](int c) {
-        const int left = max(d - c * 512, 0);
-        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg + (size_t)c * 512 * E), 0, left * E * 2, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d + c * 512), 0, left ? (rows * d - c * 512) * 2 : 0, 0x00020000);
+    const int nblk = (d + kGateBlk - 1) / kGateBlk;
+    const int full = max((d / kGateBlk - p + 3) / 4, 0);                                // whole 128-feature blocks of this partial sum
+    const int rest = (nblk - 1) % 4 == p ? (d % kGateBlk) / 8 : 0, nq = full * 16 + rest;      // octets of the last, short one, and in all
+    u32x4 *s_x = reinterpret_cast<u32x4 *>(smem + 8 * CW * 16 + 4 * NTP * ld * 4) + (size_t)p * ((nblk + 3) / 4 * 16 + 2) * NT * XV;    // [octet][token]; two octets are read past the end
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
+    int w_off[LD];                                      // (within the chunk: fewer experts than EP read its end again)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) W[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, w_off + i * E * 2, 0, 0);
-        if (tid < NT * OCT) X = __builtin_amdgcn_raw_buffer_load_b128(rx, x_off, 0, 0);
+    for (int i = 0; i < LD; ++i) w_off[i] = min(lane * 16 + i * 1024, 128 * E - 16);
+
+    const int row = E * 2;                              // bytes
+    auto x_load = [&](int q, int b) __attribute__((always_inline)) {
+        return __builtin_amdgcn_raw_buffer_load_b128(rx, (min(b, rows - 1) * d + min((p + 4 * (q >> 4)) * kGateBlk + (q & 15) * 8, d - 8)) * 2, 0, 0);
     };
-    load(0);
-    const int e = lane % EP, sub = lane / EP, ec = min(e, E - 1);
-    // (an expert's slot within its eight: turned by the number of the eight, so that neighbouring threads' writes spread over the banks)
-    const u32x4 *w_ptr = s_w + p * 16 * E + (ec & ~7) + ((ec & 7) ^ ((ec >> 3) & 7)), *x_ptr = s_x + sub * OCT + p * 16;
-    float acc = 0.0f;
-    for (int c = 0; c * 512 < d; ++c) {
-        if (oc < OCT) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                u32x4 v;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = __builtin_amdgcn_perm(W[2 * q + 1][j >> 1], W[2 * q][j >> 1], j & 1 ? 0x07060302u : 0x05040100u);
-                s_w[oc * E + eg * 8 + (j ^ (eg & 7))] = v;
-            }
+    auto x_store = [&](int q, int b, u32x4 v) __attribute__((always_inline)) {
+        if (q >= nq) return;
+        if constexpr (BF16) {
+            s_x[(q * NT + b) * 2] = u32x4{v.x << 16, v.x & 0xffff0000u, v.y << 16, v.y & 0xffff0000u};
+            s_x[(q * NT + b) * 2 + 1] = u32x4{v.z << 16, v.z & 0xffff0000u, v.w << 16, v.w & 0xffff0000u};
+        } else {
+            s_x[q * NT + b] = v;
         }
-        if (tid < NT * OCT) s_x[tid] = X;
-        __syncthreads();
-        load(c + 1);
-        const int n = min(max((d - (4 * c + p) * kGateBlk) >> 3, 0), 16);      // octets of this partial sum's block
-        auto octet = [&](u32x4 xv, u32x4 wv) {
+    };
+    float acc[TW];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                acc = fmaf(act_to_float<BF16>((uint16_t)xv[q]), act_to_float<BF16>((uint16_t)wv[q]), acc);
-                acc = fmaf(act_to_float<BF16>((uint16_t)(xv[q] >> 16)), act_to_float<BF16>((uint16_t)(wv[q] >> 16)), acc);
-            }
-        };
-        int o = 0;
-        for (; o + 4 <= n; o += 4) {
-            u32x4 xv[4], wv[4];
+    for (int w = 0; w < TW; ++w) acc[w] = 0.0f;
+    struct Octet { u32x4 x[TW][XV]; s16x4 w[2]; };
+    // sixteen lanes point at four rows of sixteen experts, four experts each; back comes an expert's four rows
+    const int w_read = (((lane & 15) >> 2) * E + (e & 16) + 4 * (lane & 3)) * 2;
+    auto x_read = [&](Octet &t, int q) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) xv[i] = x_ptr[o + i], wv[i] = w_ptr[(o + i) * E];
+        for (int w = 0; w < TW; ++w)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) octet(xv[i], wv[i]);
+            for (int h = 0; h < XV; ++h) t.x[w][h] = s_x[(q * NT + w * SUB + sub) * XV + h];
+    };
+    auto w_get = [&](Octet &t, int buf, int o) __attribute__((always_inline)) {
+        typedef __attribute__((address_space(3))) s16x4 *lds_t;
+        unsigned char *at = reinterpret_cast<unsigned char *>(s_w + buf * CW) + w_read + o * 8 * row;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) t.w[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)(at + h * 4 * row));
+    };
+    auto feature = [&](const Octet &t, auto uc) __attribute__((always_inline)) {
+        constexpr int u = decltype(uc)::value;
+#pragma unroll
+        for (int w = 0; w < TW; ++w) {
+            const float xf = BF16 ? __uint_as_float(t.x[w][XV == 2 ? u >> 2 : 0][u & 3]) : act_to_float<false>((uint16_t)(t.x[w][0][u >> 1] >> (16 * (u & 1))));
+            acc[w] = fmaf(xf, act_to_float<BF16>((uint16_t)t.w[u >> 2][u & 3]), acc[w]);
         }
-        for (; o < n; ++o) octet(x_ptr[o], w_ptr[o * E]);
-        __syncthreads();
+    };
+    u32x4 xv[XP][NT];
+#pragma unroll
+    for (int i = 0; i < XP; ++i)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) xv[i][b] = x_load(lane + 64 * i, b);
+    __builtin_amdgcn_sched_barrier(0);
+    auto base = [&](int c) { c = min(c, 2 * full - 1); return ((p + 4 * (c >> 1)) * kGateBlk + (c & 1) * 64) * row; };      // (past the end: the last one again, not used)
+    u32x4 W[2][LD];
+    auto load = [&](int i, int so) __attribute__((always_inline)) { return __builtin_amdgcn_raw_buffer_load_b128(rw, w_off[i], so, 0); };
+    if (full)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < LD; ++i) W[h][i] = load(i, base(h));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < XP; ++i)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) x_store(lane + 64 * i, b, xv[i][b]);
+    for (int q = lane + 64 * XP; q < nq; q += 64)
+#pragma unroll
+        for (int b = 0; b < NT; ++b) x_store(q, b, x_load(q, b));
+    auto fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    if (full) {
+#pragma unroll
+        for (int i = 0; i < LD; ++i) s_w[i * 64 + lane] = W[0][i];
+        const int so = base(2);
+#pragma unroll
+        for (int i = 0; i < LD; ++i) W[0][i] = load(i, so);
+        fence();
+        Octet t[4];
+        x_read(t[0], 0); w_get(t[0], 0, 0);
+        x_read(t[1], 1); w_get(t[1], 0, 1);
+        for (int b = 0; b < full; ++b) {
+            gate_static_for<0, 16>([&](auto oc) {
+                // octet oo of chunk h of the block; with its first ones go the writes of the next chunk and the loads of the one two further on
+                constexpr int o = decltype(oc)::value, h = o >> 3, oo = o & 7;
+                const int so = base(2 * b + h + 3);
+                gate_static_for<0, 8>([&](auto u) {
+                    constexpr int i = decltype(u)::value;
+                    feature(t[o & 3], u);
+                    if constexpr (i == 0) x_read(t[(o + 2) & 3], b * 16 + o + 2);
+                    if constexpr (i == 1) w_get(t[(o + 2) & 3], ((o + 2) >> 3) & 1, (o + 2) & 7);      // (from the sixth octet on in the next chunk: all of it is there)
+                    if constexpr (i == 2 && oo < LD) {
+                        s_w[(1 - h) * CW + oo * 64 + lane] = W[1 - h][oo];
+                        W[1 - h][oo] = load(oo, so);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                if constexpr (oo == 5) fence();
+            });
+        }
     }
-    part[(p * 4 + sub) * ld + e] = acc;
+    for (int o = 0; o < rest; ++o) {
+        fence();
+        const int at = ((p + 4 * full) * kGateBlk + o * 8) * row;
+        s_w[lane] = __builtin_amdgcn_raw_buffer_load_b128(rw, min(lane * 16, 16 * E - 16), at, 0);
+        fence();
+        Octet t;
+        x_read(t, full * 16 + o);
+        w_get(t, 0, 0);
+        gate_static_for<0, 8>([&](auto u) { feature(t, u); });
+    }
+#pragma unroll
+    for (int w = 0; w < TW; ++w) part[(p * NTP + w * SUB + sub) * ld + e] = acc[w];
     __syncthreads();
-    finish_tokens<1, EP / 16>(part, 4, ld, t0, p, 4, bias, finished, min(T, t0 + NT), E, k, renorm, expert_idx, expert_scale);
+    finish_tokens<1, EP / 16>(part, NTP, ld, t0, p, 4, bias, finished, min(T, t0 + NT), E, k, renorm, expert_idx, expert_scale);
 }
 
-// Few tokens, E a multiple of four up to 128: a lane per expert (two with more than 64), plain fp32 multiply-adds, the gate weight
+// Few tokens and 36 to 128 experts, a multiple of four: the same with a lane per expert (two with more than 64) and the gate weight
 // from memory straight into registers.  A lane (j, r) brings experts 4 j .. 4 j + 3 of features r and 4 + r in two 8-byte loads, and the 4 x 4
-// transposition that spreads the tokens' features above leaves it with expert 4 j + r of an octet of features; with fewer than 64 experts the sixteen
-// j of a row repeat them for SUB tokens.  TW tokens per lane, so a block takes SUB TW.  Each wavefront keeps its own partial sum's features of
-// the tokens in LDS (bf16 as fp32, which saves a conversion per lane and feature), so it waits for nobody before the end.
-// What bounds it is the chain, 8 clocks per feature and one wavefront per SIMD: the transposition of the next octet, its loads and the reads of the tokens are
-// dealt out one by one into the gaps between the additions (in the other order, spread / additions / loads, 3 % slower), and an octet still takes 130 clocks for
-// the 64 of its chain, the swaps issuing at half rate.  R octets in flight: with 4, warm launches are 0.2 us shorter and layers' steps, whose gate weight comes from memory, 0.3 % longer; with
-// 16, 1.8 % longer.  (Against the gate weight through LDS with two barriers per 512 features, 64 experts, d = 4096: 1.6 us of those each, of which the additions are 0.4.)
+// transposition that spreads the tokens' features above leaves it with expert 4 j + r of an octet of features.  Its eight instructions for the next octet
+// are dealt out one by one between the multiply-adds, where each stands in for a wait state, and so are the loads and the reads of the tokens (in the order
+// spread, additions, loads 3 % slower).  130 clocks an octet, the swaps issuing at half rate.  R octets in flight: with 4, warm launches are 0.2 us shorter and
+// layers' steps, whose gate weight comes from memory, 0.3 % longer; with 16, 1.8 % longer.
 template <bool BF16, int EP, int TW, int R = 8>
 __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg, const float *__restrict__ bias,
                                             const uint8_t *__restrict__ finished, int T, int d, int E, int k, int renorm,
@@ -619,7 +687,7 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     typedef float f4_t __attribute__((ext_vector_type(4)));
-    constexpr int EW = EP > 64 ? 2 : 1, JL = EP / EW / 4, SUB = 16 / JL, NT = TW * SUB;
+    constexpr int EW = EP / 64, NT = TW;
     constexpr int ld = EP + 4, NTP = NT < 4 ? 4 : NT;   // (four tokens finish at a time, those past NT are not stored)
     constexpr int XV = BF16 ? 2 : 1;                    // 16-byte words of an octet of a token
     constexpr int XP = 2;                               // passes of 64 octets of the tokens that are requested ahead of the weights
@@ -627,7 +695,7 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
     float *part = reinterpret_cast<float *>(smem);      // [4][NTP][ld]
     const int lane = threadIdx.x & 63;
     const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j = lane & (JL - 1), sub = (lane & 15) / JL, r = lane >> 4;
+    const int j = lane & 15, r = lane >> 4;
     const int t0 = blockIdx.x * NT, rows = min(NT, T - t0);
     const int nblk = (d + kGateBlk - 1) / kGateBlk;
     const int full = max((d / kGateBlk - p + 3) / 4, 0);                                // whole 128-feature blocks of this partial sum
@@ -691,7 +759,7 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
 #pragma unroll
         for (int w = 0; w < TW; ++w)
 #pragma unroll
-            for (int h = 0; h < XV; ++h) t.v[w][h] = s_x[(q * NT + w * SUB + sub) * XV + h];
+            for (int h = 0; h < XV; ++h) t.v[w][h] = s_x[(q * NT + w) * XV + h];
     };
     auto feature = [&](const Tok &t, const Spread &v, auto uc) __attribute__((always_inline)) {
         constexpr int u = decltype(uc)::value;
@@ -733,7 +801,6 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
         gate_static_for<0, 8>([&](auto i) { spread(ring[0], sp[0], i); });
         int ahead = R == 16 ? first + min(1, full - 1) * turn : first + R * step;       // the octet R past the one at hand
         load(ring[0], ahead);
-        // an octet's features one after the other (8 clocks each, what a chain of additions takes), an instruction of the next octet's spread in each gap
         for (int b = 0; b < full; ++b) {
             gate_static_for<0, 16>([&](auto oc) {
                 constexpr int o = decltype(oc)::value;
@@ -772,9 +839,9 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
 #pragma unroll
     for (int w = 0; w < TW; ++w)
 #pragma unroll
-        for (int s = 0; s < EW; ++s) part[(p * NTP + w * SUB + sub) * ld + 64 * s + 4 * j + r] = acc[w][s];
+        for (int s = 0; s < EW; ++s) part[(p * NTP + w) * ld + 64 * s + 4 * j + r] = acc[w][s];
     __syncthreads();
-    finish_tokens<EW, EP / EW / 16>(part, NTP, ld, t0, p, 4, bias, finished, min(T, t0 + NT), E, k, renorm, expert_idx, expert_scale);
+    finish_tokens<EW, 4>(part, NTP, ld, t0, p, 4, bias, finished, min(T, t0 + NT), E, k, renorm, expert_idx, expert_scale);
 }
 
 template <bool BF16, int EP, int TW>      // up to 64 experts
@@ -782,7 +849,8 @@ __global__ __launch_bounds__(256) void gate_token_kernel(const uint16_t *__restr
                                                          const uint8_t *__restrict__ finished, int T, int d, int E, int k, int renorm,
                                                          int32_t *__restrict__ expert_idx, float *__restrict__ expert_scale)
 {
-    gate_chains<BF16, EP, TW>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+    if constexpr (EP <= 32) gate_rows<BF16, EP, TW>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+    else gate_chains<BF16, EP, TW>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
 }
 
 template <bool BF16, int TW>              // up to 128
@@ -810,7 +878,7 @@ static bool launch_gate_chains(const uint16_t *x, const uint16_t *wg, const floa
                               int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
 {
     constexpr int NT = TW * (EP < 64 ? 64 / EP : 1), NTP = NT < 4 ? 4 : NT;
-    const size_t smem = (size_t)4 * NTP * (EP + 4) * sizeof(float) + (size_t)4 * ((d + 511) / 512 * 16 + 2) * NT * (BF16 ? 32 : 16);
+    const size_t smem = (EP <= 32 ? EP * 1024 : 0) + (size_t)4 * NTP * (EP + 4) * sizeof(float) + (size_t)4 * ((d + 511) / 512 * 16 + 2) * NT * (BF16 ? 32 : 16);
     if (smem > 152 * 1024) {
         if constexpr (TW > 1) return launch_gate_chains<BF16, EP, TW / 2>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale, s);
         return false;
@@ -830,26 +898,21 @@ static void launch_gate(const uint16_t *x, const uint16_t *wg, const float *bias
                         int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
 {
     const GateLoads pairs = E % 2 ? ODD_PAIRS : PAIRS;
-    // 24 or 32 experts, up to 1024 features, while the blocks of two tokens find a compute unit each: a lane per expert with the gate
-    // weight in LDS, against the matrix cores.  (Caches warm, d = 1024, FP16: 32 experts, 1 / 64 / 512 tokens 5.9 / 6.4 / 6.5 -> 4.7 / 5.0 / 5.3 us,
-    // 700 6.6 / 6.2, 1500 6.7 / 7.3.  Against the chains from memory below: d = 512 3.6 / 3.8, 1024 4.8 / 4.8, 2048 7.1 / 6.6, 4096 11.6 / 10.1.)
-    if (E > 16 && E <= 32 && E % 8 == 0 && T <= 512 && d <= 1024) {
-        hipLaunchKernelGGL((gate_token_kernel_lds<BF16>), dim3((T + 1) / 2), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
-        return;
-    }
-    // Else a multiple of four experts up to 128, while the blocks' tokens are few: chains from memory, more tokens per lane rather than more than a block
-    // per compute unit (64 experts, d = 4096, 512 tokens, one / two per lane 17.9 / 12.4 us).  (us, caches warm, before -> after, d = 512 / 1024 / 2048 / 4096: FP16, 16 experts on
-    // the matrix cores, 1 to 1024 tokens 4.1 / 5.3 / 7.3 / 11.3 -> 3.7 / 4.6 / 6.3 / 10.1; 64 experts, 64 tokens, weights in LDS 4.5 / 6.2 / 9.3 / 15.8 -> 4.0 / 4.9 / 6.6 / 10.2, 1024 tokens, four-token
+    // A multiple of four experts up to 128 and few tokens: chains, more tokens per lane rather than more than a block
+    // per compute unit (64 experts, d = 4096, 512 tokens, one / two per lane 17.9 / 12.4 us).  (us, caches warm, d = 512 / 1024 / 2048 / 4096, before -> after.  FP16: up to 16
+    // experts on the matrix cores, 1 to 1024 tokens 4.1 / 5.3 / 7.3 / 11.3 -> 3.5 / 4.3 / 5.7 / 8.8; 32 experts, 64 tokens, the weight transposed into LDS for the whole block 3.9 / 5.1 / 7.3 / 11.8 ->
+    // 3.9 / 4.7 / 6.2 / 9.4, 1024 tokens, matrix cores 4.5 / 6.0 / 9.1 / 15.7 -> 4.5 / 5.4 / 7.4 / 11.5; 64 experts, 64 tokens 4.5 / 6.2 / 9.3 / 15.8 -> 4.0 / 4.9 / 6.6 / 10.2, 1024 tokens, four-token
     // blocks 6.5 / 9.0 / 14.5 / 24.7 -> 5.0 / 6.7 / 9.9 / 17.5; 128 experts, 64 tokens, gate_lanes_kernel 5.9 / 8.4 / 13.2 / 22.1 -> 5.8 / 7.4 / 10.9 / 17.9, 1024 tokens 8.5 / 13.1 / 22.9 / 41.4 ->
-    // 7.4 / 10.5 / 17.2 / 30.3; bf16 64 tokens, 64 experts 4.8 / 6.9 / 10.6 / 18.0 -> 4.2 / 5.5 / 7.6 / 12.2.  Not: bf16 on up to 16 experts 5.2 / 5.4 at d = 1024 and 11.2 / 13.3 at 4096, and
-    // 513 to 1024 bf16 tokens on up to 32 6.0 / 6.2 and 15.5 / 16.1, whose conversions the matrix cores share out over sixteen tokens; 2048 tokens on 64 experts, d = 4096, 25 / 28.)
+    // 7.4 / 10.5 / 17.2 / 30.3.  bf16, 64 tokens: 16 experts 4.5 / 5.6 / 7.6 / 11.6 -> 4.0 / 5.0 / 7.0 / 11.1, 32 4.2 / 5.6 / 8.4 / 14.4 -> 4.2 / 5.2 / 7.0 / 11.0, 64 4.8 / 6.9 / 10.6 / 18.0 -> 4.2 /
+    // 5.5 / 7.6 / 12.2.  Not: 513 to 1024 bf16 tokens on 17 to 32 experts, 6.0 / 6.3 at d = 1024; 2048 tokens on 64 experts, d = 4096, 25 / 28.)
     if (E % 4 == 0 && E <= 128 && T <= 1024) {
 #define MOE_GATE_CHAINS(EP, TW) launch_gate_chains<BF16, EP, TW>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale, s)
         bool done = false;
         if (E > 64) done = T <= 256 ? MOE_GATE_CHAINS(128, 1) : T <= 512 ? MOE_GATE_CHAINS(128, 2) : MOE_GATE_CHAINS(128, 4);
         else if (E > 32) done = T <= 256 ? MOE_GATE_CHAINS(64, 1) : T <= 512 ? MOE_GATE_CHAINS(64, 2) : MOE_GATE_CHAINS(64, 4);
-        else if (E > 16 && T <= 512) done = MOE_GATE_CHAINS(32, 1);
-        else if constexpr (!BF16) done = E > 16 ? MOE_GATE_CHAINS(32, 2) : MOE_GATE_CHAINS(16, 1);
+        else if (E <= 16) done = MOE_GATE_CHAINS(16, 1);
+        else if (T <= 512) done = MOE_GATE_CHAINS(32, 1);
+        else if constexpr (!BF16) done = MOE_GATE_CHAINS(32, 2);
 #undef MOE_GATE_CHAINS
         if (done) return;
     }
