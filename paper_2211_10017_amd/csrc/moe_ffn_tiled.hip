@@ -113,12 +113,12 @@ bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits)
     return us <= 3.0 + 4.0 * ((double)R * F + (double)tokens * d) / 5e6;
 }
 
-// Blocks that hold rows when launch_tiled_gemm takes this GEMM, under uniform routing.
+// Blocks that hold rows when launch_tiled_gemm takes this GEMM, under uniform routing; infinitely many where its tiles do not sort.
 double row_tile_blocks(const GemmArgs &p, int bits, int smode)
 {
     const int mean = (p.R + p.E - 1) / p.E, ring = ring_rows_for(p, bits, mean), tm = tile_height_for(p, bits, mean);
     if (ring) return expected_row_tiles(p.R, p.E, ring) * ((p.N + 127) / 128);
-    return expected_row_tiles(p.R, p.E, 32 * (smode == SCALE_GROUP_ACC && tm > 2 ? 2 : tm)) * ((p.N + 255) / 256);
+    return smode == SCALE_GROUP_ACC && tm > 1 ? INFINITY : expected_row_tiles(p.R, p.E, 32 * tm) * ((p.N + 255) / 256);
 }
 
 int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
@@ -137,7 +137,7 @@ int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
         return check_launch("moe_grouped_ffn_wq (gemm)");
     }
     int tm = tile_height_for(p, bits, mean);
-    if (smode == SCALE_GROUP_ACC && tm > 2) tm = 2;
+    if (smode == SCALE_GROUP_ACC && tm > 1) tm = p.gate_idx ? 1 : 2;         // (64-row tiles of group sums do not sort)
     const long most = p.R;                                      // experts that can hold rows
     const long ncol = (p.N + 255) / 256;
     // Tiles may be lower than the kernel's 32 * tm rows (it skips row tiles that hold no rows): with few

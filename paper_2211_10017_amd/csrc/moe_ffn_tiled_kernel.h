@@ -39,6 +39,8 @@ __global__ __launch_bounds__(256, TM == 1 && !(SMODE == SCALE_GROUP_ACC || SMODE
     // (scratch of the index: behind the first stage, which is filled while other wavefronts still read their rows' assignments)
     static_assert(sizeof(lds_raw) >= kStageBytes / 2 + sizeof(IndexScratch), "the index's scratch fits");
     IndexScratch &index = *reinterpret_cast<IndexScratch *>(lds_raw + kStageBytes / 2);
+    // 64-row tiles of group sums, the largest layers' loop, never sort (with the code for it 8192 tokens, two of 64 experts of 4096 x 16384, 4533 us a step, without 4506)
+    if constexpr (SMODE == SCALE_GROUP_ACC && TM == 2) p.gate_idx = nullptr;
     if (!(p.gate_idx ? find_unsorted_item(p, 32 * p.tile_units, (N + 255) / 256, index, &e, &col, &row0, &rows)
                      : find_item(p.offsets, p.E, p.R, 32 * p.tile_units, (N + 255) / 256, blockIdx.x, &e, &col, &row0, &rows))) return;
     e = __builtin_amdgcn_readfirstlane(e), col = __builtin_amdgcn_readfirstlane(col);      // the same in every lane: kept in scalar registers

@@ -272,7 +272,13 @@ def test_the_unsorted_call_launches_what_the_indexed_call_does():
         if not (g == 128 and d == 64)]
     here, there = L.record([L.unsorted(*f) for f in forms]), L.record([L.indexed(f[0] * f[1], f[2], f[1], *f[3:8], f[0], f[8]) for f in forms])
     for f, a, b in zip(forms, here, there):
-        assert a.rc == b.rc == 0 and a.launches == b.launches and a.noted == b.noted, f
+        assert a.rc == b.rc == 0 and a.noted == b.noted, f
+        tall, low = ("grouped_gemm_kernel<%d, 3, %d>" % (f[5], tm) for tm in (2, 1))
+        if tall in [p.kernel for p in b.launches]:      # (fc1 in 64-row tiles of group sums, which do not sort: 32-row ones)
+            assert [p.kernel for p in a.launches] == [p.kernel.replace(tall, low) for p in b.launches]
+            assert not B.load().moe_grouped_ffn_wq_unsorted_pays(*f[:8]), f
+        else:
+            assert a.launches == b.launches, f
     refused = [L.unsorted(2049, 2, 8, 64, 64, 4), L.unsorted(4097, 1, 8, 64, 64, 4), L.unsorted(8, 1, 1025, 64, 64, 4), L.unsorted(0, 1, 8, 64, 64, 4), L.unsorted(8, 3, 8, 64, 64, 4),
                L.unsorted(8, 2, 8, 64, 64, 4, scale=True), L.unsorted(8, 1, 8, 96, 64, 4), L.unsorted(8, 1, 8, 64, 64, 5), L.unsorted(8, 1, 8, 64, 64, 4, 128),
                L.unsorted(8, 1, 8, 64, 64, 4, idx=None), L.unsorted(8, 1, 8, 64, 64, 4, act=B.MOE_F32)]
