@@ -212,6 +212,13 @@ static bool tiled_only(int R, int E, int max_rows, int d, int F, int bits, bool 
            choose_kernel(R, E, max_rows, F, d, bits, smode, bf) == GEMM_TILED;
 }
 
+// How fc1's weights meet group scales.  bf16 rows, groups of 128: exact codes, group sums folded in fp32; other group sizes: the two-term form, in the LDS ring exact
+// codes as well.
+static int fc1_group_mode(bool bf, int group_size)
+{
+    return !bf ? moe::SCALE_GROUP : group_size == 128 ? moe::SCALE_GROUP_ACC : moe::SCALE_GROUP_SPLIT;
+}
+
 static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_offsets, int R,
                     int E, int max_rows_per_expert, int d, int F, int bits, int group_size, int activation,
                     const void *w1_packed,
@@ -294,8 +301,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
         if (rc) return rc;
         g1.a = x16;
     }
-    // (groups of 128: exact codes, group sums folded in fp32; other group sizes: the two-term form, in the LDS ring exact codes as well)
-    const int channel = bf && !convert ? SCALE_CHANNEL_BF16 : SCALE_CHANNEL, smode1 = !grouped ? channel : !bf ? SCALE_GROUP : group_size == 128 ? SCALE_GROUP_ACC : SCALE_GROUP_SPLIT;
+    const int channel = bf && !convert ? SCALE_CHANNEL_BF16 : SCALE_CHANNEL, smode1 = grouped ? fc1_group_mode(bf, group_size) : channel;
     int rc = run_gemm(g1, bits, smode1, bf, tiles_only && !stream_fc1, max_rows, s);
     if (rc) return rc;
 
@@ -500,7 +506,7 @@ extern "C" int moe_grouped_ffn_wq_unsorted_pays(int T, int k, int E, int d, int 
     GemmArgs g{};
     g.R = T * k, g.E = E, g.K = d, g.N = F, g.indexed = 1;
     const bool grouped = group_size != 0 && !(group_size == d && group_size == F);
-    return row_tile_blocks(g, bits, grouped && act_dtype == MOE_BF16 && group_size == 128 ? SCALE_GROUP_ACC : SCALE_CHANNEL) <= 256 * (g.R <= 512 ? 8 : 3.5);
+    return row_tile_blocks(g, bits, grouped ? fc1_group_mode(act_dtype == MOE_BF16, group_size) : SCALE_CHANNEL) <= 256 * (g.R <= 512 ? 8 : 3.5);
 }
 
 extern "C" int moe_grouped_ffn_wq_unsorted(const void *x, int act_dtype, const int32_t *expert_idx, const float *expert_scale, int T, int k, int E,

@@ -50,10 +50,12 @@ double expected_row_tiles(long R, long E, int bm)
 //    of 8 of 2048 x 512, fc1 in tiles as well, 31.9 -> 28.7; at 1.4 blocks, 74 rows on each of 32 of 2048 x 512, 38 -> 40), unless ring_long takes those of 64.
 //  - up to eight rows per expert of 4-bit weights in 32-row blocks, from 3.9 of these per compute unit on: tiles, which unpack as much for twice the columns
 //    (fc2 of 420 tokens, two of 128 experts of 4096 x 1024, 152 -> 138).
-static int ring_rows_for(const GemmArgs &p, int bits, int mean)
+// Not for the two-term weights of register-fed tiles (bf16 rows, groups other than 128): 256 times code times scale overflows FP16 from weights of 256 on, where
+// the ring keeps exact codes and folds the scales in fp32, at half the matrix instructions.
+static int ring_rows_for(const GemmArgs &p, int bits, int smode, int mean)
 {
     const int ring = ring_rows(p, bits, mean);
-    if (!ring || p.E < 8 || !p.indexed) return ring;
+    if (!ring || p.E < 8 || !p.indexed || smode == SCALE_GROUP_SPLIT) return ring;
     const double tiles = expected_row_tiles(p.R, p.E, 32), fed = tiles * ((p.N + 255) / 256) / 256, blocks = tiles * ((p.N + 127) / 128) / 256;
     if (p.K <= 1024) return (bits == 4 ? fed >= 0.9 : mean > 10 && mean <= 64 && fed >= 0.8 && fed <= 1.8) ? 0 : ring;
     if (ring == 64 && blocks <= 1.0 && !(bits == 8 && (long)p.E * p.K * p.N >= kLongRingWeights)) return 32;
@@ -116,7 +118,7 @@ bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits)
 // Blocks that hold rows when launch_tiled_gemm takes this GEMM, under uniform routing; infinitely many where its tiles do not sort.
 double row_tile_blocks(const GemmArgs &p, int bits, int smode)
 {
-    const int mean = (p.R + p.E - 1) / p.E, ring = ring_rows_for(p, bits, mean), tm = tile_height_for(p, bits, mean);
+    const int mean = (p.R + p.E - 1) / p.E, ring = ring_rows_for(p, bits, smode, mean), tm = tile_height_for(p, bits, mean);
     if (ring) return expected_row_tiles(p.R, p.E, ring) * ((p.N + 127) / 128);
     return smode == SCALE_GROUP_ACC && tm > 1 ? INFINITY : expected_row_tiles(p.R, p.E, 32 * tm) * ((p.N + 255) / 256);
 }
@@ -125,7 +127,7 @@ int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s)
 {
     // row-tile height from the mean rows per expert (the offsets themselves stay on the device)
     const int mean = (p.R + p.E - 1) / p.E;
-    const int bm = ring_rows_for(p, bits, mean);
+    const int bm = ring_rows_for(p, bits, smode, mean);
     note_kernel(bm ? "grouped_gemm_ring_kernel" : "grouped_gemm_kernel");
     if (bm) {
         const long slots = (long)p.R / bm + (p.E < p.R ? p.E : p.R);

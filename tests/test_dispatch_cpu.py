@@ -316,3 +316,16 @@ def test_layers_of_eight_experts_and_more_leave_the_ring_by_their_expected_tiles
     cases += TAKEN
     for (sizes, want), call in zip(cases, L.record([L.indexed(*c) for c, _ in cases])):
         assert call.rc == 0 and _rows_of_tiles(call) == want, (sizes, call.launches)
+
+
+def test_two_term_weights_do_not_take_the_rings_place():
+    """bf16 rows with groups other than 128: in register-fed tiles fc1's weights are two-term FP16 numbers, which end at weights of 256; what the ring takes of
+    permuted copies it takes of rows through the index, in the same blocks."""
+    from test_gpu_indexed import LARGE_WEIGHTS
+    sizes = LARGE_WEIGHTS + [(892, 64, 2, 768, 3072, 4, 64), (470, 16, 1, 1024, 4096, 4, 256), (705, 32, 1, 768, 3072, 8, 64), (783, 16, 1, 512, 2048, 4, 64),
+                             (840, 128, 2, 2048, 1024, 4, 64), (382, 8, 1, 3072, 768, 4, 64)]
+    here = L.record([L.indexed(*s, B.MOE_BF16) for s in sizes])
+    copies = L.record([L.ffn(s[0], s[1], *s[3:], B.MOE_BF16) for s in sizes])
+    for s, a, b in zip(sizes, here, copies):
+        fc1, permuted = ([p for p in c.launches if p.kernel.startswith("grouped")][0] for c in (a, b))
+        assert a.rc == b.rc == 0 and fc1 == permuted and fc1.kernel.startswith("grouped_gemm_ring"), (s, fc1, permuted)

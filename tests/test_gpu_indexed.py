@@ -89,6 +89,31 @@ def test_tiles_of_indexed_rows_match_oracle(sizes, tiles, load):
     assert max_abs <= MAX_ABS_TOL * max(1.0, float(np.abs(want).max()) / 8) and rel <= REL_L2_TOL
 
 
+# (assignments, experts, k, d, F, bits, g): bf16 rows whose two-term weights in register-fed tiles, 256 times code times scale, would be no FP16 numbers;
+# fc1 in the ring instead (test_dispatch_cpu.py)
+LARGE_WEIGHTS = [(800, 8, 1, 256, 2048, 4, 64), (800, 8, 1, 256, 2048, 4, 256), (892, 64, 2, 128, 3072, 4, 64), (705, 32, 1, 256, 3072, 8, 64), (705, 32, 1, 256, 3072, 8, 256)]
+
+
+@pytest.mark.parametrize("sizes", LARGE_WEIGHTS)
+def test_group_scaled_weights_up_to_a_thousand_match_oracle(sizes):
+    R, E, k, d, F, bits, g = sizes
+    print(f"large weights {sizes}", flush=True)
+    rng, T = np.random.default_rng(R + g), R // k
+    w = [(rng.standard_normal((E, *s)) * 0.05).astype(np.float32) for s in ((d, F), (F, d))]
+    v = w[0].reshape(E, d // g, g, F)
+    v *= 1000.0 / np.abs(v).max(axis=2, keepdims=True) * 2.0 ** -rng.integers(0, 12, (E, d // g, 1, F))       # a group's largest: 1000 down to 0.5
+    (s1, p1), (s2, p2) = (B.moe_quantize_experts(to_dev(m, torch.float32), bits, g, want_canon=False)[1:] for m in w)
+    x = to_dev(rng.standard_normal((T, d)).astype(np.float32), torch.bfloat16)
+    idx = np.stack([(np.arange(T) * 5 + j * 3) % E for j in range(k)], 1).astype(np.int32)
+    y, src, _, off = B.moe_grouped_ffn_wq_unsorted(x, to_dev(idx, torch.int32), E, d, F, bits, g, p1, s1, p2, s2, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    (q1, o1), (q2, o2) = (oracle.quantize(m, bits, g) for m in w)
+    want = oracle.grouped_ffn(x.float().cpu().numpy()[src.cpu().numpy() // k], off.cpu().numpy(), q1, o1, q2, o2, g, oracle.BF16)
+    max_abs, rel = error_metrics(y.cpu().numpy(), want)
+    print(f"   max_abs={max_abs:.3e} rel_l2={rel:.3e} of {np.abs(want).max():.3e}", flush=True)
+    assert max_abs <= MAX_ABS_TOL * max(1.0, float(np.abs(want).max()) / 8) and rel <= REL_L2_TOL
+
+
 def test_indexed_refuses_what_does_not_fit():
     f = ctypes.c_void_p(0x1000)
     call = B.load().moe_grouped_ffn_wq_indexed
