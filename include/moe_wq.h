@@ -351,7 +351,8 @@ int moe_grouped_gemm_wq(const void *x_perm, const int32_t *expert_offsets, int R
  *   y_perm [R,d] y_dtype; out [T,d] out_dtype (each MOE_F16 | MOE_BF16 | MOE_F32); d % 8 == 0.
  *   active_rows: device pointer to the number of active rows (expert_offsets + E) or NULL.
  *       Terms whose row is at or past it belong to pruned tokens (Sec. 3.5): y_perm holds
- *       nothing for them and they are left out, so a fully pruned token gets a zero row.
+ *       nothing for them (it may end with the active rows) and they are left out unread, so a
+ *       fully pruned token gets a zero row.
  */
 int moe_combine(const void *y_perm, int y_dtype, const int32_t *inv_perm,
                 const float *expert_scale, const int32_t *active_rows, int T, int k, int d,

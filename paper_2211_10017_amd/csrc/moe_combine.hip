@@ -8,20 +8,19 @@ namespace moe {
 constexpr int kCombineVec = 8;           // channels of a thread
 
 template <int DT>
-__device__ inline void load8(const void *base, size_t idx8, float (&v)[8])
+struct Eight { uint4 w[DT == MOE_F32 ? 2 : 1]; };        // eight channels as they lie in memory
+
+template <int DT>
+__device__ inline void to_float(const Eight<DT> &u, float (&v)[8])
 {
-    if (DT == MOE_F32) {
-        const float4 a = reinterpret_cast<const float4 *>(base)[2 * idx8], b = reinterpret_cast<const float4 *>(base)[2 * idx8 + 1];
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    } else {
-        const uint4 u = reinterpret_cast<const uint4 *>(base)[idx8];
-        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint16_t b = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
-            if (DT == MOE_BF16) v[i] = __uint_as_float((uint32_t)b << 16);
-            else { __half h; *reinterpret_cast<uint16_t *>(&h) = b; v[i] = __half2float(h); }
-        }
+    for (int i = 0; i < 8; ++i) {
+        const uint4 q = u.w[DT == MOE_F32 ? i >> 2 : 0];
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+        if (DT == MOE_F32) { v[i] = __uint_as_float(w[i & 3]); continue; }
+        const uint16_t b = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
+        if (DT == MOE_BF16) v[i] = __uint_as_float((uint32_t)b << 16);
+        else { __half h; *reinterpret_cast<uint16_t *>(&h) = b; v[i] = __half2float(h); }
     }
 }
 
@@ -56,35 +55,51 @@ __device__ inline void store8(void *base, size_t idx8, const float (&v)[8])
 }
 
 // A thread combines eight channels of a token.  K: experts per token, 0 = any number, one after the other.  What bounds small batches is memory
-// latencies in a row, so the rows of both experts are requested at once, whether they are active or not (the memory is there, its values are then not
-// used): two latencies, index and rows, instead of four (a step of 405 tokens, two of 64 experts of 512 x 2048, 41.1 -> 40.4 us); large ones,
-// bytes in flight: sixteen-byte loads of both rows (8192 tokens of 4096, FP16 y: 58.7 -> 45.6 us, 5.9 TB/s).
-template <int YDT, int ODT, int K, class Index>
+// latencies in a row, so the rows of both experts are requested at once, whether they are active or not: two latencies, index and rows, instead of four (a step of 405
+// tokens, two of 64 experts of 512 x 2048, 41.1 -> 40.4 us); large ones, bytes in flight: sixteen-byte loads of both rows (8192 tokens of 4096, FP16 y: 58.7 -> 45.6 us,
+// 5.9 TB/s).  Rows of pruned tokens (Sec. 3.5), at or past *active_rows, need not be there: buffer loads whose extent ends with the active rows leave them unread
+// (branches around the loads 0.4 us more in launches of 3.5).  8192 tokens of 4096, all / two thirds / 40 % of the rows active, FP16 y, call after call: 54.8 / 46.9 /
+// 41 us, loaded whether active or not 54.6 each.  FAR: y_perm is larger than buffer loads reach, branches.
+template <int YDT, int ODT, int K, bool FAR>
 __global__ __launch_bounds__(256) void combine_kernel(const void *__restrict__ y_perm,
                                                       const int32_t *__restrict__ inv_perm,
                                                       const float *__restrict__ scale,
                                                       const int32_t *__restrict__ active_rows, int T, int k,
                                                       int d8, void *__restrict__ out)
 {
+    typedef std::conditional_t<FAR, size_t, uint32_t> Index;         // (indices of 32 bits, a good part of so small a kernel)
+    constexpr int BYTES = sizeof(Eight<YDT>), N = K ? K : 1;
     const Index total = (Index)T * d8;
     for (Index i = (Index)blockIdx.x * 256 + threadIdx.x; i < total; i += (Index)gridDim.x * 256) {
         const int t = (int)(i / d8), c = (int)(i - (Index)t * d8);
         float acc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-        constexpr int N = K ? K : 1;
         for (int j0 = 0; j0 < (K ? 1 : k); ++j0) {
             const size_t a = K ? (size_t)t * K : (size_t)t * k + j0;
             int r[N];
-            float s[N], v[N][8];
+            float s[N];
+            Eight<YDT> y[N] = {};
 #pragma unroll
             for (int j = 0; j < N; ++j) r[j] = inv_perm[a + j], s[j] = scale[a + j];
-            // rows at or past *active_rows belong to pruned tokens (Sec. 3.5): never computed, they add nothing
             const int active = active_rows ? *active_rows : 0x7fffffff;
+            const uint32_t extent = min((uint32_t)max(active, 0), (uint32_t)T * k) * d8 * BYTES;
+            const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(y_perm), 0, extent, 0x00020000);
 #pragma unroll
-            for (int j = 0; j < N; ++j) load8<YDT>(y_perm, (size_t)r[j] * d8 + c, v[j]);
+            for (int j = 0; j < N; ++j) {
+                if constexpr (FAR) {
+                    if (r[j] < active) y[j] = reinterpret_cast<const Eight<YDT> *>(y_perm)[(size_t)r[j] * d8 + c];
+                } else {
+                    const uint32_t at = ((uint32_t)r[j] * d8 + c) * BYTES;        // (of a pruned row it may wrap: some active row's values, not used)
 #pragma unroll
-            for (int j = 0; j < N; ++j)
+                    for (int h = 0; h < BYTES / 16; ++h) y[j].w[h] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ry, at + 16 * h, 0, 0));
+                }
+            }
 #pragma unroll
-                for (int q = 0; q < 8; ++q) acc[q] = r[j] < active ? fmaf(s[j], v[j][q], acc[q]) : acc[q];
+            for (int j = 0; j < N; ++j) {
+                float v[8];
+                to_float<YDT>(y[j], v);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) acc[q] = r[j] < active ? fmaf(s[j], v[q], acc[q]) : acc[q];
+            }
         }
         store8<ODT>(out, (size_t)i, acc);
     }
@@ -108,10 +123,12 @@ extern "C" int moe_combine(const void *y_perm, int y_dtype, const int32_t *inv_p
     auto launch = [&](auto y, auto o) {
         constexpr int Y = decltype(y)::value, O = decltype(o)::value;
         const dim3 grid((unsigned)(blocks > 0x400000 ? 0x400000 : blocks));
-        const bool narrow = total < 0x40000000u;        // (indices of 32 bits, a good part of so small a kernel)
-        if (k == 1 && narrow) hipLaunchKernelGGL((combine_kernel<Y, O, 1, uint32_t>), grid, dim3(256), 0, s, y_perm, inv_perm, expert_scale, active_rows, T, k, d8, out);
-        else if (k == 2 && narrow) hipLaunchKernelGGL((combine_kernel<Y, O, 2, uint32_t>), grid, dim3(256), 0, s, y_perm, inv_perm, expert_scale, active_rows, T, k, d8, out);
-        else hipLaunchKernelGGL((combine_kernel<Y, O, 0, size_t>), grid, dim3(256), 0, s, y_perm, inv_perm, expert_scale, active_rows, T, k, d8, out);
+        const bool far = (uint64_t)total * k * sizeof(Eight<Y>) > 0xffffffffu;
+        auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, y_perm, inv_perm, expert_scale, active_rows, T, k, d8, out); };
+        if (!far && k == 1) run(&combine_kernel<Y, O, 1, false>);
+        else if (!far && k == 2) run(&combine_kernel<Y, O, 2, false>);
+        else if (k == 2) run(&combine_kernel<Y, O, 2, true>);
+        else run(&combine_kernel<Y, O, 0, true>);
         return check_launch("moe_combine");
     };
     auto with_out = [&](auto y) {

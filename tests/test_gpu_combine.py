@@ -35,3 +35,53 @@ def test_combine_matches_fp32_sums_in_slot_order(T, k, d, y_dt, out_dt, prune):
     want = torch.from_numpy(want).to(out_dt)
     ulp = {F32: 2.0 ** -23, F16: 2.0 ** -10, BF16: 2.0 ** -7}[out_dt]      # (the double rounding of the reference: at most one unit in the last place)
     assert bool(((got.cpu().float() - want.float()).abs() <= ulp * want.float().abs().clamp_min(2.0 ** -14)).all())
+
+
+@pytest.mark.parametrize("T,k,d", [(1, 1, 8), (33, 1, 64), (257, 2, 72), (5, 3, 128), (129, 2, 1024)])
+@pytest.mark.parametrize("y_dt", [F16, BF16, F32])
+@pytest.mark.parametrize("share", [0.0, 0.6])
+def test_rows_past_the_active_ones_need_not_be_there(T, k, d, y_dt, share):
+    """y that holds the active rows only, and indices anywhere at or past them for the others."""
+    print(f"combine, active rows only T={T} k={k} d={d} {y_dt} {share}", flush=True)
+    rng = np.random.default_rng(T + k + d)
+    R, active = T * k, int(share * T * k)
+    y = to_dev(rng.standard_normal((max(active, 1), d)).astype(np.float32), y_dt)
+    if not active:
+        y.fill_(float("nan"))
+    inv = rng.permutation(R).astype(np.int32)
+    inv = np.where(inv < active, inv, rng.choice(np.array([active, R, 2 ** 20, 2 ** 31 - 1]), R)).astype(np.int32)
+    scale = to_dev(rng.random((T, k)).astype(np.float32), F32)
+    rows = to_dev(np.array([active], np.int32), torch.int32)
+    got = B.moe_combine(y, to_dev(inv, torch.int32), scale, T, k, active_rows=rows)
+    # the same rows where y has them all, and zeros where they are pruned
+    full = torch.zeros((R, d), dtype=y_dt, device="cuda")
+    full[:active] = y[:active]
+    scale[to_dev(inv >= active, torch.bool).view(T, k)] = 0.0
+    want = B.moe_combine(full, to_dev(np.minimum(inv, R - 1), torch.int32), scale, T, k)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) and bool((got[to_dev((inv.reshape(T, k) >= active).all(1), torch.bool)] == 0).all())
+
+
+@pytest.mark.parametrize("k", [1, 2])
+def test_more_than_four_gigabytes_of_rows(k):
+    """Beyond the reach of buffer loads: the bits of the same tokens a few at a time, pruned ones among them."""
+    print(f"combine, 4 GiB and a bit, k={k}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(k)
+    T, d = (1 << 20) // (8 * k) + 100, 8192
+    R, active = T * k, T * k - 1000
+    y = torch.randn((active, d), generator=gen, device="cuda")
+    inv = torch.randperm(R, generator=gen, device="cuda").int()
+    scale = torch.rand((T, k), generator=gen, device="cuda")
+    rows = torch.tensor([active], dtype=torch.int32, device="cuda")
+    assert R * d * 4 > 1 << 32
+    got = B.moe_combine(y, inv, scale, T, k, active_rows=rows)
+    for t in range(0, T, 8192):
+        part = inv.view(T, k)[t:t + 8192]
+        live = part < active
+        few = y[part[live].long()]
+        order = torch.full(part.shape, len(few), dtype=torch.int32, device="cuda")
+        order[live] = torch.arange(len(few), dtype=torch.int32, device="cuda")
+        want = B.moe_combine(few, order.view(-1), scale[t:t + 8192].contiguous(), len(part), k, active_rows=torch.tensor([len(few)], dtype=torch.int32, device="cuda"))
+        torch.cuda.synchronize()
+        assert torch.equal(got[t:t + 8192], want), t
