@@ -348,7 +348,8 @@ int moe_grouped_gemm_wq(const void *x_perm, const int32_t *expert_offsets, int R
 /*
  * Sec. 3.3, last step: rows return to their original order and are multiplied by
  * expert_scale:  out[t] = sum_j expert_scale[t,j] * y_perm[inv_perm[t*k+j]]  (fp32, j ascending).
- *   y_perm [R,d] y_dtype; out [T,d] out_dtype (each MOE_F16 | MOE_BF16 | MOE_F32); d % 8 == 0.
+ *   y_perm [R,d] y_dtype; out [T,d] out_dtype (each MOE_F16 | MOE_BF16 | MOE_F32); d % 8 == 0.  (R may
+ *       be more than T*k: a call for some of a batch's tokens reads the batch's y_perm.)
  *   active_rows: device pointer to the number of active rows (expert_offsets + E) or NULL.
  *       Terms whose row is at or past it belong to pruned tokens (Sec. 3.5): y_perm holds
  *       nothing for them (it may end with the active rows) and they are left out unread, so a

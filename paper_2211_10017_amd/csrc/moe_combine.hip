@@ -7,6 +7,9 @@ namespace moe {
 
 constexpr int kCombineVec = 8;           // channels of a thread
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(1))) u32x4 *global_u32x4;
+
 template <int DT>
 struct Eight { uint4 w[DT == MOE_F32 ? 2 : 1]; };        // eight channels as they lie in memory
 
@@ -54,21 +57,23 @@ __device__ inline void store8(void *base, size_t idx8, const float (&v)[8])
     }
 }
 
+// What a pruned token's row is read from.
+static __device__ const uint4 no_row[2] = {};
+
 // A thread combines eight channels of a token.  K: experts per token, 0 = any number, one after the other.  What bounds small batches is memory
 // latencies in a row, so the rows of both experts are requested at once, whether they are active or not: two latencies, index and rows, instead of four (a step of 405
 // tokens, two of 64 experts of 512 x 2048, 41.1 -> 40.4 us); large ones, bytes in flight: sixteen-byte loads of both rows (8192 tokens of 4096, FP16 y: 58.7 -> 45.6 us,
-// 5.9 TB/s).  Rows of pruned tokens (Sec. 3.5), at or past *active_rows, need not be there: buffer loads whose extent ends with the active rows leave them unread
-// (branches around the loads 0.4 us more in launches of 3.5).  8192 tokens of 4096, all / two thirds / 40 % of the rows active, FP16 y, call after call: 54.8 / 46.9 /
-// 41 us, loaded whether active or not 54.6 each.  FAR: y_perm is larger than buffer loads reach, branches.
-template <int YDT, int ODT, int K, bool FAR>
+// 5.9 TB/s).  Rows of pruned tokens (Sec. 3.5), at or past *active_rows, need not be there: their loads go to one line of zeros
+// (8192 tokens of 4096, all / two thirds / 40 % of the rows active, FP16 y 56.6 / 48.3 / 42.1 us a call, loaded whether active or not 56.3 each; launches of 2 to 4 us
+// as before, where branches around the loads take 0.4 us more).
+template <int YDT, int ODT, int K, class Index>
 __global__ __launch_bounds__(256) void combine_kernel(const void *__restrict__ y_perm,
                                                       const int32_t *__restrict__ inv_perm,
                                                       const float *__restrict__ scale,
                                                       const int32_t *__restrict__ active_rows, int T, int k,
                                                       int d8, void *__restrict__ out)
 {
-    typedef std::conditional_t<FAR, size_t, uint32_t> Index;         // (indices of 32 bits, a good part of so small a kernel)
-    constexpr int BYTES = sizeof(Eight<YDT>), N = K ? K : 1;
+    constexpr int N = K ? K : 1;
     const Index total = (Index)T * d8;
     for (Index i = (Index)blockIdx.x * 256 + threadIdx.x; i < total; i += (Index)gridDim.x * 256) {
         const int t = (int)(i / d8), c = (int)(i - (Index)t * d8);
@@ -77,21 +82,15 @@ __global__ __launch_bounds__(256) void combine_kernel(const void *__restrict__ y
             const size_t a = K ? (size_t)t * K : (size_t)t * k + j0;
             int r[N];
             float s[N];
-            Eight<YDT> y[N] = {};
+            Eight<YDT> y[N];
 #pragma unroll
             for (int j = 0; j < N; ++j) r[j] = inv_perm[a + j], s[j] = scale[a + j];
             const int active = active_rows ? *active_rows : 0x7fffffff;
-            const uint32_t extent = min((uint32_t)max(active, 0), (uint32_t)T * k) * d8 * BYTES;
-            const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(y_perm), 0, extent, 0x00020000);
 #pragma unroll
             for (int j = 0; j < N; ++j) {
-                if constexpr (FAR) {
-                    if (r[j] < active) y[j] = reinterpret_cast<const Eight<YDT> *>(y_perm)[(size_t)r[j] * d8 + c];
-                } else {
-                    const uint32_t at = ((uint32_t)r[j] * d8 + c) * BYTES;        // (of a pruned row it may wrap: some active row's values, not used)
+                const uintptr_t at = r[j] < active ? (uintptr_t)y_perm + ((size_t)r[j] * d8 + c) * sizeof(Eight<YDT>) : (uintptr_t)no_row;
 #pragma unroll
-                    for (int h = 0; h < BYTES / 16; ++h) y[j].w[h] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ry, at + 16 * h, 0, 0));
-                }
+                for (int h = 0; h < (int)sizeof(Eight<YDT>) / 16; ++h) y[j].w[h] = __builtin_bit_cast(uint4, reinterpret_cast<global_u32x4>(at)[h]);
             }
 #pragma unroll
             for (int j = 0; j < N; ++j) {
@@ -123,12 +122,11 @@ extern "C" int moe_combine(const void *y_perm, int y_dtype, const int32_t *inv_p
     auto launch = [&](auto y, auto o) {
         constexpr int Y = decltype(y)::value, O = decltype(o)::value;
         const dim3 grid((unsigned)(blocks > 0x400000 ? 0x400000 : blocks));
-        const bool far = (uint64_t)total * k * sizeof(Eight<Y>) > 0xffffffffu;
+        const bool narrow = total < 0x40000000u;        // (indices of 32 bits, a good part of so small a kernel)
         auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, y_perm, inv_perm, expert_scale, active_rows, T, k, d8, out); };
-        if (!far && k == 1) run(&combine_kernel<Y, O, 1, false>);
-        else if (!far && k == 2) run(&combine_kernel<Y, O, 2, false>);
-        else if (k == 2) run(&combine_kernel<Y, O, 2, true>);
-        else run(&combine_kernel<Y, O, 0, true>);
+        if (narrow && k == 1) run(&combine_kernel<Y, O, 1, uint32_t>);
+        else if (narrow && k == 2) run(&combine_kernel<Y, O, 2, uint32_t>);
+        else run(&combine_kernel<Y, O, 0, size_t>);
         return check_launch("moe_combine");
     };
     auto with_out = [&](auto y) {

@@ -85,3 +85,23 @@ def test_more_than_four_gigabytes_of_rows(k):
         want = B.moe_combine(few, order.view(-1), scale[t:t + 8192].contiguous(), len(part), k, active_rows=torch.tensor([len(few)], dtype=torch.int32, device="cuda"))
         torch.cuda.synchronize()
         assert torch.equal(got[t:t + 8192], want), t
+
+
+@pytest.mark.parametrize("T,k,d", [(33, 1, 64), (257, 2, 72), (6, 3, 128)])
+@pytest.mark.parametrize("y_dt", [F16, F32])
+@pytest.mark.parametrize("prune", [False, True])
+def test_a_few_tokens_of_a_batch_reach_all_of_its_rows(T, k, d, y_dt, prune):
+    """A call for some of the tokens, whose rows lie anywhere in the batch's y: the bits of the call for all of them."""
+    print(f"combine, part of the tokens T={T} k={k} d={d} {y_dt} pruned={prune}", flush=True)
+    rng = np.random.default_rng(T + k + d)
+    R = T * k
+    y = to_dev(rng.standard_normal((R, d)).astype(np.float32), y_dt)
+    inv = to_dev(rng.permutation(R).astype(np.int32), torch.int32)
+    scale = to_dev(rng.random((T, k)).astype(np.float32), F32)
+    rows = to_dev(np.array([R * 2 // 3], np.int32), torch.int32) if prune else None
+    want = B.moe_combine(y, inv, scale, T, k, active_rows=rows)
+    for t in range(0, T, 5):
+        n = min(5, T - t)
+        got = B.moe_combine(y, inv[t * k:(t + n) * k].contiguous(), scale[t:t + n].contiguous(), n, k, active_rows=rows)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want[t:t + n]) and (prune or bool((got != 0).any(1).all()))
