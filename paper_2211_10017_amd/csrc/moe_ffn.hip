@@ -283,7 +283,7 @@ static int ffn_impl(const void *x_perm, int act_dtype, const int32_t *expert_off
     GemmArgs g1{};
     const bool tiles_only = perm_src || unsorted;
     const int tokens = tiles_only ? R / k : R;                  // rows of x
-    const bool convert = bf && (grouped || !bf16_codes_pay(R, tokens, E, d, F, bits));
+    const bool convert = bf && (grouped || !bf16_codes_pay(R, tokens, E, d, F, bits, tiles_only));
     g1.a = (const uint16_t *)x_perm; g1.row_pow = convert ? pow_x : nullptr; g1.offsets = expert_offsets;
     g1.wq = (const uint8_t *)w1_packed; g1.scales = (const __half *)s1; g1.bias = (const __half *)b1;
     g1.out = h; g1.E = E; g1.R = R; g1.K = d; g1.N = F; g1.g = grouped ? group_size : d;

@@ -81,7 +81,7 @@ constexpr int kUnsortedMaxAssign = 4096, kUnsortedMaxExperts = 1024;    // of ro
 int launch_tiled_gemm(const GemmArgs &p, int bits, int smode, hipStream_t s);
 double row_tile_blocks(const GemmArgs &p, int bits, int smode);
 double expected_row_tiles(long R, long E, int bm);
-bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits);
+bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits, bool indexed);
 void launch_tiled_4(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);
 void launch_tiled_4_exact(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);
 void launch_tiled_8(const GemmArgs &p, int smode, int tm, dim3 grid, hipStream_t s);

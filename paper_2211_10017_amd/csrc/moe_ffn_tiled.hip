@@ -98,16 +98,18 @@ static int tile_height_for(const GemmArgs &p, int bits, int mean)
 // (9719 drawn layers, 100 to 16000 tokens: 0.11 % slower on average than the better way for each, at most 9 %; one figure for every kernel 0.23 % and 17 %; always converting
 // 6.7 %, never 0.7 % and 17 %.  us a step, converted / as they are: 1906 tokens, one of 16 experts of 768 x 3072 57.1 / 50.5; 609, two of 8, 8-bit, 61.4 / 57.3; 10420, two of 64,
 // 8-bit, 347 / 309; left to the conversion: 713, one of 8 of 4096 x 16384 267 / 312; 490, one of 16 of 2048 x 8192 97.7 / 111.2; 3862, one of 8 of 4096 x 16384, 8-bit, 1129 / 1211, 7 133 / 149.)
-bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits)
+// indexed: as GemmArgs has it; the tiles are those that launch_tiled_gemm takes (with those of permuted copies for rows through the index, 831, one of 64 of 1024 x 4096 91.2,
+// now 88.5; 1411, one of 128 of 1024 x 2048 103.9 / 98.3; 327, one of 8 of 2048 x 8192, converted now, 77.4 / 74.5; nineteen such layers, none slower).
+bool bf16_codes_pay(int R, int tokens, int E, int d, int F, int bits, bool indexed)
 {
     static const double ring_us[2][3] = {{16, 16, 24}, {0, 4, 0}}, tile_us[2][3] = {{7, 16, 27}, {0, 8, 21}};     // [8-bit][16, 32, 64 rows], [32, 64, 128 rows]
     GemmArgs p{};
-    p.E = E, p.R = R;
+    p.E = E, p.R = R, p.indexed = indexed;
     const int mean = (R + E - 1) / E;
     double us = 0;
     for (int fc = 0; fc < 2; ++fc) {
         p.K = fc ? F : d, p.N = fc ? d : F;
-        const int ring = ring_rows(p, bits, mean), bm = ring ? ring : 32 * tile_height(p, bits, mean);
+        const int ring = ring_rows_for(p, bits, SCALE_CHANNEL_BF16, mean), bm = ring ? ring : 32 * tile_height_for(p, bits, mean);
         const double tiles = expected_row_tiles(R, E, bm);
         us += tiles * p.K * p.N * 1e-9 * (ring ? ring_us[bits == 8][bm / 32] : tile_us[bits == 8][bm / 64]);
         if (bits == 8 && ring == 16 && tiles * ((p.N + 127) / 128) <= 256) us += p.K * 4e-4;      // nothing beside the lone block's chain

@@ -329,3 +329,12 @@ def test_two_term_weights_do_not_take_the_rings_place():
     for s, a, b in zip(sizes, here, copies):
         fc1, permuted = ([p for p in c.launches if p.kernel.startswith("grouped")][0] for c in (a, b))
         assert a.rc == b.rc == 0 and fc1 == permuted and fc1.kernel.startswith("grouped_gemm_ring"), (s, fc1, permuted)
+
+
+def test_bf16_rows_are_converted_by_what_the_launched_tiles_cost():
+    """Rows through the index on both sides of the line, at sizes whose tiles are not those of permuted copies: (sizes, whether converted)."""
+    cases = [((831, 64, 1, 1024, 4096, 4), False), ((610, 128, 2, 512, 2048, 4), False), ((1411, 128, 1, 1024, 2048, 4), False), ((592, 64, 2, 768, 3072, 4), False),
+             ((327, 8, 1, 2048, 8192, 4), True), ((713, 8, 1, 4096, 16384, 4), True), ((609 * 2, 8, 2, 768, 3072, 8), False)]
+    calls = L.record([L.indexed(*c, 0, B.MOE_BF16) for c, _ in cases])
+    for (sizes, converted), call in zip(cases, calls):
+        assert call.rc == 0 and any(p.kernel.startswith("rows_to_f16") for p in call.launches) == converted, (sizes, call.launches)
