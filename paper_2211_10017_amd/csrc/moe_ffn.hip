@@ -549,31 +549,41 @@ extern "C" size_t moe_grouped_ffn_wq_sliced_workspace_bytes(int T, int k, int E,
     return round_up(decode_ffn_partial_bytes(T * k, d, F, decode_slice_width(T * k, E, F)), 256);
 }
 
-// Few experts or small ones, beyond what moe_grouped_ffn_wq_sliced_pays lists: the launches of the other routes are most of their step there, and nearly every
-// expert's rows are one item (sixteen rows, thirty-two with 4-bit weights and more than eight rows per expert), so no weights are read twice:
-// `over`, the items that a touched expert is expected to make, may be 1.6, with more than 100 MB of weights 1.1, anything up to 17 MB.  (us a step, the best
-// other route / sliced: 40 rows on 8 experts of 512 x 2048, bf16 28.9 / 14.4, 141 on 16 of 768 x 3072, groups of 128, 31.6 / 24.4, 149 on 8 of 1024 x 4096 32.0 / 27.3, 186 on 8 of
-// 2048 x 8192, bf16 65.3 / 55.6; left out 226 on 8 of 2048 x 8192, over = 1.2, 70 / 85, 476 on 8 of 768 x 3072, 2.2, 35 / 47.)
-//  - FP16 rows on 8-bit codes with channel scales, which stream well elsewhere: over up to 1.25 and 100 MB, or at most a row per expert and 430 MB (12 on 32 of 2048 x
-//    8192 65 / 54; 7 on 32 of 4096 x 16384, 750 MB, 134 / 160).
-//  - all others up to 500 MB, with experts of up to 17 MB 600 (229 rows on 128 of 768 x 3072, 8-bit bf16, 97 / 77; 230 on 32 of 2048 x 8192, groups of 128, bf16 154 / 134);
-//    FP16 rows on 4-bit codes with channel scales up to 1200 MB while there are at most 1.6 rows per expert (22 on 16 of 4096 x 16384, 814 MB, 180 / 155; bf16
-//    11 on 64, 683 MB, 171 / 202).
+// Few experts or small ones, beyond what moe_grouped_ffn_wq_sliced_pays lists: the launches of the other routes, and in wide layers (d_ff of three times d and more) the
+// long chain of fc2, are most of their step there, while nothing much is read twice: `over`, the items that a touched expert is expected to make (sixteen rows,
+// thirty-two with 4-bit weights and more than eight rows per expert), may be 1.6, with more than 100 MB of weights 1.1, anything up to 17 MB; FP16 rows on 8-bit codes
+// with channel scales, which stream well elsewhere, 1.25 and 1.1, and from 100 MB on only up to a row per expert and 430 MB.  Further, us a step, the best other route /
+// sliced:
+//  - few rows, as every row costs its partial sums: 200, of wide layers that move 10 to 100 MB 256; bf16 rows with group scales, which the other routes convert, 56 more
+//    (141 on 16 experts of 768 x 3072, groups of 128, 31.6 / 24.4; 311, groups of 64, bf16, on 32 of 448 x 1792 32.1 / 23.6; left out 476 on 8 of 768 x 3072 35 / 47, 512 on one of 2048 x
+//    2048 36.7 / 78.9, of 2048 x 8192 71 / 350);
+//  - what moves, the items' weights and the partial sums out and back: wide layers 150 MB (149 on 8 of 1024 x 4096 32.0 / 27.3; left out 226 on 8 of 2048 x 8192 70 / 85), up
+//    to a hundred rows 300 and up to forty 500 (23 on 7 of 3904 x 15616 129 / 107), bf16 rows with channel scales 150 and 300 (left out 32, two of 48 of 2048 x 8192 108 / 119); other
+//    layers 35 (64 on 9 of 1024 x 1024, groups of 128, 22.3 / 16.5; left out 161 on 8 of 2048 x 1024 25.1 / 31.2), bf16 rows with group scales up to a hundred 100 (98 on 16 of
+//    2048 x 1024 38.5 / 28.4); and 35 where the gated call has everything in its two launches (left out 86 on 5 of 1024 x 4096 25.1 / 28.5);
+//  - beyond 35 MB, partial sums of at most twice the weights.
+// Or at most two rows on each of experts of up to 5 MB (229 on 128 of 768 x 3072, 8-bit bf16, 97 / 77), and FP16 rows on 4-bit codes with channel scales of wide layers at up to
+// 1.6 rows per expert, a hundred in all, and 1200 MB (22 on 16 of 4096 x 16384, 814 MB, 180 / 155).
 // Slices of 64 channels up to 520 blocks, as far as these were measured.
-// (402 drawn sizes that the rules before left out: this takes 182 of them, a step 1.23 times as fast on average, two of them 3 and 4 % slower.)
-static bool sliced_small(int R, int E, int d, int F, int bits, bool grouped, bool f16, double active, double bytes, bool narrow)
+// (7250 drawn sizes that the lines below leave, one to 256 experts, d_ff of d / 2 to 8 d, every form: this takes 4240 of them, a step 1.42 times as fast on average, 25 more than
+// 3 % slower, the worst 0.90; of their steps with all rows on two experts or on a quarter of them 45 of 3400 more than 5 % slower, the worst 0.70.  Without the bounds on rows, what moves and partial
+// sums 1370 were more than 3 % slower, up to five times.)
+static bool sliced_small(int R, int E, int d, int F, int bits, bool grouped, bool f16, double active, double bytes, double partial, bool narrow, bool fused)
 {
     using namespace moe;
-    if (narrow) return false;
     const double expert = 2.0 * d * F * bits / 8, over = R <= E ? 1.0 : expected_row_tiles(R, E, R > 8L * E && bits == 4 ? 32 : 16) / active;
-    if (f16 && bits == 8 && !grouped) return over <= (bytes > 100e6 ? 1.1 : 1.25) && (bytes <= 100e6 || (R <= E && bytes <= 430e6));
-    if (bytes > 17e6 && over > (bytes > 100e6 ? 1.1 : 1.6)) return false;
-    return bytes <= (expert <= 17e6 ? 600e6 : 500e6) || (f16 && bits == 4 && !grouped && 5L * R <= 8L * E && bytes <= 1200e6);
+    const bool eight = f16 && bits == 8 && !grouped, four = f16 && bits == 4 && !grouped, bf_groups = grouped && !f16, bf_channels = !grouped && !f16, wide = F >= 3 * d;
+    if (narrow || (eight ? over > (bytes > 100e6 ? 1.1 : 1.25) || (bytes > 100e6 && (R > E || bytes > 430e6)) : bytes > 17e6 && over > (bytes > 100e6 ? 1.1 : 1.6))) return false;
+    if (R <= 2L * E && expert <= 5e6 && bytes <= 600e6) return true;
+    if (wide && four && 5L * R <= 8L * E && R <= 100) return bytes <= 1200e6;
+    const double moved = over * bytes + 2 * partial;
+    const double most = fused ? 35e6 : !wide ? (bf_groups && R <= 100 ? 100e6 : 35e6) : R <= 40 ? (bf_channels ? 300e6 : 500e6) : R <= 100 && !bf_channels ? 300e6 : 150e6;
+    const int rows = 200 + (bf_groups ? 56 : 0) + (wide && moved > 10e6 && moved <= 100e6 ? 56 : 0);
+    return R <= rows && moved <= most && (partial <= 2 * bytes || moved <= 35e6);
 }
 
-// Whether a layer should take the sliced call (steps in us of the routes below against it, uniform routing; of 13898 drawn sizes of 4 to 512 assignments
-// it takes 9964, 1.40 times as fast on average; 263 of them, most with up to one row per expert, are 2 to 41 % slower; sliced_small takes in what these lines
-// leave of small and few experts):
+// Whether a layer should take the sliced call: sliced_small, and what these lines take (steps in us of the routes below against it, uniform routing; of 13898 drawn sizes of
+// 4 to 512 assignments the lines by themselves take 9964, 1.40 times as fast on average; 263 of them, most with up to one row per expert, are 2 to 41 % slower):
 //  - up to eight assignments per expert: a block takes sixteen rows, and experts with more stream their weights again (61 tokens, two of
 //    eight experts of 4096 x 16384 8-bit 182 and 320; 5 per expert of 1024 x 4096 8-bit 57 and 61).
 //    Rows on 4-bit codes, whose blocks then take thirty-two: up to sixteen, 150 MB of weights and a d_ff of twice d (192 tokens,
@@ -583,8 +593,7 @@ static bool sliced_small(int R, int E, int d, int F, int bits, bool grouped, boo
 //    bit blocks per compute unit would keep some busy twice as long as others (250 tokens, two of 60 of 1536 x 1280, 300 blocks, 53.6 and 52.4);
 //  - the partial sums of a slice, rows x d x 4 bytes, well below its weights, and no thousands of slices of 64 channels, where d_ff leaves no
 //    wider ones: a block's start then costs more than its few weights (218 tokens on 115 of 256 x 5312, group scales, 8100 blocks, 58 and 97;
-//    139 on 131 of 640 x 4544, 6100, 81 and 113; 178 on 80 of 384 x 3392, 3800, 40 and 45; 43 on 71 of 448 x 6720, 3400, 48 and 40; small layers lose by the
-//    first line what they would gain: 134 on 16 of 512 x 2048 25.7 and 15.7);
+//    139 on 131 of 640 x 4544, 6100, 81 and 113; 178 on 80 of 384 x 3392, 3800, 40 and 45; 43 on 71 of 448 x 6720, 3400, 48 and 40);
 //  - up to 300 MB of weights: beyond, the launch's fixed parts count little and the ring's loads into LDS keep more in flight (30 tokens
 //    on 32 experts of 4096 x 16384 8-bit 398 and 388; 240 on 55 of 4096 x 4096 8-bit, 1.8 GB, 314 and 370);
 //  - FP16 rows on 8-bit codes with channel scales, more rows than experts: not from 140 MB on where the routes below stream and rows are long
@@ -610,7 +619,8 @@ extern "C" int moe_grouped_ffn_wq_sliced_pays(int T, int k, int E, int d, int F,
     const int cw = decode_slice_width(R, E, F);
     const double blocks = active * (F / 64) / cw;
     if (cw == 1 && blocks > 3600) return 0;
-    if (sliced_small(R, E, d, F, bits, grouped, f16, active, bytes, cw == 1 && blocks > 520)) return 1;
+    const bool fused = moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype) && gated_shapes(T, k, E, d, F, bits, group_size, act_dtype) == 2;
+    if (sliced_small(R, E, d, F, bits, grouped, f16, active, bytes, (double)decode_ffn_partial_bytes(R, d, F, cw), cw == 1 && blocks > 520, fused)) return 1;
     if (5 * R > 4 * active * cw * bits) return 0;
     if (R > 8L * E) {
         const bool fits = grouped ? R <= 12L * E && F >= 4 * d && bytes <= 110e6 : R <= 16L * E && F >= 2 * d && bytes <= 150e6;

@@ -338,3 +338,24 @@ def test_bf16_rows_are_converted_by_what_the_launched_tiles_cost():
     calls = L.record([L.indexed(*c, 0, B.MOE_BF16) for c, _ in cases])
     for (sizes, converted), call in zip(cases, calls):
         assert call.rc == 0 and any(p.kernel.startswith("rows_to_f16") for p in call.launches) == converted, (sizes, call.launches)
+
+
+def test_partial_sums_of_few_experts_stay_within_their_weights_reach():
+    """Sizes that a layer leaves to the other routes, timed there against the sliced call; and over the whole range, beyond 35 MB in all, partial sums are at
+    most twice the active weights, or a fifth where the lines for larger layers take them."""
+    import random
+    assert not any(_pays(*c) for c in [(512, 1, 1, 2048, 2048, 4), (509, 1, 1, 3328, 3712, 4), (512, 1, 1, 2048, 8192, 4), (512, 1, 1, 1024, 4096, 4), (256, 2, 2, 1024, 4096, 4),
+                                       (256, 2, 4, 1024, 4096, 4), (256, 1, 1, 512, 2048, 4), (43, 2, 5, 1024, 4096, 4), (161, 1, 8, 2048, 1024, 4), (16, 2, 48, 2048, 8192, 4, 0, B.MOE_BF16)])
+    assert all(_pays(*c) for c in [(64, 1, 9, 1024, 1024, 4, 128), (23, 1, 7, 3904, 15616, 4), (49, 2, 16, 2048, 1024, 4, 64, B.MOE_BF16), (311, 1, 32, 448, 1792, 4, 64, B.MOE_BF16),
+                                   (40, 1, 2, 1024, 4096, 4), (16, 1, 1, 2048, 8192, 8, 0, B.MOE_BF16)])
+    rng, taken = random.Random(1), 0
+    for _ in range(20000):
+        E, k = rng.choice([1, 2, 3, 4, 6, 8, 16, 64]), rng.choice([1, 2])
+        T, d, F, bits = int(2 ** rng.uniform(0, 9 if k == 1 else 8)), 64 * rng.randint(1, 64), 64 * rng.randint(1, 128), rng.choice([4, 8])
+        sizes = (T, k, E, d, F, bits, rng.choice([0, 64]), rng.choice([B.MOE_F16, B.MOE_BF16]))
+        if k > E or not _pays(*sizes):
+            continue
+        taken += 1
+        partial, weights = B.load().moe_grouped_ffn_wq_sliced_workspace_bytes(*sizes), E * (1 - (1 - 1 / E) ** (T * k)) * 2 * d * F * bits / 8
+        assert partial <= 2.01 * weights + 256 or 2 * partial + weights <= 35.1e6, sizes
+    assert taken > 3000
