@@ -12,7 +12,7 @@
 
 #include <type_traits>
 
-#include "moe_common.h"
+#include "moe_ffn_common.h"
 
 namespace moe {
 
@@ -335,9 +335,11 @@ __global__ __launch_bounds__(256 * S) void gate_mfma_kernel(const uint16_t *__re
 
 // Few tokens and 33 to 64 experts: the same chains in v_mfma_f32_4x4x1_16b_f32, sixteen 4 x 4 x 1 products that make up
 // 4 tokens x 64 experts x 1 feature.  A block takes four tokens instead of sixteen, so the batch spreads over four times
-// as many compute units at the same rate of the matrix pipe.  A lane per expert, one 2-byte load per feature (numbers of experts that
-// are no multiple of four; the others take gate_token_kernel).  A ring of R octets.
-template <bool BF16, int R>
+// as many compute units at the same rate of the matrix pipe.  An octet of features is one 16-byte load of the tokens and two
+// 8-byte loads of the gate weight: lane (j, r) = (lane & 15, lane >> 4) brings experts 4 j .. 4 j + 3 of features r and 4 + r, and
+// the same 4 x 4 transposition that spreads the tokens' features above leaves it with expert 4 j + r of all eight.  (VEC; numbers
+// of experts that are no multiple of four: a lane per expert, one 2-byte load per feature.)  A ring of R octets.
+template <bool BF16, int R, bool VEC>
 __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
                                                             const float *__restrict__ bias,
                                                             const uint8_t *__restrict__ finished, int T, int d, int E,
@@ -346,10 +348,12 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
 {
     typedef float f4_t __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     constexpr int NT = 4, ld = 64 + 4;
     __shared__ float part[4 * NT * ld];
     const int lane = threadIdx.x & 63;
     const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int own = VEC ? 4 * (lane & 15) + (lane >> 4) : lane;      // this lane's expert
     const int t0 = blockIdx.x * NT;
     const int nblk = (d + kGateBlk - 1) / kGateBlk;
     const int mine = p < nblk ? (nblk - p + 3) / 4 : 0;
@@ -359,14 +363,19 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
     const int x_off = min(lane & 3, rows - 1) * d * 2;
-    const int w_off = min(lane, E - 1) * 2;             // (experts clamped where they do not exist)
+    const int w_off = VEC ? ((lane >> 4) * E + min(4 * (lane & 15), E - 4)) * 2 : min(own, E - 1) * 2;   // (experts clamped where they do not exist)
 
-    struct Octet { u32x4 x; uint32_t w[8]; } ring[R];
+    struct Octet { u32x4 x; uint32_t w[VEC ? 4 : 8]; } ring[R];
     auto load = [&](Octet &c, int q) __attribute__((always_inline)) {
         const int f = feature(q);
         c.x = __builtin_amdgcn_raw_buffer_load_b128(rx, x_off, f * 2, 0);
+        if constexpr (VEC) {
+            const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rw, w_off, f * E * 2, 0), b = __builtin_amdgcn_raw_buffer_load_b64(rw, w_off, (f + 4) * E * 2, 0);
+            c.w[0] = a.x; c.w[1] = a.y; c.w[2] = b.x; c.w[3] = b.y;
+        } else {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) c.w[u] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off, (f + u) * E * 2, 0);
+            for (int u = 0; u < 8; ++u) c.w[u] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rw, w_off, (f + u) * E * 2, 0);
+        }
     };
     f4_t acc = {0.f, 0.f, 0.f, 0.f};
     struct Ops { float x[8], w[8]; };
@@ -376,8 +385,15 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
             const uint32_t v = u < 2 ? c.x.x : u < 4 ? c.x.y : u < 6 ? c.x.z : c.x.w;
             o.x[u] = act_to_float<BF16>((uint16_t)(v >> (16 * (u & 1))));
         }
+        if constexpr (VEC) {
+            uint32_t q[4];
+            transpose_quads(c.w[0], c.w[1], c.w[2], c.w[3], q);     // dword u: features u and 4 + u of expert `own`
 #pragma unroll
-        for (int u = 0; u < 8; ++u) o.w[u] = act_to_float<BF16>((uint16_t)c.w[u]);
+            for (int u = 0; u < 8; ++u) o.w[u] = act_to_float<BF16>((uint16_t)(q[u & 3] >> (16 * (u >> 2))));
+        } else {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) o.w[u] = act_to_float<BF16>((uint16_t)c.w[u]);
+        }
     };
     auto multiply = [&](const Ops &o) __attribute__((always_inline)) {
 #pragma unroll
@@ -412,7 +428,7 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
         }
     });
 #pragma unroll
-    for (int i = 0; i < NT; ++i) part[(p * NT + i) * ld + lane] = acc[i];
+    for (int i = 0; i < NT; ++i) part[(p * NT + i) * ld + own] = acc[i];
     __syncthreads();
     finish_tokens<1, 4>(part, NT, ld, t0, p, 4, bias, finished, T, E, k, renorm, expert_idx, expert_scale);
 }
@@ -421,7 +437,7 @@ __global__ __launch_bounds__(256) void gate_quad_kernel(const uint16_t *__restri
 // tokens per compute unit the matrix instructions above work on rows and experts of one block alone, sixteen or four tokens by all
 // experts, and a compute unit's matrix pipe is the bound; here a block takes TB tokens, each feature costs a wavefront
 // NE TB fused multiply-adds and one load of a row of the gate weight per VW experts of a lane, and R octets of features are in flight.
-// (Caches warm, 16 / 512 tokens, d = 1024: 128 experts 9.3 / 10.9 us, 127 9.5 / 12.5, 256 12.2 / 14.2, 255 13.5 / 18.1; on the matrix
+// (Caches warm, 16 / 512 tokens, d = 1024: 127 experts 9.5 / 12.5 us, 256 12.2 / 14.2, 255 13.5 / 18.1; on the matrix
 // cores 14.8 to 16 us with 64 to 512 tokens and 65 to 128 experts, 25 with 256, 51 with 255.)
 template <bool BF16, int NE, GateLoads LOADS, int TB, int R>
 __global__ __launch_bounds__(256) void gate_lanes_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg,
@@ -525,6 +541,19 @@ __global__ __launch_bounds__(256) void gate_lanes_kernel(const uint16_t *__restr
     finish_tokens<NE == 2 ? 2 : 1, 4, NE <= 2 ? 16 : 64>(part, NT, ld, t0, p, 4, bias, finished, min(T, t0 + TB), E, k, renorm, expert_idx, expert_scale);
 }
 
+// The last, short block of features of one partial sum, for the chains below: its rows of the gate weight, as they lie, go into LDS while the chain before it runs.  (Fetched
+// at its end, an octet at a time, each octet was a trip to memory: us, then / now, 75 tokens of 112, 32 experts 5.1 / 4.1, 64 of 1000, 16 experts 5.8 / 4.7, 184 of 6248, 8 experts 17.1 /
+// 14.1, 64 bf16 tokens of 1016, 128 experts 12.3 / 10.3.)
+constexpr int gate_tail_bytes(int EP, int d) { return d % kGateBlk ? EP * 256 : 0; }
+
+__device__ __forceinline__ void gate_tail_load(const uint16_t *block, int bytes, unsigned char *lds)
+{
+    for (int i = 0; i < bytes; i += 1024)
+        load_to_lds16(reinterpret_cast<const unsigned char *>(block) + min((int)(threadIdx.x & 63) * 16 + i, bytes - 16), reinterpret_cast<uint16_t *>(lds + i));
+}
+
+__device__ __forceinline__ void gate_tail_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Few tokens, E a multiple of four up to 32: a lane per expert, SUB tokens side by side, TW of them per lane, plain fp32 multiply-adds, the gate weight through
 // LDS as it lies in memory: each wavefront copies its own partial sum's rows 64 features at a time (two chunks in LDS, two more on the way), and the transposing
 // read gives a lane four features of its expert.  What bounds it are instructions, of which a wavefront alone on its SIMD issues one in 4.4 clocks: an octet of features
@@ -554,7 +583,9 @@ __device__ __forceinline__ void gate_rows(const uint16_t *__restrict__ x, const 
     const int nblk = (d + kGateBlk - 1) / kGateBlk;
     const int full = max((d / kGateBlk - p + 3) / 4, 0);                                // whole 128-feature blocks of this partial sum
     const int rest = (nblk - 1) % 4 == p ? (d % kGateBlk) / 8 : 0, nq = full * 16 + rest;      // octets of the last, short one, and in all
-    u32x4 *s_x = reinterpret_cast<u32x4 *>(smem + 8 * CW * 16 + 4 * NTP * ld * 4) + (size_t)p * ((nblk + 3) / 4 * 16 + 2) * NT * XV;    // [octet][token]; two octets are read past the end
+    const int x_words = ((nblk + 3) / 4 * 16 + 2) * NT * XV;                             // (two octets are read past the end)
+    u32x4 *s_x = reinterpret_cast<u32x4 *>(smem + 8 * CW * 16 + 4 * NTP * ld * 4) + (size_t)p * x_words;      // [octet][token]
+    unsigned char *s_tail = smem + 8 * CW * 16 + 4 * NTP * ld * 4 + (size_t)4 * x_words * 16;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
     int w_off[LD];                                      // (within the chunk: fewer experts than EP read its end again)
@@ -586,9 +617,9 @@ __device__ __forceinline__ void gate_rows(const uint16_t *__restrict__ x, const 
 #pragma unroll
             for (int h = 0; h < XV; ++h) t.x[w][h] = s_x[(q * NT + w * SUB + sub) * XV + h];
     };
-    auto w_get = [&](Octet &t, int buf, int o) __attribute__((always_inline)) {
+    auto w_get = [&](Octet &t, const void *rows_of, int o) __attribute__((always_inline)) {
         typedef __attribute__((address_space(3))) s16x4 *lds_t;
-        unsigned char *at = reinterpret_cast<unsigned char *>(s_w + buf * CW) + w_read + o * 8 * row;
+        unsigned char *at = (unsigned char *)rows_of + w_read + o * 8 * row;
 #pragma unroll
         for (int h = 0; h < 2; ++h) t.w[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)(at + h * 4 * row));
     };
@@ -615,6 +646,7 @@ __device__ __forceinline__ void gate_rows(const uint16_t *__restrict__ x, const 
 #pragma unroll
             for (int i = 0; i < LD; ++i) W[h][i] = load(i, base(h));
     __builtin_amdgcn_sched_barrier(0);
+    if (rest) gate_tail_load(wg + (size_t)(p + 4 * full) * kGateBlk * E, rest * 8 * row, s_tail);
 #pragma unroll
     for (int i = 0; i < XP; ++i)
 #pragma unroll
@@ -635,8 +667,8 @@ __device__ __forceinline__ void gate_rows(const uint16_t *__restrict__ x, const 
         for (int i = 0; i < LD; ++i) W[0][i] = load(i, so);
         fence();
         Octet t[4];
-        x_read(t[0], 0); w_get(t[0], 0, 0);
-        x_read(t[1], 1); w_get(t[1], 0, 1);
+        x_read(t[0], 0); w_get(t[0], s_w, 0);
+        x_read(t[1], 1); w_get(t[1], s_w, 1);
         for (int b = 0; b < full; ++b) {
             gate_static_for<0, 16>([&](auto oc) {
                 // octet oo of chunk h of the block; with its first ones go the writes of the next chunk and the loads of the one two further on
@@ -646,7 +678,7 @@ __device__ __forceinline__ void gate_rows(const uint16_t *__restrict__ x, const 
                     constexpr int i = decltype(u)::value;
                     feature(t[o & 3], u);
                     if constexpr (i == 0) x_read(t[(o + 2) & 3], b * 16 + o + 2);
-                    if constexpr (i == 1) w_get(t[(o + 2) & 3], ((o + 2) >> 3) & 1, (o + 2) & 7);      // (from the sixth octet on in the next chunk: all of it is there)
+                    if constexpr (i == 1) w_get(t[(o + 2) & 3], s_w + (((o + 2) >> 3) & 1) * CW, (o + 2) & 7);      // (from the sixth octet on in the next chunk: all of it is there)
                     if constexpr (i == 2 && oo < LD) {
                         s_w[(1 - h) * CW + oo * 64 + lane] = W[1 - h][oo];
                         W[1 - h][oo] = load(oo, so);
@@ -657,15 +689,18 @@ __device__ __forceinline__ void gate_rows(const uint16_t *__restrict__ x, const 
             });
         }
     }
-    for (int o = 0; o < rest; ++o) {
-        fence();
-        const int at = ((p + 4 * full) * kGateBlk + o * 8) * row;
-        s_w[lane] = __builtin_amdgcn_raw_buffer_load_b128(rw, min(lane * 16, 16 * E - 16), at, 0);
+    if (rest) {
+        gate_tail_wait();
         fence();
         Octet t;
-        x_read(t, full * 16 + o);
-        w_get(t, 0, 0);
-        gate_static_for<0, 8>([&](auto u) { feature(t, u); });
+        x_read(t, full * 16); w_get(t, s_tail, 0);
+#pragma unroll 1
+        for (int o = 0; o < rest; ++o) {
+            Octet next;
+            x_read(next, full * 16 + o + 1); w_get(next, s_tail, o + 1);
+            gate_static_for<0, 8>([&](auto u) { feature(t, u); });
+            t = next;
+        }
     }
 #pragma unroll
     for (int w = 0; w < TW; ++w) part[(p * NTP + w * SUB + sub) * ld + e] = acc[w];
@@ -677,9 +712,9 @@ __device__ __forceinline__ void gate_rows(const uint16_t *__restrict__ x, const 
 // from memory straight into registers.  A lane (j, r) brings experts 4 j .. 4 j + 3 of features r and 4 + r in two 8-byte loads, and the 4 x 4
 // transposition that spreads the tokens' features above leaves it with expert 4 j + r of an octet of features.  Its eight instructions for the next octet
 // are dealt out one by one between the multiply-adds, where each stands in for a wait state, and so are the loads and the reads of the tokens (in the order
-// spread, additions, loads 3 % slower).  130 clocks an octet, the swaps issuing at half rate.  R octets in flight: with 4, warm launches are 0.2 us shorter and
+// spread, additions, loads 3 % slower).  130 clocks an octet, the swaps issuing at half rate.  Eight octets in flight: with 4, warm launches are 0.2 us shorter and
 // layers' steps, whose gate weight comes from memory, 0.3 % longer; with 16, 1.8 % longer.
-template <bool BF16, int EP, int TW, int R = 8>
+template <bool BF16, int EP, int TW>
 __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wg, const float *__restrict__ bias,
                                             const uint8_t *__restrict__ finished, int T, int d, int E, int k, int renorm,
                                             int32_t *__restrict__ expert_idx, float *__restrict__ expert_scale)
@@ -687,7 +722,7 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     typedef float f4_t __attribute__((ext_vector_type(4)));
-    constexpr int EW = EP / 64, NT = TW;
+    constexpr int EW = EP / 64, NT = TW, R = 8;
     constexpr int ld = EP + 4, NTP = NT < 4 ? 4 : NT;   // (four tokens finish at a time, those past NT are not stored)
     constexpr int XV = BF16 ? 2 : 1;                    // 16-byte words of an octet of a token
     constexpr int XP = 2;                               // passes of 64 octets of the tokens that are requested ahead of the weights
@@ -700,7 +735,9 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
     const int nblk = (d + kGateBlk - 1) / kGateBlk;
     const int full = max((d / kGateBlk - p + 3) / 4, 0);                                // whole 128-feature blocks of this partial sum
     const int rest = (nblk - 1) % 4 == p ? (d % kGateBlk) / 8 : 0, nq = full * 16 + rest;      // octets of the last, short one, and in all
-    u32x4 *s_x = reinterpret_cast<u32x4 *>(smem + 4 * NTP * ld * 4) + (size_t)p * ((nblk + 3) / 4 * 16 + 2) * NT * XV;    // [octet][token]; two octets are read past the end
+    const int x_words = ((nblk + 3) / 4 * 16 + 2) * NT * XV;                             // (two octets are read past the end)
+    u32x4 *s_x = reinterpret_cast<u32x4 *>(smem + 4 * NTP * ld * 4) + (size_t)p * x_words;      // [octet][token]
+    unsigned char *s_tail = smem + 4 * NTP * ld * 4 + (size_t)4 * x_words * 16;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x + (size_t)t0 * d), 0, rows * d * 2, 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wg), 0, d * E * 2, 0x00020000);
     int w_off[EW][2];                                   // features r, 4 + r
@@ -782,6 +819,7 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
             load(ring[decltype(o)::value], first + decltype(o)::value * step);
             __builtin_amdgcn_sched_barrier(0);
         });
+    if (rest) gate_tail_load(wg + (size_t)(p + 4 * full) * kGateBlk * E, rest * step, s_tail);
 #pragma unroll
     for (int i = 0; i < XP; ++i)
 #pragma unroll
@@ -799,7 +837,7 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
         x_read(tok[0], 0);
         x_read(tok[1], 1);
         gate_static_for<0, 8>([&](auto i) { spread(ring[0], sp[0], i); });
-        int ahead = R == 16 ? first + min(1, full - 1) * turn : first + R * step;       // the octet R past the one at hand
+        int ahead = first + R * step;       // the octet R past the one at hand
         load(ring[0], ahead);
         for (int b = 0; b < full; ++b) {
             gate_static_for<0, 16>([&](auto oc) {
@@ -827,14 +865,30 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
             });
         }
     }
-    for (int o = 0; o < rest; ++o) {
+    if (rest) {
+        auto from_lds = [&](Raw &c, int o) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 0; s < EW; ++s)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const u32x2 v = *reinterpret_cast<const u32x2 *>(s_tail + w_off[s][h] + o * step);
+                    c.w[s][2 * h] = v.x; c.w[s][2 * h + 1] = v.y;
+                }
+        };
+        gate_tail_wait();
         Raw c;
-        Spread v;
-        Tok t;
-        load(c, ((p + 4 * full) * kGateBlk + o * 8) * E * 2);
-        x_read(t, full * 16 + o);
-        gate_static_for<0, 8>([&](auto i) { spread(c, v, i); });
-        gate_static_for<0, 8>([&](auto u) { feature(t, v, u); });
+        from_lds(c, 0);
+#pragma unroll 1
+        for (int o = 0; o < rest; ++o) {
+            Raw next;
+            Spread v;
+            Tok t;
+            x_read(t, full * 16 + o);
+            from_lds(next, o + 1);
+            gate_static_for<0, 8>([&](auto i) { spread(c, v, i); });
+            gate_static_for<0, 8>([&](auto u) { feature(t, v, u); });
+            c = next;
+        }
     }
 #pragma unroll
     for (int w = 0; w < TW; ++w)
@@ -872,17 +926,14 @@ static void launch_gate_mfma(const uint16_t *x, const uint16_t *wg, const float 
                        finished, T, d, E, k, renorm, expert_idx, expert_scale);
 }
 
-// False where a block's tokens have too many features for the LDS (fewer tokens per lane are tried first).
+// False where a block's tokens have too many features for the LDS.
 template <bool BF16, int EP, int TW>
 static bool launch_gate_chains(const uint16_t *x, const uint16_t *wg, const float *bias, const uint8_t *finished, int T, int d, int E,
                               int k, int renorm, int32_t *expert_idx, float *expert_scale, hipStream_t s)
 {
     constexpr int NT = TW * (EP < 64 ? 64 / EP : 1), NTP = NT < 4 ? 4 : NT;
-    const size_t smem = (EP <= 32 ? EP * 1024 : 0) + (size_t)4 * NTP * (EP + 4) * sizeof(float) + (size_t)4 * ((d + 511) / 512 * 16 + 2) * NT * (BF16 ? 32 : 16);
-    if (smem > 152 * 1024) {
-        if constexpr (TW > 1) return launch_gate_chains<BF16, EP, TW / 2>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale, s);
-        return false;
-    }
+    const size_t smem = (EP <= 32 ? EP * 1024 : 0) + (size_t)4 * NTP * (EP + 4) * sizeof(float) + (size_t)4 * ((d + 511) / 512 * 16 + 2) * NT * (BF16 ? 32 : 16) + gate_tail_bytes(EP, d);
+    if (smem > 152 * 1024) return false;
     auto launch = [&](auto kernel) {
         static std::atomic<uint64_t> raised;
         raise_lds_limit(reinterpret_cast<const void *>(kernel), 152 * 1024, raised);
@@ -905,31 +956,39 @@ static void launch_gate(const uint16_t *x, const uint16_t *wg, const float *bias
     // blocks 6.5 / 9.0 / 14.5 / 24.7 -> 5.0 / 6.7 / 9.9 / 17.5; 128 experts, 64 tokens, gate_lanes_kernel 5.9 / 8.4 / 13.2 / 22.1 -> 5.8 / 7.4 / 10.9 / 17.9, 1024 tokens 8.5 / 13.1 / 22.9 / 41.4 ->
     // 7.4 / 10.5 / 17.2 / 30.3.  bf16, 64 tokens: 16 experts 4.5 / 5.6 / 7.6 / 11.6 -> 4.0 / 5.0 / 7.0 / 11.1, 32 4.2 / 5.6 / 8.4 / 14.4 -> 4.2 / 5.2 / 7.0 / 11.0, 64 4.8 / 6.9 / 10.6 / 18.0 -> 4.2 /
     // 5.5 / 7.6 / 12.2.  Not: 513 to 1024 bf16 tokens on 17 to 32 experts, 6.0 / 6.3 at d = 1024; 2048 tokens on 64 experts, d = 4096, 25 / 28.)
+    // Features past the last whole block of 128 run after the chain, slower than within it.  Left to the forms below, these / chains: 65 to 127 such features of fewer than 256 with more
+    // than 64 experts (133 tokens of 112, 128 experts, 4.9 / 5.9); more than eight of them with more than 512 bf16 tokens on 33 to 64 experts (683 of 1016, 60 experts, 7.9 / 9.0, 993 of 656, 40
+    // experts, 7.7 / 8.3).  Long bf16 tokens on up to 16 experts (878 of 6144, 15.8 / 17.5, 443 of 5120 13.6 / 14.3, 770 of 4096 11.7 / 12.3).  Tokens whose fp32 copies
+    // the LDS does not hold: more than 512 bf16 tokens on 33 to 64 experts three to a lane while these are a block per compute unit (600 of
+    // 10240, 64 experts, two to a lane 70, three 42, four-token blocks 56; 998 of 11416, 36 experts, two to a lane 80, four-token blocks 53).
     if (E % 4 == 0 && E <= 128 && T <= 1024) {
 #define MOE_GATE_CHAINS(EP, TW) launch_gate_chains<BF16, EP, TW>(x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale, s)
+        const int past = d % kGateBlk;
         bool done = false;
-        if (E > 64) done = T <= 256 ? MOE_GATE_CHAINS(128, 1) : T <= 512 ? MOE_GATE_CHAINS(128, 2) : MOE_GATE_CHAINS(128, 4);
-        else if (E > 32) done = T <= 256 ? MOE_GATE_CHAINS(64, 1) : T <= 512 ? MOE_GATE_CHAINS(64, 2) : MOE_GATE_CHAINS(64, 4);
-        else if (E <= 16) done = MOE_GATE_CHAINS(16, 1);
+        if (E > 64) done = !(past > 64 && d < 256) && (T <= 256 ? MOE_GATE_CHAINS(128, 1) : T <= 512 ? MOE_GATE_CHAINS(128, 2) : MOE_GATE_CHAINS(128, 4));
+        else if (E > 32 && T <= 512) done = T <= 256 ? MOE_GATE_CHAINS(64, 1) : MOE_GATE_CHAINS(64, 2);
+        else if (E > 32) done = !(BF16 && past > 8) && (MOE_GATE_CHAINS(64, 4) || (T <= 768 && MOE_GATE_CHAINS(64, 3)));
+        else if (E <= 16) done = (!BF16 || d <= (T <= 512 ? 4352 : 3072)) && MOE_GATE_CHAINS(16, 1);
         else if (T <= 512) done = MOE_GATE_CHAINS(32, 1);
         else if constexpr (!BF16) done = MOE_GATE_CHAINS(32, 2);
 #undef MOE_GATE_CHAINS
         if (done) return;
     }
-    // 33 to 64 experts, no multiple of four, and up to four tokens per compute unit: four-token blocks on the matrix
+    // 33 to 64 experts else and up to four tokens per compute unit: four-token blocks on the matrix
     // cores; FP16 tokens, more than one such block and up to a token per compute unit: a lane per expert.  (Lane per expert / four-token /
     // sixteen-token blocks, warm, 36 to 60 experts, d = 1024: T = 64 8.4 / 9.2 / 9.9 us, 300 11.9 / 9.2 / 10.2, 1000 20.5 / 9.3 / 10.1,
     // 2000 37 / 15.9 / 10.1; d = 4096, T = 64 21.0 / 24.9 / 25.3; bf16 27.6 / 24.9 / 25.3.  Odd numbers of experts: one token 7.4 / 8.3 / 11.3,
     // 2000 37 / 15.8 / 12.2.)
-    if (E > 32 && E <= 64 && E % 4 && T <= 1024) {
+    if (E > 32 && E <= 64 && T <= 1024) {
         if (!BF16 && T > 4 && T <= 256)
             hipLaunchKernelGGL((gate_lanes_kernel<BF16, 1, WIDE, 1, 2>), dim3(T), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
-        else hipLaunchKernelGGL((gate_quad_kernel<BF16, 8>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        else if (E % 4) hipLaunchKernelGGL((gate_quad_kernel<BF16, 8, false>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
+        else hipLaunchKernelGGL((gate_quad_kernel<BF16, 8, true>), dim3((T + 3) / 4), dim3(256), 0, s, x, wg, bias, finished, T, d, E, k, renorm, expert_idx, expert_scale);
         return;
     }
     // More than 64 experts else: a block per token up to one per compute unit, then two, then four, as far as that is faster than the
-    // matrix cores (d = 1024, T = 1024, FP16, lanes / matrix cores: 127 experts 15.4 / 21.9 us, 128 13.9 / 14.9, 256 22.7 / 24.9; bf16 128
-    // experts 17.0 / 15.0; d = 4096 128 experts 48 / 42; T = 1500: 128 19.5 / 15.1, 255 33.2 / 51, 250 30 / 41, 256 32.5 / 25).
+    // matrix cores (d = 1024, T = 1024, FP16, lanes / matrix cores: 127 experts 15.4 / 21.9 us, 256 22.7 / 24.9; T = 1500: 255 33.2 / 51, 250 30 / 41, 256 32.5 / 25;
+    // multiples of four up to 128 experts, as far as they come here, bf16, T = 1024, 17.0 / 15.0, d = 4096 48 / 42).
     const int few = E > 128 ? (E % 8 ? 2048 : 1024) : E % 2 ? (d <= 1024 ? 2048 : 1024) : !BF16 && d <= 2048 ? 1024 : 512;
     if (E > 64 && T <= few) {
 #define MOE_GATE_LANES(NE, LOADS, TB, R) \

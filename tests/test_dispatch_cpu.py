@@ -359,3 +359,15 @@ def test_partial_sums_of_few_experts_stay_within_their_weights_reach():
         partial, weights = B.load().moe_grouped_ffn_wq_sliced_workspace_bytes(*sizes), E * (1 - (1 - 1 / E) ** (T * k)) * 2 * d * F * bits / 8
         assert partial <= 2.01 * weights + 256 or 2 * partial + weights <= 35.1e6, sizes
     assert taken > 3000
+
+
+def test_the_gates_chains_leave_what_other_forms_do_faster():
+    """Many features past the last whole block of 128, long bf16 tokens on few experts, and tokens that the LDS does not hold."""
+    bf = B.MOE_BF16
+    cases = [((133, 112, 128), "gate_lanes_kernel<"), ((133, 248, 128), "gate_lanes_kernel<"), ((133, 192, 128), "gate_lanes_kernel_wide<"), ((133, 376, 128), "gate_lanes_kernel_wide<"),
+             ((683, 1016, 60, bf), "gate_quad_kernel<"), ((683, 1032, 60, bf), "gate_token_kernel<"), ((683, 1016, 60), "gate_token_kernel<"), ((512, 1016, 60, bf), "gate_token_kernel<"),
+             ((443, 5120, 8, bf), "gate_mfma_kernel<"), ((770, 4096, 12, bf), "gate_mfma_kernel<"), ((443, 4096, 8, bf), "gate_token_kernel<"), ((443, 8192, 8), "gate_token_kernel<"),
+             ((768, 10240, 64, bf), "gate_token_kernel<true, 64, 3>"), ((769, 10240, 64, bf), "gate_quad_kernel<"), ((1024, 8192, 64, bf), "gate_token_kernel<true, 64, 4>"),
+             ((592, 10240, 100, bf), "gate_mfma_kernel<")]
+    for (sizes, want), call in zip(cases, L.record([L.gate(*c) for c, _ in cases])):
+        assert call.rc == 0 and call.launches[0].kernel.startswith(want), (sizes, call.launches)
