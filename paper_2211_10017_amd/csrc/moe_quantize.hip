@@ -91,6 +91,9 @@ __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const f
         for (int q = 1; q < WU; ++q) amax = fmaxf(amax, s_amax[sub][q][nl]);
     }
     if (!live) return;                                  // (no barrier follows)
+    // Every load so far has been used, which the compiler loses sight of behind the branches above: a conversion would wait for them again, and with them for the stores
+    // of the one before (32 experts of 1024 x 4096: 4-bit 119.3 -> 116.5 us, with canonical codes 163.8 -> 157.2, 8-bit 133.6 -> 125.9).
+    __builtin_amdgcn_s_waitcnt(0x0f70);                 // (vmcnt 0)
     const __half sh = __float2half_rn(amax / (float)QMAX);   // IEEE divide, round to nearest even
     const float s = __half2float(sh);
     if (wu == 0 && lane < CH) scales[((size_t)e * G + gi) * N + n] = sh;
@@ -158,18 +161,24 @@ __global__ __launch_bounds__(WU == 16 ? 1024 : 512) void quantize_kernel(const f
                     }
                 }
             __builtin_amdgcn_wave_barrier();
-            auto leave = [&](auto vec, int at) __attribute__((always_inline)) {      // the tile's bytes from `at` on, a piece of one row
-                const int row = at / ROW;
-                if (PARTS > 1 && r * PARTS * FK + row >= g) return;                  // (the rows of a last block that is there again)
-                *reinterpret_cast<decltype(vec) *>(reinterpret_cast<uint8_t *>(q_canon) +
-                                                   (((size_t)e * K + (size_t)gi * g + (size_t)r * PARTS * FK + row) * N + nb * 32 + part * CH) * BITS / 8 + at % ROW) =
-                    *reinterpret_cast<const decltype(vec) *>(tile + at);
-            };
-            if constexpr (ROW >= 16) leave(uint4{}, lane * 16);
-            else if constexpr (ROW == 8) leave(uint2{}, lane * 8), leave(uint2{}, 512 + lane * 8);
-            else
+            if constexpr (ROW >= 16 && PARTS == 1) {
+                constexpr int VPR = ROW / 16;           // 16-byte vectors per row
+                const uint4 v = *reinterpret_cast<const uint4 *>(tile + lane * 16);
+                *reinterpret_cast<uint4 *>(reinterpret_cast<uint8_t *>(q_canon) + (((size_t)e * K + (size_t)kb * FK + lane / VPR) * N + nb * 32) * BITS / 8 + (lane % VPR) * 16) = v;
+            } else {
+                auto leave = [&](auto vec, int at) __attribute__((always_inline)) {      // the tile's bytes from `at` on, a piece of one row
+                    const int row = at / ROW;
+                    if (r * PARTS * FK + row >= g) return;                               // (the rows of a last block that is there again)
+                    *reinterpret_cast<decltype(vec) *>(reinterpret_cast<uint8_t *>(q_canon) +
+                                                       (((size_t)e * K + (size_t)gi * g + (size_t)r * PARTS * FK + row) * N + nb * 32 + part * CH) * BITS / 8 + at % ROW) =
+                        *reinterpret_cast<const decltype(vec) *>(tile + at);
+                };
+                if constexpr (ROW >= 16) leave(uint4{}, lane * 16);
+                else if constexpr (ROW == 8) leave(uint2{}, lane * 8), leave(uint2{}, 512 + lane * 8);
+                else
 #pragma unroll
-                for (int i = 0; i < 4; ++i) leave(uint32_t{}, 256 * i + lane * 4);
+                    for (int i = 0; i < 4; ++i) leave(uint32_t{}, 256 * i + lane * 4);
+            }
             __builtin_amdgcn_wave_barrier();
         }
     };
