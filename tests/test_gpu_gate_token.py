@@ -1,5 +1,5 @@
-"""The gate's form for few tokens by 17 to 64 experts (a lane per expert, the weight in LDS 512 features at a time): short and odd
-feature counts, partly filled eights of experts' lanes, odd numbers of tokens, the largest batches it takes.  The chosen experts are the
+"""The gate's chains for few tokens by 24 to 64 experts, a multiple of eight (a lane per expert, the weight through LDS up to 32, straight into registers
+beyond): short and odd feature counts, partly filled lanes, odd numbers of tokens, the largest batches of one token per lane.  The chosen experts are the
 oracle's; the logits are, bit for bit, those of the matrix-core form, whose order of additions is the contract's."""
 import numpy as np
 import pytest
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T,d,E", [(1, 8, 24), (2, 136, 32), (3, 520, 32), (511, 512, 24), (512, 1032, 32), (5, 4096, 32), (1, 504, 40), (7, 1160, 48), (256, 640, 56),
                                    (255, 2048, 64), (4, 1544, 64)])
 @pytest.mark.parametrize("act", ["f16", "bf16"])
-def test_gate_with_the_weight_in_lds_bit_exact(T, d, E, act):
+def test_gate_token_kernel_bit_exact(T, d, E, act):
     print(f"gate T={T} d={d} E={E} {act}", flush=True)
     (call,) = L.record([L.gate(T, d, E, B._DT[TORCH_DT[act]])])
     assert call.launches[0].kernel.startswith("gate_token_kernel")
