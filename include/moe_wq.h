@@ -242,7 +242,9 @@ int moe_grouped_ffn_wq_indexed(const void *x, int act_dtype, const int32_t *perm
  *   0 or E); expert_scale [T] fp32 (k = 1 only) or NULL, and out, as for moe_grouped_ffn_wq_indexed: [T,d] when expert_scale
  *   is given, where the rows of pruned tokens are not written, else y_perm [T*k,d]; perm_src, inv_perm,
  *   expert_offsets as moe_permute writes them; workspace as for moe_grouped_ffn_wq with R = T*k.
- * (Sizes that moe_grouped_ffn_wq_gated takes at level 1 and that it pays for run fc1 in its streaming kernel, the others both GEMMs in row tiles.)
+ * (Sizes that moe_grouped_ffn_wq_gated takes at level 1 and that it pays for, and whose fc2 runs in row tiles in moe_grouped_ffn_wq as well, run fc1 in its streaming
+ * kernel, all others both GEMMs in row tiles.)  With expert_scale y is scaled in fp32; without it y_perm is rounded to out_dtype first and moe_combine scales what is
+ * left: a layer of one expert per token whose y_perm is fp16 gives an active token the rounded form when any token is pruned (`finished`), 2e-4 apart, the other one otherwise.
  * moe_grouped_ffn_wq_unsorted_supported returns 1 when a call with these sizes is taken; it otherwise returns MOE_ERR_UNSUPPORTED.
  * moe_grouped_ffn_wq_unsorted_pays: 1 when it is also the faster way than the two calls (MoEExpertLayer asks this).
  */

@@ -128,7 +128,9 @@ class MoEExpertLayer:
         (input tensor, weight buffers, stream) and then replayed: in a decode-sized layer the
         kernels are shorter than the time Python needs to rebuild them.
         finished: uint8 [T] on the device, nonzero for rows pruned from the batch (their output
-        rows are zero and their experts' weights are not read on their account)."""
+        rows are zero and their experts' weights are not read on their account).  With one expert per
+        token and FP16 rows the others' results may differ in their last FP16 bits from a call
+        without it: there fc2 stores the scaled output itself, here y is stored in FP16 first."""
         for fn, args, name in self._plan(x, finished):
             rc = fn(*args)
             if rc != 0:

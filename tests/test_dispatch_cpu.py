@@ -304,6 +304,11 @@ def test_the_unsorted_call_streams_fc1_where_the_gated_call_does():
         assert a.rc == b.rc == 0 and a.launches == b.launches and _kernels(a)[0] == "stream_unrolled_kernel", (s, a.launches)
         assert bool(lib.moe_grouped_ffn_wq_unsorted_pays(*s, 0, B.MOE_F16)) == (s[1] == 1)
     assert not lib.moe_grouped_ffn_wq_unsorted_pays(256, 1, 8, 512, 2048, 8, 0, B.MOE_F16)      # level 2: everything fused in the gated call
+    # level 1 that pays, but permuted rows would stream through fc2: both GEMMs in row tiles, and no layer takes it
+    sizes = [(1, 1, 4, 1024, 4096, 8), (1, 1, 4, 1024, 3072, 8), (1, 1, 4, 2048, 8192, 4)]
+    for s, call in zip(sizes, L.record([L.unsorted(*s) for s in sizes])):
+        assert lib.moe_grouped_ffn_wq_gated_supported(*s, 0, B.MOE_F16) == 1 and lib.moe_grouped_ffn_wq_gated_pays(*s, 0, B.MOE_F16)
+        assert call.rc == 0 and all(k.startswith("grouped_gemm") for k in _kernels(call)) and not lib.moe_grouped_ffn_wq_unsorted_pays(*s, 0, B.MOE_F16), (s, call.launches)
 
 
 def test_layers_of_eight_experts_and_more_leave_the_ring_by_their_expected_tiles():
