@@ -501,7 +501,7 @@ extern "C" int moe_grouped_ffn_wq_unsorted_pays(int T, int k, int E, int d, int 
     using namespace moe;
     if (!moe_grouped_ffn_wq_unsorted_supported(T, k, E, d, F, bits, group_size, act_dtype)) return 0;
     // one expert per token, fc1 streaming: fc2 stores the output, where the gated call leaves it to moe_combine (40 tokens, one of 32 experts of 1024 x 4096, 8-bit,
-    // 46.0 / 43.8 us a step; 200, one of 8, 39.7 / 37.9)
+    // 45.0 / 43.1 us a step; 200, one of 8, 41.3 / 39.4)
     if (moe_grouped_ffn_wq_gated_pays(T, k, E, d, F, bits, group_size, act_dtype)) return k == 1 && unsorted_streams(T, k, E, d, F, bits, group_size, act_dtype);
     GemmArgs g{};
     g.R = T * k, g.E = E, g.K = d, g.N = F, g.indexed = 1;

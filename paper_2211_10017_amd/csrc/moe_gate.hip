@@ -721,7 +721,6 @@ __device__ __forceinline__ void gate_chains(const uint16_t *__restrict__ x, cons
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    typedef float f4_t __attribute__((ext_vector_type(4)));
     constexpr int EW = EP / 64, NT = TW, R = 8;
     constexpr int ld = EP + 4, NTP = NT < 4 ? 4 : NT;   // (four tokens finish at a time, those past NT are not stored)
     constexpr int XV = BF16 ? 2 : 1;                    // 16-byte words of an octet of a token
